@@ -370,3 +370,106 @@ def tolerance(case):
     if case["dtype"] == "fp32":
         return {"rel": 1.5e-6, "max": 6e-6}
     return {"rel": 1e-2, "max": 6e-2, "differ": 0.0}
+
+
+# ---------------------------------------------------------------------------------------------------------------
+# the same results in 64 bits, by plain torch
+# ---------------------------------------------------------------------------------------------------------------
+
+def _z_scores(x):
+    """x [F, P]: every frame's tokens centred and divided by their population deviation (0 where that is 0)."""
+    c = x - x.mean(1, keepdim=True)
+    sigma = c.square().mean(1, keepdim=True).sqrt()
+    return torch.where(sigma > 0, c / torch.where(sigma > 0, sigma, torch.ones_like(sigma)), torch.zeros_like(c))
+
+
+def _exact_scores(case, s):
+    H, Hkv, d, n_vis, _ = _shape(case)
+    B, F, gh, gw, P0, G = case["batch"], case["frames"], case["grid_h"], case["grid_w"], case["prefix"], H // Hkv
+    out = torch.empty((B, n_vis), dtype=torch.float64, device="cuda")
+    for b in range(B):
+        attn = torch.zeros(n_vis, dtype=torch.float64, device="cuda")
+        for q, k in zip(s["q_txt"], s["k"]):
+            for hk in range(Hkv):
+                keys = k[b, hk, P0:P0 + n_vis].double().t().contiguous()
+                for hq in range(hk * G, hk * G + G):
+                    attn += torch.softmax(q[b, :, hq].double() @ keys / math.sqrt(d), -1).sum(0)
+        emb = s["emb"][b].double() if s["emb"] is not None else \
+            s["k"][0][b, :, P0:P0 + n_vis].double().transpose(0, 1).reshape(n_vis, Hkv * d)
+        norm = emb.norm(dim=1, keepdim=True)
+        unit = (emb / torch.where(norm > 0, norm, torch.ones_like(norm))).view(F, gh, gw, -1)
+        near, count = torch.zeros((F, gh, gw), dtype=torch.float64, device="cuda"), torch.zeros(F, device="cuda")
+        if F > 1:
+            cos = (unit[1:] * unit[:-1]).sum(-1)
+            near[1:] += cos
+            near[:-1] += cos
+            count[1:] += 1
+            count[:-1] += 1
+        temp = 1.0 - near / count.clamp(min=1).view(F, 1, 1)
+        spa = torch.empty((F, gh, gw), dtype=torch.float64, device="cuda")
+        for y in range(0, gh, CROP):
+            for x in range(0, gw, CROP):
+                crop = unit[:, y:y + CROP, x:x + CROP]
+                rows = crop.reshape(F, -1, crop.shape[-1])
+                cos = torch.bmm(rows, rows.transpose(1, 2).contiguous())
+                spa[:, y:y + CROP, x:x + CROP] = cos.var(-1, unbiased=False).view(crop.shape[:3])
+        out[b] = sum(_z_scores(t.reshape(F, gh * gw)) for t in (attn / (H * case["suffix"]), temp, spa)).view(-1)
+    return out
+
+
+def _exact_attention(q, k, v, n_ctx):
+    """q [B, q_len, H, d] over k, v [B, Hkv, n_ctx + q_len, d]; row i sees the first n_ctx + 1 + i rows."""
+    B, q_len, H, d = q.shape
+    Hkv, n = k.shape[1], k.shape[2]
+    hidden = torch.arange(n, device="cuda") > n_ctx + torch.arange(q_len, device="cuda").view(1, q_len, 1)
+    out = torch.empty(q.shape, dtype=torch.float64, device="cuda")
+    for b in range(B):
+        for hk in range(Hkv):
+            heads = slice(hk * (H // Hkv), (hk + 1) * (H // Hkv))
+            rows = q[b, :, heads].double().transpose(0, 1)
+            z = (rows.reshape(-1, d) @ k[b, hk].double().t().contiguous()).view(-1, q_len, n) / math.sqrt(d)
+            p = torch.softmax(z.masked_fill(hidden, -math.inf), -1)
+            out[b, :, heads] = (p.view(-1, n) @ v[b, hk].double()).view(-1, q_len, d).transpose(0, 1)
+    return out
+
+
+def _e4m3(x):
+    """A cache [B, Hkv, N, d] -> (its values once coded in 8 bits, in 64 bits, and the heads' multipliers)."""
+    mult = (x.abs().amax((2, 3)).float() / 448).view(*x.shape[:2], 1, 1)
+    mult = torch.where(mult > 0, mult, torch.ones_like(mult))
+    codes = (x.float() / mult).to(torch.float8_e4m3fn)
+    return codes.double() * mult.double(), mult.view(x.shape[:2]).double()
+
+
+def _from_pages(pool, table, n):
+    B, d = table.shape[0], pool.shape[-1]
+    rows = pool[table.view(-1).long()].view(B, -1, pool.shape[2], d)
+    return rows[:, :n].transpose(1, 2)
+
+
+def exact(case, seed):
+    s = prepare(dict(case, graph=False), seed)
+    if case["op"] == "select":
+        return None
+    if case["op"] == "verdict":
+        alpha = None
+        if case["temperature"] > 0.0:
+            at = s["tokens"].long().unsqueeze(-1)
+            log_p, log_q = (torch.log_softmax(x.double() / case["temperature"], -1).gather(2, at).squeeze(-1)
+                            for x in (s["p"][:, :case["gamma"]], s["q"]))
+            alpha = torch.exp(log_p - log_q).clamp(max=1.0)
+        return None, None, alpha
+    if case["op"] == "score":
+        return _exact_scores(case, s)
+    if case["op"] == "fp8":
+        (k, ks), (v, vs) = _e4m3(s["k"]), _e4m3(s["v"])
+        return [None, None, ks, vs, _exact_attention(s["q"], k, v, k.shape[2] - s["q"].shape[1])]
+    out = []
+    for t in s["layers"]:
+        k, v = t["k"], t["v"]
+        if case["cache"] == "paged":
+            k, v = (_from_pages(x, t["table"], s["n_ctx"] + t["q"].shape[1]) for x in (k, v))
+        out.append(_exact_attention(t["q"], k, v, s["n_ctx"]))
+        if "qd" in t:
+            out.append(_exact_attention(t["qd"], t["kd"], t["vd"], s["n_dctx"]))
+    return out
