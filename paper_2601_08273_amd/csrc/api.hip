@@ -58,7 +58,13 @@ int plan_attention(int call, const hippo_kv_desc* kv, int q_len, int n_total, in
   pl->mfma = kv->dtype != HIPPO_DTYPE_F32;   // bf16 and 8-bit caches
   int tile, min_tiles_per_block;
   if (pl->mfma) {
-    pl->row_chunk = pl->R >= 64 ? 64 : (pl->R + 15) / 16 * 16;
+    // 65 to 128 rows go in one chunk, of 96 or 128 rows: two chunks stream the whole cache twice and give every
+    // slice half the compute units (33K x 4 heads, 91 rows: 24.5 us a call in one chunk, 28.0 in two).  Where even
+    // one-tile slices leave compute units idle the two chunks have units of their own (1K x 4 heads, 77 rows: 10.3
+    // in one, 10.1 in two); beyond 128 rows a block has no waves left for a single chunk.
+    const long long all_tiles = (long long)((n_total + 31) / 32) * kv->batch * kv->n_kv_heads;
+    pl->row_chunk = pl->R <= 64 ? (pl->R + 15) / 16 * 16
+                    : pl->R > 128 || all_tiles <= kNumCU ? 64 : pl->R <= 96 ? 96 : 128;
     tile = 32;
     min_tiles_per_block = 1;     // short caches are bound by latency, not bytes: thin slices on many compute
                                  // units win (1896 rows, 7 query rows: 59 slices of 32 rows beat 14 of 128 by 9 %)
@@ -79,6 +85,10 @@ int plan_attention(int call, const hippo_kv_desc* kv, int q_len, int n_total, in
     if (S < 1) S = 1;
     const int cap = n_tiles / min_tiles_per_block;
     if (S > cap) S = cap;
+    // wide row blocks: what a slice hands to the merge grows with its rows, so more slices than the merge takes
+    // in one step (64) have to stream at least eight tiles each (8 calls over 4K x 2 heads, 91 rows: 75 us with
+    // 64 slices, 82 with 128; over 70K, 4 calls: 91 and 69)
+    if (pl->mfma && pl->R > 64 && pl->R <= 128 && S > 64 && n_tiles < 8 * S) S = n_tiles / 8 > 64 ? n_tiles / 8 : 64;
   }
   if (S > n_tiles) S = n_tiles;
   if (S < 1) S = 1;
@@ -456,6 +466,16 @@ int hippo_verify_attention_static(const void* q, int32_t q_len, const void* k_ca
   AttnPlan pl;
   if ((rc = plan_attention(HIPPO_CALL_VERIFY_ATTENTION, kv, q_len, ctx_len + q_len, num_splits, &pl)) != HIPPO_OK)
     return rc;
+  if (pl.bytes > kStaticScratchBytes && num_splits == 0 && pl.R > 64 && pl.R <= 128) {
+    // slices for every compute unit do not fit the array at this many rows: half as many do wherever the
+    // array is meant to serve the shape (256 slots of 128 rows x 128 channels alone are its 8 MB)
+    num_splits = kNumCU / (2 * kv->batch * kv->n_kv_heads);
+    const int n_tiles = (ctx_len + q_len + 31) / 32;
+    if (num_splits > n_tiles) num_splits = n_tiles;
+    if (num_splits < 1) num_splits = 1;
+    if ((rc = plan_attention(HIPPO_CALL_VERIFY_ATTENTION, kv, q_len, ctx_len + q_len, num_splits, &pl)) != HIPPO_OK)
+      return rc;
+  }
   if (pl.bytes > kStaticScratchBytes) return HIPPO_ERR_STATIC_SCRATCH_LIMIT;
   void* ws = static_scratch(&rc);
   if (ws == nullptr) return rc;

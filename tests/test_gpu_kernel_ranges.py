@@ -1,0 +1,66 @@
+"""GPU parity at the sizes where a kernel's tiles, remainders or dispatch rules change, against the CPU oracle."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from parity_util import assert_close, dev, host, prep
+
+pytestmark = pytest.mark.gpu
+
+
+def attention_inputs(seed, B, q_len, H, Hkv, d, ctx, dtype):
+    r = np.random.default_rng(seed)
+    q = prep(r.standard_normal((B, q_len, H, d)) * 2.5, dtype)
+    k, v = (prep(r.standard_normal((B, Hkv, ctx + q_len, d)), dtype) for _ in range(2))
+    return q, k, v
+
+
+def pages(tensors, seed, size=16):
+    """caches [B, Hkv, N, d] -> their page pools [B * n, size, Hkv, d] and the page table [B, n] they share"""
+    B, Hkv, N, d = tensors[0].shape
+    n = (N + size - 1) // size
+    table = torch.from_numpy(np.random.default_rng(seed).permutation(B * n).astype(np.int32)).cuda().view(B, n)
+    pools = []
+    for x in tensors:
+        rows = torch.zeros((B, n * size, Hkv, d), dtype=x.dtype, device="cuda")
+        rows[:, :N] = x.transpose(1, 2)
+        pool = torch.empty((B * n, size, Hkv, d), dtype=x.dtype, device="cuda")
+        pool[table.view(-1).long()] = rows.view(B * n, size, Hkv, d)
+        pools.append(pool)
+    return pools, table
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("shape", [
+    # q_len, G, ctx, slices, with two sequences of two KV heads: 65 rows (one past the 64-row block), 96 | 97 (the
+    # two wide blocks), 128 | 130 (one chunk | several); the last cache with fewer 32-token tiles than compute units
+    # and the first with more; slices of a tile, of some, and of 24 and more
+    (13, 5, 2100, 0), (12, 8, 2300, 3), (97, 1, 2048, 2), (16, 8, 2400, 2), (13, 10, 2100, 0), (8, 10, 2039, 0),
+    (8, 10, 2041, 0),
+])
+def test_more_than_64_rows_in_one_block(hippo, shape, d):
+    q_len, G, ctx, S = shape
+    q, k, v = attention_inputs(q_len + d, 2, q_len, 2 * G, 2, d, ctx, "bf16")
+    ref, _ = oracle.attention(q, k, v, ctx, None)
+    qd, kd, vd = dev(q, "bf16"), dev(k, "bf16"), dev(v, "bf16")
+    what = "%s d=%d" % (shape, d)
+    assert_close(host(hippo.hippo_verify_attention(qd, kd, vd, ctx, num_splits=S)), ref, "bf16", what)
+    k2, v2 = kd.clone(), vd.clone()
+    k2[:, :, ctx:] = 7.0
+    v2[:, :, ctx:] = 7.0
+    new = [x[:, :, ctx:].transpose(1, 2).contiguous() for x in (kd, vd)]
+    out = hippo.hippo_verify_attention(qd, k2, v2, ctx, num_splits=S, k_new=new[0], v_new=new[1])
+    assert_close(host(out), ref, "bf16", what + " appended")
+    assert torch.equal(k2, kd) and torch.equal(v2, vd), what
+    pools, table = pages([kd, vd], 3)
+    out = hippo.hippo_verify_attention_paged(qd, *pools, table, ctx, num_splits=S)
+    assert_close(host(out), ref, "bf16", what + " paged")
+
+
+def test_static_scratch_serves_128_rows_of_128_channels(hippo):
+    # a slice per compute unit would need more than the static array: the call takes half as many
+    q, k, v = attention_inputs(5, 1, 16, 8, 1, 128, 9000, "bf16")
+    ref, _ = oracle.attention(q, k, v, 9000, None)
+    out = hippo.hippo_verify_attention_static(dev(q, "bf16"), dev(k, "bf16"), dev(v, "bf16"), 9000)
+    assert_close(host(out), ref, "bf16", "static, 128 rows")
