@@ -44,7 +44,6 @@ int check_video(const hippo_video_desc* v) {
 
 // ---- attention planning -------------------------------------------------------------------------
 struct AttnPlan {
-  bool mfma;
   int R, row_chunk, n_chunks, S;
   size_t off_m, off_l, bytes;
 };
@@ -55,27 +54,19 @@ int plan_attention(int call, const hippo_kv_desc* kv, int q_len, int n_total, in
   const int G = kv->n_q_heads / kv->n_kv_heads;
   if ((long long)G * q_len > 4096) return HIPPO_ERR_BAD_SHAPE;
   pl->R = G * q_len;
-  pl->mfma = kv->dtype != HIPPO_DTYPE_F32;   // bf16 and 8-bit caches
-  int tile, min_tiles_per_block;
-  if (pl->mfma) {
-    // 65 to 128 rows go in one chunk, of 96 or 128 rows: two chunks stream the whole cache twice and give every
-    // slice half the compute units (33K x 4 heads, 91 rows: 24.5 us a call in one chunk, 28.0 in two).  Where even
-    // one-tile slices leave compute units idle the two chunks have units of their own (1K x 4 heads, 77 rows: 10.3
-    // in one, 10.1 in two); beyond 128 rows a block has no waves left for a single chunk.
-    const long long all_tiles = (long long)((n_total + 31) / 32) * kv->batch * kv->n_kv_heads;
-    pl->row_chunk = pl->R <= 64 ? (pl->R + 15) / 16 * 16
-                    : pl->R > 128 || all_tiles <= kNumCU ? 64 : pl->R <= 96 ? 96 : 128;
-    tile = 32;
-    min_tiles_per_block = 1;     // short caches are bound by latency, not bytes: thin slices on many compute
-                                 // units win (1896 rows, 7 query rows: 59 slices of 32 rows beat 14 of 128 by 9 %)
-  } else {
-    pl->row_chunk = 32;
-    tile = 32;
-    min_tiles_per_block = 2;
-  }
+  const bool f32 = kv->dtype == HIPPO_DTYPE_F32;
+  // 65 to 128 rows go in one chunk, of 96 or 128 rows: two chunks stream the whole cache twice and give every
+  // slice half the compute units (33K x 4 heads, 91 rows: 24.5 us a call in one chunk, 28.0 in two).  Where even
+  // one-tile slices leave compute units idle the two chunks have units of their own (1K x 4 heads, 77 rows: 10.3
+  // in one, 10.1 in two); beyond 128 rows a block has no waves left for a single chunk.
+  const long long all_tiles = (long long)((n_total + 31) / 32) * kv->batch * kv->n_kv_heads;
+  pl->row_chunk = pl->R <= 64 ? (pl->R + 15) / 16 * 16
+                  : pl->R > 128 || all_tiles <= kNumCU ? 64 : pl->R <= 96 ? 96 : 128;
+  // short caches are bound by latency, not bytes: thin slices on many compute units win (bf16, 1896 rows, 7 query
+  // rows: 59 slices of 32 rows beat 14 of 128 by 9 %)
   pl->n_chunks = (pl->R + pl->row_chunk - 1) / pl->row_chunk;
   if ((long long)kv->batch * pl->n_chunks > 65535) return HIPPO_ERR_BAD_SHAPE;
-  const int n_tiles = (n_total + tile - 1) / tile;
+  const int n_tiles = (n_total + 31) / 32;
   int S = num_splits;
   if (S == 0) {
     // one block per compute unit (measured at the 16K configuration: 48 or 80-128 slices per KV head
@@ -83,20 +74,19 @@ int plan_attention(int call, const hippo_kv_desc* kv, int q_len, int n_total, in
     const long long per_split = (long long)kv->batch * kv->n_kv_heads * pl->n_chunks;
     S = (int)(kNumCU / per_split);          // rounded down: a block beyond the last compute unit would share one
     if (S < 1) S = 1;
-    const int cap = n_tiles / min_tiles_per_block;
-    if (S > cap) S = cap;
+    if (S > n_tiles) S = n_tiles;
     // wide row blocks: what a slice hands to the merge grows with its rows, so more slices than the merge takes
     // in one step (64) have to stream at least eight tiles each (8 calls over 4K x 2 heads, 91 rows: 75 us with
     // 64 slices, 82 with 128; over 70K, 4 calls: 91 and 69)
-    if (pl->mfma && pl->R > 64 && pl->R <= 128 && S > 64 && n_tiles < 8 * S) S = n_tiles / 8 > 64 ? n_tiles / 8 : 64;
+    if (pl->R > 64 && pl->R <= 128 && S > 64 && n_tiles < 8 * S) S = n_tiles / 8 > 64 ? n_tiles / 8 : 64;
   }
   if (S > n_tiles) S = n_tiles;
   if (S < 1) S = 1;
   if (S > 1024) S = 1024;
   pl->S = S;
   const size_t slots = (size_t)kv->batch * kv->n_kv_heads * S;
-  // the MFMA kernel hands its slices' outputs to the merge as bf16, the vector-ALU kernel as fp32
-  const size_t o_bytes = align_up(slots * pl->R * kv->head_dim * (pl->mfma ? 2 : sizeof(float)), 256);
+  // the bf16 kernel hands its slices' outputs to the merge as bf16, the fp32 kernel as fp32
+  const size_t o_bytes = align_up(slots * pl->R * kv->head_dim * (f32 ? sizeof(float) : 2), 256);
   const size_t ml_bytes = align_up(slots * pl->R * sizeof(float), 256);
   pl->off_m = o_bytes;
   pl->off_l = o_bytes + ml_bytes;
@@ -171,7 +161,7 @@ int attention_entry(int call, const void* q, int32_t q_len, const void* k_cache,
   p.k_scale = ex.fp8 ? ex.k_scale : nullptr; p.v_scale = ex.fp8 ? ex.v_scale : nullptr;
   // q and out of the 8-bit cache calls are bf16
   const int io_dtype = ex.fp8 ? (int)HIPPO_DTYPE_BF16 : kv->dtype;
-  const hipError_t e = launch_attention(p, io_dtype, kv->head_dim, pl.mfma, static_cast<hipStream_t>(stream));
+  const hipError_t e = launch_attention(p, io_dtype, kv->head_dim, static_cast<hipStream_t>(stream));
   return e == hipSuccess ? HIPPO_OK : HIPPO_ERR_HIP;
 }
 
@@ -466,11 +456,12 @@ int hippo_verify_attention_static(const void* q, int32_t q_len, const void* k_ca
   AttnPlan pl;
   if ((rc = plan_attention(HIPPO_CALL_VERIFY_ATTENTION, kv, q_len, ctx_len + q_len, num_splits, &pl)) != HIPPO_OK)
     return rc;
-  if (pl.bytes > kStaticScratchBytes && num_splits == 0 && pl.R > 64 && pl.R <= 128) {
-    // slices for every compute unit do not fit the array at this many rows: half as many do wherever the
-    // array is meant to serve the shape (256 slots of 128 rows x 128 channels alone are its 8 MB)
-    num_splits = kNumCU / (2 * kv->batch * kv->n_kv_heads);
-    const int n_tiles = (ctx_len + q_len + 31) / 32;
+  if (pl.bytes > kStaticScratchBytes && num_splits == 0) {
+    // slices for every compute unit do not fit the array at this many rows (256 slots of 128 rows x 128 channels in
+    // bf16, or of 64 in fp32, alone are its 8 MB): a slice per 64 (32) rows' worth of compute unit does
+    const int rows = kv->dtype == HIPPO_DTYPE_F32 ? 32 : 64;
+    const int n_tiles = (ctx_len + q_len + 31) / 32 / (kv->dtype == HIPPO_DTYPE_F32 ? 2 : 1);
+    num_splits = (int)(kNumCU / ((long long)kv->batch * kv->n_kv_heads * ((pl.R + rows - 1) / rows)));
     if (num_splits > n_tiles) num_splits = n_tiles;
     if (num_splits < 1) num_splits = 1;
     if ((rc = plan_attention(HIPPO_CALL_VERIFY_ATTENTION, kv, q_len, ctx_len + q_len, num_splits, &pl)) != HIPPO_OK)

@@ -11,7 +11,7 @@
 //     Instantiations of the same kernel cover the cache-format variants: rows appended by the
 //     launch itself, paged caches, and caches of 8-bit floating-point codes (converted to bf16
 //     after the LDS read).
-//   * attn_partial_valu  -- fp32 or bf16 inputs, fp32 vector ALU; used for fp32 caches.
+//   * attn_partial_f32   -- fp32, MFMA 16x16x4 with fp32 operands.
 #include <atomic>
 #include <type_traits>
 
@@ -19,9 +19,6 @@
 
 namespace hippo {
 
-// =================================================================================================
-// Vector-ALU partial kernel
-// =================================================================================================
 // Appended-row fusion: the q_len new K/V rows of (b, hk) go from k_new / v_new [B, q_len, Hkv, D] into
 // cache rows ctx_len.., bit for bit.  Called by one block per (b, hk) after its own transfers have
 // drained; no block of this launch reads those cache rows (they all read k_new / v_new instead).
@@ -36,152 +33,6 @@ __device__ __forceinline__ void append_new_rows(const AttnParams& p, int b, int 
     *(u32x4*)((T*)p.k_w + dst) = *(const u32x4*)((const T*)p.k_new + src);
     *(u32x4*)((T*)p.v_w + dst) = *(const u32x4*)((const T*)p.v_new + src);
   }
-}
-
-constexpr int kValuTile = 32;   // tokens per tile
-constexpr int kValuRows = 32;   // query rows per block
-
-template <typename T, int D>
-__global__ __launch_bounds__(256) void attn_partial_valu(AttnParams p) {
-  constexpr int TT = kValuTile, RC = kValuRows;
-  constexpr int NG = 256 / D;          // row groups in the PV phase
-  constexpr int RPT = RC / NG;         // rows per thread in the PV phase
-  constexpr int VPR = D / Elem<T>::kPerVec;  // 16-byte vectors per row
-
-  __shared__ float Ks[TT][D + 1];
-  __shared__ float Vs[TT][D];
-  __shared__ float Qs[RC][D + 1];
-  __shared__ float Ps[RC][TT];
-  __shared__ float alpha_s[RC];
-
-  const int tid = threadIdx.x;
-  const int split = blockIdx.x, hk = blockIdx.y;
-  const int b = blockIdx.z / p.n_chunks, chunk = blockIdx.z % p.n_chunks;
-  const int r0 = chunk * RC;
-
-  const T* kbase = (const T*)p.k + (long long)b * p.sb + (long long)hk * p.sh;
-  const T* vbase = (const T*)p.v + (long long)b * p.sb + (long long)hk * p.sh;
-
-  // stage the query rows of this chunk (zero rows beyond R)
-  for (int e = tid; e < RC * D; e += 256) {
-    const int rr = e / D, c = e % D, r = r0 + rr;
-    float val = 0.f;
-    if (r < p.R) {
-      const int i = r / p.G, g = r % p.G;
-      val = Elem<T>::load((const T*)p.q + (((long long)b * p.q_len + i) * p.H + hk * p.G + g) * D + c);
-    }
-    Qs[rr][c] = val;
-  }
-
-  // QK / softmax role: token = tid % 32, row group = tid / 32 -> rows rg + 8 * x
-  const int tok = tid & 31, rg = tid >> 5;
-  float m_run[4], l_run[4];
-  int lim[4];
-#pragma unroll
-  for (int x = 0; x < 4; ++x) {
-    m_run[x] = -INFINITY;
-    l_run[x] = 0.f;
-    const int r = r0 + rg + 8 * x;
-    lim[x] = (r < p.R) ? p.ctx_len + r / p.G : -1;   // last visible cache row
-  }
-  // PV role: column c, row group grp -> rows grp + NG * x
-  const int c_pv = tid % D, grp = tid / D;
-  float acc[RPT];
-#pragma unroll
-  for (int x = 0; x < RPT; ++x) acc[x] = 0.f;
-
-  const int n_tiles = (p.n_total + TT - 1) / TT;
-  const int t_lo = (int)((long long)split * n_tiles / p.S);
-  const int t_hi = (int)((long long)(split + 1) * n_tiles / p.S);
-
-  for (int t = t_lo; t < t_hi; ++t) {
-    const int n0 = t * TT;
-    __syncthreads();   // previous tile fully consumed (also orders the Q staging)
-    for (int e = tid; e < TT * VPR; e += 256) {
-      const int row = e / VPR, vec = e % VPR, n = n0 + row;
-      float kf[Elem<T>::kPerVec], vf[Elem<T>::kPerVec];
-      if (n < p.n_total) {
-        const T* ks = kbase + (long long)n * p.sn;
-        const T* vs = vbase + (long long)n * p.sn;
-        if (p.block_table != nullptr) {                      // paged cache: page of row n, row inside it
-          int pg = p.block_table[(long long)b * p.max_pages + (n >> p.page_shift)];
-          pg = pg < 0 ? 0 : (pg >= p.n_pool_pages ? p.n_pool_pages - 1 : pg);
-          const long long o = (long long)pg * p.page_stride + (long long)(n & ((1 << p.page_shift) - 1)) * p.sn +
-                              (long long)hk * p.sh;
-          ks = (const T*)p.k + o;
-          vs = (const T*)p.v + o;
-        }
-        if (p.k_new != nullptr && n >= p.ctx_len) {          // a row that has not reached the cache yet
-          const long long o = (((long long)b * p.q_len + (n - p.ctx_len)) * p.Hkv + hk) * D;
-          ks = (const T*)p.k_new + o;
-          vs = (const T*)p.v_new + o;
-        }
-        const u32x4 kv4 = *(const u32x4*)(ks + vec * Elem<T>::kPerVec);
-        const u32x4 vv4 = *(const u32x4*)(vs + vec * Elem<T>::kPerVec);
-        Elem<T>::unpack(kv4, kf);
-        Elem<T>::unpack(vv4, vf);
-      } else {
-#pragma unroll
-        for (int u = 0; u < Elem<T>::kPerVec; ++u) kf[u] = vf[u] = 0.f;
-      }
-#pragma unroll
-      for (int u = 0; u < Elem<T>::kPerVec; ++u) {
-        Ks[row][vec * Elem<T>::kPerVec + u] = kf[u];
-        Vs[row][vec * Elem<T>::kPerVec + u] = vf[u];
-      }
-    }
-    __syncthreads();
-
-    // logits of this thread's token against its 4 rows
-    float s[4] = {0.f, 0.f, 0.f, 0.f};
-    for (int c = 0; c < D; ++c) {
-      const float kc = Ks[tok][c];
-#pragma unroll
-      for (int x = 0; x < 4; ++x) s[x] = fmaf(kc, Qs[rg + 8 * x][c], s[x]);
-    }
-    const int n = n0 + tok;
-#pragma unroll
-    for (int x = 0; x < 4; ++x) {
-      float sv = (n <= lim[x]) ? s[x] * p.scale_log2 : -INFINITY;
-      const float mx = half32_max(sv);
-      const float m_new = max_nan(m_run[x], mx);
-      const float m_safe = (m_new == -INFINITY) ? 0.f : m_new;
-      const float pv = fast_exp2(sv - m_safe);
-      const float ps = half32_sum(pv);
-      const float a = fast_exp2(m_run[x] - m_safe);
-      l_run[x] = l_run[x] * a + ps;
-      m_run[x] = m_new;
-      Ps[rg + 8 * x][tok] = pv;
-      if (tok == 0) alpha_s[rg + 8 * x] = a;
-    }
-    __syncthreads();
-
-#pragma unroll
-    for (int x = 0; x < RPT; ++x) acc[x] *= alpha_s[grp + NG * x];
-    for (int tt = 0; tt < TT; ++tt) {
-      const float vv = Vs[tt][c_pv];
-#pragma unroll
-      for (int x = 0; x < RPT; ++x) acc[x] = fmaf(Ps[grp + NG * x][tt], vv, acc[x]);
-    }
-  }
-
-  const long long slot = ((long long)b * p.Hkv + hk) * p.S + split;
-#pragma unroll
-  for (int x = 0; x < RPT; ++x) {
-    const int r = r0 + grp + NG * x;
-    if (r < p.R) ((float*)p.part_o)[(slot * p.R + r) * D + c_pv] = acc[x];
-  }
-  if (tok == 0) {
-#pragma unroll
-    for (int x = 0; x < 4; ++x) {
-      const int r = r0 + rg + 8 * x;
-      if (r < p.R) {
-        p.part_m[slot * p.R + r] = m_run[x];
-        p.part_l[slot * p.R + r] = l_run[x];
-      }
-    }
-  }
-  if (p.k_new != nullptr && split == 0 && chunk == 0) append_new_rows<T, D>(p, b, hk);
 }
 
 // =================================================================================================
@@ -665,8 +516,252 @@ __global__ __launch_bounds__(RB * TG * 64) void attn_partial_grid(AttnParams p) 
 }
 
 // =================================================================================================
+// fp32 partial kernel (v_mfma_f32_16x16x4_f32: fp32 operands, products and sums)
+// =================================================================================================
+// Bound by the matrix unit's fp32 rate (1/16 of its bf16 rate) and HBM about equally: 4 * 16 * RB * D flops
+// against 8 * D bytes per token.  The vector-ALU kernel that it replaces spent one LDS read and four shared
+// multiply-adds per pair of operands, and streamed the cache once per 32 query rows.  A verification call, us: 8K x
+// 4 heads x 128, 42 rows, a draft call beside it 88 -> 28; two sequences x 4K x 8 heads, 80 rows, paged 246 -> 47;
+// 12.7K x 8 heads, 104 rows 418 -> 74 (5.5 GFLOP: 74 TFLOP/s of a peak of 157); 64 channels, 70K x 2 heads, 49
+// rows 154 -> 36.  Its error against 64 bits is a third to a half of the former kernel's (shorter serial sums).
+// The same frame as attn_partial_grid: grid (S, H_kv, B * n_chunks), wave (rb, tg) owns 16 query rows and every
+// TG-th 16-token tile, tiles go HBM -> LDS by direct transfers into a ring of NST super-tiles, one barrier per
+// super-tile.  Operands (lane = j + 16g): A row j, contraction slot g; B column j, slot g; result column j, rows
+// 4g..4g+3.  Which element rides in which slot is free as long as both operands agree:
+//   S^T = K Q^T   step (s, c): slot g is channel 16s + 4g + c, so a lane's four steps are one 16-byte read.
+//   O^T = V^T P^T step e: slot g is token 4g + e, the score register e as it stands; result row r of block (h, c)
+//                 is channel 64h + 4r + c, so 16 bytes of a V row give a lane its operands of four blocks, and the
+//                 four blocks of h leave it with 16 consecutive channels.
+// Rows of K and V are stored unpadded, 16-byte piece p of tile row r at p ^ r: the 16 lanes of a K read (16 rows, one
+// piece each) and of a V read (one row, 16 pieces) then spread over all banks.
+template <int D, int TG, int NST>
+struct F32Smem {
+  static constexpr int kTileBytes = 16 * D * 4;
+  static constexpr int kSuperBytes = TG * 2 * kTileBytes;
+  static constexpr int stat_bytes(int rb) { return 2 * TG * rb * 16 * 4; }
+  static constexpr int q_bytes(int rb) { return rb * 16 * D * 4; }
+  static constexpr int xbuf_bytes(int rb) { return rb * TG * (D / 16) * 1024; }
+  // [statistics | queries | ring]; the merge staging overlays queries and ring
+  static constexpr int total(int rb) {
+    const int stream = q_bytes(rb) + NST * kSuperBytes;
+    return stat_bytes(rb) + (stream > xbuf_bytes(rb) ? stream : xbuf_bytes(rb));
+  }
+};
+
+template <int D, int RB, int TG, int NST, int MODE>
+__global__ __launch_bounds__(RB * TG * 64) void attn_partial_f32(AttnParams p) {
+  constexpr bool APPEND = MODE == 1, PAGED = MODE == 2;
+  using SM = F32Smem<D, TG, NST>;
+  constexpr int WAVES = RB * TG;
+  constexpr int CPR = D / 4;                           // 16-byte pieces per row
+  constexpr int RPI = 64 / CPR;                        // rows per transfer
+  constexpr int NLD = 16 / RPI;                        // transfers per K (or V) tile
+  constexpr int NS = D / 16;                           // 16-channel steps of S^T
+  constexpr int NH = D / 64;                           // 64-channel groups of O^T
+  constexpr int XFERS = TG * 2 * NLD;
+  constexpr int ISSUERS = WAVES >= 8 ? 8 : 4;
+  constexpr int PER = XFERS / ISSUERS;
+  static_assert(WAVES >= 4 && XFERS % ISSUERS == 0 && PER * (NST - 1) <= 63, "transfer split");
+
+  if (p.wave_prio) __builtin_amdgcn_s_setprio(2);
+  extern __shared__ __align__(16) unsigned char smem[];
+  float* stat_m = (float*)smem;                        // [TG][RB*16]
+  float* stat_l = stat_m + TG * RB * 16;
+  unsigned char* Qs = smem + SM::stat_bytes(RB);
+  unsigned char* ring = Qs + SM::q_bytes(RB);
+
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int rb = wave % RB, tg = wave / RB;
+  const int j = lane & 15, g = lane >> 4;
+  const int split = blockIdx.x, hk = blockIdx.y;
+  const int b = p.n_chunks == 1 ? (int)blockIdx.z : (int)(blockIdx.z / p.n_chunks);
+  const int chunk = p.n_chunks == 1 ? 0 : (int)(blockIdx.z % p.n_chunks);
+  const float inv_g = __builtin_amdgcn_rcpf((float)p.G);
+  const unsigned ring_addr = (unsigned)(uintptr_t)ring;
+  const unsigned q_addr = (unsigned)(uintptr_t)Qs;
+  const char* kbase = (const char*)p.k + ((PAGED ? 0ll : (long long)b * p.sb) + (long long)hk * p.sh) * 4;
+  const char* vbase = (const char*)p.v + ((PAGED ? 0ll : (long long)b * p.sb) + (long long)hk * p.sh) * 4;
+  const unsigned row_bytes = (unsigned)(p.sn * 4);     // the host caps the row stride at 2^24 elements
+  const int ld_row = lane / CPR, ld_pc = lane % CPR;
+
+  const int tq = p.tiles_q, tr = p.tiles_r;
+  const int t_lo = split * tq + min(split, tr);
+  const int t_hi = t_lo + tq + (split < tr ? 1 : 0);
+  const int n_blk = t_hi - t_lo;
+  const int n_super = (n_blk + TG - 1) / TG;
+  const int row_cap = min(t_hi * 16, p.n_total) - 1;
+  int* page_s = (int*)(smem + SM::total(RB));
+  const int page_mask = PAGED ? (1 << p.page_shift) - 1 : 0;
+  const int slot_lo = PAGED ? (t_lo * 16) >> p.page_shift : 0;
+  if (PAGED) {
+    const int n_slots = n_blk > 0 ? (row_cap >> p.page_shift) - slot_lo + 1 : 0;
+    for (int i = tid; i < n_slots && i < kMaxSlicePages; i += WAVES * 64) {
+      int pg = p.block_table[(long long)b * p.max_pages + slot_lo + i];
+      pg = pg < 0 ? 0 : (pg >= p.n_pool_pages ? p.n_pool_pages - 1 : pg);
+      page_s[i] = pg;
+    }
+    __syncthreads();
+  }
+  // as in attn_partial_grid: tiles past the block's range and rows past the cache's end re-read the last valid
+  // row, so every super-tile costs every issuer exactly PER transfers
+  auto issue_super = [&](int si) {
+    const unsigned dst = ring_addr + (si % NST) * SM::kSuperBytes;
+    const int tile0 = t_lo + si * TG;
+#pragma unroll
+    for (int u = 0; u < PER; ++u) {
+      const int x = wave * PER + u;
+      const int tt = x / (2 * NLD), which = (x / NLD) & 1, n = x % NLD;
+      const int r = n * RPI + ld_row;
+      const int row = min((tile0 + tt) * 16 + r, row_cap);
+      const char* src = (which ? vbase : kbase) + (unsigned long long)(unsigned)row * row_bytes;
+      if (PAGED)
+        src = (which ? vbase : kbase) + ((long long)page_s[(row >> p.page_shift) - slot_lo] * p.page_stride +
+                                         (long long)(row & page_mask) * p.sn) * 4;
+      if (APPEND && row >= p.ctx_len)
+        src = (const char*)(which ? p.v_new : p.k_new) +
+              ((((long long)b * p.q_len + (row - p.ctx_len)) * p.Hkv + hk) * D) * 4;
+      dma16(src + ((ld_pc ^ r) * 16), dst + (tt * 2 + which) * SM::kTileBytes + n * 1024);
+    }
+  };
+  const bool issuer = wave < ISSUERS;
+  // the first stage goes out first, then the queries (transfers complete in order: the wait for super-tile 0 covers
+  // them), then the other stages
+  int issued = n_super < NST ? n_super : NST;
+  if (issuer && issued > 0) issue_super(0);
+#pragma unroll
+  for (int n = 0; n < RB * NLD; ++n) {
+    if ((n % WAVES) == wave) {
+      const int rr = n * RPI + ld_row;
+      const int r = min(chunk * (RB * 16) + rr, p.R - 1);   // padding rows repeat the last real row
+      const int i = row_div_group(r, inv_g), gq = r - i * p.G;
+      const char* src = (const char*)p.q + ((((long long)b * p.q_len + i) * p.H + hk * p.G + gq) * D) * 4 +
+                        ((ld_pc ^ (rr & 15)) * 16);
+      dma16(src, q_addr + n * 1024);
+    }
+  }
+  if (issuer)
+    for (int si = 1; si < issued; ++si) issue_super(si);
+
+  const int row = chunk * (RB * 16) + rb * 16 + j;     // this lane's query row
+  const int lim = row < p.R ? p.ctx_len + row_div_group(row, inv_g) : 0x7fffffff;
+  float m_run = -INFINITY, l_run = 0.f;
+  f32x4 qop[NS];
+  f32x4 acc[NH][4];
+#pragma unroll
+  for (int h = 0; h < NH; ++h)
+#pragma unroll
+    for (int c = 0; c < 4; ++c) acc[h][c] = (f32x4){0.f, 0.f, 0.f, 0.f};
+
+  for (int si = 0; si < n_super; ++si) {
+    if (issuer) WaitLadder<NST - 1>::template run<PER>(issued - 1 - si); else wait_vmcnt<0>();
+    __syncthreads();
+    if (si > 0 && issued < n_super) {                  // refill the stage just vacated
+      if (issuer) issue_super(issued);
+      ++issued;
+    }
+    if (si == 0) {
+#pragma unroll
+      for (int s = 0; s < NS; ++s)
+        qop[s] = *(const f32x4*)(Qs + (rb * 16 + j) * (D * 4) + (((4 * s + g) ^ j) * 16));
+    }
+    const int ti = si * TG + tg;
+    if (ti >= n_blk) continue;                         // ragged last super-tile
+    const unsigned char* Kt = ring + (si % NST) * SM::kSuperBytes + tg * 2 * SM::kTileBytes;
+    const unsigned char* Vt = Kt + SM::kTileBytes;
+    const int n0 = (t_lo + ti) * 16;
+
+    f32x4 z[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};   // two chains, even and odd steps
+#pragma unroll
+    for (int s = 0; s < NS; ++s) {
+      const f32x4 kop = *(const f32x4*)(Kt + j * (D * 4) + (((4 * s + g) ^ j) * 16));
+#pragma unroll
+      for (int c = 0; c < 4; ++c)
+        z[c & 1] = __builtin_amdgcn_mfma_f32_16x16x4f32(kop[c], qop[s][c], z[c & 1], 0, 0, 0);
+    }
+    float sv[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) sv[e] = z[0][e] + z[1][e];
+    if (n0 + 15 > p.ctx_len) {                         // tile touches the causal edge
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        if (n0 + 4 * g + e > lim) sv[e] = -INFINITY;
+    }
+    const float mx = rows4_max(max_nan_of(sv)) * p.scale_log2;
+    const bool up = mx > m_run + kRescaleGap;          // lazy reference, as in attn_partial_grid
+    if (__any(up)) {
+      const float a = up ? fast_exp2(m_run - mx) : 1.f;
+      if (up) m_run = mx;
+      l_run *= a;
+#pragma unroll
+      for (int h = 0; h < NH; ++h)
+#pragma unroll
+        for (int c = 0; c < 4; ++c) acc[h][c] *= a;
+    }
+    const float neg_m = (m_run == -INFINITY) ? 0.f : -m_run;
+    float pr[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) pr[e] = fast_exp2(fmaf(sv[e], p.scale_log2, neg_m));
+    l_run += (pr[0] + pr[1]) + (pr[2] + pr[3]);        // per-lane share; groups g meet at the end
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const int vr = 4 * g + e;
+#pragma unroll
+      for (int h = 0; h < NH; ++h) {
+        const f32x4 vop = *(const f32x4*)(Vt + vr * (D * 4) + (((16 * h + j) ^ vr) * 16));
+#pragma unroll
+        for (int c = 0; c < 4; ++c)
+          acc[h][c] = __builtin_amdgcn_mfma_f32_16x16x4f32(vop[c], pr[e], acc[h][c], 0, 0, 0);
+      }
+    }
+  }
+  wait_vmcnt<0>();   // no transfer may still be writing LDS past this point
+
+  // ---- merge the TG token groups of every row block: group tg finishes vectors tg, tg + TG, ... of the lane's
+  // 4 * NH output vectors (vector (h, e): channels 64h + 16g + 4e .. + 3) ----
+  l_run = rows4_sum(l_run);
+  if (g == 0) {
+    stat_m[tg * RB * 16 + rb * 16 + j] = m_run;
+    stat_l[tg * RB * 16 + rb * 16 + j] = l_run;
+  }
+  constexpr int NV = 4 * NH;
+  f32x4* xbuf = (f32x4*)Qs;                            // [WAVES][NV][64 lanes]
+  __syncthreads();   // every wave is done reading queries and ring
+#pragma unroll
+  for (int v = 0; v < NV; ++v)
+    xbuf[(wave * NV + v) * 64 + lane] = (f32x4){acc[v / 4][0][v % 4], acc[v / 4][1][v % 4], acc[v / 4][2][v % 4],
+                                                acc[v / 4][3][v % 4]};
+  __syncthreads();
+  float f[TG], mm = -INFINITY, ll = 0.f;
+#pragma unroll
+  for (int w = 0; w < TG; ++w) { f[w] = stat_m[w * RB * 16 + rb * 16 + j]; mm = max_nan(mm, f[w]); }
+#pragma unroll
+  for (int w = 0; w < TG; ++w) {
+    f[w] = (f[w] == -INFINITY) ? 0.f : fast_exp2(f[w] - mm);
+    ll = fmaf(f[w], stat_l[w * RB * 16 + rb * 16 + j], ll);
+  }
+  const long long slot = ((long long)b * p.Hkv + hk) * p.S + split;
+  if (row < p.R) {
+    float* o_row = (float*)p.part_o + (slot * p.R + row) * D + 16 * g;
+#pragma unroll
+    for (int vv = 0; vv < NV / TG; ++vv) {
+      const int v = vv * TG + tg;
+      f32x4 o = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int w = 0; w < TG; ++w) o += xbuf[((w * RB + rb) * NV + v) * 64 + lane] * f[w];
+      *(f32x4*)(o_row + 64 * (v / 4) + 4 * (v % 4)) = o;
+    }
+    if (tg == 0 && g == 0) {
+      p.part_m[slot * p.R + row] = mm;
+      p.part_l[slot * p.R + row] = ll;
+    }
+  }
+  if (APPEND && split == 0 && chunk == 0) append_new_rows<float, D>(p, b, hk);
+}
+
+// =================================================================================================
 // Merge of the KV slices: out = sum_s 2^(m_s - m*) o_s / sum_s 2^(m_s - m*) l_s
-// The slices' outputs o_s are fp32 (PO16 = false: the vector-ALU kernel's) or bf16 (the MFMA kernel's).
+// The slices' outputs o_s are fp32 (PO16 = false: the fp32 kernel's) or bf16 (the bf16 kernel's).
 // One block per (query row, KV head, batch element).  The slices are spread over the threads: first
 // the S weights (one slice per thread, block-wide max and sum), then thread (sg, vec) accumulates
 // 16-byte vector `vec` of the row over slices sg, sg + NSG, ... and the NSG groups meet in LDS.
@@ -803,22 +898,29 @@ __global__ __launch_bounds__(256) void attn_combine(AttnParams p) {
 // =================================================================================================
 // host launch
 // =================================================================================================
-template <int D, int RB, int TG, int TT, int NST, int MODE, bool KV8 = false, bool NT = false, bool ROT = false>
-static hipError_t launch_grid_mode(const AttnParams& p, hipStream_t st) {
-  // the paged variant keeps its slice of the page table behind the ring
-  constexpr int smem = GridSmem<D, TG, TT, NST, KV8 ? 1 : 2>::total(RB) + (MODE == 2 ? kMaxSlicePages * 4 : 0);
-  // the attribute belongs to a (kernel, device) pair: set it once for each device this process uses
+// Lets KERNEL use `smem` bytes of dynamic LDS.  The attribute belongs to a (kernel, device) pair: it is set once for
+// each device this process uses.
+template <void (*KERNEL)(AttnParams)>
+static hipError_t allow_dynamic_lds(int smem) {
   static std::atomic<unsigned long long> attr_set{0};
   int dev = 0;
   hipError_t e = hipGetDevice(&dev);
   if (e != hipSuccess) return e;
   const unsigned long long bit = 1ull << (dev & 63);
   if (!(attr_set.load(std::memory_order_acquire) & bit)) {
-    e = hipFuncSetAttribute((const void*)attn_partial_grid<D, RB, TG, TT, NST, MODE, KV8, NT, ROT>,
-                            hipFuncAttributeMaxDynamicSharedMemorySize, smem);
+    e = hipFuncSetAttribute((const void*)KERNEL, hipFuncAttributeMaxDynamicSharedMemorySize, smem);
     if (e != hipSuccess) return e;
     attr_set.fetch_or(bit, std::memory_order_release);
   }
+  return hipSuccess;
+}
+
+template <int D, int RB, int TG, int TT, int NST, int MODE, bool KV8 = false, bool NT = false, bool ROT = false>
+static hipError_t launch_grid_mode(const AttnParams& p, hipStream_t st) {
+  // the paged variant keeps its slice of the page table behind the ring
+  constexpr int smem = GridSmem<D, TG, TT, NST, KV8 ? 1 : 2>::total(RB) + (MODE == 2 ? kMaxSlicePages * 4 : 0);
+  const hipError_t e = allow_dynamic_lds<attn_partial_grid<D, RB, TG, TT, NST, MODE, KV8, NT, ROT>>(smem);
+  if (e != hipSuccess) return e;
   dim3 grid(p.S, p.Hkv, p.B * p.n_chunks);
   AttnParams q = p;                               // the slices' tile counts for this kernel's tile size
   const int n_tiles = (p.n_total + TT - 1) / TT;
@@ -918,11 +1020,41 @@ static hipError_t launch_mfma_d(const AttnParams& p, hipStream_t st) {
   }
 }
 
-template <typename T, int D>
-static hipError_t launch_valu(const AttnParams& p, hipStream_t st) {
-  dim3 grid(p.S, p.Hkv, p.B * p.n_chunks);
-  hipLaunchKernelGGL((attn_partial_valu<T, D>), grid, dim3(256), 0, st, p);
+template <int D, int RB, int TG, int NST, int MODE>
+static hipError_t launch_f32_mode(const AttnParams& p, hipStream_t st) {
+  constexpr int smem = F32Smem<D, TG, NST>::total(RB) + (MODE == 2 ? kMaxSlicePages * 4 : 0);
+  const hipError_t e = allow_dynamic_lds<attn_partial_f32<D, RB, TG, NST, MODE>>(smem);
+  if (e != hipSuccess) return e;
+  AttnParams q = p;
+  const int n_tiles = (p.n_total + 15) / 16;
+  q.tiles_q = n_tiles / p.S;
+  q.tiles_r = n_tiles % p.S;
+  hipLaunchKernelGGL((attn_partial_f32<D, RB, TG, NST, MODE>), dim3(p.S, p.Hkv, p.B * p.n_chunks), dim3(RB * TG * 64),
+                     smem, st, q);
   return hipGetLastError();
+}
+
+template <int D, int RB, int TG, int NST>
+static hipError_t launch_f32(const AttnParams& p, hipStream_t st) {
+  if (p.block_table != nullptr) return launch_f32_mode<D, RB, TG, NST, 2>(p, st);
+  if (p.k_new != nullptr) return launch_f32_mode<D, RB, TG, NST, 1>(p, st);
+  return launch_f32_mode<D, RB, TG, NST, 0>(p, st);
+}
+
+// row blocks x token groups: four groups while LDS and sixteen waves allow them
+template <int D>
+static hipError_t launch_f32_d(const AttnParams& p, hipStream_t st) {
+  // ring stages: what 160 KB of LDS hold beside the queries
+  constexpr bool W = D == 128;
+  switch (p.row_chunk / 16) {
+    case 1: return launch_f32<D, 1, 4, W ? 2 : 4>(p, st);
+    case 2: return launch_f32<D, 2, 4, W ? 2 : 4>(p, st);
+    case 3: return launch_f32<D, 3, 4, W ? 2 : 4>(p, st);
+    case 4: return launch_f32<D, 4, W ? 2 : 4, W ? 3 : 4>(p, st);
+    case 6: return launch_f32<D, 6, 2, W ? 3 : 4>(p, st);
+    case 8: return launch_f32<D, 8, 2, W ? 2 : 4>(p, st);
+    default: return hipErrorInvalidValue;
+  }
 }
 
 template <typename T, int D, bool PO16>
@@ -931,16 +1063,15 @@ static hipError_t launch_combine(const AttnParams& p, hipStream_t st) {
   return hipGetLastError();
 }
 
-hipError_t launch_attention(const AttnParams& p, int dtype, int head_dim, bool use_mfma, hipStream_t st) {
+hipError_t launch_attention(const AttnParams& p, int dtype, int head_dim, hipStream_t st) {
   hipError_t e;
   if (dtype == HIPPO_DTYPE_BF16) {
     if (p.k_scale != nullptr) e = (head_dim == 128) ? launch_kv8_d<128>(p, st) : launch_kv8_d<64>(p, st);
-    else if (use_mfma) e = (head_dim == 128) ? launch_mfma_d<128>(p, st) : launch_mfma_d<64>(p, st);
-    else return hipErrorInvalidValue;       // 16- and 8-bit caches have no vector-ALU path
+    else e = (head_dim == 128) ? launch_mfma_d<128>(p, st) : launch_mfma_d<64>(p, st);
     if (e != hipSuccess) return e;
     return (head_dim == 128) ? launch_combine<uint16_t, 128, true>(p, st) : launch_combine<uint16_t, 64, true>(p, st);
   }
-  e = (head_dim == 128) ? launch_valu<float, 128>(p, st) : launch_valu<float, 64>(p, st);
+  e = (head_dim == 128) ? launch_f32_d<128>(p, st) : launch_f32_d<64>(p, st);
   if (e != hipSuccess) return e;
   return (head_dim == 128) ? launch_combine<float, 128, false>(p, st) : launch_combine<float, 64, false>(p, st);
 }

@@ -223,7 +223,7 @@ struct AttnParams {
   const void* v;
   void* out;
   float* lse;       // may be null
-  void* part_o;     // [B, Hkv, S, R, D] unnormalised partial outputs: bf16 from the MFMA kernel, fp32 from the vector-ALU kernel
+  void* part_o;     // [B, Hkv, S, R, D] unnormalised partial outputs: bf16 from the bf16 kernel, fp32 from the fp32 kernel
   float* part_m;    // [B, Hkv, S, R] running maxima (log2 domain)
   float* part_l;    // [B, Hkv, S, R] partial denominators
   int B, q_len, H, Hkv, G, R;
@@ -233,7 +233,7 @@ struct AttnParams {
   int S;                  // number of KV splits
   int row_chunk;          // query rows handled by one block
   int n_chunks;           // ceil(R / row_chunk)
-  int tiles_q, tiles_r;   // MFMA partial kernel: n_tiles / S and n_tiles % S (set by its launcher)
+  int tiles_q, tiles_r;   // n_tiles / S and n_tiles % S (set by its launcher)
   float phase_per_head;   // 1 / (B * Hkv): (batch element, KV head) number i starts its slices i * this of the
                           // way in and wraps around; 0 = every slice is walked from its first tile
   int wave_prio;          // 1: the partial kernel's waves raise their issue priority (verification is
@@ -257,7 +257,7 @@ struct AttnParams {
 constexpr int kMaxSlicePages = 1024;   // page-table entries a block stages in LDS
 
 // Launchers, one per translation unit.  All return a hipError_t from hipGetLastError().
-hipError_t launch_attention(const AttnParams& p, int dtype, int head_dim, bool use_mfma, hipStream_t st);
+hipError_t launch_attention(const AttnParams& p, int dtype, int head_dim, hipStream_t st);
 
 constexpr int kMaxScoreLayers = 64;   // layers whose s_attn sweeps can share one launch
 

@@ -64,3 +64,41 @@ def test_static_scratch_serves_128_rows_of_128_channels(hippo):
     ref, _ = oracle.attention(q, k, v, 9000, None)
     out = hippo.hippo_verify_attention_static(dev(q, "bf16"), dev(k, "bf16"), dev(v, "bf16"), 9000)
     assert_close(host(out), ref, "bf16", "static, 128 rows")
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("shape", [
+    # q_len, G, ctx, slices: one row to 128 in every row-block size and just past it, and more than one chunk;
+    # slices of part of a tile, a tile, and of more super-tiles than the ring has stages
+    (1, 1, 0, 0), (1, 16, 16, 0), (17, 1, 300, 0), (3, 11, 1000, 1), (7, 7, 1200, 2), (8, 8, 2500, 0), (13, 5, 4200, 0),
+    (97, 1, 4096, 3), (16, 8, 4100, 0), (13, 10, 900, 2),
+])
+def test_fp32_attention_row_blocks(hippo, shape, d):
+    q_len, G, ctx, S = shape
+    q, k, v = attention_inputs(q_len + d, 1, q_len, 2 * G, 2, d, ctx, "fp32")
+    ref, ref_lse = oracle.attention(q, k, v, ctx, None)
+    qd, kd, vd = dev(q, "fp32"), dev(k, "fp32"), dev(v, "fp32")
+    what = "%s d=%d" % (shape, d)
+    plain, lse = hippo.hippo_verify_attention(qd, kd, vd, ctx, num_splits=S, want_lse=True)
+    assert_close(host(plain), ref, "fp32", what)
+    np.testing.assert_allclose(host(lse), ref_lse, rtol=2e-5, atol=2e-5, err_msg=what)
+    k2, v2 = kd.clone(), vd.clone()
+    k2[:, :, ctx:] = 7.0
+    v2[:, :, ctx:] = 7.0
+    new = [x[:, :, ctx:].transpose(1, 2).contiguous() for x in (kd, vd)]
+    out = hippo.hippo_verify_attention(qd, k2, v2, ctx, num_splits=S, k_new=new[0], v_new=new[1])
+    assert torch.equal(out, plain) and torch.equal(k2, kd) and torch.equal(v2, vd), what   # the same arithmetic
+    pools, table = pages([kd, vd], 3)
+    assert torch.equal(hippo.hippo_verify_attention_paged(qd, *pools, table, ctx, num_splits=S), plain), what
+    # rows of a wider buffer: any 16-byte-aligned row stride
+    wide = [torch.zeros((1, 2, ctx + q_len, d + 12), device="cuda") for _ in range(2)]
+    views = [w[..., :d].copy_(x) for w, x in zip(wide, (kd, vd))]
+    assert torch.equal(hippo.hippo_verify_attention(qd, *views, ctx, num_splits=S), plain), what
+
+
+@pytest.mark.parametrize("q_len", [8, 16])
+def test_static_scratch_serves_what_half_the_slices_fit(hippo, q_len):
+    q, k, v = attention_inputs(5, 1, q_len, 8, 1, 128, 9000, "fp32")
+    ref, _ = oracle.attention(q, k, v, 9000, None)
+    out = hippo.hippo_verify_attention_static(dev(q, "fp32"), dev(k, "fp32"), dev(v, "fp32"), 9000)
+    assert_close(host(out), ref, "fp32", "static, %d rows" % (8 * q_len))
