@@ -289,7 +289,7 @@ struct ScoreParams {
   int n_tile;        // token tiles of pass 1
   int n_rsplit;      // runs the query rows of a KV head are cut into (one block each)
   // what every wave of the sweeps would otherwise divide out for itself (filled in by launch_score)
-  int rows_per_split;            // rows of a run: whole 64-row chunks
+  int rows_per_split;            // rows of a run: whole chunks (64 rows in bf16, 32 in fp32)
   int q_step_i, q_step_g;        // 64 / G and 64 % G: how (i, g) of row r = i*G + g move from chunk to chunk
   int q_last_i, q_last_g;        // (i, g) of the KV head's last row
   int emb_run;                   // consecutive frames of one crop position that a block of the frame-run kernel owns

@@ -12,12 +12,6 @@
 
 namespace hippo {
 
-// =================================================================================================
-// s_attn, vector-ALU version (fp32 inputs).  PASS 1: row statistics; PASS 2: column sums.
-// Block: 32 tokens x all rows (in chunks of 32); thread = (token tid%32, row group tid/32).
-// =================================================================================================
-constexpr int kSaValuTile = 32;
-
 // Where pass 1 leaves the (max, sum) of query row r = i*G + g of KV head hk for token tile `tile`:
 // tile-major slabs of all Bz*H*L rows in (bz, hk, r) order, so a block writes consecutive floats and
 // the merge reads consecutive rows; bz = layer * B + b counts (layer, batch element) pairs when several
@@ -26,91 +20,170 @@ __device__ __forceinline__ long long sattn_part_at(const ScoreParams& p, int til
   return (long long)tile * ((long long)p.Bz * p.H * p.L) + ((long long)b * p.Hkv + hk) * ((long long)p.L * p.G) + r;
 }
 
-template <typename T, int D, int PASS>
-__global__ __launch_bounds__(256) void sattn_valu(ScoreParams p) {
-  constexpr int TT = kSaValuTile, RC = 32;
-  constexpr int VPR = D / Elem<T>::kPerVec;
-  __shared__ float Ks[TT][D + 1];
-  __shared__ float Qs[RC][D + 1];
-  __shared__ float lse_s[RC];
-  __shared__ float col_s[8][TT];
+// =================================================================================================
+// s_attn, fp32 version (v_mfma_f32_16x16x4_f32: fp32 operands, products and sums).
+// PASS 1: row statistics; PASS 2: column sums.
+// Bound by the matrix unit's fp32 rate: 2 * L * H * N_v * D flops a pass against 157 TFLOP/s.  A block's four waves
+// (one per SIMD) own 32 tokens each, whose keys stay in registers as A operands, and sweep a run of the KV head's
+// query rows in chunks of 32 that travel HBM -> LDS by direct transfers, two chunks deep.  Z^T = K Q^T: contraction
+// step (s, c), slot g is channel 16s + 4g + c, so 16 bytes of a row give a lane its operands of four steps; lane
+// (row j, group g) ends with tokens tb*16 + 4g + e.  32 tokens a wave are two independent chains of products, which
+// is what keeps the unit busy with few waves; 128-token blocks and row runs leave a short video enough blocks.
+// The vector-ALU sweep that it replaces read LDS for every product: a scoring call of 12K tokens x 28 heads x 64 rows
+// x 128 channels 608 -> 178 us (both passes together 570 -> 100), of 3K x 14 heads x 64 rows x 64 channels 135 -> 47.
+// =================================================================================================
+constexpr int kSaF32Tile = 128;       // tokens per block
+constexpr int kSaF32Rows = 32;        // query rows per chunk
 
-  const int tid = threadIdx.x, tok = tid & 31, rg = tid >> 5;
-  const int tile = blockIdx.x, hk = blockIdx.y, bz = blockIdx.z;
-  const int b = bz % p.B, layer = bz / p.B;          // several layers' sweeps share a launch
-  const int n0 = tile * TT;
+template <int D, int PASS>
+__global__ __launch_bounds__(256, 2) void sattn_f32(ScoreParams p) {
+  constexpr int NW = 4, TPW = kSaF32Tile / NW, TBW = TPW / 16, RCH = kSaF32Rows;
+  constexpr int NS = D / 16;
+  constexpr int CPR = D / 4;                       // 16-byte pieces per row
+  constexpr int RPI = 64 / CPR;                    // rows per transfer
+  constexpr int XPW = RCH / RPI / NW;              // transfers per wave per chunk
+  constexpr int CHUNKB = RCH * D * 4;
+  __shared__ __align__(16) unsigned char Qs[2 * CHUNKB];
+  __shared__ float lse_s[2][RCH];
+  __shared__ float wm_s[2][NW][RCH], wl_s[2][NW][RCH];
+
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int j = lane & 15, g = lane >> 4;
+  const int hk = blockIdx.x, tile = blockIdx.y;
+  const int rs = blockIdx.z % p.n_rsplit, bz = blockIdx.z / p.n_rsplit;
+  const int b = bz % p.B, layer = bz / p.B;        // several layers' sweeps share a launch
+  const int n0 = tile * kSaF32Tile + wave * TPW;   // first token of this wave
   const int Rs = p.L * p.G;
+  const int row_begin = rs * p.rows_per_split, row_end = min(Rs, row_begin + p.rows_per_split);
   const float scale_log2 = rsqrtf((float)D) * kLog2e;
+  const bool small_rows = Rs < (1 << 20);
+  const float inv_g = __builtin_amdgcn_rcpf((float)p.G);
 
-  const T* kbase = (const T*)p.k_layers[layer] + (long long)b * p.sb + (long long)hk * p.sh +
-                   (long long)p.vis_off * p.sn;
-  const T* qlayer = (const T*)p.q_layers[layer];
-  for (int e = tid; e < TT * VPR; e += 256) {
-    const int row = e / VPR, vec = e % VPR, n = n0 + row;
-    float kf[Elem<T>::kPerVec];
-    if (n < p.Nv) {
-      const u32x4 kv4 = *(const u32x4*)(kbase + (long long)n * p.sn + vec * Elem<T>::kPerVec);
-      Elem<T>::unpack(kv4, kf);
-    } else {
+  const float* qbase = (const float*)p.q_layers[layer] + ((long long)b * p.L * p.H + hk * p.G) * D;
+  const unsigned qs_addr = (unsigned)(uintptr_t)Qs;
+  float lse_reg = INFINITY;
+  // rows past the end re-read the last row: pass 1 does not write their statistics, pass 2 gives them an infinite
+  // normaliser.  16-byte piece c of chunk row r lies at c ^ (r & 15).
+  auto request_chunk = [&](int buf, int r0) {
 #pragma unroll
-      for (int u = 0; u < Elem<T>::kPerVec; ++u) kf[u] = 0.f;
+    for (int u = 0; u < XPW; ++u) {
+      const int rr = (wave * XPW + u) * RPI + lane / CPR;
+      const int r = min(r0 + rr, Rs - 1);
+      const int i = small_rows ? row_div_group(r, inv_g) : r / p.G;
+      dma16((const char*)(qbase + ((long long)i * p.H + (r - i * p.G)) * D) + (((lane % CPR) ^ (rr & 15)) * 16),
+            qs_addr + buf * CHUNKB + (wave * XPW + u) * 1024);
     }
+    if (PASS == 2 && tid < RCH) {
+      lse_reg = INFINITY;                          // padding rows contribute exp2(-inf) = 0
+      if (r0 + tid < Rs) lse_reg = p.row_lse[((long long)bz * p.Hkv + hk) * Rs + r0 + tid];
+    }
+  };
+  if (row_begin < row_end) request_chunk(0, row_begin);
+  f32x4 kop[TBW][NS];
+  {
+    const float* kbase = (const float*)p.k_layers[layer] + (long long)b * p.sb + (long long)hk * p.sh +
+                         (long long)p.vis_off * p.sn + 4 * g;
 #pragma unroll
-    for (int u = 0; u < Elem<T>::kPerVec; ++u) Ks[row][vec * Elem<T>::kPerVec + u] = kf[u];
+    for (int tb = 0; tb < TBW; ++tb) {
+      const float* krow = kbase + (long long)min(n0 + tb * 16 + j, p.Nv - 1) * p.sn;   // in bounds; masked below
+#pragma unroll
+      for (int s = 0; s < NS; ++s) kop[tb][s] = *(const f32x4*)(krow + 16 * s);
+    }
+    // settled before the loop: the compiler, which does not count the transfers, would otherwise wait for the keys
+    // inside it and with them for the chunk in flight
+#pragma unroll
+    for (int tb = 0; tb < TBW; ++tb)
+#pragma unroll
+      for (int s = 0; s < NS; ++s) asm volatile("" : "+v"(kop[tb][s]));
   }
+  const bool wave_full = n0 + TPW <= p.Nv;
+  float col[TBW][4];
+#pragma unroll
+  for (int tb = 0; tb < TBW; ++tb)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) col[tb][e] = 0.f;
 
-  const bool tok_ok = (n0 + tok) < p.Nv;
-  float col = 0.f;
-  for (int r0 = 0; r0 < Rs; r0 += RC) {
-    __syncthreads();
-    for (int e = tid; e < RC * D; e += 256) {
-      const int rr = e / D, c = e % D, r = r0 + rr;
-      float val = 0.f;
-      if (r < Rs) {
-        const int i = r / p.G, gq = r % p.G;
-        val = Elem<T>::load(qlayer + (((long long)b * p.L + i) * p.H + hk * p.G + gq) * D + c);
+  // the waves' (max, sum) of chunk row rr, left in half `h` by the chunk that starts at r0 -> the tile's slab
+  auto merge_rows = [&](int h, int r0) {
+    if (tid < RCH && r0 + tid < Rs) {
+      float mm = -INFINITY, ll = 0.f;
+#pragma unroll
+      for (int w = 0; w < NW; ++w) mm = max_nan(mm, wm_s[h][w][tid]);
+#pragma unroll
+      for (int w = 0; w < NW; ++w)
+        ll += (wm_s[h][w][tid] == -INFINITY) ? 0.f : wl_s[h][w][tid] * fast_exp2(wm_s[h][w][tid] - mm);
+      const long long at = sattn_part_at(p, tile, bz, hk, r0 + tid);
+      p.row_m[at] = mm;
+      p.row_l[at] = ll;
+    }
+  };
+  int buf = 0;
+  for (int r0 = row_begin; r0 < row_end; r0 += RCH, buf ^= 1) {
+    wait_vmcnt<0>();                               // this wave's share of the chunk has arrived
+    if (PASS == 2 && tid < RCH) lse_s[buf][tid] = lse_reg;
+    __syncthreads();                               // ... and everyone else's; everyone is done with the chunk before
+    if (r0 + RCH < row_end) request_chunk(buf ^ 1, r0 + RCH);
+    if (PASS == 1 && r0 > row_begin) merge_rows(buf ^ 1, r0 - RCH);
+    const unsigned char* Qc = Qs + buf * CHUNKB;
+#pragma unroll
+    for (int rb = 0; rb < RCH / 16; ++rb) {
+      f32x4 z[TBW];
+#pragma unroll
+      for (int tb = 0; tb < TBW; ++tb) z[tb] = (f32x4){0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int s = 0; s < NS; ++s) {
+        const f32x4 qop = *(const f32x4*)(Qc + (rb * 16 + j) * (D * 4) + (((4 * s + g) ^ j) * 16));
+#pragma unroll
+        for (int c = 0; c < 4; ++c)
+#pragma unroll
+          for (int tb = 0; tb < TBW; ++tb)
+            z[tb] = __builtin_amdgcn_mfma_f32_16x16x4f32(kop[tb][s][c], qop[c], z[tb], 0, 0, 0);
       }
-      Qs[rr][c] = val;
-    }
-    if (PASS == 2 && tid < RC) {
-      const int r = r0 + tid;
-      float v = INFINITY;   // padding rows contribute exp2(-inf) = 0
-      if (r < Rs) v = p.row_lse[((long long)bz * p.Hkv + hk) * Rs + r];
-      lse_s[tid] = v;
-    }
-    __syncthreads();
-    float s[4] = {0.f, 0.f, 0.f, 0.f};
-    for (int c = 0; c < D; ++c) {
-      const float kc = Ks[tok][c];
-#pragma unroll
-      for (int x = 0; x < 4; ++x) s[x] = fmaf(kc, Qs[rg + 8 * x][c], s[x]);
-    }
-#pragma unroll
-    for (int x = 0; x < 4; ++x) {
-      const int r = r0 + rg + 8 * x;
-      const float sv = tok_ok ? s[x] * scale_log2 : -INFINITY;
       if (PASS == 1) {
-        const float mx = half32_max(sv);
-        const float ps = half32_sum(fast_exp2(sv - mx));      // the tile always holds at least one valid token
-        if (tok == 0 && r < Rs) {
-          const long long at = sattn_part_at(p, tile, bz, hk, r);
-          p.row_m[at] = mx;
-          p.row_l[at] = ps;
+        if (!wave_full) {
+#pragma unroll
+          for (int tb = 0; tb < TBW; ++tb)
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+              if (n0 + tb * 16 + 4 * g + e >= p.Nv) z[tb][e] = -INFINITY;
+        }
+        float zv[TBW * 4];
+#pragma unroll
+        for (int e = 0; e < TBW * 4; ++e) zv[e] = z[e >> 2][e & 3];
+        const float mx = rows4_max(max_nan_of(zv)) * scale_log2;
+        const float neg_m = (mx == -INFINITY) ? 0.f : -mx;
+        float ps = 0.f;
+#pragma unroll
+        for (int e = 0; e < TBW * 4; ++e) ps += fast_exp2(fmaf(zv[e], scale_log2, neg_m));
+        ps = rows4_sum(ps);
+        if (g == 0) {
+          wm_s[buf][wave][rb * 16 + j] = mx;
+          wl_s[buf][wave][rb * 16 + j] = ps;
         }
       } else {
-        col += fast_exp2(sv - lse_s[rg + 8 * x]);
+        const float lse = lse_s[buf][rb * 16 + j];
+#pragma unroll
+        for (int tb = 0; tb < TBW; ++tb)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) col[tb][e] += fast_exp2(fmaf(z[tb][e], scale_log2, -lse));
       }
     }
   }
-  if (PASS == 2) {
-    col_s[rg][tok] = col;
+  if (PASS == 1 && row_begin < row_end) {
     __syncthreads();
-    if (tid < TT && (n0 + tid) < p.Nv) {
-      float t = 0.f;
+    merge_rows(buf ^ 1, row_begin + (row_end - row_begin - 1) / RCH * RCH);
+  }
+  if (PASS == 2) {
 #pragma unroll
-      for (int w = 0; w < 8; ++w) t += col_s[w][tid];
-      p.col_part[((long long)bz * p.Hkv + hk) * p.Nv + n0 + tid] = t;
-    }
+    for (int tb = 0; tb < TBW; ++tb)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const float v = row16_sum(col[tb][e]);     // the 16 rows held by the lanes of each group g
+        const int n = n0 + tb * 16 + 4 * g + e;
+        if (j == 0 && n < p.Nv)
+          p.col_part[((long long)bz * p.Hkv * p.n_rsplit + hk + p.Hkv * rs) * p.Nv + n] = v;
+      }
   }
 }
 
@@ -1293,7 +1366,7 @@ __global__ __launch_bounds__(256) void fuse_scores_reg(ScoreParams p) {
 // =================================================================================================
 // host launch
 // =================================================================================================
-int score_token_tile(int dtype) { return dtype == HIPPO_DTYPE_BF16 ? kSaMfmaTile : kSaValuTile; }
+int score_token_tile(int dtype) { return dtype == HIPPO_DTYPE_BF16 ? kSaMfmaTile : kSaF32Tile; }
 
 // Row splits of the s_attn sweeps (bf16 path): enough blocks for two per compute unit, which is what
 // lets the MFMA and the exp work of different waves overlap; a split keeps at least two 64-row chunks.
@@ -1305,9 +1378,22 @@ int score_token_tile(int dtype) { return dtype == HIPPO_DTYPE_BF16 ? kSaMfmaTile
 // block on a few units, which then start a 28-chunk sweep when all others are done (91 us against 81-83
 // with three or four runs); 256 blocks of 14 chunks are best cut in two (one round, two blocks per unit).
 int score_row_splits(int dtype, long long blocks_unsplit, int rows_per_kv_head) {
-  if (dtype != HIPPO_DTYPE_BF16) return 1;
-  const int chunks = (rows_per_kv_head + 63) / 64;
   int best = 1;
+  if (dtype != HIPPO_DTYPE_BF16) {
+    // fp32: a wave per SIMD keeps the matrix unit busy, so a compute unit takes its blocks one after the other in
+    // effect; a block's start costs about what 0.7 of its 32-row chunks do
+    const int chunks = (rows_per_kv_head + kSaF32Rows - 1) / kSaF32Rows;
+    double best_cost = 0.0;
+    for (int rs = 1; rs <= 8 && rs <= chunks; ++rs) {
+      const double cost = (double)((blocks_unsplit * rs + kNumCU - 1) / kNumCU) * ((chunks + rs - 1) / rs + 0.7);
+      if (rs == 1 || cost < best_cost * 0.97) {
+        best = rs;
+        best_cost = cost;
+      }
+    }
+    return best;
+  }
+  const int chunks = (rows_per_kv_head + 63) / 64;
   double best_cost = 0.0;
   for (int rs = 1; rs <= 4; ++rs) {
     if (rs > 1 && chunks / rs < 2) break;                       // at least two chunks per block
@@ -1323,13 +1409,14 @@ int score_row_splits(int dtype, long long blocks_unsplit, int rows_per_kv_head) 
   return best;
 }
 
-template <typename T, int D>
-static hipError_t launch_sattn_valu(const ScoreParams& p, hipStream_t st) {
-  dim3 grid(p.n_tile, p.Hkv, p.Bz);
-  hipLaunchKernelGGL((sattn_valu<T, D, 1>), grid, dim3(256), 0, st, p);
+template <int D>
+static hipError_t launch_sattn_f32(const ScoreParams& p, hipStream_t st) {
+  if (p.n_tile > 65535 || (long long)p.n_rsplit * p.Bz > 65535) return hipErrorInvalidValue;
+  const dim3 grid(p.Hkv, p.n_tile, p.n_rsplit * p.Bz);     // KV head fastest, as the bf16 sweeps
+  hipLaunchKernelGGL((sattn_f32<D, 1>), grid, dim3(256), 0, st, p);
   const long long rows = (long long)p.Bz * p.H * p.L;
   hipLaunchKernelGGL(sattn_row_lse, dim3((unsigned)((rows + 31) / 32)), dim3(256), 0, st, p);
-  hipLaunchKernelGGL((sattn_valu<T, D, 2>), grid, dim3(256), 0, st, p);
+  hipLaunchKernelGGL((sattn_f32<D, 2>), grid, dim3(256), 0, st, p);
   return hipGetLastError();
 }
 
@@ -1357,8 +1444,9 @@ static hipError_t launch_sattn_mfma(const ScoreParams& p, hipStream_t st, long l
 hipError_t launch_score(const ScoreParams& p_in, hipStream_t st) {
   ScoreParams p = p_in;
   {
-    const int rows = p.L * p.G, chunks = (rows + 63) / 64, rs = p.n_rsplit > 0 ? p.n_rsplit : 1;
-    p.rows_per_split = (chunks + rs - 1) / rs * 64;
+    const int unit = p.dtype == HIPPO_DTYPE_BF16 ? 64 : kSaF32Rows;      // rows per chunk of the sweeps
+    const int rows = p.L * p.G, chunks = (rows + unit - 1) / unit, rs = p.n_rsplit > 0 ? p.n_rsplit : 1;
+    p.rows_per_split = (chunks + rs - 1) / rs * unit;
     p.q_step_i = 64 / p.G;
     p.q_step_g = 64 % p.G;
     p.q_last_i = (rows - 1) / p.G;
@@ -1389,7 +1477,7 @@ hipError_t launch_score(const ScoreParams& p_in, hipStream_t st) {
       e = (p.D == 128) ? launch_sattn_mfma<128>(p, st, riders, emb_in_runs)
                        : launch_sattn_mfma<64>(p, st, riders, emb_in_runs);
     else
-      e = (p.D == 128) ? launch_sattn_valu<float, 128>(p, st) : launch_sattn_valu<float, 64>(p, st);
+      e = (p.D == 128) ? launch_sattn_f32<128>(p, st) : launch_sattn_f32<64>(p, st);
     if (e != hipSuccess) return e;
     if (accumulate_only) {   // otherwise the fusion kernel finishes the attention mass itself
       const long long n = (long long)p.B * p.Nv;

@@ -102,3 +102,30 @@ def test_static_scratch_serves_what_half_the_slices_fit(hippo, q_len):
     ref, _ = oracle.attention(q, k, v, 9000, None)
     out = hippo.hippo_verify_attention_static(dev(q, "fp32"), dev(k, "fp32"), dev(v, "fp32"), 9000)
     assert_close(host(out), ref, "fp32", "static, %d rows" % (8 * q_len))
+
+
+def score_inputs(seed, B, L, H, Hkv, d, n, dtype, scale=2.0):
+    r = np.random.default_rng(seed)
+    return prep(r.standard_normal((B, L, H, d)) * scale, dtype), prep(r.standard_normal((B, Hkv, n, d)), dtype)
+
+
+def attention_mass(hippo, q, k, dtype, frames, gh, gw, prefix):
+    """the raw s_attn term of a call that scores by attention alone"""
+    _, comps = hippo.hippo_score_tokens(dev(q, dtype), dev(k, dtype), hippo.video_desc(frames, gh, gw, prefix),
+                                        flags=1, want_components=True)
+    return host(comps)[0]
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("shape", [
+    # B, text rows, G, frames, grid: 1 token and 1 row; 127, 128, 129 tokens; 32 and 33 rows; row runs of unequal
+    # lengths; runs that come out empty (6 runs of 3 chunks over 14)
+    (1, 1, 1, 1, 1, 1), (1, 32, 1, 1, 1, 127), (2, 33, 1, 1, 8, 16), (1, 5, 7, 1, 3, 43), (1, 64, 7, 5, 9, 11),
+    (1, 31, 14, 3, 13, 17), (3, 17, 3, 2, 15, 16),
+])
+def test_fp32_attention_mass(hippo, shape, d):
+    B, L, G, frames, gh, gw = shape
+    n_vis = frames * gh * gw
+    q, k = score_inputs(L + d, B, L, 2 * G, 2, d, n_vis + 9, "fp32")
+    got = attention_mass(hippo, q, k, "fp32", frames, gh, gw, 4)
+    assert_close(got, oracle.s_attn(q, k, 4, n_vis), "fp32", "%s d=%d" % (shape, d))
