@@ -4,9 +4,9 @@
 //                     normaliser over the N_v visual keys, pass 2 recomputes the logits and sums
 //                     exp(z - lse_row) down the columns.  A block owns a tile of tokens (its keys
 //                     stay in registers / LDS) and sweeps all L_txt*G query rows of the KV head.
-//   s_temp, s_spa (Eq. 3-6)  one block per crop: the crop's embeddings and those of the same
-//                     positions in the two neighbouring frames pass through LDS in channel chunks;
-//                     the crop's Gram matrix and the temporal dot products accumulate in registers.
+//   s_temp, s_spa (Eq. 3-6)  one block per crop position and run of frames: the crops pass through
+//                     LDS frame by frame; Gram matrices and dot products with the frame before on MFMA
+//                     (crops above 32 tokens: a block per crop and frame).
 //   fusion (Eq. 7)    one block per frame: per-term mean / population std, z-scores summed.
 #include "common.h"
 
@@ -789,198 +789,37 @@ __global__ __launch_bounds__(256) void emb_scores_mfma(ScoreParams p) {
 }
 
 // =================================================================================================
-// s_temp and s_spa on MFMA, crops of at most 32 tokens (the paper's 5 x 5): channel-split variant.
-// Same products as emb_scores_mfma, but here the waves split the CHANNELS in two halves and the
-// neighbour frames between them (waves 0,1: Gram and previous frame; waves 2,3: next frame), so an
-// operand is fetched at most twice per block; the two channel halves are summed through LDS.
-// =================================================================================================
-struct Emb32Smem {
-  static constexpr int MP = 32;
-  // blocks: Gram (0,0) (0,1) (1,1); then for prev and for next: dot rb0, dot rb1, norm rb0, norm rb1
-  static constexpr int NBLK = 11;
-  f32x4 red[2][3][64];                              // Gram blocks of the two channel halves
-  float redd[2][NBLK - 3][16];                      // diagonals of the dot / norm blocks, likewise
-  float G[MP][MP + 1];
-  float tdot[4][MP];
-  float inv_norm[MP];
-  int tok_s[MP];
-};
-
-// One crop, computed by the 256 threads `tid` = 0..255 of a group; every thread of the block must
-// call it (it contains block-wide barriers).  BATCH = channel steps whose operands are in flight.
-template <int BATCH>
-__device__ __forceinline__ void emb_mfma32_body(const ScoreParams& p, Emb32Smem& sm, const int tid,
-                                                const int crop_in_frame, const int f, const int b) {
-  constexpr int MP = Emb32Smem::MP;
-  constexpr int NBLK = Emb32Smem::NBLK;
-  auto& red = sm.red;
-  auto& redd = sm.redd;
-  auto& G = sm.G;
-  auto& tdot = sm.tdot;
-  auto& inv_norm = sm.inv_norm;
-  auto& tok_s = sm.tok_s;
-
-  const int lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int cg = wave & 1;                          // channel half: channel steps cg, cg+2, ...
-  const int ig = wave >> 1;                         // 0: Gram + previous frame, 1: next frame
-  const int j = lane & 15, g = lane >> 4;
-  const int ncx = (p.gw + p.cw - 1) / p.cw;
-  const int cy = crop_in_frame / ncx, cx = crop_in_frame % ncx;
-  const int y0 = cy * p.ch, x0 = cx * p.cw;
-  const int mh = min(p.ch, p.gh - y0), mw = min(p.cw, p.gw - x0);
-  const int M = mh * mw;
-  if (tid < MP) {
-    const int t = tid < M ? tid : M - 1;            // padding slots repeat the last token
-    tok_s[tid] = f * p.P + (y0 + t / mw) * p.gw + x0 + t % mw;
-  }
-  const bool has_prev = f > 0, has_next = f + 1 < p.F;
-  const int de = p.emb ? p.emb_dim : p.Hkv * p.D;
-  const int n_ks = (de + 31) / 32;
-  __syncthreads();
-
-  // frames without a neighbour re-read the frame itself (finite data, result unused)
-  const int dnb = ig == 0 ? (has_prev ? -1 : 0) : (has_next ? 1 : 0);
-  // Row pointers of this lane's two tokens (row blocks 0 and 1) in this frame and in the neighbour
-  // frame, computed once; a channel step then only adds its channel offset.  With keys as the
-  // embedding, channel c is element c % D of KV head c / D (D is a power of two).
-  const uint16_t* row_cur[2];
-  const uint16_t* row_nb[2];
-  const int dsh = p.D == 128 ? 7 : 6;
-#pragma unroll
-  for (int rbk = 0; rbk < 2; ++rbk) {
-    const long long tokn = tok_s[rbk * 16 + j];
-    if (p.emb) {
-      row_cur[rbk] = (const uint16_t*)p.emb + (long long)b * p.emb_stride_b + tokn * p.emb_stride_tok;
-      row_nb[rbk] = row_cur[rbk] + (long long)dnb * p.P * p.emb_stride_tok;
-    } else {
-      row_cur[rbk] = (const uint16_t*)p.k_cache + (long long)b * p.sb + (p.vis_off + tokn) * p.sn;
-      row_nb[rbk] = row_cur[rbk] + (long long)dnb * p.P * p.sn;
-    }
-  }
-  const bool keys_as_emb = p.emb == nullptr;
-  auto operand = [&](const uint16_t* row, int ks) -> bf16x8 {
-    const int c = ks * 32 + g * 8;
-    const bool ok = ks < n_ks && c < de;
-    const int cs = ok ? c : 0;                         // a valid address either way; zeroed below
-    const long long off = keys_as_emb ? (long long)(cs >> dsh) * p.sh + (cs & (p.D - 1)) : (long long)cs;
-    const bf16x8 v = *(const bf16x8*)(row + off);
-    return ok ? v : (bf16x8){0, 0, 0, 0, 0, 0, 0, 0};
-  };
-
-  f32x4 acc[7];   // ig 0: Gram x3, dot x2, norm x2;  ig 1: (unused x3), dot x2, norm x2
-#pragma unroll
-  for (int i = 0; i < 7; ++i) acc[i] = (f32x4){0.f, 0.f, 0.f, 0.f};
-  for (int ks0 = cg; ks0 < n_ks; ks0 += 2 * BATCH) {   // BATCH channel steps of this wave per round
-    bf16x8 cur[BATCH][2], nb[BATCH][2];
-#pragma unroll
-    for (int u = 0; u < BATCH; ++u)
-#pragma unroll
-      for (int rbk = 0; rbk < 2; ++rbk) {
-        cur[u][rbk] = operand(row_cur[rbk], ks0 + 2 * u);
-        nb[u][rbk] = operand(row_nb[rbk], ks0 + 2 * u);
-      }
-#pragma unroll
-    for (int u = 0; u < BATCH; ++u) {
-      if (ig == 0) {
-        acc[0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(cur[u][0], cur[u][0], acc[0], 0, 0, 0);
-        acc[1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(cur[u][0], cur[u][1], acc[1], 0, 0, 0);
-        acc[2] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(cur[u][1], cur[u][1], acc[2], 0, 0, 0);
-      }
-#pragma unroll
-      for (int rbk = 0; rbk < 2; ++rbk) {
-        acc[3 + rbk] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(cur[u][rbk], nb[u][rbk], acc[3 + rbk], 0, 0, 0);
-        acc[5 + rbk] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(nb[u][rbk], nb[u][rbk], acc[5 + rbk], 0, 0, 0);
-      }
-    }
-  }
-  // D[i][j']: a lane holds column j' = j, rows i = 4g..4g+3; of the dot / norm blocks only the
-  // diagonal (token with itself) is needed: lane (j, g = j/4), element j%4
-  if (ig == 0) {
-#pragma unroll
-    for (int i = 0; i < 3; ++i) red[cg][i][lane] = acc[i];
-  }
-  if ((j >> 2) == g) {
-#pragma unroll
-    for (int i = 3; i < 7; ++i) {                    // 0,1 prev dot; 2,3 prev norm; 4,5 next dot; 6,7 next norm
-      float* dst = &redd[cg][(ig == 0 ? 0 : 4) + i - 3][j];
-#pragma unroll
-      for (int e = 0; e < 4; ++e)
-        if ((j & 3) == e) *dst = acc[i][e];
-    }
-  }
-  __syncthreads();
-  // sum the two channel halves: waves 0..2 finish one Gram block each, wave 3 the diagonals
-  if (wave < 3) {
-    const int blk = wave;
-    const f32x4 v = red[0][blk][lane] + red[1][blk][lane];
-    const int ra = blk == 2 ? 1 : 0, rbk = blk == 0 ? 0 : 1;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      G[ra * 16 + 4 * g + e][rbk * 16 + j] = v[e];
-      G[rbk * 16 + j][ra * 16 + 4 * g + e] = v[e];
-    }
-  } else {
-    for (int e = lane; e < (NBLK - 3) * 16; e += 64) {
-      const int t = e >> 4, jj = e & 15;
-      tdot[t >> 1][(t & 1) * 16 + jj] = redd[0][t][jj] + redd[1][t][jj];
-    }
-  }
-  __syncthreads();
-  if (tid < MP) inv_norm[tid] = G[tid][tid] > 0.f ? 1.f / sqrtf(G[tid][tid]) : 0.f;   // 0: zero-norm row
-  __syncthreads();
-
-  if (tid < M) {
-    const int a = tid;
-    const float ia = inv_norm[a];
-    float mu = 0.f;
-    for (int c2 = 0; c2 < M; ++c2) mu += G[a][c2] * ia * inv_norm[c2];
-    mu /= (float)M;
-    float var = 0.f;
-    for (int c2 = 0; c2 < M; ++c2) {
-      const float cs = G[a][c2] * ia * inv_norm[c2];
-      var = fmaf(cs - mu, cs - mu, var);
-    }
-    const long long o = (long long)b * p.Nv + tok_s[a];
-    p.s_spa[o] = var / (float)M;
-    float sum = 0.f;
-    int cnt = 0;
-    if (has_prev) {
-      const float nb2 = tdot[1][a];
-      sum += (nb2 > 0.f) ? tdot[0][a] * ia / sqrtf(nb2) : 0.f;
-      ++cnt;
-    }
-    if (has_next) {
-      const float nb2 = tdot[3][a];
-      sum += (nb2 > 0.f) ? tdot[2][a] * ia / sqrtf(nb2) : 0.f;
-      ++cnt;
-    }
-    p.s_temp[o] = 1.f - (cnt ? sum / (float)cnt : 0.f);
-  }
-}
-
-// =================================================================================================
-// s_temp and s_spa on MFMA, crops of at most 32 tokens, at most 512 channels: frame-run variant.
+// s_temp and s_spa on MFMA, crops of at most 32 tokens: frame runs.
 // A block of eight waves owns ONE crop position over a run of consecutive frames, so a frame's crop
-// is fetched once and serves as "this frame" for its Gram matrix (Eq. 5-6; its diagonal holds the
-// norms) and as "the neighbour" of the frame before and after it (Eq. 3-4) -- against four fetches
-// per crop when every (crop, frame) is a block of its own.  Wave w owns channels 64w .. 64w+63 (two
-// MFMA channel steps) of all 32 rows; the eight partial Gram and dot blocks are summed through LDS.
-// The operands travel HBM -> LDS by direct transfers, a lane fetching 16 bytes of a 128-byte row
+// serves as "this frame" for its Gram matrix (Eq. 5-6; its diagonal holds the norms) and as "the
+// neighbour" of the frame before and after it (Eq. 3-4) -- against four fetches per crop when every
+// (crop, frame) is a block of its own.  The wave holds 16 * U lanes' worth of 16-byte pieces of all 32
+// rows (U per lane and row block); the eight partial Gram and dot blocks are summed through LDS.
+// The operands travel HBM -> LDS by direct transfers, a lane fetching 16 bytes of a 64 * U-byte row
 // segment next to its neighbour's (an MFMA operand lane holds ITS OWN row, so fetching operands
 // straight into registers makes neighbouring lanes read rows far apart, and the address unit then
 // spends a clock per lane instead of a clock per four); the wave reads them back in operand layout
-// from its own 4 KB strip, whose rows are XOR-swizzled against bank conflicts.  The strip then
+// from its own strip, whose rows are XOR-swizzled against bank conflicts.  The strip then
 // carries the wave's partial Gram blocks to the reduction, so the next frame's transfer is requested
 // once the reduction has read them and lands under the rest of the frame's arithmetic.
+//
+// One pass over a block's channels (512 in bf16 with U = 2 and in fp32 with U = 4) keeps the frame before in
+// registers.  WIDE embeddings take several passes per frame; what does not fit then is the frame before, whose
+// pass is fetched again behind this frame's: two fetches per crop and frame instead of one, against four (a row
+// per lane) in the block-per-two-crops kernel that this replaces.  Whole scoring calls, us: 4 x 36864 tokens, 1024
+// channels 831 -> 778; 2 x 40000 tokens, 768 channels 98 -> 88; 2 x 16320 tokens, 768 channels 86 and 86.
+// fp32 takes the same frame with four 16x16x4 products per 16-byte operand (3136 tokens, 128 channels 47 -> 37;
+// 12288 tokens, 512 channels 178 -> 143; 11040 tokens, 1024 channels 624 -> 562).  The vector-ALU kernel (a block
+// per crop and frame, two LDS reads per multiply-add) is left for fp32 crops above 32 tokens.
 // =================================================================================================
 // 16 bytes of zeros in device memory: what a transfer lane fetches for channels beyond the last
 __device__ __align__(16) const unsigned char g_zero_piece[16] = {0};
 
+template <int U>
 struct EmbRunSmem {
   static constexpr int MP = 32;
   static constexpr int NW = 8;
-  __align__(16) unsigned char strip[NW][4096];      // operands in (32 rows x 128 B), then Gram partials out (3 x 64 x 16 B)
+  __align__(16) unsigned char strip[NW][MP * 64 * U];   // operands in (32 rows x 64 U B), then Gram partials out (3 x 64 x 16 B)
   float redd[NW][2][16];                            // diagonals of the (this frame) x (frame before) blocks
   float G[MP][MP + 1];
   float dotv[MP];
@@ -988,12 +827,33 @@ struct EmbRunSmem {
   int tok_s[MP];
 };
 
+// acc += A B^T over the channels of two 16-byte operands: 8 bf16 channels or 4 fp32 channels per lane group
+template <bool F32>
+__device__ __forceinline__ f32x4 emb_mma(const u32x4& a, const u32x4& b, f32x4 acc) {
+  if constexpr (F32) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      acc = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(a[e]), __uint_as_float(b[e]), acc, 0, 0, 0);
+    return acc;
+  } else {
+    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), acc,
+                                                   0, 0, 0);
+  }
+}
+
 // One crop position `pos` of batch element b over the frames f0 .. f0 + p.emb_run - 1 (cut at the
 // video's end), by the 512 threads of a block; every thread must call it (block-wide barriers).
-__device__ __forceinline__ void emb_run32_body(const ScoreParams& p, EmbRunSmem& sm, const int tid, const int pos,
+template <bool F32, int U, bool WIDE>
+__device__ __forceinline__ void emb_run32_body(const ScoreParams& p, EmbRunSmem<U>& sm, const int tid, const int pos,
                                                const int f0, const int b) {
-  constexpr int MP = EmbRunSmem::MP;
-  constexpr int NW = EmbRunSmem::NW;
+  constexpr int MP = EmbRunSmem<U>::MP;
+  constexpr int NW = EmbRunSmem<U>::NW;
+  constexpr int EB = F32 ? 4 : 2;                   // bytes per channel
+  constexpr int EPP = 16 / EB;                      // channels per 16-byte piece
+  constexpr int PPR = 4 * U;                        // pieces of a row in a wave's strip
+  constexpr int RPT = 64 / PPR;                     // rows per transfer
+  constexpr int NT = MP / RPT;                      // transfers per frame and pass
+  constexpr int CW = PPR * EPP, CB = NW * CW;       // channels per pass: of a wave, of the block
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int j = lane & 15, g = lane >> 4;
@@ -1013,43 +873,62 @@ __device__ __forceinline__ void emb_run32_body(const ScoreParams& p, EmbRunSmem&
   const int dsh = p.D == 128 ? 7 : 6;
   __syncthreads();
 
-  // Transfer i of a frame (0..3) brings rows 8i .. 8i+7 of the crop: lane l fetches, for strip
-  // position l % 8 of row 8i + l / 8, the 16-byte piece (l % 8) ^ (row & 7) of the wave's 128 bytes.
+  // Transfer i of a pass brings rows RPT*i .. of the crop: lane l fetches, for strip position
+  // l % PPR of its row, the 16-byte piece (l % PPR) ^ (row & (PPR - 1)) of the wave's segment.
   // With keys as the embedding, channel c is element c % D of KV head c / D (D is a power of two).
-  // Pieces beyond the last channel are fetched from 16 bytes of zeros (and stay there from frame to
-  // frame), so the operands need no masking.
-  const uint16_t* src[4];
-  const int c = wave * 64 + (((lane & 7) ^ ((lane >> 3) & 7)) * 8);   // (row & 7 is the same in all four transfers)
-  const long long src_step = c >= de ? 0 : (long long)p.P * (keys_as_emb ? p.sn : p.emb_stride_tok);
+  // Pieces beyond the last channel are fetched from 16 bytes of zeros, so the operands need no masking.
+  const char* const base = keys_as_emb
+      ? (const char*)p.k_cache + ((long long)b * p.sb + (long long)p.vis_off * p.sn) * EB
+      : (const char*)p.emb + (long long)b * p.emb_stride_b * EB;
+  const long long tok_step = (keys_as_emb ? p.sn : p.emb_stride_tok) * EB;
+  const long long frame_step = (long long)p.P * tok_step;
+  auto channel = [&](int i, int pass) {             // first channel of this lane's piece
+    return pass * CB + wave * CW + ((lane % PPR) ^ ((i * RPT + lane / PPR) & (PPR - 1))) * EPP;
+  };
+  auto channel_at = [&](int c) -> long long {
+    return (keys_as_emb ? (long long)(c >> dsh) * p.sh + (c & (p.D - 1)) : (long long)c) * EB;
+  };
+  // single pass: the piece is the same in every frame, so its address is kept and moved on frame by frame; several
+  // passes: worked out for each transfer (registers are what the riding blocks are short of)
+  const char* src[WIDE ? 1 : NT];
+  long long src_step[WIDE ? 1 : NT];
+  if constexpr (!WIDE) {
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const long long tokn = (long long)lo * p.P + sm.tok_s[i * 8 + (lane >> 3)];
-    if (c >= de)
-      src[i] = (const uint16_t*)g_zero_piece;
-    else if (keys_as_emb)
-      src[i] = (const uint16_t*)p.k_cache + (long long)b * p.sb + (p.vis_off + tokn) * p.sn +
-               (long long)(c >> dsh) * p.sh + (c & (p.D - 1));
-    else
-      src[i] = (const uint16_t*)p.emb + (long long)b * p.emb_stride_b + tokn * p.emb_stride_tok + c;
+    for (int i = 0; i < NT; ++i) {
+      const int c = channel(i, 0);
+      src[i] = base + ((long long)lo * p.P + sm.tok_s[i * RPT + lane / PPR]) * tok_step + channel_at(c);
+      src_step[i] = frame_step;
+      if (c >= de) {
+        src[i] = (const char*)g_zero_piece;
+        src_step[i] = 0;
+      }
+    }
   }
   unsigned char* strip = &sm.strip[wave][0];
   const unsigned strip_addr = (unsigned)(uintptr_t)strip;
-  auto request_frame = [&]() {
+  auto request = [&](int frame, int pass) {         // single pass: frames lo, lo + 1, ... in turn
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      dma16(src[i], strip_addr + i * 1024);
-      src[i] += src_step;
+    for (int i = 0; i < NT; ++i) {
+      if constexpr (!WIDE) {
+        dma16(src[i], strip_addr + i * 1024);
+        src[i] += src_step[i];
+      } else {
+        const int c = channel(i, pass);
+        const char* at = base + ((long long)frame * p.P + sm.tok_s[i * RPT + lane / PPR]) * tok_step + channel_at(c);
+        dma16(c < de ? at : (const char*)g_zero_piece, strip_addr + i * 1024);
+      }
     }
   };
-  // operand (row block rbk, channel step u of the wave): lane (j, g) holds piece 4u + g of row 16 rbk + j
-  auto operand = [&](int rbk, int u) -> bf16x8 {
-    return *(const bf16x8*)(strip + (rbk * 16 + j) * 128 + (((4 * u + g) ^ (j & 7)) * 16));
+  // operand (row block rbk, step u of the wave's segment): lane (j, g) holds piece 4u + g of row 16 rbk + j
+  auto operand = [&](int rbk, int u) -> u32x4 {
+    return *(const u32x4*)(strip + (rbk * 16 + j) * (64 * U) + (((4 * u + g) ^ (j & (PPR - 1))) * 16));
   };
-  // 1 / sqrt(x) by the hardware's reciprocal square root (1 ulp), which ignores denormals: tiny
-  // arguments are scaled by 2^64 first, the result by 2^32; 0 for a zero-norm row.  (The riding
+  // 1 / sqrt(x), 0 for a zero-norm row.  bf16: by the hardware's reciprocal square root (1 ulp), which ignores
+  // denormals: tiny arguments are scaled by 2^64 first, the result by 2^32.  (The riding
   // blocks compete with the sweep for vector-instruction issue and nothing else, so what the crop's
   // closing arithmetic costs in instructions is what the embedding terms cost the launch.)
   auto inv_sqrt = [](float x) -> float {
+    if constexpr (F32) return x > 0.f ? 1.f / sqrtf(x) : 0.f;
     const bool tiny = x < 0x1p-60f;
     const float r = __builtin_amdgcn_rsqf(tiny ? x * 0x1p64f : x);
     return x > 0.f ? (tiny ? r * 0x1p32f : r) : 0.f;
@@ -1062,42 +941,82 @@ __device__ __forceinline__ void emb_run32_body(const ScoreParams& p, EmbRunSmem&
   const int a = tid >> 4, c0 = (tid & 15) * 2;
   const long long out_base = (long long)b * p.Nv + sm.tok_s[a];
 
-  bf16x8 prev[2][2];                                // the operands of the frame before
+  const int n_pass = WIDE ? (de + CB - 1) / CB : 1;
+  constexpr int UP = WIDE ? 1 : U;
+  u32x4 prev[2][UP];                                // single pass: the operands of the frame before
 #pragma unroll
   for (int rbk = 0; rbk < 2; ++rbk)
 #pragma unroll
-    for (int u = 0; u < 2; ++u) prev[rbk][u] = (bf16x8){0, 0, 0, 0, 0, 0, 0, 0};
-  request_frame();
+    for (int u = 0; u < UP; ++u) prev[rbk][u] = (u32x4){0u, 0u, 0u, 0u};
+  request(lo, 0);
   for (int fr = lo; fr <= hi; ++fr) {
     f32x4 dot[2];
-    bf16x8 cur[2][2];
-    wait_vmcnt<0>();                                // the frame is in this wave's strip
-#pragma unroll
-    for (int rbk = 0; rbk < 2; ++rbk)
-#pragma unroll
-      for (int u = 0; u < 2; ++u) cur[rbk][u] = operand(rbk, u);
-    // D[i][j']: a lane holds column j' = j, rows i = 4g..4g+3.  The strip's operands are in registers
-    // (a wave's LDS operations complete in order), so it can take the Gram partials at once
-    // (one block at a time: few accumulators live beside the two frames' operands).  A neighbour frame
+    dot[0] = dot[1] = (f32x4){0.f, 0.f, 0.f, 0.f};
+    // D[i][j']: a lane holds column j' = j, rows i = 4g..4g+3.  Gram blocks (0,0) (0,1) (1,1); a neighbour frame
     // beyond the run is here for its norms and dot products: the diagonal blocks suffice.
     const bool own_frame = fr >= f0 && fr < f_end;  // (uniform)
+    if constexpr (!WIDE) {
+      u32x4 cur[2][U];
+      wait_vmcnt<0>();                              // the frame is in this wave's strip
 #pragma unroll
-    for (int i = 0; i < 3; ++i) {                    // Gram blocks (0,0) (0,1) (1,1)
-      if (i == 1 && !own_frame) continue;
-      f32x4 gram = {0.f, 0.f, 0.f, 0.f};
+      for (int rbk = 0; rbk < 2; ++rbk)
 #pragma unroll
-      for (int u = 0; u < 2; ++u)
-        gram = __builtin_amdgcn_mfma_f32_16x16x32_bf16(cur[i >> 1][u], cur[(i + 1) >> 1][u], gram, 0, 0, 0);
-      *(f32x4*)(strip + (i * 64 + lane) * 16) = gram;
-    }
-    dot[0] = dot[1] = (f32x4){0.f, 0.f, 0.f, 0.f};
+        for (int u = 0; u < U; ++u) cur[rbk][u] = operand(rbk, u);
+      // the strip's operands are in registers (a wave's LDS operations complete in order), so it can take the Gram
+      // partials at once, one block at a time: few accumulators live beside the two frames' operands
 #pragma unroll
-    for (int rbk = 0; rbk < 2; ++rbk)
+      for (int i = 0; i < 3; ++i) {
+        if (i == 1 && !own_frame) continue;
+        f32x4 gram = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-      for (int u = 0; u < 2; ++u) {
-        dot[rbk] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(cur[rbk][u], prev[rbk][u], dot[rbk], 0, 0, 0);
-        prev[rbk][u] = cur[rbk][u];
+        for (int u = 0; u < U; ++u) gram = emb_mma<F32>(cur[i >> 1][u], cur[(i + 1) >> 1][u], gram);
+        *(f32x4*)(strip + (i * 64 + lane) * 16) = gram;
       }
+#pragma unroll
+      for (int rbk = 0; rbk < 2; ++rbk)
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          dot[rbk] = emb_mma<F32>(cur[rbk][u], prev[rbk][u % UP], dot[rbk]);
+          prev[rbk][u % UP] = cur[rbk][u];
+        }
+    } else {
+      f32x4 gram[3];
+#pragma unroll
+      for (int i = 0; i < 3; ++i) gram[i] = (f32x4){0.f, 0.f, 0.f, 0.f};
+      const bool has_before = fr > lo;
+      for (int pass = 0; pass < n_pass; ++pass) {
+        u32x4 cur[2][U];
+        wait_vmcnt<0>();
+#pragma unroll
+        for (int rbk = 0; rbk < 2; ++rbk)
+#pragma unroll
+          for (int u = 0; u < U; ++u) cur[rbk][u] = operand(rbk, u);
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // read before the next transfer may overwrite them
+        if (has_before) request(fr - 1, pass);
+        else if (pass + 1 < n_pass) request(fr, pass + 1);
+#pragma unroll
+        for (int i = 0; i < 3; ++i)
+          if (i != 1 || own_frame)
+#pragma unroll
+            for (int u = 0; u < U; ++u) gram[i] = emb_mma<F32>(cur[i >> 1][u], cur[(i + 1) >> 1][u], gram[i]);
+        if (has_before) {
+          wait_vmcnt<0>();
+#pragma unroll
+          for (int rbk = 0; rbk < 2; ++rbk) {
+            u32x4 before[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) before[u] = operand(rbk, u);
+#pragma unroll
+            for (int u = 0; u < U; ++u) dot[rbk] = emb_mma<F32>(cur[rbk][u], before[u], dot[rbk]);
+          }
+          asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+          if (pass + 1 < n_pass) request(fr, pass + 1);
+        }
+      }
+#pragma unroll
+      for (int i = 0; i < 3; ++i)
+        if (i != 1 || own_frame) *(f32x4*)(strip + (i * 64 + lane) * 16) = gram[i];
+    }
     // of a dot block only the diagonal (token with itself) is needed: lane (j, g = j/4), element j%4
     if ((j >> 2) == g) {
 #pragma unroll
@@ -1137,7 +1056,7 @@ __device__ __forceinline__ void emb_run32_body(const ScoreParams& p, EmbRunSmem&
       sm.dotv[lane] = d;
     }
     __syncthreads();
-    if (fr < hi) request_frame();                   // the strips are free again: the next frame travels meanwhile
+    if (fr < hi) request(fr + 1, 0);                // the strips are free again: the next frame travels meanwhile
 
     // cosines of token a against tokens c0, c0 + 1 (16 lanes cover the crop; padding rows hold
     // finite values and are masked); Eq. 5-6: their variance -- for the run's own frames only
@@ -1169,37 +1088,34 @@ __device__ __forceinline__ void emb_run32_body(const ScoreParams& p, EmbRunSmem&
 }
 
 // block number -> (crop position, run of frames, batch element), positions fastest
-__device__ __forceinline__ void emb_run32_block(const ScoreParams& p, EmbRunSmem& sm, const unsigned blk) {
+template <bool F32, int U, bool WIDE>
+__device__ __forceinline__ void emb_run32_block(const ScoreParams& p, EmbRunSmem<U>& sm, const unsigned blk) {
   const unsigned ncf = (unsigned)(((p.gh + p.ch - 1) / p.ch) * ((p.gw + p.cw - 1) / p.cw));   // crops per frame
   const unsigned n_runs = (unsigned)((p.F + p.emb_run - 1) / p.emb_run);
   const unsigned rest = blk / ncf, pos = blk - rest * ncf;
   const unsigned bb = rest / n_runs, run = rest - bb * n_runs;
-  emb_run32_body(p, sm, threadIdx.x, (int)pos, (int)run * p.emb_run, (int)bb);
+  emb_run32_body<F32, U, WIDE>(p, sm, threadIdx.x, (int)pos, (int)run * p.emb_run, (int)bb);
 }
 
+template <bool F32, bool WIDE>
 __global__ __launch_bounds__(512) void emb_scores_run32(ScoreParams p) {
-  __shared__ EmbRunSmem sm;
-  emb_run32_block(p, sm, blockIdx.x);
-}
-
-__global__ __launch_bounds__(256) void emb_scores_mfma32(ScoreParams p) {
-  __shared__ Emb32Smem sm;
-  emb_mfma32_body<4>(p, sm, threadIdx.x, blockIdx.x, blockIdx.y, blockIdx.z);
+  constexpr int U = F32 ? 4 : 2;
+  __shared__ EmbRunSmem<U> sm;
+  emb_run32_block<F32, U, WIDE>(p, sm, blockIdx.x);
 }
 
 // Pass 1 of s_attn and the embedding terms in ONE launch: the first n_sattn blocks run the
 // (compute-bound) row-statistics sweep, two per compute unit; the remaining blocks run the crops and
 // fill the third block slot of the compute units, so the memory-bound embedding work hides under the
 // sweep instead of following it.  Three blocks fit a compute unit: 8 waves of at most 80 registers
-// each and the larger of the shared-memory layouts.  RUNS: a riding block owns one crop position over
-// a run of frames (up to 512 channels); otherwise it owns two crops, four waves each.
-template <int D, bool RUNS>
+// each and the larger of the shared-memory layouts.  A riding block owns one crop position over a run of frames;
+// WIDE: of more than 512 channels.
+template <int D, bool WIDE>
 __global__ __launch_bounds__(kSaWaves * 64, 6) void sattn_pass1_with_emb(ScoreParams p, int n_sattn) {
-  static_assert(kSaWaves == EmbRunSmem::NW, "the riding blocks use the sweep's block size");
+  static_assert(kSaWaves == EmbRunSmem<2>::NW, "the riding blocks use the sweep's block size");
   union Smem {
     SattnSmem<D, 1> sa;
-    EmbRunSmem run;
-    Emb32Smem emb[2];
+    EmbRunSmem<2> run;
   };
   __shared__ Smem sm;
   const int blk = blockIdx.x;
@@ -1211,19 +1127,7 @@ __global__ __launch_bounds__(kSaWaves * 64, 6) void sattn_pass1_with_emb(ScorePa
   }
   // (the host admits this launch only when its block count stays below 2^31: crop numbers fit 32 bits,
   // and 32-bit divisions are all that stands in front of a riding block's first load)
-  if constexpr (RUNS) {
-    emb_run32_block(p, sm.run, (unsigned)(blk - n_sattn));
-  } else {
-    const int ncf = ((p.gh + p.ch - 1) / p.ch) * ((p.gw + p.cw - 1) / p.cw);   // crops per frame
-    const unsigned n_crops = (unsigned)ncf * (unsigned)p.F * (unsigned)p.B;
-    const int half = threadIdx.x >> 8;
-    unsigned crop = 2u * (unsigned)(blk - n_sattn) + (unsigned)half;
-    if (crop >= n_crops) crop = n_crops - 1;       // odd count: the idle half repeats the last crop
-    const unsigned fb = crop / (unsigned)ncf;
-    const int c = (int)(crop - fb * (unsigned)ncf);
-    const unsigned bb = fb / (unsigned)p.F;
-    emb_mfma32_body<2>(p, sm.emb[half], threadIdx.x & 255, c, (int)(fb - bb * (unsigned)p.F), (int)bb);
-  }
+  emb_run32_block<false, 2, WIDE>(p, sm.run, (unsigned)(blk - n_sattn));
 }
 
 // =================================================================================================
@@ -1420,15 +1324,15 @@ static hipError_t launch_sattn_f32(const ScoreParams& p, hipStream_t st) {
   return hipGetLastError();
 }
 
-// riders: 0 = pass 1 in a launch of its own, else that many riding blocks (run_riders: of the frame-run kind)
+// riders: 0 = pass 1 in a launch of its own, else that many riding blocks (wide: of more than 512 channels)
 template <int D>
-static hipError_t launch_sattn_mfma(const ScoreParams& p, hipStream_t st, long long riders, bool run_riders) {
+static hipError_t launch_sattn_mfma(const ScoreParams& p, hipStream_t st, long long riders, bool wide) {
   if (p.n_tile > 65535 || (long long)p.n_rsplit * p.Bz > 65535) return hipErrorInvalidValue;
   dim3 grid(p.Hkv, p.n_tile, p.n_rsplit * p.Bz);
   if (riders > 0) {
     const long long n_sattn = (long long)p.n_tile * p.Hkv * p.n_rsplit * p.Bz;
     const dim3 fused((unsigned)(n_sattn + riders));
-    if (run_riders)
+    if (wide)
       hipLaunchKernelGGL((sattn_pass1_with_emb<D, true>), fused, dim3(kSaWaves * 64), 0, st, p, (int)n_sattn);
     else
       hipLaunchKernelGGL((sattn_pass1_with_emb<D, false>), fused, dim3(kSaWaves * 64), 0, st, p, (int)n_sattn);
@@ -1456,26 +1360,27 @@ hipError_t launch_score(const ScoreParams& p_in, hipStream_t st) {
   const bool accumulate_only = (p.flags & HIPPO_SCORE_ACCUMULATE_ONLY) != 0;
   // bf16 with the paper's small crops: the embedding terms ride in the launch of s_attn's pass 1
   const bool want_emb = (p.flags & (HIPPO_SCORE_TEMP | HIPPO_SCORE_SPA)) != 0;
-  // bf16 crops of at most 32 tokens.  Up to 512 channels a block sweeps one crop position over a run
-  // of frames; the runs are as long as still leaves every compute unit a block (at most 8 frames: a
-  // run fetches its two neighbour frames on top of its own).  Wider embeddings: a block per two crops.
+  // Crops of at most 32 tokens: a block sweeps one crop position over a run of frames.  The runs are as long as
+  // still leaves every compute unit a block (at most 8 frames: a run fetches its two neighbour frames on top of its
+  // own); fp32 blocks, which ride in no other launch, fit a compute unit twice and hide each other's trips.
   const long long crops_per_frame = (long long)((p.gh + p.ch - 1) / p.ch) * ((p.gw + p.cw - 1) / p.cw);
+  const bool bf16 = p.dtype == HIPPO_DTYPE_BF16;
   {
-    const long long per_cu = crops_per_frame * p.F * p.B / kNumCU;
-    p.emb_run = (int)std::max<long long>(1, std::min<long long>(std::min<long long>(8, p.F), per_cu));
+    const long long crops = crops_per_frame * p.F * p.B;
+    const long long run = bf16 ? crops / kNumCU : (crops + 2 * kNumCU - 1) / (2 * kNumCU);
+    p.emb_run = (int)std::max<long long>(1, std::min<long long>(std::min<long long>(8, p.F), run));
   }
-  const bool small_crops = p.dtype == HIPPO_DTYPE_BF16 && p.ch * p.cw <= 32;
-  const bool emb_in_runs = small_crops && (p.emb ? p.emb_dim : p.Hkv * p.D) <= 512;
-  const long long n_riders = emb_in_runs ? crops_per_frame * ((p.F + p.emb_run - 1) / p.emb_run) * p.B
-                                         : (crops_per_frame * p.F * p.B + 1) / 2;
+  const bool small_crops = p.ch * p.cw <= 32;
+  const bool wide = (p.emb ? p.emb_dim : p.Hkv * p.D) > 512;
+  const long long n_riders = crops_per_frame * ((p.F + p.emb_run - 1) / p.emb_run) * p.B;
   const long long fused_blocks = (long long)p.n_tile * p.Hkv * p.n_rsplit * p.Bz + n_riders;
-  const bool emb_rides = want_emb && !accumulate_only && (p.flags & HIPPO_SCORE_ATTN) && small_crops &&
+  const bool emb_rides = bf16 && want_emb && !accumulate_only && (p.flags & HIPPO_SCORE_ATTN) && small_crops &&
                          fused_blocks < (1ll << 31);
   const long long riders = emb_rides ? n_riders : 0;
   if ((p.flags & HIPPO_SCORE_ATTN) || accumulate_only) {
     if (p.dtype == HIPPO_DTYPE_BF16)
-      e = (p.D == 128) ? launch_sattn_mfma<128>(p, st, riders, emb_in_runs)
-                       : launch_sattn_mfma<64>(p, st, riders, emb_in_runs);
+      e = (p.D == 128) ? launch_sattn_mfma<128>(p, st, riders, wide)
+                       : launch_sattn_mfma<64>(p, st, riders, wide);
     else
       e = (p.D == 128) ? launch_sattn_f32<128>(p, st) : launch_sattn_f32<64>(p, st);
     if (e != hipSuccess) return e;
@@ -1488,15 +1393,19 @@ hipError_t launch_score(const ScoreParams& p_in, hipStream_t st) {
   if (want_emb && !emb_rides) {
     const int ncy = (p.gh + p.ch - 1) / p.ch, ncx = (p.gw + p.cw - 1) / p.cw;
     dim3 grid(ncy * ncx, p.F, p.B);
-    if (p.dtype == HIPPO_DTYPE_BF16) {
-      const int crop = p.ch * p.cw;
-      if (emb_in_runs && n_riders < (1ll << 31))
-        hipLaunchKernelGGL(emb_scores_run32, dim3((unsigned)n_riders), dim3(512), 0, st, p);
-      else if (crop <= 32) hipLaunchKernelGGL(emb_scores_mfma32, grid, dim3(256), 0, st, p);
-      else if (crop <= 48) hipLaunchKernelGGL(emb_scores_mfma<3>, grid, dim3(256), 0, st, p);
-      else hipLaunchKernelGGL(emb_scores_mfma<4>, grid, dim3(256), 0, st, p);
-    } else {
+    if (small_crops) {
+      if (n_riders >= (1ll << 31)) return hipErrorInvalidValue;
+      const dim3 runs((unsigned)n_riders);
+      if (bf16 && wide) hipLaunchKernelGGL((emb_scores_run32<false, true>), runs, dim3(512), 0, st, p);
+      else if (bf16) hipLaunchKernelGGL((emb_scores_run32<false, false>), runs, dim3(512), 0, st, p);
+      else if (wide) hipLaunchKernelGGL((emb_scores_run32<true, true>), runs, dim3(512), 0, st, p);
+      else hipLaunchKernelGGL((emb_scores_run32<true, false>), runs, dim3(512), 0, st, p);
+    } else if (!bf16) {
       hipLaunchKernelGGL(emb_scores<float>, grid, dim3(256), 0, st, p);
+    } else if (p.ch * p.cw <= 48) {
+      hipLaunchKernelGGL(emb_scores_mfma<3>, grid, dim3(256), 0, st, p);
+    } else {
+      hipLaunchKernelGGL(emb_scores_mfma<4>, grid, dim3(256), 0, st, p);
     }
     if ((e = hipGetLastError()) != hipSuccess) return e;
   }

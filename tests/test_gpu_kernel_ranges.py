@@ -129,3 +129,40 @@ def test_fp32_attention_mass(hippo, shape, d):
     q, k = score_inputs(L + d, B, L, 2 * G, 2, d, n_vis + 9, "fp32")
     got = attention_mass(hippo, q, k, "fp32", frames, gh, gw, 4)
     assert_close(got, oracle.s_attn(q, k, 4, n_vis), "fp32", "%s d=%d" % (shape, d))
+
+
+@pytest.mark.parametrize("dtype", ["fp32", "bf16"])
+@pytest.mark.parametrize("shape", [
+    # B, frames, grid, channels, crop: a pass is 512 channels; one pass and one piece more, short last passes, a
+    # single piece; one frame, two, runs of several with a short last one; crops cut at the edges, of one token, of 32
+    (1, 1, 5, 5, 512, 5, 5), (1, 2, 5, 7, 8, 5, 5), (2, 9, 11, 13, 520, 5, 5), (1, 3, 6, 5, 1024, 5, 5),
+    (1, 40, 16, 16, 768, 5, 5), (1, 37, 11, 12, 504, 4, 8), (1, 5, 3, 3, 1544, 1, 1),
+])
+def test_embedding_terms_over_passes_of_channels(hippo, shape, dtype):
+    B, F, gh, gw, ch, cy, cx = shape
+    r = np.random.default_rng(F * ch)
+    n = F * gh * gw
+    emb = r.standard_normal((B, F, gh, gw, ch))
+    emb = prep((emb + 0.7 * np.roll(emb, 1, 1) + 0.7 * np.roll(emb, 1, 3)).reshape(B, n, ch), dtype)
+    emb[:, n // 2] = 0.0                                              # a zero-norm row
+    q, k = score_inputs(1, B, 3, 2, 1, 64, n, dtype)
+    vid = hippo.video_desc(F, gh, gw, 0, cy, cx)
+    st, ss = oracle.s_temp(emb, F), oracle.s_spa(emb, F, gh, gw, cy, cx)
+    for flags in (7, 6):                                              # beside the attention term, and alone
+        _, comps = hippo.hippo_score_tokens(dev(q, dtype), dev(k, dtype), vid, emb=dev(emb, dtype), flags=flags,
+                                            want_components=True)
+        assert_close(host(comps)[1], st, dtype, "s_temp %s %d" % (shape, flags))
+        # a crop's variance is a difference of cosines: its error is measured against the largest one
+        np.testing.assert_allclose(host(comps)[2], ss, rtol=0, atol=(2e-6 if dtype == "fp32" else 2e-3) * ss.max() + 1e-9)
+
+
+def test_wide_keys_as_embedding(hippo):
+    # 8 KV heads x 128 channels: the keys of all heads side by side, 1024 channels in two passes
+    for dtype in ("fp32", "bf16"):
+        q, k = score_inputs(9, 1, 3, 8, 8, 128, 4 * 6 * 11 + 3, dtype)
+        emb = oracle.keys_as_embedding(k, 2, 4 * 6 * 11)
+        _, comps = hippo.hippo_score_tokens(dev(q, dtype), dev(k, dtype), hippo.video_desc(4, 6, 11, 2),
+                                            want_components=True)
+        assert_close(host(comps)[1], oracle.s_temp(emb, 4), dtype, "s_temp")
+        ss = oracle.s_spa(emb, 4, 6, 11)
+        np.testing.assert_allclose(host(comps)[2], ss, rtol=0, atol=(2e-6 if dtype == "fp32" else 2e-3) * ss.max())
