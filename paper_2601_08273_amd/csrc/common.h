@@ -127,6 +127,18 @@ __device__ __forceinline__ float rows4_sum(float v) {
   return __uint_as_float(b[0]) + __uint_as_float(b[1]);
 }
 
+// The same sum, for four values at once, in two steps: rows_sum_swap16(a, b) leaves in even rows a's and in odd rows
+// b's sum over the row and its neighbour, rows_sum_swap32(ab, cd) in row g the sum over all rows of value g: three
+// swaps and three additions where four rows4_sum take eight of each.
+__device__ __forceinline__ float rows_sum_swap16(float a, float b) {
+  auto s = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+  return __uint_as_float(s[0]) + __uint_as_float(s[1]);
+}
+__device__ __forceinline__ float rows_sum_swap32(float ab, float cd) {
+  auto s = __builtin_amdgcn_permlane32_swap(__float_as_uint(ab), __float_as_uint(cd), false, false);
+  return __uint_as_float(s[0]) + __uint_as_float(s[1]);
+}
+
 // over each half of the wavefront (lanes 0-31, lanes 32-63), result in all its lanes
 __device__ __forceinline__ float half32_max(float v) {
   v = row16_max(v);

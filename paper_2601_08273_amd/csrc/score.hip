@@ -364,15 +364,18 @@ __device__ __forceinline__ void sattn_mfma_body(const ScoreParams& p, SattnSmem<
           z[tb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kop[tb][ks], qop, z[tb], 0, 0, 0);
       }
     };
+    auto mask_tokens = [&](f32x4 (&z)[TBW]) {
+      if (!wave_full) {                         // wave-uniform: only the ragged last wave masks
+#pragma unroll
+        for (int tb = 0; tb < TBW; ++tb)
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+            if (!tok_ok[tb][e]) z[tb][e] = -INFINITY;
+      }
+    };
     auto reduce = [&](int rb, f32x4 (&z)[TBW]) {
       if (PASS == 1) {
-        if (!wave_full) {                       // wave-uniform: only the ragged last wave masks
-#pragma unroll
-          for (int tb = 0; tb < TBW; ++tb)
-#pragma unroll
-            for (int e = 0; e < 4; ++e)
-              if (!tok_ok[tb][e]) z[tb][e] = -INFINITY;
-        }
+        mask_tokens(z);
         float zv[TBW * 4];                      // the scale is positive: take the max of the raw logits
 #pragma unroll
         for (int e = 0; e < TBW * 4; ++e) zv[e] = z[e >> 2][e & 3];
@@ -397,11 +400,56 @@ __device__ __forceinline__ void sattn_mfma_body(const ScoreParams& p, SattnSmem<
           for (int e = 0; e < 4; ++e) col[tb][e] += fast_exp2(fmaf(z[tb][e], scale_log2, -lse));
       }
     };
+    if (PASS == 2) {
 #pragma unroll
-    for (int rb = 0; rb < RCH / 16; ++rb) {
-      f32x4 z[TBW];
-      products(rb, z);
-      reduce(rb, z);
+      for (int rb = 0; rb < RCH / 16; ++rb) {
+        f32x4 z[TBW];
+        products(rb, z);
+        reduce(rb, z);
+      }
+    } else {
+      // Without a reference: exp2 of the logits as they are, and one transposing sum across the lane groups per 64
+      // rows (lane (j, g) ends with row 16g + j of the chunk), 3.4 vector instructions per logit against 6.25 with
+      // a maximum per 16 rows (scoring calls, us: 16384 tokens 51.6 -> 48.4, four layers of 32768 tokens 567 -> 512, 4 x
+      // 36864 tokens of 64 heads 819 -> 760).  Good as long as every row's sum over the wave's tokens stays within 2^-90 .. 2^100: then nothing overflowed, a term that was flushed to zero is below
+      // 2^-31 of the sum, and the tiles' sums can be added up.  Otherwise the wave goes over the chunk again with
+      // the maximum as the reference.
+      static_assert(RCH == 64, "four row blocks, one per lane group");
+      float pair[2];
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        float ps[2];
+#pragma unroll
+        for (int r2 = 0; r2 < 2; ++r2) {
+          f32x4 z[TBW];
+          products(2 * h + r2, z);
+          mask_tokens(z);
+          float t[TBW];
+#pragma unroll
+          for (int tb = 0; tb < TBW; ++tb)
+            t[tb] = (fast_exp2(z[tb][0] * scale_log2) + fast_exp2(z[tb][1] * scale_log2)) +
+                    (fast_exp2(z[tb][2] * scale_log2) + fast_exp2(z[tb][3] * scale_log2));
+          ps[r2] = t[0];
+#pragma unroll
+          for (int tb = 1; tb < TBW; ++tb) ps[r2] += t[tb];
+        }
+        pair[h] = rows_sum_swap16(ps[0], ps[1]);
+        __builtin_amdgcn_sched_barrier(0);     // two row blocks at a time: more in flight spills
+      }
+      const float tot = rows_sum_swap32(pair[0], pair[1]);
+      const bool good = (tot >= 0x1p-90f && tot <= 0x1p100f) || !wave_has_tokens;    // (false for NaN)
+      const int at = ((r0 - row_begin) % RDEF) + lane;
+      if (__all(good)) {
+        wm_s[wave][at] = wave_has_tokens ? 0.f : -INFINITY;
+        wl_s[wave][at] = tot;
+      } else {
+#pragma unroll 1
+        for (int rb = 0; rb < RCH / 16; ++rb) {
+          f32x4 z[TBW];
+          products(rb, z);
+          reduce(rb, z);
+        }
+      }
     }
     if (PASS == 1 && (((r0 - row_begin + RCH) % RDEF) == 0 || r0 + RCH >= row_end)) {
       // merge the waves' (max, sum) of the rows gathered since the last merge and write them out

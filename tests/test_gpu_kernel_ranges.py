@@ -166,3 +166,20 @@ def test_wide_keys_as_embedding(hippo):
         assert_close(host(comps)[1], oracle.s_temp(emb, 4), dtype, "s_temp")
         ss = oracle.s_spa(emb, 4, 6, 11)
         np.testing.assert_allclose(host(comps)[2], ss, rtol=0, atol=(2e-6 if dtype == "fp32" else 2e-3) * ss.max())
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("scale, shift", [
+    # logits that fit fp32's exponent range as they are; rows whose exponentials overflow, underflow to denormals or
+    # to zero without a reference; both kinds of rows and of 32-token tiles in one call
+    (3.0, 0.0), (40.0, 0.0), (1.0, 150.0), (1.0, -80.0), (1.0, -150.0), (120.0, 0.0),
+])
+def test_attention_mass_over_the_exponent_range(hippo, scale, shift, d):
+    q, k = score_inputs(7, 2, 21, 14, 2, d, 3 * 11 * 13 + 5, "bf16", scale)
+    if shift:                                       # a shared component that moves every logit by about `shift`
+        q[..., 0] = np.sqrt(d) * np.log(2.0)
+        k[..., 0] = shift
+        q[:, ::3, :, 0] = 0.0                       # every third text row stays where it was
+        q, k = prep(q, "bf16"), prep(k, "bf16")
+    got = attention_mass(hippo, q, k, "bf16", 3, 11, 13, 2)
+    assert_close(got, oracle.s_attn(q, k, 2, 3 * 11 * 13), "bf16", "scale %g shift %g d=%d" % (scale, shift, d))
