@@ -183,3 +183,19 @@ def test_attention_mass_over_the_exponent_range(hippo, scale, shift, d):
         q, k = prep(q, "bf16"), prep(k, "bf16")
     got = attention_mass(hippo, q, k, "bf16", 3, 11, 13, 2)
     assert_close(got, oracle.s_attn(q, k, 2, 3 * 11 * 13), "bf16", "scale %g shift %g d=%d" % (scale, shift, d))
+
+
+@pytest.mark.parametrize("dtype", ["fp32", "bf16"])
+@pytest.mark.parametrize("rows, d", [(1, 64), (2047, 128), (2049, 128), (70001, 64)])
+def test_codes_over_the_exponent_range(hippo, dtype, rows, d):
+    # codes are the rounded quotients' whatever the multiplier: ordinary, tiny and huge heads, and one of zeros
+    r = np.random.default_rng(rows)
+    x = r.standard_normal((1, 4, rows, d)) * np.exp2(r.integers(-12, 1, (1, 4, rows, 1)))
+    x *= np.array([1.0, 2.0 ** -90, 2.0 ** 100, 0.0]).reshape(1, 4, 1, 1)
+    x = prep(x, dtype)
+    k, v, ks, vs = hippo.hippo_quantize_kv_e4m3(dev(x, dtype), dev(-x, dtype))
+    codes, scale = oracle.quantize_e4m3(x)
+    np.testing.assert_array_equal(ks.cpu().numpy(), scale)
+    np.testing.assert_array_equal(vs.cpu().numpy(), scale)
+    np.testing.assert_array_equal(k.cpu().numpy(), codes)
+    np.testing.assert_array_equal(v.cpu().numpy() & 0x7f, codes & 0x7f)
