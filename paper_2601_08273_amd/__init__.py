@@ -6,7 +6,6 @@ is no fallback path.
 """
 from __future__ import annotations
 
-import contextlib
 import ctypes as C
 import os
 from typing import Optional, Tuple
@@ -168,16 +167,21 @@ def _ptr(t) -> Optional[int]:
 
 
 def _stream(stream) -> Optional[int]:
+    if stream is not None:
+        return stream.cuda_stream or None
     torch = _torch()
-    s = torch.cuda.current_stream() if stream is None else stream
-    return s.cuda_stream or None
+    if not torch.cuda.is_initialized():
+        return torch.cuda.current_stream().cuda_stream or None
+    # the current stream's handle without a Stream object around it (0.3 against 2.8 us)
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice()) or None
 
 
 def kv_desc(cache, n_q_heads: int) -> KvDesc:
     """Descriptor of a [B, H_kv, N, d] cache tensor (any strides with unit stride on d)."""
     assert cache.dim() == 4 and cache.stride(3) == 1
     B, Hkv, _, d = cache.shape
-    return KvDesc(B, n_q_heads, Hkv, d, _dtype_code(cache), cache.stride(0), cache.stride(1), cache.stride(2))
+    sb, sh, sn, _ = cache.stride()
+    return KvDesc(B, n_q_heads, Hkv, d, _dtype_code(cache), sb, sh, sn)
 
 
 def video_desc(n_frames, grid_h, grid_w, vis_offset, crop_h=5, crop_w=5) -> VideoDesc:
@@ -196,28 +200,32 @@ def _on(stream):
     current when it was allocated and may hand it out again, on that stream, as soon as the tensor is
     dropped; allocated under another stream than the kernels', a workspace could be recycled while they
     still use it."""
-    return _torch().cuda.stream(stream) if stream is not None else contextlib.nullcontext()
+    return _torch().cuda.stream(stream)
 
 
 def _allocates_on_its_stream(fn):
     """Run the marshalling of `fn` with its `stream=` argument as the current stream (see _on)."""
     import functools
     import inspect
-    sig = inspect.signature(fn)
+    at = list(inspect.signature(fn).parameters).index("stream")
 
     @functools.wraps(fn)
     def wrapper(*args, **kwargs):
-        stream = sig.bind(*args, **kwargs).arguments.get("stream")
+        # (binding the whole signature took 3 us of a call whose kernels take 10)
+        stream = args[at] if len(args) > at else kwargs.get("stream")
+        if stream is None:
+            return fn(*args, **kwargs)
         with _on(stream):
             return fn(*args, **kwargs)
     return wrapper
 
 
-def _workspace(nbytes: int, device, workspace=None):
+def _workspace(nbytes, device, workspace=None):
+    """`workspace`, or a new one of nbytes() bytes"""
     torch = _torch()
     if workspace is not None:
         return workspace
-    return torch.empty(max(nbytes, 256), dtype=torch.uint8, device=device)
+    return torch.empty(max(nbytes(), 256), dtype=torch.uint8, device=device)
 
 
 def _check(status: int, what: str):
@@ -240,8 +248,7 @@ def hippo_score_tokens(q_txt, k_cache, vid: VideoDesc, emb=None, flags: int = SC
     B, L, H, d = q_txt.shape
     kv = kv_desc(k_cache, H)
     n_vis = vid.n_frames * vid.grid_h * vid.grid_w
-    nbytes = workspace_bytes(CALL_SCORE_TOKENS, kv, vid, L, k_cache.shape[2])
-    ws = _workspace(nbytes, q_txt.device, workspace)
+    ws = _workspace(lambda: workspace_bytes(CALL_SCORE_TOKENS, kv, vid, L, k_cache.shape[2]), q_txt.device, workspace)
     acc_only = bool(flags & SCORE_ACCUMULATE_ONLY)
     scores = scores_out
     if scores is None and not acc_only:
@@ -273,8 +280,8 @@ def hippo_score_tokens_layers(q_txt_layers, k_cache_layers, vid: VideoDesc, emb_
         assert q.is_contiguous() and q.shape == q0.shape and k.shape == k0.shape and k.stride() == k0.stride()
     kv = kv_desc(k0, H)
     n_vis = vid.n_frames * vid.grid_h * vid.grid_w
-    nbytes = int(lib.hippo_score_layers_workspace_bytes(C.byref(kv), C.byref(vid), L, n_layers))
-    ws = _workspace(nbytes, q0.device, workspace)
+    ws = _workspace(lambda: int(lib.hippo_score_layers_workspace_bytes(C.byref(kv), C.byref(vid), L, n_layers)),
+                    q0.device, workspace)
     acc_only = bool(flags & SCORE_ACCUMULATE_ONLY)
     scores = scores_out
     if scores is None and not acc_only:
@@ -315,7 +322,7 @@ def hippo_select_gather_kv(scores, k: int, k_src, v_src, vid: VideoDesc, n_q_hea
         dst = kv_desc(k_dst, H)
     else:
         k_dst = v_dst = None
-    ws = _workspace(256, scores.device, workspace)
+    ws = _workspace(lambda: 256, scores.device, workspace)
     st = lib.hippo_select_gather_kv(_ptr(scores), k, _ptr(k_src), _ptr(v_src), C.byref(src), N, C.byref(vid),
                                     _ptr(k_dst), _ptr(v_dst), C.byref(dst) if dst is not None else None,
                                     _ptr(idx), _ptr(ws), ws.numel(), _stream(stream))
@@ -332,8 +339,7 @@ def _attention(fn_name, call, q, k_cache, v_cache, ctx_len, softmax_scale, num_s
     B, q_len, H, d = q.shape
     kv = kv_desc(k_cache, H)
     assert v_cache.stride() == k_cache.stride() and v_cache.shape == k_cache.shape
-    nbytes = workspace_bytes(call, kv, None, q_len, ctx_len + q_len, 0, num_splits)
-    ws = _workspace(nbytes, q.device, workspace)
+    ws = _workspace(lambda: workspace_bytes(call, kv, None, q_len, ctx_len + q_len, 0, num_splits), q.device, workspace)
     if out is None:
         out = torch.empty_like(q)
     lse = torch.empty((B, H, q_len), dtype=torch.float32, device=q.device) if want_lse else None
@@ -403,8 +409,7 @@ def _attention_fp8kv(fn_name, call, q, k_codes, v_codes, k_scale, v_scale, ctx_l
     for t in (k_scale, v_scale):
         assert t.shape == (B, Hkv) and t.is_contiguous() and t.dtype == torch.float32
     kv = KvDesc(B, H, Hkv, d, DTYPE_FP8_E4M3, k_codes.stride(0), k_codes.stride(1), k_codes.stride(2))
-    nbytes = workspace_bytes(call, kv, None, q_len, ctx_len + q_len, 0, num_splits)
-    ws = _workspace(nbytes, q.device, workspace)
+    ws = _workspace(lambda: workspace_bytes(call, kv, None, q_len, ctx_len + q_len, 0, num_splits), q.device, workspace)
     if out is None:
         out = torch.empty_like(q)
     lse = torch.empty((B, H, q_len), dtype=torch.float32, device=q.device) if want_lse else None
@@ -449,7 +454,7 @@ def hippo_quantize_kv_e4m3(k_src, v_src, n_rows: Optional[int] = None, k_codes=N
     dst = kv_desc(k_codes, Hkv)
     k_scale = torch.empty((B, Hkv), dtype=torch.float32, device=k_src.device)
     v_scale = torch.empty_like(k_scale)
-    ws = _workspace(int(lib.hippo_quantize_kv_workspace_bytes(C.byref(src), n_rows)), k_src.device, workspace)
+    ws = _workspace(lambda: int(lib.hippo_quantize_kv_workspace_bytes(C.byref(src), n_rows)), k_src.device, workspace)
     st = lib.hippo_quantize_kv_e4m3(_ptr(k_src), _ptr(v_src), C.byref(src), n_rows, _ptr(k_codes), _ptr(v_codes),
                                     C.byref(dst), _ptr(k_scale), _ptr(v_scale), _ptr(ws), ws.numel(), _stream(stream))
     _check(st, "hippo_quantize_kv_e4m3")
@@ -469,8 +474,7 @@ def _attention_paged(fn_name, call, q, k_pool, v_pool, block_table, ctx_len, sof
     pd = PagedKvDesc(B, H, Hkv, d, _dtype_code(k_pool), page_size, block_table.shape[1], n_pages,
                      k_pool.stride(0), k_pool.stride(1), k_pool.stride(2))
     flat = KvDesc(B, H, Hkv, d, _dtype_code(k_pool), 0, k_pool.stride(2), k_pool.stride(1))
-    nbytes = workspace_bytes(call, flat, None, q_len, ctx_len + q_len, 0, num_splits)
-    ws = _workspace(nbytes, q.device, workspace)
+    ws = _workspace(lambda: workspace_bytes(call, flat, None, q_len, ctx_len + q_len, 0, num_splits), q.device, workspace)
     if out is None:
         out = torch.empty_like(q)
     lse = torch.empty((B, H, q_len), dtype=torch.float32, device=q.device) if want_lse else None
@@ -521,7 +525,7 @@ def hippo_spec_verify(p_logits, q_logits, draft_tokens, u_accept, u_sample, temp
     nxt = next_token_out if next_token_out is not None else torch.empty(B, dtype=torch.int32, device=dev)
     alpha = torch.empty((B, gamma), dtype=torch.float32, device=dev) if want_alpha else None
     code = _dtype_code(p_logits)
-    ws = _workspace(int(lib.hippo_spec_verify_workspace_bytes(B, gamma, V, code)), dev, workspace)
+    ws = _workspace(lambda: int(lib.hippo_spec_verify_workspace_bytes(B, gamma, V, code)), dev, workspace)
     st = lib.hippo_spec_verify(_ptr(p_logits), _ptr(q_logits), code, p_logits.stride(1), q_stride,
                                _ptr(draft_tokens), _ptr(u_accept), _ptr(u_sample), B, gamma, V,
                                float(temperature), _ptr(n_acc), _ptr(nxt), _ptr(alpha), _ptr(ws), ws.numel(),
