@@ -55,18 +55,21 @@ int plan_attention(int call, const hippo_kv_desc* kv, int q_len, int n_total, in
   if ((long long)G * q_len > 4096) return HIPPO_ERR_BAD_SHAPE;
   pl->R = G * q_len;
   const bool f32 = kv->dtype == HIPPO_DTYPE_F32;
-  // 65 to 128 rows go in one chunk, of 96 or 128 rows: two chunks stream the whole cache twice and give every
-  // slice half the compute units (33K x 4 heads, 91 rows: 24.5 us a call in one chunk, 28.0 in two).  Where even
-  // one-tile slices leave compute units idle the two chunks have units of their own (1K x 4 heads, 77 rows: 10.3
-  // in one, 10.1 in two); beyond 128 rows a block has no waves left for a single chunk.
-  const long long all_tiles = (long long)((n_total + 31) / 32) * kv->batch * kv->n_kv_heads;
-  pl->row_chunk = pl->R <= 64 ? (pl->R + 15) / 16 * 16
-                  : pl->R > 128 || all_tiles <= kNumCU ? 64 : pl->R <= 96 ? 96 : 128;
+  // 65 to 128 rows go in one chunk, of 96 or 128 rows: two chunks stream the whole cache twice and give every slice
+  // half the compute units (33K x 4 heads, 91 rows: 23.9 us a call in one chunk, 28.0 in two).  Not where a slice per
+  // compute unit leaves units idle, which the two chunks then have to themselves (1K x 4 heads, 77 rows: 10.3 in one,
+  // 10.1 in two); nor where it means more than 64 slices, the most the merge takes in one step, of under eight tiles
+  // (64 channels, 9K x 2 heads, 91 rows: 10.4 in one chunk and 64 slices, 10.1 in two; 4K: 10.2 in one and 128
+  // slices, 9.1 in two; but 70K, 70 rows: 17.2 and 19.5).  Beyond 128 rows a block has no waves left for one chunk.
+  const int n_tiles = (n_total + 31) / 32;
+  const long long heads = (long long)kv->batch * kv->n_kv_heads;
+  const bool one_chunk = pl->R > 64 && pl->R <= 128 && n_tiles * heads > kNumCU &&
+                         (kNumCU <= 64 * heads || n_tiles * heads >= 8 * kNumCU);
+  pl->row_chunk = pl->R <= 64 ? (pl->R + 15) / 16 * 16 : !one_chunk ? 64 : pl->R <= 96 ? 96 : 128;
   // short caches are bound by latency, not bytes: thin slices on many compute units win (bf16, 1896 rows, 7 query
   // rows: 59 slices of 32 rows beat 14 of 128 by 9 %)
   pl->n_chunks = (pl->R + pl->row_chunk - 1) / pl->row_chunk;
   if ((long long)kv->batch * pl->n_chunks > 65535) return HIPPO_ERR_BAD_SHAPE;
-  const int n_tiles = (n_total + 31) / 32;
   int S = num_splits;
   if (S == 0) {
     // one block per compute unit (measured at the 16K configuration: 48 or 80-128 slices per KV head
@@ -75,10 +78,6 @@ int plan_attention(int call, const hippo_kv_desc* kv, int q_len, int n_total, in
     S = (int)(kNumCU / per_split);          // rounded down: a block beyond the last compute unit would share one
     if (S < 1) S = 1;
     if (S > n_tiles) S = n_tiles;
-    // wide row blocks: what a slice hands to the merge grows with its rows, so more slices than the merge takes
-    // in one step (64) have to stream at least eight tiles each (8 calls over 4K x 2 heads, 91 rows: 75 us with
-    // 64 slices, 82 with 128; over 70K, 4 calls: 91 and 69)
-    if (pl->R > 64 && pl->R <= 128 && S > 64 && n_tiles < 8 * S) S = n_tiles / 8 > 64 ? n_tiles / 8 : 64;
   }
   if (S > n_tiles) S = n_tiles;
   if (S < 1) S = 1;

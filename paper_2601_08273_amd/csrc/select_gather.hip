@@ -12,7 +12,8 @@ namespace hippo {
 
 constexpr int kSelThreads = 1024;
 constexpr int kSelWaves = kSelThreads / 64;
-constexpr int kKeysPerThread = 40;       // keys held in registers: sequences up to 40960 tokens
+constexpr int kKeysPerThread = 72;       // keys held in registers: sequences up to 73728 tokens
+constexpr int kPackedCounts = 40;        // keys per thread up to which two counts of a block fit 16 bits each
 constexpr int kBins = 4096;              // 12-bit digits (the last pass uses 256 of them)
 constexpr int kHistStride = kBins + kBins / 64;   // padded histogram
 __device__ __forceinline__ int hist_slot(int bin) { return bin + (bin >> 6); }
@@ -239,8 +240,7 @@ __global__ __launch_bounds__(kSelThreads) void topk_select(SelectParams p) {
   // ---- compaction in index order ----
   __syncthreads();
   if (CACHED) {
-    // counts of keys above / equal to the threshold, packed (both fit 16 bits: a block caches at
-    // most 40960 keys).  Index order inside a wave is (group of VW slots, lane, slot in the group):
+    // counts of keys above / equal to the threshold, packed (a wave's both fit 16 bits, a block's up to 40960 keys).  Index order inside a wave is (group of VW slots, lane, slot in the group):
     // one wave scan per group, a running total over the groups, then the totals of the waves in
     // front; every thread then writes its own survivors.
     unsigned excl[NV], run = 0;
@@ -254,11 +254,19 @@ __global__ __launch_bounds__(kSelThreads) void topk_select(SelectParams p) {
       excl[v] = run + incl - mine;
       run += (unsigned)__builtin_amdgcn_readlane((int)incl, 63);
     }
-    const unsigned in_front = waves_in_front(run, wave_tot[0], lane, wave);
+    unsigned gt_front, eq_front;
+    if constexpr (NC <= kPackedCounts) {
+      const unsigned in_front = waves_in_front(run, wave_tot[0], lane, wave);
+      gt_front = in_front >> 16;
+      eq_front = in_front & 0xffffu;
+    } else {
+      gt_front = waves_in_front(run >> 16, wave_tot[0], lane, wave);
+      eq_front = waves_in_front(run & 0xffffu, wave_tot[1], lane, wave);
+    }
     int32_t* const dst = out;
 #pragma unroll
     for (int v = 0; v < NV; ++v) {
-      unsigned gt_before = (in_front + excl[v]) >> 16, eq_before = (in_front + excl[v]) & 0xffffu;
+      unsigned gt_before = gt_front + (excl[v] >> 16), eq_before = eq_front + (excl[v] & 0xffffu);
 #pragma unroll
       for (int e = 0; e < VW; ++e) {
         const unsigned key = keys[v * VW + e];
@@ -331,6 +339,8 @@ hipError_t launch_select_gather(const SelectParams& p, hipStream_t st) {
   else if (n_chunks <= 16) HIPPO_TOPK(16);
   else if (n_chunks <= 24) HIPPO_TOPK(24);
   else if (n_chunks <= 32) HIPPO_TOPK(32);
+  else if (n_chunks <= 40) HIPPO_TOPK(40);
+  else if (n_chunks <= 56) HIPPO_TOPK(56);       // (select calls, us, against keys re-read: 4 x 48K tokens 108, 145; 70K 38, 99)
   else if (n_chunks <= kKeysPerThread) HIPPO_TOPK(kKeysPerThread);
   else HIPPO_TOPK(0);
 #undef HIPPO_TOPK

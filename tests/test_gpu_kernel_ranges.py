@@ -199,3 +199,19 @@ def test_codes_over_the_exponent_range(hippo, dtype, rows, d):
     np.testing.assert_array_equal(vs.cpu().numpy(), scale)
     np.testing.assert_array_equal(k.cpu().numpy(), codes)
     np.testing.assert_array_equal(v.cpu().numpy() & 0x7f, codes & 0x7f)
+
+
+@pytest.mark.parametrize("n", [40960, 40961, 57344, 57345, 70657, 73728, 73729])
+@pytest.mark.parametrize("ties", [False, True])
+def test_topk_of_long_sequences(hippo, n, ties):
+    r = np.random.default_rng(n)
+    s = r.standard_normal((2, n)).astype(np.float32)
+    if ties:
+        s = np.round(s * 2) / 2                      # some ten values: the k-th largest is one of thousands of ties
+        s[1] = 0.25                                  # and a sequence of nothing but ties
+    cache = torch.zeros((2, 1, n, 64), dtype=torch.bfloat16, device="cuda")
+    vid = hippo.video_desc(1, 1, n, 0)
+    for k in (1, n // 4, n - 3, n):
+        idx, _, _ = hippo.hippo_select_gather_kv(torch.from_numpy(s).cuda(), k, cache, cache, vid, gather=False)
+        want = np.sort(np.argsort(-s, axis=1, kind="stable")[:, :k], axis=1)
+        np.testing.assert_array_equal(idx.cpu().numpy(), want)
