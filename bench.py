@@ -240,7 +240,7 @@ def main():
         us["alone:score_tokens"] = round(med(capture(score_only)), 2)
         if dt == "bf16":
             # the draft call again on the same values held as an fp32 cache: that cache type runs the
-            # vector-ALU split-KV kernel, the bf16 cache the MFMA kernel padded to one 16-row block
+            # fp32 split-KV kernel, both padded to one 16-row block
             kp32, vp32 = [x.float() for x in kp], [x.float() for x in vp]
             qdraft32 = [x.float() for x in qdraft]
             out_dr32 = torch.empty_like(qdraft32[0])
@@ -251,7 +251,7 @@ def main():
                 for l in range(L):
                     h.hippo_draft_attention(qdraft32[l], kp32[l], vp32[l], n_dctx, out=out_dr32, workspace=ws_dr32)
 
-            us["alone:draft_per_layer(fp32 cache: vector-ALU kernel)"] = round(med(capture(draft_fp32_all), per=L), 3)
+            us["alone:draft_per_layer(fp32 cache)"] = round(med(capture(draft_fp32_all), per=L), 3)
             del kp32, vp32
         us["alone:prune"] = round(med(run_prune), 2)
 
