@@ -55,15 +55,17 @@ int plan_attention(int call, const hippo_kv_desc* kv, int q_len, int n_total, in
   if ((long long)G * q_len > 4096) return HIPPO_ERR_BAD_SHAPE;
   pl->R = G * q_len;
   const bool f32 = kv->dtype == HIPPO_DTYPE_F32;
-  // 65 to 128 rows go in one chunk, of 96 or 128 rows: two chunks stream the whole cache twice and give every slice
-  // half the compute units (33K x 4 heads, 91 rows: 23.9 us a call in one chunk, 28.0 in two).  Not where a slice per
-  // compute unit leaves units idle, which the two chunks then have to themselves (1K x 4 heads, 77 rows: 10.3 in one,
-  // 10.1 in two); nor where it means more than 64 slices, the most the merge takes in one step, of under eight tiles
-  // (64 channels, 9K x 2 heads, 91 rows: 10.4 in one chunk and 64 slices, 10.1 in two; 4K: 10.2 in one and 128
-  // slices, 9.1 in two; but 70K, 70 rows: 17.2 and 19.5).  Beyond 128 rows a block has no waves left for one chunk.
+  // A block takes at most 64 rows of a 16- or 8-bit cache: more go in chunks of 64, the same slices and tiles in every
+  // cache format.  The fp32 kernel takes 65 to 128 in one chunk: two chunks stream the whole cache twice and give every
+  // slice half the compute units (a call over 33K x 4 heads x 128 channels, 91 rows: 74 us in one chunk, 92 in two; two
+  // sequences x 4K x 8 heads, 80 rows: 45 and 53; 64 channels, 70K x 2 heads, 70 rows: 43 and 52).  Not where a slice
+  // per compute unit leaves units idle, which the two chunks then have to themselves (1K x 4 heads x 128, 77 rows: 16.4
+  // in one, 15.0 in two); nor where it means more than 64 slices, the most the merge takes in one step, of under eight
+  // tiles (64 channels x 2 heads, 91 rows, 4K: 14.9 in one and 128 slices, 12.9 in two; 16K: 22.0 and 21.2; 128
+  // channels x 1 head, 128 rows, 9K: 31.1 and 22.2).  Beyond 128 rows a block has no waves left for one chunk.
   const int n_tiles = (n_total + 31) / 32;
   const long long heads = (long long)kv->batch * kv->n_kv_heads;
-  const bool one_chunk = pl->R > 64 && pl->R <= 128 && n_tiles * heads > kNumCU &&
+  const bool one_chunk = f32 && pl->R > 64 && pl->R <= 128 && n_tiles * heads > kNumCU &&
                          (kNumCU <= 64 * heads || n_tiles * heads >= 8 * kNumCU);
   pl->row_chunk = pl->R <= 64 ? (pl->R + 15) / 16 * 16 : !one_chunk ? 64 : pl->R <= 96 ? 96 : 128;
   // short caches are bound by latency, not bytes: thin slices on many compute units win (bf16, 1896 rows, 7 query

@@ -80,11 +80,10 @@ struct GridSmem {
   static constexpr int q_bytes(int rb) { return rb * 16 * D * 2; }   // queries are always bf16
   static constexpr int stat_bytes(int rb) { return 2 * TG * rb * 16 * 4; }
   static constexpr int xbuf_bytes(int rb) { return rb * TG * (D / 16) * 1024; }   // merge staging
-  // [statistics | queries | ring]; the merge staging overlays queries and ring, both spent by then
-  static constexpr int total(int rb) {
-    const int stream = q_bytes(rb) + NST * kSuperBytes;
-    return stat_bytes(rb) + (stream > xbuf_bytes(rb) ? stream : xbuf_bytes(rb));
+  static constexpr int ring_bytes(int rb) {
+    return NST * kSuperBytes > xbuf_bytes(rb) ? NST * kSuperBytes : xbuf_bytes(rb);
   }
+  static constexpr int total(int rb) { return q_bytes(rb) + stat_bytes(rb) + ring_bytes(rb); }
 };
 
 //
@@ -148,10 +147,10 @@ __global__ __launch_bounds__(RB * TG * 64) void attn_partial_grid(AttnParams p) 
   // against the draft call's waves that share a compute unit with them
   if (p.wave_prio) __builtin_amdgcn_s_setprio(2);
   extern __shared__ __align__(16) unsigned char smem[];
-  float* stat_m = (float*)smem;                              // [TG][RB*16]
+  unsigned char* Qs = smem;
+  float* stat_m = (float*)(smem + SM::q_bytes(RB));          // [TG][RB*16]
   float* stat_l = stat_m + TG * RB * 16;
-  unsigned char* Qs = smem + SM::stat_bytes(RB);
-  unsigned char* ring = Qs + SM::q_bytes(RB);
+  unsigned char* ring = smem + SM::q_bytes(RB) + SM::stat_bytes(RB);
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -439,8 +438,8 @@ __global__ __launch_bounds__(RB * TG * 64) void attn_partial_grid(AttnParams p) 
     stat_m[tg * RB * 16 + rb * 16 + j] = m_run;
     stat_l[tg * RB * 16 + rb * 16 + j] = l_run;
   }
-  f32x4* xbuf = (f32x4*)Qs;                                // [WAVES][DB][64 lanes]
-  __syncthreads();   // (a) every wave is done reading queries and ring before anyone overwrites them
+  f32x4* xbuf = (f32x4*)ring;                              // [WAVES][DB][64 lanes]
+  __syncthreads();   // (a) every wave is done reading the ring before anyone overwrites it
   // a wave finishes head-dim blocks tg, tg + TG, ...: those stay in its registers, only the blocks
   // that other waves finish go through LDS.  The body is instantiated once per value of tg (it is
   // wave-uniform), so which blocks stay and which travel is known at compile time: straight-line
@@ -953,22 +952,6 @@ template <int D, int RB>
 static hipError_t launch_grid_rb(const AttnParams& p, hipStream_t st) {
   const int tiles32_per_block = ((p.n_total + 31) / 32) / (p.S > 0 ? p.S : 1);
   const bool small_tiles = tiles32_per_block < 24;
-  // 65 to 128 rows.  Short slices of 128 channels: one token group, whose states need no merge in LDS, and four
-  // stages of 32-token tiles (eight calls over 16K x 4 heads, 70 rows: 131 us; two groups 138-141; over 33K, 91
-  // rows: 183, two groups 189-194); page look-ups want the issue slots of more waves (33K from pages: 202 us in one
-  // group, 190 in two with 16-token tiles, 195-198 with 32-token ones).  Otherwise two groups, the most that sixteen
-  // waves allow (two calls, four sequences x 8 heads x 37K, 104 rows: 267 us, one group 298; rotated walks 283,
-  // non-temporal transfers with them 277; 64 channels, 70K x 2 heads, 70 rows: 69 with three stages, 72 with two,
-  // 74 in one group).
-  if constexpr (RB > 4) {
-    if (small_tiles && p.block_table != nullptr) return launch_grid_mode<D, RB, 2, 16, 4, 2>(p, st);
-    if constexpr (D == 128) {
-      if (small_tiles)
-        return p.k_new != nullptr ? launch_grid_mode<D, RB, 1, 32, 4, 1>(p, st)
-                                  : launch_grid_mode<D, RB, 1, 32, 4, 0>(p, st);
-    }
-    return launch_grid<D, RB, 2, 32, D == 128 ? 2 : 3>(p, st);
-  } else {
   if (!small_tiles)
     return stream_exceeds_caches(p, D, 2) ? launch_grid<D, RB, 4, 32, 2, true, true>(p, st)
                                           : launch_grid<D, RB, 4, 32, 2, false, true>(p, st);
@@ -979,7 +962,6 @@ static hipError_t launch_grid_rb(const AttnParams& p, hipStream_t st) {
   if (RB == 4 && tiles32_per_block >= 12) return launch_grid<D, RB, 2, 32, 3>(p, st);
   if (RB >= 3) return launch_grid<D, RB, 2, 16, 4>(p, st);
   return launch_grid<D, RB, 4, 16, 3>(p, st);
-  }
 }
 
 // fp8 cache: 32-token tiles only; short slices keep the whole slice in flight (two token groups, four
@@ -989,9 +971,8 @@ static hipError_t launch_kv8_rb(const AttnParams& p, hipStream_t st) {
   const int tiles32_per_block = ((p.n_total + 31) / 32) / (p.S > 0 ? p.S : 1);
   if (tiles32_per_block < 24)
     return launch_grid_mode<D, RB, 2, 32, 4, 0, true>(p, st);
-  constexpr int TG = RB > 4 ? 2 : 4, NST = RB > 4 ? 4 : 2;
-  if (stream_exceeds_caches(p, D, 1)) return launch_grid_mode<D, RB, TG, 32, NST, 0, true, true, true>(p, st);
-  return launch_grid_mode<D, RB, TG, 32, NST, 0, true, false, true>(p, st);
+  if (stream_exceeds_caches(p, D, 1)) return launch_grid_mode<D, RB, 4, 32, 2, 0, true, true, true>(p, st);
+  return launch_grid_mode<D, RB, 4, 32, 2, 0, true, false, true>(p, st);
 }
 
 template <int D>
@@ -1001,8 +982,6 @@ static hipError_t launch_kv8_d(const AttnParams& p, hipStream_t st) {
     case 2: return launch_kv8_rb<D, 2>(p, st);
     case 3: return launch_kv8_rb<D, 3>(p, st);
     case 4: return launch_kv8_rb<D, 4>(p, st);
-    case 6: return launch_kv8_rb<D, 6>(p, st);
-    case 8: return launch_kv8_rb<D, 8>(p, st);
     default: return hipErrorInvalidValue;
   }
 }
@@ -1014,8 +993,6 @@ static hipError_t launch_mfma_d(const AttnParams& p, hipStream_t st) {
     case 2: return launch_grid_rb<D, 2>(p, st);
     case 3: return launch_grid_rb<D, 3>(p, st);
     case 4: return launch_grid_rb<D, 4>(p, st);
-    case 6: return launch_grid_rb<D, 6>(p, st);
-    case 8: return launch_grid_rb<D, 8>(p, st);
     default: return hipErrorInvalidValue;
   }
 }

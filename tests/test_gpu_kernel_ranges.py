@@ -33,29 +33,28 @@ def pages(tensors, seed, size=16):
 
 @pytest.mark.parametrize("d", [64, 128])
 @pytest.mark.parametrize("shape", [
-    # q_len, G, ctx, slices, with two sequences of two KV heads: 65 rows (one past the 64-row block), 96 | 97 (the
-    # two wide blocks), 128 | 130 (one chunk | several); the last cache with fewer 32-token tiles than compute units
-    # and the first with more; slices of a tile, of some, and of 24 and more
+    # q_len, G, ctx, slices, with two sequences of two KV heads: 65 rows (one past the 64-row block), 96 | 97, 128 (two
+    # whole blocks), 130 (a third); caches of just under and over a 32-token tile per compute unit; slices of a tile,
+    # of some, and of 24 and more
     (13, 5, 2100, 0), (12, 8, 2300, 3), (97, 1, 2048, 2), (16, 8, 2400, 2), (13, 10, 2100, 0), (8, 10, 2039, 0),
     (8, 10, 2041, 0),
 ])
-def test_more_than_64_rows_in_one_block(hippo, shape, d):
+def test_more_than_64_rows(hippo, shape, d):
     q_len, G, ctx, S = shape
     q, k, v = attention_inputs(q_len + d, 2, q_len, 2 * G, 2, d, ctx, "bf16")
     ref, _ = oracle.attention(q, k, v, ctx, None)
     qd, kd, vd = dev(q, "bf16"), dev(k, "bf16"), dev(v, "bf16")
     what = "%s d=%d" % (shape, d)
-    assert_close(host(hippo.hippo_verify_attention(qd, kd, vd, ctx, num_splits=S)), ref, "bf16", what)
+    plain = hippo.hippo_verify_attention(qd, kd, vd, ctx, num_splits=S)
+    assert_close(host(plain), ref, "bf16", what)
     k2, v2 = kd.clone(), vd.clone()
     k2[:, :, ctx:] = 7.0
     v2[:, :, ctx:] = 7.0
     new = [x[:, :, ctx:].transpose(1, 2).contiguous() for x in (kd, vd)]
     out = hippo.hippo_verify_attention(qd, k2, v2, ctx, num_splits=S, k_new=new[0], v_new=new[1])
-    assert_close(host(out), ref, "bf16", what + " appended")
-    assert torch.equal(k2, kd) and torch.equal(v2, vd), what
+    assert torch.equal(out, plain) and torch.equal(k2, kd) and torch.equal(v2, vd), what   # the same arithmetic
     pools, table = pages([kd, vd], 3)
-    out = hippo.hippo_verify_attention_paged(qd, *pools, table, ctx, num_splits=S)
-    assert_close(host(out), ref, "bf16", what + " paged")
+    assert torch.equal(hippo.hippo_verify_attention_paged(qd, *pools, table, ctx, num_splits=S), plain), what
 
 
 def test_static_scratch_serves_128_rows_of_128_channels(hippo):
