@@ -3,6 +3,7 @@
 // enqueued.
 #include <math.h>
 
+#include <algorithm>
 #include <atomic>
 
 #include "common.h"
@@ -43,6 +44,8 @@ int check_video(const hippo_video_desc* v) {
 }
 
 // ---- attention planning -------------------------------------------------------------------------
+constexpr size_t kStaticScratchBytes = 8u << 20;   // hippo_verify_attention_static's array
+
 struct AttnPlan {
   int R, row_chunk, n_chunks, S;
   size_t off_m, off_l, bytes;
@@ -57,16 +60,22 @@ int plan_attention(int call, const hippo_kv_desc* kv, int q_len, int n_total, in
   const bool f32 = kv->dtype == HIPPO_DTYPE_F32;
   // A block takes at most 64 rows of a 16- or 8-bit cache: more go in chunks of 64, the same slices and tiles in every
   // cache format.  The fp32 kernel takes 65 to 128 in one chunk: two chunks stream the whole cache twice and give every
-  // slice half the compute units (a call over 33K x 4 heads x 128 channels, 91 rows: 74 us in one chunk, 92 in two; two
-  // sequences x 4K x 8 heads, 80 rows: 45 and 53; 64 channels, 70K x 2 heads, 70 rows: 43 and 52).  Not where a slice
-  // per compute unit leaves units idle, which the two chunks then have to themselves (1K x 4 heads x 128, 77 rows: 16.4
-  // in one, 15.0 in two); nor where it means more than 64 slices, the most the merge takes in one step, of under eight
-  // tiles (64 channels x 2 heads, 91 rows, 4K: 14.9 in one and 128 slices, 12.9 in two; 16K: 22.0 and 21.2; 128
-  // channels x 1 head, 128 rows, 9K: 31.1 and 22.2).  Beyond 128 rows a block has no waves left for one chunk.
+  // slice half the compute units (a call over 70K x 2 heads x 64 channels, 70 rows: 43 us in one chunk, 52 in two; four
+  // sequences x 9K, 91 rows: 28.9 and 33.6).  Not where a slice per compute unit leaves units idle, which the two chunks
+  // then have to themselves (1K x 4 heads x 128, 77 rows: 16.4 in one, 15.0 in two); nor where it means more than 64
+  // slices, the most the merge takes in one step, of under eight tiles (64 channels x 2 heads, 91 rows, 4K: 14.9 in one
+  // and 128 slices, 12.9 in two; 16K: 22.0 and 21.2).  Beyond 128 rows a block has no waves left for one chunk.
   const int n_tiles = (n_total + 31) / 32;
   const long long heads = (long long)kv->batch * kv->n_kv_heads;
+  // The library's choice never takes more slices than the static array has room for (one excepted), so that the static
+  // call serves it with the same slices and hence the same bits.  A slice per compute unit of up to 124 fp32 rows of 64
+  // channels fits, of 65 rows of 128 channels does not: those go in two chunks (33K x 4 heads, 91 rows: 92 us; 95 in one
+  // chunk of as many slices as fit, 74 in one of a slice per compute unit).
+  const size_t slice_bytes = (size_t)heads * pl->R * (kv->head_dim * (f32 ? sizeof(float) : 2) + 2 * sizeof(float));
+  const long long fit = std::max<long long>(1, (long long)((kStaticScratchBytes - 3 * 256) / slice_bytes));
   const bool one_chunk = f32 && pl->R > 64 && pl->R <= 128 && n_tiles * heads > kNumCU &&
-                         (kNumCU <= 64 * heads || n_tiles * heads >= 8 * kNumCU);
+                         (kNumCU <= 64 * heads || n_tiles * heads >= 8 * kNumCU) &&
+                         (num_splits > 0 || kNumCU / heads <= fit);
   pl->row_chunk = pl->R <= 64 ? (pl->R + 15) / 16 * 16 : !one_chunk ? 64 : pl->R <= 96 ? 96 : 128;
   // short caches are bound by latency, not bytes: thin slices on many compute units win (bf16, 1896 rows, 7 query
   // rows: 59 slices of 32 rows beat 14 of 128 by 9 %)
@@ -79,7 +88,7 @@ int plan_attention(int call, const hippo_kv_desc* kv, int q_len, int n_total, in
     const long long per_split = (long long)kv->batch * kv->n_kv_heads * pl->n_chunks;
     S = (int)(kNumCU / per_split);          // rounded down: a block beyond the last compute unit would share one
     if (S < 1) S = 1;
-    if (S > n_tiles) S = n_tiles;
+    if (S > fit) S = (int)fit;
   }
   if (S > n_tiles) S = n_tiles;
   if (S < 1) S = 1;
@@ -234,7 +243,6 @@ int plan_spec(int batch, int gamma, int vocab, int dtype, SpecPlan* pl) {
 // a device until the process ends.  In host code the name `scratch` is only a handle for the runtime's
 // symbol lookup, never an address a kernel could use; the per-device address comes from
 // hipGetSymbolAddress and is what every launch receives.
-constexpr size_t kStaticScratchBytes = 8u << 20;
 static __device__ __align__(256) unsigned char scratch[kStaticScratchBytes];
 
 namespace {
@@ -457,17 +465,6 @@ int hippo_verify_attention_static(const void* q, int32_t q_len, const void* k_ca
   AttnPlan pl;
   if ((rc = plan_attention(HIPPO_CALL_VERIFY_ATTENTION, kv, q_len, ctx_len + q_len, num_splits, &pl)) != HIPPO_OK)
     return rc;
-  if (pl.bytes > kStaticScratchBytes && num_splits == 0) {
-    // slices for every compute unit do not fit the array at this many rows (256 slots of 128 rows x 128 channels in
-    // bf16, or of 64 in fp32, alone are its 8 MB): a slice per 64 (32) rows' worth of compute unit does
-    const int rows = kv->dtype == HIPPO_DTYPE_F32 ? 32 : 64;
-    const int n_tiles = (ctx_len + q_len + 31) / 32 / (kv->dtype == HIPPO_DTYPE_F32 ? 2 : 1);
-    num_splits = (int)(kNumCU / ((long long)kv->batch * kv->n_kv_heads * ((pl.R + rows - 1) / rows)));
-    if (num_splits > n_tiles) num_splits = n_tiles;
-    if (num_splits < 1) num_splits = 1;
-    if ((rc = plan_attention(HIPPO_CALL_VERIFY_ATTENTION, kv, q_len, ctx_len + q_len, num_splits, &pl)) != HIPPO_OK)
-      return rc;
-  }
   if (pl.bytes > kStaticScratchBytes) return HIPPO_ERR_STATIC_SCRATCH_LIMIT;
   void* ws = static_scratch(&rc);
   if (ws == nullptr) return rc;

@@ -520,8 +520,8 @@ __global__ __launch_bounds__(RB * TG * 64) void attn_partial_grid(AttnParams p) 
 // Bound by the matrix unit's fp32 rate (1/16 of its bf16 rate) and HBM about equally: 4 * 16 * RB * D flops
 // against 8 * D bytes per token.  The vector-ALU kernel that it replaces spent one LDS read and four shared
 // multiply-adds per pair of operands, and streamed the cache once per 32 query rows.  A verification call, us: 8K x
-// 4 heads x 128, 42 rows, a draft call beside it 88 -> 28; two sequences x 4K x 8 heads, 80 rows, paged 246 -> 47;
-// 12.7K x 8 heads, 104 rows 418 -> 74 (5.5 GFLOP: 74 TFLOP/s of a peak of 157); 64 channels, 70K x 2 heads, 49
+// 4 heads x 128, 42 rows, a draft call beside it 88 -> 28; two sequences x 4K x 8 heads, 80 rows 223 -> 53;
+// 12.7K x 8 heads, 104 rows 413 -> 74 (5.5 GFLOP: 74 TFLOP/s of a peak of 157); 64 channels, 70K x 2 heads, 49
 // rows 154 -> 36.  Its error against 64 bits is a third to a half of the former kernel's (shorter serial sums).
 // The same frame as attn_partial_grid: grid (S, H_kv, B * n_chunks), wave (rb, tg) owns 16 query rows and every
 // TG-th 16-token tile, tiles go HBM -> LDS by direct transfers into a ring of NST super-tiles, one barrier per

@@ -3,6 +3,7 @@ header declares, and rejects bad arguments with the documented status before lau
 Pointers handed over here are fake, aligned, non-null addresses -- they are never dereferenced
 because validation fails first."""
 import ctypes as C
+import itertools
 import os
 import re
 
@@ -106,6 +107,18 @@ def test_static_scratch_argument_errors(lib):
     assert h.workspace_bytes(h.CALL_VERIFY_ATTENTION, big, None, 6, 37126, 0, 64) > limit
     assert call(big, ctx=37120, splits=64) == h.ERR_STATIC_SCRATCH_LIMIT
     assert "static" in h.status_string(h.ERR_STATIC_SCRATCH_LIMIT)
+
+
+def test_static_scratch_holds_the_librarys_choice_of_slices(lib):
+    """What the library plans by itself fits the static array wherever one slice per KV head does: the static call and
+    the workspace call then take the same slices, and only what cannot be served at all is refused."""
+    limit = lib.hippo_static_scratch_bytes()
+    for dtype in (h.DTYPE_F32, h.DTYPE_BF16):
+        for batch, heads, group, d, q_len, ctx in itertools.product((1, 2, 5, 16, 70), (1, 2, 4, 8), (1, 5, 8), (64, 128),
+                                                                    (1, 8, 13, 16, 25, 64), (0, 500, 9000, 33280)):
+            kv = _kv(batch=batch, n_q_heads=heads * group, n_kv_heads=heads, head_dim=d, dtype=dtype)
+            need, one = (h.workspace_bytes(h.CALL_VERIFY_ATTENTION, kv, None, q_len, ctx + q_len, 0, s) for s in (0, 1))
+            assert 0 < need <= max(limit, one), (dtype, batch, heads, group, d, q_len, ctx)
 
 
 def test_workspace_query(lib):

@@ -57,29 +57,48 @@ def test_more_than_64_rows(hippo, shape, d):
     assert torch.equal(hippo.hippo_verify_attention_paged(qd, *pools, table, ctx, num_splits=S), plain), what
 
 
-def test_static_scratch_serves_128_rows_of_128_channels(hippo):
-    # a slice per compute unit would need more than the static array: the call takes half as many
-    q, k, v = attention_inputs(5, 1, 16, 8, 1, 128, 9000, "bf16")
-    ref, _ = oracle.attention(q, k, v, 9000, None)
-    out = hippo.hippo_verify_attention_static(dev(q, "bf16"), dev(k, "bf16"), dev(v, "bf16"), 9000)
-    assert_close(host(out), ref, "bf16", "static, 128 rows")
+@pytest.mark.parametrize("shape", [
+    # B, q_len, G, KV heads, head dim, ctx, dtype: a slice per compute unit whose partials fit the static array, ones
+    # that would exceed it in fp32 (by a little, by half), and more heads than compute units
+    (1, 16, 8, 4, 128, 9000, "bf16"), (1, 16, 8, 1, 64, 20000, "fp32"), (1, 8, 8, 1, 128, 9000, "fp32"),
+    (1, 16, 4, 2, 128, 9000, "fp32"), (1, 13, 7, 4, 128, 2100, "fp32"), (1, 16, 8, 4, 64, 2100, "fp32"),
+    (33, 4, 8, 8, 64, 40, "fp32"),
+])
+def test_static_scratch_call_takes_the_workspace_calls_slices(hippo, shape):
+    B, q_len, G, Hkv, d, ctx, dtype = shape
+    q, k, v = attention_inputs(5, B, q_len, Hkv * G, Hkv, d, ctx, dtype)
+    ref, _ = oracle.attention(q, k, v, ctx, None)
+    q, k, v = dev(q, dtype), dev(k, dtype), dev(v, dtype)
+    need = hippo.workspace_bytes(hippo.CALL_VERIFY_ATTENTION, hippo.kv_desc(k, Hkv * G), None, q_len, ctx + q_len)
+    assert need <= hippo.load().hippo_static_scratch_bytes()
+    out = hippo.hippo_verify_attention_static(q, k, v, ctx)
+    assert torch.equal(out, hippo.hippo_verify_attention(q, k, v, ctx))
+    assert_close(host(out), ref, dtype, "static %s" % (shape,))
 
 
 @pytest.mark.parametrize("d", [64, 128])
 @pytest.mark.parametrize("shape", [
-    # q_len, G, ctx, slices: one row to 128 in every row-block size and just past it, and more than one chunk;
-    # slices of part of a tile, a tile, and of more super-tiles than the ring has stages
+    # q_len, G, ctx, slices, with two sequences of two KV heads: one row to 128 in every row-block size and just past
+    # it (65 to 128 in one block where the slice count is given, or their partials fit the static array: 120 rows of 64
+    # channels; otherwise in two), and more than one chunk; slices of part of a tile, a tile, and of more super-tiles
+    # than the ring has stages
     (1, 1, 0, 0), (1, 16, 16, 0), (17, 1, 300, 0), (3, 11, 1000, 1), (7, 7, 1200, 2), (8, 8, 2500, 0), (13, 5, 4200, 0),
-    (97, 1, 4096, 3), (16, 8, 4100, 0), (13, 10, 900, 2),
+    (12, 8, 2100, 2), (97, 1, 4096, 3), (15, 8, 2100, 0), (16, 8, 4100, 0), (16, 8, 2100, 40), (13, 10, 900, 2),
 ])
 def test_fp32_attention_row_blocks(hippo, shape, d):
     q_len, G, ctx, S = shape
-    q, k, v = attention_inputs(q_len + d, 1, q_len, 2 * G, 2, d, ctx, "fp32")
+    q, k, v = attention_inputs(q_len + d, 2, q_len, 2 * G, 2, d, ctx, "fp32")
     ref, ref_lse = oracle.attention(q, k, v, ctx, None)
     qd, kd, vd = dev(q, "fp32"), dev(k, "fp32"), dev(v, "fp32")
     what = "%s d=%d" % (shape, d)
     plain, lse = hippo.hippo_verify_attention(qd, kd, vd, ctx, num_splits=S, want_lse=True)
-    assert_close(host(plain), ref, "fp32", what)
+    # A logit z that is a sum of d products in fp32 is off by some |z| sqrt(d/3) 2^-24 / sqrt(3) / sqrt(2) (random walk
+    # in two chains of growing partial sums): 1.9e-6 for the largest here, z = 12 at d = 128, and so is the weight of the
+    # token it may leave alone to decide a row.  Twice that of sum_n p_n |v_n| is allowed where it is more than the fp32
+    # bound, which a row of cancelling values can miss (the largest seen: 2.0e-6 of that sum).
+    spread, _ = oracle.attention(q, k, np.abs(v), ctx, None)
+    err = np.abs(host(plain) - ref)
+    assert (err <= np.maximum(1e-5 * np.maximum(np.abs(ref), np.sqrt(np.mean(ref ** 2))), 2.0 ** -18 * spread)).all(), what
     np.testing.assert_allclose(host(lse), ref_lse, rtol=2e-5, atol=2e-5, err_msg=what)
     k2, v2 = kd.clone(), vd.clone()
     k2[:, :, ctx:] = 7.0
@@ -90,17 +109,9 @@ def test_fp32_attention_row_blocks(hippo, shape, d):
     pools, table = pages([kd, vd], 3)
     assert torch.equal(hippo.hippo_verify_attention_paged(qd, *pools, table, ctx, num_splits=S), plain), what
     # rows of a wider buffer: any 16-byte-aligned row stride
-    wide = [torch.zeros((1, 2, ctx + q_len, d + 12), device="cuda") for _ in range(2)]
+    wide = [torch.zeros((2, 2, ctx + q_len, d + 12), device="cuda") for _ in range(2)]
     views = [w[..., :d].copy_(x) for w, x in zip(wide, (kd, vd))]
     assert torch.equal(hippo.hippo_verify_attention(qd, *views, ctx, num_splits=S), plain), what
-
-
-@pytest.mark.parametrize("q_len", [8, 16])
-def test_static_scratch_serves_what_half_the_slices_fit(hippo, q_len):
-    q, k, v = attention_inputs(5, 1, q_len, 8, 1, 128, 9000, "fp32")
-    ref, _ = oracle.attention(q, k, v, 9000, None)
-    out = hippo.hippo_verify_attention_static(dev(q, "fp32"), dev(k, "fp32"), dev(v, "fp32"), 9000)
-    assert_close(host(out), ref, "fp32", "static, %d rows" % (8 * q_len))
 
 
 def score_inputs(seed, B, L, H, Hkv, d, n, dtype, scale=2.0):
