@@ -1111,8 +1111,9 @@ __device__ __forceinline__ void emb_run32_body(const ScoreParams& p, EmbRunSmem<
     const float ia = sm.inv_norm[a];
     float var = 0.f;
     if (own_frame) {
-      const float cs0 = c0 < M ? sm.G[a][c0] * (ia * sm.inv_norm[c0]) : 0.f;
-      const float cs1 = c0 + 1 < M ? sm.G[a][c0 + 1] * (ia * sm.inv_norm[c0 + 1]) : 0.f;
+      // (from left to right: the two reciprocal norms alone can exceed fp32's range)
+      const float cs0 = c0 < M ? sm.G[a][c0] * ia * sm.inv_norm[c0] : 0.f;
+      const float cs1 = c0 + 1 < M ? sm.G[a][c0 + 1] * ia * sm.inv_norm[c0 + 1] : 0.f;
       const float mu = row16_sum(cs0 + cs1) * inv_M;
       const float d0 = c0 < M ? cs0 - mu : 0.f, d1 = c0 + 1 < M ? cs1 - mu : 0.f;
       var = row16_sum(fmaf(d0, d0, d1 * d1)) * inv_M;

@@ -166,6 +166,26 @@ def test_embedding_terms_over_passes_of_channels(hippo, shape, dtype):
         np.testing.assert_allclose(host(comps)[2], ss, rtol=0, atol=(2e-6 if dtype == "fp32" else 2e-3) * ss.max() + 1e-9)
 
 
+@pytest.mark.parametrize("dtype", ["fp32", "bf16"])
+@pytest.mark.parametrize("ch", [64, 520])
+def test_rows_of_denormal_squared_norm(hippo, ch, dtype):
+    # entries of 0 and +-2^-70: squared norms are denormal and, like all dot products of such rows, exact
+    r = np.random.default_rng(ch)
+    emb = r.standard_normal((1, 4, 6, 7, ch))
+    emb[0, 0, 1, 2] = r.integers(-1, 2, ch) * 2.0 ** -70              # alone in its crop
+    for at in ((2, 1, 2), (2, 1, 3), (3, 1, 2)):                      # two in a crop, and one a frame on
+        emb[(0,) + at] = r.integers(-1, 2, ch) * 2.0 ** -70
+    emb = prep(emb.reshape(1, 4 * 42, ch), dtype)
+    q, k = score_inputs(1, 1, 3, 2, 1, 64, 4 * 42, dtype)
+    st, ss = oracle.s_temp(emb, 4), oracle.s_spa(emb, 4, 6, 7)
+    for flags in (7, 6):
+        scores, comps = hippo.hippo_score_tokens(dev(q, dtype), dev(k, dtype), hippo.video_desc(4, 6, 7, 0),
+                                                 emb=dev(emb, dtype), flags=flags, want_components=True)
+        assert_close(host(comps)[1], st, dtype, "s_temp")
+        np.testing.assert_allclose(host(comps)[2], ss, rtol=0, atol=(2e-6 if dtype == "fp32" else 2e-3) * ss.max())
+        assert np.isfinite(host(scores)).all()
+
+
 def test_wide_keys_as_embedding(hippo):
     # 8 KV heads x 128 channels: the keys of all heads side by side, 1024 channels in two passes
     for dtype in ("fp32", "bf16"):
