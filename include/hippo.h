@@ -118,7 +118,7 @@ size_t hippo_workspace_bytes(int32_t call, const hippo_kv_desc* kv, const hippo_
  *   s_spa[j]  = population variance over the tokens k of j's crop of cos(emb_j, emb_k)    (Eq. 5-6)
  *   scores[j] = sum over enabled terms of (s - mean_f) / std_f, statistics per frame, population
  *               std, a term with std_f = 0 contributes 0                                   (Eq. 7)
- * A zero-norm embedding has cosine 0 with everything.
+ * An embedding without a positive norm (of zeros, or with a NaN) has cosine 0 with everything.
  *
  * q_txt   [B, l_txt, H, d] contiguous, dtype kv->dtype: the text-prompt queries.
  * k_cache the cache whose keys guide pruning; rows [vis_offset, vis_offset + N_v) are read.

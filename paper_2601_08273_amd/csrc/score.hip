@@ -971,16 +971,19 @@ __device__ __forceinline__ void emb_run32_body(const ScoreParams& p, EmbRunSmem<
   auto operand = [&](int rbk, int u) -> u32x4 {
     return *(const u32x4*)(strip + (rbk * 16 + j) * (64 * U) + (((4 * u + g) ^ (j & (PPR - 1))) * 16));
   };
-  // 1 / sqrt(x), 0 for a zero-norm row.  bf16: by the hardware's reciprocal square root (1 ulp), which ignores
-  // denormals: tiny arguments are scaled by 2^64 first, the result by 2^32.  (The riding
-  // blocks compete with the sweep for vector-instruction issue and nothing else, so what the crop's
-  // closing arithmetic costs in instructions is what the embedding terms cost the launch.)
+  // 1 / sqrt(x), or -1 for a row without a positive norm (of zeros, or with a NaN), whose cosines are 0.  bf16: by the
+  // hardware's reciprocal square root (1 ulp), which ignores denormals: tiny arguments are scaled by 2^64 first, the
+  // result by 2^32.  (The riding blocks compete with the sweep for vector-instruction issue and nothing else, so what
+  // the crop's closing arithmetic costs in instructions is what the embedding terms cost the launch.)
   auto inv_sqrt = [](float x) -> float {
-    if constexpr (F32) return x > 0.f ? 1.f / sqrtf(x) : 0.f;
+    if constexpr (F32) return x > 0.f ? 1.f / sqrtf(x) : -1.f;
     const bool tiny = x < 0x1p-60f;
     const float r = __builtin_amdgcn_rsqf(tiny ? x * 0x1p64f : x);
-    return x > 0.f ? (tiny ? r * 0x1p32f : r) : 0.f;
+    return x > 0.f ? (tiny ? r * 0x1p32f : r) : -1.f;
   };
+  // dot product and both reciprocal norms -> cosine (from left to right: the norms' product can exceed fp32's range;
+  // the dot product is what is replaced, so that the last product still fuses with the sum that it goes into)
+  auto cosine = [](float dot, float ia, float ib) { return (fminf(ia, ib) < 0.f ? 0.f : dot) * ia * ib; };
   const float inv_M = 1.f / (float)M;
 
   // state of the tokens' temporal term, kept by lane 0 of each 16-lane row (token a = tid / 16):
@@ -1111,9 +1114,8 @@ __device__ __forceinline__ void emb_run32_body(const ScoreParams& p, EmbRunSmem<
     const float ia = sm.inv_norm[a];
     float var = 0.f;
     if (own_frame) {
-      // (from left to right: the two reciprocal norms alone can exceed fp32's range)
-      const float cs0 = c0 < M ? sm.G[a][c0] * ia * sm.inv_norm[c0] : 0.f;
-      const float cs1 = c0 + 1 < M ? sm.G[a][c0 + 1] * ia * sm.inv_norm[c0 + 1] : 0.f;
+      const float cs0 = c0 < M ? cosine(sm.G[a][c0], ia, sm.inv_norm[c0]) : 0.f;
+      const float cs1 = c0 + 1 < M ? cosine(sm.G[a][c0 + 1], ia, sm.inv_norm[c0 + 1]) : 0.f;
       const float mu = row16_sum(cs0 + cs1) * inv_M;
       const float d0 = c0 < M ? cs0 - mu : 0.f, d1 = c0 + 1 < M ? cs1 - mu : 0.f;
       var = row16_sum(fmaf(d0, d0, d1 * d1)) * inv_M;
@@ -1123,7 +1125,7 @@ __device__ __forceinline__ void emb_run32_body(const ScoreParams& p, EmbRunSmem<
       if (own_frame) p.s_spa[out_base + (long long)fr * p.P] = var;
       // Eq. 3-4 of the frame before, whose two neighbours are known now
       if (fr > lo && fr - 1 >= f0) {
-        const float next = dcur * inv_n1 * ia, before = dot1 * inv_n1 * inv_n2;
+        const float next = cosine(dcur, inv_n1, ia), before = cosine(dot1, inv_n1, inv_n2);
         p.s_temp[out_base + (long long)(fr - 1) * p.P] = 1.f - (fr - 1 > 0 ? 0.5f * (next + before) : next);
       }
       inv_n2 = inv_n1;
@@ -1133,7 +1135,7 @@ __device__ __forceinline__ void emb_run32_body(const ScoreParams& p, EmbRunSmem<
   }
   // a run that reaches the video's last frame: that frame has no successor
   if ((tid & 15) == 0 && a < M && hi < f_end)
-    p.s_temp[out_base + (long long)hi * p.P] = 1.f - (hi > 0 ? dot1 * inv_n1 * inv_n2 : 0.f);
+    p.s_temp[out_base + (long long)hi * p.P] = 1.f - (hi > 0 ? cosine(dot1, inv_n1, inv_n2) : 0.f);
 }
 
 // block number -> (crop position, run of frames, batch element), positions fastest

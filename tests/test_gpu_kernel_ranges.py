@@ -186,6 +186,25 @@ def test_rows_of_denormal_squared_norm(hippo, ch, dtype):
         assert np.isfinite(host(scores)).all()
 
 
+@pytest.mark.parametrize("dtype", ["fp32", "bf16"])
+@pytest.mark.parametrize("ch, crop", [(64, 5), (520, 5), (64, 6), (64, 8)])      # one pass, two; crops above 32 tokens
+def test_rows_with_a_nan_have_cosine_zero(hippo, ch, crop, dtype):
+    emb = prep(np.random.default_rng(ch).standard_normal((1, 4 * 63, ch)), dtype)
+    rows = [2 * 63 + 9 + 2, 3 * 63 + 62]                              # inside a crop; the last token of the last frame
+    zeroed = emb.copy()
+    zeroed[0, rows] = 0.0
+    emb[0, rows[0], 3] = np.nan
+    emb[0, rows[1], ch - 1] = np.nan
+    q, k = score_inputs(1, 1, 3, 2, 1, 64, 4 * 63, dtype)
+    st, ss = oracle.s_temp(zeroed, 4), oracle.s_spa(zeroed, 4, 7, 9, crop, crop)
+    for flags in (7, 6):
+        scores, comps = hippo.hippo_score_tokens(dev(q, dtype), dev(k, dtype), hippo.video_desc(4, 7, 9, 0, crop, crop),
+                                                 emb=dev(emb, dtype), flags=flags, want_components=True)
+        assert_close(host(comps)[1], st, dtype, "s_temp")
+        np.testing.assert_allclose(host(comps)[2], ss, rtol=0, atol=(2e-6 if dtype == "fp32" else 2e-3) * ss.max())
+        assert np.isfinite(host(scores)).all()
+
+
 def test_wide_keys_as_embedding(hippo):
     # 8 KV heads x 128 channels: the keys of all heads side by side, 1024 channels in two passes
     for dtype in ("fp32", "bf16"):
