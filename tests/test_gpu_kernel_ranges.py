@@ -234,6 +234,20 @@ def test_attention_mass_over_the_exponent_range(hippo, scale, shift, d):
     assert_close(got, oracle.s_attn(q, k, 2, 3 * 11 * 13), "bf16", "scale %g shift %g d=%d" % (scale, shift, d))
 
 
+@pytest.mark.parametrize("shift", [0.0, 6.0, 24.0, 64.0, -24.0])
+def test_attention_mass_keeps_its_precision_at_large_logits(hippo, shift):
+    # Logits around `shift`.  A row's normaliser is rounded to fp32 at its own magnitude, at 64..128 powers of two by up
+    # to 2^-18, 2.6e-6 of the row's weights, to either side: over 448 rows that averages out to less than a tenth.  A
+    # logarithm with a bias would show whole in the column sums (2.6e-6 here), as the bound of 2^-20 must not allow.
+    q, k = score_inputs(11, 1, 64, 14, 2, 128, 2048, "bf16", 1.0)
+    q[..., 0] = np.sqrt(128)
+    k[..., 0] = shift
+    q, k = prep(q, "bf16"), prep(k, "bf16")
+    ref = oracle.s_attn(q, k, 0, 2048)
+    got = attention_mass(hippo, q, k, "bf16", 8, 16, 16, 0)
+    assert np.linalg.norm(got - ref) <= 2.0 ** -20 * np.linalg.norm(ref)
+
+
 @pytest.mark.parametrize("dtype", ["fp32", "bf16"])
 @pytest.mark.parametrize("rows, d", [(1, 64), (2047, 128), (2049, 128), (70001, 64)])
 def test_codes_over_the_exponent_range(hippo, dtype, rows, d):
