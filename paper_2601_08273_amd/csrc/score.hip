@@ -201,6 +201,7 @@ constexpr int kSaWaves = 8;           // waves per block, 32 tokens each: two wa
 // that exceeded 1e-7.  From 2^-90 to 2^90, where nothing overflows either, it was up to 1.3 times for spread logits of
 // more than 20 powers of two, and up to 4 times for rows that one token decides.
 constexpr float kPlainMin = 0x1p-12f, kPlainMax = 0x1p14f;
+constexpr float kPlainSlack = 0x1p-6f;   // how far outside a wave's last plain sums may lie
 
 template <int D, int PASS>
 struct SattnSmem {
@@ -351,6 +352,7 @@ __device__ __forceinline__ void sattn_mfma_body(const ScoreParams& p, SattnSmem<
       }
     }
   }
+  bool plain = PASS == 1;                     // (wave-uniform)
   for (int r0 = row_begin; r0 < row_end; r0 += RCH, buf ^= 1) {
     wait_vmcnt<0>();                          // this wave's share of the chunk (and its normalisers) has arrived
     if (PASS == 2 && tid < RCH) sm.lse_s[buf][tid] = lse_reg;
@@ -419,37 +421,45 @@ __device__ __forceinline__ void sattn_mfma_body(const ScoreParams& p, SattnSmem<
       // rows (lane (j, g) ends with row 16g + j of the chunk), 3.4 vector instructions per logit against 6.25 with
       // a maximum per 16 rows (scoring calls, us: 16384 tokens 51.6 -> 48.4, four layers of 32768 tokens 567 -> 512, 4 x
       // 36864 tokens of 64 heads 819 -> 760).  As long as every row's sum over the wave's tokens stays within kPlainMin ..
-      // kPlainMax; otherwise the wave goes over the chunk again with the maximum as the reference.
+      // kPlainMax.  From the first chunk on where one does not, the wave takes the maximum as the reference (and goes over
+      // that chunk again, if it is far outside): large logits come in whole heads.  Calls over 16384 and 4 x 36864 tokens,
+      // us, against the maximum alone: all logits 150 higher 56.4 and 856 (53.5 and 860; trying every chunk both ways 69
+      // and 1088); spread three times as wide 52.1 and 838 (52.1 and 896), five times 54.4 and 885 (52.1 and 899).
       static_assert(RCH == 64, "four row blocks, one per lane group");
-      float pair[2];
+      bool done = false;
+      if (plain) {
+        float pair[2];
 #pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        float ps[2];
+        for (int h = 0; h < 2; ++h) {
+          float ps[2];
 #pragma unroll
-        for (int r2 = 0; r2 < 2; ++r2) {
-          f32x4 z[TBW];
-          products(2 * h + r2, z);
-          mask_tokens(z);
-          float t[TBW];
+          for (int r2 = 0; r2 < 2; ++r2) {
+            f32x4 z[TBW];
+            products(2 * h + r2, z);
+            mask_tokens(z);
+            float t[TBW];
 #pragma unroll
-          for (int tb = 0; tb < TBW; ++tb)
-            t[tb] = (fast_exp2(z[tb][0] * scale_log2) + fast_exp2(z[tb][1] * scale_log2)) +
-                    (fast_exp2(z[tb][2] * scale_log2) + fast_exp2(z[tb][3] * scale_log2));
-          ps[r2] = t[0];
+            for (int tb = 0; tb < TBW; ++tb)
+              t[tb] = (fast_exp2(z[tb][0] * scale_log2) + fast_exp2(z[tb][1] * scale_log2)) +
+                      (fast_exp2(z[tb][2] * scale_log2) + fast_exp2(z[tb][3] * scale_log2));
+            ps[r2] = t[0];
 #pragma unroll
-          for (int tb = 1; tb < TBW; ++tb) ps[r2] += t[tb];
+            for (int tb = 1; tb < TBW; ++tb) ps[r2] += t[tb];
+          }
+          pair[h] = rows_sum_swap16(ps[0], ps[1]);
+          __builtin_amdgcn_sched_barrier(0);     // two row blocks at a time: more in flight spills
         }
-        pair[h] = rows_sum_swap16(ps[0], ps[1]);
-        __builtin_amdgcn_sched_barrier(0);     // two row blocks at a time: more in flight spills
+        const float tot = rows_sum_swap32(pair[0], pair[1]);        // (the comparisons are false for NaN)
+        plain = __all((tot >= kPlainMin && tot <= kPlainMax) || !wave_has_tokens);
+        done = plain || __all((tot >= kPlainMin * kPlainSlack && tot <= kPlainMax / kPlainSlack) || !wave_has_tokens);
+        if (done) {
+          const int at = ((r0 - row_begin) % RDEF) + lane;
+          wm_s[wave][at] = wave_has_tokens ? 0.f : -INFINITY;
+          wl_s[wave][at] = tot;
+        }
       }
-      const float tot = rows_sum_swap32(pair[0], pair[1]);
-      const bool good = (tot >= kPlainMin && tot <= kPlainMax) || !wave_has_tokens;    // (false for NaN)
-      const int at = ((r0 - row_begin) % RDEF) + lane;
-      if (__all(good)) {
-        wm_s[wave][at] = wave_has_tokens ? 0.f : -INFINITY;
-        wl_s[wave][at] = tot;
-      } else {
-#pragma unroll 1
+      if (!done) {
+#pragma unroll
         for (int rb = 0; rb < RCH / 16; ++rb) {
           f32x4 z[TBW];
           products(rb, z);

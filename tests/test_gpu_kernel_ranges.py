@@ -221,7 +221,7 @@ def test_wide_keys_as_embedding(hippo):
 @pytest.mark.parametrize("scale, shift", [
     # logits that fit fp32's exponent range as they are; rows whose exponentials overflow, underflow to denormals or
     # to zero without a reference; both kinds of rows and of 32-token tiles in one call
-    (3.0, 0.0), (40.0, 0.0), (1.0, 150.0), (1.0, -80.0), (1.0, -150.0), (120.0, 0.0),
+    (0.5, 0.0), (3.0, 0.0), (40.0, 0.0), (1.0, 150.0), (1.0, -80.0), (1.0, -150.0), (120.0, 0.0),
 ])
 def test_attention_mass_over_the_exponent_range(hippo, scale, shift, d):
     q, k = score_inputs(7, 2, 21, 14, 2, d, 3 * 11 * 13 + 5, "bf16", scale)
@@ -246,6 +246,20 @@ def test_attention_mass_keeps_its_precision_at_large_logits(hippo, shift):
     ref = oracle.s_attn(q, k, 0, 2048)
     got = attention_mass(hippo, q, k, "bf16", 8, 16, 16, 0)
     assert np.linalg.norm(got - ref) <= 2.0 ** -20 * np.linalg.norm(ref)
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("first, last", [(0, 1), (8, 12), (14, 15), (39, 40)])
+def test_attention_mass_where_some_rows_leave_the_exponent_range(hippo, first, last, d):
+    # 560 query rows in blocks of three 64-row chunks: large logits in a block's first chunk, a later one or its last, and
+    # in no chunk of the other blocks; a video whose last wave has one token
+    q, k = score_inputs(8, 1, 40, 28, 2, d, 257 + 5, "bf16", 0.5)
+    q[..., 0] = 0.0
+    q[:, first:last, :, 0] = np.sqrt(d)
+    k[..., 0] = 120.0 + np.arange(k.shape[2]) % 7
+    q, k = prep(q, "bf16"), prep(k, "bf16")
+    got = attention_mass(hippo, q, k, "bf16", 1, 1, 257, 2)
+    assert_close(got, oracle.s_attn(q, k, 2, 257), "bf16", "rows %d to %d d=%d" % (first, last, d))
 
 
 @pytest.mark.parametrize("dtype", ["fp32", "bf16"])
