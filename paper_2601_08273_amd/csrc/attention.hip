@@ -38,7 +38,6 @@ __device__ __forceinline__ void append_new_rows(const AttnParams& p, int b, int 
 // =================================================================================================
 // MFMA partial kernel (bf16): helpers
 // =================================================================================================
-constexpr int kMfmaTile = 32;         // tokens per tile the host-side split heuristic counts in
 constexpr float kRescaleGap = 8.f;    // log2 units, see the lazy rescale in the kernel
 
 typedef __attribute__((ext_vector_type(4))) short s16x4;

@@ -8,7 +8,6 @@
 
 namespace hippo {
 
-constexpr int kWave = 64;          // CDNA wavefront
 constexpr int kNumCU = 256;        // MI355X compute units (8 XCDs x 32)
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kLn2 = 0.6931471805599453f;
@@ -139,17 +138,6 @@ __device__ __forceinline__ float rows_sum_swap32(float ab, float cd) {
   return __uint_as_float(s[0]) + __uint_as_float(s[1]);
 }
 
-// over each half of the wavefront (lanes 0-31, lanes 32-63), result in all its lanes
-__device__ __forceinline__ float half32_max(float v) {
-  v = row16_max(v);
-  auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-  return max_nan(__uint_as_float(a[0]), __uint_as_float(a[1]));
-}
-__device__ __forceinline__ float half32_sum(float v) {
-  v = row16_sum(v);
-  auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-  return __uint_as_float(a[0]) + __uint_as_float(a[1]);
-}
 // exact integer reduction (op associative and commutative: min, max, or, ...) over all 64 lanes
 template <typename Op>
 __device__ __forceinline__ int wave_reduce_i32(int v, Op op) {

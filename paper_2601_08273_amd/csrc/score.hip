@@ -419,12 +419,13 @@ __device__ __forceinline__ void sattn_mfma_body(const ScoreParams& p, SattnSmem<
     } else {
       // Without a reference: exp2 of the logits as they are, and one transposing sum across the lane groups per 64
       // rows (lane (j, g) ends with row 16g + j of the chunk), 3.4 vector instructions per logit against 6.25 with
-      // a maximum per 16 rows (scoring calls, us: 16384 tokens 51.6 -> 48.4, four layers of 32768 tokens 567 -> 512, 4 x
-      // 36864 tokens of 64 heads 819 -> 760).  As long as every row's sum over the wave's tokens stays within kPlainMin ..
-      // kPlainMax.  From the first chunk on where one does not, the wave takes the maximum as the reference (and goes over
-      // that chunk again, if it is far outside): large logits come in whole heads.  Calls over 16384 and 4 x 36864 tokens,
-      // us, against the maximum alone: all logits 150 higher 56.4 and 856 (53.5 and 860; trying every chunk both ways 69
-      // and 1088); spread three times as wide 52.1 and 838 (52.1 and 896), five times 54.4 and 885 (52.1 and 899).
+      // a maximum per 16 rows (scoring calls, us: 16384 tokens 51.6 -> 48.4, four layers of 32768 tokens 567 -> 512,
+      // 4 x 36864 tokens of 64 heads 819 -> 760).  As long as every row's sum over the wave's tokens stays within
+      // kPlainMin .. kPlainMax.  From the first chunk on where one does not, the wave takes the maximum as the reference
+      // (and goes over that chunk again, if it is far outside): large logits come in whole heads.  Calls over 16384 and
+      // 4 x 36864 tokens, us, against the maximum alone: all logits 150 higher 56.4 and 856 (53.5 and 860; trying every
+      // chunk both ways 69 and 1088); spread three times as wide 52.1 and 838 (52.1 and 896), five times 54.4 and 885
+      // (52.1 and 899).
       static_assert(RCH == 64, "four row blocks, one per lane group");
       bool done = false;
       if (plain) {
@@ -553,7 +554,8 @@ __global__ __launch_bounds__(256) void sattn_row_lse(ScoreParams p) {
     // log2 by exponent and significand in [1, 2): the hardware's logarithm of the whole sum, up to 2^100 where no
     // maximum was taken out, is rounded towards one side at its own magnitude, for all rows alike, and the column sums
     // would keep the bias (their error against 64 bits at logits around 2 powers of two 3.3e-7, 0.6e-7 like this)
-    p.row_lse[row] = mx + ((float)(__builtin_amdgcn_frexp_expf(tot) - 1) + __log2f(2.f * __builtin_amdgcn_frexp_mantf(tot)));
+    const float exponent = (float)(__builtin_amdgcn_frexp_expf(tot) - 1);
+    p.row_lse[row] = mx + (exponent + __log2f(2.f * __builtin_amdgcn_frexp_mantf(tot)));
   }
 }
 
@@ -590,12 +592,11 @@ __global__ __launch_bounds__(256) void sattn_finalize(ScoreParams p) {
 }
 
 // =================================================================================================
-// s_temp and s_spa: one block per (crop, frame, batch element)
+// s_temp and s_spa, fp32 crops above 32 tokens: one block per (crop, frame, batch element)
 // =================================================================================================
 constexpr int kEmbChunk = 64;     // channels per LDS pass
 constexpr int kMaxCrop = 64;      // tokens per crop
 
-template <typename T>
 __global__ __launch_bounds__(256) void emb_scores(ScoreParams p) {
   // E: this frame, previous frame, next frame.  G (the finished Gram matrix) reuses E's storage
   // once the channel sweep is over.
@@ -624,32 +625,32 @@ __global__ __launch_bounds__(256) void emb_scores(ScoreParams p) {
   float tacc = 0.f;                                  // threads [0,4*64): quantity tid/64 of token tid%64
   __syncthreads();
 
-  constexpr int VPC = kEmbChunk / Elem<T>::kPerVec;  // vectors per chunk row
+  constexpr int kVec = Elem<float>::kPerVec, VPC = kEmbChunk / kVec;  // vectors per chunk row
   for (int c0 = 0; c0 < de; c0 += kEmbChunk) {
     // ---- stage chunk [c0, c0+64) of the 3*M vectors ----
     for (int e = tid; e < 3 * M * VPC; e += 256) {
       const int which = e / (M * VPC), rem = e % (M * VPC);
       const int t = rem / VPC, vec = rem % VPC;
-      const int c = c0 + vec * Elem<T>::kPerVec;
-      float vals[Elem<T>::kPerVec];
+      const int c = c0 + vec * kVec;
+      float vals[kVec];
 #pragma unroll
-      for (int u = 0; u < Elem<T>::kPerVec; ++u) vals[u] = 0.f;
+      for (int u = 0; u < kVec; ++u) vals[u] = 0.f;
       const bool present = (which == 0) || (which == 1 && has_prev) || (which == 2 && has_next);
       if (present && c < de) {
         const long long tokn = tok_s[t] + (which == 1 ? -p.P : (which == 2 ? p.P : 0));
-        const T* src;
+        const float* src;
         if (p.emb) {
-          src = (const T*)p.emb + (long long)b * p.emb_stride_b + tokn * p.emb_stride_tok + c;
+          src = (const float*)p.emb + (long long)b * p.emb_stride_b + tokn * p.emb_stride_tok + c;
         } else {
           const int hk = c / p.D, cc = c % p.D;
-          src = (const T*)p.k_cache + (long long)b * p.sb + (long long)hk * p.sh +
+          src = (const float*)p.k_cache + (long long)b * p.sb + (long long)hk * p.sh +
                 (p.vis_off + tokn) * p.sn + cc;
         }
         const u32x4 v4 = *(const u32x4*)src;
-        Elem<T>::unpack(v4, vals);
+        Elem<float>::unpack(v4, vals);
       }
 #pragma unroll
-      for (int u = 0; u < Elem<T>::kPerVec; ++u) E[which][t][vec * Elem<T>::kPerVec + u] = vals[u];
+      for (int u = 0; u < kVec; ++u) E[which][t][vec * kVec + u] = vals[u];
     }
     __syncthreads();
     // ---- Gram of the crop ----
@@ -725,7 +726,8 @@ __global__ __launch_bounds__(256) void emb_scores(ScoreParams p) {
 }
 
 // =================================================================================================
-// s_temp and s_spa on MFMA (bf16): one block per (crop, frame, batch element), RBC*16 >= crop size.
+// s_temp and s_spa on MFMA, bf16 crops above 32 tokens: one block per (crop, frame, batch element), RBC*16 >= crop
+// size.
 // The crop's Gram matrix E E^T and the temporal products (E_f E_{f-1}^T, E_{f-1} E_{f-1}^T and the
 // same for f+1, of which only the diagonals are used) are 16x16 output blocks of one and the same
 // operand: a lane's A operand for row block rb -- token rb*16 + lane%16, 8 consecutive channels --
@@ -1471,7 +1473,7 @@ hipError_t launch_score(const ScoreParams& p_in, hipStream_t st) {
       else if (wide) hipLaunchKernelGGL((emb_scores_run32<true, true>), runs, dim3(512), 0, st, p);
       else hipLaunchKernelGGL((emb_scores_run32<true, false>), runs, dim3(512), 0, st, p);
     } else if (!bf16) {
-      hipLaunchKernelGGL(emb_scores<float>, grid, dim3(256), 0, st, p);
+      hipLaunchKernelGGL(emb_scores, grid, dim3(256), 0, st, p);
     } else if (p.ch * p.cw <= 48) {
       hipLaunchKernelGGL(emb_scores_mfma<3>, grid, dim3(256), 0, st, p);
     } else {

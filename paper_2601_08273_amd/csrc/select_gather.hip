@@ -12,7 +12,11 @@ namespace hippo {
 
 constexpr int kSelThreads = 1024;
 constexpr int kSelWaves = kSelThreads / 64;
-constexpr int kKeysPerThread = 72;       // keys held in registers: sequences up to 73728 tokens
+// Keys a thread holds: sequences up to 73728 tokens, the longest that the configurations span (128 frames of 24 x 24).
+// Beyond 40 keys a thread's 128 registers do not hold them all (56 keys: 11 spilled, 72: 47, in private memory), which
+// still beats fetching the scores anew in every pass (us: 48000 tokens 25 against 66, 73728 tokens 35 against 98).
+// Longer sequences take the re-reading kernel unchanged (73729 tokens 100, 98304 130; 96 keys a thread would take 48).
+constexpr int kKeysPerThread = 72;
 constexpr int kPackedCounts = 40;        // keys per thread up to which two counts of a block fit 16 bits each
 constexpr int kBins = 4096;              // 12-bit digits (the last pass uses 256 of them)
 constexpr int kHistStride = kBins + kBins / 64;   // padded histogram
@@ -240,9 +244,9 @@ __global__ __launch_bounds__(kSelThreads) void topk_select(SelectParams p) {
   // ---- compaction in index order ----
   __syncthreads();
   if (CACHED) {
-    // counts of keys above / equal to the threshold, packed (a wave's both fit 16 bits, a block's up to 40960 keys).  Index order inside a wave is (group of VW slots, lane, slot in the group):
-    // one wave scan per group, a running total over the groups, then the totals of the waves in
-    // front; every thread then writes its own survivors.
+    // counts of keys above / equal to the threshold, packed (a wave's both fit 16 bits, a block's up to 40960 keys).
+    // Index order inside a wave is (group of VW slots, lane, slot in the group): one wave scan per group, a running total
+    // over the groups, then the totals of the waves in front; every thread then writes its own survivors.
     unsigned excl[NV], run = 0;
 #pragma unroll
     for (int v = 0; v < NV; ++v) {
@@ -340,7 +344,7 @@ hipError_t launch_select_gather(const SelectParams& p, hipStream_t st) {
   else if (n_chunks <= 24) HIPPO_TOPK(24);
   else if (n_chunks <= 32) HIPPO_TOPK(32);
   else if (n_chunks <= 40) HIPPO_TOPK(40);
-  else if (n_chunks <= 56) HIPPO_TOPK(56);       // (select calls, us, against keys re-read: 4 x 48K tokens 108, 145; 70K 38, 99)
+  else if (n_chunks <= 56) HIPPO_TOPK(56);
   else if (n_chunks <= kKeysPerThread) HIPPO_TOPK(kKeysPerThread);
   else HIPPO_TOPK(0);
 #undef HIPPO_TOPK
