@@ -698,8 +698,13 @@ __global__ __launch_bounds__(RB * TG * 64) void attn_partial_f32(AttnParams p) {
     }
     const float neg_m = (m_run == -INFINITY) ? 0.f : -m_run;
     float pr[4];
+    {
+      // product and sum rounded one by one, as the reference's own product is: a fused sum would leave the product's
+      // rounding error, beyond any exponent for logits of 1e9 and more
+#pragma clang fp contract(off)
 #pragma unroll
-    for (int e = 0; e < 4; ++e) pr[e] = fast_exp2(fmaf(sv[e], p.scale_log2, neg_m));
+      for (int e = 0; e < 4; ++e) pr[e] = fast_exp2(sv[e] * p.scale_log2 + neg_m);
+    }
     l_run += (pr[0] + pr[1]) + (pr[2] + pr[3]);        // per-lane share; groups g meet at the end
 #pragma unroll
     for (int e = 0; e < 4; ++e) {

@@ -154,19 +154,25 @@ __global__ __launch_bounds__(256, 2) void sattn_f32(ScoreParams p) {
         const float mx = rows4_max(max_nan_of(zv)) * scale_log2;
         const float neg_m = (mx == -INFINITY) ? 0.f : -mx;
         float ps = 0.f;
+        {
+          // (product and sum rounded one by one here and in pass 2, as the reference's own product is: a fused sum would
+          // leave the product's rounding error, beyond any exponent for logits of 1e9 and more)
+#pragma clang fp contract(off)
 #pragma unroll
-        for (int e = 0; e < TBW * 4; ++e) ps += fast_exp2(fmaf(zv[e], scale_log2, neg_m));
+          for (int e = 0; e < TBW * 4; ++e) ps += fast_exp2(zv[e] * scale_log2 + neg_m);
+        }
         ps = rows4_sum(ps);
         if (g == 0) {
           wm_s[buf][wave][rb * 16 + j] = mx;
           wl_s[buf][wave][rb * 16 + j] = ps;
         }
       } else {
+#pragma clang fp contract(off)
         const float lse = lse_s[buf][rb * 16 + j];
 #pragma unroll
         for (int tb = 0; tb < TBW; ++tb)
 #pragma unroll
-          for (int e = 0; e < 4; ++e) col[tb][e] += fast_exp2(fmaf(z[tb][e], scale_log2, -lse));
+          for (int e = 0; e < 4; ++e) col[tb][e] += fast_exp2(z[tb][e] * scale_log2 - lse);
       }
     }
   }

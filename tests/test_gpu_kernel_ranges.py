@@ -114,6 +114,27 @@ def test_fp32_attention_row_blocks(hippo, shape, d):
     assert torch.equal(hippo.hippo_verify_attention(qd, *views, ctx, num_splits=S), plain), what
 
 
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("size", [1e9, 1e20, 3e37])
+def test_fp32_logits_of_any_finite_size(hippo, size, d):
+    # one token's key decides every row, for it or against it; then all tokens' logits are huge and alike (the attention
+    # mass, whose normaliser is one fp32 number of that size, cannot hold their count beside it)
+    q, k, v = attention_inputs(d, 2, 5, 14, 2, d, 700, "fp32")
+    q[..., 3] = np.where(np.abs(q[..., 3]) < 0.5, 0.5, q[..., 3]).clip(-3, 3)
+    k[:, :, 300, 3] = size
+    ref, _ = oracle.attention(q, k, v, 700, None)
+    assert_close(host(hippo.hippo_verify_attention(dev(q, "fp32"), dev(k, "fp32"), dev(v, "fp32"), 700)), ref, "fp32",
+                 "attention")
+    got = attention_mass(hippo, q, k, "fp32", 4, 12, 14, 10)
+    assert_close(got, oracle.s_attn(q, k, 10, 4 * 12 * 14), "fp32", "attention mass")
+    q[..., 4:] = 0.0
+    k[:, :, :, 3] = size
+    q[..., :3] = 0.0                                                   # exactly alike: uniform weights
+    ref, _ = oracle.attention(q, k, v, 700, None)
+    assert_close(host(hippo.hippo_verify_attention(dev(q, "fp32"), dev(k, "fp32"), dev(v, "fp32"), 700)), ref, "fp32",
+                 "attention, uniform")
+
+
 def score_inputs(seed, B, L, H, Hkv, d, n, dtype, scale=2.0):
     r = np.random.default_rng(seed)
     return prep(r.standard_normal((B, L, H, d)) * scale, dtype), prep(r.standard_normal((B, Hkv, n, d)), dtype)
