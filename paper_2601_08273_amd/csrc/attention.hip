@@ -666,8 +666,13 @@ __global__ __launch_bounds__(RB * TG * 64) void attn_partial_f32(AttnParams p) {
     const int ti = si * TG + tg;
     if (ti >= n_blk) continue;                         // ragged last super-tile
     const unsigned char* Kt = ring + (si % NST) * SM::kSuperBytes + tg * 2 * SM::kTileBytes;
-    const unsigned char* Vt = Kt + SM::kTileBytes;
+    unsigned char* Vt = ring + (si % NST) * SM::kSuperBytes + tg * 2 * SM::kTileBytes + SM::kTileBytes;
     const int n0 = (t_lo + ti) * 16;
+    // V rows past the cache's end repeat the last one, which may hold an infinity, and that times their weight of 0 is
+    // a NaN: cleared, by each wave before its own reads (a wave's LDS operations complete in order, and all that share
+    // the tile write the same).  In the cache's last tile only; a select at every operand cost the call 5 to 10 %.
+    for (int r = row_cap - n0 + 1; r < 16; ++r)
+      if (lane < CPR) *(f32x4*)(Vt + r * (D * 4) + lane * 16) = (f32x4){0.f, 0.f, 0.f, 0.f};
 
     f32x4 z[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};   // two chains, even and odd steps
 #pragma unroll

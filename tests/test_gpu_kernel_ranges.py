@@ -115,6 +115,20 @@ def test_fp32_attention_row_blocks(hippo, shape, d):
 
 
 @pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("ctx", [0, 15, 16, 700])
+def test_fp32_infinity_in_the_last_value_row(hippo, ctx, d):
+    # the one row that sees it gets the infinity, not a NaN from rows past the cache's end
+    q, k, v = attention_inputs(d, 2, 1, 14, 2, d, ctx, "fp32")
+    ref, _ = oracle.attention(q, k, v, ctx, None)
+    v[:, :, ctx, 5] = np.inf
+    v[:, :, ctx, 6] = -np.inf
+    got = host(hippo.hippo_verify_attention(dev(q, "fp32"), dev(k, "fp32"), dev(v, "fp32"), ctx))
+    assert (got[..., 5] == np.inf).all() and (got[..., 6] == -np.inf).all()
+    rest = [c for c in range(d) if c not in (5, 6)]
+    assert_close(got[..., rest], ref[..., rest], "fp32", "ctx %d d=%d" % (ctx, d))
+
+
+@pytest.mark.parametrize("d", [64, 128])
 @pytest.mark.parametrize("size", [1e9, 1e20, 3e37])
 def test_fp32_logits_of_any_finite_size(hippo, size, d):
     # one token's key decides every row, for it or against it; then all tokens' logits are huge and alike (the attention
