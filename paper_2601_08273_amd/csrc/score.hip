@@ -898,7 +898,7 @@ struct EmbRunSmem {
   float redd[NW][2][16];                            // diagonals of the (this frame) x (frame before) blocks
   float G[MP][MP + 1];
   float dotv[MP];
-  float inv_norm[MP];
+  float scale[MP];                                  // of the rows' norms, see scale_of
   int tok_s[MP];
 };
 
@@ -998,24 +998,30 @@ __device__ __forceinline__ void emb_run32_body(const ScoreParams& p, EmbRunSmem<
   auto operand = [&](int rbk, int u) -> u32x4 {
     return *(const u32x4*)(strip + (rbk * 16 + j) * (64 * U) + (((4 * u + g) ^ (j & (PPR - 1))) * 16));
   };
-  // 1 / sqrt(x), or -1 for a row without a positive norm (of zeros, or with a NaN), whose cosines are 0.  bf16: by the
-  // hardware's reciprocal square root (1 ulp), which ignores denormals: tiny arguments are scaled by 2^64 first, the
-  // result by 2^32.  (The riding blocks compete with the sweep for vector-instruction issue and nothing else, so what
-  // the crop's closing arithmetic costs in instructions is what the embedding terms cost the launch.)
-  auto inv_sqrt = [](float x) -> float {
-    if constexpr (F32) return x > 0.f ? 1.f / sqrtf(x) : -1.f;
+  // Squared norm -> what cosine() takes of a row: bf16 its reciprocal norm, fp32 its norm; -1 for a row without a
+  // positive norm (of zeros, or with a NaN), whose cosines are 0.  bf16: by the hardware's reciprocal square root
+  // (1 ulp), which ignores denormals: tiny arguments are scaled by 2^64 first, the result by 2^32.  (The riding blocks
+  // compete with the sweep for vector-instruction issue and nothing else, so what the crop's closing arithmetic costs in
+  // instructions is what the embedding terms cost the launch.)  fp32: two divisions; with reciprocals s_temp was up to
+  // 8 % further from 64 bits, and the call no faster.
+  auto scale_of = [](float x) -> float {
+    if constexpr (F32) return x > 0.f ? sqrtf(x) : -1.f;
     const bool tiny = x < 0x1p-60f;
     const float r = __builtin_amdgcn_rsqf(tiny ? x * 0x1p64f : x);
     return x > 0.f ? (tiny ? r * 0x1p32f : r) : -1.f;
   };
-  // dot product and both reciprocal norms -> cosine (from left to right: the norms' product can exceed fp32's range;
-  // the dot product is what is replaced, so that the last product still fuses with the sum that it goes into)
-  auto cosine = [](float dot, float ia, float ib) { return (fminf(ia, ib) < 0.f ? 0.f : dot) * ia * ib; };
+  // (from left to right: the product of two norms, or of their reciprocals, can exceed fp32's range; the dot product is
+  // what is replaced, so that the last product still fuses with the sum that it goes into)
+  auto cosine = [](float dot, float sa, float sb) {
+    const float d = fminf(sa, sb) < 0.f ? 0.f : dot;
+    if constexpr (F32) return d / sa / sb;
+    else return d * sa * sb;
+  };
   const float inv_M = 1.f / (float)M;
 
   // state of the tokens' temporal term, kept by lane 0 of each 16-lane row (token a = tid / 16):
-  // 1 / norm of the last two frames, and their dot product
-  float inv_n1 = 0.f, inv_n2 = 0.f, dot1 = 0.f;
+  // the scale of its norm in the last two frames, and their dot product
+  float scale_1 = 0.f, scale_2 = 0.f, dot1 = 0.f;
   const int a = tid >> 4, c0 = (tid & 15) * 2;
   const long long out_base = (long long)b * p.Nv + sm.tok_s[a];
 
@@ -1108,7 +1114,7 @@ __device__ __forceinline__ void emb_run32_body(const ScoreParams& p, EmbRunSmem<
     }
     __syncthreads();
     // sum the eight channel slices in a fixed order: waves 0..2 one Gram block each (the diagonal
-    // blocks also give the rows' 1 / norm), wave 3 the diagonals of the dot blocks
+    // blocks also give the scales of the rows' norms), wave 3 the diagonals of the dot blocks
     if (wave < 3 && (own_frame || wave != 1)) {
       const int blk = wave;
       f32x4 v = *(const f32x4*)(&sm.strip[0][0] + (blk * 64 + lane) * 16);
@@ -1125,7 +1131,7 @@ __device__ __forceinline__ void emb_run32_body(const ScoreParams& p, EmbRunSmem<
 #pragma unroll
         for (int e = 1; e < 4; ++e)
           if ((j & 3) == e) d = v[e];
-        sm.inv_norm[ra * 16 + j] = inv_sqrt(d);
+        sm.scale[ra * 16 + j] = scale_of(d);
       }
     } else if (wave == 3 && lane < MP) {
       float d = sm.redd[0][lane >> 4][lane & 15];
@@ -1138,11 +1144,11 @@ __device__ __forceinline__ void emb_run32_body(const ScoreParams& p, EmbRunSmem<
 
     // cosines of token a against tokens c0, c0 + 1 (16 lanes cover the crop; padding rows hold
     // finite values and are masked); Eq. 5-6: their variance -- for the run's own frames only
-    const float ia = sm.inv_norm[a];
+    const float sa = sm.scale[a];
     float var = 0.f;
     if (own_frame) {
-      const float cs0 = c0 < M ? cosine(sm.G[a][c0], ia, sm.inv_norm[c0]) : 0.f;
-      const float cs1 = c0 + 1 < M ? cosine(sm.G[a][c0 + 1], ia, sm.inv_norm[c0 + 1]) : 0.f;
+      const float cs0 = c0 < M ? cosine(sm.G[a][c0], sa, sm.scale[c0]) : 0.f;
+      const float cs1 = c0 + 1 < M ? cosine(sm.G[a][c0 + 1], sa, sm.scale[c0 + 1]) : 0.f;
       const float mu = row16_sum(cs0 + cs1) * inv_M;
       const float d0 = c0 < M ? cs0 - mu : 0.f, d1 = c0 + 1 < M ? cs1 - mu : 0.f;
       var = row16_sum(fmaf(d0, d0, d1 * d1)) * inv_M;
@@ -1152,17 +1158,17 @@ __device__ __forceinline__ void emb_run32_body(const ScoreParams& p, EmbRunSmem<
       if (own_frame) p.s_spa[out_base + (long long)fr * p.P] = var;
       // Eq. 3-4 of the frame before, whose two neighbours are known now
       if (fr > lo && fr - 1 >= f0) {
-        const float next = cosine(dcur, inv_n1, ia), before = cosine(dot1, inv_n1, inv_n2);
+        const float next = cosine(dcur, scale_1, sa), before = cosine(dot1, scale_1, scale_2);
         p.s_temp[out_base + (long long)(fr - 1) * p.P] = 1.f - (fr - 1 > 0 ? 0.5f * (next + before) : next);
       }
-      inv_n2 = inv_n1;
-      inv_n1 = ia;
+      scale_2 = scale_1;
+      scale_1 = sa;
       dot1 = dcur;
     }
   }
   // a run that reaches the video's last frame: that frame has no successor
   if ((tid & 15) == 0 && a < M && hi < f_end)
-    p.s_temp[out_base + (long long)hi * p.P] = 1.f - (hi > 0 ? cosine(dot1, inv_n1, inv_n2) : 0.f);
+    p.s_temp[out_base + (long long)hi * p.P] = 1.f - (hi > 0 ? cosine(dot1, scale_1, scale_2) : 0.f);
 }
 
 // block number -> (crop position, run of frames, batch element), positions fastest
