@@ -133,7 +133,7 @@ size_t hippo_workspace_bytes(int32_t call, const hippo_kv_desc* kv, const hippo_
  * components_out optional [3, B, N_v] fp32: raw s_attn (this call's, or accumulated), s_temp, s_spa.
  * Errors: NULL_ARG, BAD_SHAPE (l_txt < 1, N_v < 1, vis_offset + N_v > seq_len, crop too large,
  *         no term enabled; beyond the launch limits: B * layers > 65535, more than 65535 frames,
- *         bf16 with N_v > 65535 * 256 tokens), BAD_DTYPE, BAD_ALIGN, WORKSPACE_TOO_SMALL, HIP.
+ *         N_v > 65535 * 256 tokens in bf16, 65535 * 128 in fp32), BAD_DTYPE, BAD_ALIGN, WORKSPACE_TOO_SMALL, HIP.
  */
 int hippo_score_tokens(const void* q_txt, int32_t l_txt,
                        const void* k_cache, const hippo_kv_desc* kv, int32_t seq_len,
@@ -210,11 +210,11 @@ int hippo_verify_attention(const void* q, int32_t q_len,
 
 /*
  * Draft-decode attention over the pruned cache (Preliminaries, "Speculative Decoding": the draft
- * model is invoked gamma times, one new token per forward).  Same contract, arguments, kernels and
- * split heuristic as hippo_verify_attention (measured: the matrix-unit kernel padded to one 16-row
- * block beats the vector-ALU kernel 4-9 x at G = 7 or 8 rows); the one difference is that its waves
- * do not raise their issue priority, so a verification running beside it keeps the right of way.  Running it on
- * the cache hippo_select_gather_kv built with k = N_v equals attention over the unpruned cache.
+ * model is invoked gamma times, one new token per forward).  Same contract, arguments, kernels (padded
+ * to one 16-row block at G = 7 or 8 rows) and split heuristic as hippo_verify_attention; the one
+ * difference is that its waves do not raise their issue priority, so a verification running beside it
+ * keeps the right of way.  Running it on the cache hippo_select_gather_kv built with k = N_v equals
+ * attention over the unpruned cache.
  */
 int hippo_draft_attention(const void* q, int32_t q_len,
                           const void* k_cache, const void* v_cache, const hippo_kv_desc* kv,
