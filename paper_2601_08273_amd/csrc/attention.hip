@@ -521,7 +521,7 @@ __global__ __launch_bounds__(RB * TG * 64) void attn_partial_grid(AttnParams p) 
 // multiply-adds per pair of operands, and streamed the cache once per 32 query rows.  A verification call, us: 8K x
 // 4 heads x 128, 42 rows, a draft call beside it 88 -> 28; two sequences x 4K x 8 heads, 80 rows 223 -> 53;
 // 12.7K x 8 heads, 104 rows 413 -> 74 (5.5 GFLOP: 74 TFLOP/s of a peak of 157); 64 channels, 70K x 2 heads, 49
-// rows 154 -> 36.  Its error against 64 bits is a third to a half of the former kernel's (shorter serial sums).
+// rows 154 -> 36.  Its error against 64 bits is 0.5 to 0.7 times the former kernel's (shorter serial sums).
 // The same frame as attn_partial_grid: grid (S, H_kv, B * n_chunks), wave (rb, tg) owns 16 query rows and every
 // TG-th 16-token tile, tiles go HBM -> LDS by direct transfers into a ring of NST super-tiles, one barrier per
 // super-tile.  Operands (lane = j + 16g): A row j, contraction slot g; B column j, slot g; result column j, rows
