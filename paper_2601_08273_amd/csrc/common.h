@@ -96,6 +96,14 @@ __device__ __forceinline__ float row16_reduce(float v, Op op) {
 __device__ __forceinline__ float row16_max(float v) { return row16_reduce(v, [](float a, float b) { return max_nan(a, b); }); }
 __device__ __forceinline__ float row16_sum(float v) { return row16_reduce(v, [](float a, float b) { return a + b; }); }
 
+// the same over each 8 lanes
+__device__ __forceinline__ float row8_sum(float v) {
+  v += dpp_f32<kDppQuadXor1>(v);
+  v += dpp_f32<kDppQuadXor2>(v);
+  v += dpp_f32<kDppRowHalfMirror>(v);
+  return v;
+}
+
 // Inclusive prefix sum over the 64 lanes: Hillis-Steele inside the rows (row_shr 1, 2, 4, 8), then
 // row 0's total into row 1 and row 2's into row 3, then the lower half's total into the upper half.
 __device__ __forceinline__ unsigned wave_scan_incl(unsigned v) {

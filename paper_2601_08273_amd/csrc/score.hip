@@ -35,23 +35,31 @@ __device__ __forceinline__ long long sattn_part_at(const ScoreParams& p, int til
 constexpr int kSaF32Tile = 128;       // tokens per block
 constexpr int kSaF32Rows = 32;        // query rows per chunk
 
+template <int D>
+struct SattnF32Smem {
+  static constexpr int NW = 4, RCH = kSaF32Rows;
+  __align__(16) unsigned char Qs[2 * RCH * D * 4];
+  float lse_s[2][RCH];
+  float wm_s[2][NW][RCH], wl_s[2][NW][RCH];
+};
+
 template <int D, int PASS>
-__global__ __launch_bounds__(256, 2) void sattn_f32(ScoreParams p) {
-  constexpr int NW = 4, TPW = kSaF32Tile / NW, TBW = TPW / 16, RCH = kSaF32Rows;
+__device__ __forceinline__ void sattn_f32_body(const ScoreParams& p, SattnF32Smem<D>& sm, const int tile, const int hk,
+                                               const int rs, const int bz) {
+  constexpr int NW = SattnF32Smem<D>::NW, TPW = kSaF32Tile / NW, TBW = TPW / 16, RCH = kSaF32Rows;
   constexpr int NS = D / 16;
   constexpr int CPR = D / 4;                       // 16-byte pieces per row
   constexpr int RPI = 64 / CPR;                    // rows per transfer
   constexpr int XPW = RCH / RPI / NW;              // transfers per wave per chunk
   constexpr int CHUNKB = RCH * D * 4;
-  __shared__ __align__(16) unsigned char Qs[2 * CHUNKB];
-  __shared__ float lse_s[2][RCH];
-  __shared__ float wm_s[2][NW][RCH], wl_s[2][NW][RCH];
+  unsigned char* Qs = sm.Qs;
+  auto& lse_s = sm.lse_s;
+  auto& wm_s = sm.wm_s;
+  auto& wl_s = sm.wl_s;
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int j = lane & 15, g = lane >> 4;
-  const int hk = blockIdx.x, tile = blockIdx.y;
-  const int rs = blockIdx.z % p.n_rsplit, bz = blockIdx.z / p.n_rsplit;
   const int b = bz % p.B, layer = bz / p.B;        // several layers' sweeps share a launch
   const int n0 = tile * kSaF32Tile + wave * TPW;   // first token of this wave
   const int Rs = p.L * p.G;
@@ -191,6 +199,13 @@ __global__ __launch_bounds__(256, 2) void sattn_f32(ScoreParams p) {
           p.col_part[((long long)bz * p.Hkv * p.n_rsplit + hk + p.Hkv * rs) * p.Nv + n] = v;
       }
   }
+}
+
+// Grid (H_kv, n_tile, n_rsplit * Bz), as the bf16 sweeps
+template <int D, int PASS>
+__global__ __launch_bounds__(256, 2) void sattn_f32(ScoreParams p) {
+  __shared__ SattnF32Smem<D> sm;
+  sattn_f32_body<D, PASS>(p, sm, blockIdx.y, blockIdx.x, blockIdx.z % p.n_rsplit, blockIdx.z / p.n_rsplit);
 }
 
 // =================================================================================================
@@ -865,11 +880,11 @@ __global__ __launch_bounds__(256) void emb_scores_mfma(ScoreParams p) {
 
 // =================================================================================================
 // s_temp and s_spa on MFMA, crops of at most 32 tokens: frame runs.
-// A block of eight waves owns ONE crop position over a run of consecutive frames, so a frame's crop
+// A block of eight waves (fp32: four) owns ONE crop position over a run of consecutive frames, so a frame's crop
 // serves as "this frame" for its Gram matrix (Eq. 5-6; its diagonal holds the norms) and as "the
 // neighbour" of the frame before and after it (Eq. 3-4) -- against four fetches per crop when every
 // (crop, frame) is a block of its own.  The wave holds 16 * U lanes' worth of 16-byte pieces of all 32
-// rows (U per lane and row block); the eight partial Gram and dot blocks are summed through LDS.
+// rows (U per lane and row block); the waves' partial Gram and dot blocks are summed through LDS.
 // The operands travel HBM -> LDS by direct transfers, a lane fetching 16 bytes of a 64 * U-byte row
 // segment next to its neighbour's (an MFMA operand lane holds ITS OWN row, so fetching operands
 // straight into registers makes neighbouring lanes read rows far apart, and the address unit then
@@ -878,22 +893,22 @@ __global__ __launch_bounds__(256) void emb_scores_mfma(ScoreParams p) {
 // carries the wave's partial Gram blocks to the reduction, so the next frame's transfer is requested
 // once the reduction has read them and lands under the rest of the frame's arithmetic.
 //
-// One pass over a block's channels (512 in bf16 with U = 2 and in fp32 with U = 4) keeps the frame before in
+// One pass over a block's channels (512 in bf16 with U = 2, 256 in fp32 with U = 4) keeps the frame before in
 // registers.  WIDE embeddings take several passes per frame; what does not fit then is the frame before, whose
 // pass is fetched again behind this frame's: two fetches per crop and frame instead of one, against four (a row
 // per lane) in the block-per-two-crops kernel that this replaces.  Whole scoring calls, us: 4 x 36864 tokens, 1024
 // channels 831 -> 778; 2 x 40000 tokens, 768 channels 98 -> 88; 2 x 16320 tokens, 768 channels 86 and 86.
 // fp32 takes the same frame with four 16x16x4 products per 16-byte operand (3136 tokens, 128 channels 47 -> 37;
-// 12288 tokens, 512 channels 178 -> 143; 11040 tokens, 1024 channels 624 -> 562).  The vector-ALU kernel (a block
+// 12288 tokens, 512 channels 178 -> 143; 11040 tokens, 1024 channels 624 -> 562); its blocks are those of the fp32
+// sweeps, four waves, so that they ride beside pass 1 as the bf16 ones do (sattn_f32_pass1_with_emb).  The vector-ALU kernel (a block
 // per crop and frame, two LDS reads per multiply-add) is left for fp32 crops above 32 tokens.
 // =================================================================================================
 // 16 bytes of zeros in device memory: what a transfer lane fetches for channels beyond the last
 __device__ __align__(16) const unsigned char g_zero_piece[16] = {0};
 
-template <int U>
+template <int U, int NW>
 struct EmbRunSmem {
   static constexpr int MP = 32;
-  static constexpr int NW = 8;
   __align__(16) unsigned char strip[NW][MP * 64 * U];   // operands in (32 rows x 64 U B), then Gram partials out (3 x 64 x 16 B)
   float redd[NW][2][16];                            // diagonals of the (this frame) x (frame before) blocks
   float G[MP][MP + 1];
@@ -917,12 +932,13 @@ __device__ __forceinline__ f32x4 emb_mma(const u32x4& a, const u32x4& b, f32x4 a
 }
 
 // One crop position `pos` of batch element b over the frames f0 .. f0 + p.emb_run - 1 (cut at the
-// video's end), by the 512 threads of a block; every thread must call it (block-wide barriers).
-template <bool F32, int U, bool WIDE>
-__device__ __forceinline__ void emb_run32_body(const ScoreParams& p, EmbRunSmem<U>& sm, const int tid, const int pos,
+// video's end), by the 64 * NW threads of a block; every thread must call it (block-wide barriers).
+template <bool F32, int U, int NW, bool WIDE>
+__device__ __forceinline__ void emb_run32_body(const ScoreParams& p, EmbRunSmem<U, NW>& sm, const int tid, const int pos,
                                                const int f0, const int b) {
-  constexpr int MP = EmbRunSmem<U>::MP;
-  constexpr int NW = EmbRunSmem<U>::NW;
+  constexpr int MP = EmbRunSmem<U, NW>::MP;
+  constexpr int TPT = NW * 64 / MP, CPT = MP / TPT; // threads per token, cosines per thread
+  static_assert((NW == 8 && TPT == 16) || (NW == 4 && TPT == 8), "a token's threads are half or all of a 16-lane row");
   constexpr int EB = F32 ? 4 : 2;                   // bytes per channel
   constexpr int EPP = 16 / EB;                      // channels per 16-byte piece
   constexpr int PPR = 4 * U;                        // pieces of a row in a wave's strip
@@ -1019,10 +1035,11 @@ __device__ __forceinline__ void emb_run32_body(const ScoreParams& p, EmbRunSmem<
   };
   const float inv_M = 1.f / (float)M;
 
-  // state of the tokens' temporal term, kept by lane 0 of each 16-lane row (token a = tid / 16):
+  // state of the tokens' temporal term, kept by the first of the token's threads (token a = tid / TPT):
   // the scale of its norm in the last two frames, and their dot product
   float scale_1 = 0.f, scale_2 = 0.f, dot1 = 0.f;
-  const int a = tid >> 4, c0 = (tid & 15) * 2;
+  const int a = tid / TPT, c0 = (tid % TPT) * CPT;
+  auto token_sum = [](float v) { return NW == 8 ? row16_sum(v) : row8_sum(v); };
   const long long out_base = (long long)b * p.Nv + sm.tok_s[a];
 
   const int n_pass = WIDE ? (de + CB - 1) / CB : 1;
@@ -1064,11 +1081,18 @@ __device__ __forceinline__ void emb_run32_body(const ScoreParams& p, EmbRunSmem<
           prev[rbk][u % UP] = cur[rbk][u];
         }
     } else {
-      f32x4 gram[3];
+      // four waves take 512 channels in two passes, which are summed apart (as eight waves would): a sum of twice as many
+      // channels in a row put the fused score of 512 fp32 channels 1.3 times, of 1024 1.5 times as far from 64 bits
+      constexpr int SETS = 8 / NW;
+      f32x4 gram[SETS][3], dots[SETS][2];
 #pragma unroll
-      for (int i = 0; i < 3; ++i) gram[i] = (f32x4){0.f, 0.f, 0.f, 0.f};
+      for (int s = 0; s < SETS; ++s) {
+#pragma unroll
+        for (int i = 0; i < 3; ++i) gram[s][i] = (f32x4){0.f, 0.f, 0.f, 0.f};
+        dots[s][0] = dots[s][1] = (f32x4){0.f, 0.f, 0.f, 0.f};
+      }
       const bool has_before = fr > lo;
-      for (int pass = 0; pass < n_pass; ++pass) {
+      auto take_pass = [&](int pass, f32x4 (&gram)[3], f32x4 (&dot)[2]) {
         u32x4 cur[2][U];
         wait_vmcnt<0>();
 #pragma unroll
@@ -1096,10 +1120,22 @@ __device__ __forceinline__ void emb_run32_body(const ScoreParams& p, EmbRunSmem<
           asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
           if (pass + 1 < n_pass) request(fr, pass + 1);
         }
+      };
+      for (int pass = 0; pass < n_pass; pass += SETS) {
+        take_pass(pass, gram[0], dots[0]);
+        if (SETS == 2 && pass + 1 < n_pass) take_pass(pass + 1, gram[SETS - 1], dots[SETS - 1]);
       }
+      if (SETS == 2) {
+#pragma unroll
+        for (int i = 0; i < 3; ++i) gram[0][i] += gram[SETS - 1][i];
+#pragma unroll
+        for (int rbk = 0; rbk < 2; ++rbk) dots[0][rbk] += dots[SETS - 1][rbk];
+      }
+      dot[0] = dots[0][0];
+      dot[1] = dots[0][1];
 #pragma unroll
       for (int i = 0; i < 3; ++i)
-        if (i != 1 || own_frame) *(f32x4*)(strip + (i * 64 + lane) * 16) = gram[i];
+        if (i != 1 || own_frame) *(f32x4*)(strip + (i * 64 + lane) * 16) = gram[0][i];
     }
     // of a dot block only the diagonal (token with itself) is needed: lane (j, g = j/4), element j%4
     if ((j >> 2) == g) {
@@ -1113,7 +1149,7 @@ __device__ __forceinline__ void emb_run32_body(const ScoreParams& p, EmbRunSmem<
       }
     }
     __syncthreads();
-    // sum the eight channel slices in a fixed order: waves 0..2 one Gram block each (the diagonal
+    // sum the waves' channel slices in a fixed order: waves 0..2 one Gram block each (the diagonal
     // blocks also give the scales of the rows' norms), wave 3 the diagonals of the dot blocks
     if (wave < 3 && (own_frame || wave != 1)) {
       const int blk = wave;
@@ -1142,18 +1178,26 @@ __device__ __forceinline__ void emb_run32_body(const ScoreParams& p, EmbRunSmem<
     __syncthreads();
     if (fr < hi) request(fr + 1, 0);                // the strips are free again: the next frame travels meanwhile
 
-    // cosines of token a against tokens c0, c0 + 1 (16 lanes cover the crop; padding rows hold
+    // cosines of token a against tokens c0 .. c0 + CPT - 1 (its TPT threads cover the crop; padding rows hold
     // finite values and are masked); Eq. 5-6: their variance -- for the run's own frames only
     const float sa = sm.scale[a];
     float var = 0.f;
     if (own_frame) {
-      const float cs0 = c0 < M ? cosine(sm.G[a][c0], sa, sm.scale[c0]) : 0.f;
-      const float cs1 = c0 + 1 < M ? cosine(sm.G[a][c0 + 1], sa, sm.scale[c0 + 1]) : 0.f;
-      const float mu = row16_sum(cs0 + cs1) * inv_M;
-      const float d0 = c0 < M ? cs0 - mu : 0.f, d1 = c0 + 1 < M ? cs1 - mu : 0.f;
-      var = row16_sum(fmaf(d0, d0, d1 * d1)) * inv_M;
+      float cs[CPT];
+#pragma unroll
+      for (int i = 0; i < CPT; ++i) cs[i] = c0 + i < M ? cosine(sm.G[a][c0 + i], sa, sm.scale[c0 + i]) : 0.f;
+      float mu = cs[0];
+#pragma unroll
+      for (int i = 1; i < CPT; ++i) mu += cs[i];
+      mu = token_sum(mu) * inv_M;
+#pragma unroll
+      for (int i = 0; i < CPT; ++i) cs[i] = c0 + i < M ? cs[i] - mu : 0.f;
+      float sq = cs[CPT - 1] * cs[CPT - 1];
+#pragma unroll
+      for (int i = CPT - 2; i >= 0; --i) sq = fmaf(cs[i], cs[i], sq);
+      var = token_sum(sq) * inv_M;
     }
-    if ((tid & 15) == 0 && a < M) {
+    if (tid % TPT == 0 && a < M) {
       const float dcur = sm.dotv[a];                // <this frame, frame before>
       if (own_frame) p.s_spa[out_base + (long long)fr * p.P] = var;
       // Eq. 3-4 of the frame before, whose two neighbours are known now
@@ -1167,25 +1211,48 @@ __device__ __forceinline__ void emb_run32_body(const ScoreParams& p, EmbRunSmem<
     }
   }
   // a run that reaches the video's last frame: that frame has no successor
-  if ((tid & 15) == 0 && a < M && hi < f_end)
+  if (tid % TPT == 0 && a < M && hi < f_end)
     p.s_temp[out_base + (long long)hi * p.P] = 1.f - (hi > 0 ? cosine(dot1, scale_1, scale_2) : 0.f);
 }
 
 // block number -> (crop position, run of frames, batch element), positions fastest
-template <bool F32, int U, bool WIDE>
-__device__ __forceinline__ void emb_run32_block(const ScoreParams& p, EmbRunSmem<U>& sm, const unsigned blk) {
+template <bool F32, int U, int NW, bool WIDE>
+__device__ __forceinline__ void emb_run32_block(const ScoreParams& p, EmbRunSmem<U, NW>& sm, const unsigned blk) {
   const unsigned ncf = (unsigned)(((p.gh + p.ch - 1) / p.ch) * ((p.gw + p.cw - 1) / p.cw));   // crops per frame
   const unsigned n_runs = (unsigned)((p.F + p.emb_run - 1) / p.emb_run);
   const unsigned rest = blk / ncf, pos = blk - rest * ncf;
   const unsigned bb = rest / n_runs, run = rest - bb * n_runs;
-  emb_run32_body<F32, U, WIDE>(p, sm, threadIdx.x, (int)pos, (int)run * p.emb_run, (int)bb);
+  emb_run32_body<F32, U, NW, WIDE>(p, sm, threadIdx.x, (int)pos, (int)run * p.emb_run, (int)bb);
 }
 
-template <bool F32, bool WIDE>
-__global__ __launch_bounds__(512) void emb_scores_run32(ScoreParams p) {
+template <bool F32, int NW, bool WIDE>
+__global__ __launch_bounds__(64 * NW) void emb_scores_run32(ScoreParams p) {
   constexpr int U = F32 ? 4 : 2;
-  __shared__ EmbRunSmem<U> sm;
-  emb_run32_block<F32, U, WIDE>(p, sm, blockIdx.x);
+  __shared__ EmbRunSmem<U, NW> sm;
+  emb_run32_block<F32, U, NW, WIDE>(p, sm, blockIdx.x);
+}
+
+// fp32: pass 1 and the embedding terms in one launch, the sweep's blocks first.  A wave of the sweep per SIMD keeps the
+// matrix unit busy, so a riding block's trips to memory cost next to nothing; in a launch of their own the crops took
+// as long as the sweep (3136 tokens: 10.5 us of pass 1 and 13 of crops, together 14.7).  Whole scoring calls, us: 936
+// tokens 30.6 -> 22.2; 3136 tokens 37.4 -> 29.3; 2 x 12 frames, 768 channels 112 -> 99; 3 x 7220 tokens, two layers 130 -> 105;
+// 12288 tokens, 512 channels 145 -> 138; 10080 tokens, 1024 channels 160 -> 155.  Up to 168 registers a wave, 38 KB of LDS:
+// three blocks on a compute unit.
+template <int D, bool WIDE>
+__global__ __launch_bounds__(256, 3) void sattn_f32_pass1_with_emb(ScoreParams p, int n_sattn) {
+  union Smem {
+    SattnF32Smem<D> sa;
+    EmbRunSmem<4, 4> run;
+  };
+  __shared__ Smem sm;
+  const int blk = blockIdx.x;
+  if (blk < n_sattn) {
+    const int hk = blk % p.Hkv, rest = blk / p.Hkv;
+    const int tile = rest % p.n_tile, rest2 = rest / p.n_tile;
+    sattn_f32_body<D, 1>(p, sm.sa, tile, hk, rest2 % p.n_rsplit, rest2 / p.n_rsplit);
+    return;
+  }
+  emb_run32_block<true, 4, 4, WIDE>(p, sm.run, (unsigned)(blk - n_sattn));
 }
 
 // Pass 1 of s_attn and the embedding terms in ONE launch: the first n_sattn blocks run the
@@ -1196,10 +1263,10 @@ __global__ __launch_bounds__(512) void emb_scores_run32(ScoreParams p) {
 // WIDE: of more than 512 channels.
 template <int D, bool WIDE>
 __global__ __launch_bounds__(kSaWaves * 64, 6) void sattn_pass1_with_emb(ScoreParams p, int n_sattn) {
-  static_assert(kSaWaves == EmbRunSmem<2>::NW, "the riding blocks use the sweep's block size");
+  static_assert(kSaWaves == 8, "the riding blocks use the sweep's block size");
   union Smem {
     SattnSmem<D, 1> sa;
-    EmbRunSmem<2> run;
+    EmbRunSmem<2, 8> run;
   };
   __shared__ Smem sm;
   const int blk = blockIdx.x;
@@ -1211,7 +1278,7 @@ __global__ __launch_bounds__(kSaWaves * 64, 6) void sattn_pass1_with_emb(ScorePa
   }
   // (the host admits this launch only when its block count stays below 2^31: crop numbers fit 32 bits,
   // and 32-bit divisions are all that stands in front of a riding block's first load)
-  emb_run32_block<false, 2, WIDE>(p, sm.run, (unsigned)(blk - n_sattn));
+  emb_run32_block<false, 2, 8, WIDE>(p, sm.run, (unsigned)(blk - n_sattn));
 }
 
 // =================================================================================================
@@ -1398,17 +1465,26 @@ int score_row_splits(int dtype, long long blocks_unsplit, int rows_per_kv_head) 
 }
 
 template <int D>
-static hipError_t launch_sattn_f32(const ScoreParams& p, hipStream_t st) {
+static hipError_t launch_sattn_f32(const ScoreParams& p, hipStream_t st, long long riders, bool wide) {
   if (p.n_tile > 65535 || (long long)p.n_rsplit * p.Bz > 65535) return hipErrorInvalidValue;
   const dim3 grid(p.Hkv, p.n_tile, p.n_rsplit * p.Bz);     // KV head fastest, as the bf16 sweeps
-  hipLaunchKernelGGL((sattn_f32<D, 1>), grid, dim3(256), 0, st, p);
+  if (riders > 0) {
+    const long long n_sattn = (long long)p.n_tile * p.Hkv * p.n_rsplit * p.Bz;
+    const dim3 fused((unsigned)(n_sattn + riders));
+    if (wide)
+      hipLaunchKernelGGL((sattn_f32_pass1_with_emb<D, true>), fused, dim3(256), 0, st, p, (int)n_sattn);
+    else
+      hipLaunchKernelGGL((sattn_f32_pass1_with_emb<D, false>), fused, dim3(256), 0, st, p, (int)n_sattn);
+  } else {
+    hipLaunchKernelGGL((sattn_f32<D, 1>), grid, dim3(256), 0, st, p);
+  }
   const long long rows = (long long)p.Bz * p.H * p.L;
   hipLaunchKernelGGL(sattn_row_lse, dim3((unsigned)((rows + 31) / 32)), dim3(256), 0, st, p);
   hipLaunchKernelGGL((sattn_f32<D, 2>), grid, dim3(256), 0, st, p);
   return hipGetLastError();
 }
 
-// riders: 0 = pass 1 in a launch of its own, else that many riding blocks (wide: of more than 512 channels)
+// riders: 0 = pass 1 in a launch of its own, else that many riding blocks (wide: of more channels than a pass takes)
 template <int D>
 static hipError_t launch_sattn_mfma(const ScoreParams& p, hipStream_t st, long long riders, bool wide) {
   if (p.n_tile > 65535 || (long long)p.n_rsplit * p.Bz > 65535) return hipErrorInvalidValue;
@@ -1442,23 +1518,24 @@ hipError_t launch_score(const ScoreParams& p_in, hipStream_t st) {
   }
   hipError_t e = hipSuccess;
   const bool accumulate_only = (p.flags & HIPPO_SCORE_ACCUMULATE_ONLY) != 0;
-  // bf16 with the paper's small crops: the embedding terms ride in the launch of s_attn's pass 1
+  // the paper's small crops: the embedding terms ride in the launch of s_attn's pass 1
   const bool want_emb = (p.flags & (HIPPO_SCORE_TEMP | HIPPO_SCORE_SPA)) != 0;
   // Crops of at most 32 tokens: a block sweeps one crop position over a run of frames.  The runs are as long as
   // still leaves every compute unit a block (at most 8 frames: a run fetches its two neighbour frames on top of its
-  // own); fp32 blocks, which ride in no other launch, fit a compute unit twice and hide each other's trips.
+  // own).  Half as long, two blocks per compute unit, was slower for fp32 crops beside the sweep (12288 tokens 142 against
+  // 138 us a call, 3 x 7220 tokens 112 against 105).
   const long long crops_per_frame = (long long)((p.gh + p.ch - 1) / p.ch) * ((p.gw + p.cw - 1) / p.cw);
   const bool bf16 = p.dtype == HIPPO_DTYPE_BF16;
   {
     const long long crops = crops_per_frame * p.F * p.B;
-    const long long run = bf16 ? crops / kNumCU : (crops + 2 * kNumCU - 1) / (2 * kNumCU);
+    const long long run = crops / kNumCU;
     p.emb_run = (int)std::max<long long>(1, std::min<long long>(std::min<long long>(8, p.F), run));
   }
   const bool small_crops = p.ch * p.cw <= 32;
-  const bool wide = (p.emb ? p.emb_dim : p.Hkv * p.D) > 512;
+  const bool wide = (p.emb ? p.emb_dim : p.Hkv * p.D) > (bf16 ? 512 : 256);
   const long long n_riders = crops_per_frame * ((p.F + p.emb_run - 1) / p.emb_run) * p.B;
   const long long fused_blocks = (long long)p.n_tile * p.Hkv * p.n_rsplit * p.Bz + n_riders;
-  const bool emb_rides = bf16 && want_emb && !accumulate_only && (p.flags & HIPPO_SCORE_ATTN) && small_crops &&
+  const bool emb_rides = want_emb && !accumulate_only && (p.flags & HIPPO_SCORE_ATTN) && small_crops &&
                          fused_blocks < (1ll << 31);
   const long long riders = emb_rides ? n_riders : 0;
   if ((p.flags & HIPPO_SCORE_ATTN) || accumulate_only) {
@@ -1466,7 +1543,7 @@ hipError_t launch_score(const ScoreParams& p_in, hipStream_t st) {
       e = (p.D == 128) ? launch_sattn_mfma<128>(p, st, riders, wide)
                        : launch_sattn_mfma<64>(p, st, riders, wide);
     else
-      e = (p.D == 128) ? launch_sattn_f32<128>(p, st) : launch_sattn_f32<64>(p, st);
+      e = (p.D == 128) ? launch_sattn_f32<128>(p, st, riders, wide) : launch_sattn_f32<64>(p, st, riders, wide);
     if (e != hipSuccess) return e;
     if (accumulate_only) {   // otherwise the fusion kernel finishes the attention mass itself
       const long long n = (long long)p.B * p.Nv;
@@ -1480,10 +1557,15 @@ hipError_t launch_score(const ScoreParams& p_in, hipStream_t st) {
     if (small_crops) {
       if (n_riders >= (1ll << 31)) return hipErrorInvalidValue;
       const dim3 runs((unsigned)n_riders);
-      if (bf16 && wide) hipLaunchKernelGGL((emb_scores_run32<false, true>), runs, dim3(512), 0, st, p);
-      else if (bf16) hipLaunchKernelGGL((emb_scores_run32<false, false>), runs, dim3(512), 0, st, p);
-      else if (wide) hipLaunchKernelGGL((emb_scores_run32<true, true>), runs, dim3(512), 0, st, p);
-      else hipLaunchKernelGGL((emb_scores_run32<true, false>), runs, dim3(512), 0, st, p);
+      // fp32 of 257 to 512 channels: eight waves take them in one pass and fetch a frame once (2 x 12 frames of 512 channels,
+      // us: 24 against 27, 48 frames 24 against 35); up to 256, half of eight waves would idle (128 frames of 128 channels 29
+      // against 42), and beyond 512 four waves are the better ones again (1024 channels 48.5 against 52)
+      const int de = p.emb ? p.emb_dim : p.Hkv * p.D;
+      if (bf16 && wide) hipLaunchKernelGGL((emb_scores_run32<false, 8, true>), runs, dim3(512), 0, st, p);
+      else if (bf16) hipLaunchKernelGGL((emb_scores_run32<false, 8, false>), runs, dim3(512), 0, st, p);
+      else if (wide && de <= 512) hipLaunchKernelGGL((emb_scores_run32<true, 8, false>), runs, dim3(512), 0, st, p);
+      else if (wide) hipLaunchKernelGGL((emb_scores_run32<true, 4, true>), runs, dim3(256), 0, st, p);
+      else hipLaunchKernelGGL((emb_scores_run32<true, 4, false>), runs, dim3(256), 0, st, p);
     } else if (!bf16) {
       hipLaunchKernelGGL(emb_scores, grid, dim3(256), 0, st, p);
     } else if (p.ch * p.cw <= 48) {

@@ -201,6 +201,23 @@ def test_embedding_terms_over_passes_of_channels(hippo, shape, dtype):
         np.testing.assert_allclose(host(comps)[2], ss, rtol=0, atol=(2e-6 if dtype == "fp32" else 2e-3) * ss.max() + 1e-9)
 
 
+@pytest.mark.parametrize("shape", [
+    # an fp32 block takes 256 channels a pass, odd and even passes summed apart: a pass, less a piece and one more; two
+    # passes and a piece more; batch elements and frame runs of several with a short last one
+    (2, 3, 6, 7, 252, 5, 5), (1, 4, 5, 5, 256, 5, 5), (1, 2, 11, 6, 260, 4, 8), (1, 21, 16, 16, 512, 5, 5),
+    (3, 19, 11, 11, 516, 5, 5),
+])
+def test_fp32_embedding_terms_beside_the_sweep(hippo, shape):
+    test_embedding_terms_over_passes_of_channels(hippo, shape, "fp32")
+    B, F, gh, gw, ch, cy, cx = shape
+    q, k = score_inputs(ch, B, 37, 6, 2, 128, F * gh * gw + 11, "fp32")
+    vid = hippo.video_desc(F, gh, gw, 5, cy, cx)
+    comps = [hippo.hippo_score_tokens(dev(q, "fp32"), dev(k, "fp32"), vid, flags=flags, want_components=True)[1]
+             for flags in (7, 1, 6)]
+    assert torch.equal(comps[0][0], comps[1][0])                      # the sweep's blocks, with and without riders
+    assert torch.equal(comps[0][1:], comps[2][1:])                    # the riders' blocks, beside a sweep and alone
+
+
 @pytest.mark.parametrize("dtype", ["fp32", "bf16"])
 @pytest.mark.parametrize("ch", [64, 520])
 def test_rows_of_denormal_squared_norm(hippo, ch, dtype):
