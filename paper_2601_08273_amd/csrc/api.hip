@@ -219,7 +219,7 @@ int check_crop(const hippo_video_desc* vid) {
 // ---- speculative-sampling verification planning -------------------------------------------------
 struct SpecPlan {
   int n_seg, n_rows;
-  size_t off_cells, off_chosen, bytes;
+  size_t off_cells, off_arrived, bytes;
 };
 
 int plan_spec(int batch, int gamma, int vocab, int dtype, SpecPlan* pl) {
@@ -231,8 +231,8 @@ int plan_spec(int batch, int gamma, int vocab, int dtype, SpecPlan* pl) {
   const size_t stats = align_up((size_t)batch * pl->n_rows * pl->n_seg * sizeof(SegStat), 256);
   const size_t cells = align_up((size_t)batch * 2 * pl->n_seg * spec_cells_per_segment(dtype) * sizeof(float), 256);
   pl->off_cells = stats;
-  pl->off_chosen = stats + cells;
-  pl->bytes = stats + cells + align_up((size_t)batch * sizeof(Chosen), 256);
+  pl->off_arrived = stats + cells;
+  pl->bytes = stats + cells + align_up((size_t)batch * sizeof(int), 256);
   return HIPPO_OK;
 }
 
@@ -511,7 +511,7 @@ int hippo_spec_verify(const void* p_logits, const void* q_logits, int32_t dtype,
   char* ws = static_cast<char*>(workspace);
   p.stats = reinterpret_cast<SegStat*>(ws);
   p.cells = reinterpret_cast<float*>(ws + pl.off_cells);
-  p.chosen = reinterpret_cast<Chosen*>(ws + pl.off_chosen);
+  p.arrived = reinterpret_cast<int*>(ws + pl.off_arrived);
   const hipError_t e = launch_spec_verify(p, dtype, static_cast<hipStream_t>(stream));
   return e == hipSuccess ? HIPPO_OK : HIPPO_ERR_HIP;
 }

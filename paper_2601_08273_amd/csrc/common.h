@@ -350,7 +350,6 @@ struct Chosen {    // the row the next token is drawn from, and its normalisers
   int row;         // first rejected position, or gamma after a full acceptance
   int use_residual;
   float mp, inv_zp, mq, inv_zq;
-  int pad0, pad1;
 };
 
 struct SpecParams {
@@ -371,7 +370,7 @@ struct SpecParams {
   // workspace pieces
   SegStat* stats;            // [B, n_rows, n_seg]
   float* cells;              // [B, 2 (p, residual), n_seg * cells_per_segment]
-  Chosen* chosen;            // [B]
+  int* arrived;              // [B] blocks of the sequence whose cell sums are written
 };
 hipError_t launch_spec_verify(const SpecParams& p, int dtype, hipStream_t st);
 int spec_cells_per_segment(int dtype);

@@ -109,6 +109,39 @@ def test_sampling_parity(hippo, dtype, B, gamma, V, T, pad):
 
 
 @pytest.mark.parametrize("dtype", ["fp32", "bf16"])
+@pytest.mark.parametrize("B,V", [(1, 8), (70, 8200), (3, 1 << 20)])      # one block, two a sequence, the most there are
+def test_one_workspace_for_call_after_call(hippo, dtype, B, V):
+    # the sequences' counts of finished blocks live in the workspace: whatever it holds before, and from replay to replay
+    pl, ql, r = synth_logits(B, 2, V, B + V, 0.6)
+    tok = draw_from(ql, 1.0, r)
+    ua, us = r.random((B, 2)).astype(np.float32), r.random(B).astype(np.float32)
+    ref = run_case(hippo, pl, ql, tok, ua, us, 1.0, dtype, what="%s B%d V%d" % (dtype, B, V))
+    args = (dev(prep(pl, dtype), dtype), dev(prep(ql, dtype), dtype), torch.from_numpy(tok).cuda(),
+            torch.from_numpy(ua).cuda(), torch.from_numpy(us).cuda(), 1.0)
+    ws = torch.full((hippo.load().hippo_spec_verify_workspace_bytes(B, 2, V, 0 if dtype == "fp32" else 1),), 0xa5,
+                    dtype=torch.uint8, device="cuda")
+    acc, nxt = (torch.empty(B, dtype=torch.int32, device="cuda") for _ in range(2))
+
+    def call():
+        hippo.hippo_spec_verify(*args, n_accept_out=acc, next_token_out=nxt, workspace=ws)
+
+    def check():
+        np.testing.assert_array_equal(acc.cpu().numpy(), ref[0])
+        np.testing.assert_array_equal(nxt.cpu().numpy(), ref[1])
+    for _ in range(2):
+        call()
+        check()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        call()
+    for _ in range(3):
+        nxt.fill_(-1)
+        graph.replay()
+        check()
+        ws.fill_(0x5a)
+
+
+@pytest.mark.parametrize("dtype", ["fp32", "bf16"])
 def test_masked_words_edge_uniforms_and_bad_tokens(hippo, dtype):
     B, gamma, V, T = 40, 4, 20000, 1.0
     pl, ql, r = synth_logits(B, gamma, V, 5, 0.5)
