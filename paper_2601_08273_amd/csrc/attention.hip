@@ -96,7 +96,13 @@ struct GridSmem {
 // lane j receives column j of the 8 rows) then fetches exactly those 8 tokens of V^T in one read.
 template <int D, bool KV8>
 __device__ __forceinline__ int tile_swizzle(int r) {
-  if constexpr (!KV8) return lds_row_swizzle<D>(r);
+  // 16-bit rows: the K reads of 16 lanes touch 16 consecutive rows, one piece each; the V reads of 32 lanes eight
+  // consecutive rows, two neighbouring pieces each, so it is the piece's upper bits that must differ from row to row
+  // (the 16 lanes of a K read are not consecutive: with the pieces g * KS + ks of four lane groups, r itself as the swizzle
+  // doubled the K reads' time too; measured 44 % of the LDS cycles of a 33K call of 91 rows were conflicts, now none of
+  // the reads': 25.25 -> 24.85 us a call, 4 x 8 heads x 37K 107.5 -> 106.9)
+  if constexpr (!KV8 && D == 128) return ((r & 7) << 1) | ((r >> 3) & 1);
+  else if constexpr (!KV8) return (((r >> 1) & 3) << 1) | ((r >> 3) & 1);   // two rows in 256 bytes
   // 128-byte rows: the K reads of 16 lanes touch rows {0-3, 8-11, 16-19, 24-27} (+4), the V reads of
   // 32 lanes 16 consecutive rows; both must spread over the 16 16-byte slots of 256 bytes
   else if constexpr (D == 128) return ((r >> 1) ^ ((r >> 3) & 2)) & 7;
@@ -222,9 +228,8 @@ __global__ __launch_bounds__(RB * TG * 64) void attn_partial_grid(AttnParams p) 
     }
     __syncthreads();
   }
-  auto issue_super = [&](int si) {
+  auto issue_rows = [&](int si, int tile0, auto select) {
     const unsigned dst = ring_addr + (si % NST) * SM::kSuperBytes;
-    const int tile0 = t_lo + super_at(si) * TG;
 #pragma unroll
     for (int u = 0; u < PER; ++u) {
       const int x = wave * PER + u;
@@ -235,11 +240,18 @@ __global__ __launch_bounds__(RB * TG * 64) void attn_partial_grid(AttnParams p) 
       if (PAGED)
         src = (which ? vbase : kbase) + ((long long)page_s[(row >> p.page_shift) - slot_lo] * p.page_stride +
                                          (long long)(row & page_mask) * p.sn) * 2;
-      if (APPEND && row >= p.ctx_len)                      // a row that has not reached the cache yet
+      if (decltype(select)::value && row >= p.ctx_len)     // a row that has not reached the cache yet
         src = (const char*)(which ? p.v_new : p.k_new) +
               ((((long long)b * p.q_len + (row - p.ctx_len)) * p.Hkv + hk) * D) * 2;
       dma16<NT>(src + ((ld_pc ^ tile_swizzle<D, KV8>(r)) * 16), dst + (tt * 2 + which) * SM::kTileBytes + n * 1024);
     }
+  };
+  // (only the last tiles hold appended rows: the source select, formed for every lane of every transfer, stood in front of
+  // the first bytes of every slice; 16K x 4 heads, 42 rows 13.55 -> 13.3 us a call)
+  auto issue_super = [&](int si) {
+    const int tile0 = t_lo + super_at(si) * TG;
+    if (APPEND && (tile0 + TG) * TT > p.ctx_len) issue_rows(si, tile0, std::true_type());
+    else issue_rows(si, tile0, std::false_type());
   };
   // ---- prologue: the first ring stage goes out before anything else (its bytes are the ones
   // the first products wait for), then the query block, then the remaining stages.  Transfers
