@@ -58,8 +58,9 @@ int plan_attention(int call, const hippo_kv_desc* kv, int q_len, int n_total, in
   if ((long long)G * q_len > 4096) return HIPPO_ERR_BAD_SHAPE;
   pl->R = G * q_len;
   const bool f32 = kv->dtype == HIPPO_DTYPE_F32;
-  // A block takes at most 64 rows of a 16- or 8-bit cache: more go in chunks of 64, the same slices and tiles in every
-  // cache format.  The fp32 kernel takes 65 to 128 in one chunk: two chunks stream the whole cache twice and give every
+  // A block takes at most 64 rows of a 16- or 8-bit cache: more go in equal chunks, the same slices and tiles in every
+  // cache format (chunks of 64 and a rest, us a call: 33K x 4 heads, 91 rows 25.0 against 22.5; 8K, 77 rows 13.6 and
+  // 12.95; 2 x 8 heads x 8K, 96 rows 24.9 and 22.6).  The fp32 kernel takes 65 to 128 in one chunk: two chunks stream the whole cache twice and give every
   // slice half the compute units (a call over 70K x 2 heads x 64 channels, 70 rows: 43 us in one chunk, 52 in two; four
   // sequences x 9K, 91 rows: 28.9 and 33.6).  Not where a slice per compute unit leaves units idle, which the two chunks
   // then have to themselves (1K x 4 heads x 128, 77 rows: 16.4 in one, 15.0 in two); nor where it means more than 64
@@ -76,7 +77,8 @@ int plan_attention(int call, const hippo_kv_desc* kv, int q_len, int n_total, in
   const bool one_chunk = f32 && pl->R > 64 && pl->R <= 128 && n_tiles * heads > kNumCU &&
                          (kNumCU <= 64 * heads || n_tiles * heads >= 8 * kNumCU) &&
                          (num_splits > 0 || kNumCU / heads <= fit);
-  pl->row_chunk = pl->R <= 64 ? (pl->R + 15) / 16 * 16 : !one_chunk ? 64 : pl->R <= 96 ? 96 : 128;
+  const int n_equal = (pl->R + 63) / 64;
+  pl->row_chunk = one_chunk ? (pl->R <= 96 ? 96 : 128) : f32 && pl->R > 64 ? 64 : ((pl->R + n_equal - 1) / n_equal + 15) / 16 * 16;
   // short caches are bound by latency, not bytes: thin slices on many compute units win (bf16, 1896 rows, 7 query
   // rows: 59 slices of 32 rows beat 14 of 128 by 9 %)
   pl->n_chunks = (pl->R + pl->row_chunk - 1) / pl->row_chunk;

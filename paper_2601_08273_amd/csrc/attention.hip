@@ -391,7 +391,10 @@ __global__ __launch_bounds__(RB * TG * 64) void attn_partial_grid(AttnParams p) 
     const float mx = m8 * scale_log2;                      // scale > 0: max commutes with it
     // lazy rescale: the reference m_run moves only when the tile maximum exceeds it by more than
     // kRescaleGap, so probabilities stay below 2^kRescaleGap and rescales are rare
-    const bool up = mx > m_run + kRescaleGap;              // also true for the first finite maximum
+    // (long slices of 16-token tiles take the second tile's maximum too: the further the slice's largest probabilities lie
+    // above the reference, the smaller their significands and the larger their rounding, 0.4 % of the output's error)
+    const float gap = ROT && TT == 16 && si == 1 ? 0.f : kRescaleGap;
+    const bool up = mx > m_run + gap;                      // also true for the first finite maximum
     if (__any(up)) {
       const float a = up ? fast_exp2(m_run - mx) : 1.f;    // m_run = -inf -> 0
       if (up) m_run = mx;
@@ -973,14 +976,26 @@ template <int D, int RB>
 static hipError_t launch_grid_rb(const AttnParams& p, hipStream_t st) {
   const int tiles32_per_block = ((p.n_total + 31) / 32) / (p.S > 0 ? p.S : 1);
   const bool small_tiles = tiles32_per_block < 24;
-  if (!small_tiles)
-    return stream_exceeds_caches(p, D, 2) ? launch_grid<D, RB, 4, 32, 2, true, true>(p, st)
-                                          : launch_grid<D, RB, 4, 32, 2, false, true>(p, st);
+  if (!small_tiles) {
+    const bool nt = stream_exceeds_caches(p, D, 2);
+    // Three and four row blocks: stages of 16-token tiles, four of them, keep three quarters of the ring in flight under a
+    // stage's products, two of 32-token tiles half of it.  That pays where the tiles come from the L2 (the second row chunk
+    // of a slice runs on the same XCD; us a call in chunks of 48: 33K x 4 heads, 91 rows, paged 27.2 -> 24.7; 2 x 8 heads x
+    // 20K, 96 rows 47.7 -> 42.2; 4 x 8 x 36K, 72 rows 147 -> 128) and for rows of 64 channels, whose 32-token ring is half
+    // as large (3 x 2 heads x 70K, 42 rows 26.9 -> 25.2, 91 rows 41.0 -> 37.8); one chunk of 128 channels has HBM to wait for,
+    // and the fewer barriers of the larger tiles are worth 1 to 3 % (2 x 8 x 37K, 64 rows 58.3 against 59.8).
+    if constexpr (RB >= 3)
+      if (D == 64 || p.n_chunks > 1)
+        return nt ? launch_grid<D, RB, 4, 16, 4, true, true>(p, st) : launch_grid<D, RB, 4, 16, 4, false, true>(p, st);
+    return nt ? launch_grid<D, RB, 4, 32, 2, true, true>(p, st) : launch_grid<D, RB, 4, 32, 2, false, true>(p, st);
+  }
   // measured at the 16K configuration: with 3-4 row blocks, two token groups and a four-stage ring
   // (the whole slice in flight at once) beat four groups by ~8 %; the block merge moves half the data
-  // four row blocks (49-64 query rows) over slices of 12-23 32-token tiles, the 33K long-video shape:
-  // the per-tile work of the vector unit weighs most there, and 32-token tiles halve it per token
-  if (RB == 4 && tiles32_per_block >= 12) return launch_grid<D, RB, 2, 32, 3>(p, st);
+  // four row blocks (49-64 query rows) over slices of 12-23 32-token tiles, three over 16-23, the 33K long-video shape:
+  // the per-tile work of the vector unit weighs most there, and 32-token tiles halve it per token (three row blocks, 42
+  // rows, us a call: 33K 19.6 -> 18.9, 40K 21.2 -> 20.9; at 26K, 12 tiles, 16.2 against 16.4; two chunks of 48, 84 rows at 16K
+  // 17.6 -> 16.1)
+  if (RB >= 3 && tiles32_per_block >= (RB == 4 ? 12 : 16)) return launch_grid<D, RB, 2, 32, 3>(p, st);
   if (RB >= 3) return launch_grid<D, RB, 2, 16, 4>(p, st);
   return launch_grid<D, RB, 4, 16, 3>(p, st);
 }
