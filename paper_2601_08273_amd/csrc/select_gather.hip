@@ -6,6 +6,8 @@
 // radix select finds the k-th largest key, and an index-ordered compaction emits every key above
 // it plus the first (lowest-index) ties.  All counting is integer, so there is no run-to-run
 // variation.
+#include <algorithm>
+
 #include "common.h"
 
 namespace hippo {
@@ -20,6 +22,7 @@ constexpr int kKeysPerThread = 72;
 constexpr int kPackedCounts = 40;        // keys per thread up to which two counts of a block fit 16 bits each
 constexpr int kBins = 4096;              // 12-bit digits (the last pass uses 256 of them)
 constexpr int kHistStride = kBins + kBins / 64;   // padded histogram
+constexpr int kHistWords = 2 * kHistStride + 256 + 4;   // one per radix pass; indices, once the threshold is known (GATHER)
 __device__ __forceinline__ int hist_slot(int bin) { return bin + (bin >> 6); }
 
 // larger score -> larger key; -0 == +0; NaN -> 1, below every number (-inf maps to 0x00800000).
@@ -94,6 +97,11 @@ __device__ __forceinline__ unsigned block_scan_excl(unsigned mine, unsigned* tot
   return incl - mine + waves_in_front((unsigned)__builtin_amdgcn_readlane((int)incl, 63), tot, lane, wave);
 }
 
+// byte offset of vector e's place inside the row that starts at element `row`
+__device__ __forceinline__ long long gather_offset(long long row, const SelectParams& p, int e, int vpr_shift) {
+  return row * p.elem_bytes + (e & ((1 << vpr_shift) - 1)) * 16;
+}
+
 // One block per sequence.  NC > 0: every thread keeps NC keys in registers, so the scores are read
 // from memory once and every loop over them is unrolled to the sequence's size class.  A wave owns
 // 64 NC consecutive scores, dealt to its lanes VW at a time (slot c of lane l is score
@@ -106,18 +114,23 @@ __device__ __forceinline__ unsigned block_scan_excl(unsigned mine, unsigned* tot
 // third histogram are built from that list instead of from another sweep over every thread's keys.
 // The compaction is index-ordered: when the keys are cached, one wave scan per group of VW slots plus
 // one scan of the wave totals, per-(chunk, wave) ballots with running totals otherwise.
-template <int NC>
-__global__ __launch_bounds__(kSelThreads) void topk_select(SelectParams p) {
+//
+// GATHER: the launch builds the draft cache too.  Grid (H_kv * parts, B): every block selects for itself -- the same
+// integers, while all compute units but one would idle -- keeps the indices in LDS and copies its part of one KV head's
+// rows.  Saves a launch on the host (4 us) and its start on the GPU (16384 tokens x 4 heads, 10 %: 9.2 + 4.3 us of kernels
+// -> 12.1, the call 18.2 -> 15.5; 1568 x 2 heads 4.1 + 2.6 -> 6.3; 4 x 36864 x 8 heads 18.6 + 20.7 -> 37.8).
+template <int NC, bool GATHER>
+__global__ __launch_bounds__(kSelThreads) void topk_select(SelectParams p, int vpr_shift) {
   constexpr bool CACHED = NC > 0;
+  static_assert(CACHED || !GATHER, "the indices are in LDS only where the keys are in registers");
   // one histogram per radix pass (12, 12, 8 bits); bin i lives at i + i/64, so that the 64 lanes of
   // the scanning wave, which own runs of 64 consecutive bins, hit different LDS banks
-  constexpr int kHistWords = 2 * kHistStride + 256 + 4;
   constexpr int kListCap = kBins;            // candidate list: the first histogram's memory, once its digit is known
   __shared__ unsigned hist[kHistWords];
   __shared__ unsigned wave_tot[2][kSelWaves];
   __shared__ unsigned sh_prefix, sh_need, sh_bin_count, sh_list_n;
 
-  const int b = blockIdx.x, tid = threadIdx.x;
+  const int b = GATHER ? blockIdx.y : blockIdx.x, tid = threadIdx.x;
   const int lane = tid & 63, wave = tid >> 6;
   const float* sc = p.scores + (long long)b * p.Nv;
   int32_t* out = p.idx_out + (long long)b * p.k;
@@ -267,7 +280,7 @@ __global__ __launch_bounds__(kSelThreads) void topk_select(SelectParams p) {
       gt_front = waves_in_front(run >> 16, wave_tot[0], lane, wave);
       eq_front = waves_in_front(run & 0xffffu, wave_tot[1], lane, wave);
     }
-    int32_t* const dst = out;
+    const bool writes = !GATHER || blockIdx.x == 0;
 #pragma unroll
     for (int v = 0; v < NV; ++v) {
       unsigned gt_before = gt_front + (excl[v] >> 16), eq_before = eq_front + (excl[v] & 0xffffu);
@@ -275,9 +288,39 @@ __global__ __launch_bounds__(kSelThreads) void topk_select(SelectParams p) {
       for (int e = 0; e < VW; ++e) {
         const unsigned key = keys[v * VW + e];
         const bool gt = key > thr, eq = key == thr;
-        if (gt || (eq && eq_before < need_eq)) dst[gt_before + min(eq_before, need_eq)] = slot_index(v * VW + e);
+        if (gt || (eq && eq_before < need_eq)) {
+          const unsigned at = gt_before + min(eq_before, need_eq);
+          if (writes) out[at] = slot_index(v * VW + e);
+          if (GATHER) hist[at] = (unsigned)slot_index(v * VW + e);
+        }
         gt_before += gt ? 1u : 0u;
         eq_before += eq ? 1u : 0u;
+      }
+    }
+    if constexpr (GATHER) {
+      __syncthreads();
+      const int hk = blockIdx.x % p.Hkv, part = blockIdx.x / p.Hkv, parts = gridDim.x / p.Hkv;
+      const int per_head = p.dst_len << vpr_shift;
+      constexpr int U = 4;                       // vectors of K and of V in flight per thread
+      for (int e0 = part * kSelThreads + tid; e0 < per_head; e0 += U * parts * kSelThreads) {
+        u32x4 kv[U], vv[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          const int e = min(e0 + u * parts * kSelThreads, per_head - 1);     // past the end: a repeat, not stored
+          const int n = e >> vpr_shift, kept = min(max(n - p.vis_off, 0), p.k - 1);
+          const int from = n < p.vis_off ? n : n < p.vis_off + p.k ? p.vis_off + (int)hist[kept] : n - p.k + p.Nv;
+          const long long so = gather_offset(b * p.ssb + hk * p.ssh + from * p.ssn, p, e, vpr_shift);
+          kv[u] = *(const u32x4*)((const char*)p.k_src + so);
+          vv[u] = *(const u32x4*)((const char*)p.v_src + so);
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          const int e = e0 + u * parts * kSelThreads;
+          if (e >= per_head) break;
+          const long long dof = gather_offset(b * p.dsb + hk * p.dsh + (e >> vpr_shift) * p.dsn, p, e, vpr_shift);
+          *(u32x4*)((char*)p.k_dst + dof) = kv[u];
+          *(u32x4*)((char*)p.v_dst + dof) = vv[u];
+        }
       }
     }
   } else {
@@ -336,27 +379,38 @@ __global__ __launch_bounds__(256) void gather_kv(SelectParams p, int vpr_shift) 
 
 hipError_t launch_select_gather(const SelectParams& p, hipStream_t st) {
   const int n_chunks = (p.Nv + kSelThreads - 1) / kSelThreads;
-#define HIPPO_TOPK(NC_) hipLaunchKernelGGL(topk_select<NC_>, dim3(p.B), dim3(kSelThreads), 0, st, p)
-  if (n_chunks <= 2) HIPPO_TOPK(2);
-  else if (n_chunks <= 4) HIPPO_TOPK(4);
-  else if (n_chunks <= 8) HIPPO_TOPK(8);
-  else if (n_chunks <= 16) HIPPO_TOPK(16);
-  else if (n_chunks <= 24) HIPPO_TOPK(24);
-  else if (n_chunks <= 32) HIPPO_TOPK(32);
-  else if (n_chunks <= 40) HIPPO_TOPK(40);
-  else if (n_chunks <= 56) HIPPO_TOPK(56);
-  else if (n_chunks <= kKeysPerThread) HIPPO_TOPK(kKeysPerThread);
-  else HIPPO_TOPK(0);
-#undef HIPPO_TOPK
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess || p.k_dst == nullptr) return e;
   const int vpr = p.D * p.elem_bytes / 16;                 // 16-byte vectors per row: 4, 8, 16 or 32
   int vpr_shift = 0;
   while ((1 << vpr_shift) < vpr) ++vpr_shift;
-  if ((1 << vpr_shift) != vpr || p.Hkv > 65535 || p.B > 65535) return hipErrorInvalidValue;
-  const long long per_head = (long long)p.dst_len * vpr;
-  if (per_head == 0) return hipSuccess;
+  const bool gather = p.k_dst != nullptr;
+  const long long per_head = gather ? (long long)p.dst_len * vpr : 0;
+  if (gather && ((1 << vpr_shift) != vpr || p.Hkv > 65535 || p.B > 65535)) return hipErrorInvalidValue;
   if ((per_head + 255) / 256 > 0x7fffffffll) return hipErrorInvalidValue;
+  // One launch wherever the keys stay in registers without spilling and the indices fit the histograms' LDS (8576).  A block
+  // takes two vectors a thread, up to a block per compute unit: with one vector twice the blocks fetch the scores and run
+  // the histograms side by side (40320 tokens x 8 heads 22.8 against 22.0 us a call), with four there are too few (22.5).
+  const bool one_launch = per_head > 0 && n_chunks <= kPackedCounts && p.k <= kHistWords && per_head <= (1ll << 24);
+  const long long parts = std::max<long long>(1, std::min<long long>((per_head + 2 * kSelThreads - 1) / (2 * kSelThreads),
+                                                                     kNumCU / ((long long)p.B * p.Hkv)));
+#define HIPPO_TOPK(NC_)                                                                                      \
+  if (one_launch)                                                                                            \
+    hipLaunchKernelGGL((topk_select<NC_, (NC_ > 0 && NC_ <= kPackedCounts)>), dim3((unsigned)(p.Hkv * parts), p.B), \
+                       dim3(kSelThreads), 0, st, p, vpr_shift);                                              \
+  else                                                                                                       \
+    hipLaunchKernelGGL((topk_select<NC_, false>), dim3(p.B), dim3(kSelThreads), 0, st, p, vpr_shift)
+  if (n_chunks <= 2) { HIPPO_TOPK(2); }
+  else if (n_chunks <= 4) { HIPPO_TOPK(4); }
+  else if (n_chunks <= 8) { HIPPO_TOPK(8); }
+  else if (n_chunks <= 16) { HIPPO_TOPK(16); }
+  else if (n_chunks <= 24) { HIPPO_TOPK(24); }
+  else if (n_chunks <= 32) { HIPPO_TOPK(32); }
+  else if (n_chunks <= 40) { HIPPO_TOPK(40); }
+  else if (n_chunks <= 56) { HIPPO_TOPK(56); }
+  else if (n_chunks <= kKeysPerThread) { HIPPO_TOPK(kKeysPerThread); }
+  else { HIPPO_TOPK(0); }
+#undef HIPPO_TOPK
+  const hipError_t e = hipGetLastError();
+  if (e != hipSuccess || per_head == 0 || one_launch) return e;
   hipLaunchKernelGGL(gather_kv, dim3((unsigned)((per_head + 255) / 256), p.Hkv, p.B), dim3(256), 0, st, p, vpr_shift);
   return hipGetLastError();
 }

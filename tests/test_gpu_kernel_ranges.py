@@ -354,3 +354,31 @@ def test_topk_of_long_sequences(hippo, n, ties):
         idx, _, _ = hippo.hippo_select_gather_kv(torch.from_numpy(s).cuda(), k, cache, cache, vid, gather=False)
         want = np.sort(np.argsort(-s, axis=1, kind="stable")[:, :k], axis=1)
         np.testing.assert_array_equal(idx.cpu().numpy(), want)
+
+
+@pytest.mark.parametrize("shape", [
+    # B, heads, d, tokens, k: one block a head and several; more heads than compute units share, heads that do not divide
+    # them; the last indices that fit LDS and one more; the last tokens that registers hold and one more; all kept
+    (1, 1, 64, 1, 1), (2, 3, 128, 1025, 600), (1, 300, 64, 70, 33), (3, 7, 64, 4097, 1000), (1, 2, 64, 9000, 8576),
+    (1, 2, 64, 9000, 8577), (1, 1, 128, 40960, 4000), (1, 1, 128, 40961, 4000), (40, 8, 64, 97, 97),
+])
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32, torch.uint8])
+def test_draft_cache_in_one_launch(hippo, shape, dtype):
+    B, Hkv, d, n, k = shape
+    g = torch.Generator(device="cuda").manual_seed(n + k)
+    scores = torch.randint(0, 50, (B, n), generator=g, device="cuda").float()         # ties at the threshold
+    N = n + 11
+    kc, vc = (torch.randint(0, 250, (B, N, Hkv, d), generator=g, device="cuda").to(dtype).transpose(1, 2) for _ in range(2))
+    vid = hippo.video_desc(1, 1, n, 4)
+    idx, ref_idx = [hippo.hippo_select_gather_kv(scores, k, kc, vc, vid, gather=flag)[0] for flag in (True, False)]
+    assert torch.equal(idx, ref_idx)                                                  # with the gather, and without
+    order = torch.sort(scores, dim=1, descending=True, stable=True).indices[:, :k].sort(1).values
+    assert torch.equal(idx.long(), order)
+    dst = [torch.full((B, Hkv, 11 + k, d + 16), 7, device="cuda").to(dtype) for _ in range(2)]
+    out = [x[..., :d] for x in dst]                                                   # rows with a gap behind them
+    hippo.hippo_select_gather_kv(scores, k, kc, vc, vid, k_dst=out[0], v_dst=out[1])
+    rows = torch.cat([torch.arange(4, device="cuda").expand(B, 4), 4 + order,
+                      torch.arange(4 + n, N, device="cuda").expand(B, 7)], 1)
+    for src, got, whole in zip((kc, vc), out, dst):
+        assert torch.equal(got, torch.stack([src[b][:, rows[b]] for b in range(B)]))
+        assert bool((whole[..., d:].float() == 7).all())
