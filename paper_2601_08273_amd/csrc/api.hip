@@ -91,6 +91,12 @@ int plan_attention(int call, const hippo_kv_desc* kv, int q_len, int n_total, in
     S = (int)(kNumCU / per_split);          // rounded down: a block beyond the last compute unit would share one
     if (S < 1) S = 1;
     if (S > fit) S = (int)fit;
+    // A cache of a few tiles under up to 16 query rows goes in one slice, whose block writes the output itself: no merge
+    // launch.  Where the line lies, us a call in a graph, slices and merge -> one slice (eager 10.7 -> 8): bf16, 7 rows,
+    // 4 heads x 128: 100 rows 6.2 -> 4.1, 250 6.2 -> 5.3, 500 6.3 -> 8.3; fp32: 100 8.1 -> 7.1, 250 8.0 -> 10.8; bf16, 35 rows:
+    // 100 6.7 -> 5.5, 250 6.9 -> 7.6.
+    const int few_tiles = pl->R > 16 ? 0 : f32 ? 4 : 8;
+    if (n_tiles <= few_tiles) S = 1;
   }
   if (S > n_tiles) S = n_tiles;
   if (S < 1) S = 1;

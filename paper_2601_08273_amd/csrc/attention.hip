@@ -35,6 +35,13 @@ __device__ __forceinline__ void append_new_rows(const AttnParams& p, int b, int 
   }
 }
 
+// Element 0 of query row `row` of (b, hk) in the output, and the row's place in lse [B, H, q_len].
+__device__ __forceinline__ long long out_row(const AttnParams& p, int b, int hk, int row, float inv_g, long long* lse_at) {
+  const int i = row_div_group(row, inv_g), h = hk * p.G + row - i * p.G;
+  *lse_at = ((long long)b * p.H + h) * p.q_len + i;
+  return (((long long)b * p.q_len + i) * p.H + h);
+}
+
 // =================================================================================================
 // MFMA partial kernel (bf16): helpers
 // =================================================================================================
@@ -124,7 +131,9 @@ __device__ __forceinline__ bf16x8 e4m3x8_to_bf16(int lo, int hi) {
 
 // TT = tokens per tile (16 or 32), NST = ring stages (super-tiles resident in LDS)
 // MODE: 0 = contiguous cache, 1 = contiguous cache with appended-row fusion, 2 = paged cache
-template <int D, int RB, int TG, int TT, int NST, int MODE, bool KV8 = false, bool NT = false, bool ROT = false>
+// ONE = the slice is the whole cache: the block writes its rows' output
+template <int D, int RB, int TG, int TT, int NST, int MODE, bool KV8 = false, bool NT = false, bool ROT = false,
+          bool ONE = false>
 __global__ __launch_bounds__(RB * TG * 64) void attn_partial_grid(AttnParams p) {
   constexpr bool APPEND = MODE == 1, PAGED = MODE == 2;
   constexpr int ES = KV8 ? 1 : 2;                      // bytes per cache element
@@ -484,6 +493,14 @@ __global__ __launch_bounds__(RB * TG * 64) void attn_partial_grid(AttnParams p) 
 #pragma unroll
       for (int w = 0; w < TG; ++w) f[w] *= v_mult;         // after the denominator took the plain weights
     }
+    long long lse_at = 0;
+    uint16_t* o_row = (uint16_t*)p.part_o + (slot * p.R + row) * D;
+    if constexpr (ONE) {
+      o_row = (uint16_t*)p.out + out_row(p, b, hk, row, inv_g, &lse_at) * D;
+      const float inv = 1.f / ll;
+#pragma unroll
+      for (int w = 0; w < TG; ++w) f[w] *= inv;
+    }
 #pragma unroll
     for (int dd = 0; dd < DB / TG; ++dd) {
       const int db = TGC + TG * dd;
@@ -501,12 +518,16 @@ __global__ __launch_bounds__(RB * TG * 64) void attn_partial_grid(AttnParams p) 
         uint2 w;
         w.x = __builtin_bit_cast(unsigned, __builtin_convertvector(lo, bf16x2_t));
         w.y = __builtin_bit_cast(unsigned, __builtin_convertvector(hi, bf16x2_t));
-        *(uint2*)((uint16_t*)p.part_o + (slot * p.R + row) * D + db * 16 + 4 * g) = w;
+        *(uint2*)(o_row + db * 16 + 4 * g) = w;
       }
     }
     if (TGC == 0 && g == 0 && row < p.R) {
-      p.part_m[slot * p.R + row] = mm;
-      p.part_l[slot * p.R + row] = ll;
+      if constexpr (ONE) {
+        if (p.lse != nullptr) p.lse[lse_at] = (mm + __log2f(ll)) * kLn2;
+      } else {
+        p.part_m[slot * p.R + row] = mm;
+        p.part_l[slot * p.R + row] = ll;
+      }
     }
   };
   static_assert(TG == 1 || TG == 2 || TG == 4, "token groups");
@@ -561,7 +582,7 @@ struct F32Smem {
   }
 };
 
-template <int D, int RB, int TG, int NST, int MODE>
+template <int D, int RB, int TG, int NST, int MODE, bool ONE = false>
 __global__ __launch_bounds__(RB * TG * 64) void attn_partial_f32(AttnParams p) {
   constexpr bool APPEND = MODE == 1, PAGED = MODE == 2;
   using SM = F32Smem<D, TG, NST>;
@@ -766,6 +787,13 @@ __global__ __launch_bounds__(RB * TG * 64) void attn_partial_f32(AttnParams p) {
   const long long slot = ((long long)b * p.Hkv + hk) * p.S + split;
   if (row < p.R) {
     float* o_row = (float*)p.part_o + (slot * p.R + row) * D + 16 * g;
+    long long lse_at = 0;
+    if constexpr (ONE) {
+      o_row = (float*)p.out + out_row(p, b, hk, row, inv_g, &lse_at) * D + 16 * g;
+      const float inv = 1.f / ll;
+#pragma unroll
+      for (int w = 0; w < TG; ++w) f[w] *= inv;
+    }
 #pragma unroll
     for (int vv = 0; vv < NV / TG; ++vv) {
       const int v = vv * TG + tg;
@@ -775,8 +803,12 @@ __global__ __launch_bounds__(RB * TG * 64) void attn_partial_f32(AttnParams p) {
       *(f32x4*)(o_row + 64 * (v / 4) + 4 * (v % 4)) = o;
     }
     if (tg == 0 && g == 0) {
-      p.part_m[slot * p.R + row] = mm;
-      p.part_l[slot * p.R + row] = ll;
+      if constexpr (ONE) {
+        if (p.lse != nullptr) p.lse[lse_at] = (mm + __log2f(ll)) * kLn2;
+      } else {
+        p.part_m[slot * p.R + row] = mm;
+        p.part_l[slot * p.R + row] = ll;
+      }
     }
   }
   if (APPEND && split == 0 && chunk == 0) append_new_rows<float, D>(p, b, hk);
@@ -938,29 +970,35 @@ static hipError_t allow_dynamic_lds(int smem) {
   return hipSuccess;
 }
 
-template <int D, int RB, int TG, int TT, int NST, int MODE, bool KV8 = false, bool NT = false, bool ROT = false>
+template <int D, int RB, int TG, int TT, int NST, int MODE, bool KV8 = false, bool NT = false, bool ROT = false,
+          bool ONE = false>
 static hipError_t launch_grid_mode(const AttnParams& p, hipStream_t st) {
   // the paged variant keeps its slice of the page table behind the ring
   constexpr int smem = GridSmem<D, TG, TT, NST, KV8 ? 1 : 2>::total(RB) + (MODE == 2 ? kMaxSlicePages * 4 : 0);
-  const hipError_t e = allow_dynamic_lds<attn_partial_grid<D, RB, TG, TT, NST, MODE, KV8, NT, ROT>>(smem);
+  const hipError_t e = allow_dynamic_lds<attn_partial_grid<D, RB, TG, TT, NST, MODE, KV8, NT, ROT, ONE>>(smem);
   if (e != hipSuccess) return e;
   dim3 grid(p.S, p.Hkv, p.B * p.n_chunks);
   AttnParams q = p;                               // the slices' tile counts for this kernel's tile size
   const int n_tiles = (p.n_total + TT - 1) / TT;
   q.tiles_q = n_tiles / p.S;
   q.tiles_r = n_tiles % p.S;
-  hipLaunchKernelGGL((attn_partial_grid<D, RB, TG, TT, NST, MODE, KV8, NT, ROT>), grid, dim3(RB * TG * 64), smem, st, q);
+  hipLaunchKernelGGL((attn_partial_grid<D, RB, TG, TT, NST, MODE, KV8, NT, ROT, ONE>), grid, dim3(RB * TG * 64), smem, st, q);
   return hipGetLastError();
 }
 
 // the appended-row and paged variants are separate instantiations, so the plain call carries none of
 // their address selects
-template <int D, int RB, int TG, int TT, int NST, bool NT = false, bool ROT = false>
+template <int D, int RB, int TG, int TT, int NST, bool NT = false, bool ROT = false, bool ONE = false>
 static hipError_t launch_grid(const AttnParams& p, hipStream_t st) {
-  if (p.block_table != nullptr) return launch_grid_mode<D, RB, TG, TT, NST, 2, false, NT, ROT>(p, st);
-  if (p.k_new != nullptr) return launch_grid_mode<D, RB, TG, TT, NST, 1, false, NT, ROT>(p, st);
-  return launch_grid_mode<D, RB, TG, TT, NST, 0, false, NT, ROT>(p, st);
+  if (p.block_table != nullptr) return launch_grid_mode<D, RB, TG, TT, NST, 2, false, NT, ROT, ONE>(p, st);
+  if (p.k_new != nullptr) return launch_grid_mode<D, RB, TG, TT, NST, 1, false, NT, ROT, ONE>(p, st);
+  return launch_grid_mode<D, RB, TG, TT, NST, 0, false, NT, ROT, ONE>(p, st);
 }
+
+// Up to 16 query rows and one slice of a short cache (the library's choice up to 256 rows, 128 in fp32): the block
+// writes the output, and no merge is launched.  An instantiation of its own: as a branch of the others' epilogue it cost
+// them up to 0.1 us.
+static bool one_slice_call(const AttnParams& p) { return p.S == 1 && p.row_chunk == 16 && (p.n_total + 31) / 32 < 24; }
 
 // A call whose K and V exceed the chip's last-level cache (256 MB) streams them with non-temporal
 // transfers: nothing of such a stream can be served from a cache again, and left to itself it evicts
@@ -997,6 +1035,8 @@ static hipError_t launch_grid_rb(const AttnParams& p, hipStream_t st) {
   // 17.6 -> 16.1)
   if (RB >= 3 && tiles32_per_block >= (RB == 4 ? 12 : 16)) return launch_grid<D, RB, 2, 32, 3>(p, st);
   if (RB >= 3) return launch_grid<D, RB, 2, 16, 4>(p, st);
+  if constexpr (RB == 1)
+    if (one_slice_call(p)) return launch_grid<D, RB, 4, 16, 3, false, false, true>(p, st);
   return launch_grid<D, RB, 4, 16, 3>(p, st);
 }
 
@@ -1005,6 +1045,8 @@ static hipError_t launch_grid_rb(const AttnParams& p, hipStream_t st) {
 template <int D, int RB>
 static hipError_t launch_kv8_rb(const AttnParams& p, hipStream_t st) {
   const int tiles32_per_block = ((p.n_total + 31) / 32) / (p.S > 0 ? p.S : 1);
+  if constexpr (RB == 1)
+    if (one_slice_call(p)) return launch_grid_mode<D, RB, 2, 32, 4, 0, true, false, false, true>(p, st);
   if (tiles32_per_block < 24)
     return launch_grid_mode<D, RB, 2, 32, 4, 0, true>(p, st);
   if (stream_exceeds_caches(p, D, 1)) return launch_grid_mode<D, RB, 4, 32, 2, 0, true, true, true>(p, st);
@@ -1033,25 +1075,25 @@ static hipError_t launch_mfma_d(const AttnParams& p, hipStream_t st) {
   }
 }
 
-template <int D, int RB, int TG, int NST, int MODE>
+template <int D, int RB, int TG, int NST, int MODE, bool ONE>
 static hipError_t launch_f32_mode(const AttnParams& p, hipStream_t st) {
   constexpr int smem = F32Smem<D, TG, NST>::total(RB) + (MODE == 2 ? kMaxSlicePages * 4 : 0);
-  const hipError_t e = allow_dynamic_lds<attn_partial_f32<D, RB, TG, NST, MODE>>(smem);
+  const hipError_t e = allow_dynamic_lds<attn_partial_f32<D, RB, TG, NST, MODE, ONE>>(smem);
   if (e != hipSuccess) return e;
   AttnParams q = p;
   const int n_tiles = (p.n_total + 15) / 16;
   q.tiles_q = n_tiles / p.S;
   q.tiles_r = n_tiles % p.S;
-  hipLaunchKernelGGL((attn_partial_f32<D, RB, TG, NST, MODE>), dim3(p.S, p.Hkv, p.B * p.n_chunks), dim3(RB * TG * 64),
+  hipLaunchKernelGGL((attn_partial_f32<D, RB, TG, NST, MODE, ONE>), dim3(p.S, p.Hkv, p.B * p.n_chunks), dim3(RB * TG * 64),
                      smem, st, q);
   return hipGetLastError();
 }
 
-template <int D, int RB, int TG, int NST>
+template <int D, int RB, int TG, int NST, bool ONE = false>
 static hipError_t launch_f32(const AttnParams& p, hipStream_t st) {
-  if (p.block_table != nullptr) return launch_f32_mode<D, RB, TG, NST, 2>(p, st);
-  if (p.k_new != nullptr) return launch_f32_mode<D, RB, TG, NST, 1>(p, st);
-  return launch_f32_mode<D, RB, TG, NST, 0>(p, st);
+  if (p.block_table != nullptr) return launch_f32_mode<D, RB, TG, NST, 2, ONE>(p, st);
+  if (p.k_new != nullptr) return launch_f32_mode<D, RB, TG, NST, 1, ONE>(p, st);
+  return launch_f32_mode<D, RB, TG, NST, 0, ONE>(p, st);
 }
 
 // row blocks x token groups: four groups while LDS and sixteen waves allow them
@@ -1060,7 +1102,7 @@ static hipError_t launch_f32_d(const AttnParams& p, hipStream_t st) {
   // ring stages: what 160 KB of LDS hold beside the queries
   constexpr bool W = D == 128;
   switch (p.row_chunk / 16) {
-    case 1: return launch_f32<D, 1, 4, W ? 2 : 4>(p, st);
+    case 1: return one_slice_call(p) ? launch_f32<D, 1, 4, W ? 2 : 4, true>(p, st) : launch_f32<D, 1, 4, W ? 2 : 4>(p, st);
     case 2: return launch_f32<D, 2, 4, W ? 2 : 4>(p, st);
     case 3: return launch_f32<D, 3, 4, W ? 2 : 4>(p, st);
     case 4: return launch_f32<D, 4, W ? 2 : 4, W ? 3 : 4>(p, st);
@@ -1081,11 +1123,11 @@ hipError_t launch_attention(const AttnParams& p, int dtype, int head_dim, hipStr
   if (dtype == HIPPO_DTYPE_BF16) {
     if (p.k_scale != nullptr) e = (head_dim == 128) ? launch_kv8_d<128>(p, st) : launch_kv8_d<64>(p, st);
     else e = (head_dim == 128) ? launch_mfma_d<128>(p, st) : launch_mfma_d<64>(p, st);
-    if (e != hipSuccess) return e;
+    if (e != hipSuccess || one_slice_call(p)) return e;
     return (head_dim == 128) ? launch_combine<uint16_t, 128, true>(p, st) : launch_combine<uint16_t, 64, true>(p, st);
   }
   e = (head_dim == 128) ? launch_f32_d<128>(p, st) : launch_f32_d<64>(p, st);
-  if (e != hipSuccess) return e;
+  if (e != hipSuccess || one_slice_call(p)) return e;
   return (head_dim == 128) ? launch_combine<float, 128, false>(p, st) : launch_combine<float, 64, false>(p, st);
 }
 

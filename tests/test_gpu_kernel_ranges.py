@@ -57,6 +57,34 @@ def test_more_than_64_rows(hippo, shape, d):
     assert torch.equal(hippo.hippo_verify_attention_paged(qd, *pools, table, ctx, num_splits=S), plain), what
 
 
+@pytest.mark.parametrize("dtype", ["fp32", "bf16", "fp8"])
+@pytest.mark.parametrize("shape", [
+    # q_len, G, ctx: up to 16 query rows and 128 (fp32) or 256 rows of cache by the library's choice, and just beyond; one
+    # slice asked for up to 736 rows and beyond; an empty context
+    (2, 8, 0), (1, 7, 127), (1, 7, 128), (4, 4, 252), (4, 4, 253), (2, 9, 126), (1, 16, 735), (1, 16, 736), (13, 7, 115),
+])
+def test_one_slice_writes_the_output(hippo, shape, dtype):
+    q_len, G, ctx = shape
+    for d in (64, 128):
+        q, k, v = attention_inputs(ctx + d, 3, q_len, 2 * G, 2, d, ctx, "fp32" if dtype == "fp32" else "bf16")
+        if dtype == "fp8":
+            kd, vd = dev(k, "bf16"), dev(v, "bf16")
+            codes = hippo.hippo_quantize_kv_e4m3(kd, vd)
+            k, v = (host(c.view(torch.float8_e4m3fn).float()) * host(m)[..., None, None] for c, m in
+                    ((codes[0], codes[2]), (codes[1], codes[3])))
+            call = lambda S: hippo.hippo_verify_attention_fp8kv(dev(q, "bf16"), *codes, ctx, num_splits=S, want_lse=True)
+        else:
+            kd, vd = dev(k, dtype), dev(v, dtype)
+            call = lambda S: hippo.hippo_verify_attention(dev(q, dtype), kd, vd, ctx, num_splits=S, want_lse=True)
+        ref, ref_lse = oracle.attention(q, k, v, ctx, None)
+        tol = "fp32" if dtype == "fp32" else "bf16"
+        for S in (0, 1, 2):
+            out, lse = call(S)
+            assert_close(host(out), ref, tol, "%s d=%d S=%d" % (shape, d, S))
+            # lse inherits the denominator's rounding: 1e-5, or 2^-9 where the probabilities are rounded to bf16
+            np.testing.assert_allclose(host(lse), ref_lse, rtol=0, atol=2e-5 if dtype == "fp32" else 2.0 ** -8)
+
+
 @pytest.mark.parametrize("d", [64, 128])
 @pytest.mark.parametrize("shape", [
     # q_len, G, ctx, slices of 72 to 73 32-token tiles: three row blocks over 14, 18 and 24 tiles a slice; four over 24; two
