@@ -404,8 +404,10 @@ __global__ __launch_bounds__(kSdThreads) void sd_cells(SpecParams p) {
     const float r = wave_sum(sr[v]);
     if (lane == 0) { cells_p[v * kSdWaves + wave] = a; cells_r[v * kSdWaves + wave] = r; }
   }
-  // The last of the sequence's blocks to get here draws the word: the others' cell sums are in memory by then (every
-  // block's count follows its barrier and is a release), nobody waits for anybody.
+  // The last of the sequence's blocks to get here draws the word: the others' cell sums are in memory by then, nobody
+  // waits for anybody.  Each wave waits for its own stores before the barrier: the barrier alone orders them only within
+  // the block, and the release of the thread that counts waits only for its own wave's.
+  wait_vmcnt<0>();
   __syncthreads();
   if (tid == 0) sh_j = __hip_atomic_fetch_add(p.arrived + b, 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
   __syncthreads();
