@@ -386,7 +386,7 @@ hipError_t launch_select_gather(const SelectParams& p, hipStream_t st) {
   const long long per_head = gather ? (long long)p.dst_len * vpr : 0;
   if (gather && ((1 << vpr_shift) != vpr || p.Hkv > 65535 || p.B > 65535)) return hipErrorInvalidValue;
   if ((per_head + 255) / 256 > 0x7fffffffll) return hipErrorInvalidValue;
-  // One launch wherever the keys stay in registers without spilling and the indices fit the histograms' LDS (8576).  A block
+  // One launch wherever the keys stay in registers without spilling and the indices fit the histograms' LDS (8580).  A block
   // takes two vectors a thread, up to a block per compute unit: with one vector twice the blocks fetch the scores and run
   // the histograms side by side (40320 tokens x 8 heads 22.8 against 22.0 us a call), with four there are too few (22.5).
   const bool one_launch = per_head > 0 && n_chunks <= kPackedCounts && p.k <= kHistWords && per_head <= (1ll << 24);
