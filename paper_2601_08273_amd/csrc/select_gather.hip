@@ -389,7 +389,12 @@ hipError_t launch_select_gather(const SelectParams& p, hipStream_t st) {
   // One launch wherever the keys stay in registers without spilling and the indices fit the histograms' LDS (8580).  A block
   // takes two vectors a thread, up to a block per compute unit: with one vector twice the blocks fetch the scores and run
   // the histograms side by side (40320 tokens x 8 heads 22.8 against 22.0 us a call), with four there are too few (22.5).
-  const bool one_launch = per_head > 0 && n_chunks <= kPackedCounts && p.k <= kHistWords && per_head <= (1ll << 24);
+  // Not beyond 128 MiB read and written: there the copy is what the call takes, and blocks of 1024 threads with the keys in
+  // registers copy more slowly than gather_kv's (us a call in a graph, two launches -> one: 4 x 16384 x 8 heads, 100 MB,
+  // 24.2 -> 22.8; 8 x 16384, 112 MB, 25.8 -> 24.1; 2 x 34000, 140 MB, 37.5 -> 37.8; 12 x 16384, 167 MB, 32.9 -> 35.2;
+  // 4 x 34000, 281 MB, 57.7 -> 61.3; 48 x 8192, 182 MB, 33.6 -> 37.1).
+  const bool one_launch = per_head > 0 && n_chunks <= kPackedCounts && p.k <= kHistWords && per_head <= (1ll << 24) &&
+                          per_head * p.B * p.Hkv <= (128ll << 20) / 64;
   const long long parts = std::max<long long>(1, std::min<long long>((per_head + 2 * kSelThreads - 1) / (2 * kSelThreads),
                                                                      kNumCU / ((long long)p.B * p.Hkv)));
 #define HIPPO_TOPK(NC_)                                                                                      \
