@@ -20,6 +20,7 @@ constexpr int kSelWaves = kSelThreads / 64;
 // Longer sequences take the re-reading kernel unchanged (73729 tokens 100, 98304 130; 96 keys a thread would take 48).
 constexpr int kKeysPerThread = 72;
 constexpr int kPackedCounts = 40;        // keys per thread up to which two counts of a block fit 16 bits each
+constexpr int kGatherKeys = 24;          // keys per thread up to which the selecting launch copies the rows too
 constexpr int kBins = 4096;              // 12-bit digits (the last pass uses 256 of them)
 constexpr int kHistStride = kBins + kBins / 64;   // padded histogram
 constexpr int kHistWords = 2 * kHistStride + 256 + 4;   // one per radix pass; indices, once the threshold is known (GATHER)
@@ -118,7 +119,7 @@ __device__ __forceinline__ long long gather_offset(long long row, const SelectPa
 // GATHER: the launch builds the draft cache too.  Grid (H_kv * parts, B): every block selects for itself -- the same
 // integers, while all compute units but one would idle -- keeps the indices in LDS and copies its part of one KV head's
 // rows.  Saves a launch on the host (4 us) and its start on the GPU (16384 tokens x 4 heads, 10 %: 9.2 + 4.3 us of kernels
-// -> 12.1, the call 18.2 -> 15.5; 1568 x 2 heads 4.1 + 2.6 -> 6.3; 4 x 36864 x 8 heads 18.6 + 20.7 -> 37.8).
+// -> 12.1, the call 18.2 -> 15.5; 1568 x 2 heads 4.1 + 2.6 -> 6.3).
 template <int NC, bool GATHER>
 __global__ __launch_bounds__(kSelThreads) void topk_select(SelectParams p, int vpr_shift) {
   constexpr bool CACHED = NC > 0;
@@ -386,20 +387,23 @@ hipError_t launch_select_gather(const SelectParams& p, hipStream_t st) {
   const long long per_head = gather ? (long long)p.dst_len * vpr : 0;
   if (gather && ((1 << vpr_shift) != vpr || p.Hkv > 65535 || p.B > 65535)) return hipErrorInvalidValue;
   if ((per_head + 255) / 256 > 0x7fffffffll) return hipErrorInvalidValue;
-  // One launch wherever the keys stay in registers without spilling and the indices fit the histograms' LDS (8580).  A block
+  // One launch up to 24576 tokens (the selection of longer sequences takes as much longer in every block as the launch
+  // saves: us a call, two launches -> one, 30000 x 4 heads 18.3 -> 18.6, 34000 x 8 28.3 -> 28.4, 4 x 36864 x 8 35.1 -> 35.1;
+  // 20000 x 2 heads x 4 17.4 -> 15.2) whose indices fit the histograms' LDS (8580).  A block
   // takes two vectors a thread, up to a block per compute unit: with one vector twice the blocks fetch the scores and run
-  // the histograms side by side (40320 tokens x 8 heads 22.8 against 22.0 us a call), with four there are too few (22.5).
+  // the histograms side by side (with such a launch over 40320 tokens x 8 heads 22.8 against 22.0 us a call), with four there
+  // are too few (22.5).
   // Not beyond 128 MiB read and written: there the copy is what the call takes, and blocks of 1024 threads with the keys in
   // registers copy more slowly than gather_kv's (us a call in a graph, two launches -> one: 4 x 16384 x 8 heads, 100 MB,
   // 24.2 -> 22.8; 8 x 16384, 112 MB, 25.8 -> 24.1; 2 x 34000, 140 MB, 37.5 -> 37.8; 12 x 16384, 167 MB, 32.9 -> 35.2;
   // 4 x 34000, 281 MB, 57.7 -> 61.3; 48 x 8192, 182 MB, 33.6 -> 37.1).
-  const bool one_launch = per_head > 0 && n_chunks <= kPackedCounts && p.k <= kHistWords && per_head <= (1ll << 24) &&
+  const bool one_launch = per_head > 0 && n_chunks <= kGatherKeys && p.k <= kHistWords && per_head <= (1ll << 24) &&
                           per_head * p.B * p.Hkv <= (128ll << 20) / 64;
   const long long parts = std::max<long long>(1, std::min<long long>((per_head + 2 * kSelThreads - 1) / (2 * kSelThreads),
                                                                      kNumCU / ((long long)p.B * p.Hkv)));
 #define HIPPO_TOPK(NC_)                                                                                      \
   if (one_launch)                                                                                            \
-    hipLaunchKernelGGL((topk_select<NC_, (NC_ > 0 && NC_ <= kPackedCounts)>), dim3((unsigned)(p.Hkv * parts), p.B), \
+    hipLaunchKernelGGL((topk_select<NC_, (NC_ > 0 && NC_ <= kGatherKeys)>), dim3((unsigned)(p.Hkv * parts), p.B), \
                        dim3(kSelThreads), 0, st, p, vpr_shift);                                              \
   else                                                                                                       \
     hipLaunchKernelGGL((topk_select<NC_, false>), dim3(p.B), dim3(kSelThreads), 0, st, p, vpr_shift)

@@ -386,10 +386,10 @@ def test_topk_of_long_sequences(hippo, n, ties):
 
 @pytest.mark.parametrize("shape", [
     # B, heads, d, tokens, k: one block a head and several; more heads than compute units share, heads that do not divide
-    # them; the last indices that fit LDS and one more; the last tokens that registers hold and one more; all kept; more than
+    # them; the last indices that fit LDS and one more; the last tokens of the one launch and one more; all kept; more than
     # 128 MiB to copy, and in 8 bits less
     (1, 1, 64, 1, 1), (2, 3, 128, 1025, 600), (1, 300, 64, 70, 33), (3, 7, 64, 4097, 1000), (1, 2, 64, 9000, 8580),
-    (1, 2, 64, 9000, 8581), (1, 1, 128, 40960, 4000), (1, 1, 128, 40961, 4000), (40, 8, 64, 97, 97), (20, 8, 128, 1000, 900),
+    (1, 2, 64, 9000, 8581), (1, 1, 128, 24576, 4000), (1, 1, 128, 24577, 4000), (40, 8, 64, 97, 97), (20, 8, 128, 1000, 900),
 ])
 @pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32, torch.uint8])
 def test_draft_cache_in_one_launch(hippo, shape, dtype):
