@@ -1032,8 +1032,9 @@ static hipError_t launch_grid_rb(const AttnParams& p, hipStream_t st) {
   // four row blocks (49-64 query rows) over slices of 12-23 32-token tiles, three over 16-23, the 33K long-video shape:
   // the per-tile work of the vector unit weighs most there, and 32-token tiles halve it per token (three row blocks, 42
   // rows, us a call: 33K 19.6 -> 18.9, 40K 21.2 -> 20.9; at 26K, 12 tiles, 16.2 against 16.4; two chunks of 48, 84 rows at 16K
-  // 17.6 -> 16.1)
-  if (RB >= 3 && tiles32_per_block >= (RB == 4 ? 12 : 16)) return launch_grid<D, RB, 2, 32, 3>(p, st);
+  // 17.6 -> 16.1, so two chunks take them from 12 tiles on as well, caches not in the last-level cache: 91 rows, 16000 tokens
+  // 18.6 -> 17.0, chunks of 64 and a rest 18.4; 12500 tokens, 12 tiles, 15.7 against 16.7; 2 x 7000 16.1 against 17.4)
+  if (RB >= 3 && tiles32_per_block >= (RB == 4 || p.n_chunks > 1 ? 12 : 16)) return launch_grid<D, RB, 2, 32, 3>(p, st);
   if (RB >= 3) return launch_grid<D, RB, 2, 16, 4>(p, st);
   if constexpr (RB == 1)
     if (one_slice_call(p)) return launch_grid<D, RB, 4, 16, 3, false, false, true>(p, st);

@@ -88,8 +88,8 @@ def test_one_slice_writes_the_output(hippo, shape, dtype):
 @pytest.mark.parametrize("d", [64, 128])
 @pytest.mark.parametrize("shape", [
     # q_len, G, ctx, slices of 72 to 73 32-token tiles: three row blocks over 14, 18 and 24 tiles a slice; four over 24; two
-    # equal chunks of three blocks over 18 and 24, the second with a row less; four chunks of four
-    (6, 7, 2300, 5), (6, 7, 2300, 4), (6, 7, 2311, 3), (7, 8, 2300, 3), (13, 7, 2290, 4), (11, 7, 2300, 3), (31, 8, 2300, 3),
+    # equal chunks of three blocks over 18 and 24, the second with a row less; four chunks of four; two of three over 12 and 14
+    (6, 7, 2300, 5), (6, 7, 2300, 4), (6, 7, 2311, 3), (7, 8, 2300, 3), (13, 7, 2290, 4), (11, 7, 2300, 3), (31, 8, 2300, 3), (13, 7, 2290, 6), (13, 7, 2290, 5),
 ])
 def test_tile_shapes_by_slice_length_and_rows(hippo, shape, d):
     test_more_than_64_rows(hippo, shape, d)
