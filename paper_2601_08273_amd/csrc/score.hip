@@ -909,8 +909,9 @@ __device__ __align__(16) const unsigned char g_zero_piece[16] = {0};
 template <int U, int NW>
 struct EmbRunSmem {
   static constexpr int MP = 32;
-  __align__(16) unsigned char strip[NW][MP * 64 * U];   // operands in (32 rows x 64 U B), then Gram partials out (3 x 64 x 16 B)
-  float redd[NW][2][16];                            // diagonals of the (this frame) x (frame before) blocks
+  // operands in (32 rows x 64 U B), then Gram partials out (3 x 64 x 16 B, from four waves two sets of them)
+  __align__(16) unsigned char strip[NW][MP * 64 * U];
+  float redd[8][2][16];                             // diagonals of the (this frame) x (frame before) blocks
   float G[MP][MP + 1];
   float dotv[MP];
   float scale[MP];                                  // of the rows' norms, see scale_of
@@ -1043,6 +1044,13 @@ __device__ __forceinline__ void emb_run32_body(const ScoreParams& p, EmbRunSmem<
   const long long out_base = (long long)b * p.Nv + sm.tok_s[a];
 
   const int n_pass = WIDE ? (de + CB - 1) / CB : 1;
+  // Several passes of four waves: odd and even passes are two sets of partial sums, which stand for waves 4 to 7 and 0 to 3
+  // of eight: a frame's Gram and dot products are the same chains of channels, summed in the same order, whichever
+  // kernel takes them.  (One chain over both put the fused score of 512 fp32 channels 1.3 times, of 1024 1.5 times as far
+  // from 64 bits.)
+  constexpr int SETS = WIDE ? 8 / NW : 1;
+  constexpr int kSetBytes = 3 * 64 * 16;
+  static_assert(SETS * kSetBytes <= (int)sizeof(sm.strip[0]) && SETS * NW <= 8, "a strip takes its wave's partial sums");
   constexpr int UP = WIDE ? 1 : U;
   u32x4 prev[2][UP];                                // single pass: the operands of the frame before
 #pragma unroll
@@ -1051,8 +1059,7 @@ __device__ __forceinline__ void emb_run32_body(const ScoreParams& p, EmbRunSmem<
     for (int u = 0; u < UP; ++u) prev[rbk][u] = (u32x4){0u, 0u, 0u, 0u};
   request(lo, 0);
   for (int fr = lo; fr <= hi; ++fr) {
-    f32x4 dot[2];
-    dot[0] = dot[1] = (f32x4){0.f, 0.f, 0.f, 0.f};
+    f32x4 dot[SETS][2];
     // D[i][j']: a lane holds column j' = j, rows i = 4g..4g+3.  Gram blocks (0,0) (0,1) (1,1); a neighbour frame
     // beyond the run is here for its norms and dot products: the diagonal blocks suffice.
     const bool own_frame = fr >= f0 && fr < f_end;  // (uniform)
@@ -1074,22 +1081,21 @@ __device__ __forceinline__ void emb_run32_body(const ScoreParams& p, EmbRunSmem<
         *(f32x4*)(strip + (i * 64 + lane) * 16) = gram;
       }
 #pragma unroll
-      for (int rbk = 0; rbk < 2; ++rbk)
+      for (int rbk = 0; rbk < 2; ++rbk) {
+        dot[0][rbk] = (f32x4){0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-          dot[rbk] = emb_mma<F32>(cur[rbk][u], prev[rbk][u % UP], dot[rbk]);
+          dot[0][rbk] = emb_mma<F32>(cur[rbk][u], prev[rbk][u % UP], dot[0][rbk]);
           prev[rbk][u % UP] = cur[rbk][u];
         }
+      }
     } else {
-      // four waves take 512 channels in two passes, which are summed apart (as eight waves would): a sum of twice as many
-      // channels in a row put the fused score of 512 fp32 channels 1.3 times, of 1024 1.5 times as far from 64 bits
-      constexpr int SETS = 8 / NW;
-      f32x4 gram[SETS][3], dots[SETS][2];
+      f32x4 gram[SETS][3];
 #pragma unroll
       for (int s = 0; s < SETS; ++s) {
 #pragma unroll
         for (int i = 0; i < 3; ++i) gram[s][i] = (f32x4){0.f, 0.f, 0.f, 0.f};
-        dots[s][0] = dots[s][1] = (f32x4){0.f, 0.f, 0.f, 0.f};
+        dot[s][0] = dot[s][1] = (f32x4){0.f, 0.f, 0.f, 0.f};
       }
       const bool has_before = fr > lo;
       auto take_pass = [&](int pass, f32x4 (&gram)[3], f32x4 (&dot)[2]) {
@@ -1122,40 +1128,37 @@ __device__ __forceinline__ void emb_run32_body(const ScoreParams& p, EmbRunSmem<
         }
       };
       for (int pass = 0; pass < n_pass; pass += SETS) {
-        take_pass(pass, gram[0], dots[0]);
-        if (SETS == 2 && pass + 1 < n_pass) take_pass(pass + 1, gram[SETS - 1], dots[SETS - 1]);
+        take_pass(pass, gram[0], dot[0]);
+        if (SETS == 2 && pass + 1 < n_pass) take_pass(pass + 1, gram[SETS - 1], dot[SETS - 1]);
       }
-      if (SETS == 2) {
 #pragma unroll
-        for (int i = 0; i < 3; ++i) gram[0][i] += gram[SETS - 1][i];
+      for (int s = 0; s < SETS; ++s)
 #pragma unroll
-        for (int rbk = 0; rbk < 2; ++rbk) dots[0][rbk] += dots[SETS - 1][rbk];
-      }
-      dot[0] = dots[0][0];
-      dot[1] = dots[0][1];
-#pragma unroll
-      for (int i = 0; i < 3; ++i)
-        if (i != 1 || own_frame) *(f32x4*)(strip + (i * 64 + lane) * 16) = gram[0][i];
+        for (int i = 0; i < 3; ++i)
+          if (i != 1 || own_frame) *(f32x4*)(strip + s * kSetBytes + (i * 64 + lane) * 16) = gram[s][i];
     }
     // of a dot block only the diagonal (token with itself) is needed: lane (j, g = j/4), element j%4
     if ((j >> 2) == g) {
 #pragma unroll
-      for (int rbk = 0; rbk < 2; ++rbk) {
-        float d = dot[rbk][0];
+      for (int s = 0; s < SETS; ++s)
 #pragma unroll
-        for (int e = 1; e < 4; ++e)
-          if ((j & 3) == e) d = dot[rbk][e];
-        sm.redd[wave][rbk][j] = d;
-      }
+        for (int rbk = 0; rbk < 2; ++rbk) {
+          float d = dot[s][rbk][0];
+#pragma unroll
+          for (int e = 1; e < 4; ++e)
+            if ((j & 3) == e) d = dot[s][rbk][e];
+          sm.redd[s * NW + wave][rbk][j] = d;
+        }
     }
     __syncthreads();
-    // sum the waves' channel slices in a fixed order: waves 0..2 one Gram block each (the diagonal
+    // sum the waves' channel slices in the order of their channels: waves 0..2 one Gram block each (the diagonal
     // blocks also give the scales of the rows' norms), wave 3 the diagonals of the dot blocks
     if (wave < 3 && (own_frame || wave != 1)) {
       const int blk = wave;
       f32x4 v = *(const f32x4*)(&sm.strip[0][0] + (blk * 64 + lane) * 16);
 #pragma unroll
-      for (int w = 1; w < NW; ++w) v += *(const f32x4*)(&sm.strip[w][0] + (blk * 64 + lane) * 16);
+      for (int w = 1; w < SETS * NW; ++w)
+        v += *(const f32x4*)(&sm.strip[w % NW][0] + (w / NW) * kSetBytes + (blk * 64 + lane) * 16);
       const int ra = blk == 2 ? 1 : 0, rbk = blk == 0 ? 0 : 1;
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
@@ -1172,7 +1175,7 @@ __device__ __forceinline__ void emb_run32_body(const ScoreParams& p, EmbRunSmem<
     } else if (wave == 3 && lane < MP) {
       float d = sm.redd[0][lane >> 4][lane & 15];
 #pragma unroll
-      for (int w = 1; w < NW; ++w) d += sm.redd[w][lane >> 4][lane & 15];
+      for (int w = 1; w < SETS * NW; ++w) d += sm.redd[w][lane >> 4][lane & 15];
       sm.dotv[lane] = d;
     }
     __syncthreads();
@@ -1186,15 +1189,14 @@ __device__ __forceinline__ void emb_run32_body(const ScoreParams& p, EmbRunSmem<
       float cs[CPT];
 #pragma unroll
       for (int i = 0; i < CPT; ++i) cs[i] = c0 + i < M ? cosine(sm.G[a][c0 + i], sa, sm.scale[c0 + i]) : 0.f;
-      float mu = cs[0];
-#pragma unroll
-      for (int i = 1; i < CPT; ++i) mu += cs[i];
+      // (in pairs, then over the threads: the same tree of sums for two and for four cosines a thread)
+      float mu = cs[0] + cs[1];
+      if constexpr (CPT == 4) mu += cs[2] + cs[3];
       mu = token_sum(mu) * inv_M;
 #pragma unroll
       for (int i = 0; i < CPT; ++i) cs[i] = c0 + i < M ? cs[i] - mu : 0.f;
-      float sq = cs[CPT - 1] * cs[CPT - 1];
-#pragma unroll
-      for (int i = CPT - 2; i >= 0; --i) sq = fmaf(cs[i], cs[i], sq);
+      float sq = fmaf(cs[0], cs[0], cs[1] * cs[1]);
+      if constexpr (CPT == 4) sq += fmaf(cs[2], cs[2], cs[3] * cs[3]);
       var = token_sum(sq) * inv_M;
     }
     if (tid % TPT == 0 && a < M) {

@@ -240,20 +240,24 @@ def test_embedding_terms_over_passes_of_channels(hippo, shape, dtype):
 
 
 @pytest.mark.parametrize("shape", [
-    # an fp32 block takes 256 channels a pass, odd and even passes summed apart: a pass, less a piece and one more; two
-    # passes and a piece more; batch elements and frame runs of several with a short last one
+    # an fp32 block of four waves takes 256 channels a pass, one of eight 512: a pass, less a piece and one more; two passes
+    # and a piece more; four; batch elements and frame runs of several with a short last one; 0: the keys of both KV heads
     (2, 3, 6, 7, 252, 5, 5), (1, 4, 5, 5, 256, 5, 5), (1, 2, 11, 6, 260, 4, 8), (1, 21, 16, 16, 512, 5, 5),
-    (3, 19, 11, 11, 516, 5, 5),
+    (3, 19, 11, 11, 516, 5, 5), (1, 5, 7, 11, 384, 5, 5), (1, 40, 16, 16, 768, 5, 5), (2, 7, 6, 6, 1024, 5, 5),
+    (1, 70, 11, 11, 1020, 5, 5), (2, 9, 7, 6, 0, 5, 5),
 ])
 def test_fp32_embedding_terms_beside_the_sweep(hippo, shape):
-    test_embedding_terms_over_passes_of_channels(hippo, shape, "fp32")
     B, F, gh, gw, ch, cy, cx = shape
-    q, k = score_inputs(ch, B, 37, 6, 2, 128, F * gh * gw + 11, "fp32")
+    if ch:
+        test_embedding_terms_over_passes_of_channels(hippo, shape, "fp32")
+    n = F * gh * gw
+    q, k = score_inputs(ch, B, 37, 6, 2, 128, n + 11, "fp32")
+    emb = dev(prep(np.random.default_rng(n + ch).standard_normal((B, n, ch)), "fp32"), "fp32") if ch else None
     vid = hippo.video_desc(F, gh, gw, 5, cy, cx)
-    comps = [hippo.hippo_score_tokens(dev(q, "fp32"), dev(k, "fp32"), vid, flags=flags, want_components=True)[1]
+    comps = [hippo.hippo_score_tokens(dev(q, "fp32"), dev(k, "fp32"), vid, emb=emb, flags=flags, want_components=True)[1]
              for flags in (7, 1, 6)]
     assert torch.equal(comps[0][0], comps[1][0])                      # the sweep's blocks, with and without riders
-    assert torch.equal(comps[0][1:], comps[2][1:])                    # the riders' blocks, beside a sweep and alone
+    assert torch.equal(comps[0][1:], comps[2][1:])                    # the crops' sums, beside a sweep and alone
 
 
 @pytest.mark.parametrize("dtype", ["fp32", "bf16"])
@@ -296,15 +300,16 @@ def test_rows_with_a_nan_have_cosine_zero(hippo, ch, crop, dtype):
 
 
 def test_wide_keys_as_embedding(hippo):
-    # 8 KV heads x 128 channels: the keys of all heads side by side, 1024 channels in two passes
-    for dtype in ("fp32", "bf16"):
-        q, k = score_inputs(9, 1, 3, 8, 8, 128, 4 * 6 * 11 + 3, dtype)
+    # 8 KV heads x 128 channels: the keys of all heads side by side, 1024 channels in two passes; 4 heads: one, fp32 two
+    for dtype, heads in (("fp32", 8), ("bf16", 8), ("fp32", 4), ("bf16", 4)):
+        q, k = score_inputs(9, 1, 3, heads, heads, 128, 4 * 6 * 11 + 3, dtype)
         emb = oracle.keys_as_embedding(k, 2, 4 * 6 * 11)
-        _, comps = hippo.hippo_score_tokens(dev(q, dtype), dev(k, dtype), hippo.video_desc(4, 6, 11, 2),
-                                            want_components=True)
-        assert_close(host(comps)[1], oracle.s_temp(emb, 4), dtype, "s_temp")
         ss = oracle.s_spa(emb, 4, 6, 11)
-        np.testing.assert_allclose(host(comps)[2], ss, rtol=0, atol=(2e-6 if dtype == "fp32" else 2e-3) * ss.max())
+        for flags in (7, 6):
+            _, comps = hippo.hippo_score_tokens(dev(q, dtype), dev(k, dtype), hippo.video_desc(4, 6, 11, 2), flags=flags,
+                                                want_components=True)
+            assert_close(host(comps)[1], oracle.s_temp(emb, 4), dtype, "s_temp")
+            np.testing.assert_allclose(host(comps)[2], ss, rtol=0, atol=(2e-6 if dtype == "fp32" else 2e-3) * ss.max())
 
 
 @pytest.mark.parametrize("d", [64, 128])
