@@ -1227,8 +1227,9 @@ __device__ __forceinline__ void emb_run32_block(const ScoreParams& p, EmbRunSmem
   emb_run32_body<F32, U, NW, WIDE>(p, sm, threadIdx.x, (int)pos, (int)run * p.emb_run, (int)bb);
 }
 
+// (four waves: three blocks on a compute unit; with registers for two, 4 x 72 frames of 768 channels took 256 us, not 187)
 template <bool F32, int NW, bool WIDE>
-__global__ __launch_bounds__(64 * NW) void emb_scores_run32(ScoreParams p) {
+__global__ __launch_bounds__(64 * NW, NW == 4 ? 3 : 2) void emb_scores_run32(ScoreParams p) {
   constexpr int U = F32 ? 4 : 2;
   __shared__ EmbRunSmem<U, NW> sm;
   emb_run32_block<F32, U, NW, WIDE>(p, sm, blockIdx.x);
