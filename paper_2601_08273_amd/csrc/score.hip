@@ -1508,6 +1508,53 @@ static hipError_t launch_sattn_mfma(const ScoreParams& p, hipStream_t st, long l
   return hipGetLastError();
 }
 
+// fp32 crops of more than 256 channels: beside pass 1 by four-wave blocks in passes of 256 channels, or in a launch of their
+// own, where blocks of eight waves take 512 in a pass and fetch a frame's channels half as often.
+//
+// Where they ride.  Channels that fill their last pass of 512 by half or less (an odd number of passes of 256): four waves
+// lose nothing by their passes.  They ride beside a sweep of up to two blocks a compute unit and beside a long one (rounds of
+// blocks x 32-row chunks, a block's start as 0.7 of a chunk); beside a short sweep of many blocks they wait for its
+// blocks' slots and then crowd on few compute units.  768 channels, us a call, alone -> riding: 26 x 14 x 14 tokens, 52
+// sweep blocks, 41.4 -> 36.8; 220 sweep blocks of 11 chunks 113 -> 103; 736 of 10 chunks 201 -> 189; and where they stay alone:
+// 936 of one chunk 91 against 101, 1016 of four 177 against 220, 1184 of two 161 against 189.
+// Otherwise eight waves are the better ones, and the crops ride only where the sweep leaves compute units idle: 512
+// channels, 152 sweep blocks and 108 crops 49.4 -> 42.7, 176 and 64 51.6 -> 43.0; where they stay alone: 410 blocks of three
+// chunks 69 against 87, 568 of one 54 against 68, 1024 channels, 712 of two 102 against 145, 360 of one chunk 78 against 88.
+static bool wide_f32_rides(const ScoreParams& p, long long n_sattn, long long n_riders, int de) {
+  if ((de + 255) / 256 % 2 == 1) {
+    const double rounds = (double)((n_sattn + kNumCU - 1) / kNumCU);
+    return n_sattn <= 2 * kNumCU || rounds * (p.rows_per_split / (double)kSaF32Rows + 0.7) >= 22.0;
+  }
+  return n_sattn <= kNumCU && n_riders <= kNumCU / 2 &&
+         (long long)p.rows_per_split * p.D >= (n_sattn + n_riders <= kNumCU ? 4096 : 16384);
+}
+
+// A launch of their own: frames a run (p.emb_run) and waves a block (the result: eight) of the least estimated time.  A frame
+// costs the same in every block, so a run's time is that of its frames and two neighbours, times the blocks that a compute
+// unit takes one after the other (eight waves: one at a time; four: two side by side at 1.4 times the time of one, more at
+// 0.59 of a block's).  A fixed number of blocks was wrong on both sides: two a compute unit make a second round of
+// eight-wave blocks, crops / compute units rounded down a few blocks too many (1440 crops of 512 channels, us: 46 in 480
+// blocks, 58 in 288, 39 in 240).
+static bool wide_f32_plan(ScoreParams& p, long long crops_a_frame, int de) {
+  const int longest = std::min(8, p.F);
+  bool eight = true;
+  double best = 0.0;
+  for (int run = 1; run <= longest; ++run) {
+    const long long blocks = crops_a_frame * ((p.F + run - 1) / run), rounds = (blocks + kNumCU - 1) / kNumCU;
+    if (rounds > 2 && run < longest) continue;      // many crops: the two neighbour frames' bytes decide
+    const double t8 = (double)rounds * ((de + 511) / 512);
+    const double t4 = (rounds == 1 ? 0.7 : rounds == 2 ? 1.0 : 0.59 * blocks / kNumCU) * ((de + 255) / 256);
+    const bool use8 = de <= 512 || t8 <= t4;        // one pass holds the frame before in registers
+    const double t = (run + 2) * (use8 ? t8 : t4);
+    if (best == 0.0 || t < best) {
+      best = t;
+      p.emb_run = run;
+      eight = use8;
+    }
+  }
+  return eight;
+}
+
 hipError_t launch_score(const ScoreParams& p_in, hipStream_t st) {
   ScoreParams p = p_in;
   {
@@ -1529,17 +1576,22 @@ hipError_t launch_score(const ScoreParams& p_in, hipStream_t st) {
   // 138 us a call, 3 x 7220 tokens 112 against 105).
   const long long crops_per_frame = (long long)((p.gh + p.ch - 1) / p.ch) * ((p.gw + p.cw - 1) / p.cw);
   const bool bf16 = p.dtype == HIPPO_DTYPE_BF16;
+  const int de = p.emb ? p.emb_dim : p.Hkv * p.D;
+  const bool small_crops = p.ch * p.cw <= 32;
+  const bool wide = de > (bf16 ? 512 : 256);
   {
-    const long long crops = crops_per_frame * p.F * p.B;
-    const long long run = crops / kNumCU;
+    const long long run = crops_per_frame * p.F * p.B / kNumCU;
     p.emb_run = (int)std::max<long long>(1, std::min<long long>(std::min<long long>(8, p.F), run));
   }
-  const bool small_crops = p.ch * p.cw <= 32;
-  const bool wide = (p.emb ? p.emb_dim : p.Hkv * p.D) > (bf16 ? 512 : 256);
-  const long long n_riders = crops_per_frame * ((p.F + p.emb_run - 1) / p.emb_run) * p.B;
-  const long long fused_blocks = (long long)p.n_tile * p.Hkv * p.n_rsplit * p.Bz + n_riders;
+  long long n_riders = crops_per_frame * ((p.F + p.emb_run - 1) / p.emb_run) * p.B;
+  const long long n_sattn = (long long)p.n_tile * p.Hkv * p.n_rsplit * p.Bz;
   const bool emb_rides = want_emb && !accumulate_only && (p.flags & HIPPO_SCORE_ATTN) && small_crops &&
-                         fused_blocks < (1ll << 31);
+                         n_sattn + n_riders < (1ll << 31) && (bf16 || !wide || wide_f32_rides(p, n_sattn, n_riders, de));
+  bool eight_waves = false;
+  if (!emb_rides && !bf16 && wide) {
+    eight_waves = wide_f32_plan(p, crops_per_frame * p.B, de);
+    n_riders = crops_per_frame * ((p.F + p.emb_run - 1) / p.emb_run) * p.B;
+  }
   const long long riders = emb_rides ? n_riders : 0;
   if ((p.flags & HIPPO_SCORE_ATTN) || accumulate_only) {
     if (p.dtype == HIPPO_DTYPE_BF16)
@@ -1560,13 +1612,11 @@ hipError_t launch_score(const ScoreParams& p_in, hipStream_t st) {
     if (small_crops) {
       if (n_riders >= (1ll << 31)) return hipErrorInvalidValue;
       const dim3 runs((unsigned)n_riders);
-      // fp32 of 257 to 512 channels: eight waves take them in one pass and fetch a frame once (2 x 12 frames of 512 channels,
-      // us: 24 against 27, 48 frames 24 against 35); up to 256, half of eight waves would idle (128 frames of 128 channels 29
-      // against 42), and beyond 512 four waves are the better ones again (1024 channels 48.5 against 52)
-      const int de = p.emb ? p.emb_dim : p.Hkv * p.D;
+      // (fp32 up to 256 channels: half of eight waves would idle; 128 frames of 128 channels 29 against 42 us)
       if (bf16 && wide) hipLaunchKernelGGL((emb_scores_run32<false, 8, true>), runs, dim3(512), 0, st, p);
       else if (bf16) hipLaunchKernelGGL((emb_scores_run32<false, 8, false>), runs, dim3(512), 0, st, p);
       else if (wide && de <= 512) hipLaunchKernelGGL((emb_scores_run32<true, 8, false>), runs, dim3(512), 0, st, p);
+      else if (wide && eight_waves) hipLaunchKernelGGL((emb_scores_run32<true, 8, true>), runs, dim3(512), 0, st, p);
       else if (wide) hipLaunchKernelGGL((emb_scores_run32<true, 4, true>), runs, dim3(256), 0, st, p);
       else hipLaunchKernelGGL((emb_scores_run32<true, 4, false>), runs, dim3(256), 0, st, p);
     } else if (!bf16) {

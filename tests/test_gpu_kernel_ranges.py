@@ -245,6 +245,8 @@ def test_embedding_terms_over_passes_of_channels(hippo, shape, dtype):
     (2, 3, 6, 7, 252, 5, 5), (1, 4, 5, 5, 256, 5, 5), (1, 2, 11, 6, 260, 4, 8), (1, 21, 16, 16, 512, 5, 5),
     (3, 19, 11, 11, 516, 5, 5), (1, 5, 7, 11, 384, 5, 5), (1, 40, 16, 16, 768, 5, 5), (2, 7, 6, 6, 1024, 5, 5),
     (1, 70, 11, 11, 1020, 5, 5), (2, 9, 7, 6, 0, 5, 5),
+    # crops for two four-wave blocks a compute unit in runs of eight frames
+    (1, 240, 11, 11, 516, 5, 5),
 ])
 def test_fp32_embedding_terms_beside_the_sweep(hippo, shape):
     B, F, gh, gw, ch, cy, cx = shape
