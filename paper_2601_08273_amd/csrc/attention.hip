@@ -400,8 +400,8 @@ __global__ __launch_bounds__(RB * TG * 64) void attn_partial_grid(AttnParams p) 
     const float mx = m8 * scale_log2;                      // scale > 0: max commutes with it
     // lazy rescale: the reference m_run moves only when the tile maximum exceeds it by more than
     // kRescaleGap, so probabilities stay below 2^kRescaleGap and rescales are rare
-    // (long slices of 16-token tiles take the second tile's maximum too: the further the slice's largest probabilities lie
-    // above the reference, the smaller their significands and the larger their rounding, 0.4 % of the output's error)
+    // (long slices of 16-token tiles take the second tile's maximum too, as 32-token tiles take that of 32 tokens: the further
+    // the slice's largest probabilities lie above the reference, the larger their rounding, 0.4 % of the output's error)
     const float gap = ROT && TT == 16 && si == 1 ? 0.f : kRescaleGap;
     const bool up = mx > m_run + gap;                      // also true for the first finite maximum
     if (__any(up)) {
@@ -1016,15 +1016,17 @@ static hipError_t launch_grid_rb(const AttnParams& p, hipStream_t st) {
   const bool small_tiles = tiles32_per_block < 24;
   if (!small_tiles) {
     const bool nt = stream_exceeds_caches(p, D, 2);
-    // Three and four row blocks: stages of 16-token tiles, four of them, keep three quarters of the ring in flight under a
-    // stage's products, two of 32-token tiles half of it.  That pays where the tiles come from the L2 (the second row chunk
-    // of a slice runs on the same XCD; us a call in chunks of 48: 33K x 4 heads, 91 rows, paged 27.2 -> 24.7; 2 x 8 heads x
-    // 20K, 96 rows 47.7 -> 42.2; 4 x 8 x 36K, 72 rows 147 -> 128) and for rows of 64 channels, whose 32-token ring is half
-    // as large (3 x 2 heads x 70K, 42 rows 26.9 -> 25.2, 91 rows 41.0 -> 37.8); one chunk of 128 channels has HBM to wait for,
-    // and the fewer barriers of the larger tiles are worth 1 to 3 % (2 x 8 x 37K, 64 rows 58.3 against 59.8).
-    if constexpr (RB >= 3)
-      if (D == 64 || p.n_chunks > 1)
-        return nt ? launch_grid<D, RB, 4, 16, 4, true, true>(p, st) : launch_grid<D, RB, 4, 16, 4, false, true>(p, st);
+    // A stream that no cache holds, under three row blocks (of 128 channels: more than one chunk of them) or, of 64 channels,
+    // one chunk of four: stages of 16-token tiles, four of them, keep three quarters of the ring in flight under a stage's
+    // products, two of 32-token tiles half of it.  Us a call, 32-token tiles -> 16: 4 x 8 heads x 128 x 20K, 72 rows 90.5 ->
+    // 80.4, 36K, 96 rows 140.6 -> 126.9; of 64 channels, 40K, 40 rows 64.5 -> 58.2, 64 rows 66.3 -> 60.2, 72 rows 100.0 -> 90.9;
+    // one chunk of 128 channels only waits for HBM (2 x 8 x 37K, 64 rows 58.3 against 59.8), two chunks of four row blocks
+    // gain nothing (4 x 8 x 128 x 20K, 104 rows 84.8 and 85.7; 64 channels x 40K 102 and 104).
+    // Where the last-level cache can hold K and V the smaller tiles pay only while it does not, as in a round over many
+    // layers (2 x 8 x 128 x 20K, 72 rows 53.1 -> 46.9; 33K x 4 heads from 24.5 to 23.7), and cost as much when it does, as in
+    // calls over one layer (34.9 -> 42.2; 20.4 -> 22.4; 64 channels x 20K, 104 rows 28.7 -> 32.8): there the 32-token tiles stay.
+    if constexpr (RB == 3 || (RB == 4 && D == 64))
+      if (nt && (D == 64 ? RB == 3 || p.n_chunks == 1 : p.n_chunks > 1)) return launch_grid<D, RB, 4, 16, 4, true, true>(p, st);
     return nt ? launch_grid<D, RB, 4, 32, 2, true, true>(p, st) : launch_grid<D, RB, 4, 32, 2, false, true>(p, st);
   }
   // measured at the 16K configuration: with 3-4 row blocks, two token groups and a four-stage ring

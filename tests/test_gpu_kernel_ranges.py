@@ -57,6 +57,19 @@ def test_more_than_64_rows(hippo, shape, d):
     assert torch.equal(hippo.hippo_verify_attention_paged(qd, *pools, table, ctx, num_splits=S), plain), what
 
 
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("G, S", [(7, 3), (8, 2), (5, 1)])
+def test_a_row_does_not_depend_on_the_rows_beside_it(hippo, G, S, d):
+    # slices of 24 32-token tiles and more of a cache that a last-level cache holds: the tiles are the same for 16, 48, 64 and
+    # more rows, so a call's first rows are bit for bit those of a call over fewer (the last tile masks what they do not see)
+    ctx = 2305
+    q, k, v = (dev(x, "bf16") for x in attention_inputs(G + d, 2, 13, 2 * G, 2, d, ctx, "bf16"))
+    whole = hippo.hippo_verify_attention(q, k, v, ctx, num_splits=S)
+    for n in (2, 6, 64 // G, 12):
+        few = hippo.hippo_verify_attention(q[:, :n].contiguous(), k[:, :, :ctx + n], v[:, :, :ctx + n], ctx, num_splits=S)
+        assert torch.equal(few, whole[:, :n]), n
+
+
 @pytest.mark.parametrize("dtype", ["fp32", "bf16", "fp8"])
 @pytest.mark.parametrize("shape", [
     # q_len, G, ctx: up to 16 query rows and 128 (fp32) or 256 rows of cache by the library's choice, and just beyond; one
