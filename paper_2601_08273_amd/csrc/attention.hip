@@ -101,15 +101,19 @@ struct GridSmem {
 // is tile row 8*(m/4) + 4*tb + m%4, so the 8 probabilities a lane holds belong to 8 consecutive
 // tokens 8g..8g+7, and ds_read_b64_tr_b8 (lane i of a 16-lane group addresses 8 bytes of row i/2,
 // lane j receives column j of the 8 rows) then fetches exactly those 8 tokens of V^T in one read.
-template <int D, bool KV8>
+template <int D, bool KV8, bool LONG32>
 __device__ __forceinline__ int tile_swizzle(int r) {
   // 16-bit rows: the K reads of 16 lanes touch 16 consecutive rows, one piece each; the V reads of 32 lanes eight
   // consecutive rows, two neighbouring pieces each, so it is the piece's upper bits that must differ from row to row
   // (the 16 lanes of a K read are not consecutive: with the pieces g * KS + ks of four lane groups, r itself as the swizzle
-  // doubled the K reads' time too; measured 44 % of the LDS cycles of a 33K call of 91 rows were conflicts, now none of
-  // the reads': 25.25 -> 24.85 us a call, 4 x 8 heads x 37K 107.5 -> 106.9)
+  // doubled the K reads' time too; 47 % of the LDS cycles of a 33K call of 91 rows were conflicts, now none: 25.25 ->
+  // 24.85 us a call, 4 x 8 heads x 37K 107.5 -> 106.9)
   if constexpr (!KV8 && D == 128) return ((r & 7) << 1) | ((r >> 3) & 1);
-  else if constexpr (!KV8) return (((r >> 1) & 3) << 1) | ((r >> 3) & 1);   // two rows in 256 bytes
+  // (64 channels, two rows in 256 bytes.  The 32-token tiles of long slices keep the pair's number: 48 % of their LDS cycles
+  // are conflicts, but the waves of four row blocks hide them, and without a conflict the same loop is slower, from the
+  // last-level cache 2 x 8 heads x 20K, 72 rows 25.0 us a call against 23.8, 104 rows 28.5 and 27.4; from HBM the same.)
+  else if constexpr (!KV8 && LONG32) return lds_row_swizzle<D>(r);
+  else if constexpr (!KV8) return (((r >> 1) & 3) << 1) | ((r >> 3) & 1);
   // 128-byte rows: the K reads of 16 lanes touch rows {0-3, 8-11, 16-19, 24-27} (+4), the V reads of
   // 32 lanes 16 consecutive rows; both must spread over the 16 16-byte slots of 256 bytes
   else if constexpr (D == 128) return ((r >> 1) ^ ((r >> 3) & 2)) & 7;
@@ -136,6 +140,7 @@ template <int D, int RB, int TG, int TT, int NST, int MODE, bool KV8 = false, bo
           bool ONE = false>
 __global__ __launch_bounds__(RB * TG * 64) void attn_partial_grid(AttnParams p) {
   constexpr bool APPEND = MODE == 1, PAGED = MODE == 2;
+  constexpr bool LONG32 = ROT && TT == 32;
   constexpr int ES = KV8 ? 1 : 2;                      // bytes per cache element
   using SM = GridSmem<D, TG, TT, NST, ES>;
   constexpr int WAVES = RB * TG;
@@ -252,7 +257,7 @@ __global__ __launch_bounds__(RB * TG * 64) void attn_partial_grid(AttnParams p) 
       if (decltype(select)::value && row >= p.ctx_len)     // a row that has not reached the cache yet
         src = (const char*)(which ? p.v_new : p.k_new) +
               ((((long long)b * p.q_len + (row - p.ctx_len)) * p.Hkv + hk) * D) * 2;
-      dma16<NT>(src + ((ld_pc ^ tile_swizzle<D, KV8>(r)) * 16), dst + (tt * 2 + which) * SM::kTileBytes + n * 1024);
+      dma16<NT>(src + ((ld_pc ^ tile_swizzle<D, KV8, LONG32>(r)) * 16), dst + (tt * 2 + which) * SM::kTileBytes + n * 1024);
     }
   };
   // (only the last tiles hold appended rows: the source select, formed for every lane of every transfer, stood in front of
@@ -288,7 +293,7 @@ __global__ __launch_bounds__(RB * TG * 64) void attn_partial_grid(AttnParams p) 
       r = r < p.R ? r : p.R - 1;                          // padding rows repeat the last real row
       const int i = row_div_group(r, inv_g), gq = r - i * p.G;
       const char* src = (const char*)p.q + ((((long long)b * p.q_len + i) * p.H + hk * p.G + gq) * D) * 2 +
-                        (((lane % QCPR) ^ tile_swizzle<D, false>(rr)) * 16);
+                        (((lane % QCPR) ^ tile_swizzle<D, false, LONG32>(rr)) * 16);
       dma16(src, q_addr + n * 1024);
     }
   }
@@ -310,11 +315,11 @@ __global__ __launch_bounds__(RB * TG * 64) void attn_partial_grid(AttnParams p) 
   unsigned k_off[NKOFF];
   unsigned v_off[DB];
   if constexpr (!KV8) {
-    const int swz_k = tile_swizzle<D, false>(j);
+    const int swz_k = tile_swizzle<D, false, LONG32>(j);
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) k_off[ks] = j * ROWB + (((g * KS + ks) ^ swz_k) * 16);
     const int v_row = 4 * g + (j >> 2);
-    const int swz_v = tile_swizzle<D, false>(v_row);
+    const int swz_v = tile_swizzle<D, false, LONG32>(v_row);
 #pragma unroll
     for (int db = 0; db < DB; ++db)
       v_off[db] = v_row * ROWB + (((2 * db + ((j & 3) >> 1)) ^ swz_v) * 16) + (j & 1) * 8;
@@ -324,12 +329,12 @@ __global__ __launch_bounds__(RB * TG * 64) void attn_partial_grid(AttnParams p) 
       const int k_row = 8 * (j >> 2) + 4 * tb + (j & 3);
 #pragma unroll
       for (int c = 0; c < NKC; ++c)
-        k_off[tb * NKC + c] = k_row * ROWB + (((g * NKC + c) ^ tile_swizzle<D, true>(k_row)) * 16);
+        k_off[tb * NKC + c] = k_row * ROWB + (((g * NKC + c) ^ tile_swizzle<D, true, LONG32>(k_row)) * 16);
     }
     const int v_row = 8 * g + (j >> 1);
 #pragma unroll
     for (int db = 0; db < DB; ++db)
-      v_off[db] = v_row * ROWB + ((db ^ tile_swizzle<D, true>(v_row)) * 16) + (j & 1) * 8;
+      v_off[db] = v_row * ROWB + ((db ^ tile_swizzle<D, true, LONG32>(v_row)) * 16) + (j & 1) * 8;
   }
   // keep the swizzled lane offsets in registers: left to itself the compiler recomputes them from
   // (j, g) for every tile, which costs more vector instructions than the tile's arithmetic
@@ -351,7 +356,7 @@ __global__ __launch_bounds__(RB * TG * 64) void attn_partial_grid(AttnParams p) 
 #pragma unroll
       for (int ks = 0; ks < KS; ++ks)
         qop[ks] = *(const bf16x8*)(Qs + rb * 16 * QROWB + j * QROWB +
-                                   (((g * KS + ks) ^ tile_swizzle<D, false>(j)) * 16));
+                                   (((g * KS + ks) ^ tile_swizzle<D, false, LONG32>(j)) * 16));
     }
     if (si > 0 && issued < n_super) {                      // refill the stage just vacated
       if (issuer) issue_super(issued);
