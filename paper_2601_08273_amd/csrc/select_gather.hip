@@ -21,6 +21,7 @@ constexpr int kSelWaves = kSelThreads / 64;
 constexpr int kKeysPerThread = 72;
 constexpr int kPackedCounts = 40;        // keys per thread up to which two counts of a block fit 16 bits each
 constexpr int kGatherKeys = 24;          // keys per thread up to which the selecting launch copies the rows too
+constexpr int kShortKeys = 4;            // and up to which it may do so in two rounds of blocks
 constexpr int kBins = 4096;              // 12-bit digits (the last pass uses 256 of them)
 constexpr int kHistStride = kBins + kBins / 64;   // padded histogram
 constexpr int kHistWords = 2 * kHistStride + 256 + 4;   // one per radix pass; indices, once the threshold is known (GATHER)
@@ -397,10 +398,16 @@ hipError_t launch_select_gather(const SelectParams& p, hipStream_t st) {
   // registers copy more slowly than gather_kv's (us a call in a graph, two launches -> one: 4 x 16384 x 8 heads, 100 MB,
   // 24.2 -> 22.8; 8 x 16384, 112 MB, 25.8 -> 24.1; 2 x 34000, 140 MB, 37.5 -> 37.8; 12 x 16384, 167 MB, 32.9 -> 35.2;
   // 4 x 34000, 281 MB, 57.7 -> 61.3; 48 x 8192, 182 MB, 33.6 -> 37.1).
+  // Not where KV heads outnumber the compute units, whose second round of blocks would select once more (us a call in a graph,
+  // two launches -> one: 32 x 8 heads x 1568 14.4 -> 12.9; 33 x 8 x 16384 19.1 -> 28.0; 64 x 8 x 16384 20.6 -> 28.6; 128 x 8 x
+  // 1568 18.8 -> 20.2), but for two rounds over up to 4096 tokens (64 x 8 x 1568 21.5 -> 19.9, x 4096 18.2 -> 17.1, x 8192
+  // 18.4 -> 18.9).
+  const long long heads = (long long)p.B * p.Hkv;
   const bool one_launch = per_head > 0 && n_chunks <= kGatherKeys && p.k <= kHistWords && per_head <= (1ll << 24) &&
-                          per_head * p.B * p.Hkv <= (128ll << 20) / 64;
+                          per_head * heads <= (128ll << 20) / 64 &&
+                          heads <= (n_chunks <= kShortKeys ? 2 * kNumCU : kNumCU);
   const long long parts = std::max<long long>(1, std::min<long long>((per_head + 2 * kSelThreads - 1) / (2 * kSelThreads),
-                                                                     kNumCU / ((long long)p.B * p.Hkv)));
+                                                                     kNumCU / heads));
 #define HIPPO_TOPK(NC_)                                                                                      \
   if (one_launch)                                                                                            \
     hipLaunchKernelGGL((topk_select<NC_, (NC_ > 0 && NC_ <= kGatherKeys)>), dim3((unsigned)(p.Hkv * parts), p.B), \

@@ -410,6 +410,8 @@ def test_topk_of_long_sequences(hippo, n, ties):
     # 128 MiB to copy, and in 8 bits less
     (1, 1, 64, 1, 1), (2, 3, 128, 1025, 600), (1, 300, 64, 70, 33), (3, 7, 64, 4097, 1000), (1, 2, 64, 9000, 8580),
     (1, 2, 64, 9000, 8581), (1, 1, 128, 24576, 4000), (1, 1, 128, 24577, 4000), (40, 8, 64, 97, 97), (20, 8, 128, 1000, 900),
+    # a head per compute unit and one more; two of up to 4096 tokens and one more, of 4096 tokens and one more
+    (1, 256, 64, 4097, 30), (1, 257, 64, 4097, 30), (1, 512, 64, 4096, 30), (1, 513, 64, 4096, 30), (2, 256, 64, 4097, 30),
 ])
 @pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32, torch.uint8])
 def test_draft_cache_in_one_launch(hippo, shape, dtype):
