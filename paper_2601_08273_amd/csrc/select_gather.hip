@@ -22,6 +22,7 @@ constexpr int kKeysPerThread = 72;
 constexpr int kPackedCounts = 40;        // keys per thread up to which two counts of a block fit 16 bits each
 constexpr int kGatherKeys = 24;          // keys per thread up to which the selecting launch copies the rows too
 constexpr int kShortKeys = 4;            // and up to which it may do so in two rounds of blocks
+constexpr int kGraphKeys = 16;           // and, with little to copy, in a graph
 constexpr int kBins = 4096;              // 12-bit digits (the last pass uses 256 of them)
 constexpr int kHistStride = kBins + kBins / 64;   // padded histogram
 constexpr int kHistWords = 2 * kHistStride + 256 + 4;   // one per radix pass; indices, once the threshold is known (GATHER)
@@ -379,6 +380,17 @@ __global__ __launch_bounds__(256) void gather_kv(SelectParams p, int vpr_shift) 
   *(u32x4*)((char*)p.v_dst + dof + vec * 16) = vv;
 }
 
+// Whether a call on the stream becomes a node of a graph.  (The null stream cannot be captured.)
+static bool is_captured(hipStream_t st) {
+  hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+  if (st == nullptr) return false;
+  if (hipStreamIsCapturing(st, &status) != hipSuccess) {
+    (void)hipGetLastError();
+    return false;
+  }
+  return status == hipStreamCaptureStatusActive;
+}
+
 hipError_t launch_select_gather(const SelectParams& p, hipStream_t st) {
   const int n_chunks = (p.Nv + kSelThreads - 1) / kSelThreads;
   const int vpr = p.D * p.elem_bytes / 16;                 // 16-byte vectors per row: 4, 8, 16 or 32
@@ -402,10 +414,15 @@ hipError_t launch_select_gather(const SelectParams& p, hipStream_t st) {
   // two launches -> one: 32 x 8 heads x 1568 14.4 -> 12.9; 33 x 8 x 16384 19.1 -> 28.0; 64 x 8 x 16384 20.6 -> 28.6; 128 x 8 x
   // 1568 18.8 -> 20.2), but for two rounds over up to 4096 tokens (64 x 8 x 1568 21.5 -> 19.9, x 4096 18.2 -> 17.1, x 8192
   // 18.4 -> 18.9).
+  // Nor in a graph, where a second launch costs the host nothing, beyond 16384 tokens with up to 20 MB to copy (in a graph, two
+  // launches -> one: 4 heads x 20000, 1000 kept 14.2 -> 14.8, 24576 15.3 -> 15.8, 4 x 2 heads x 17000 13.8 -> 14.1, x 24000
+  // 14.7 -> 15.4; eager 18.0 -> 15.3, 18.4 -> 15.4, 18.6 -> 15.3, 18.6 -> 15.4; in a graph from 16384 tokens down 12.1 -> 12.0,
+  // 11.2 -> 11.2, 9.3 -> 9.2, and with 21 MB or more 16.5 -> 16.5, 16.0 -> 15.7, 17.6 -> 17.1).
   const long long heads = (long long)p.B * p.Hkv;
   const bool one_launch = per_head > 0 && n_chunks <= kGatherKeys && p.k <= kHistWords && per_head <= (1ll << 24) &&
                           per_head * heads <= (128ll << 20) / 64 &&
-                          heads <= (n_chunks <= kShortKeys ? 2 * kNumCU : kNumCU);
+                          heads <= (n_chunks <= kShortKeys ? 2 * kNumCU : kNumCU) &&
+                          !(n_chunks > kGraphKeys && per_head * heads <= (20ll << 20) / 64 && is_captured(st));
   const long long parts = std::max<long long>(1, std::min<long long>((per_head + 2 * kSelThreads - 1) / (2 * kSelThreads),
                                                                      kNumCU / heads));
 #define HIPPO_TOPK(NC_)                                                                                      \

@@ -433,3 +433,24 @@ def test_draft_cache_in_one_launch(hippo, shape, dtype):
     for src, got, whole in zip((kc, vc), out, dst):
         assert torch.equal(got, torch.stack([src[b][:, rows[b]] for b in range(B)]))
         assert bool((whole[..., d:].float() == 7).all())
+
+
+@pytest.mark.parametrize("n", [16384, 16385, 24576])
+def test_draft_cache_in_a_graph(hippo, n):
+    # the same rows and indices from a replayed graph, whichever number of launches it holds, over new scores each time
+    g = torch.Generator(device="cuda").manual_seed(n)
+    scores = torch.empty((2, n), device="cuda")
+    kc, vc = (torch.randn((2, 2, n + 9, 64), generator=g, device="cuda").to(torch.bfloat16) for _ in range(2))
+    vid = hippo.video_desc(1, 1, n, 3)
+    scores.normal_(generator=g)
+    outs = hippo.hippo_select_gather_kv(scores, 700, kc, vc, vid)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        held = hippo.hippo_select_gather_kv(scores, 700, kc, vc, vid)
+    for _ in range(4):
+        scores.normal_(generator=g)
+        graph.replay()
+        outs = hippo.hippo_select_gather_kv(scores, 700, kc, vc, vid)
+        torch.cuda.synchronize()
+        assert all(torch.equal(a, b) for a, b in zip(held, outs))
