@@ -13,10 +13,10 @@
 //                  over the cell sums -> total mass and the cell in which the running sum first
 //                  exceeds u * total; one wave re-evaluates that cell and finds the word (inverse
 //                  CDF in index order).  The count is cleared by the first launch.
-// Bound by latency: the trips to memory that depend on each other.  Drawing in a launch of its own took
-// 5.0 us against the 4.3 that it adds to the last block (7.2 -> 11.5 us), and a launch more to enqueue
-// (4 us of a host thread); each thread's cell sums in one trip instead of one by one, and again from
-// memory.  A call over 4 x 11 rows of 152064 bf16 words, us: 18.9 -> 16.8.
+// Bound by latency: the trips to memory that depend on each other.  Drawing in a launch of its own is a
+// start more on the GPU and a launch more to enqueue.  Us a call, three launches -> two, in a graph and
+// eager: 4 x 11 rows of 152064 bf16 words 15.7 -> 14.9 and 16.7 -> 14.7, 7 x 25 rows 29.2 -> 28.0 and
+// 28.2 -> 26.7, one sequence of 3 rows of 32000 words 12.4 -> 12.4 and 16.7 -> 14.2.
 // Greedy decoding (temperature 0) needs only the first launch over the target rows and a
 // one-block-per-sequence comparison of argmax with the draft tokens.
 //
@@ -66,6 +66,14 @@ constexpr int kSdThreads = 256;
 constexpr int kSdWaves = kSdThreads / 64;
 constexpr int kSdPerThread = kSdSeg / kSdThreads;   // 32 logits per thread, held in registers
 constexpr int kSdLdsStats = 1024;                   // segment statistics staged in LDS (16 KB)
+
+// Stores and loads of what other blocks of the launch read or wrote: device scope, past the caches of an XCD.
+__device__ __forceinline__ void store_agent(float* at, float v) {
+  __hip_atomic_store(at, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ float load_agent(const float* at) {
+  return __hip_atomic_load(at, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
 
 // words idx .. of a row of V, -inf past its end
 template <typename T>
@@ -165,7 +173,7 @@ __device__ __forceinline__ void draw_word(const SpecParams& p, const int b, cons
   for (;;) {
     const float* cells = p.cells + ((long long)b * 2 + which) * n_cells;
 #pragma unroll
-    for (int q = 0; q < kMaxCpt; ++q) cell_sum[q] = c0 + q < c1 ? cells[c0 + q] : 0.f;
+    for (int q = 0; q < kMaxCpt; ++q) cell_sum[q] = c0 + q < c1 ? load_agent(cells + c0 + q) : 0.f;
     local = 0.f;
 #pragma unroll
     for (int q = 0; q < kMaxCpt; ++q) local += cell_sum[q];
@@ -402,17 +410,20 @@ __global__ __launch_bounds__(kSdThreads) void sd_cells(SpecParams p) {
   for (int v = 0; v < NV; ++v) {
     const float a = wave_sum(sp[v]);
     const float r = wave_sum(sr[v]);
-    if (lane == 0) { cells_p[v * kSdWaves + wave] = a; cells_r[v * kSdWaves + wave] = r; }
+    if (lane == 0) {
+      store_agent(cells_p + v * kSdWaves + wave, a);
+      store_agent(cells_r + v * kSdWaves + wave, r);
+    }
   }
   // The last of the sequence's blocks to get here draws the word: the others' cell sums are in memory by then, nobody
-  // waits for anybody.  Each wave waits for its own stores before the barrier: the barrier alone orders them only within
-  // the block, and the release of the thread that counts waits only for its own wave's.
+  // waits for anybody.  The sums are written through to the device's memory and read from there, and each wave waits for
+  // its own stores before the barrier in front of the count, so the count needs no fence; a release in every block writes
+  // the whole L2 back each time (16 x 11 rows of 152064 words 33.1 us against 29.1 with a launch of its own).
   wait_vmcnt<0>();
   __syncthreads();
-  if (tid == 0) sh_j = __hip_atomic_fetch_add(p.arrived + b, 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
+  if (tid == 0) sh_j = __hip_atomic_fetch_add(p.arrived + b, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   __syncthreads();
   if (sh_j != p.n_seg - 1) return;
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
   draw_word<T>(p, b, Chosen{j, rejected ? 1 : 0, mp, inv_zp, mq, inv_zq}, u_draw);
 }
 

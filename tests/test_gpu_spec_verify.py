@@ -142,6 +142,28 @@ def test_one_workspace_for_call_after_call(hippo, dtype, B, V):
 
 
 @pytest.mark.parametrize("dtype", ["fp32", "bf16"])
+@pytest.mark.parametrize("B,V", [(4, 152064), (64, 32000)])
+def test_a_call_sees_no_sums_of_the_call_before(hippo, dtype, B, V):
+    # one workspace under calls over other inputs, one after the other: a word drawn from cell sums that another block has
+    # not written yet would come from the call before
+    sets, refs = [], []
+    for seed in range(3):
+        pl, ql, r = synth_logits(B, 2, V, 10 * B + seed, 0.6)
+        tok = draw_from(ql, 1.0, r)
+        ua, us = r.random((B, 2)).astype(np.float32), r.random(B).astype(np.float32)
+        refs.append(run_case(hippo, pl, ql, tok, ua, us, 1.0, dtype, what="%s B%d V%d" % (dtype, B, V))[1])
+        sets.append((dev(prep(pl, dtype), dtype), dev(prep(ql, dtype), dtype), torch.from_numpy(tok).cuda(),
+                     torch.from_numpy(ua).cuda(), torch.from_numpy(us).cuda(), 1.0))
+    ws = torch.empty((hippo.load().hippo_spec_verify_workspace_bytes(B, 2, V, 0 if dtype == "fp32" else 1),),
+                     dtype=torch.uint8, device="cuda")
+    words = [torch.empty(B, dtype=torch.int32, device="cuda") for _ in range(30)]
+    for i, out in enumerate(words):
+        hippo.hippo_spec_verify(*sets[i % 3], next_token_out=out, workspace=ws)
+    for i, out in enumerate(words):
+        np.testing.assert_array_equal(out.cpu().numpy(), refs[i % 3])
+
+
+@pytest.mark.parametrize("dtype", ["fp32", "bf16"])
 def test_masked_words_edge_uniforms_and_bad_tokens(hippo, dtype):
     B, gamma, V, T = 40, 4, 20000, 1.0
     pl, ql, r = synth_logits(B, gamma, V, 5, 0.5)
