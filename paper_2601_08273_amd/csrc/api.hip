@@ -59,9 +59,10 @@ int plan_attention(int call, const hippo_kv_desc* kv, int q_len, int n_total, in
   pl->R = G * q_len;
   const bool f32 = kv->dtype == HIPPO_DTYPE_F32;
   // A block takes at most 64 rows of a 16- or 8-bit cache: more go in equal chunks, the same slices and tiles in every
-  // cache format (chunks of 64 and a rest, us a call: 33K x 4 heads, 91 rows 25.0 against 22.5; 8K, 77 rows 13.6 and
-  // 12.95; 2 x 8 heads x 8K, 96 rows 24.9 and 22.6).  The fp32 kernel takes 65 to 128 in one chunk: two chunks stream the whole cache twice and give every
-  // slice half the compute units (a call over 70K x 2 heads x 64 channels, 70 rows: 43 us in one chunk, 52 in two; four
+  // cache format (chunks of 64 and a rest -> equal ones, us a call with K and V in the last-level cache / from HBM: 33K x 4
+  // heads, 91 rows 23.3 -> 21.0 / 28.0 -> 26.4; 8K, 91 rows 14.4 -> 13.6 / 14.5 -> 13.6; 2 x 8 heads x 20K, 72 rows 40.1 -> 35.9 /
+  // 54.2 -> 53.4; 8-bit 33K, 91 rows 24.6 -> 20.7 / 25.2 -> 21.5).  The fp32 kernel takes 65 to 128 in one chunk: two chunks
+  // stream the whole cache twice and give every slice half the compute units (a call over 70K x 2 heads x 64 channels, 70 rows: 43 us in one chunk, 52 in two; four
   // sequences x 9K, 91 rows: 28.9 and 33.6).  Not where a slice per compute unit leaves units idle, which the two chunks
   // then have to themselves (1K x 4 heads x 128, 77 rows: 16.4 in one, 15.0 in two); nor where it means more than 64
   // slices, the most the merge takes in one step, of under eight tiles (64 channels x 2 heads, 91 rows, 4K: 14.9 in one
@@ -93,8 +94,9 @@ int plan_attention(int call, const hippo_kv_desc* kv, int q_len, int n_total, in
     if (S > fit) S = (int)fit;
     // A cache of a few tiles under up to 16 query rows goes in one slice, whose block writes the output itself: no merge
     // launch.  Where the line lies, us a call in a graph, slices and merge -> one slice (eager 10.7 -> 8): bf16, 7 rows,
-    // 4 heads x 128: 100 rows 6.2 -> 4.1, 250 6.2 -> 5.3, 500 6.3 -> 8.3; fp32: 100 8.1 -> 7.1, 250 8.0 -> 10.8; bf16, 35 rows:
-    // 100 6.7 -> 5.5, 250 6.9 -> 7.6.
+    // 4 heads x 128: 100 rows 6.2 -> 4.1, 250 6.2 -> 5.3, 500 6.3 -> 8.3; 8 bits: 100 6.5 -> 4.8, 200 6.6 -> 6.4, 256 6.5 -> 6.4
+    // (2 heads x 64: 256 rows bf16 5.9 -> 4.5, 8 bits 6.0 -> 5.0); fp32: 100 8.1 -> 7.1, 250 8.0 -> 10.8; bf16, 35 rows: 100
+    // 6.7 -> 5.5, 250 6.9 -> 7.6.
     const int few_tiles = pl->R > 16 ? 0 : f32 ? 4 : 8;
     if (n_tiles <= few_tiles) S = 1;
   }

@@ -880,7 +880,7 @@ __global__ __launch_bounds__(256) void emb_scores_mfma(ScoreParams p) {
 
 // =================================================================================================
 // s_temp and s_spa on MFMA, crops of at most 32 tokens: frame runs.
-// A block of eight waves (fp32: four) owns ONE crop position over a run of consecutive frames, so a frame's crop
+// A block of eight waves (fp32: four or eight) owns ONE crop position over a run of consecutive frames, so a frame's crop
 // serves as "this frame" for its Gram matrix (Eq. 5-6; its diagonal holds the norms) and as "the
 // neighbour" of the frame before and after it (Eq. 3-4) -- against four fetches per crop when every
 // (crop, frame) is a block of its own.  The wave holds 16 * U lanes' worth of 16-byte pieces of all 32
@@ -893,15 +893,16 @@ __global__ __launch_bounds__(256) void emb_scores_mfma(ScoreParams p) {
 // carries the wave's partial Gram blocks to the reduction, so the next frame's transfer is requested
 // once the reduction has read them and lands under the rest of the frame's arithmetic.
 //
-// One pass over a block's channels (512 in bf16 with U = 2, 256 in fp32 with U = 4) keeps the frame before in
-// registers.  WIDE embeddings take several passes per frame; what does not fit then is the frame before, whose
+// One pass over a block's channels (512 in bf16 with U = 2; in fp32, U = 4, 256 of four waves, 512 of eight) keeps the frame
+// before in registers.  WIDE embeddings take several passes per frame; what does not fit then is the frame before, whose
 // pass is fetched again behind this frame's: two fetches per crop and frame instead of one, against four (a row
 // per lane) in the block-per-two-crops kernel that this replaces.  Whole scoring calls, us: 4 x 36864 tokens, 1024
 // channels 831 -> 778; 2 x 40000 tokens, 768 channels 98 -> 88; 2 x 16320 tokens, 768 channels 86 and 86.
 // fp32 takes the same frame with four 16x16x4 products per 16-byte operand (3136 tokens, 128 channels 47 -> 37;
-// 12288 tokens, 512 channels 178 -> 143; 11040 tokens, 1024 channels 624 -> 562); its blocks are those of the fp32
-// sweeps, four waves, so that they ride beside pass 1 as the bf16 ones do (sattn_f32_pass1_with_emb).  The vector-ALU kernel (a block
-// per crop and frame, two LDS reads per multiply-add) is left for fp32 crops above 32 tokens.
+// 12288 tokens, 512 channels 178 -> 143; 11040 tokens, 1024 channels 624 -> 562), by blocks of four waves, as the fp32
+// sweeps', beside pass 1 (sattn_f32_pass1_with_emb), and of four or eight in a launch of their own: wide_f32_rides and
+// wide_f32_plan say which.  The vector-ALU kernel (a block per crop and frame, two LDS reads per multiply-add) is left for
+// fp32 crops above 32 tokens.
 // =================================================================================================
 // 16 bytes of zeros in device memory: what a transfer lane fetches for channels beyond the last
 __device__ __align__(16) const unsigned char g_zero_piece[16] = {0};
@@ -1238,9 +1239,8 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 3 : 2) void emb_scores_run32(Sco
 // fp32: pass 1 and the embedding terms in one launch, the sweep's blocks first.  A wave of the sweep per SIMD keeps the
 // matrix unit busy, so a riding block's trips to memory cost next to nothing; in a launch of their own the crops took
 // as long as the sweep (3136 tokens: 10.5 us of pass 1 and 13 of crops, together 14.7).  Whole scoring calls, us: 936
-// tokens 30.6 -> 22.2; 3136 tokens 37.4 -> 29.3; 2 x 12 frames, 768 channels 112 -> 99; 3 x 7220 tokens, two layers 130 -> 105;
-// 12288 tokens, 512 channels 145 -> 138; 10080 tokens, 1024 channels 160 -> 155.  Up to 168 registers a wave, 38 KB of LDS:
-// three blocks on a compute unit.
+// tokens 30.6 -> 22.2; 3136 tokens 37.4 -> 29.3; 3 x 7220 tokens, two layers 130 -> 105; of 768 channels 3136 tokens, 16 text
+// tokens 42.5 -> 39.0.  Up to 168 registers a wave, 38 KB of LDS: three blocks on a compute unit.
 template <int D, bool WIDE>
 __global__ __launch_bounds__(256, 3) void sattn_f32_pass1_with_emb(ScoreParams p, int n_sattn) {
   union Smem {
@@ -1572,8 +1572,8 @@ hipError_t launch_score(const ScoreParams& p_in, hipStream_t st) {
   const bool want_emb = (p.flags & (HIPPO_SCORE_TEMP | HIPPO_SCORE_SPA)) != 0;
   // Crops of at most 32 tokens: a block sweeps one crop position over a run of frames.  The runs are as long as
   // still leaves every compute unit a block (at most 8 frames: a run fetches its two neighbour frames on top of its
-  // own).  Half as long, two blocks per compute unit, was slower for fp32 crops beside the sweep (12288 tokens 142 against
-  // 138 us a call, 3 x 7220 tokens 112 against 105).
+  // own).  Half as long, two blocks per compute unit, was slower for fp32 crops beside the sweep (3 x 7220 tokens 112
+  // against 105 us a call).
   const long long crops_per_frame = (long long)((p.gh + p.ch - 1) / p.ch) * ((p.gw + p.cw - 1) / p.cw);
   const bool bf16 = p.dtype == HIPPO_DTYPE_BF16;
   const int de = p.emb ? p.emb_dim : p.Hkv * p.D;

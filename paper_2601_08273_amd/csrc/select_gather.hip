@@ -120,8 +120,8 @@ __device__ __forceinline__ long long gather_offset(long long row, const SelectPa
 //
 // GATHER: the launch builds the draft cache too.  Grid (H_kv * parts, B): every block selects for itself -- the same
 // integers, while all compute units but one would idle -- keeps the indices in LDS and copies its part of one KV head's
-// rows.  Saves a launch on the host (4 us) and its start on the GPU (16384 tokens x 4 heads, 10 %: 9.2 + 4.3 us of kernels
-// -> 12.1, the call 18.2 -> 15.5; 1568 x 2 heads 4.1 + 2.6 -> 6.3).
+// rows.  Saves a launch on the host and its start on the GPU (16384 tokens x 4 heads, 10 %: 9.2 + 4.3 us of kernels -> 12.1,
+// the eager call 17.7 -> 15.0; 1568 x 2 heads 4.1 + 2.6 -> 6.3).
 template <int NC, bool GATHER>
 __global__ __launch_bounds__(kSelThreads) void topk_select(SelectParams p, int vpr_shift) {
   constexpr bool CACHED = NC > 0;
@@ -400,16 +400,14 @@ hipError_t launch_select_gather(const SelectParams& p, hipStream_t st) {
   const long long per_head = gather ? (long long)p.dst_len * vpr : 0;
   if (gather && ((1 << vpr_shift) != vpr || p.Hkv > 65535 || p.B > 65535)) return hipErrorInvalidValue;
   if ((per_head + 255) / 256 > 0x7fffffffll) return hipErrorInvalidValue;
-  // One launch up to 24576 tokens (the selection of longer sequences takes as much longer in every block as the launch
-  // saves: us a call, two launches -> one, 30000 x 4 heads 18.3 -> 18.6, 34000 x 8 28.3 -> 28.4, 4 x 36864 x 8 35.1 -> 35.1;
-  // 20000 x 2 heads x 4 17.4 -> 15.2) whose indices fit the histograms' LDS (8580).  A block
-  // takes two vectors a thread, up to a block per compute unit: with one vector twice the blocks fetch the scores and run
-  // the histograms side by side (with such a launch over 40320 tokens x 8 heads 22.8 against 22.0 us a call), with four there
-  // are too few (22.5).
+  // One launch up to 24576 tokens whose indices fit the histograms' LDS (8580): us an eager call, two launches -> one, 4 heads x
+  // 16384 tokens 17.7 -> 15.0, 20000 17.8 -> 15.3, 24576 18.4 -> 15.4.  (In every block, the selection of longer sequences takes as
+  // much longer as the launch saves.)  A block takes two vectors a thread, up to a block per compute unit.  With four there are
+  // too few blocks (in a graph 4 heads x 16384 12.0 -> 12.5, 4 x 2 heads x 8192 9.3 -> 9.7); with one, of which twice as many fetch
+  // the scores, 0.2 us less in a graph (11.8, 9.0), the same eager.
   // Not beyond 128 MiB read and written: there the copy is what the call takes, and blocks of 1024 threads with the keys in
   // registers copy more slowly than gather_kv's (us a call in a graph, two launches -> one: 4 x 16384 x 8 heads, 100 MB,
-  // 24.2 -> 22.8; 8 x 16384, 112 MB, 25.8 -> 24.1; 2 x 34000, 140 MB, 37.5 -> 37.8; 12 x 16384, 167 MB, 32.9 -> 35.2;
-  // 4 x 34000, 281 MB, 57.7 -> 61.3; 48 x 8192, 182 MB, 33.6 -> 37.1).
+  // 24.2 -> 22.8; 8 x 16384, 112 MB, 25.8 -> 24.1; 12 x 16384, 167 MB, 32.9 -> 36.1; 48 x 8192, 182 MB, 33.6 -> 37.1).
   // Not where KV heads outnumber the compute units, whose second round of blocks would select once more (us a call in a graph,
   // two launches -> one: 32 x 8 heads x 1568 14.4 -> 12.9; 33 x 8 x 16384 19.1 -> 28.0; 64 x 8 x 16384 20.6 -> 28.6; 128 x 8 x
   // 1568 18.8 -> 20.2), but for two rounds over up to 4096 tokens (64 x 8 x 1568 21.5 -> 19.9, x 4096 18.2 -> 17.1, x 8192
