@@ -188,6 +188,8 @@ int attention_entry(int call, const void* q, int32_t q_len, const void* k_cache,
 // ---- scoring planning ---------------------------------------------------------------------------
 struct ScorePlan {
   int n_tile, n_rsplit;
+  bool once;
+  size_t off_word, off_large, off_arrived, once_bytes, off_redo;   // one sweep: the first three are cleared together
   size_t off_row_l, off_row_lse, off_col, off_sa, off_st, off_ss, bytes;
 };
 
@@ -217,7 +219,18 @@ int plan_score(const hippo_kv_desc* kv, const hippo_video_desc* vid, int l_txt, 
   o += col;                 pl->off_sa = o;
   o += vec;                 pl->off_st = o;
   o += vec;                 pl->off_ss = o;
-  o += vec;                 pl->bytes = o;
+  o += vec;
+  pl->once = score_once(kv->dtype, Nv);
+  if (pl->once) {
+    const size_t heads = (size_t)kv->n_kv_heads * kv->batch * n_layers, runs = heads * pl->n_rsplit;
+    const size_t words = heads * score_once_words(l_txt * (kv->n_q_heads / kv->n_kv_heads)) * sizeof(unsigned long long);
+    pl->off_word = o;       o += align_up(words, 256);
+    pl->off_large = o;      o += align_up(runs * sizeof(int), 256);
+    pl->off_arrived = o;    o += align_up(runs * sizeof(int), 256);
+    pl->once_bytes = o - pl->off_word;
+    pl->off_redo = o;       o += align_up(runs * pl->n_tile * sizeof(int), 256);
+  }
+  pl->bytes = o;
   return HIPPO_OK;
 }
 
@@ -387,6 +400,14 @@ int hippo_score_tokens_layers(int32_t n_layers, const void* const* q_txt_layers,
   p.s_spa = reinterpret_cast<float*>(ws + pl.off_ss);
   p.n_tile = pl.n_tile;
   p.n_rsplit = pl.n_rsplit;
+  p.row_word = nullptr;
+  if (pl.once) {
+    p.row_word = reinterpret_cast<unsigned long long*>(ws + pl.off_word);
+    p.run_large = reinterpret_cast<int*>(ws + pl.off_large);
+    p.run_arrived = reinterpret_cast<int*>(ws + pl.off_arrived);
+    p.tile_redo = reinterpret_cast<int*>(ws + pl.off_redo);
+    p.once_bytes = pl.once_bytes;
+  }
   const hipError_t e = launch_score(p, static_cast<hipStream_t>(stream));
   return e == hipSuccess ? HIPPO_OK : HIPPO_ERR_HIP;
 }

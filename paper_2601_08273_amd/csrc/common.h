@@ -195,6 +195,15 @@ __device__ __forceinline__ void dma16(const void* gptr, unsigned lds_addr) {
                  : "v"(gptr), "s"(uniform_addr)
                  : "memory");
 }
+// the same, past the caches that other compute units' atomics do not reach (what a relaxed load at device scope does)
+__device__ __forceinline__ void dma16_agent(const void* gptr, unsigned lds_addr) {
+  const unsigned uniform_addr = __builtin_amdgcn_readfirstlane(lds_addr);
+  unsigned saved_m0;
+  asm volatile("s_mov_b32 %0, m0\n\ts_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off sc1\n\ts_mov_b32 m0, %0"
+               : "=&s"(saved_m0)
+               : "v"(gptr), "s"(uniform_addr)
+               : "memory");
+}
 // A tile that such transfers fill is row-major and unpadded (a lane's 16 bytes land at base + lane*16);
 // bank conflicts of the MFMA operand reads are avoided by fetching, for physical 16-byte chunk c of
 // tile row r, logical chunk c ^ lds_row_swizzle(r).  D = bf16 elements per row.
@@ -296,6 +305,15 @@ struct ScoreParams {
   float* s_spa;      // [B, Nv]
   int n_tile;        // token tiles of pass 1
   int n_rsplit;      // runs the query rows of a KV head are cut into (one block each)
+  // fp32 in one sweep (row_word null: two sweeps); cleared before it, once_bytes from row_word on
+  unsigned long long* row_word;  // [Bz, Hkv, row_words, copies] row sums and the number of tiles in them
+  int* run_large;                // [Bz, n_rsplit, Hkv] a run has rows out of the words' range
+  int* run_arrived;              // [Bz, n_rsplit, Hkv] tiles of such a run whose statistics are written
+  int* tile_redo;                // [Bz, n_rsplit, Hkv, n_tile] left to the redo launch (not cleared: every block writes)
+  size_t once_bytes;
+  int row_words;                 // rows of a KV head, padded to whole chunks
+  float once_unit;               // (filled in by launch_score, as once_polls)
+  int once_polls;
   // what every wave of the sweeps would otherwise divide out for itself (filled in by launch_score)
   int rows_per_split;            // rows of a run: whole chunks (64 rows in bf16, 32 in fp32)
   int q_step_i, q_step_g;        // 64 / G and 64 % G: how (i, g) of row r = i*G + g move from chunk to chunk
@@ -304,6 +322,8 @@ struct ScoreParams {
 };
 hipError_t launch_score(const ScoreParams& p, hipStream_t st);
 int score_token_tile(int dtype);   // tokens per block in the s_attn passes
+bool score_once(int dtype, long long n_vis);       // s_attn in one sweep
+int score_once_words(int rows_per_kv_head);        // its words, of a KV head
 int score_row_splits(int dtype, long long blocks_unsplit, int rows_per_kv_head);
 
 struct SelectParams {

@@ -208,6 +208,339 @@ __global__ __launch_bounds__(256, 2) void sattn_f32(ScoreParams p) {
   sattn_f32_body<D, PASS>(p, sm, blockIdx.y, blockIdx.x, blockIdx.z % p.n_rsplit, blockIdx.z / p.n_rsplit);
 }
 
+// log2 by exponent and significand in [1, 2): the hardware's logarithm of the whole sum, up to 2^100 where no
+// maximum was taken out, is rounded towards one side at its own magnitude, for all rows alike, and the column sums
+// would keep the bias (their error against 64 bits at logits around 2 powers of two 3.3e-7, 0.6e-7 like this)
+__device__ __forceinline__ float log2_of_sum(float tot) {
+  const float exponent = (float)(__builtin_amdgcn_frexp_expf(tot) - 1);
+  return exponent + __log2f(2.f * __builtin_amdgcn_frexp_mantf(tot));
+}
+
+// =================================================================================================
+// s_attn in ONE sweep (fp32): the exponentials stay in registers until their rows' sums are known.
+//
+// The two sweeps form every product twice, because a column wants 1 / (row sum) and a row's sum is known only when every
+// block of the KV head has been through the row; in fp32 the products are all the time there is.  Here a block keeps the
+// exponentials of its last kOnceHold chunks of 32 rows in registers (16 a lane and chunk, where the products were), adds
+// its row sums to a 64-bit word a row in device memory, and adds exponential x 1 / sum to the columns kOnceHold chunks
+// later, when the words have counted every tile.
+//   The words: bits 0..52 a sum in units of p.once_unit, bits 53..62 how many tiles have added theirs.  One 64-bit add
+// carries both, so nothing relies on the order of two locations, and integer sums do not depend on the order of the
+// tiles.  Four words a row, by tile: adds to one word queue up at some 25 ns each.
+//   Waiting: a block waits for the tiles of its own (layer, batch element, KV head, row run), which stand next to each
+// other in the launch order, kOnceMaxTiles of them at most.  A wave that has asked for sums once_polls times in all no
+// longer waits: its block says so in tile_redo and sattn_f32_redo sweeps that tile again, with all sums known, the same
+// operations in the same order.  So every wait ends, and no result depends on a wait, whatever else the GPU runs.
+//   Range: a wave's sums up to kOnceMax and row sums from kOnceMinUnits on (an exponential's mean over the row between
+// 2^-8 and 2^20, none above 2^25; a sum's units are then 2^-24 of it and less).  Where any row of a run leaves it, all
+// blocks of the run find that out at the same chunk (a tile does not add such a sum, and says so in run_large), write
+// (max, sum) of their rows as pass 1 does, and the last of them merges these; sattn_f32_redo runs pass 2 for that run.
+// That costs the sweep up to there: 3136 tokens x 14 heads, 16384 x 28 and 36864 x 28 with the queries of the cases times
+// 1, 3 or 6 take 24, 181 and 220 us a call (two sweeps 30, 302, 259), times 12 59, 455 and 490.
+// =================================================================================================
+constexpr int kOnceHold = 5;           // chunks between a row's exponentials and their columns
+constexpr int kOnceCopies = 4;         // words a row
+constexpr int kOnceMaxTiles = 512;     // two blocks on every compute unit
+constexpr int kOnceCountBit = 53;
+constexpr float kOnceMax = 0x1p25f;    // of a wave's 32 tokens
+constexpr float kOnceMinUnits = 0x1p24f;
+
+template <int D>
+struct SattnOnceSmem {
+  static constexpr int NW = 4, RCH = kSaF32Rows;
+  __align__(16) unsigned char Qs[2][RCH * D * 4];
+  __align__(16) unsigned long long word_s[2][kOnceCopies][RCH];   // of the chunk whose columns come next
+  float sum_s[2][NW][RCH];                               // the waves' row sums; NaN: out of range
+  int state_s[NW];
+  int large_s;                                           // a wave has met a row out of range
+  int last_s;
+};
+
+enum OnceState { kOnceDone = 0, kOnceGaveUp = 1, kOnceLarge = 2 };
+
+// where sattn_once counts and flags the row run of a block
+__device__ __forceinline__ long long once_run(const ScoreParams& p, int hk, int rs, int bz) {
+  return ((long long)bz * p.n_rsplit + rs) * p.Hkv + hk;
+}
+
+// PUBLISH = false: all words are complete (the redo launch)
+template <int D, bool PUBLISH>
+__device__ __forceinline__ int sattn_once_body(const ScoreParams& p, SattnOnceSmem<D>& sm, const int tile, const int hk,
+                                               const int rs, const int bz) {
+  constexpr int NW = SattnOnceSmem<D>::NW, RCH = SattnOnceSmem<D>::RCH, H = kOnceHold;
+  constexpr int TPW = kSaF32Tile / NW, TBW = TPW / 16;
+  constexpr int NS = D / 16;
+  constexpr int CPR = D / 4, RPI = 64 / CPR, XPW = RCH / RPI / NW, CHUNKB = RCH * D * 4;
+  constexpr int CW = RCH * kOnceCopies;                  // words a chunk
+  static_assert(RCH == 32 && CW * 8 == 64 * 16, "a transfer brings a chunk's words, a lane's sum is that of row lane % 32");
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int j = lane & 15, g = lane >> 4;
+  const int b = bz % p.B, layer = bz / p.B;
+  const int n0 = tile * kSaF32Tile + wave * TPW;
+  const int Rs = p.L * p.G;
+  const int row_begin = rs * p.rows_per_split, row_end = min(Rs, row_begin + p.rows_per_split);
+  const int n_chunks = max(0, (row_end - row_begin + RCH - 1) / RCH);
+  const float scale_log2 = rsqrtf((float)D) * kLog2e;
+  const bool small_rows = Rs < (1 << 20);
+  const float inv_g = __builtin_amdgcn_rcpf((float)p.G);
+  const float* qbase = (const float*)p.q_layers[layer] + ((long long)b * p.L * p.H + hk * p.G) * D;
+  const unsigned qs_addr = (unsigned)(uintptr_t)&sm.Qs[0][0];
+  unsigned long long* const words = p.row_word + ((long long)(bz * p.Hkv + hk) * p.row_words + row_begin) * kOnceCopies;
+  int* const run_large = p.run_large + once_run(p, hk, rs, bz);
+
+  auto request_chunk = [&](int c) {                      // into buffer c & 1; rows past the end re-read the last row
+#pragma unroll
+    for (int u = 0; u < XPW; ++u) {
+      const int rr = (wave * XPW + u) * RPI + lane / CPR;
+      const int r = min(row_begin + c * RCH + rr, Rs - 1);
+      const int i = small_rows ? row_div_group(r, inv_g) : r / p.G;
+      dma16((const char*)(qbase + ((long long)i * p.H + (r - i * p.G)) * D) + (((lane % CPR) ^ (rr & 15)) * 16),
+            qs_addr + (c & 1) * CHUNKB + (wave * XPW + u) * 1024);
+    }
+  };
+  if (n_chunks > 0) request_chunk(0);
+  if (tid == 0) sm.large_s = 0;
+  f32x4 kop[TBW][NS];
+  {
+    const float* kbase = (const float*)p.k_layers[layer] + (long long)b * p.sb + (long long)hk * p.sh +
+                         (long long)p.vis_off * p.sn + 4 * g;
+#pragma unroll
+    for (int tb = 0; tb < TBW; ++tb) {
+      const float* krow = kbase + (long long)min(n0 + tb * 16 + j, p.Nv - 1) * p.sn;   // in bounds; masked by `start`
+#pragma unroll
+      for (int s = 0; s < NS; ++s) kop[tb][s] = *(const f32x4*)(krow + 16 * s);
+    }
+#pragma unroll
+    for (int tb = 0; tb < TBW; ++tb)
+#pragma unroll
+      for (int s = 0; s < NS; ++s) asm volatile("" : "+v"(kop[tb][s]));     // settled before the loop, as in the sweeps
+  }
+  f32x4 start[TBW], col[TBW];              // where a token's product starts: minus infinity past the last token
+#pragma unroll
+  for (int tb = 0; tb < TBW; ++tb)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      start[tb][e] = n0 + tb * 16 + 4 * g + e < p.Nv ? 0.f : -INFINITY;
+      col[tb][e] = 0.f;
+    }
+  f32x4 ex[H][2][TBW];                                   // exponentials: [chunk % H][16-row block][16-token block]
+  int state = kOnceDone, polls = p.once_polls;
+
+  // Start of step c: chunk c, the waves' sums of chunk c - 1 and the words that step c - 1 asked for are there.
+  // False: a wave has met a row out of range and the block stops (what other blocks wait for before they find the same
+  // has been added).
+  auto begin_step = [&](int c) -> bool {
+    // (the wave that added the last sums leaves that one operation, issued after its transfers, in flight)
+    if (PUBLISH && c >= 2 && wave == (c & 3)) wait_vmcnt<1>();
+    else wait_vmcnt<0>();
+    __syncthreads();
+    if (__builtin_amdgcn_readfirstlane(sm.large_s)) return false;
+    if (c + 1 < n_chunks) request_chunk(c + 1);
+    if (PUBLISH && c + 1 >= H && c < n_chunks && wave == (c & 3))
+      dma16_agent(words + (c + 1 - H) * CW + 2 * lane, (unsigned)(uintptr_t)&sm.word_s[(c + 1) & 1][0][0]);
+    if (PUBLISH && c >= 1 && wave == ((c + 1) & 3)) {
+      const float(&s)[NW][RCH] = sm.sum_s[(c - 1) & 1];
+      const int rr = lane & (RCH - 1);
+      const float units = ((s[0][rr] + s[1][rr]) + (s[2][rr] + s[3][rr])) * p.once_unit;
+      const float hi = truncf(units * 0x1p-32f), lo = rintf(units - hi * 0x1p32f);
+      const unsigned long long add =
+          (1ull << kOnceCountBit) + ((unsigned long long)(unsigned)hi << 32) + (unsigned)lo;
+      if (lane < RCH && row_begin + (c - 1) * RCH + lane < Rs) {
+        if (units == units)
+          __hip_atomic_fetch_add(words + (c - 1) * CW + (tile & (kOnceCopies - 1)) * RCH + lane, add, __ATOMIC_RELAXED,
+                                 __HIP_MEMORY_SCOPE_AGENT);
+        else                               // never counted: who waits for this row looks at the flag
+          __hip_atomic_store(run_large, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      }
+    }
+    return true;
+  };
+  // 1 / sum of rows 16 * rb + j of chunk c; asked: its words were requested by the step before
+  auto weights = [&](int c, bool asked, float (&w)[2]) {
+    const int rr = lane & (RCH - 1);
+    const bool real = row_begin + c * RCH + rr < Rs;
+    auto ask = [&]() {
+      unsigned long long word = 0;
+#pragma unroll
+      for (int k = 0; k < kOnceCopies; ++k)
+        word += __hip_atomic_load(words + c * CW + k * RCH + rr, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      return word;
+    };
+    unsigned long long word = 0;
+    if (!PUBLISH) {
+      word = ask();
+    } else {
+      if (asked) {
+#pragma unroll
+        for (int k = 0; k < kOnceCopies; ++k) word += sm.word_s[(c + H) & 1][k][rr];
+      }
+      while (state == kOnceDone && !__all(!real || (unsigned)(word >> kOnceCountBit) == (unsigned)p.n_tile)) {
+        if (__hip_atomic_load(run_large, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) state = kOnceLarge;
+        else if (--polls < 0) state = kOnceGaveUp;
+        else word = ask();
+      }
+    }
+    const unsigned hi = (unsigned)(word >> 32) & ((1u << (kOnceCountBit - 32)) - 1);
+    const float units = fmaf((float)hi, 0x1p32f, (float)(unsigned)word);
+    if (state == kOnceDone && __any(real && units < kOnceMinUnits)) {
+      state = kOnceLarge;
+      if (PUBLISH) __hip_atomic_store(run_large, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    if (state == kOnceLarge) sm.large_s = 1;
+    const unsigned inv = __float_as_uint(real ? p.once_unit / units : 0.f);
+    auto a = __builtin_amdgcn_permlane16_swap(inv, inv, false, false);
+    w[0] = __uint_as_float(a[0]);
+    w[1] = __uint_as_float(a[1]);
+  };
+  auto add_columns = [&](const f32x4 (&z)[TBW], float w) {
+#pragma unroll
+    for (int tb = 0; tb < TBW; ++tb)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) col[tb][e] = fmaf(z[tb][e], w, col[tb][e]);
+  };
+  auto produce = [&](int c, f32x4 (&z)[2][TBW]) {
+    const unsigned char* Qc = &sm.Qs[c & 1][0];
+    float ps[2];
+#pragma unroll
+    for (int rb = 0; rb < 2; ++rb) {
+#pragma unroll
+      for (int s = 0; s < NS; ++s) {
+        const f32x4 qop = *(const f32x4*)(Qc + (rb * 16 + j) * (D * 4) + (((4 * s + g) ^ j) * 16));
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+#pragma unroll
+          for (int tb = 0; tb < TBW; ++tb)
+            z[rb][tb] = __builtin_amdgcn_mfma_f32_16x16x4f32(kop[tb][s][k], qop[k], s + k == 0 ? start[tb] : z[rb][tb],
+                                                             0, 0, 0);
+      }
+      float t[TBW];
+#pragma unroll
+      for (int tb = 0; tb < TBW; ++tb) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) z[rb][tb][e] = fast_exp2(z[rb][tb][e] * scale_log2);
+        t[tb] = (z[rb][tb][0] + z[rb][tb][1]) + (z[rb][tb][2] + z[rb][tb][3]);
+      }
+      ps[rb] = t[0] + t[1];
+    }
+    // lane (j, g) -> row 16 * (g & 1) + j
+    const float pair = rows_sum_swap16(ps[0], ps[1]), tot = rows_sum_swap32(pair, pair);
+    if (lane < RCH) sm.sum_s[c & 1][wave][lane] = tot <= kOnceMax ? tot : NAN;       // (false for NaN)
+  };
+
+  bool going = true;
+#pragma unroll
+  for (int h = 0; h < H; ++h) {
+    if (h <= n_chunks) begin_step(h);
+    if (h < n_chunks) produce(h, ex[h]);
+  }
+  for (int c0 = H; c0 < n_chunks + H && going; c0 += H) {
+#pragma unroll
+    for (int h = 0; h < H; ++h) {
+      const int c = c0 + h;
+      if (c >= n_chunks + H) break;
+      if (c <= n_chunks && !begin_step(c)) {
+        going = false;
+        break;
+      }
+      float w[2];
+      weights(c - H, c <= n_chunks, w);
+#pragma unroll
+      for (int rb = 0; rb < 2; ++rb) add_columns(ex[h][rb], w[rb]);
+      if (c < n_chunks) produce(c, ex[h]);
+    }
+  }
+  if (lane == 0) sm.state_s[wave] = state;
+  __syncthreads();
+  int worst = sm.state_s[0];
+#pragma unroll
+  for (int w = 1; w < NW; ++w) worst = max(worst, sm.state_s[w]);
+  __syncthreads();
+  if (worst == kOnceDone) {
+#pragma unroll
+    for (int tb = 0; tb < TBW; ++tb)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const float v = row16_sum(col[tb][e]);           // the 16 rows held by the lanes of each group g
+        const int n = n0 + tb * 16 + 4 * g + e;
+        if (j == 0 && n < p.Nv)
+          p.col_part[((long long)bz * p.Hkv * p.n_rsplit + hk + p.Hkv * rs) * p.Nv + n] = v;
+      }
+  }
+  return worst;
+}
+
+// block -> tile fastest, then KV head, row run, (layer, batch element): blocks that wait for each other start together
+__device__ __forceinline__ void once_block(const ScoreParams& p, unsigned blk, int& tile, int& hk, int& rs, int& bz) {
+  const unsigned run = blk / (unsigned)p.n_tile, rest = run / (unsigned)p.Hkv;
+  tile = (int)(blk - run * (unsigned)p.n_tile);
+  hk = (int)(run - rest * (unsigned)p.Hkv);
+  rs = (int)(rest % (unsigned)p.n_rsplit);
+  bz = (int)(rest / (unsigned)p.n_rsplit);
+}
+
+// the words, run_large and run_arrived, which lie one behind the other
+__global__ __launch_bounds__(256) void sattn_once_clear(u32x4* at, long long n) {
+  const long long i = (long long)blockIdx.x * 256 + threadIdx.x;
+  if (i < n) at[i] = (u32x4){0u, 0u, 0u, 0u};
+}
+
+template <int D>
+__device__ __forceinline__ void sattn_once_block(const ScoreParams& p, SattnOnceSmem<D>& once, SattnF32Smem<D>& sweep,
+                                                 const unsigned blk) {
+  int tile, hk, rs, bz;
+  once_block(p, blk, tile, hk, rs, bz);
+  const int state = sattn_once_body<D, true>(p, once, tile, hk, rs, bz);
+  if (threadIdx.x == 0) p.tile_redo[blk] = state != kOnceDone;
+  if (state == kOnceDone) return;
+  // Statistics as pass 1's, for the case that the run's rows are out of range; then every block of the run comes here.
+  // (one thread's release and acquire stand for the block's, whose stores and loads the barriers order with it)
+  sattn_f32_body<D, 1>(p, sweep, tile, hk, rs, bz);
+  __syncthreads();
+  if (threadIdx.x == 0)
+    once.last_s = __hip_atomic_fetch_add(p.run_arrived + once_run(p, hk, rs, bz), 1, __ATOMIC_ACQ_REL,
+                                         __HIP_MEMORY_SCOPE_AGENT) == p.n_tile - 1;
+  __syncthreads();
+  if (!once.last_s) return;
+  const int Rs = p.L * p.G, row_begin = rs * p.rows_per_split, row_end = min(Rs, row_begin + p.rows_per_split);
+  for (int r = row_begin + (int)threadIdx.x; r < row_end; r += 256) {
+    constexpr int NB = 16;                               // tiles in flight: this block is alone with all of them
+    float mx = -INFINITY, tot = 0.f;
+    for (int t0 = 0; t0 < p.n_tile; t0 += NB) {
+      float m[NB], l[NB], to = mx;
+#pragma unroll
+      for (int u = 0; u < NB; ++u) {
+        const long long at = sattn_part_at(p, min(t0 + u, p.n_tile - 1), bz, hk, r);
+        m[u] = t0 + u < p.n_tile ? p.row_m[at] : -INFINITY;
+        l[u] = t0 + u < p.n_tile ? p.row_l[at] : 0.f;
+      }
+#pragma unroll
+      for (int u = 0; u < NB; ++u) to = max_nan(to, m[u]);
+      tot *= mx != -INFINITY ? fast_exp2(mx - to) : 0.f;
+#pragma unroll
+      for (int u = 0; u < NB; ++u) tot += m[u] != -INFINITY ? l[u] * fast_exp2(m[u] - to) : 0.f;
+      mx = to;
+    }
+    p.row_lse[((long long)bz * p.Hkv + hk) * Rs + r] = mx + log2_of_sum(tot);
+  }
+}
+
+// The tiles that sattn_once left: all of a run with rows out of range (pass 2), and those that no longer waited.
+template <int D>
+__global__ __launch_bounds__(256, 2) void sattn_f32_redo(ScoreParams p) {
+  if (p.tile_redo[blockIdx.x] == 0) return;
+  union Smem {
+    SattnOnceSmem<D> once;
+    SattnF32Smem<D> sweep;
+  };
+  __shared__ Smem sm;
+  int tile, hk, rs, bz;
+  once_block(p, blockIdx.x, tile, hk, rs, bz);
+  // (row sums too small, but not one block of the run that waited for them and said so: all wrote statistics)
+  if (p.run_large[once_run(p, hk, rs, bz)] || sattn_once_body<D, false>(p, sm.once, tile, hk, rs, bz) == kOnceLarge)
+    sattn_f32_body<D, 2>(p, sm.sweep, tile, hk, rs, bz);
+}
+
 // =================================================================================================
 // s_attn, MFMA version (bf16).  Block = 8 waves x 32 tokens; each wave keeps its 32 keys as MFMA A
 // operands in registers for the whole sweep over the query rows, which are staged through LDS in
@@ -572,11 +905,7 @@ __global__ __launch_bounds__(256) void sattn_row_lse(ScoreParams p) {
     float tot = 0.f;
 #pragma unroll
     for (int u = 0; u < 8; ++u) tot += (sm[u][rl] != -INFINITY) ? sl[u][rl] * fast_exp2(sm[u][rl] - mx) : 0.f;
-    // log2 by exponent and significand in [1, 2): the hardware's logarithm of the whole sum, up to 2^100 where no
-    // maximum was taken out, is rounded towards one side at its own magnitude, for all rows alike, and the column sums
-    // would keep the bias (their error against 64 bits at logits around 2 powers of two 3.3e-7, 0.6e-7 like this)
-    const float exponent = (float)(__builtin_amdgcn_frexp_expf(tot) - 1);
-    p.row_lse[row] = mx + (exponent + __log2f(2.f * __builtin_amdgcn_frexp_mantf(tot)));
+    p.row_lse[row] = mx + log2_of_sum(tot);
   }
 }
 
@@ -1258,6 +1587,19 @@ __global__ __launch_bounds__(256, 3) void sattn_f32_pass1_with_emb(ScoreParams p
   emb_run32_block<true, 4, 4, WIDE>(p, sm.run, (unsigned)(blk - n_sattn));
 }
 
+// The same beside the one sweep
+template <int D, bool WIDE>
+__global__ __launch_bounds__(256, 2) void sattn_once_with_emb(ScoreParams p, int n_sattn) {
+  union Smem {
+    SattnOnceSmem<D> once;
+    SattnF32Smem<D> sweep;
+    EmbRunSmem<4, 4> run;
+  };
+  __shared__ Smem sm;
+  if ((int)blockIdx.x < n_sattn) sattn_once_block<D>(p, sm.once, sm.sweep, blockIdx.x);
+  else emb_run32_block<true, 4, 4, WIDE>(p, sm.run, blockIdx.x - (unsigned)n_sattn);
+}
+
 // Pass 1 of s_attn and the embedding terms in ONE launch: the first n_sattn blocks run the
 // (compute-bound) row-statistics sweep, two per compute unit; the remaining blocks run the crops and
 // fill the third block slot of the compute units, so the memory-bound embedding work hides under the
@@ -1438,12 +1780,16 @@ int score_token_tile(int dtype) { return dtype == HIPPO_DTYPE_BF16 ? kSaMfmaTile
 int score_row_splits(int dtype, long long blocks_unsplit, int rows_per_kv_head) {
   int best = 1;
   if (dtype != HIPPO_DTYPE_BF16) {
-    // fp32: a wave per SIMD keeps the matrix unit busy, so a compute unit takes its blocks one after the other in
-    // effect; a block's start costs about what 0.7 of its 32-row chunks do
+    // fp32: a wave per SIMD nearly keeps the matrix unit busy, so a compute unit takes its blocks one after the other in
+    // effect, and one alone about an eighth longer than two side by side; a block's start, and in the one sweep the way of
+    // its last sums, cost about what 2.2 of its 32-row chunks do.  (us a call, in runs as chosen | one run | others: 4096
+    // tokens, 64 heads, 128 text rows 133 | 144 | 135-147; 12288 tokens, 28 heads, 64 rows 119 | 115 | 113-140; 36864
+    // tokens, 28 heads, 40 rows 228 | 228 | 248-394.)
     const int chunks = (rows_per_kv_head + kSaF32Rows - 1) / kSaF32Rows;
     double best_cost = 0.0;
     for (int rs = 1; rs <= 8 && rs <= chunks; ++rs) {
-      const double cost = (double)((blocks_unsplit * rs + kNumCU - 1) / kNumCU) * ((chunks + rs - 1) / rs + 0.7);
+      const long long rounds = (blocks_unsplit * rs + kNumCU - 1) / kNumCU;
+      const double cost = (rounds == 1 ? 1.12 : (double)rounds) * ((chunks + rs - 1) / rs + 2.2);
       if (rs == 1 || cost < best_cost * 0.97) {
         best = rs;
         best_cost = cost;
@@ -1465,6 +1811,32 @@ int score_row_splits(int dtype, long long blocks_unsplit, int rows_per_kv_head) 
     }
   }
   return best;
+}
+
+// Beyond kOnceMaxTiles (65536 tokens) a run's blocks would not all fit on the chip at once, and two sweeps stay.  Below, one
+// sweep was the faster everywhere, also where a run's tiles fill compute units unevenly (36864 tokens: 288 blocks wait
+// for the 32 compute units that hold two of them).  Whole calls replayed from a graph, us, two sweeps -> one: 484 tokens x
+// 4 heads, 16 text rows 24.1 -> 23.0; 936 x 14 24.9 -> 23.7; 3136 x 14, 64 rows 32.5 -> 28.7; 4096 x 64 heads, 128 rows
+// 224 -> 133; 12288 x 28, 64 rows 140 -> 119; 16384 x 28, 128 rows 307 -> 188; 36864 x 28, 40 rows 264 -> 228; 60500 x 4,
+// 64 rows 112 -> 97.  Rows out of the words' range cost the sweep up to where they are met.
+bool score_once(int dtype, long long n_vis) {
+  return dtype == HIPPO_DTYPE_F32 && (n_vis + kSaF32Tile - 1) / kSaF32Tile <= kOnceMaxTiles;
+}
+int score_once_words(int rows_per_kv_head) {
+  return (rows_per_kv_head + kSaF32Rows - 1) / kSaF32Rows * kSaF32Rows * kOnceCopies;
+}
+
+// riders: blocks of the embedding terms beside the sweep (wide: of more channels than a pass takes)
+template <int D>
+static hipError_t launch_sattn_once(const ScoreParams& p, hipStream_t st, long long riders, bool wide) {
+  const long long n_sattn = (long long)p.n_tile * p.Hkv * p.n_rsplit * p.Bz;
+  const long long n_clear = (long long)(p.once_bytes / sizeof(u32x4));
+  hipLaunchKernelGGL(sattn_once_clear, dim3((unsigned)((n_clear + 255) / 256)), dim3(256), 0, st, (u32x4*)p.row_word, n_clear);
+  const dim3 grid((unsigned)(n_sattn + riders));
+  if (wide) hipLaunchKernelGGL((sattn_once_with_emb<D, true>), grid, dim3(256), 0, st, p, (int)n_sattn);
+  else hipLaunchKernelGGL((sattn_once_with_emb<D, false>), grid, dim3(256), 0, st, p, (int)n_sattn);
+  hipLaunchKernelGGL(sattn_f32_redo<D>, dim3((unsigned)n_sattn), dim3(256), 0, st, p);
+  return hipGetLastError();
 }
 
 template <int D>
@@ -1561,6 +1933,13 @@ hipError_t launch_score(const ScoreParams& p_in, hipStream_t st) {
     const int unit = p.dtype == HIPPO_DTYPE_BF16 ? 64 : kSaF32Rows;      // rows per chunk of the sweeps
     const int rows = p.L * p.G, chunks = (rows + unit - 1) / unit, rs = p.n_rsplit > 0 ? p.n_rsplit : 1;
     p.rows_per_split = (chunks + rs - 1) / rs * unit;
+    p.row_words = chunks * unit;
+    // one sweep: units of the words (of its inverse: 2^32 over the tokens as a power of two, so that the sums of all waves
+    // at kOnceMax stay below 2^53), and how often a wave asks in all (about a microsecond each): a few times as long as
+    // the sweep of its own run of rows takes
+    p.once_unit = 0x1p27f;
+    for (long long n = 32; n < p.Nv; n *= 2) p.once_unit *= 0.5f;
+    p.once_polls = 64 + 16 * (p.rows_per_split / kSaF32Rows);
     p.q_step_i = 64 / p.G;
     p.q_step_g = 64 % p.G;
     p.q_last_i = (rows - 1) / p.G;
@@ -1597,6 +1976,8 @@ hipError_t launch_score(const ScoreParams& p_in, hipStream_t st) {
     if (p.dtype == HIPPO_DTYPE_BF16)
       e = (p.D == 128) ? launch_sattn_mfma<128>(p, st, riders, wide)
                        : launch_sattn_mfma<64>(p, st, riders, wide);
+    else if (p.row_word != nullptr)
+      e = (p.D == 128) ? launch_sattn_once<128>(p, st, riders, wide) : launch_sattn_once<64>(p, st, riders, wide);
     else
       e = (p.D == 128) ? launch_sattn_f32<128>(p, st, riders, wide) : launch_sattn_f32<64>(p, st, riders, wide);
     if (e != hipSuccess) return e;

@@ -372,6 +372,34 @@ def test_attention_mass_where_some_rows_leave_the_exponent_range(hippo, first, l
     assert_close(got, oracle.s_attn(q, k, 2, 257), "bf16", "rows %d to %d d=%d" % (first, last, d))
 
 
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("n, L, H, Hkv", [
+    # tiles of 128 tokens: one with idle waves, whole ones, one token more; chunks of 32 query rows: one row, one chunk, as many
+    # as stay in registers (5), one more, several runs; the most tiles that take one sweep, and one token more
+    (97, 1, 1, 1), (128, 8, 4, 1), (129, 23, 14, 2), (1408, 40, 4, 1), (257, 41, 4, 1), (3000, 91, 14, 2),
+    (65536, 3, 2, 1), (65537, 3, 2, 1),
+])
+@pytest.mark.parametrize("rows_out", [None, (0, 1, 60.0), (-1, None, 60.0), (0, 1, -30.0), (0, None, 60.0)])
+def test_fp32_attention_mass_in_one_sweep(hippo, n, L, H, Hkv, d, rows_out):
+    # logits of a few units, and text rows (the first, the last, all) whose exponentials leave the range of the sums that
+    # the blocks exchange, upwards or downwards
+    if rows_out is not None and n > 4000:
+        rows_out = rows_out[:2] + (rows_out[2] / 2,)
+    q, k = score_inputs(n + L, 2 if n < 200 else 1, L, H, Hkv, d, n + 5, "fp32", 0.7)
+    q[..., 0] = 0.0
+    if rows_out is not None:
+        first, last, shift = rows_out
+        q[:, first:last, :, 0] = np.sqrt(d)
+        k[..., 0] = shift
+    ref = oracle.s_attn(q, k, 2, n)
+    got = attention_mass(hippo, q, k, "fp32", 1, 1, n, 2)
+    # 1e-5, and of a logit of `shift`: the channel that makes it comes first, so each of d additions, the product with the
+    # scale and the one with log2(e) round by up to 2^-24 of it, and an exponential moves by as much
+    shift = 0.0 if rows_out is None else abs(rows_out[2])
+    bound = (1e-5 + shift * (d + 2) * 2.0 ** -24) * np.maximum(np.abs(ref), np.sqrt((ref ** 2).mean()))
+    assert (np.abs(got - ref) <= bound).all(), np.abs((got - ref) / bound).max()
+
+
 @pytest.mark.parametrize("dtype", ["fp32", "bf16"])
 @pytest.mark.parametrize("rows, d", [(1, 64), (2047, 128), (2049, 128), (70001, 64)])
 def test_codes_over_the_exponent_range(hippo, dtype, rows, d):
