@@ -1223,10 +1223,12 @@ __global__ __launch_bounds__(256) void emb_scores_mfma(ScoreParams p) {
 // once the reduction has read them and lands under the rest of the frame's arithmetic.
 //
 // One pass over a block's channels (512 in bf16 with U = 2; in fp32, U = 4, 256 of four waves, 512 of eight) keeps the frame
-// before in registers.  WIDE embeddings take several passes per frame; what does not fit then is the frame before, whose
-// pass is fetched again behind this frame's: two fetches per crop and frame instead of one, against four (a row
-// per lane) in the block-per-two-crops kernel that this replaces.  Whole scoring calls, us: 4 x 36864 tokens, 1024
-// channels 831 -> 778; 2 x 40000 tokens, 768 channels 98 -> 88; 2 x 16320 tokens, 768 channels 86 and 86.
+// before in registers.  WIDE embeddings take several passes per frame.  Up to two of them in bf16 (NB = 2) keep it there too,
+// 32 registers, and have both passes in flight at once, each in a strip of its own: what bounded them was that the
+// frame before was fetched again behind this frame's, from beyond the L2 (two strips alone gained nothing).  The terms
+// alone | whole scoring calls, us: 4 x 36864 tokens of 1024 channels 112 -> 75 | 735 -> 712, 4 x 16384 of 1024 83 -> 47 |
+// 222 -> 197, 4 x 36864 x 14 heads, of 768 90 -> 65 | 157 -> 122, 3 x 20520 of 1024, 16 text rows 51 -> 38 | 112 -> 93.
+// More passes, and fp32, fetch it again: two fetches per crop and frame.
 // fp32 takes the same frame with four 16x16x4 products per 16-byte operand (3136 tokens, 128 channels 47 -> 37;
 // 12288 tokens, 512 channels 178 -> 143; 11040 tokens, 1024 channels 624 -> 562), by blocks of four waves, as the fp32
 // sweeps', beside pass 1 (sattn_f32_pass1_with_emb), and of four or eight in a launch of their own: wide_f32_rides and
@@ -1236,11 +1238,12 @@ __global__ __launch_bounds__(256) void emb_scores_mfma(ScoreParams p) {
 // 16 bytes of zeros in device memory: what a transfer lane fetches for channels beyond the last
 __device__ __align__(16) const unsigned char g_zero_piece[16] = {0};
 
-template <int U, int NW>
+// NB: strips of a wave
+template <int U, int NW, int NB = 1>
 struct EmbRunSmem {
   static constexpr int MP = 32;
   // operands in (32 rows x 64 U B), then Gram partials out (3 x 64 x 16 B, from four waves two sets of them)
-  __align__(16) unsigned char strip[NW][MP * 64 * U];
+  __align__(16) unsigned char strip[NB][NW][MP * 64 * U];
   float redd[8][2][16];                             // diagonals of the (this frame) x (frame before) blocks
   float G[MP][MP + 1];
   float dotv[MP];
@@ -1264,10 +1267,11 @@ __device__ __forceinline__ f32x4 emb_mma(const u32x4& a, const u32x4& b, f32x4 a
 
 // One crop position `pos` of batch element b over the frames f0 .. f0 + p.emb_run - 1 (cut at the
 // video's end), by the 64 * NW threads of a block; every thread must call it (block-wide barriers).
-template <bool F32, int U, int NW, bool WIDE>
-__device__ __forceinline__ void emb_run32_body(const ScoreParams& p, EmbRunSmem<U, NW>& sm, const int tid, const int pos,
+template <bool F32, int U, int NW, bool WIDE, int NB>
+__device__ __forceinline__ void emb_run32_body(const ScoreParams& p, EmbRunSmem<U, NW, NB>& sm, const int tid, const int pos,
                                                const int f0, const int b) {
-  constexpr int MP = EmbRunSmem<U, NW>::MP;
+  constexpr int MP = EmbRunSmem<U, NW, NB>::MP;
+  static_assert((WIDE || NB == 1) && (NB == 1 || NW == 8), "one pass: the next frame travels while this one is reduced");
   constexpr int TPT = NW * 64 / MP, CPT = MP / TPT; // threads per token, cosines per thread
   static_assert((NW == 8 && TPT == 16) || (NW == 4 && TPT == 8), "a token's threads are half or all of a 16-lane row");
   constexpr int EB = F32 ? 4 : 2;                   // bytes per channel
@@ -1326,8 +1330,8 @@ __device__ __forceinline__ void emb_run32_body(const ScoreParams& p, EmbRunSmem<
       }
     }
   }
-  unsigned char* strip = &sm.strip[wave][0];
-  const unsigned strip_addr = (unsigned)(uintptr_t)strip;
+  unsigned char* strip = &sm.strip[0][wave][0];     // (two: the one that is read)
+  unsigned strip_addr = (unsigned)(uintptr_t)strip;
   auto request = [&](int frame, int pass) {         // single pass: frames lo, lo + 1, ... in turn
 #pragma unroll
     for (int i = 0; i < NT; ++i) {
@@ -1380,14 +1384,57 @@ __device__ __forceinline__ void emb_run32_body(const ScoreParams& p, EmbRunSmem<
   // from 64 bits.)
   constexpr int SETS = WIDE ? 8 / NW : 1;
   constexpr int kSetBytes = 3 * 64 * 16;
-  static_assert(SETS * kSetBytes <= (int)sizeof(sm.strip[0]) && SETS * NW <= 8, "a strip takes its wave's partial sums");
+  static_assert(SETS * kSetBytes <= (int)sizeof(sm.strip[0][0]) && SETS * NW <= 8, "a strip takes its wave's partial sums");
   constexpr int UP = WIDE ? 1 : U;
   u32x4 prev[2][UP];                                // single pass: the operands of the frame before
 #pragma unroll
   for (int rbk = 0; rbk < 2; ++rbk)
 #pragma unroll
     for (int u = 0; u < UP; ++u) prev[rbk][u] = (u32x4){0u, 0u, 0u, 0u};
-  request(lo, 0);
+  // Two strips and at most two passes: the frame before stays in registers as with one pass.
+  constexpr int HP = NB == 2 ? 2 : 1;
+  const bool hold = NB == 2 && n_pass <= HP;
+  u32x4 held[HP][2][U];
+#pragma unroll
+  for (int h = 0; h < HP; ++h)
+#pragma unroll
+    for (int rbk = 0; rbk < 2; ++rbk)
+#pragma unroll
+      for (int u = 0; u < U; ++u) held[h][rbk][u] = (u32x4){0u, 0u, 0u, 0u};
+  // Two strips: the transfers of a run in the order in which they are wanted, into one and the other in turn, so that one
+  // travels while the other is multiplied and while a frame is reduced.
+  int t_fr = lo, t_pass = 0, in_flight = 0;
+  bool t_before = false;
+  unsigned put = 0, take = 0;
+  auto issue = [&]() {
+    if (t_fr > hi) return;
+    strip_addr = (unsigned)(uintptr_t)&sm.strip[put][wave][0];
+    request(t_before ? t_fr - 1 : t_fr, t_pass);
+    put ^= 1;
+    ++in_flight;
+    if (!hold && !t_before && t_fr > lo) {
+      t_before = true;
+    } else {
+      t_before = false;
+      if (++t_pass == n_pass) {
+        t_pass = 0;
+        ++t_fr;
+      }
+    }
+  };
+  auto arrive = [&]() {                             // the oldest transfer in flight is in its strip
+    if (in_flight > 1) wait_vmcnt<NT>();
+    else wait_vmcnt<0>();
+    --in_flight;
+    strip = &sm.strip[take][wave][0];
+    take ^= 1;
+  };
+  if constexpr (NB == 2) {
+    issue();
+    issue();
+  } else {
+    request(lo, 0);
+  }
   for (int fr = lo; fr <= hi; ++fr) {
     f32x4 dot[SETS][2];
     // D[i][j']: a lane holds column j' = j, rows i = 4g..4g+3.  Gram blocks (0,0) (0,1) (1,1); a neighbour frame
@@ -1430,21 +1477,27 @@ __device__ __forceinline__ void emb_run32_body(const ScoreParams& p, EmbRunSmem<
       const bool has_before = fr > lo;
       auto take_pass = [&](int pass, f32x4 (&gram)[3], f32x4 (&dot)[2]) {
         u32x4 cur[2][U];
-        wait_vmcnt<0>();
+        if constexpr (NB == 2) arrive();
+        else wait_vmcnt<0>();
 #pragma unroll
         for (int rbk = 0; rbk < 2; ++rbk)
 #pragma unroll
           for (int u = 0; u < U; ++u) cur[rbk][u] = operand(rbk, u);
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // read before the next transfer may overwrite them
-        if (has_before) request(fr - 1, pass);
-        else if (pass + 1 < n_pass) request(fr, pass + 1);
+        if constexpr (NB == 2) {
+          if (has_before || pass + 1 < n_pass) issue();      // (the frame's last strip takes the partial sums first)
+        } else {
+          if (has_before) request(fr - 1, pass);
+          else if (pass + 1 < n_pass) request(fr, pass + 1);
+        }
 #pragma unroll
         for (int i = 0; i < 3; ++i)
           if (i != 1 || own_frame)
 #pragma unroll
             for (int u = 0; u < U; ++u) gram[i] = emb_mma<F32>(cur[i >> 1][u], cur[(i + 1) >> 1][u], gram[i]);
         if (has_before) {
-          wait_vmcnt<0>();
+          if constexpr (NB == 2) arrive();
+          else wait_vmcnt<0>();
 #pragma unroll
           for (int rbk = 0; rbk < 2; ++rbk) {
             u32x4 before[U];
@@ -1454,12 +1507,42 @@ __device__ __forceinline__ void emb_run32_body(const ScoreParams& p, EmbRunSmem<
             for (int u = 0; u < U; ++u) dot[rbk] = emb_mma<F32>(cur[rbk][u], before[u], dot[rbk]);
           }
           asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-          if (pass + 1 < n_pass) request(fr, pass + 1);
+          if (pass + 1 < n_pass) {
+            if constexpr (NB == 2) issue();
+            else request(fr, pass + 1);
+          }
         }
       };
-      for (int pass = 0; pass < n_pass; pass += SETS) {
-        take_pass(pass, gram[0], dot[0]);
-        if (SETS == 2 && pass + 1 < n_pass) take_pass(pass + 1, gram[SETS - 1], dot[SETS - 1]);
+      if (NB == 2 && hold) {
+#pragma unroll
+        for (int h = 0; h < HP; ++h) {
+          if (h >= n_pass) break;
+          u32x4 cur[2][U];
+          arrive();
+#pragma unroll
+          for (int rbk = 0; rbk < 2; ++rbk)
+#pragma unroll
+            for (int u = 0; u < U; ++u) cur[rbk][u] = operand(rbk, u);
+          asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+          if (h + 1 < n_pass) issue();
+#pragma unroll
+          for (int i = 0; i < 3; ++i)
+            if (i != 1 || own_frame)
+#pragma unroll
+              for (int u = 0; u < U; ++u) gram[0][i] = emb_mma<F32>(cur[i >> 1][u], cur[(i + 1) >> 1][u], gram[0][i]);
+#pragma unroll
+          for (int rbk = 0; rbk < 2; ++rbk)
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+              dot[0][rbk] = emb_mma<F32>(cur[rbk][u], held[h][rbk][u], dot[0][rbk]);
+              held[h][rbk][u] = cur[rbk][u];
+            }
+        }
+      } else {
+        for (int pass = 0; pass < n_pass; pass += SETS) {
+          take_pass(pass, gram[0], dot[0]);
+          if (SETS == 2 && pass + 1 < n_pass) take_pass(pass + 1, gram[SETS - 1], dot[SETS - 1]);
+        }
       }
 #pragma unroll
       for (int s = 0; s < SETS; ++s)
@@ -1485,10 +1568,11 @@ __device__ __forceinline__ void emb_run32_body(const ScoreParams& p, EmbRunSmem<
     // blocks also give the scales of the rows' norms), wave 3 the diagonals of the dot blocks
     if (wave < 3 && (own_frame || wave != 1)) {
       const int blk = wave;
-      f32x4 v = *(const f32x4*)(&sm.strip[0][0] + (blk * 64 + lane) * 16);
+      const unsigned used = NB == 2 ? take ^ 1 : 0;  // the strips that took the partial sums
+      f32x4 v = *(const f32x4*)(&sm.strip[used][0][0] + (blk * 64 + lane) * 16);
 #pragma unroll
       for (int w = 1; w < SETS * NW; ++w)
-        v += *(const f32x4*)(&sm.strip[w % NW][0] + (w / NW) * kSetBytes + (blk * 64 + lane) * 16);
+        v += *(const f32x4*)(&sm.strip[used][w % NW][0] + (w / NW) * kSetBytes + (blk * 64 + lane) * 16);
       const int ra = blk == 2 ? 1 : 0, rbk = blk == 0 ? 0 : 1;
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
@@ -1509,7 +1593,8 @@ __device__ __forceinline__ void emb_run32_body(const ScoreParams& p, EmbRunSmem<
       sm.dotv[lane] = d;
     }
     __syncthreads();
-    if (fr < hi) request(fr + 1, 0);                // the strips are free again: the next frame travels meanwhile
+    if constexpr (NB == 2) issue();                 // the strips are free again: the next frame travels meanwhile
+    else if (fr < hi) request(fr + 1, 0);
 
     // cosines of token a against tokens c0 .. c0 + CPT - 1 (its TPT threads cover the crop; padding rows hold
     // finite values and are masked); Eq. 5-6: their variance -- for the run's own frames only
@@ -1548,21 +1633,21 @@ __device__ __forceinline__ void emb_run32_body(const ScoreParams& p, EmbRunSmem<
 }
 
 // block number -> (crop position, run of frames, batch element), positions fastest
-template <bool F32, int U, int NW, bool WIDE>
-__device__ __forceinline__ void emb_run32_block(const ScoreParams& p, EmbRunSmem<U, NW>& sm, const unsigned blk) {
+template <bool F32, int U, int NW, bool WIDE, int NB = 1>
+__device__ __forceinline__ void emb_run32_block(const ScoreParams& p, EmbRunSmem<U, NW, NB>& sm, const unsigned blk) {
   const unsigned ncf = (unsigned)(((p.gh + p.ch - 1) / p.ch) * ((p.gw + p.cw - 1) / p.cw));   // crops per frame
   const unsigned n_runs = (unsigned)((p.F + p.emb_run - 1) / p.emb_run);
   const unsigned rest = blk / ncf, pos = blk - rest * ncf;
   const unsigned bb = rest / n_runs, run = rest - bb * n_runs;
-  emb_run32_body<F32, U, NW, WIDE>(p, sm, threadIdx.x, (int)pos, (int)run * p.emb_run, (int)bb);
+  emb_run32_body<F32, U, NW, WIDE, NB>(p, sm, threadIdx.x, (int)pos, (int)run * p.emb_run, (int)bb);
 }
 
 // (four waves: three blocks on a compute unit; with registers for two, 4 x 72 frames of 768 channels took 256 us, not 187)
 template <bool F32, int NW, bool WIDE>
 __global__ __launch_bounds__(64 * NW, NW == 4 ? 3 : 2) void emb_scores_run32(ScoreParams p) {
-  constexpr int U = F32 ? 4 : 2;
-  __shared__ EmbRunSmem<U, NW> sm;
-  emb_run32_block<F32, U, NW, WIDE>(p, sm, blockIdx.x);
+  constexpr int U = F32 ? 4 : 2, NB = WIDE && !F32 ? 2 : 1;
+  __shared__ EmbRunSmem<U, NW, NB> sm;
+  emb_run32_block<F32, U, NW, WIDE, NB>(p, sm, blockIdx.x);
 }
 
 // fp32: pass 1 and the embedding terms in one launch, the sweep's blocks first.  A wave of the sweep per SIMD keeps the
@@ -1604,18 +1689,19 @@ __global__ __launch_bounds__(256, 2) void sattn_once_with_emb(ScoreParams p, int
 // (compute-bound) row-statistics sweep, two per compute unit; the remaining blocks run the crops and
 // fill the third block slot of the compute units, so the memory-bound embedding work hides under the
 // sweep instead of following it.  Three blocks fit a compute unit: 8 waves of at most 80 registers
-// each and the larger of the shared-memory layouts.  A riding block owns one crop position over a run of frames;
-// WIDE: of more than 512 channels.
+// each and the larger of the shared-memory layouts.  A riding block owns one crop position over a run of frames.
+// WIDE: of more than 512 channels.  Its riders keep the frame before in registers and two transfers in flight (116 registers,
+// 70 KB of LDS: two blocks on a compute unit), and n_lead of them stand in front of the n_sattn blocks of the sweep.
 template <int D, bool WIDE>
-__global__ __launch_bounds__(kSaWaves * 64, 6) void sattn_pass1_with_emb(ScoreParams p, int n_sattn) {
+__global__ __launch_bounds__(kSaWaves * 64, WIDE ? 4 : 6) void sattn_pass1_with_emb(ScoreParams p, int n_lead, int n_sattn) {
   static_assert(kSaWaves == 8, "the riding blocks use the sweep's block size");
   union Smem {
     SattnSmem<D, 1> sa;
-    EmbRunSmem<2, 8> run;
+    EmbRunSmem<2, 8, WIDE ? 2 : 1> run;
   };
   __shared__ Smem sm;
-  const int blk = blockIdx.x;
-  if (blk < n_sattn) {                       // the order of sattn_mfma's grid: KV head fastest, then key tile, ...
+  const int blk = (int)blockIdx.x - n_lead;
+  if (blk >= 0 && blk < n_sattn) {           // the order of sattn_mfma's grid: KV head fastest, then key tile, ...
     const int hk = blk % p.Hkv, rest = blk / p.Hkv;
     const int tile = rest % p.n_tile, rest2 = rest / p.n_tile;
     sattn_mfma_body<D, 1>(p, sm.sa, tile, hk + p.Hkv * (rest2 % p.n_rsplit), rest2 / p.n_rsplit);
@@ -1623,7 +1709,7 @@ __global__ __launch_bounds__(kSaWaves * 64, 6) void sattn_pass1_with_emb(ScorePa
   }
   // (the host admits this launch only when its block count stays below 2^31: crop numbers fit 32 bits,
   // and 32-bit divisions are all that stands in front of a riding block's first load)
-  emb_run32_block<false, 2, 8, WIDE>(p, sm.run, (unsigned)(blk - n_sattn));
+  emb_run32_block<false, 2, 8, WIDE, WIDE ? 2 : 1>(p, sm.run, blk < 0 ? blockIdx.x : (unsigned)(blk - n_sattn));
 }
 
 // =================================================================================================
@@ -1867,10 +1953,14 @@ static hipError_t launch_sattn_mfma(const ScoreParams& p, hipStream_t st, long l
   if (riders > 0) {
     const long long n_sattn = (long long)p.n_tile * p.Hkv * p.n_rsplit * p.Bz;
     const dim3 fused((unsigned)(n_sattn + riders));
+    // (wide riders lead where a sweep block has less than eight chunks and the riders' bytes are most of the launch; us a
+    // call, led | followed by them: 3 x 20520 tokens, 64 heads, 16 text rows 94 | 102, 4 x 36864 x 14, 64 rows 124 | 129;
+    // of 512 query rows a block and more: 4 x 16384 x 64 heads, 64 rows 201 | 197, 2 x 32768 x 28, 256 rows 290 | 285)
     if (wide)
-      hipLaunchKernelGGL((sattn_pass1_with_emb<D, true>), fused, dim3(kSaWaves * 64), 0, st, p, (int)n_sattn);
+      hipLaunchKernelGGL((sattn_pass1_with_emb<D, true>), fused, dim3(kSaWaves * 64), 0, st, p,
+                         p.rows_per_split < 512 ? (int)riders : 0, (int)n_sattn);
     else
-      hipLaunchKernelGGL((sattn_pass1_with_emb<D, false>), fused, dim3(kSaWaves * 64), 0, st, p, (int)n_sattn);
+      hipLaunchKernelGGL((sattn_pass1_with_emb<D, false>), fused, dim3(kSaWaves * 64), 0, st, p, 0, (int)n_sattn);
   } else {
     hipLaunchKernelGGL((sattn_mfma<D, 1>), grid, dim3(kSaWaves * 64), 0, st, p);
   }

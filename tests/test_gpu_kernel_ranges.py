@@ -233,6 +233,8 @@ def test_fp32_attention_mass(hippo, shape, d):
     # single piece; one frame, two, runs of several with a short last one; crops cut at the edges, of one token, of 32
     (1, 1, 5, 5, 512, 5, 5), (1, 2, 5, 7, 8, 5, 5), (2, 9, 11, 13, 520, 5, 5), (1, 3, 6, 5, 1024, 5, 5),
     (1, 40, 16, 16, 768, 5, 5), (1, 37, 11, 12, 504, 4, 8), (1, 5, 3, 3, 1544, 1, 1),
+    # bf16 keeps the frame before in registers up to two passes: three, over runs of several frames
+    (1, 60, 16, 16, 1032, 5, 5),
 ])
 def test_embedding_terms_over_passes_of_channels(hippo, shape, dtype):
     B, F, gh, gw, ch, cy, cx = shape
@@ -273,6 +275,19 @@ def test_fp32_embedding_terms_beside_the_sweep(hippo, shape):
              for flags in (7, 1, 6)]
     assert torch.equal(comps[0][0], comps[1][0])                      # the sweep's blocks, with and without riders
     assert torch.equal(comps[0][1:], comps[2][1:])                    # the crops' sums, beside a sweep and alone
+
+
+@pytest.mark.parametrize("L, frames", [(16, 24), (64, 64)])     # the riders lead; the sweep's blocks of 512 query rows do
+def test_wide_embedding_terms_beside_the_sweep(hippo, L, frames):
+    n = frames * 256
+    q, k = score_inputs(L, 1, L, 64, 8, 128, n + 3, "bf16", 0.5)
+    q, k, vid = dev(q, "bf16"), dev(k, "bf16"), hippo.video_desc(frames, 16, 16, 3)
+    comps = [hippo.hippo_score_tokens(q, k, vid, flags=flags, want_components=True)[1] for flags in (7, 1, 6)]
+    assert torch.equal(comps[0][0], comps[1][0]) and torch.equal(comps[0][1:], comps[2][1:])
+    emb = oracle.keys_as_embedding(host(k)[:, :, :3 + 3 * 256], 3, 3 * 256)
+    st, ss = oracle.s_temp(emb, 3), oracle.s_spa(emb, 3, 16, 16)      # the first two frames, whose neighbours are among three
+    assert_close(host(comps[0])[1][:, :512], st[:, :512], "bf16", "s_temp")
+    np.testing.assert_allclose(host(comps[0])[2][:, :512], ss[:, :512], rtol=0, atol=2e-3 * ss.max())
 
 
 @pytest.mark.parametrize("dtype", ["fp32", "bf16"])
