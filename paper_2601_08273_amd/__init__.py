@@ -151,15 +151,19 @@ def _torch():
     return torch
 
 
+_dtype_codes = {}
+
+
 def _dtype_code(t) -> int:
-    torch = _torch()
-    if t.dtype == torch.float32:
-        return DTYPE_F32
-    if t.dtype == torch.bfloat16:
-        return DTYPE_BF16
-    if t.dtype in (torch.uint8, torch.float8_e4m3fn):       # E4M3 cache codes
-        return DTYPE_FP8_E4M3
-    raise TypeError("unsupported dtype %s (fp32, bf16, or uint8 / float8_e4m3fn cache codes)" % t.dtype)
+    code = _dtype_codes.get(t.dtype)
+    if code is None:
+        torch = _torch()
+        _dtype_codes.update({torch.float32: DTYPE_F32, torch.bfloat16: DTYPE_BF16,
+                             torch.uint8: DTYPE_FP8_E4M3, torch.float8_e4m3fn: DTYPE_FP8_E4M3})   # E4M3 cache codes
+        code = _dtype_codes.get(t.dtype)
+        if code is None:
+            raise TypeError("unsupported dtype %s (fp32, bf16, or uint8 / float8_e4m3fn cache codes)" % t.dtype)
+    return code
 
 
 def _ptr(t) -> Optional[int]:
@@ -178,10 +182,13 @@ def _stream(stream) -> Optional[int]:
 
 def kv_desc(cache, n_q_heads: int) -> KvDesc:
     """Descriptor of a [B, H_kv, N, d] cache tensor (any strides with unit stride on d)."""
-    assert cache.dim() == 4 and cache.stride(3) == 1
-    B, Hkv, _, d = cache.shape
-    sb, sh, sn, _ = cache.stride()
-    return KvDesc(B, n_q_heads, Hkv, d, _dtype_code(cache), sb, sh, sn)
+    return _kv_desc(cache, cache.shape, cache.stride(), n_q_heads)
+
+
+def _kv_desc(cache, shape, strides, n_q_heads: int) -> KvDesc:
+    """kv_desc, for a caller that has the cache's shape and strides in hand (a tensor's cost 0.2 us each to ask for)"""
+    assert len(strides) == 4 and strides[3] == 1
+    return KvDesc(shape[0], n_q_heads, shape[1], shape[3], _dtype_code(cache), *strides[:3])
 
 
 def video_desc(n_frames, grid_h, grid_w, vis_offset, crop_h=5, crop_w=5) -> VideoDesc:
@@ -211,7 +218,8 @@ def _allocates_on_its_stream(fn):
 
     @functools.wraps(fn)
     def wrapper(*args, **kwargs):
-        # (binding the whole signature took 3 us of a call whose kernels take 10)
+        # (binding the whole signature took 3 us of a call whose kernels take 10; where it is None, callers that know
+        # take __wrapped__)
         stream = args[at] if len(args) > at else kwargs.get("stream")
         if stream is None:
             return fn(*args, **kwargs)
@@ -306,11 +314,12 @@ def hippo_select_gather_kv(scores, k: int, k_src, v_src, vid: VideoDesc, n_q_hea
     torch = _torch()
     lib = load()
     assert scores.dtype == torch.float32 and scores.is_contiguous()
-    B, Hkv, N, d = k_src.shape
+    shape, strides = k_src.shape, k_src.stride()
+    B, Hkv, N, d = shape
     n_vis = vid.n_frames * vid.grid_h * vid.grid_w
     H = n_q_heads or Hkv
-    src = kv_desc(k_src, H)
-    assert v_src.stride() == k_src.stride() and v_src.shape == k_src.shape
+    src = _kv_desc(k_src, shape, strides, H)
+    assert v_src.stride() == strides and v_src.shape == shape
     idx = idx_out if idx_out is not None else torch.empty((B, k), dtype=torch.int32, device=scores.device)
     dst = None
     if gather:
@@ -318,8 +327,9 @@ def hippo_select_gather_kv(scores, k: int, k_src, v_src, vid: VideoDesc, n_q_hea
         if k_dst is None:
             k_dst = torch.empty((B, Hkv, max(n_dst, 0), d), dtype=k_src.dtype, device=k_src.device)
             v_dst = torch.empty_like(k_dst)
-        assert k_dst.shape == (B, Hkv, n_dst, d) and v_dst.shape == k_dst.shape and v_dst.stride() == k_dst.stride()
-        dst = kv_desc(k_dst, H)
+        shape, strides = k_dst.shape, k_dst.stride()
+        assert shape == (B, Hkv, n_dst, d) and v_dst.shape == shape and v_dst.stride() == strides
+        dst = _kv_desc(k_dst, shape, strides, H)
     else:
         k_dst = v_dst = None
     ws = _workspace(lambda: 256, scores.device, workspace)
@@ -337,27 +347,33 @@ def _attention(fn_name, call, q, k_cache, v_cache, ctx_len, softmax_scale, num_s
     lib = load()
     assert q.is_contiguous() and q.dim() == 4
     B, q_len, H, d = q.shape
-    kv = kv_desc(k_cache, H)
-    assert v_cache.stride() == k_cache.stride() and v_cache.shape == k_cache.shape
-    ws = _workspace(lambda: workspace_bytes(call, kv, None, q_len, ctx_len + q_len, 0, num_splits), q.device, workspace)
+    shape, strides = k_cache.shape, k_cache.stride()
+    kv = _kv_desc(k_cache, shape, strides, H)
+    assert v_cache.stride() == strides and v_cache.shape == shape
+    ws = workspace
+    if ws is None:
+        ws = _workspace(lambda: workspace_bytes(call, kv, None, q_len, ctx_len + q_len, 0, num_splits), q.device)
     if out is None:
         out = torch.empty_like(q)
     lse = torch.empty((B, H, q_len), dtype=torch.float32, device=q.device) if want_lse else None
     if k_new is not None:
         fn_name += "_append"
-        Hkv = k_cache.shape[1]
         for t in (k_new, v_new):
-            assert t.shape == (B, q_len, Hkv, d) and t.is_contiguous() and t.dtype == k_cache.dtype
+            assert t.shape == (B, q_len, shape[1], d) and t.is_contiguous() and t.dtype == k_cache.dtype
         st = getattr(lib, fn_name)(_ptr(q), q_len, _ptr(k_new), _ptr(v_new), _ptr(k_cache), _ptr(v_cache),
                                    C.byref(kv), ctx_len, float(softmax_scale or 0.0), num_splits, _ptr(out),
                                    _ptr(lse), _ptr(ws), ws.numel(), _stream(stream))
         _check(st, fn_name)
         return (out, lse) if want_lse else out
-    st = getattr(lib, fn_name)(_ptr(q), q_len, _ptr(k_cache), _ptr(v_cache), C.byref(kv), ctx_len,
-                               float(softmax_scale or 0.0), num_splits, _ptr(out), _ptr(lse), _ptr(ws),
-                               ws.numel(), _stream(stream))
-    _check(st, fn_name)
+    st = getattr(lib, fn_name)(q.data_ptr(), q_len, k_cache.data_ptr(), v_cache.data_ptr(), C.byref(kv), ctx_len,
+                               float(softmax_scale or 0.0), num_splits, out.data_ptr(),
+                               None if lse is None else lse.data_ptr(), ws.data_ptr(), ws.numel(), _stream(stream))
+    if st != OK:
+        _check(st, fn_name)
     return (out, lse) if want_lse else out
+
+
+_attention_here = _attention.__wrapped__
 
 
 def hippo_verify_attention(q, k_cache, v_cache, ctx_len: int, softmax_scale: float = 0.0, num_splits: int = 0,
@@ -365,14 +381,16 @@ def hippo_verify_attention(q, k_cache, v_cache, ctx_len: int, softmax_scale: flo
     """q [B,q_len,H,d]; caches hold ctx_len+q_len rows; row i attends to [0, ctx_len+i].
     With k_new / v_new [B,q_len,Hkv,d] the new rows are taken from there and appended to the caches
     by the same launch (hippo_verify_attention_append)."""
-    return _attention("hippo_verify_attention", CALL_VERIFY_ATTENTION, q, k_cache, v_cache, ctx_len,
-                      softmax_scale, num_splits, want_lse, out, workspace, stream, k_new, v_new)
+    attention = _attention_here if stream is None else _attention
+    return attention("hippo_verify_attention", CALL_VERIFY_ATTENTION, q, k_cache, v_cache, ctx_len,
+                     softmax_scale, num_splits, want_lse, out, workspace, stream, k_new, v_new)
 
 
 def hippo_draft_attention(q, k_cache, v_cache, ctx_len: int, softmax_scale: float = 0.0, num_splits: int = 0,
                           want_lse: bool = False, out=None, workspace=None, stream=None, k_new=None, v_new=None):
-    return _attention("hippo_draft_attention", CALL_DRAFT_ATTENTION, q, k_cache, v_cache, ctx_len,
-                      softmax_scale, num_splits, want_lse, out, workspace, stream, k_new, v_new)
+    attention = _attention_here if stream is None else _attention
+    return attention("hippo_draft_attention", CALL_DRAFT_ATTENTION, q, k_cache, v_cache, ctx_len,
+                     softmax_scale, num_splits, want_lse, out, workspace, stream, k_new, v_new)
 
 
 @_allocates_on_its_stream
