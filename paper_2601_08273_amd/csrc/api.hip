@@ -220,10 +220,11 @@ int plan_score(const hippo_kv_desc* kv, const hippo_video_desc* vid, int l_txt, 
   o += vec;                 pl->off_st = o;
   o += vec;                 pl->off_ss = o;
   o += vec;
-  pl->once = score_once(kv->dtype, Nv);
+  const size_t heads = (size_t)kv->n_kv_heads * kv->batch * n_layers, runs = heads * pl->n_rsplit;
+  const size_t words = heads * score_once_words(l_txt * (kv->n_q_heads / kv->n_kv_heads)) * sizeof(unsigned long long);
+  // (its launches are one-dimensional: a grid's threads stay below 2^32)
+  pl->once = score_once(kv->dtype, Nv) && runs * pl->n_tile < (1u << 22) && words < (1ull << 32);
   if (pl->once) {
-    const size_t heads = (size_t)kv->n_kv_heads * kv->batch * n_layers, runs = heads * pl->n_rsplit;
-    const size_t words = heads * score_once_words(l_txt * (kv->n_q_heads / kv->n_kv_heads)) * sizeof(unsigned long long);
     pl->off_word = o;       o += align_up(words, 256);
     pl->off_large = o;      o += align_up(runs * sizeof(int), 256);
     pl->off_arrived = o;    o += align_up(runs * sizeof(int), 256);

@@ -323,7 +323,7 @@ struct ScoreParams {
 hipError_t launch_score(const ScoreParams& p, hipStream_t st);
 int score_token_tile(int dtype);   // tokens per block in the s_attn passes
 bool score_once(int dtype, long long n_vis);       // s_attn in one sweep
-int score_once_words(int rows_per_kv_head);        // its words, of a KV head
+size_t score_once_words(int rows_per_kv_head);     // its words, of a KV head
 int score_row_splits(int dtype, long long blocks_unsplit, int rows_per_kv_head);
 
 struct SelectParams {

@@ -22,14 +22,15 @@ __device__ __forceinline__ long long sattn_part_at(const ScoreParams& p, int til
 
 // =================================================================================================
 // s_attn, fp32 version (v_mfma_f32_16x16x4_f32: fp32 operands, products and sums).
-// PASS 1: row statistics; PASS 2: column sums.
+// PASS 1: row statistics; PASS 2: column sums.  Videos of up to 65536 tokens take sattn_once_body instead; the two sweeps
+// are left for longer ones, and for runs of rows whose sums it cannot hold.
 // Bound by the matrix unit's fp32 rate: 2 * L * H * N_v * D flops a pass against 157 TFLOP/s.  A block's four waves
 // (one per SIMD) own 32 tokens each, whose keys stay in registers as A operands, and sweep a run of the KV head's
 // query rows in chunks of 32 that travel HBM -> LDS by direct transfers, two chunks deep.  Z^T = K Q^T: contraction
 // step (s, c), slot g is channel 16s + 4g + c, so 16 bytes of a row give a lane its operands of four steps; lane
 // (row j, group g) ends with tokens tb*16 + 4g + e.  32 tokens a wave are two independent chains of products, which
 // is what keeps the unit busy with few waves; 128-token blocks and row runs leave a short video enough blocks.
-// The vector-ALU sweep that it replaces read LDS for every product: a scoring call of 12K tokens x 28 heads x 64 rows
+// The vector-ALU sweep that they replace read LDS for every product: a scoring call of 12K tokens x 28 heads x 64 rows
 // x 128 channels 608 -> 178 us (both passes together 570 -> 100), of 3K x 14 heads x 64 rows x 64 channels 135 -> 47.
 // =================================================================================================
 constexpr int kSaF32Tile = 128;       // tokens per block
@@ -1650,11 +1651,9 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 3 : 2) void emb_scores_run32(Sco
   emb_run32_block<F32, U, NW, WIDE, NB>(p, sm, blockIdx.x);
 }
 
-// fp32: pass 1 and the embedding terms in one launch, the sweep's blocks first.  A wave of the sweep per SIMD keeps the
+// fp32 beyond 65536 tokens: pass 1 and the embedding terms in one launch, the sweep's blocks first.  A wave of the sweep per SIMD keeps the
 // matrix unit busy, so a riding block's trips to memory cost next to nothing; in a launch of their own the crops took
-// as long as the sweep (3136 tokens: 10.5 us of pass 1 and 13 of crops, together 14.7).  Whole scoring calls, us: 936
-// tokens 30.6 -> 22.2; 3136 tokens 37.4 -> 29.3; 3 x 7220 tokens, two layers 130 -> 105; of 768 channels 3136 tokens, 16 text
-// tokens 42.5 -> 39.0.  Up to 168 registers a wave, 38 KB of LDS: three blocks on a compute unit.
+// as long as the sweep (3136 tokens: 10.5 us of pass 1 and 13 of crops, together 14.7).  Up to 168 registers a wave, 38 KB of LDS: three blocks on a compute unit.
 template <int D, bool WIDE>
 __global__ __launch_bounds__(256, 3) void sattn_f32_pass1_with_emb(ScoreParams p, int n_sattn) {
   union Smem {
@@ -1672,7 +1671,8 @@ __global__ __launch_bounds__(256, 3) void sattn_f32_pass1_with_emb(ScoreParams p
   emb_run32_block<true, 4, 4, WIDE>(p, sm.run, (unsigned)(blk - n_sattn));
 }
 
-// The same beside the one sweep
+// The same beside the one sweep (3136 tokens: 15.8 us; 936 tokens, whole calls, beside a sweep 30.6 -> 22.2, 3 x 7220 tokens in
+// two layers 130 -> 105).  Five chunks of exponentials take up to 245 registers: two blocks on a compute unit.
 template <int D, bool WIDE>
 __global__ __launch_bounds__(256, 2) void sattn_once_with_emb(ScoreParams p, int n_sattn) {
   union Smem {
@@ -1908,8 +1908,8 @@ int score_row_splits(int dtype, long long blocks_unsplit, int rows_per_kv_head) 
 bool score_once(int dtype, long long n_vis) {
   return dtype == HIPPO_DTYPE_F32 && (n_vis + kSaF32Tile - 1) / kSaF32Tile <= kOnceMaxTiles;
 }
-int score_once_words(int rows_per_kv_head) {
-  return (rows_per_kv_head + kSaF32Rows - 1) / kSaF32Rows * kSaF32Rows * kOnceCopies;
+size_t score_once_words(int rows_per_kv_head) {
+  return ((size_t)rows_per_kv_head + kSaF32Rows - 1) / kSaF32Rows * kSaF32Rows * kOnceCopies;
 }
 
 // riders: blocks of the embedding terms beside the sweep (wide: of more channels than a pass takes)
@@ -1974,20 +1974,21 @@ static hipError_t launch_sattn_mfma(const ScoreParams& p, hipStream_t st, long l
 // own, where blocks of eight waves take 512 in a pass and fetch a frame's channels half as often.
 //
 // Where they ride.  Channels that fill their last pass of 512 by half or less (an odd number of passes of 256): four waves
-// lose nothing by their passes.  They ride beside a sweep of up to two blocks a compute unit and beside a long one (rounds of
+// lose nothing by their passes.  They ride beside a sweep of up to a block a compute unit, and beside a long one (rounds of
 // blocks x 32-row chunks, a block's start as 0.7 of a chunk); beside a short sweep of many blocks they wait for its
-// blocks' slots and then crowd on few compute units.  768 channels, us a call, alone -> riding: 26 x 14 x 14 tokens, 52
-// sweep blocks, 41.4 -> 36.8; 220 sweep blocks of 11 chunks 113 -> 103; 736 of 10 chunks 201 -> 189; and where they stay alone:
-// 936 of one chunk 91 against 101, 1016 of four 177 against 220, 1184 of two 161 against 189.
-// Otherwise eight waves are the better ones, and the crops ride only where the sweep leaves compute units idle: 512
-// channels, 152 sweep blocks and 108 crops 49.4 -> 42.7, 176 and 64 51.6 -> 43.0; where they stay alone: 410 blocks of three
-// chunks 69 against 87, 568 of one 54 against 68, 1024 channels, 712 of two 102 against 145, 360 of one chunk 78 against 88.
+// blocks' slots and then crowd on few compute units.  768 channels, us a call, alone -> riding: 26 x 14 x 14 tokens of 14
+// heads, 240 sweep blocks, 57.6 -> 47.3; 512 of 14 chunks 146 -> 141; 480 of eight 82 -> 80; and where they stay alone:
+// 512 of seven 123 against 131; with two sweeps, 1016 of four chunks 177 against 220, 1184 of two 161 against 189.
+// Otherwise eight waves are the better ones, and the crops ride only where the sweep leaves room for all of them: 512
+// channels, 256 sweep blocks and 256 crops 55.2 -> 48.7, 1024 channels likewise 95 -> 82; where they stay alone: 768 sweep
+// blocks of seven chunks 112 against 120, 384 of four 67 against 76, 1024 channels, 768 of ten 287 against 307.
 static bool wide_f32_rides(const ScoreParams& p, long long n_sattn, long long n_riders, int de) {
   if ((de + 255) / 256 % 2 == 1) {
     const double rounds = (double)((n_sattn + kNumCU - 1) / kNumCU);
-    return n_sattn <= 2 * kNumCU || rounds * (p.rows_per_split / (double)kSaF32Rows + 0.7) >= 22.0;
+    return n_sattn <= kNumCU ||
+           rounds * (p.rows_per_split / (double)kSaF32Rows + 0.7) >= (n_sattn <= 2 * kNumCU ? 16.0 : 22.0);
   }
-  return n_sattn <= kNumCU && n_riders <= kNumCU / 2 &&
+  return n_sattn <= kNumCU && n_riders <= kNumCU &&
          (long long)p.rows_per_split * p.D >= (n_sattn + n_riders <= kNumCU ? 4096 : 16384);
 }
 
@@ -2055,7 +2056,7 @@ hipError_t launch_score(const ScoreParams& p_in, hipStream_t st) {
   long long n_riders = crops_per_frame * ((p.F + p.emb_run - 1) / p.emb_run) * p.B;
   const long long n_sattn = (long long)p.n_tile * p.Hkv * p.n_rsplit * p.Bz;
   const bool emb_rides = want_emb && !accumulate_only && (p.flags & HIPPO_SCORE_ATTN) && small_crops &&
-                         n_sattn + n_riders < (1ll << 31) && (bf16 || !wide || wide_f32_rides(p, n_sattn, n_riders, de));
+                         n_sattn + n_riders < (p.row_word != nullptr ? 1ll << 23 : 1ll << 31) && (bf16 || !wide || wide_f32_rides(p, n_sattn, n_riders, de));
   bool eight_waves = false;
   if (!emb_rides && !bf16 && wide) {
     eight_waves = wide_f32_plan(p, crops_per_frame * p.B, de);
