@@ -227,7 +227,8 @@ __device__ __forceinline__ float log2_of_sum(float tot) {
 // later, when the words have counted every tile.
 //   The words: bits 0..52 a sum in units of p.once_unit, bits 53..62 how many tiles have added theirs.  One 64-bit add
 // carries both, so nothing relies on the order of two locations, and integer sums do not depend on the order of the
-// tiles.  Four words a row, by tile: adds to one word queue up at some 25 ns each.
+// tiles.  Four words a row, by tile: adds to one word wait for each other (a bf16
+// form of this sweep, whose chunks are shorter, took 1140 us with one word a row and 770 with eight).
 //   Waiting: a block waits for the tiles of its own (layer, batch element, KV head, row run), which stand next to each
 // other in the launch order, kOnceMaxTiles of them at most.  A wave that has asked for sums once_polls times in all no
 // longer waits: its block says so in tile_redo and sattn_f32_redo sweeps that tile again, with all sums known, the same
@@ -1651,9 +1652,10 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 3 : 2) void emb_scores_run32(Sco
   emb_run32_block<F32, U, NW, WIDE, NB>(p, sm, blockIdx.x);
 }
 
-// fp32 beyond 65536 tokens: pass 1 and the embedding terms in one launch, the sweep's blocks first.  A wave of the sweep per SIMD keeps the
-// matrix unit busy, so a riding block's trips to memory cost next to nothing; in a launch of their own the crops took
-// as long as the sweep (3136 tokens: 10.5 us of pass 1 and 13 of crops, together 14.7).  Up to 168 registers a wave, 38 KB of LDS: three blocks on a compute unit.
+// fp32 beyond 65536 tokens: pass 1 and the embedding terms in one launch, the sweep's blocks first.  A wave of the sweep
+// per SIMD keeps the matrix unit busy, so a riding block's trips to memory cost next to nothing; in a launch of their own the crops took
+// as long as the sweep (3136 tokens: 10.5 us of pass 1 and 13 of crops, together 14.7).  Up to 168 registers a wave, 38 KB of
+// LDS: three blocks on a compute unit.
 template <int D, bool WIDE>
 __global__ __launch_bounds__(256, 3) void sattn_f32_pass1_with_emb(ScoreParams p, int n_sattn) {
   union Smem {
@@ -1917,7 +1919,8 @@ template <int D>
 static hipError_t launch_sattn_once(const ScoreParams& p, hipStream_t st, long long riders, bool wide) {
   const long long n_sattn = (long long)p.n_tile * p.Hkv * p.n_rsplit * p.Bz;
   const long long n_clear = (long long)(p.once_bytes / sizeof(u32x4));
-  hipLaunchKernelGGL(sattn_once_clear, dim3((unsigned)((n_clear + 255) / 256)), dim3(256), 0, st, (u32x4*)p.row_word, n_clear);
+  hipLaunchKernelGGL(sattn_once_clear, dim3((unsigned)((n_clear + 255) / 256)), dim3(256), 0, st, (u32x4*)p.row_word,
+                     n_clear);
   const dim3 grid((unsigned)(n_sattn + riders));
   if (wide) hipLaunchKernelGGL((sattn_once_with_emb<D, true>), grid, dim3(256), 0, st, p, (int)n_sattn);
   else hipLaunchKernelGGL((sattn_once_with_emb<D, false>), grid, dim3(256), 0, st, p, (int)n_sattn);
@@ -2056,7 +2059,8 @@ hipError_t launch_score(const ScoreParams& p_in, hipStream_t st) {
   long long n_riders = crops_per_frame * ((p.F + p.emb_run - 1) / p.emb_run) * p.B;
   const long long n_sattn = (long long)p.n_tile * p.Hkv * p.n_rsplit * p.Bz;
   const bool emb_rides = want_emb && !accumulate_only && (p.flags & HIPPO_SCORE_ATTN) && small_crops &&
-                         n_sattn + n_riders < (p.row_word != nullptr ? 1ll << 23 : 1ll << 31) && (bf16 || !wide || wide_f32_rides(p, n_sattn, n_riders, de));
+                         n_sattn + n_riders < (p.row_word != nullptr ? 1ll << 23 : 1ll << 31) &&
+                         (bf16 || !wide || wide_f32_rides(p, n_sattn, n_riders, de));
   bool eight_waves = false;
   if (!emb_rides && !bf16 && wide) {
     eight_waves = wide_f32_plan(p, crops_per_frame * p.B, de);
