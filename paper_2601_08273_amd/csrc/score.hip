@@ -254,7 +254,7 @@ struct SattnOnceSmem {
   __align__(16) unsigned long long word_s[2][kOnceCopies][RCH];   // of the chunk whose columns come next
   float sum_s[2][NW][RCH];                               // the waves' row sums; NaN: out of range
   int state_s[NW];
-  int large_s;                                           // a wave has met a row out of range
+  int large_s[2];                                        // a wave has met a row out of range, in steps of either parity
   int last_s;
 };
 
@@ -302,7 +302,7 @@ __device__ __forceinline__ int sattn_once_body(const ScoreParams& p, SattnOnceSm
     }
   };
   if (n_chunks > 0) request_chunk(0);
-  if (tid == 0) sm.large_s = 0;
+  if (tid == 0) sm.large_s[0] = sm.large_s[1] = 0;
   f32x4 kop[TBW][NS];
   {
     const float* kbase = (const float*)p.k_layers[layer] + (long long)b * p.sb + (long long)hk * p.sh +
@@ -331,13 +331,14 @@ __device__ __forceinline__ int sattn_once_body(const ScoreParams& p, SattnOnceSm
 
   // Start of step c: chunk c, the waves' sums of chunk c - 1 and the words that step c - 1 asked for are there.
   // False: a wave has met a row out of range and the block stops (what other blocks wait for before they find the same
-  // has been added).
+  // has been added).  A wave that is past this step's barrier may be writing the word of this step: the word read here is
+  // that of the step before, which nobody writes any more, so that all waves leave at the same step.
   auto begin_step = [&](int c) -> bool {
     // (the wave that added the last sums leaves that one operation, issued after its transfers, in flight)
     if (PUBLISH && c >= 2 && wave == (c & 3)) wait_vmcnt<1>();
     else wait_vmcnt<0>();
     __syncthreads();
-    if (__builtin_amdgcn_readfirstlane(sm.large_s)) return false;
+    if (__builtin_amdgcn_readfirstlane(sm.large_s[(c + 1) & 1])) return false;
     if (c + 1 < n_chunks) request_chunk(c + 1);
     if (PUBLISH && c + 1 >= H && c < n_chunks && wave == (c & 3))
       dma16_agent(words + (c + 1 - H) * CW + 2 * lane, (unsigned)(uintptr_t)&sm.word_s[(c + 1) & 1][0][0]);
@@ -358,7 +359,7 @@ __device__ __forceinline__ int sattn_once_body(const ScoreParams& p, SattnOnceSm
     }
     return true;
   };
-  // 1 / sum of rows 16 * rb + j of chunk c; asked: its words were requested by the step before
+  // 1 / sum of rows 16 * rb + j of chunk c, in step c + H; asked: its words were requested by the step before
   auto weights = [&](int c, bool asked, float (&w)[2]) {
     const int rr = lane & (RCH - 1);
     const bool real = row_begin + c * RCH + rr < Rs;
@@ -389,7 +390,7 @@ __device__ __forceinline__ int sattn_once_body(const ScoreParams& p, SattnOnceSm
       state = kOnceLarge;
       if (PUBLISH) __hip_atomic_store(run_large, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
-    if (state == kOnceLarge) sm.large_s = 1;
+    if (state == kOnceLarge) sm.large_s[(c + H) & 1] = 1;
     const unsigned inv = __float_as_uint(real ? p.once_unit / units : 0.f);
     auto a = __builtin_amdgcn_permlane16_swap(inv, inv, false, false);
     w[0] = __uint_as_float(a[0]);

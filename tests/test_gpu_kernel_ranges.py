@@ -415,6 +415,24 @@ def test_fp32_attention_mass_in_one_sweep(hippo, n, L, H, Hkv, d, rows_out):
     assert (np.abs(got - ref) <= bound).all(), np.abs((got - ref) / bound).max()
 
 
+@pytest.mark.parametrize("shift", [110.0, -110.0])
+@pytest.mark.parametrize("chunk", [0, 3, 4, 5, 8, 9])
+def test_fp32_attention_mass_where_a_long_run_meets_a_row_out_of_range(hippo, chunk, shift):
+    # one run of ten chunks a KV head: the row is met while its block's waves still sweep (steps of both parities), at the
+    # last step that they share and at those behind it; all must leave the sweep together
+    L, H, Hkv, d, n = 80, 16, 4, 64, 8192
+    q, k = score_inputs(chunk + 70, 1, L, H, Hkv, d, n, "fp32", 0.7)
+    q[..., 0] = 0.0
+    q[:, chunk * 32 // (H // Hkv), :, 0] = np.sqrt(d)
+    k[..., 0] = shift
+    ref = oracle.s_attn(q, k, 0, n)
+    got = [attention_mass(hippo, q, k, "fp32", 1, 1, n, 0) for _ in range(3)]
+    assert np.array_equal(got[0], got[1]) and np.array_equal(got[0], got[2])
+    # 1e-5, and of a logit of `shift`: each of d additions and two products round by up to 2^-24 of it
+    bound = (1e-5 + abs(shift) * (d + 2) * 2.0 ** -24) * np.maximum(np.abs(ref), np.sqrt((ref ** 2).mean()))
+    assert (np.abs(got[0] - ref) <= bound).all(), np.abs((got[0] - ref) / bound).max()
+
+
 @pytest.mark.parametrize("dtype", ["fp32", "bf16"])
 @pytest.mark.parametrize("rows, d", [(1, 64), (2047, 128), (2049, 128), (70001, 64)])
 def test_codes_over_the_exponent_range(hippo, dtype, rows, d):
