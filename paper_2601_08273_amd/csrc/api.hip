@@ -189,7 +189,7 @@ int attention_entry(int call, const void* q, int32_t q_len, const void* k_cache,
 struct ScorePlan {
   int n_tile, n_rsplit;
   bool once;
-  size_t off_word, off_large, off_arrived, once_bytes, off_redo;   // one sweep: the first three are cleared together
+  size_t off_word, off_large, off_arrived, clear_bytes, off_redo;   // one sweep: the first three are cleared together
   size_t off_row_l, off_row_lse, off_col, off_sa, off_st, off_ss, bytes;
 };
 
@@ -228,7 +228,7 @@ int plan_score(const hippo_kv_desc* kv, const hippo_video_desc* vid, int l_txt, 
     pl->off_word = o;       o += align_up(words, 256);
     pl->off_large = o;      o += align_up(runs * sizeof(int), 256);
     pl->off_arrived = o;    o += align_up(runs * sizeof(int), 256);
-    pl->once_bytes = o - pl->off_word;
+    pl->clear_bytes = o - pl->off_word;
     pl->off_redo = o;       o += align_up(runs * pl->n_tile * sizeof(int), 256);
   }
   pl->bytes = o;
@@ -401,15 +401,15 @@ int hippo_score_tokens_layers(int32_t n_layers, const void* const* q_txt_layers,
   p.s_spa = reinterpret_cast<float*>(ws + pl.off_ss);
   p.n_tile = pl.n_tile;
   p.n_rsplit = pl.n_rsplit;
-  p.row_word = nullptr;
+  ScoreOnce once{};
   if (pl.once) {
-    p.row_word = reinterpret_cast<unsigned long long*>(ws + pl.off_word);
-    p.run_large = reinterpret_cast<int*>(ws + pl.off_large);
-    p.run_arrived = reinterpret_cast<int*>(ws + pl.off_arrived);
-    p.tile_redo = reinterpret_cast<int*>(ws + pl.off_redo);
-    p.once_bytes = pl.once_bytes;
+    once.row_word = reinterpret_cast<unsigned long long*>(ws + pl.off_word);
+    once.run_large = reinterpret_cast<int*>(ws + pl.off_large);
+    once.run_arrived = reinterpret_cast<int*>(ws + pl.off_arrived);
+    once.tile_redo = reinterpret_cast<int*>(ws + pl.off_redo);
+    once.clear_bytes = pl.clear_bytes;
   }
-  const hipError_t e = launch_score(p, static_cast<hipStream_t>(stream));
+  const hipError_t e = launch_score(p, once, static_cast<hipStream_t>(stream));
   return e == hipSuccess ? HIPPO_OK : HIPPO_ERR_HIP;
 }
 

@@ -305,22 +305,26 @@ struct ScoreParams {
   float* s_spa;      // [B, Nv]
   int n_tile;        // token tiles of pass 1
   int n_rsplit;      // runs the query rows of a KV head are cut into (one block each)
-  // fp32 in one sweep (row_word null: two sweeps); cleared before it, once_bytes from row_word on
-  unsigned long long* row_word;  // [Bz, Hkv, row_words, copies] row sums and the number of tiles in them
-  int* run_large;                // [Bz, n_rsplit, Hkv] a run has rows out of the words' range
-  int* run_arrived;              // [Bz, n_rsplit, Hkv] tiles of such a run whose statistics are written
-  int* tile_redo;                // [Bz, n_rsplit, Hkv, n_tile] left to the redo launch (not cleared: every block writes)
-  size_t once_bytes;
-  int row_words;                 // rows of a KV head, padded to whole chunks
-  float once_unit;               // (filled in by launch_score, as once_polls)
-  int once_polls;
   // what every wave of the sweeps would otherwise divide out for itself (filled in by launch_score)
   int rows_per_split;            // rows of a run: whole chunks (64 rows in bf16, 32 in fp32)
   int q_step_i, q_step_g;        // 64 / G and 64 % G: how (i, g) of row r = i*G + g move from chunk to chunk
   int q_last_i, q_last_g;        // (i, g) of the KV head's last row
   int emb_run;                   // consecutive frames of one crop position that a block of the frame-run kernel owns
 };
-hipError_t launch_score(const ScoreParams& p, hipStream_t st);
+// fp32 s_attn in one sweep: arguments of its own kernels alone.  (Among ScoreParams' they cost every bf16 kernel another
+// trip for its arguments: 13824 tokens x 14 heads, 149 text rows 33.1 -> 34.2 us a call.)
+struct ScoreOnce {
+  unsigned long long* row_word;  // [Bz, Hkv, row_words, copies] row sums and the number of tiles in them; null: two sweeps
+  int* run_large;                // [Bz, n_rsplit, Hkv] a run has rows out of the words' range
+  int* run_arrived;              // [Bz, n_rsplit, Hkv] tiles of such a run whose statistics are written
+  int* tile_redo;                // [Bz, n_rsplit, Hkv, n_tile] left to the redo launch (not cleared: every block writes)
+  size_t clear_bytes;            // what is cleared before the sweep, from row_word on: all but tile_redo
+  // filled in by launch_score
+  int row_words;                 // rows of a KV head, padded to whole chunks
+  float unit;
+  int polls;
+};
+hipError_t launch_score(const ScoreParams& p, const ScoreOnce& once, hipStream_t st);
 int score_token_tile(int dtype);   // tokens per block in the s_attn passes
 bool score_once(int dtype, long long n_vis);       // s_attn in one sweep
 size_t score_once_words(int rows_per_kv_head);     // its words, of a KV head

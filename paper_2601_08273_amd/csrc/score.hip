@@ -225,12 +225,12 @@ __device__ __forceinline__ float log2_of_sum(float tot) {
 // exponentials of its last kOnceHold chunks of 32 rows in registers (16 a lane and chunk, where the products were), adds
 // its row sums to a 64-bit word a row in device memory, and adds exponential x 1 / sum to the columns kOnceHold chunks
 // later, when the words have counted every tile.
-//   The words: bits 0..52 a sum in units of p.once_unit, bits 53..62 how many tiles have added theirs.  One 64-bit add
+//   The words: bits 0..52 a sum in units of once.unit, bits 53..62 how many tiles have added theirs.  One 64-bit add
 // carries both, so nothing relies on the order of two locations, and integer sums do not depend on the order of the
 // tiles.  Four words a row, by tile: adds to one word wait for each other (a bf16
 // form of this sweep, whose chunks are shorter, took 1140 us with one word a row and 770 with eight).
 //   Waiting: a block waits for the tiles of its own (layer, batch element, KV head, row run), which stand next to each
-// other in the launch order, kOnceMaxTiles of them at most.  A wave that has asked for sums once_polls times in all no
+// other in the launch order, kOnceMaxTiles of them at most.  A wave that has asked for sums once.polls times in all no
 // longer waits: its block says so in tile_redo and sattn_f32_redo sweeps that tile again, with all sums known, the same
 // operations in the same order.  So every wait ends, and no result depends on a wait, whatever else the GPU runs.
 //   Range: a wave's sums up to kOnceMax and row sums from kOnceMinUnits on (an exponential's mean over the row between
@@ -267,8 +267,8 @@ __device__ __forceinline__ long long once_run(const ScoreParams& p, int hk, int 
 
 // PUBLISH = false: all words are complete (the redo launch)
 template <int D, bool PUBLISH>
-__device__ __forceinline__ int sattn_once_body(const ScoreParams& p, SattnOnceSmem<D>& sm, const int tile, const int hk,
-                                               const int rs, const int bz) {
+__device__ __forceinline__ int sattn_once_body(const ScoreParams& p, const ScoreOnce& once, SattnOnceSmem<D>& sm,
+                                               const int tile, const int hk, const int rs, const int bz) {
   constexpr int NW = SattnOnceSmem<D>::NW, RCH = SattnOnceSmem<D>::RCH, H = kOnceHold;
   constexpr int TPW = kSaF32Tile / NW, TBW = TPW / 16;
   constexpr int NS = D / 16;
@@ -288,8 +288,8 @@ __device__ __forceinline__ int sattn_once_body(const ScoreParams& p, SattnOnceSm
   const float inv_g = __builtin_amdgcn_rcpf((float)p.G);
   const float* qbase = (const float*)p.q_layers[layer] + ((long long)b * p.L * p.H + hk * p.G) * D;
   const unsigned qs_addr = (unsigned)(uintptr_t)&sm.Qs[0][0];
-  unsigned long long* const words = p.row_word + ((long long)(bz * p.Hkv + hk) * p.row_words + row_begin) * kOnceCopies;
-  int* const run_large = p.run_large + once_run(p, hk, rs, bz);
+  unsigned long long* const words = once.row_word + ((long long)(bz * p.Hkv + hk) * once.row_words + row_begin) * kOnceCopies;
+  int* const run_large = once.run_large + once_run(p, hk, rs, bz);
 
   auto request_chunk = [&](int c) {                      // into buffer c & 1; rows past the end re-read the last row
 #pragma unroll
@@ -327,7 +327,7 @@ __device__ __forceinline__ int sattn_once_body(const ScoreParams& p, SattnOnceSm
       col[tb][e] = 0.f;
     }
   f32x4 ex[H][2][TBW];                                   // exponentials: [chunk % H][16-row block][16-token block]
-  int state = kOnceDone, polls = p.once_polls;
+  int state = kOnceDone, polls = once.polls;
 
   // Start of step c: chunk c, the waves' sums of chunk c - 1 and the words that step c - 1 asked for are there.
   // False: a wave has met a row out of range and the block stops (what other blocks wait for before they find the same
@@ -345,7 +345,7 @@ __device__ __forceinline__ int sattn_once_body(const ScoreParams& p, SattnOnceSm
     if (PUBLISH && c >= 1 && wave == ((c + 1) & 3)) {
       const float(&s)[NW][RCH] = sm.sum_s[(c - 1) & 1];
       const int rr = lane & (RCH - 1);
-      const float units = ((s[0][rr] + s[1][rr]) + (s[2][rr] + s[3][rr])) * p.once_unit;
+      const float units = ((s[0][rr] + s[1][rr]) + (s[2][rr] + s[3][rr])) * once.unit;
       const float hi = truncf(units * 0x1p-32f), lo = rintf(units - hi * 0x1p32f);
       const unsigned long long add =
           (1ull << kOnceCountBit) + ((unsigned long long)(unsigned)hi << 32) + (unsigned)lo;
@@ -391,7 +391,7 @@ __device__ __forceinline__ int sattn_once_body(const ScoreParams& p, SattnOnceSm
       if (PUBLISH) __hip_atomic_store(run_large, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
     if (state == kOnceLarge) sm.large_s[(c + H) & 1] = 1;
-    const unsigned inv = __float_as_uint(real ? p.once_unit / units : 0.f);
+    const unsigned inv = __float_as_uint(real ? once.unit / units : 0.f);
     auto a = __builtin_amdgcn_permlane16_swap(inv, inv, false, false);
     w[0] = __uint_as_float(a[0]);
     w[1] = __uint_as_float(a[1]);
@@ -489,22 +489,22 @@ __global__ __launch_bounds__(256) void sattn_once_clear(u32x4* at, long long n) 
 }
 
 template <int D>
-__device__ __forceinline__ void sattn_once_block(const ScoreParams& p, SattnOnceSmem<D>& once, SattnF32Smem<D>& sweep,
-                                                 const unsigned blk) {
+__device__ __forceinline__ void sattn_once_block(const ScoreParams& p, const ScoreOnce& once, SattnOnceSmem<D>& sm,
+                                                 SattnF32Smem<D>& sweep, const unsigned blk) {
   int tile, hk, rs, bz;
   once_block(p, blk, tile, hk, rs, bz);
-  const int state = sattn_once_body<D, true>(p, once, tile, hk, rs, bz);
-  if (threadIdx.x == 0) p.tile_redo[blk] = state != kOnceDone;
+  const int state = sattn_once_body<D, true>(p, once, sm, tile, hk, rs, bz);
+  if (threadIdx.x == 0) once.tile_redo[blk] = state != kOnceDone;
   if (state == kOnceDone) return;
   // Statistics as pass 1's, for the case that the run's rows are out of range; then every block of the run comes here.
   // (one thread's release and acquire stand for the block's, whose stores and loads the barriers order with it)
   sattn_f32_body<D, 1>(p, sweep, tile, hk, rs, bz);
   __syncthreads();
   if (threadIdx.x == 0)
-    once.last_s = __hip_atomic_fetch_add(p.run_arrived + once_run(p, hk, rs, bz), 1, __ATOMIC_ACQ_REL,
-                                         __HIP_MEMORY_SCOPE_AGENT) == p.n_tile - 1;
+    sm.last_s = __hip_atomic_fetch_add(once.run_arrived + once_run(p, hk, rs, bz), 1, __ATOMIC_ACQ_REL,
+                                       __HIP_MEMORY_SCOPE_AGENT) == p.n_tile - 1;
   __syncthreads();
-  if (!once.last_s) return;
+  if (!sm.last_s) return;
   const int Rs = p.L * p.G, row_begin = rs * p.rows_per_split, row_end = min(Rs, row_begin + p.rows_per_split);
   for (int r = row_begin + (int)threadIdx.x; r < row_end; r += 256) {
     constexpr int NB = 16;                               // tiles in flight: this block is alone with all of them
@@ -530,8 +530,8 @@ __device__ __forceinline__ void sattn_once_block(const ScoreParams& p, SattnOnce
 
 // The tiles that sattn_once left: all of a run with rows out of range (pass 2), and those that no longer waited.
 template <int D>
-__global__ __launch_bounds__(256, 2) void sattn_f32_redo(ScoreParams p) {
-  if (p.tile_redo[blockIdx.x] == 0) return;
+__global__ __launch_bounds__(256, 2) void sattn_f32_redo(ScoreParams p, ScoreOnce once) {
+  if (once.tile_redo[blockIdx.x] == 0) return;
   union Smem {
     SattnOnceSmem<D> once;
     SattnF32Smem<D> sweep;
@@ -540,7 +540,7 @@ __global__ __launch_bounds__(256, 2) void sattn_f32_redo(ScoreParams p) {
   int tile, hk, rs, bz;
   once_block(p, blockIdx.x, tile, hk, rs, bz);
   // (row sums too small, but not one block of the run that waited for them and said so: all wrote statistics)
-  if (p.run_large[once_run(p, hk, rs, bz)] || sattn_once_body<D, false>(p, sm.once, tile, hk, rs, bz) == kOnceLarge)
+  if (once.run_large[once_run(p, hk, rs, bz)] || sattn_once_body<D, false>(p, once, sm.once, tile, hk, rs, bz) == kOnceLarge)
     sattn_f32_body<D, 2>(p, sm.sweep, tile, hk, rs, bz);
 }
 
@@ -1677,14 +1677,14 @@ __global__ __launch_bounds__(256, 3) void sattn_f32_pass1_with_emb(ScoreParams p
 // The same beside the one sweep (3136 tokens: 15.8 us; 936 tokens, whole calls, beside a sweep 30.6 -> 22.2, 3 x 7220 tokens in
 // two layers 130 -> 105).  Five chunks of exponentials take up to 245 registers: two blocks on a compute unit.
 template <int D, bool WIDE>
-__global__ __launch_bounds__(256, 2) void sattn_once_with_emb(ScoreParams p, int n_sattn) {
+__global__ __launch_bounds__(256, 2) void sattn_once_with_emb(ScoreParams p, ScoreOnce once, int n_sattn) {
   union Smem {
     SattnOnceSmem<D> once;
     SattnF32Smem<D> sweep;
     EmbRunSmem<4, 4> run;
   };
   __shared__ Smem sm;
-  if ((int)blockIdx.x < n_sattn) sattn_once_block<D>(p, sm.once, sm.sweep, blockIdx.x);
+  if ((int)blockIdx.x < n_sattn) sattn_once_block<D>(p, once, sm.once, sm.sweep, blockIdx.x);
   else emb_run32_block<true, 4, 4, WIDE>(p, sm.run, blockIdx.x - (unsigned)n_sattn);
 }
 
@@ -1696,15 +1696,15 @@ __global__ __launch_bounds__(256, 2) void sattn_once_with_emb(ScoreParams p, int
 // WIDE: of more than 512 channels.  Its riders keep the frame before in registers and two transfers in flight (116 registers,
 // 70 KB of LDS: two blocks on a compute unit), and n_lead of them stand in front of the n_sattn blocks of the sweep.
 template <int D, bool WIDE>
-__global__ __launch_bounds__(kSaWaves * 64, WIDE ? 4 : 6) void sattn_pass1_with_emb(ScoreParams p, int n_lead, int n_sattn) {
+__global__ __launch_bounds__(kSaWaves * 64, WIDE ? 4 : 6) void sattn_pass1_with_emb(ScoreParams p, int n_sattn, int n_lead) {
   static_assert(kSaWaves == 8, "the riding blocks use the sweep's block size");
   union Smem {
     SattnSmem<D, 1> sa;
     EmbRunSmem<2, 8, WIDE ? 2 : 1> run;
   };
   __shared__ Smem sm;
-  const int blk = (int)blockIdx.x - n_lead;
-  if (blk >= 0 && blk < n_sattn) {           // the order of sattn_mfma's grid: KV head fastest, then key tile, ...
+  const int blk = (int)blockIdx.x - (WIDE ? n_lead : 0);
+  if ((!WIDE || blk >= 0) && blk < n_sattn) {           // the order of sattn_mfma's grid: KV head fastest, then key tile, ...
     const int hk = blk % p.Hkv, rest = blk / p.Hkv;
     const int tile = rest % p.n_tile, rest2 = rest / p.n_tile;
     sattn_mfma_body<D, 1>(p, sm.sa, tile, hk + p.Hkv * (rest2 % p.n_rsplit), rest2 / p.n_rsplit);
@@ -1712,7 +1712,8 @@ __global__ __launch_bounds__(kSaWaves * 64, WIDE ? 4 : 6) void sattn_pass1_with_
   }
   // (the host admits this launch only when its block count stays below 2^31: crop numbers fit 32 bits,
   // and 32-bit divisions are all that stands in front of a riding block's first load)
-  emb_run32_block<false, 2, 8, WIDE, WIDE ? 2 : 1>(p, sm.run, blk < 0 ? blockIdx.x : (unsigned)(blk - n_sattn));
+  emb_run32_block<false, 2, 8, WIDE, WIDE ? 2 : 1>(p, sm.run,
+                                                          WIDE && blk < 0 ? blockIdx.x : (unsigned)(blk - n_sattn));
 }
 
 // =================================================================================================
@@ -1917,15 +1918,15 @@ size_t score_once_words(int rows_per_kv_head) {
 
 // riders: blocks of the embedding terms beside the sweep (wide: of more channels than a pass takes)
 template <int D>
-static hipError_t launch_sattn_once(const ScoreParams& p, hipStream_t st, long long riders, bool wide) {
+static hipError_t launch_sattn_once(const ScoreParams& p, const ScoreOnce& once, hipStream_t st, long long riders, bool wide) {
   const long long n_sattn = (long long)p.n_tile * p.Hkv * p.n_rsplit * p.Bz;
-  const long long n_clear = (long long)(p.once_bytes / sizeof(u32x4));
-  hipLaunchKernelGGL(sattn_once_clear, dim3((unsigned)((n_clear + 255) / 256)), dim3(256), 0, st, (u32x4*)p.row_word,
+  const long long n_clear = (long long)(once.clear_bytes / sizeof(u32x4));
+  hipLaunchKernelGGL(sattn_once_clear, dim3((unsigned)((n_clear + 255) / 256)), dim3(256), 0, st, (u32x4*)once.row_word,
                      n_clear);
   const dim3 grid((unsigned)(n_sattn + riders));
-  if (wide) hipLaunchKernelGGL((sattn_once_with_emb<D, true>), grid, dim3(256), 0, st, p, (int)n_sattn);
-  else hipLaunchKernelGGL((sattn_once_with_emb<D, false>), grid, dim3(256), 0, st, p, (int)n_sattn);
-  hipLaunchKernelGGL(sattn_f32_redo<D>, dim3((unsigned)n_sattn), dim3(256), 0, st, p);
+  if (wide) hipLaunchKernelGGL((sattn_once_with_emb<D, true>), grid, dim3(256), 0, st, p, once, (int)n_sattn);
+  else hipLaunchKernelGGL((sattn_once_with_emb<D, false>), grid, dim3(256), 0, st, p, once, (int)n_sattn);
+  hipLaunchKernelGGL(sattn_f32_redo<D>, dim3((unsigned)n_sattn), dim3(256), 0, st, p, once);
   return hipGetLastError();
 }
 
@@ -1961,10 +1962,10 @@ static hipError_t launch_sattn_mfma(const ScoreParams& p, hipStream_t st, long l
     // call, led | followed by them: 3 x 20520 tokens, 64 heads, 16 text rows 94 | 102, 4 x 36864 x 14, 64 rows 124 | 129;
     // of 512 query rows a block and more: 4 x 16384 x 64 heads, 64 rows 201 | 197, 2 x 32768 x 28, 256 rows 290 | 285)
     if (wide)
-      hipLaunchKernelGGL((sattn_pass1_with_emb<D, true>), fused, dim3(kSaWaves * 64), 0, st, p,
-                         p.rows_per_split < 512 ? (int)riders : 0, (int)n_sattn);
+      hipLaunchKernelGGL((sattn_pass1_with_emb<D, true>), fused, dim3(kSaWaves * 64), 0, st, p, (int)n_sattn,
+                         p.rows_per_split < 512 ? (int)riders : 0);
     else
-      hipLaunchKernelGGL((sattn_pass1_with_emb<D, false>), fused, dim3(kSaWaves * 64), 0, st, p, 0, (int)n_sattn);
+      hipLaunchKernelGGL((sattn_pass1_with_emb<D, false>), fused, dim3(kSaWaves * 64), 0, st, p, (int)n_sattn, 0);
   } else {
     hipLaunchKernelGGL((sattn_mfma<D, 1>), grid, dim3(kSaWaves * 64), 0, st, p);
   }
@@ -2022,19 +2023,20 @@ static bool wide_f32_plan(ScoreParams& p, long long crops_a_frame, int de) {
   return eight;
 }
 
-hipError_t launch_score(const ScoreParams& p_in, hipStream_t st) {
+hipError_t launch_score(const ScoreParams& p_in, const ScoreOnce& once_in, hipStream_t st) {
   ScoreParams p = p_in;
+  ScoreOnce once = once_in;
   {
     const int unit = p.dtype == HIPPO_DTYPE_BF16 ? 64 : kSaF32Rows;      // rows per chunk of the sweeps
     const int rows = p.L * p.G, chunks = (rows + unit - 1) / unit, rs = p.n_rsplit > 0 ? p.n_rsplit : 1;
     p.rows_per_split = (chunks + rs - 1) / rs * unit;
-    p.row_words = chunks * unit;
+    once.row_words = chunks * unit;
     // one sweep: units of the words (of its inverse: 2^32 over the tokens as a power of two, so that the sums of all waves
     // at kOnceMax stay below 2^53), and how often a wave asks in all (about a microsecond each): a few times as long as
     // the sweep of its own run of rows takes
-    p.once_unit = 0x1p27f;
-    for (long long n = 32; n < p.Nv; n *= 2) p.once_unit *= 0.5f;
-    p.once_polls = 64 + 16 * (p.rows_per_split / kSaF32Rows);
+    once.unit = 0x1p27f;
+    for (long long n = 32; n < p.Nv; n *= 2) once.unit *= 0.5f;
+    once.polls = 64 + 16 * (p.rows_per_split / kSaF32Rows);
     p.q_step_i = 64 / p.G;
     p.q_step_g = 64 % p.G;
     p.q_last_i = (rows - 1) / p.G;
@@ -2060,7 +2062,7 @@ hipError_t launch_score(const ScoreParams& p_in, hipStream_t st) {
   long long n_riders = crops_per_frame * ((p.F + p.emb_run - 1) / p.emb_run) * p.B;
   const long long n_sattn = (long long)p.n_tile * p.Hkv * p.n_rsplit * p.Bz;
   const bool emb_rides = want_emb && !accumulate_only && (p.flags & HIPPO_SCORE_ATTN) && small_crops &&
-                         n_sattn + n_riders < (p.row_word != nullptr ? 1ll << 23 : 1ll << 31) &&
+                         n_sattn + n_riders < (once.row_word != nullptr ? 1ll << 23 : 1ll << 31) &&
                          (bf16 || !wide || wide_f32_rides(p, n_sattn, n_riders, de));
   bool eight_waves = false;
   if (!emb_rides && !bf16 && wide) {
@@ -2072,8 +2074,9 @@ hipError_t launch_score(const ScoreParams& p_in, hipStream_t st) {
     if (p.dtype == HIPPO_DTYPE_BF16)
       e = (p.D == 128) ? launch_sattn_mfma<128>(p, st, riders, wide)
                        : launch_sattn_mfma<64>(p, st, riders, wide);
-    else if (p.row_word != nullptr)
-      e = (p.D == 128) ? launch_sattn_once<128>(p, st, riders, wide) : launch_sattn_once<64>(p, st, riders, wide);
+    else if (once.row_word != nullptr)
+      e = (p.D == 128) ? launch_sattn_once<128>(p, once, st, riders, wide)
+                       : launch_sattn_once<64>(p, once, st, riders, wide);
     else
       e = (p.D == 128) ? launch_sattn_f32<128>(p, st, riders, wide) : launch_sattn_f32<64>(p, st, riders, wide);
     if (e != hipSuccess) return e;
