@@ -1226,12 +1226,12 @@ __global__ __launch_bounds__(256) void emb_scores_mfma(ScoreParams p) {
 // once the reduction has read them and lands under the rest of the frame's arithmetic.
 //
 // One pass over a block's channels (512 in bf16 with U = 2; in fp32, U = 4, 256 of four waves, 512 of eight) keeps the frame
-// before in registers.  WIDE embeddings take several passes per frame.  Up to two of them in bf16 (NB = 2) keep it there too,
+// before in registers.  WIDE embeddings take several passes per frame.  Two of them in bf16 (kHold) keep it there too,
 // 32 registers, and have both passes in flight at once, each in a strip of its own: what bounded them was that the
 // frame before was fetched again behind this frame's, from beyond the L2 (two strips alone gained nothing).  The terms
 // alone | whole scoring calls, us: 4 x 36864 tokens of 1024 channels 112 -> 75 | 735 -> 712, 4 x 16384 of 1024 83 -> 47 |
 // 222 -> 197, 4 x 36864 x 14 heads, of 768 90 -> 65 | 157 -> 122, 3 x 20520 of 1024, 16 text rows 51 -> 38 | 112 -> 93.
-// More passes, and fp32, fetch it again: two fetches per crop and frame.
+// More passes, and fp32, fetch it again: two fetches per crop and frame (kRefetch; kRefetch2 through two strips).
 // fp32 takes the same frame with four 16x16x4 products per 16-byte operand (3136 tokens, 128 channels 47 -> 37;
 // 12288 tokens, 512 channels 178 -> 143; 11040 tokens, 1024 channels 624 -> 562), by blocks of four waves, as the fp32
 // sweeps', beside pass 1 (sattn_f32_pass1_with_emb), and of four or eight in a launch of their own: wide_f32_rides and
@@ -1242,7 +1242,7 @@ __global__ __launch_bounds__(256) void emb_scores_mfma(ScoreParams p) {
 __device__ __align__(16) const unsigned char g_zero_piece[16] = {0};
 
 // NB: strips of a wave
-template <int U, int NW, int NB = 1>
+template <int U, int NW, int NB>
 struct EmbRunSmem {
   static constexpr int MP = 32;
   // operands in (32 rows x 64 U B), then Gram partials out (3 x 64 x 16 B, from four waves two sets of them)
@@ -1270,11 +1270,15 @@ __device__ __forceinline__ f32x4 emb_mma(const u32x4& a, const u32x4& b, f32x4 a
 
 // One crop position `pos` of batch element b over the frames f0 .. f0 + p.emb_run - 1 (cut at the
 // video's end), by the 64 * NW threads of a block; every thread must call it (block-wide barriers).
-template <bool F32, int U, int NW, bool WIDE, int NB>
-__device__ __forceinline__ void emb_run32_body(const ScoreParams& p, EmbRunSmem<U, NW, NB>& sm, const int tid, const int pos,
-                                               const int f0, const int b) {
-  constexpr int MP = EmbRunSmem<U, NW, NB>::MP;
-  static_assert((WIDE || NB == 1) && (NB == 1 || NW == 8), "one pass: the next frame travels while this one is reduced");
+// KIND: channels of one pass; of several, fetched again for the next frame, through one strip or two; of two passes, held.
+enum EmbKind { kOnePass, kRefetch, kRefetch2, kHold };
+constexpr int emb_strips(int kind) { return kind >= kRefetch2 ? 2 : 1; }
+template <bool F32, int U, int NW, int KIND>
+__device__ __forceinline__ void emb_run32_body(const ScoreParams& p, EmbRunSmem<U, NW, emb_strips(KIND)>& sm, const int tid,
+                                               const int pos, const int f0, const int b) {
+  constexpr bool WIDE = KIND != kOnePass, TWO = KIND >= kRefetch2, HOLD = KIND == kHold;
+  constexpr int MP = EmbRunSmem<U, NW, emb_strips(KIND)>::MP;
+  static_assert(!TWO || NW == 8, "one set of partial sums");
   constexpr int TPT = NW * 64 / MP, CPT = MP / TPT; // threads per token, cosines per thread
   static_assert((NW == 8 && TPT == 16) || (NW == 4 && TPT == 8), "a token's threads are half or all of a 16-lane row");
   constexpr int EB = F32 ? 4 : 2;                   // bytes per channel
@@ -1380,7 +1384,8 @@ __device__ __forceinline__ void emb_run32_body(const ScoreParams& p, EmbRunSmem<
   auto token_sum = [](float v) { return NW == 8 ? row16_sum(v) : row8_sum(v); };
   const long long out_base = (long long)b * p.Nv + sm.tok_s[a];
 
-  const int n_pass = WIDE ? (de + CB - 1) / CB : 1;
+  constexpr int HP = HOLD ? 2 : 1;                  // passes that are held
+  const int n_pass = HOLD ? HP : WIDE ? (de + CB - 1) / CB : 1;
   // Several passes of four waves: odd and even passes are two sets of partial sums, which stand for waves 4 to 7 and 0 to 3
   // of eight: a frame's Gram and dot products are the same chains of channels, summed in the same order, whichever
   // kernel takes them.  (One chain over both put the fused score of 512 fp32 channels 1.3 times, of 1024 1.5 times as far
@@ -1394,9 +1399,6 @@ __device__ __forceinline__ void emb_run32_body(const ScoreParams& p, EmbRunSmem<
   for (int rbk = 0; rbk < 2; ++rbk)
 #pragma unroll
     for (int u = 0; u < UP; ++u) prev[rbk][u] = (u32x4){0u, 0u, 0u, 0u};
-  // Two strips and at most two passes: the frame before stays in registers as with one pass.
-  constexpr int HP = NB == 2 ? 2 : 1;
-  const bool hold = NB == 2 && n_pass <= HP;
   u32x4 held[HP][2][U];
 #pragma unroll
   for (int h = 0; h < HP; ++h)
@@ -1415,14 +1417,10 @@ __device__ __forceinline__ void emb_run32_body(const ScoreParams& p, EmbRunSmem<
     request(t_before ? t_fr - 1 : t_fr, t_pass);
     put ^= 1;
     ++in_flight;
-    if (!hold && !t_before && t_fr > lo) {
-      t_before = true;
-    } else {
-      t_before = false;
-      if (++t_pass == n_pass) {
-        t_pass = 0;
-        ++t_fr;
-      }
+    t_before = !HOLD && !t_before && t_fr > lo;
+    if (!t_before && ++t_pass == n_pass) {
+      t_pass = 0;
+      ++t_fr;
     }
   };
   auto arrive = [&]() {                             // the oldest transfer in flight is in its strip
@@ -1432,7 +1430,7 @@ __device__ __forceinline__ void emb_run32_body(const ScoreParams& p, EmbRunSmem<
     strip = &sm.strip[take][wave][0];
     take ^= 1;
   };
-  if constexpr (NB == 2) {
+  if constexpr (TWO) {
     issue();
     issue();
   } else {
@@ -1480,14 +1478,14 @@ __device__ __forceinline__ void emb_run32_body(const ScoreParams& p, EmbRunSmem<
       const bool has_before = fr > lo;
       auto take_pass = [&](int pass, f32x4 (&gram)[3], f32x4 (&dot)[2]) {
         u32x4 cur[2][U];
-        if constexpr (NB == 2) arrive();
+        if constexpr (TWO) arrive();
         else wait_vmcnt<0>();
 #pragma unroll
         for (int rbk = 0; rbk < 2; ++rbk)
 #pragma unroll
           for (int u = 0; u < U; ++u) cur[rbk][u] = operand(rbk, u);
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // read before the next transfer may overwrite them
-        if constexpr (NB == 2) {
+        if constexpr (TWO) {
           if (has_before || pass + 1 < n_pass) issue();      // (the frame's last strip takes the partial sums first)
         } else {
           if (has_before) request(fr - 1, pass);
@@ -1499,7 +1497,7 @@ __device__ __forceinline__ void emb_run32_body(const ScoreParams& p, EmbRunSmem<
 #pragma unroll
             for (int u = 0; u < U; ++u) gram[i] = emb_mma<F32>(cur[i >> 1][u], cur[(i + 1) >> 1][u], gram[i]);
         if (has_before) {
-          if constexpr (NB == 2) arrive();
+          if constexpr (TWO) arrive();
           else wait_vmcnt<0>();
 #pragma unroll
           for (int rbk = 0; rbk < 2; ++rbk) {
@@ -1511,15 +1509,14 @@ __device__ __forceinline__ void emb_run32_body(const ScoreParams& p, EmbRunSmem<
           }
           asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
           if (pass + 1 < n_pass) {
-            if constexpr (NB == 2) issue();
+            if constexpr (TWO) issue();
             else request(fr, pass + 1);
           }
         }
       };
-      if (NB == 2 && hold) {
+      if constexpr (HOLD) {
 #pragma unroll
         for (int h = 0; h < HP; ++h) {
-          if (h >= n_pass) break;
           u32x4 cur[2][U];
           arrive();
 #pragma unroll
@@ -1527,7 +1524,7 @@ __device__ __forceinline__ void emb_run32_body(const ScoreParams& p, EmbRunSmem<
 #pragma unroll
             for (int u = 0; u < U; ++u) cur[rbk][u] = operand(rbk, u);
           asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-          if (h + 1 < n_pass) issue();
+          if (h + 1 < HP) issue();
 #pragma unroll
           for (int i = 0; i < 3; ++i)
             if (i != 1 || own_frame)
@@ -1571,7 +1568,7 @@ __device__ __forceinline__ void emb_run32_body(const ScoreParams& p, EmbRunSmem<
     // blocks also give the scales of the rows' norms), wave 3 the diagonals of the dot blocks
     if (wave < 3 && (own_frame || wave != 1)) {
       const int blk = wave;
-      const unsigned used = NB == 2 ? take ^ 1 : 0;  // the strips that took the partial sums
+      const unsigned used = TWO ? take ^ 1 : 0;  // the strips that took the partial sums
       f32x4 v = *(const f32x4*)(&sm.strip[used][0][0] + (blk * 64 + lane) * 16);
 #pragma unroll
       for (int w = 1; w < SETS * NW; ++w)
@@ -1596,7 +1593,7 @@ __device__ __forceinline__ void emb_run32_body(const ScoreParams& p, EmbRunSmem<
       sm.dotv[lane] = d;
     }
     __syncthreads();
-    if constexpr (NB == 2) issue();                 // the strips are free again: the next frame travels meanwhile
+    if constexpr (TWO) issue();                 // the strips are free again: the next frame travels meanwhile
     else if (fr < hi) request(fr + 1, 0);
 
     // cosines of token a against tokens c0 .. c0 + CPT - 1 (its TPT threads cover the crop; padding rows hold
@@ -1636,21 +1633,22 @@ __device__ __forceinline__ void emb_run32_body(const ScoreParams& p, EmbRunSmem<
 }
 
 // block number -> (crop position, run of frames, batch element), positions fastest
-template <bool F32, int U, int NW, bool WIDE, int NB = 1>
-__device__ __forceinline__ void emb_run32_block(const ScoreParams& p, EmbRunSmem<U, NW, NB>& sm, const unsigned blk) {
+template <bool F32, int U, int NW, int KIND>
+__device__ __forceinline__ void emb_run32_block(const ScoreParams& p, EmbRunSmem<U, NW, emb_strips(KIND)>& sm,
+                                                const unsigned blk) {
   const unsigned ncf = (unsigned)(((p.gh + p.ch - 1) / p.ch) * ((p.gw + p.cw - 1) / p.cw));   // crops per frame
   const unsigned n_runs = (unsigned)((p.F + p.emb_run - 1) / p.emb_run);
   const unsigned rest = blk / ncf, pos = blk - rest * ncf;
   const unsigned bb = rest / n_runs, run = rest - bb * n_runs;
-  emb_run32_body<F32, U, NW, WIDE, NB>(p, sm, threadIdx.x, (int)pos, (int)run * p.emb_run, (int)bb);
+  emb_run32_body<F32, U, NW, KIND>(p, sm, threadIdx.x, (int)pos, (int)run * p.emb_run, (int)bb);
 }
 
 // (four waves: three blocks on a compute unit; with registers for two, 4 x 72 frames of 768 channels took 256 us, not 187)
-template <bool F32, int NW, bool WIDE>
+template <bool F32, int NW, int KIND>
 __global__ __launch_bounds__(64 * NW, NW == 4 ? 3 : 2) void emb_scores_run32(ScoreParams p) {
-  constexpr int U = F32 ? 4 : 2, NB = WIDE && !F32 ? 2 : 1;
-  __shared__ EmbRunSmem<U, NW, NB> sm;
-  emb_run32_block<F32, U, NW, WIDE, NB>(p, sm, blockIdx.x);
+  constexpr int U = F32 ? 4 : 2;
+  __shared__ EmbRunSmem<U, NW, emb_strips(KIND)> sm;
+  emb_run32_block<F32, U, NW, KIND>(p, sm, blockIdx.x);
 }
 
 // fp32 beyond 65536 tokens: pass 1 and the embedding terms in one launch, the sweep's blocks first.  A wave of the sweep
@@ -1661,7 +1659,7 @@ template <int D, bool WIDE>
 __global__ __launch_bounds__(256, 3) void sattn_f32_pass1_with_emb(ScoreParams p, int n_sattn) {
   union Smem {
     SattnF32Smem<D> sa;
-    EmbRunSmem<4, 4> run;
+    EmbRunSmem<4, 4, 1> run;
   };
   __shared__ Smem sm;
   const int blk = blockIdx.x;
@@ -1671,7 +1669,7 @@ __global__ __launch_bounds__(256, 3) void sattn_f32_pass1_with_emb(ScoreParams p
     sattn_f32_body<D, 1>(p, sm.sa, tile, hk, rest2 % p.n_rsplit, rest2 / p.n_rsplit);
     return;
   }
-  emb_run32_block<true, 4, 4, WIDE>(p, sm.run, (unsigned)(blk - n_sattn));
+  emb_run32_block<true, 4, 4, WIDE ? kRefetch : kOnePass>(p, sm.run, (unsigned)(blk - n_sattn));
 }
 
 // The same beside the one sweep (3136 tokens: 15.8 us; 936 tokens, whole calls, beside a sweep 30.6 -> 22.2, 3 x 7220 tokens in
@@ -1681,11 +1679,11 @@ __global__ __launch_bounds__(256, 2) void sattn_once_with_emb(ScoreParams p, Sco
   union Smem {
     SattnOnceSmem<D> once;
     SattnF32Smem<D> sweep;
-    EmbRunSmem<4, 4> run;
+    EmbRunSmem<4, 4, 1> run;
   };
   __shared__ Smem sm;
   if ((int)blockIdx.x < n_sattn) sattn_once_block<D>(p, once, sm.once, sm.sweep, blockIdx.x);
-  else emb_run32_block<true, 4, 4, WIDE>(p, sm.run, blockIdx.x - (unsigned)n_sattn);
+  else emb_run32_block<true, 4, 4, WIDE ? kRefetch : kOnePass>(p, sm.run, blockIdx.x - (unsigned)n_sattn);
 }
 
 // Pass 1 of s_attn and the embedding terms in ONE launch: the first n_sattn blocks run the
@@ -1693,18 +1691,20 @@ __global__ __launch_bounds__(256, 2) void sattn_once_with_emb(ScoreParams p, Sco
 // fill the third block slot of the compute units, so the memory-bound embedding work hides under the
 // sweep instead of following it.  Three blocks fit a compute unit: 8 waves of at most 80 registers
 // each and the larger of the shared-memory layouts.  A riding block owns one crop position over a run of frames.
-// WIDE: of more than 512 channels.  Its riders keep the frame before in registers and two transfers in flight (116 registers,
-// 70 KB of LDS: two blocks on a compute unit), and n_lead of them stand in front of the n_sattn blocks of the sweep.
-template <int D, bool WIDE>
-__global__ __launch_bounds__(kSaWaves * 64, WIDE ? 4 : 6) void sattn_pass1_with_emb(ScoreParams p, int n_sattn, int n_lead) {
+// Riders of two strips (kRefetch2, kHold: 117 and 99 registers, 70 KB of LDS) leave two blocks on a compute unit; n_lead of them
+// stand in front of the n_sattn blocks of the sweep.  wide_bf16_riders says which take which.
+template <int D, int KIND>
+__global__ __launch_bounds__(kSaWaves * 64, emb_strips(KIND) == 2 ? 4 : 6)
+void sattn_pass1_with_emb(ScoreParams p, int n_sattn, int n_lead) {
+  constexpr bool LEAD = emb_strips(KIND) == 2;
   static_assert(kSaWaves == 8, "the riding blocks use the sweep's block size");
   union Smem {
     SattnSmem<D, 1> sa;
-    EmbRunSmem<2, 8, WIDE ? 2 : 1> run;
+    EmbRunSmem<2, 8, emb_strips(KIND)> run;
   };
   __shared__ Smem sm;
-  const int blk = (int)blockIdx.x - (WIDE ? n_lead : 0);
-  if ((!WIDE || blk >= 0) && blk < n_sattn) {           // the order of sattn_mfma's grid: KV head fastest, then key tile, ...
+  const int blk = (int)blockIdx.x - (LEAD ? n_lead : 0);
+  if ((!LEAD || blk >= 0) && blk < n_sattn) {   // the order of sattn_mfma's grid: KV head fastest, then key tile, ...
     const int hk = blk % p.Hkv, rest = blk / p.Hkv;
     const int tile = rest % p.n_tile, rest2 = rest / p.n_tile;
     sattn_mfma_body<D, 1>(p, sm.sa, tile, hk + p.Hkv * (rest2 % p.n_rsplit), rest2 / p.n_rsplit);
@@ -1712,8 +1712,7 @@ __global__ __launch_bounds__(kSaWaves * 64, WIDE ? 4 : 6) void sattn_pass1_with_
   }
   // (the host admits this launch only when its block count stays below 2^31: crop numbers fit 32 bits,
   // and 32-bit divisions are all that stands in front of a riding block's first load)
-  emb_run32_block<false, 2, 8, WIDE, WIDE ? 2 : 1>(p, sm.run,
-                                                          WIDE && blk < 0 ? blockIdx.x : (unsigned)(blk - n_sattn));
+  emb_run32_block<false, 2, 8, KIND>(p, sm.run, LEAD && blk < 0 ? blockIdx.x : (unsigned)(blk - n_sattn));
 }
 
 // =================================================================================================
@@ -1951,6 +1950,34 @@ static hipError_t launch_sattn_f32(const ScoreParams& p, hipStream_t st, long lo
 }
 
 // riders: 0 = pass 1 in a launch of its own, else that many riding blocks (wide: of more channels than a pass takes)
+// bf16 riders of more than 512 channels: which of them, and how many stand in front of the sweep's blocks.
+// The two-strip ones take a third of the compute units' block slots from the launch; what longer takes (a rider, by its
+// frames and passes, or a block of the sweep, by its chunks of 64 rows) goes first.  us a call from a graph, one strip | two
+// strips in front | two strips behind:
+//   two passes, held: 3 x 10692 tokens, 64 heads, 15 text rows 75 | 61 | 68; 27830 x 14 heads x 2, 36 rows 81 | 57 | 61; 3 x 3822 x 64, 95
+//     rows 68 | 72 | 66; 2 x 45356 x 14, 171 rows 161 | 148 | 141.  Only a sweep of many times the riders' work is the better one
+//     with three slots: 4 x 1452 x 64 in four layers, 239 rows 218 | 228 | 223; 2640 x 64 in four, 201 rows 105 | 112 | 108
+//     (at 14 times; nearer than that within 2.5 % either way).
+//   more passes, fetched again: two strips gain as long as the riders go first and the sweep fills the chip (3 x 15312 x 64
+//     heads, 76 rows, 3584 channels 297 | 248 | 294; 15750 x 14 x 2 in four layers, 37 rows, 2048 channels 109 | 96 | 113), or where all
+//     blocks fit two a compute unit and there is a compute unit for each rider (1785 x 64, 178 rows, 2048 channels 46 | 42 | 46); else one
+//     strip (3 x 4056 x 64 in two layers, 105 rows, 1536 channels 130 | 140 | 136; 3726 x 64, 254 rows 61 | 65 | 64).
+struct Riders {
+  int kind;
+  long long lead;
+};
+static Riders wide_bf16_riders(const ScoreParams& p, long long n_sattn, long long riders) {
+  const long long de = p.emb ? p.emb_dim : (long long)p.Hkv * p.D, passes = (de + 511) / 512;
+  const long long chunks = p.rows_per_split / 64, frames = p.emb_run;
+  const bool first = 3 * chunks <= 2 * (frames + 1) * passes;
+  if (passes == 2) {
+    if (n_sattn * chunks >= 14 * riders * (frames + 2)) return {kRefetch, 0};
+    return {kHold, first ? riders : 0};
+  }
+  const bool two = n_sattn > kNumCU ? first : n_sattn + riders > kNumCU && riders <= kNumCU;
+  return two ? Riders{kRefetch2, riders} : Riders{kRefetch, 0};
+}
+
 template <int D>
 static hipError_t launch_sattn_mfma(const ScoreParams& p, hipStream_t st, long long riders, bool wide) {
   if (p.n_tile > 65535 || (long long)p.n_rsplit * p.Bz > 65535) return hipErrorInvalidValue;
@@ -1958,14 +1985,12 @@ static hipError_t launch_sattn_mfma(const ScoreParams& p, hipStream_t st, long l
   if (riders > 0) {
     const long long n_sattn = (long long)p.n_tile * p.Hkv * p.n_rsplit * p.Bz;
     const dim3 fused((unsigned)(n_sattn + riders));
-    // (wide riders lead where a sweep block has less than eight chunks and the riders' bytes are most of the launch; us a
-    // call, led | followed by them: 3 x 20520 tokens, 64 heads, 16 text rows 94 | 102, 4 x 36864 x 14, 64 rows 124 | 129;
-    // of 512 query rows a block and more: 4 x 16384 x 64 heads, 64 rows 201 | 197, 2 x 32768 x 28, 256 rows 290 | 285)
-    if (wide)
-      hipLaunchKernelGGL((sattn_pass1_with_emb<D, true>), fused, dim3(kSaWaves * 64), 0, st, p, (int)n_sattn,
-                         p.rows_per_split < 512 ? (int)riders : 0);
-    else
-      hipLaunchKernelGGL((sattn_pass1_with_emb<D, false>), fused, dim3(kSaWaves * 64), 0, st, p, (int)n_sattn, 0);
+    const Riders r = wide ? wide_bf16_riders(p, n_sattn, riders) : Riders{kOnePass, 0};
+    const auto launch = r.kind == kHold       ? sattn_pass1_with_emb<D, kHold>
+                        : r.kind == kRefetch2 ? sattn_pass1_with_emb<D, kRefetch2>
+                        : r.kind == kRefetch  ? sattn_pass1_with_emb<D, kRefetch>
+                                              : sattn_pass1_with_emb<D, kOnePass>;
+    hipLaunchKernelGGL(launch, fused, dim3(kSaWaves * 64), 0, st, p, (int)n_sattn, (int)r.lead);
   } else {
     hipLaunchKernelGGL((sattn_mfma<D, 1>), grid, dim3(kSaWaves * 64), 0, st, p);
   }
@@ -2093,12 +2118,15 @@ hipError_t launch_score(const ScoreParams& p_in, const ScoreOnce& once_in, hipSt
       if (n_riders >= (1ll << 31)) return hipErrorInvalidValue;
       const dim3 runs((unsigned)n_riders);
       // (fp32 up to 256 channels: half of eight waves would idle; 128 frames of 128 channels 29 against 42 us)
-      if (bf16 && wide) hipLaunchKernelGGL((emb_scores_run32<false, 8, true>), runs, dim3(512), 0, st, p);
-      else if (bf16) hipLaunchKernelGGL((emb_scores_run32<false, 8, false>), runs, dim3(512), 0, st, p);
-      else if (wide && de <= 512) hipLaunchKernelGGL((emb_scores_run32<true, 8, false>), runs, dim3(512), 0, st, p);
-      else if (wide && eight_waves) hipLaunchKernelGGL((emb_scores_run32<true, 8, true>), runs, dim3(512), 0, st, p);
-      else if (wide) hipLaunchKernelGGL((emb_scores_run32<true, 4, true>), runs, dim3(256), 0, st, p);
-      else hipLaunchKernelGGL((emb_scores_run32<true, 4, false>), runs, dim3(256), 0, st, p);
+      // (more than two passes: through two strips, two blocks a compute unit, 2 x 17680 tokens of 3584 channels took 129 us, not
+      // 108; 19800 of 2048 53, not 48; 18590 of 1536 40, not 38; 4056 of 2048 to 3584 within 10 % either way)
+      if (bf16 && de > 1024) hipLaunchKernelGGL((emb_scores_run32<false, 8, kRefetch>), runs, dim3(512), 0, st, p);
+      else if (bf16 && wide) hipLaunchKernelGGL((emb_scores_run32<false, 8, kHold>), runs, dim3(512), 0, st, p);
+      else if (bf16) hipLaunchKernelGGL((emb_scores_run32<false, 8, kOnePass>), runs, dim3(512), 0, st, p);
+      else if (wide && de <= 512) hipLaunchKernelGGL((emb_scores_run32<true, 8, kOnePass>), runs, dim3(512), 0, st, p);
+      else if (wide && eight_waves) hipLaunchKernelGGL((emb_scores_run32<true, 8, kRefetch>), runs, dim3(512), 0, st, p);
+      else if (wide) hipLaunchKernelGGL((emb_scores_run32<true, 4, kRefetch>), runs, dim3(256), 0, st, p);
+      else hipLaunchKernelGGL((emb_scores_run32<true, 4, kOnePass>), runs, dim3(256), 0, st, p);
     } else if (!bf16) {
       hipLaunchKernelGGL(emb_scores, grid, dim3(256), 0, st, p);
     } else if (p.ch * p.cw <= 48) {

@@ -233,7 +233,7 @@ def test_fp32_attention_mass(hippo, shape, d):
     # single piece; one frame, two, runs of several with a short last one; crops cut at the edges, of one token, of 32
     (1, 1, 5, 5, 512, 5, 5), (1, 2, 5, 7, 8, 5, 5), (2, 9, 11, 13, 520, 5, 5), (1, 3, 6, 5, 1024, 5, 5),
     (1, 40, 16, 16, 768, 5, 5), (1, 37, 11, 12, 504, 4, 8), (1, 5, 3, 3, 1544, 1, 1),
-    # bf16 keeps the frame before in registers up to two passes: three, over runs of several frames
+    # bf16 keeps the frame before in registers for two passes: three, over runs of several frames
     (1, 60, 16, 16, 1032, 5, 5),
 ])
 def test_embedding_terms_over_passes_of_channels(hippo, shape, dtype):
@@ -288,6 +288,24 @@ def test_wide_embedding_terms_beside_the_sweep(hippo, L, frames):
     st, ss = oracle.s_temp(emb, 3), oracle.s_spa(emb, 3, 16, 16)      # the first two frames, whose neighbours are among three
     assert_close(host(comps[0])[1][:, :512], st[:, :512], "bf16", "s_temp")
     np.testing.assert_allclose(host(comps[0])[2][:, :512], ss[:, :512], rtol=0, atol=2e-3 * ss.max())
+
+
+@pytest.mark.parametrize("ch, L, frames", [
+    # two passes beside a sweep of many times their work; three: before a short sweep that fills the chip, beside one that does
+    # not, behind a long one, and in few blocks
+    (768, 1024, 4), (1536, 16, 33), (1536, 16, 12), (1536, 256, 33), (1544, 16, 3),
+])
+def test_wide_embeddings_of_their_own_beside_the_sweep(hippo, ch, L, frames):
+    n = frames * 256
+    q, k = score_inputs(L, 1, L, 64, 8, 128, n, "bf16", 0.5)
+    emb = np.random.default_rng(ch).standard_normal((1, frames, 256, ch))
+    emb = prep((emb + 0.7 * np.roll(emb, 1, 1)).reshape(1, n, ch), "bf16")
+    q, k, vid, e = dev(q, "bf16"), dev(k, "bf16"), hippo.video_desc(frames, 16, 16, 0), dev(emb, "bf16")
+    comps = [hippo.hippo_score_tokens(q, k, vid, emb=e, flags=flags, want_components=True)[1] for flags in (7, 1, 6)]
+    assert torch.equal(comps[0][0], comps[1][0]) and torch.equal(comps[0][1:], comps[2][1:])
+    st, ss = oracle.s_temp(emb, frames), oracle.s_spa(emb, frames, 16, 16)
+    assert_close(host(comps[0])[1], st, "bf16", "s_temp")
+    np.testing.assert_allclose(host(comps[0])[2], ss, rtol=0, atol=2e-3 * ss.max())
 
 
 @pytest.mark.parametrize("dtype", ["fp32", "bf16"])
