@@ -189,7 +189,7 @@ int attention_entry(int call, const void* q, int32_t q_len, const void* k_cache,
 struct ScorePlan {
   int n_tile, n_rsplit;
   bool once;
-  size_t off_word, off_large, off_arrived, clear_bytes, off_redo;   // one sweep: the first three are cleared together
+  size_t off_word, off_bin, off_flags, off_arrived, clear_bytes, off_redo;   // one sweep: all but the last are cleared together
   size_t off_row_l, off_row_lse, off_col, off_sa, off_st, off_ss, bytes;
 };
 
@@ -221,12 +221,14 @@ int plan_score(const hippo_kv_desc* kv, const hippo_video_desc* vid, int l_txt, 
   o += vec;                 pl->off_ss = o;
   o += vec;
   const size_t heads = (size_t)kv->n_kv_heads * kv->batch * n_layers, runs = heads * pl->n_rsplit;
-  const size_t words = heads * score_once_words(l_txt * (kv->n_q_heads / kv->n_kv_heads)) * sizeof(unsigned long long);
+  const size_t once_rows = heads * score_once_rows(l_txt * (kv->n_q_heads / kv->n_kv_heads)) * sizeof(unsigned long long);
+  const size_t words = once_rows * kScoreOnceWords, bins = once_rows * kScoreOnceBins;
   // (its launches are one-dimensional: a grid's threads stay below 2^32)
-  pl->once = score_once(kv->dtype, Nv) && runs * pl->n_tile < (1u << 22) && words < (1ull << 32);
+  pl->once = score_once(kv->dtype, Nv) && runs * pl->n_tile < (1u << 22) && words + bins < (1ull << 34);
   if (pl->once) {
     pl->off_word = o;       o += align_up(words, 256);
-    pl->off_large = o;      o += align_up(runs * sizeof(int), 256);
+    pl->off_bin = o;        o += align_up(bins, 256);
+    pl->off_flags = o;      o += align_up(runs * 2 * sizeof(unsigned), 256);
     pl->off_arrived = o;    o += align_up(runs * sizeof(int), 256);
     pl->clear_bytes = o - pl->off_word;
     pl->off_redo = o;       o += align_up(runs * pl->n_tile * sizeof(int), 256);
@@ -404,7 +406,8 @@ int hippo_score_tokens_layers(int32_t n_layers, const void* const* q_txt_layers,
   ScoreOnce once{};
   if (pl.once) {
     once.row_word = reinterpret_cast<unsigned long long*>(ws + pl.off_word);
-    once.run_large = reinterpret_cast<int*>(ws + pl.off_large);
+    once.row_bin = reinterpret_cast<unsigned long long*>(ws + pl.off_bin);
+    once.run_flags = reinterpret_cast<unsigned*>(ws + pl.off_flags);
     once.run_arrived = reinterpret_cast<int*>(ws + pl.off_arrived);
     once.tile_redo = reinterpret_cast<int*>(ws + pl.off_redo);
     once.clear_bytes = pl.clear_bytes;

@@ -315,19 +315,21 @@ struct ScoreParams {
 // trip for its arguments: 13824 tokens x 14 heads, 149 text rows 33.1 -> 34.2 us a call.)
 struct ScoreOnce {
   unsigned long long* row_word;  // [Bz, Hkv, row_words, copies] row sums and the number of tiles in them; null: two sweeps
-  int* run_large;                // [Bz, n_rsplit, Hkv] a run has rows out of the words' range
+  unsigned long long* row_bin;   // [Bz, Hkv, row_words, bins] the same of the tiles whose sums those words cannot hold
+  unsigned* run_flags;           // [Bz, n_rsplit, Hkv, 2] a run has rows out of range; it has sums in the bins
   int* run_arrived;              // [Bz, n_rsplit, Hkv] tiles of such a run whose statistics are written
   int* tile_redo;                // [Bz, n_rsplit, Hkv, n_tile] left to the redo launch (not cleared: every block writes)
   size_t clear_bytes;            // what is cleared before the sweep, from row_word on: all but tile_redo
   // filled in by launch_score
   int row_words;                 // rows of a KV head, padded to whole chunks
-  float unit;
+  unsigned range;                // of a float's bits, from kOnceLow on: what of a tile goes to row_word
   int polls;
 };
 hipError_t launch_score(const ScoreParams& p, const ScoreOnce& once, hipStream_t st);
 int score_token_tile(int dtype);   // tokens per block in the s_attn passes
 bool score_once(int dtype, long long n_vis);       // s_attn in one sweep
-size_t score_once_words(int rows_per_kv_head);     // its words, of a KV head
+size_t score_once_rows(int rows_per_kv_head);      // rows of a KV head that it has words for
+extern const int kScoreOnceWords, kScoreOnceBins;  // its 64-bit words a row
 int score_row_splits(int dtype, long long blocks_unsplit, int rows_per_kv_head);
 
 struct SelectParams {

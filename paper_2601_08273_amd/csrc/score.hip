@@ -225,27 +225,36 @@ __device__ __forceinline__ float log2_of_sum(float tot) {
 // exponentials of its last kOnceHold chunks of 32 rows in registers (16 a lane and chunk, where the products were), adds
 // its row sums to a 64-bit word a row in device memory, and adds exponential x 1 / sum to the columns kOnceHold chunks
 // later, when the words have counted every tile.
-//   The words: bits 0..52 a sum in units of once.unit, bits 53..62 how many tiles have added theirs.  One 64-bit add
+//   The words: bits 0..52 a sum in units of kOnceUnit, bits 53..62 how many tiles have added theirs.  One 64-bit add
 // carries both, so nothing relies on the order of two locations, and integer sums do not depend on the order of the
 // tiles.  Four words a row, by tile: adds to one word wait for each other (a bf16
 // form of this sweep, whose chunks are shorter, took 1140 us with one word a row and 770 with eight).
+//   A word takes a tile's sum whole: from kOnceLow on, whose last bit is a unit, up to where the sum of all tiles would leave
+// its bits (mean exponentials from 2^-13 to 2^9 at 16384 tokens).  What is outside goes, whole too, to one of kOnceBins words a
+// row, each for 20 powers of two.  A wave that has used them, or that waits in vain for the words while a tile of the run
+// says that it has, fetches them along with the words.  So a row's sum is that of its tiles' sums rounded no more than twice,
+// wherever it lies.  (Rounded to the units of one word a row, they lost up to half a unit a tile: 1.4e-5 of a row that one token
+// decides among 65536, whose columns are 1.1e-7 from 64 bits now and were 1.6e-6 with two sweeps.)
 //   Waiting: a block waits for the tiles of its own (layer, batch element, KV head, row run), which stand next to each
 // other in the launch order, kOnceMaxTiles of them at most.  A wave that has asked for sums once.polls times in all no
 // longer waits: its block says so in tile_redo and sattn_f32_redo sweeps that tile again, with all sums known, the same
 // operations in the same order.  So every wait ends, and no result depends on a wait, whatever else the GPU runs.
-//   Range: a wave's sums up to kOnceMax and row sums from kOnceMinUnits on (an exponential's mean over the row between
-// 2^-8 and 2^20, none above 2^25; a sum's units are then 2^-24 of it and less).  Where any row of a run leaves it, all
-// blocks of the run find that out at the same chunk (a tile does not add such a sum, and says so in run_large), write
+//   Range: a wave's sums up to kOnceMax and row sums from kOnceMin on (logits within some 60 to 80 nats; the exponentials
+// below 2^-126 that a row of the least sum loses are 2^-24 of it).  Where any row of a run leaves it, all
+// blocks of the run find that out at the same chunk (a tile does not add such a sum, and says so in run_flags), write
 // (max, sum) of their rows as pass 1 does, and the last of them merges these; sattn_f32_redo runs pass 2 for that run.
-// That costs the sweep up to there: 3136 tokens x 14 heads, 16384 x 28 and 36864 x 28 with the queries of the cases times
-// 1, 3 or 6 take 24, 181 and 220 us a call (two sweeps 30, 302, 259), times 12 59, 455 and 490.
+// RANGE_FIGURES
 // =================================================================================================
 constexpr int kOnceHold = 5;           // chunks between a row's exponentials and their columns
 constexpr int kOnceCopies = 4;         // words a row
 constexpr int kOnceMaxTiles = 512;     // two blocks on every compute unit
 constexpr int kOnceCountBit = 53;
-constexpr float kOnceMax = 0x1p25f;    // of a wave's 32 tokens
-constexpr float kOnceMinUnits = 0x1p24f;
+constexpr float kOnceLow = 0x1p-6f, kOnceUnit = kOnceLow * 0x1p-23f;
+constexpr int kOnceBins = 12, kOnceBinBits = 20, kOnceBinLow = -122;   // powers of two: of a bin, where the first begins
+constexpr float kOnceMax = 0x1p115f;   // of a wave's 32 tokens; a row of 512 tiles stays below 2^126, whose inverse is normal
+constexpr float kOnceMin = 0x1p-86f;   // of a row
+static_assert((unsigned long long)kOnceMaxTiles << (kOnceBinBits + 24) <= 1ull << kOnceCountBit && kOnceMaxTiles < 1 << 10,
+              "sums and numbers of all tiles");
 
 template <int D>
 struct SattnOnceSmem {
@@ -253,12 +262,22 @@ struct SattnOnceSmem {
   __align__(16) unsigned char Qs[2][RCH * D * 4];
   __align__(16) unsigned long long word_s[2][kOnceCopies][RCH];   // of the chunk whose columns come next
   float sum_s[2][NW][RCH];                               // the waves' row sums; NaN: out of range
+  __align__(16) unsigned long long bin_s[2][kOnceBins][RCH];      // its bins, if asked_s
+  __align__(16) unsigned long long own_bin_s[NW][kOnceBins][RCH]; // what a wave that waits has fetched
+  int asked_s[2], told_s;                                // (told_s: the block has set the run's flag)
   int state_s[NW];
   int large_s[2];                                        // a wave has met a row out of range, in steps of either parity
   int last_s;
 };
 
 enum OnceState { kOnceDone = 0, kOnceGaveUp = 1, kOnceLarge = 2 };
+
+// the power of two that a bin's unit is
+__device__ __forceinline__ int once_bin_unit(int bin) { return kOnceBinLow - 23 + kOnceBinBits * bin; }
+__device__ __forceinline__ float once_units(unsigned long long word) {
+  const unsigned hi = (unsigned)(word >> 32) & ((1u << (kOnceCountBit - 32)) - 1);
+  return fmaf((float)hi, 0x1p32f, (float)(unsigned)word);
+}
 
 // where sattn_once counts and flags the row run of a block
 __device__ __forceinline__ long long once_run(const ScoreParams& p, int hk, int rs, int bz) {
@@ -274,7 +293,9 @@ __device__ __forceinline__ int sattn_once_body(const ScoreParams& p, const Score
   constexpr int NS = D / 16;
   constexpr int CPR = D / 4, RPI = 64 / CPR, XPW = RCH / RPI / NW, CHUNKB = RCH * D * 4;
   constexpr int CW = RCH * kOnceCopies;                  // words a chunk
-  static_assert(RCH == 32 && CW * 8 == 64 * 16, "a transfer brings a chunk's words, a lane's sum is that of row lane % 32");
+  constexpr int BW = RCH * kOnceBins;                    // bins a chunk
+  static_assert(RCH == 32 && CW * 8 == 64 * 16 && BW * 8 % 1024 == 0,
+                "a transfer brings a chunk's words, a few its bins; a lane's sum is that of row lane % 32");
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int j = lane & 15, g = lane >> 4;
@@ -289,7 +310,10 @@ __device__ __forceinline__ int sattn_once_body(const ScoreParams& p, const Score
   const float* qbase = (const float*)p.q_layers[layer] + ((long long)b * p.L * p.H + hk * p.G) * D;
   const unsigned qs_addr = (unsigned)(uintptr_t)&sm.Qs[0][0];
   unsigned long long* const words = once.row_word + ((long long)(bz * p.Hkv + hk) * once.row_words + row_begin) * kOnceCopies;
-  int* const run_large = once.run_large + once_run(p, hk, rs, bz);
+  unsigned long long* const bins =
+      once.row_bin + ((long long)(bz * p.Hkv + hk) * once.row_words + row_begin) * kOnceBins;   // [chunk][bin][row]
+  unsigned* const run_flags = once.run_flags + 2 * once_run(p, hk, rs, bz);
+  auto flag = [&](int which) { __hip_atomic_store(run_flags + which, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); };
 
   auto request_chunk = [&](int c) {                      // into buffer c & 1; rows past the end re-read the last row
 #pragma unroll
@@ -301,8 +325,16 @@ __device__ __forceinline__ int sattn_once_body(const ScoreParams& p, const Score
             qs_addr + (c & 1) * CHUNKB + (wave * XPW + u) * 1024);
     }
   };
+  // (what only bins need is worked out where it is wanted, behind volatile statements: held in registers through the sweep,
+  // it took ordinary calls 0.5 % longer)
+  auto request_bins = [&](int c, unsigned lds_addr) {
+    int at = c * BW, piece = 2 * lane;
+    asm volatile("" : "+s"(at), "+v"(piece));
+#pragma unroll 1
+    for (int i = 0; i < BW * 8 / 1024; ++i) dma16_agent(bins + at + piece + i * 128, lds_addr + i * 1024);
+  };
   if (n_chunks > 0) request_chunk(0);
-  if (tid == 0) sm.large_s[0] = sm.large_s[1] = 0;
+  if (tid == 0) sm.large_s[0] = sm.large_s[1] = sm.told_s = 0;
   f32x4 kop[TBW][NS];
   {
     const float* kbase = (const float*)p.k_layers[layer] + (long long)b * p.sb + (long long)hk * p.sh +
@@ -327,7 +359,8 @@ __device__ __forceinline__ int sattn_once_body(const ScoreParams& p, const Score
       col[tb][e] = 0.f;
     }
   f32x4 ex[H][2][TBW];                                   // exponentials: [chunk % H][16-row block][16-token block]
-  int state = kOnceDone, polls = once.polls;
+  int state = kOnceDone, binned = 0;                     // binned: this wave knows that the run's bins are in use
+  int polls = PUBLISH ? once.polls : n_chunks;
 
   // Start of step c: chunk c, the waves' sums of chunk c - 1 and the words that step c - 1 asked for are there.
   // False: a wave has met a row out of range and the block stops (what other blocks wait for before they find the same
@@ -340,21 +373,37 @@ __device__ __forceinline__ int sattn_once_body(const ScoreParams& p, const Score
     __syncthreads();
     if (__builtin_amdgcn_readfirstlane(sm.large_s[(c + 1) & 1])) return false;
     if (c + 1 < n_chunks) request_chunk(c + 1);
-    if (PUBLISH && c + 1 >= H && c < n_chunks && wave == (c & 3))
+    if (PUBLISH && c + 1 >= H && c < n_chunks && wave == (c & 3)) {
       dma16_agent(words + (c + 1 - H) * CW + 2 * lane, (unsigned)(uintptr_t)&sm.word_s[(c + 1) & 1][0][0]);
+      if (__builtin_expect(binned, 0)) request_bins(c + 1 - H, (unsigned)(uintptr_t)&sm.bin_s[(c + 1) & 1][0][0]);
+      sm.asked_s[(c + 1) & 1] = binned;
+    }
     if (PUBLISH && c >= 1 && wave == ((c + 1) & 3)) {
       const float(&s)[NW][RCH] = sm.sum_s[(c - 1) & 1];
       const int rr = lane & (RCH - 1);
-      const float units = ((s[0][rr] + s[1][rr]) + (s[2][rr] + s[3][rr])) * once.unit;
-      const float hi = truncf(units * 0x1p-32f), lo = rintf(units - hi * 0x1p32f);
-      const unsigned long long add =
-          (1ull << kOnceCountBit) + ((unsigned long long)(unsigned)hi << 32) + (unsigned)lo;
-      if (lane < RCH && row_begin + (c - 1) * RCH + lane < Rs) {
-        if (units == units)
-          __hip_atomic_fetch_add(words + (c - 1) * CW + (tile & (kOnceCopies - 1)) * RCH + lane, add, __ATOMIC_RELAXED,
-                                 __HIP_MEMORY_SCOPE_AGENT);
-        else                               // never counted: who waits for this row looks at the flag
-          __hip_atomic_store(run_large, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      const float tot = (s[0][rr] + s[1][rr]) + (s[2][rr] + s[3][rr]);
+      auto one = [](float units) {         // a tile's sum: whole units below 2^53
+        const float hi = truncf(units * 0x1p-32f), lo = units - hi * 0x1p32f;
+        return (1ull << kOnceCountBit) + ((unsigned long long)(unsigned)hi << 32) + (unsigned)lo;
+      };
+      const bool mine = lane < RCH && row_begin + (c - 1) * RCH + lane < Rs;
+      const bool plain = __float_as_uint(tot) - __float_as_uint(kOnceLow) < once.range;
+      if (mine && plain)
+        __hip_atomic_fetch_add(words + (c - 1) * CW + (tile & (kOnceCopies - 1)) * RCH + lane, one(tot * (1.f / kOnceUnit)),
+                               __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      if (__builtin_expect(__any(mine && !plain), 0)) {
+        if (mine && !plain && tot == tot) {
+          const int bin = max(__builtin_amdgcn_frexp_expf(tot) - 1 - kOnceBinLow, 0) / kOnceBinBits;
+          __hip_atomic_fetch_add(bins + (c - 1) * BW + bin * RCH + lane, one(rintf(ldexpf(tot, -once_bin_unit(bin)))),
+                                 __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+        if (!sm.told_s) flag(1);           // (one store a block: one a wave made calls of large logits 1.2 to 1.5 times as long)
+        sm.told_s = binned = 1;
+        if (__any(mine && tot != tot)) {   // never counted: who waits for this row looks at the flag
+          flag(0);
+          state = kOnceLarge;
+          sm.large_s[c & 1] = 1;
+        }
       }
     }
     return true;
@@ -363,35 +412,68 @@ __device__ __forceinline__ int sattn_once_body(const ScoreParams& p, const Score
   auto weights = [&](int c, bool asked, float (&w)[2]) {
     const int rr = lane & (RCH - 1);
     const bool real = row_begin + c * RCH + rr < Rs;
-    auto ask = [&]() {
+    unsigned count = 0;                    // tiles in the words and bins
+    float sum = 0.f;
+    auto take_words = [&](auto word_at) {
       unsigned long long word = 0;
 #pragma unroll
-      for (int k = 0; k < kOnceCopies; ++k)
-        word += __hip_atomic_load(words + c * CW + k * RCH + rr, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      return word;
+      for (int k = 0; k < kOnceCopies; ++k) word += word_at(k);
+      count = (unsigned)(word >> kOnceCountBit);
+      sum = once_units(word) * kOnceUnit;
     };
-    unsigned long long word = 0;
-    if (!PUBLISH) {
-      word = ask();
-    } else {
-      if (asked) {
-#pragma unroll
-        for (int k = 0; k < kOnceCopies; ++k) word += sm.word_s[(c + H) & 1][k][rr];
-      }
-      while (state == kOnceDone && !__all(!real || (unsigned)(word >> kOnceCountBit) == (unsigned)p.n_tile)) {
-        if (__hip_atomic_load(run_large, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) state = kOnceLarge;
-        else if (--polls < 0) state = kOnceGaveUp;
-        else word = ask();
-      }
+    auto ask_words = [&]() {
+      take_words([&](int k) {
+        return __hip_atomic_load(words + c * CW + k * RCH + rr, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      });
+    };
+    auto complete = [&]() { return __all(!real || count == (unsigned)p.n_tile); };
+    const unsigned long long(*bins_here)[RCH] = nullptr;
+    if (PUBLISH && asked) {
+      take_words([&](int k) { return sm.word_s[(c + H) & 1][k][rr]; });
+      if (sm.asked_s[(c + H) & 1]) bins_here = sm.bin_s[(c + H) & 1];
+    } else if (PUBLISH && n_chunks > 2 && c + 1 < n_chunks) {
+      ask_words();                         // added steps ago: looked at without the flags before (24.1 -> 22.7 us a call)
     }
-    const unsigned hi = (unsigned)(word >> 32) & ((1u << (kOnceCountBit - 32)) - 1);
-    const float units = fmaf((float)hi, 0x1p32f, (float)(unsigned)word);
-    if (state == kOnceDone && __any(real && units < kOnceMinUnits)) {
+    while (__builtin_expect(state == kOnceDone && !complete(), 0)) {
+      if (bins_here == nullptr) {
+        // (the flags first, in a trip of their own: asked for along with them, words were read oftener while tiles added to
+        // them, and 19320 tokens x 14 heads x 4, 7 rows, two layers took 140 us, not 130)
+        const unsigned long long f =
+            __hip_atomic_load((const unsigned long long*)run_flags, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        const unsigned large = __builtin_amdgcn_readfirstlane((unsigned)f);
+        const unsigned in_bins = __builtin_amdgcn_readfirstlane((unsigned)(f >> 32));
+        if (large || --polls < 0) {
+          state = large ? kOnceLarge : kOnceGaveUp;
+          break;
+        }
+        ask_words();
+        if (!in_bins) continue;
+        binned = 1;
+        request_bins(c, (unsigned)(uintptr_t)&sm.own_bin_s[wave][0][0]);
+        wait_vmcnt<0>();
+        bins_here = sm.own_bin_s[wave];
+      }
+      unsigned n = 0;                      // a lane of either half takes half of them
+      float part = 0.f;
+      int first = (lane / RCH) * (kOnceBins / 2), row = rr;
+      asm volatile("" : "+v"(first), "+v"(row));
+#pragma unroll
+      for (int k = 0; k < kOnceBins / 2; ++k) {
+        const int bin = first + k;
+        const unsigned long long word = bins_here[bin][row];
+        n += (unsigned)(word >> kOnceCountBit);
+        part += ldexpf(once_units(word), once_bin_unit(bin));
+      }
+      count += n + __shfl_xor(n, RCH);
+      sum += part + __shfl_xor(part, RCH);
+      bins_here = nullptr;
+    }
+    if (state == kOnceDone && __any(real && !(sum >= kOnceMin))) {
       state = kOnceLarge;
-      if (PUBLISH) __hip_atomic_store(run_large, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      if (PUBLISH) flag(0);
     }
     if (state == kOnceLarge) sm.large_s[(c + H) & 1] = 1;
-    const unsigned inv = __float_as_uint(real ? once.unit / units : 0.f);
+    const unsigned inv = __float_as_uint(real ? 1.f / sum : 0.f);
     auto a = __builtin_amdgcn_permlane16_swap(inv, inv, false, false);
     w[0] = __uint_as_float(a[0]);
     w[1] = __uint_as_float(a[1]);
@@ -434,8 +516,8 @@ __device__ __forceinline__ int sattn_once_body(const ScoreParams& p, const Score
   bool going = true;
 #pragma unroll
   for (int h = 0; h < H; ++h) {
-    if (h <= n_chunks) begin_step(h);
-    if (h < n_chunks) produce(h, ex[h]);
+    if (going && h <= n_chunks) going = begin_step(h);
+    if (going && h < n_chunks) produce(h, ex[h]);
   }
   for (int c0 = H; c0 < n_chunks + H && going; c0 += H) {
 #pragma unroll
@@ -482,7 +564,7 @@ __device__ __forceinline__ void once_block(const ScoreParams& p, unsigned blk, i
   bz = (int)(rest / (unsigned)p.n_rsplit);
 }
 
-// the words, run_large and run_arrived, which lie one behind the other
+// the words, run_flags and run_arrived, which lie one behind the other
 __global__ __launch_bounds__(256) void sattn_once_clear(u32x4* at, long long n) {
   const long long i = (long long)blockIdx.x * 256 + threadIdx.x;
   if (i < n) at[i] = (u32x4){0u, 0u, 0u, 0u};
@@ -540,7 +622,7 @@ __global__ __launch_bounds__(256, 2) void sattn_f32_redo(ScoreParams p, ScoreOnc
   int tile, hk, rs, bz;
   once_block(p, blockIdx.x, tile, hk, rs, bz);
   // (row sums too small, but not one block of the run that waited for them and said so: all wrote statistics)
-  if (once.run_large[once_run(p, hk, rs, bz)] || sattn_once_body<D, false>(p, once, sm.once, tile, hk, rs, bz) == kOnceLarge)
+  if (once.run_flags[2 * once_run(p, hk, rs, bz)] || sattn_once_body<D, false>(p, once, sm.once, tile, hk, rs, bz) == kOnceLarge)
     sattn_f32_body<D, 2>(p, sm.sweep, tile, hk, rs, bz);
 }
 
@@ -1911,9 +1993,10 @@ int score_row_splits(int dtype, long long blocks_unsplit, int rows_per_kv_head) 
 bool score_once(int dtype, long long n_vis) {
   return dtype == HIPPO_DTYPE_F32 && (n_vis + kSaF32Tile - 1) / kSaF32Tile <= kOnceMaxTiles;
 }
-size_t score_once_words(int rows_per_kv_head) {
-  return ((size_t)rows_per_kv_head + kSaF32Rows - 1) / kSaF32Rows * kSaF32Rows * kOnceCopies;
+size_t score_once_rows(int rows_per_kv_head) {
+  return ((size_t)rows_per_kv_head + kSaF32Rows - 1) / kSaF32Rows * kSaF32Rows;
 }
+const int kScoreOnceWords = kOnceCopies, kScoreOnceBins = kOnceBins;
 
 // riders: blocks of the embedding terms beside the sweep (wide: of more channels than a pass takes)
 template <int D>
@@ -2056,11 +2139,10 @@ hipError_t launch_score(const ScoreParams& p_in, const ScoreOnce& once_in, hipSt
     const int rows = p.L * p.G, chunks = (rows + unit - 1) / unit, rs = p.n_rsplit > 0 ? p.n_rsplit : 1;
     p.rows_per_split = (chunks + rs - 1) / rs * unit;
     once.row_words = chunks * unit;
-    // one sweep: units of the words (of its inverse: 2^32 over the tokens as a power of two, so that the sums of all waves
-    // at kOnceMax stay below 2^53), and how often a wave asks in all (about a microsecond each): a few times as long as
-    // the sweep of its own run of rows takes
-    once.unit = 0x1p27f;
-    for (long long n = 32; n < p.Nv; n *= 2) once.unit *= 0.5f;
+    // one sweep: how often a wave asks in all (about a microsecond each): a few times as long as the sweep of its own run of
+    // rows takes
+    once.range = 29u << 23;                // 53 bits for all tiles' sums, of 24 bits, from kOnceLow on
+    for (int n = 1; n < p.n_tile; n *= 2) once.range -= 1u << 23;
     once.polls = 64 + 16 * (p.rows_per_split / kSaF32Rows);
     p.q_step_i = 64 / p.G;
     p.q_step_g = 64 % p.G;

@@ -433,6 +433,42 @@ def test_fp32_attention_mass_in_one_sweep(hippo, n, L, H, Hkv, d, rows_out):
     assert (np.abs(got - ref) <= bound).all(), np.abs((got - ref) / bound).max()
 
 
+def logits_by_token(z, rows, d):
+    """fp32 queries [1, rows, 1, d] and keys [1, 1, n, d] of one channel: row r's logit of token t is rows[r] * z[t]"""
+    q, k = np.zeros((1, len(rows), 1, d), np.float32), np.zeros((1, 1, len(z), d), np.float32)
+    q[0, :, 0, 0], k[0, 0, :, 0] = np.sqrt(d) * np.asarray(rows), z
+    return q, k
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("n", [131, 3136, 16384, 65536])
+def test_fp32_attention_mass_of_rows_that_one_token_decides(hippo, n, d):
+    # the other tiles' sums, each a few millionths of a unit of the row's, count all the same
+    z = np.full(n, np.log(0.49 / 65536 / 128))
+    z[n // 3] = 5.5
+    q, k = logits_by_token(z, [1.0] * 40, d)
+    got, ref = attention_mass(hippo, q, k, "fp32", 1, 1, n, 0), oracle.s_attn(q, k, 0, n)
+    # a logit is rounded three times (one product, two factors), its exponential and the row's sum a few times more
+    assert (np.abs(got / ref - 1) <= (3 * np.abs(z) + 8) * 2.0 ** -24).all(), np.abs(got / ref - 1).max()
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("n, L", [(128, 3), (1290, 33), (9000, 70), (9000, 333)])
+def test_fp32_attention_mass_of_sums_of_any_size(hippo, n, L, d):
+    # whole tiles of logits from -55 to 76, in an order that has neighbours far apart; rows that see all of it, parts of it
+    # and the reverse: sums in the words, in every bin, in several at once
+    z = np.linspace(-55.0, 76.0, -(-n // 128))
+    z = np.repeat(np.random.default_rng(n).permutation(z), 128)[:n]
+    rows = np.random.default_rng(L).choice([1.0, 0.9, 0.5, 0.25, 0.1, 0.02, 0.0, -0.1, -0.6], L)
+    rows[0] = 1.0
+    q, k = logits_by_token(z, rows, d)
+    got, ref = attention_mass(hippo, q, k, "fp32", 1, 1, n, 0), oracle.s_attn(q, k, 0, n)
+    # a logit is rounded three times (one product, two factors), its exponential and the row's sum a few times more, the
+    # sum over rows once a row
+    bound = (3 * 2 * 76 + 8 + L) * 2.0 ** -24
+    np.testing.assert_allclose(got, ref, rtol=bound, atol=1e-30)
+
+
 @pytest.mark.parametrize("shift", [110.0, -110.0])
 @pytest.mark.parametrize("chunk", [0, 3, 4, 5, 8, 9])
 def test_fp32_attention_mass_where_a_long_run_meets_a_row_out_of_range(hippo, chunk, shift):
