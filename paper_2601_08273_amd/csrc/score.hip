@@ -243,7 +243,9 @@ __device__ __forceinline__ float log2_of_sum(float tot) {
 // below 2^-126 that a row of the least sum loses are 2^-24 of it).  Where any row of a run leaves it, all
 // blocks of the run find that out at the same chunk (a tile does not add such a sum, and says so in run_flags), write
 // (max, sum) of their rows as pass 1 does, and the last of them merges these; sattn_f32_redo runs pass 2 for that run.
-// RANGE_FIGURES
+//   What that costs, us a call from a graph (3136 tokens x 14 heads, 64 rows; 16384 x 28, 128; 36864 x 28, 40; 4096 x 64, 128): two
+// sweeps 31, 308, 265, 222; one, sums in the words 28, 190, 230, 128; in the bins (logits 12 nats and more off, or spread by 6 to
+// 12) 34, 209, 280, 138; out of range (100 nats off, or spread by 20 and more) 55 to 72, 407 to 465, 415 to 580, 237 to 282.
 // =================================================================================================
 constexpr int kOnceHold = 5;           // chunks between a row's exponentials and their columns
 constexpr int kOnceCopies = 4;         // words a row
