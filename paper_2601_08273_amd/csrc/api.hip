@@ -203,8 +203,10 @@ int plan_score(const hippo_kv_desc* kv, const hippo_video_desc* vid, int l_txt, 
   const size_t rows = (size_t)kv->batch * n_layers * kv->n_q_heads * l_txt;
   const size_t row_part = align_up(rows * pl->n_tile * sizeof(float), 256);
   const size_t row_lse = align_up(rows * sizeof(float), 256);
+  const int rows_per_kv_head = l_txt * (kv->n_q_heads / kv->n_kv_heads);
+  pl->once = score_once(kv->dtype, Nv, rows_per_kv_head);
   pl->n_rsplit = score_row_splits(kv->dtype, (long long)pl->n_tile * kv->n_kv_heads * kv->batch * n_layers,
-                                  l_txt * (kv->n_q_heads / kv->n_kv_heads));
+                                  rows_per_kv_head, pl->once);
   // launch limits of the sweeps (KV heads on grid x, key tiles on y, row runs x (layer, batch element) on z) and of
   // the row merge (32 rows per block)
   if (pl->n_tile > 65535 || (long long)kv->batch * n_layers * pl->n_rsplit > 65535 || kv->n_kv_heads > 65535 ||
@@ -221,10 +223,10 @@ int plan_score(const hippo_kv_desc* kv, const hippo_video_desc* vid, int l_txt, 
   o += vec;                 pl->off_ss = o;
   o += vec;
   const size_t heads = (size_t)kv->n_kv_heads * kv->batch * n_layers, runs = heads * pl->n_rsplit;
-  const size_t once_rows = heads * score_once_rows(l_txt * (kv->n_q_heads / kv->n_kv_heads)) * sizeof(unsigned long long);
+  const size_t once_rows = heads * score_once_rows(rows_per_kv_head) * sizeof(unsigned long long);
   const size_t words = once_rows * kScoreOnceWords, bins = once_rows * kScoreOnceBins;
   // (its launches are one-dimensional: a grid's threads stay below 2^32)
-  pl->once = score_once(kv->dtype, Nv) && runs * pl->n_tile < (1u << 22) && words + bins < (1ull << 34);
+  pl->once = pl->once && runs * pl->n_tile < (1u << 22) && words + bins < (1ull << 34);
   if (pl->once) {
     pl->off_word = o;       o += align_up(words, 256);
     pl->off_bin = o;        o += align_up(bins, 256);

@@ -22,8 +22,8 @@ __device__ __forceinline__ long long sattn_part_at(const ScoreParams& p, int til
 
 // =================================================================================================
 // s_attn, fp32 version (v_mfma_f32_16x16x4_f32: fp32 operands, products and sums).
-// PASS 1: row statistics; PASS 2: column sums.  Videos of up to 65536 tokens take sattn_once_body instead; the two sweeps
-// are left for longer ones, and for runs of rows whose sums it cannot hold.
+// PASS 1: row statistics; PASS 2: column sums.  Videos of up to 65536 tokens take sattn_once_body instead (score_once); the
+// two sweeps are left for longer ones, for few rows over many tokens, and for runs of rows whose sums it cannot hold.
 // Bound by the matrix unit's fp32 rate: 2 * L * H * N_v * D flops a pass against 157 TFLOP/s.  A block's four waves
 // (one per SIMD) own 32 tokens each, whose keys stay in registers as A operands, and sweep a run of the KV head's
 // query rows in chunks of 32 that travel HBM -> LDS by direct transfers, two chunks deep.  Z^T = K Q^T: contraction
@@ -1735,7 +1735,7 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 3 : 2) void emb_scores_run32(Sco
   emb_run32_block<F32, U, NW, KIND>(p, sm, blockIdx.x);
 }
 
-// fp32 beyond 65536 tokens: pass 1 and the embedding terms in one launch, the sweep's blocks first.  A wave of the sweep
+// fp32 in two sweeps: pass 1 and the embedding terms in one launch, the sweep's blocks first.  A wave of the sweep
 // per SIMD keeps the matrix unit busy, so a riding block's trips to memory cost next to nothing; in a launch of their own the crops took
 // as long as the sweep (3136 tokens: 10.5 us of pass 1 and 13 of crops, together 14.7).  Up to 168 registers a wave, 38 KB of
 // LDS: three blocks on a compute unit.
@@ -1950,19 +1950,19 @@ int score_token_tile(int dtype) { return dtype == HIPPO_DTYPE_BF16 ? kSaMfmaTile
 // blocks, two at a time, an odd last one alone.  520 unsplit blocks of 28 chunks, for example, put a third
 // block on a few units, which then start a 28-chunk sweep when all others are done (91 us against 81-83
 // with three or four runs); 256 blocks of 14 chunks are best cut in two (one round, two blocks per unit).
-int score_row_splits(int dtype, long long blocks_unsplit, int rows_per_kv_head) {
+int score_row_splits(int dtype, long long blocks_unsplit, int rows_per_kv_head, bool once) {
   int best = 1;
   if (dtype != HIPPO_DTYPE_BF16) {
     // fp32: a wave per SIMD nearly keeps the matrix unit busy, so a compute unit takes its blocks one after the other in
-    // effect, and one alone about an eighth longer than two side by side; a block's start, and in the one sweep the way of
-    // its last sums, cost about what 2.2 of its 32-row chunks do.  (us a call, in runs as chosen | one run | others: 4096
-    // tokens, 64 heads, 128 text rows 133 | 144 | 135-147; 12288 tokens, 28 heads, 64 rows 119 | 115 | 113-140; 36864
-    // tokens, 28 heads, 40 rows 228 | 228 | 248-394.)
+    // effect; a block's start costs about what 0.7 of its 32-row chunks do.  In the one sweep one block alone takes about an
+    // eighth longer than two side by side, and a start with the way of the last sums 2.2 chunks (us a call, in runs as chosen |
+    // one run | others: 4096 tokens, 64 heads, 128 text rows 133 | 144 | 135-147; 12288 tokens, 28 heads, 64 rows 119 | 115 |
+    // 113-140; 36864 tokens, 28 heads, 40 rows 228 | 228 | 248-394).
     const int chunks = (rows_per_kv_head + kSaF32Rows - 1) / kSaF32Rows;
     double best_cost = 0.0;
     for (int rs = 1; rs <= 8 && rs <= chunks; ++rs) {
       const long long rounds = (blocks_unsplit * rs + kNumCU - 1) / kNumCU;
-      const double cost = (rounds == 1 ? 1.12 : (double)rounds) * ((chunks + rs - 1) / rs + 2.2);
+      const double cost = (once && rounds == 1 ? 1.12 : (double)rounds) * ((chunks + rs - 1) / rs + (once ? 2.2 : 0.7));
       if (rs == 1 || cost < best_cost * 0.97) {
         best = rs;
         best_cost = cost;
@@ -1987,13 +1987,16 @@ int score_row_splits(int dtype, long long blocks_unsplit, int rows_per_kv_head) 
 }
 
 // Beyond kOnceMaxTiles (65536 tokens) a run's blocks would not all fit on the chip at once, and two sweeps stay.  Below, one
-// sweep was the faster everywhere, also where a run's tiles fill compute units unevenly (36864 tokens: 288 blocks wait
-// for the 32 compute units that hold two of them).  Whole calls replayed from a graph, us, two sweeps -> one: 484 tokens x
-// 4 heads, 16 text rows 24.1 -> 23.0; 936 x 14 24.9 -> 23.7; 3136 x 14, 64 rows 32.5 -> 28.7; 4096 x 64 heads, 128 rows
-// 224 -> 133; 12288 x 28, 64 rows 140 -> 119; 16384 x 28, 128 rows 307 -> 188; 36864 x 28, 40 rows 264 -> 228; 60500 x 4,
-// 64 rows 112 -> 97.  Rows out of the words' range cost the sweep up to where they are met.
-bool score_once(int dtype, long long n_vis) {
-  return dtype == HIPPO_DTYPE_F32 && (n_vis + kSaF32Tile - 1) / kSaF32Tile <= kOnceMaxTiles;
+// sweep is the faster from four chunks of rows a KV head on, also where a run's tiles fill compute units unevenly (36864 tokens:
+// 288 blocks wait for the 32 compute units that hold two of them).  Fewer chunks leave a block nothing to do while its run's
+// other tiles start, and the more of these there are the longer that takes: 88 tiles a chunk.  Whole calls replayed from a
+// graph, us, two sweeps -> one: 484 tokens x 4 heads, 16 text rows 24.1 -> 23.0; 936 x 14 24.9 -> 23.7; 3136 x 14, 64 rows 31.5
+// -> 28.4; 4096 x 64 heads, 128 rows 222 -> 128; 16384 x 28, 128 rows 308 -> 190; 36864 x 28, 40 rows 265 -> 230; 60500 x 4,
+// 64 rows 112 -> 97.  Two chunks: 173 tiles 138 -> 126, 181 99 -> 87, 213 306 -> 320, 335 136 -> 180, 435 726 -> 976; one: 54
+// 66 -> 63, 79 81 -> 79, 109 67 -> 74, 262 65 -> 77, 268 185 -> 265; three: 238 113 -> 97, 270 126 -> 141; four: 466 368 -> 328.
+bool score_once(int dtype, long long n_vis, int rows_per_kv_head) {
+  const long long tiles = (n_vis + kSaF32Tile - 1) / kSaF32Tile, chunks = (rows_per_kv_head + kSaF32Rows - 1) / kSaF32Rows;
+  return dtype == HIPPO_DTYPE_F32 && tiles <= kOnceMaxTiles && (chunks >= 4 || tiles <= 88 * chunks);
 }
 size_t score_once_rows(int rows_per_kv_head) {
   return ((size_t)rows_per_kv_head + kSaF32Rows - 1) / kSaF32Rows * kSaF32Rows;

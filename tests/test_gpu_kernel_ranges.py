@@ -469,6 +469,14 @@ def test_fp32_attention_mass_of_sums_of_any_size(hippo, n, L, d):
     np.testing.assert_allclose(got, ref, rtol=bound, atol=1e-30)
 
 
+@pytest.mark.parametrize("n, rows", [(88 * 128, 32), (88 * 128 + 1, 32), (176 * 128, 33), (176 * 128 + 1, 64), (264 * 128 + 1, 96),
+                                     (264 * 128 + 1, 97)])
+def test_fp32_attention_mass_of_few_rows_over_many_tokens(hippo, n, rows):
+    # one sweep up to 88 tiles of tokens a chunk of 32 rows, and from four chunks on; two sweeps else
+    q, k = score_inputs(rows, 1, rows, 1, 1, 64, n + 1, "fp32", 0.7)
+    assert_close(attention_mass(hippo, q, k, "fp32", 1, 1, n, 1), oracle.s_attn(q, k, 1, n), "fp32", "s_attn")
+
+
 @pytest.mark.parametrize("shift", [110.0, -110.0])
 @pytest.mark.parametrize("chunk", [0, 3, 4, 5, 8, 9])
 def test_fp32_attention_mass_where_a_long_run_meets_a_row_out_of_range(hippo, chunk, shift):
