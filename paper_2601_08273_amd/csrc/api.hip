@@ -347,11 +347,13 @@ size_t hippo_score_layers_workspace_bytes(const hippo_kv_desc* kv, const hippo_v
   return pl.bytes;
 }
 
-int hippo_score_tokens_layers(int32_t n_layers, const void* const* q_txt_layers, int32_t l_txt,
-                              const void* const* k_cache_layers, int32_t emb_layer, const hippo_kv_desc* kv,
-                              int32_t seq_len, const hippo_video_desc* vid, const void* emb, int32_t emb_dim,
-                              int64_t emb_stride_tok, uint32_t flags, float* attn_mass_inout, float* scores_out,
-                              float* components_out, void* workspace, size_t workspace_bytes, void* stream) {
+// polls: see ScoreOnce.  Not in hippo.h: it lets the tests end every wait at once, which a GPU to itself hardly ever does.
+int hippo_score_tokens_layers_polls(int32_t n_layers, const void* const* q_txt_layers, int32_t l_txt,
+                                    const void* const* k_cache_layers, int32_t emb_layer, const hippo_kv_desc* kv,
+                                    int32_t seq_len, const hippo_video_desc* vid, const void* emb, int32_t emb_dim,
+                                    int64_t emb_stride_tok, uint32_t flags, float* attn_mass_inout, float* scores_out,
+                                    float* components_out, void* workspace, size_t workspace_bytes, void* stream,
+                                    int32_t polls) {
   if (q_txt_layers == nullptr || k_cache_layers == nullptr || workspace == nullptr) return HIPPO_ERR_NULL_ARG;
   if (n_layers < 1 || n_layers > kMaxScoreLayers || emb_layer < 0 || emb_layer >= n_layers) return HIPPO_ERR_BAD_SHAPE;
   for (int l = 0; l < n_layers; ++l)
@@ -406,6 +408,7 @@ int hippo_score_tokens_layers(int32_t n_layers, const void* const* q_txt_layers,
   p.n_tile = pl.n_tile;
   p.n_rsplit = pl.n_rsplit;
   ScoreOnce once{};
+  once.polls = polls;
   if (pl.once) {
     once.row_word = reinterpret_cast<unsigned long long*>(ws + pl.off_word);
     once.row_bin = reinterpret_cast<unsigned long long*>(ws + pl.off_bin);
@@ -416,6 +419,16 @@ int hippo_score_tokens_layers(int32_t n_layers, const void* const* q_txt_layers,
   }
   const hipError_t e = launch_score(p, once, static_cast<hipStream_t>(stream));
   return e == hipSuccess ? HIPPO_OK : HIPPO_ERR_HIP;
+}
+
+int hippo_score_tokens_layers(int32_t n_layers, const void* const* q_txt_layers, int32_t l_txt,
+                              const void* const* k_cache_layers, int32_t emb_layer, const hippo_kv_desc* kv,
+                              int32_t seq_len, const hippo_video_desc* vid, const void* emb, int32_t emb_dim,
+                              int64_t emb_stride_tok, uint32_t flags, float* attn_mass_inout, float* scores_out,
+                              float* components_out, void* workspace, size_t workspace_bytes, void* stream) {
+  return hippo_score_tokens_layers_polls(n_layers, q_txt_layers, l_txt, k_cache_layers, emb_layer, kv, seq_len, vid, emb,
+                                         emb_dim, emb_stride_tok, flags, attn_mass_inout, scores_out, components_out,
+                                         workspace, workspace_bytes, stream, -1);
 }
 
 int hippo_score_tokens(const void* q_txt, int32_t l_txt, const void* k_cache, const hippo_kv_desc* kv,

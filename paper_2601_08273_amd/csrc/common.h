@@ -320,10 +320,10 @@ struct ScoreOnce {
   int* run_arrived;              // [Bz, n_rsplit, Hkv] tiles of such a run whose statistics are written
   int* tile_redo;                // [Bz, n_rsplit, Hkv, n_tile] left to the redo launch (not cleared: every block writes)
   size_t clear_bytes;            // what is cleared before the sweep, from row_word on: all but tile_redo
+  int polls;                     // how often a wave looks for sums before it no longer waits; -1: as launch_score finds right
   // filled in by launch_score
   int row_words;                 // rows of a KV head, padded to whole chunks
   unsigned range;                // of a float's bits, from kOnceLow on: what of a tile goes to row_word
-  int polls;
 };
 hipError_t launch_score(const ScoreParams& p, const ScoreOnce& once, hipStream_t st);
 int score_token_tile(int dtype);   // tokens per block in the s_attn passes

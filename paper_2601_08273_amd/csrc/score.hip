@@ -2148,7 +2148,7 @@ hipError_t launch_score(const ScoreParams& p_in, const ScoreOnce& once_in, hipSt
     // rows takes
     once.range = 29u << 23;                // 53 bits for all tiles' sums, of 24 bits, from kOnceLow on
     for (int n = 1; n < p.n_tile; n *= 2) once.range -= 1u << 23;
-    once.polls = 64 + 16 * (p.rows_per_split / kSaF32Rows);
+    if (once.polls < 0) once.polls = 64 + 16 * (p.rows_per_split / kSaF32Rows);
     p.q_step_i = 64 / p.G;
     p.q_step_g = 64 % p.G;
     p.q_last_i = (rows - 1) / p.G;
