@@ -2167,12 +2167,21 @@ hipError_t launch_score(const ScoreParams& p_in, const ScoreOnce& once_in, hipSt
   const int de = p.emb ? p.emb_dim : p.Hkv * p.D;
   const bool small_crops = p.ch * p.cw <= 32;
   const bool wide = de > (bf16 ? 512 : 256);
+  const long long n_sattn = (long long)p.n_tile * p.Hkv * p.n_rsplit * p.Bz, all_crops = crops_per_frame * p.F * p.B;
   {
-    const long long run = crops_per_frame * p.F * p.B / kNumCU;
+    long long run = all_crops / kNumCU;
+    // Beside the one sweep two blocks fit a compute unit, not three: the shortest run that leaves room for all of them, if it is
+    // not far longer.  us a call from a graph, two sweeps | a second round of riders | this: 4752 tokens x 4 heads x 3, 31 rows
+    // (run 1 to 2) 32.3 | 35.7 | 28.6; 5808 x 4 x 3, 42 rows (1 to 2) 32.4 | 35.2 | 30.6; 8400 x 4 x 2, 62 rows (2 to 3) 46.5 |
+    // 45.2 | 33.4; 19844 x 4, 47 rows (4 to 7) 51.8 | 50.4 | 41.9; longer still 52 -> 58 (4 to 8 of 9 that fit), 39.5 -> 40.5 (2 to 7).
+    const long long room = 2 * kNumCU - n_sattn;
+    if (once.row_word != nullptr && !wide && room > 0) {
+      const long long fits = (all_crops + room - 1) / room;
+      if (fits > run && fits <= std::min<long long>(8, 2 * std::max<long long>(1, run) + 2)) run = fits;
+    }
     p.emb_run = (int)std::max<long long>(1, std::min<long long>(std::min<long long>(8, p.F), run));
   }
   long long n_riders = crops_per_frame * ((p.F + p.emb_run - 1) / p.emb_run) * p.B;
-  const long long n_sattn = (long long)p.n_tile * p.Hkv * p.n_rsplit * p.Bz;
   const bool emb_rides = want_emb && !accumulate_only && (p.flags & HIPPO_SCORE_ATTN) && small_crops &&
                          n_sattn + n_riders < (once.row_word != nullptr ? 1ll << 23 : 1ll << 31) &&
                          (bf16 || !wide || wide_f32_rides(p, n_sattn, n_riders, de));
