@@ -254,9 +254,10 @@ def hippo_score_tokens(q_txt, k_cache, vid: VideoDesc, emb=None, flags: int = SC
     lib = load()
     assert q_txt.is_contiguous() and q_txt.dim() == 4
     B, L, H, d = q_txt.shape
-    kv = kv_desc(k_cache, H)
+    shape = k_cache.shape
+    kv = _kv_desc(k_cache, shape, k_cache.stride(), H)
     n_vis = vid.n_frames * vid.grid_h * vid.grid_w
-    ws = _workspace(lambda: workspace_bytes(CALL_SCORE_TOKENS, kv, vid, L, k_cache.shape[2]), q_txt.device, workspace)
+    ws = _workspace(lambda: workspace_bytes(CALL_SCORE_TOKENS, kv, vid, L, shape[2]), q_txt.device, workspace)
     acc_only = bool(flags & SCORE_ACCUMULATE_ONLY)
     scores = scores_out
     if scores is None and not acc_only:
@@ -265,9 +266,9 @@ def hippo_score_tokens(q_txt, k_cache, vid: VideoDesc, emb=None, flags: int = SC
     emb_dim, emb_stride = (0, 0) if emb is None else (emb.shape[2], emb.stride(1))
     if emb is not None:
         assert emb.dim() == 3 and emb.stride(2) == 1 and emb.stride(0) == emb.shape[1] * emb.stride(1)
-    st = lib.hippo_score_tokens(_ptr(q_txt), L, _ptr(k_cache), C.byref(kv), k_cache.shape[2], C.byref(vid),
+    st = lib.hippo_score_tokens(q_txt.data_ptr(), L, k_cache.data_ptr(), C.byref(kv), shape[2], C.byref(vid),
                                 _ptr(emb), emb_dim, emb_stride, flags, _ptr(attn_mass_inout), _ptr(scores),
-                                _ptr(comps), _ptr(ws), ws.numel(), _stream(stream))
+                                _ptr(comps), ws.data_ptr(), ws.numel(), _stream(stream))
     _check(st, "hippo_score_tokens")
     return (scores, comps) if want_components else scores
 
@@ -284,9 +285,10 @@ def hippo_score_tokens_layers(q_txt_layers, k_cache_layers, vid: VideoDesc, emb_
     assert n_layers == len(k_cache_layers) and n_layers >= 1
     q0, k0 = q_txt_layers[0], k_cache_layers[0]
     B, L, H, d = q0.shape
+    shape, strides = k0.shape, k0.stride()
     for q, k in zip(q_txt_layers, k_cache_layers):
-        assert q.is_contiguous() and q.shape == q0.shape and k.shape == k0.shape and k.stride() == k0.stride()
-    kv = kv_desc(k0, H)
+        assert q.is_contiguous() and q.shape == q0.shape and k.shape == shape and k.stride() == strides
+    kv = _kv_desc(k0, shape, strides, H)
     n_vis = vid.n_frames * vid.grid_h * vid.grid_w
     ws = _workspace(lambda: int(lib.hippo_score_layers_workspace_bytes(C.byref(kv), C.byref(vid), L, n_layers)),
                     q0.device, workspace)
@@ -299,7 +301,7 @@ def hippo_score_tokens_layers(q_txt_layers, k_cache_layers, vid: VideoDesc, emb_
     qs = (C.c_void_p * n_layers)(*[q.data_ptr() for q in q_txt_layers])
     ks = (C.c_void_p * n_layers)(*[k.data_ptr() for k in k_cache_layers])
     st = lib.hippo_score_tokens_layers(n_layers, C.cast(qs, C.c_void_p), L, C.cast(ks, C.c_void_p), emb_layer,
-                                       C.byref(kv), k0.shape[2], C.byref(vid), _ptr(emb), emb_dim, emb_stride, flags,
+                                       C.byref(kv), shape[2], C.byref(vid), _ptr(emb), emb_dim, emb_stride, flags,
                                        _ptr(attn_mass_inout), _ptr(scores), _ptr(comps), _ptr(ws), ws.numel(),
                                        _stream(stream))
     _check(st, "hippo_score_tokens_layers")
