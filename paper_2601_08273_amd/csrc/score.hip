@@ -1756,8 +1756,8 @@ __global__ __launch_bounds__(256, 3) void sattn_f32_pass1_with_emb(ScoreParams p
   emb_run32_block<true, 4, 4, WIDE ? kRefetch : kOnePass>(p, sm.run, (unsigned)(blk - n_sattn));
 }
 
-// The same beside the one sweep (3136 tokens: 15.8 us; 936 tokens, whole calls, beside a sweep 30.6 -> 22.2, 3 x 7220 tokens in
-// two layers 130 -> 105).  Five chunks of exponentials take up to 245 registers: two blocks on a compute unit.
+// The same beside the one sweep (3136 tokens: 15.4 us; 936 tokens, whole calls, beside a sweep 30.6 -> 22.2, 3 x 7220 tokens in
+// two layers 130 -> 105).  Five chunks of exponentials take up to 254 registers: two blocks on a compute unit.
 template <int D, bool WIDE>
 __global__ __launch_bounds__(256, 2) void sattn_once_with_emb(ScoreParams p, ScoreOnce once, int n_sattn) {
   union Smem {
@@ -1775,7 +1775,7 @@ __global__ __launch_bounds__(256, 2) void sattn_once_with_emb(ScoreParams p, Sco
 // fill the third block slot of the compute units, so the memory-bound embedding work hides under the
 // sweep instead of following it.  Three blocks fit a compute unit: 8 waves of at most 80 registers
 // each and the larger of the shared-memory layouts.  A riding block owns one crop position over a run of frames.
-// Riders of two strips (kRefetch2, kHold: 117 and 99 registers, 70 KB of LDS) leave two blocks on a compute unit; n_lead of them
+// Riders of two strips (kRefetch2, kHold: up to 99 registers, 70 KB of LDS) leave two blocks on a compute unit; n_lead of them
 // stand in front of the n_sattn blocks of the sweep.  wide_bf16_riders says which take which.
 template <int D, int KIND>
 __global__ __launch_bounds__(kSaWaves * 64, emb_strips(KIND) == 2 ? 4 : 6)
