@@ -408,14 +408,15 @@ def test_attention_mass_where_some_rows_leave_the_exponent_range(hippo, first, l
 @pytest.mark.parametrize("d", [64, 128])
 @pytest.mark.parametrize("n, L, H, Hkv", [
     # tiles of 128 tokens: one with idle waves, whole ones, one token more; chunks of 32 query rows: one row, one chunk, as many
-    # as stay in registers (5), one more, several runs; the most tiles that take one sweep, and one token more
+    # as stay in registers (5), one more, several runs; the most tiles that take one sweep, and one token more, of few rows
+    # (two sweeps) and of as many as take one
     (97, 1, 1, 1), (128, 8, 4, 1), (129, 23, 14, 2), (1408, 40, 4, 1), (257, 41, 4, 1), (3000, 91, 14, 2),
-    (65536, 3, 2, 1), (65537, 3, 2, 1),
+    (65536, 3, 2, 1), (65537, 3, 2, 1), (65536, 98, 1, 1), (65537, 98, 1, 1),
 ])
 @pytest.mark.parametrize("rows_out", [None, (0, 1, 60.0), (-1, None, 60.0), (0, 1, -30.0), (0, None, 60.0)])
 def test_fp32_attention_mass_in_one_sweep(hippo, n, L, H, Hkv, d, rows_out):
-    # logits of a few units, and text rows (the first, the last, all) whose exponentials leave the range of the sums that
-    # the blocks exchange, upwards or downwards
+    # logits of a few units, and text rows (the first, the last, all) whose tiles' sums leave the words that the blocks
+    # exchange for the bins, upwards or downwards
     if rows_out is not None and n > 4000:
         rows_out = rows_out[:2] + (rows_out[2] / 2,)
     q, k = score_inputs(n + L, 2 if n < 200 else 1, L, H, Hkv, d, n + 5, "fp32", 0.7)
@@ -446,10 +447,11 @@ def test_fp32_attention_mass_of_rows_that_one_token_decides(hippo, n, d):
     # the other tiles' sums, each a few millionths of a unit of the row's, count all the same
     z = np.full(n, np.log(0.49 / 65536 / 128))
     z[n // 3] = 5.5
-    q, k = logits_by_token(z, [1.0] * 40, d)
+    q, k = logits_by_token(z, [1.0] * 98, d)           # (four chunks of rows: one sweep at all these sizes)
     got, ref = attention_mass(hippo, q, k, "fp32", 1, 1, n, 0), oracle.s_attn(q, k, 0, n)
-    # a logit is rounded three times (one product, two factors), its exponential and the row's sum a few times more
-    assert (np.abs(got / ref - 1) <= (3 * np.abs(z) + 8) * 2.0 ** -24).all(), np.abs(got / ref - 1).max()
+    # a logit is rounded three times (one product, two factors), its exponential and the row's sum a few times more, the sum
+    # over the rows, all alike, once a row, by half a unit of what is there so far
+    assert (np.abs(got / ref - 1) <= (3 * np.abs(z) + 8 + 98 / 2) * 2.0 ** -24).all(), np.abs(got / ref - 1).max()
 
 
 @pytest.mark.parametrize("d", [64, 128])

@@ -67,7 +67,7 @@ def test_no_result_depends_on_a_wait(hippo, rows_out, shift, d):
 
 @pytest.mark.parametrize("F, L, H, Hkv, d", [(16, 32, 14, 2, 64), (160, 40, 4, 1, 64), (144, 20, 28, 4, 128)])
 def test_two_calls_share_the_gpu(hippo, F, L, H, Hkv, d):
-    # 29, 280 and 252 tiles a run: neither call's blocks are all there at once
+    # 28, 280 and 252 tiles a run: both calls' blocks fit on the chip, one run of theirs or the other's, or two
     vid, n = hippo.video_desc(F, 14, 16, 1), F * 14 * 16
     data = [inputs(s, 1, 1, L, H, Hkv, d, n + 1) for s in (1, 2)]
     data = [(dev(q[0], "fp32"), dev(k[0], "fp32")) for q, k in data]
