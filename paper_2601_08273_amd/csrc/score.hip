@@ -240,9 +240,10 @@ __device__ __forceinline__ float log2_of_sum(float tot) {
 // longer waits: its block says so in tile_redo and sattn_f32_redo sweeps that tile again, with all sums known, the same
 // operations in the same order.  So every wait ends, and no result depends on a wait, whatever else the GPU runs.
 //   Range: a wave's sums up to kOnceMax and row sums from kOnceMin on (logits within some 60 to 80 nats; the exponentials
-// below 2^-126 that a row of the least sum loses are 2^-24 of it).  Where any row of a run leaves it, all
-// blocks of the run find that out at the same chunk (a tile does not add such a sum, and says so in run_flags), write
-// (max, sum) of their rows as pass 1 does, and the last of them merges these; sattn_f32_redo runs pass 2 for that run.
+// below 2^-126 that a row of the least sum loses are 2^-24 of it).  Where any row of a run leaves it, all blocks of the run stop
+// (a tile does not add such a sum, says so in run_flags and leaves at the next step; the others at that chunk, whose tiles are
+// never all counted), write (max, sum) of their rows as pass 1 does, and the last of them merges these; sattn_f32_redo runs pass 2
+// for that run.
 //   What that costs, us a call from a graph (3136 tokens x 14 heads, 64 rows; 16384 x 28, 128; 36864 x 28, 40; 4096 x 64, 128): two
 // sweeps 31, 308, 265, 222; one, sums in the words 28, 190, 230, 128; in the bins (logits 12 nats and more off, or spread by 6 to
 // 12) 34, 209, 280, 138; out of range (100 nats off, or spread by 20 and more) 55 to 72, 407 to 465, 415 to 580, 237 to 282.
@@ -2042,14 +2043,15 @@ static hipError_t launch_sattn_f32(const ScoreParams& p, hipStream_t st, long lo
 // The two-strip ones take a third of the compute units' block slots from the launch; what longer takes (a rider, by its
 // frames and passes, or a block of the sweep, by its chunks of 64 rows) goes first.  us a call from a graph, one strip | two
 // strips in front | two strips behind:
-//   two passes, held: 3 x 10692 tokens, 64 heads, 15 text rows 75 | 61 | 68; 27830 x 14 heads x 2, 36 rows 81 | 57 | 61; 3 x 3822 x 64, 95
-//     rows 68 | 72 | 66; 2 x 45356 x 14, 171 rows 161 | 148 | 141.  Only a sweep of many times the riders' work is the better one
-//     with three slots: 4 x 1452 x 64 in four layers, 239 rows 218 | 228 | 223; 2640 x 64 in four, 201 rows 105 | 112 | 108
-//     (at 14 times; nearer than that within 2.5 % either way).
+//   two passes, held: 3 x 10692 tokens, 64 heads, 15 text rows 75 | 61 | 68; 27830 x 14 heads x 2, 36 rows 81 | 57 | 61; 3 x
+//     3822 x 64, 95 rows 68 | 72 | 66; 2 x 45356 x 14, 171 rows 161 | 148 | 141.  Only a sweep of many times the riders' work is
+//     the better one with three slots: 4 x 1452 x 64 in four layers, 239 rows 218 | 228 | 223; 2640 x 64 in four, 201 rows 105 |
+//     112 | 108 (at 14 times; nearer than that within 2.5 % either way).
 //   more passes, fetched again: two strips gain as long as the riders go first and the sweep fills the chip (3 x 15312 x 64
-//     heads, 76 rows, 3584 channels 297 | 248 | 294; 15750 x 14 x 2 in four layers, 37 rows, 2048 channels 109 | 96 | 113), or where all
-//     blocks fit two a compute unit and there is a compute unit for each rider (1785 x 64, 178 rows, 2048 channels 46 | 42 | 46); else one
-//     strip (3 x 4056 x 64 in two layers, 105 rows, 1536 channels 130 | 140 | 136; 3726 x 64, 254 rows 61 | 65 | 64).
+//     heads, 76 rows, 3584 channels 297 | 248 | 294; 15750 x 14 x 2 in four layers, 37 rows, 2048 channels 109 | 96 | 113), or
+//     where all blocks fit two a compute unit and there is a compute unit for each rider (1785 x 64, 178 rows, 2048 channels 46 |
+//     42 | 46); else one strip (3 x 4056 x 64 in two layers, 105 rows, 1536 channels 130 | 140 | 136; 3726 x 64, 254 rows 61 | 65 |
+//     64).
 struct Riders {
   int kind;
   long long lead;
