@@ -656,12 +656,13 @@ int hippo_draft_attention_fp8kv(const void* q, int32_t q_len, const void* k_code
 
 size_t hippo_quantize_kv_workspace_bytes(const hippo_kv_desc* src, int32_t n_rows) {
   if (check_kv(src) != HIPPO_OK || n_rows < 1) return 0;
-  return align_up((size_t)src->batch * src->n_kv_heads * 2 * quant_slices(n_rows, src->head_dim) * sizeof(float), 256);
+  return align_up((size_t)src->batch * src->n_kv_heads * 2 * align_up(quant_slices(n_rows, src->head_dim), 4) * sizeof(float), 256);
 }
 
-int hippo_quantize_kv_e4m3(const void* k_src, const void* v_src, const hippo_kv_desc* src, int32_t n_rows,
-                           void* k_codes, void* v_codes, const hippo_kv_desc* dst, float* k_scale, float* v_scale,
-                           void* workspace, size_t workspace_bytes, void* stream) {
+// polls: see QuantParams.  Not in hippo.h: it lets the tests end every wait at once.
+int hippo_quantize_kv_e4m3_polls(const void* k_src, const void* v_src, const hippo_kv_desc* src, int32_t n_rows,
+                                 void* k_codes, void* v_codes, const hippo_kv_desc* dst, float* k_scale, float* v_scale,
+                                 void* workspace, size_t workspace_bytes, void* stream, int32_t polls) {
   if (k_src == nullptr || v_src == nullptr || k_codes == nullptr || v_codes == nullptr || k_scale == nullptr ||
       v_scale == nullptr || workspace == nullptr)
     return HIPPO_ERR_NULL_ARG;
@@ -684,8 +685,16 @@ int hippo_quantize_kv_e4m3(const void* k_src, const void* v_src, const hippo_kv_
   p.n_slices = quant_slices(n_rows, src->head_dim); p.src_dtype = src->dtype;
   p.ssb = src->stride_b; p.ssh = src->stride_h; p.ssn = src->stride_n;
   p.dsb = dst->stride_b; p.dsh = dst->stride_h; p.dsn = dst->stride_n;
+  p.polls = polls;
   const hipError_t e = launch_quantize(p, static_cast<hipStream_t>(stream));
   return e == hipSuccess ? HIPPO_OK : HIPPO_ERR_HIP;
+}
+
+int hippo_quantize_kv_e4m3(const void* k_src, const void* v_src, const hippo_kv_desc* src, int32_t n_rows,
+                           void* k_codes, void* v_codes, const hippo_kv_desc* dst, float* k_scale, float* v_scale,
+                           void* workspace, size_t workspace_bytes, void* stream) {
+  return hippo_quantize_kv_e4m3_polls(k_src, v_src, src, n_rows, k_codes, v_codes, dst, k_scale, v_scale, workspace,
+                                      workspace_bytes, stream, -1);
 }
 
 }  // extern "C"

@@ -3,21 +3,21 @@
 // (batch element, KV head) and tensor.
 //   multiplier = max|x| / 448 over the head's rows (1 when the maximum is 0)
 //   code       = the E4M3 value nearest to x / multiplier, ties to the even code
-// Two launches: every block reduces |x| over its slice of a head's rows; then every block reduces
-// the (few) slice maxima of its head again, encodes its slice and slice 0 stores the multiplier.
-// No atomics, no ordering between blocks: the result is deterministic.
-// Bound by HBM: the source twice, the codes once.  The second launch walks the slices backwards, so that it begins
-// with what the last-level cache still holds of the first, and stores its codes non-temporally, so that they do not
-// push the rest out.  Codes by a product and exact corrections instead of divisions, 16 source bytes per lane next to
-// its neighbour's (not 32 for 16 codes), eight loads in flight.  Quantisation and a verification call over the codes,
-// us: 4 x 8 heads x 37K rows x 128 342 -> 318 (encoding 189 -> 146: 6.2 TB/s), 2 x 4 heads x 71K 177 -> 160, 3 x 8 heads x
-// 21K 156 -> 133; forward order with plain stores 322, 176 and 144.  Groups of heads small enough for the 256 MB cache,
-// encoded beside the maxima of the next group, were slower: 337-362 at 48 to 200 MB a group.
+// No atomics, and no result depends on an order between blocks: deterministic.
+// Bound by HBM: codes by a product and exact corrections instead of divisions, 16 source bytes per lane next to its
+// neighbour's (not 32 for 16 codes).  Large sources are read once (kv_quantize_once below).  Small ones, and heads of more than
+// 32 MB, take two launches: every block reduces |x| over its slice of a head's rows; then every block reduces the (few)
+// slice maxima of its head again, encodes its slice and slice 0 stores the multiplier.  The second launch walks the slices
+// backwards, so that it begins with what the last-level cache still holds of the first, and stores its codes
+// non-temporally, so that they do not push the rest out; eight loads in flight.  Quantisation and a verification call over
+// the codes, us, two launches -> one sweep: 4 x 8 heads x 37K rows x 128 316 -> 234, 2 x 4 heads x 71K 153 -> 137, 3 x 8
+// heads x 21K 131 -> 109.
 #include "common.h"
 
 namespace hippo {
 
 constexpr int kQuantThreads = 256;
+constexpr int kQuantMaxSlices = 256;       // of a head: one a thread where the head's maximum is put together
 
 // 16-byte source vectors per row and elements per vector, for T = float or bf16 bits
 template <typename T>
@@ -69,24 +69,29 @@ __device__ __forceinline__ float* quant_partials(const QuantParams& p, const Qua
 
 constexpr int kQuantInFlight = 8;   // source vectors in flight per thread
 
-template <typename T>
-__global__ __launch_bounds__(kQuantThreads) void kv_absmax(QuantParams p) {
-  __shared__ float red[4];
+// max|x| over this thread's vectors of a slice
+template <typename T, int THREADS>
+__device__ __forceinline__ float slice_absmax(const T* src, const QuantParams& p, const QuantSlice& q) {
   constexpr int PV = Elem<T>::kPerVec, N = kQuantInFlight;
-  const QuantSlice q = quant_slice<T>(p, blockIdx.x, blockIdx.y, blockIdx.z);
-  const T* src = quant_src<T>(p, q);
   float m = 0.f;
-  for (long long e0 = q.lo + threadIdx.x; e0 < q.hi; e0 += N * kQuantThreads) {
+  for (long long e0 = q.lo + threadIdx.x; e0 < q.hi; e0 += N * THREADS) {
     u32x4 v[N];
 #pragma unroll
     for (int u = 0; u < N; ++u) {
-      const long long e = min(e0 + u * kQuantThreads, q.hi - 1);     // past the slice: a repeat, which changes no maximum
+      const long long e = min(e0 + u * THREADS, q.hi - 1);             // past the slice: a repeat, which changes no maximum
       v[u] = *(const u32x4*)(src + (e >> q.vshift) * p.ssn + ((int)e & q.vmask) * PV);
     }
 #pragma unroll
     for (int u = 0; u < N; ++u) m = fmaxf(m, vec_absmax<T>(v[u]));
   }
-  m = block_max_256(m, red);
+  return m;
+}
+
+template <typename T>
+__global__ __launch_bounds__(kQuantThreads) void kv_absmax(QuantParams p) {
+  __shared__ float red[4];
+  const QuantSlice q = quant_slice<T>(p, blockIdx.x, blockIdx.y, blockIdx.z);
+  const float m = block_max_256(slice_absmax<T, kQuantThreads>(quant_src<T>(p, q), p, q), red);
   if (threadIdx.x == 0) quant_partials(p, q)[blockIdx.x] = m;
 }
 
@@ -108,6 +113,30 @@ __device__ __forceinline__ float quotient(float x, float mult, float r) {
   return __builtin_copysignf(fmaf(fmaf(n, mult, x), r, -n), x);
 }
 
+// the codes of one source vector, and their store past the caches
+template <typename T> struct VecCodes { unsigned w[Elem<T>::kPerVec / 4]; };
+template <typename T, bool EXACT_DIV>
+__device__ __forceinline__ VecCodes<T> encode_vec(const u32x4& raw, float mult, float r) {
+  constexpr int PV = Elem<T>::kPerVec;
+  float x[PV];
+  Elem<T>::unpack(raw, x);
+#pragma unroll
+  for (int i = 0; i < PV; ++i) x[i] = EXACT_DIV ? x[i] / mult : quotient<T>(x[i], mult, r);
+  VecCodes<T> c;
+#pragma unroll
+  for (int i = 0; i < PV / 4; ++i) c.w[i] = encode2(x[4 * i], x[4 * i + 1]) | (encode2(x[4 * i + 2], x[4 * i + 3]) << 16);
+  return c;
+}
+template <typename T>
+__device__ __forceinline__ void store_codes(unsigned char* at, const VecCodes<T>& c) {
+  if constexpr (Elem<T>::kPerVec == 8) {
+    const unsigned long long v = (unsigned long long)c.w[0] | (unsigned long long)c.w[1] << 32;
+    __builtin_nontemporal_store(v, (unsigned long long*)at);
+  } else {
+    __builtin_nontemporal_store(c.w[0], (unsigned*)at);
+  }
+}
+
 template <typename T, bool EXACT_DIV>
 __device__ __forceinline__ void encode_vectors(const QuantParams& p, const QuantSlice& q, float mult) {
   constexpr int PV = Elem<T>::kPerVec, N = kQuantInFlight;
@@ -125,18 +154,7 @@ __device__ __forceinline__ void encode_vectors(const QuantParams& p, const Quant
     for (int u = 0; u < N; ++u) {
       const long long e = e0 + u * kQuantThreads;
       if (e >= q.hi) break;
-      float x[PV];
-      Elem<T>::unpack(raw[u], x);
-#pragma unroll
-      for (int i = 0; i < PV; ++i) x[i] = EXACT_DIV ? x[i] / mult : quotient<T>(x[i], mult, r);
-      unsigned w[PV / 4];
-#pragma unroll
-      for (int i = 0; i < PV / 4; ++i) w[i] = encode2(x[4 * i], x[4 * i + 1]) | (encode2(x[4 * i + 2], x[4 * i + 3]) << 16);
-      unsigned char* at = dst + (e >> q.vshift) * p.dsn + ((int)e & q.vmask) * PV;
-      if constexpr (PV == 8)
-        __builtin_nontemporal_store((unsigned long long)w[0] | (unsigned long long)w[1] << 32, (unsigned long long*)at);
-      else
-        __builtin_nontemporal_store(w[0], (unsigned*)at);
+      store_codes<T>(dst + (e >> q.vshift) * p.dsn + ((int)e & q.vmask) * PV, encode_vec<T, EXACT_DIV>(raw[u], mult, r));
     }
   }
 }
@@ -154,24 +172,179 @@ __global__ __launch_bounds__(kQuantThreads) void kv_encode(QuantParams p) {
   else encode_vectors<T, true>(p, q, mult);
 }
 
+// ---- the slice stays in registers ----------------------------------------------------------------
+// A block fetches its slice once, publishes the slice's maximum and encodes from its registers when all maxima of its
+// head are there, so the source crosses the memory bus once instead of twice.  A word holds a slice's maximum and is its own
+// flag: a launch in front sets it to kQuantUnset, which no maximum's bits are, one relaxed device-scope store fills it,
+// and the first wave of every block of the head looks at all of them with one load instruction.
+// A head's slices stand together in the launch order and are at most half of what the chip holds, so they run beside each
+// other while the next heads' slices load.  No result depends on a wait: a wave that has looked `polls` times in vain
+// leaves the missing slices to its block, which takes their maxima from the source itself.
+// What bounds it: HBM, and how many looks the words' memory channels serve; every look of a head goes to the same few
+// lines.  4 x 8 heads x 37K rows x 128 (608 MB in, 304 out), us: two launches that read the source twice 254; here without
+// any wait 163 (wrong, but the floor), slices of 64 KB whose threads look at a word each every half microsecond 253, whose
+// first wave looks for all 218, every two microseconds 202, slices of 128 KB 175 (5.2 TB/s), of 256 KB in one block a
+// compute unit 205; 24 vectors a thread and three waves a SIMD 177; one word and one counter a head by atomics 410.
+constexpr unsigned kQuantUnset = 0xffffffffu;
+constexpr int kQuantHeld = 16;               // source vectors held per thread (64 registers: four waves a SIMD)
+constexpr int kQuantOnceThreads = 512;       // two blocks of 128 KB a compute unit
+
+// words of a head: whole vectors of four
+__host__ __device__ constexpr int quant_words(int n_slices) { return (n_slices + 3) / 4 * 4; }
+
+__global__ __launch_bounds__(kQuantThreads) void quant_clear(unsigned* words, int n) {
+  const int i = blockIdx.x * kQuantThreads + threadIdx.x;
+  if (i < n) words[i] = kQuantUnset;
+}
+
+template <int THREADS>
+__device__ __forceinline__ float block_max(float v, float* red) {
+  v = wave_max(v);
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
+  __syncthreads();
+  float m = red[0];
+#pragma unroll
+  for (int w = 1; w < THREADS / 64; ++w) m = fmaxf(m, red[w]);
+  return m;
+}
+
+// A thread's vectors lie THREADS apart: a whole number of rows, so one address and a step reach them all.
+template <typename T, bool EXACT_DIV>
+__device__ __forceinline__ void encode_held(unsigned char* dst, long long step, int count, const u32x4 (&raw)[kQuantHeld],
+                                            float mult) {
+  const float r = 1.0f / mult;
+#pragma unroll
+  for (int u = 0; u < kQuantHeld; ++u) {
+    if (u < count) store_codes<T>(dst, encode_vec<T, EXACT_DIV>(raw[u], mult, r));
+    dst += step;
+  }
+}
+
+// The maxima of a head's slices, four a lane (0 where there is none).  Bit i of the result: this lane's word i is missing.
+__device__ __forceinline__ unsigned look_for_maxima(const unsigned* words, int n_slices, int polls, float& m) {
+  const int lane = threadIdx.x & 63, at = 4 * lane;
+  u32x4 w = {kQuantUnset, kQuantUnset, kQuantUnset, kQuantUnset};
+  unsigned missing = 0;
+  for (;;) {
+    missing = 0;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) missing |= (w[i] == kQuantUnset && at + i < n_slices ? 1u : 0u) << i;
+    if (polls-- <= 0 || !__any(missing != 0)) break;
+    // (lanes beyond the last word look at the first ones; a line of words is whole lanes' worth)
+    asm volatile("global_load_dwordx4 %0, %1, off sc1\n\ts_waitcnt vmcnt(0)"
+                 : "=&v"(w) : "v"(words + (at < n_slices ? at : 0)) : "memory");
+    bool there = true;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) there &= w[i] != kQuantUnset || at + i >= n_slices;
+    if (!__all(there) && polls > 0) __builtin_amdgcn_s_sleep(64);       // 4096 clocks
+  }
+  m = 0.f;
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+    if (at + i < n_slices && w[i] != kQuantUnset) m = fmaxf(m, __uint_as_float(w[i]));
+  return missing;
+}
+
+template <typename T, bool PAST>
+__global__ __launch_bounds__(kQuantOnceThreads, 4) void kv_quantize_once(QuantParams p) {
+  __shared__ float red[2][kQuantOnceThreads / 64];
+  __shared__ unsigned char missing[64];
+  constexpr int PV = Elem<T>::kPerVec, N = kQuantHeld, THREADS = kQuantOnceThreads;
+  const int tid = threadIdx.x;
+  const QuantSlice q = quant_slice<T>(p, blockIdx.x, blockIdx.y, blockIdx.z);
+  const T* src = quant_src<T>(p, q);
+  const long long e0 = q.lo + tid;
+  const int count = e0 < q.hi ? (int)((q.hi - e0 + THREADS - 1) / THREADS) : 0;     // this thread's vectors, at most N
+  u32x4 raw[N];
+  {
+    const long long e = min(e0, q.hi - 1);
+    const T* at = src + (e >> q.vshift) * p.ssn + ((int)e & q.vmask) * PV;
+    const long long step = (long long)(THREADS >> q.vshift) * p.ssn;
+#pragma unroll
+    for (int u = 0; u < N; ++u) {                                       // past the slice: a repeat, not stored
+      raw[u] = PAST ? __builtin_nontemporal_load((const u32x4*)at) : *(const u32x4*)at;
+      if (u + 1 < count) at += step;
+    }
+  }
+  float m = 0.f;
+#pragma unroll
+  for (int u = 0; u < N; ++u) m = fmaxf(m, vec_absmax<T>(raw[u]));
+#pragma unroll
+  for (int u = 0; u < N; ++u) asm volatile("" : "+v"(raw[u]));          // held as they came, not unpacked
+  m = block_max<THREADS>(m, red[0]);
+  if (p.n_slices > 1) {
+    unsigned* words = (unsigned*)p.partial + ((long long)(q.b * p.Hkv + q.hk) * 2 + q.which) * quant_words(p.n_slices);
+    if (tid < 64) {
+      if (tid == 0) __hip_atomic_store(words + blockIdx.x, __float_as_uint(m), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      float others;
+      missing[tid] = (unsigned char)look_for_maxima(words, p.n_slices, p.polls, others);
+      others = wave_max(others);
+      if (tid == 0) red[1][0] = others;
+    }
+    __syncthreads();
+    m = fmaxf(m, red[1][0]);
+    if (__any(missing[tid & 63] != 0)) {                                // the same in every wave
+      float rest = 0.f;
+      for (int s = 0; s < p.n_slices; ++s)
+        if (missing[s >> 2] >> (s & 3) & 1) {
+          const float here = slice_absmax<T, THREADS>(src, p, quant_slice<T>(p, s, blockIdx.y, blockIdx.z));
+          // (published by now: its block may be writing codes, and a caller may have put them where the source is)
+          const unsigned w = __hip_atomic_load(words + s, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          rest = fmaxf(rest, w != kQuantUnset ? __uint_as_float(w) : here);
+        }
+      m = fmaxf(m, block_max<THREADS>(rest, red[0]));
+    }
+  }
+  const float mult = m > 0.f ? m / 448.0f : 1.0f;
+  if (blockIdx.x == 0 && tid == 0) (q.which ? p.v_scale : p.k_scale)[q.b * p.Hkv + q.hk] = mult;
+  unsigned char* dst = (unsigned char*)(q.which ? p.v_dst : p.k_dst) + (long long)q.b * p.dsb + (long long)q.hk * p.dsh +
+                       (e0 >> q.vshift) * p.dsn + ((int)e0 & q.vmask) * PV;
+  const long long step = (long long)(THREADS >> q.vshift) * p.dsn;
+  if (mult >= 0x1p-80f && mult <= 0x1p80f) encode_held<T, false>(dst, step, count, raw, mult);
+  else encode_held<T, true>(dst, step, count, raw, mult);
+}
+
+// From how many source bytes on the slices stay in registers, and are fetched past the caches.  us, two launches -> one
+// sweep, source from HBM: 32 MiB 18.9 -> 20.2, 47 25.6 -> 23.9, 65 32.0 -> 33.8 (8 heads of 16K rows) and 30.0 -> 23.8 (16 of
+// 8K), 98 48 -> 44, 260 112 -> 89, 781 371 -> 257; from the last-level cache: 32 17.9 -> 17.5, 64 30.7 -> 28.6, 98 43.2 -> 40.1.
+// Fetched past the caches, up to 256 MiB are 2 % faster from HBM and 3 to 10 % slower where that cache holds them.
+constexpr long long kQuantOnceBytes = 72ll << 20, kQuantPastBytes = 256ll << 20;
+
 int quant_slices(int n_rows, int head_dim) {
   // about 16 KB of codes per block, at most one slice per thread of the second reduction
   const long long codes = (long long)n_rows * head_dim;
   long long n = (codes + 16383) / 16384;
   if (n < 1) n = 1;
-  if (n > kQuantThreads) n = kQuantThreads;
+  if (n > kQuantMaxSlices) n = kQuantMaxSlices;
   return (int)n;
 }
 
-hipError_t launch_quantize(const QuantParams& p, hipStream_t st) {
-  dim3 grid(p.n_slices, 2 * p.Hkv, p.B);
-  if (p.src_dtype == HIPPO_DTYPE_BF16) {
-    hipLaunchKernelGGL(kv_absmax<uint16_t>, grid, dim3(kQuantThreads), 0, st, p);
-    hipLaunchKernelGGL(kv_encode<uint16_t>, grid, dim3(kQuantThreads), 0, st, p);
-  } else {
-    hipLaunchKernelGGL(kv_absmax<float>, grid, dim3(kQuantThreads), 0, st, p);
-    hipLaunchKernelGGL(kv_encode<float>, grid, dim3(kQuantThreads), 0, st, p);
+template <typename T>
+static void launch(QuantParams p, hipStream_t st) {
+  const long long n_vec = (long long)p.n_rows * (p.D / Elem<T>::kPerVec), heads = 2ll * p.Hkv * p.B;
+  constexpr long long held = (long long)kQuantOnceThreads * kQuantHeld;
+  if (n_vec <= kQuantMaxSlices * held && heads * n_vec * 16 >= kQuantOnceBytes) {
+    p.n_slices = (int)((n_vec + held - 1) / held);       // no more words than quant_slices, in whole vectors
+    if (p.polls < 0) p.polls = 64;
+    const dim3 grid(p.n_slices, 2 * p.Hkv, p.B);
+    const int words = (int)heads * quant_words(p.n_slices);
+    if (p.n_slices > 1)
+      hipLaunchKernelGGL(quant_clear, dim3((words + kQuantThreads - 1) / kQuantThreads), dim3(kQuantThreads), 0, st,
+                         (unsigned*)p.partial, words);
+    if (heads * n_vec * 16 >= kQuantPastBytes)
+      hipLaunchKernelGGL((kv_quantize_once<T, true>), grid, dim3(kQuantOnceThreads), 0, st, p);
+    else
+      hipLaunchKernelGGL((kv_quantize_once<T, false>), grid, dim3(kQuantOnceThreads), 0, st, p);
+    return;
   }
+  const dim3 grid(p.n_slices, 2 * p.Hkv, p.B);
+  hipLaunchKernelGGL(kv_absmax<T>, grid, dim3(kQuantThreads), 0, st, p);
+  hipLaunchKernelGGL(kv_encode<T>, grid, dim3(kQuantThreads), 0, st, p);
+}
+
+hipError_t launch_quantize(const QuantParams& p, hipStream_t st) {
+  if (p.src_dtype == HIPPO_DTYPE_BF16) launch<uint16_t>(p, st);
+  else launch<float>(p, st);
   return hipGetLastError();
 }
 

@@ -1,6 +1,8 @@
 """GPU parity: hippo_verify_attention_fp8kv / hippo_draft_attention_fp8kv (through the C ABI) vs the
 CPU oracle's attention over the dequantised cache.  The arithmetic is the bf16 path's (codes convert
 to bf16 exactly, the multipliers are fp32 factors), so the bf16 tolerances apply unchanged."""
+import ctypes as C
+
 import numpy as np
 import pytest
 import torch
@@ -229,3 +231,65 @@ def test_quantize_strided_prefix_then_attend(hippo):
     assert torch.all(codes[:, :, n:] == 0x7F)                # nothing written past n_rows
     ro, _ = oracle.attention_fp8kv(q, rk, rv, rkm, rvm, ctx)
     assert_close(host(out), ro, "bf16", "attention over the library's own quantisation")
+
+
+def quantize(hippo, k, v, n, polls):
+    """hippo_quantize_kv_e4m3 whose blocks look `polls` times for each other's maxima, into code rows with a gap"""
+    lib = hippo.load()
+    fn = lib.hippo_quantize_kv_e4m3_polls
+    fn.argtypes, fn.restype = lib.hippo_quantize_kv_e4m3.argtypes + [C.c_int32], C.c_int
+    B, Hkv, _, d = k.shape
+    codes = torch.full((2, B, Hkv, n + 1, d + 16), 0x7F, dtype=torch.uint8, device="cuda")[..., :d]
+    scale = torch.full((2, B, Hkv), -1.0, device="cuda")
+    src, dst = hippo.kv_desc(k, Hkv), hippo.kv_desc(codes[0], Hkv)
+    ws = torch.full((lib.hippo_quantize_kv_workspace_bytes(C.byref(src), n),), 1, dtype=torch.uint8, device="cuda")
+    hippo._check(fn(k.data_ptr(), v.data_ptr(), C.byref(src), n, codes[0].data_ptr(), codes[1].data_ptr(), C.byref(dst),
+                    scale[0].data_ptr(), scale[1].data_ptr(), ws.data_ptr(), ws.numel(), hippo._stream(None), polls),
+                 "hippo_quantize_kv_e4m3_polls")
+    return codes, scale
+
+
+@pytest.mark.parametrize("B, Hkv, n, d, dtype", [
+    (24, 12, 512, 128, "bf16"), (24, 12, 513, 128, "bf16"), (40, 6, 640, 128, "fp32"),   # one slice a head; two; three
+    (2, 3, 53001, 64, "bf16"), (1, 3, 25001, 128, "fp32"),                               # 52 and 98, the last ones short
+    (1, 2, 131072, 128, "bf16"), (1, 2, 131001, 64, "fp32"),                             # 256, the most
+    (2, 4, 68001, 128, "bf16"), (3, 4, 45003, 64, "fp32"),                               # fetched past the caches
+])
+def test_large_sources_are_quantised_as_their_heads_are(hippo, B, Hkv, n, d, dtype):
+    """A source of many megabytes, whose slices stay in registers, against its heads one by one, which take two launches:
+    the same codes and multipliers, whatever the blocks' waits come to."""
+    g = torch.Generator(device="cuda").manual_seed(n)
+    rows = torch.randn((2, B, Hkv, n + 2, d + 8), generator=g, device="cuda")[..., :d]
+    rows *= torch.exp2(torch.randint(-9, 9, (2, B, Hkv, 1, 1), generator=g, device="cuda").float())
+    # every head's largest value in a row of its own, another sign in V; a head of zeros, a tiny one; rows beyond n larger
+    at = torch.randint(0, n, (B, Hkv), generator=g, device="cuda")
+    at.view(-1)[-1] = n - 1
+    b, hk = torch.meshgrid(torch.arange(B, device="cuda"), torch.arange(Hkv, device="cuda"), indexing="ij")
+    rows[0, b, hk, at, d - 1], rows[1, b, hk, at, 0] = 5000.0, -7000.0
+    rows[:, :, :, n:] = 1e6
+    rows[1, 0, 0, :n] = 0.0
+    rows[0, -1, 0, :n] *= 2.0 ** -100
+    k, v = rows.to(torch.bfloat16 if dtype == "bf16" else torch.float32)
+    want = [hippo.hippo_quantize_kv_e4m3(k[i:i + 1, j:j + 1], v[i:i + 1, j:j + 1], n_rows=n)
+            for i in range(B) for j in range(Hkv)]
+    for polls in (-1, 0, 1):
+        codes, scale = quantize(hippo, k, v, n, polls)
+        assert torch.equal(scale, torch.stack([torch.cat([w[2 + t] for w in want]).view(B, Hkv) for t in (0, 1)]))
+        for t in (0, 1):
+            assert torch.equal(codes[t, :, :, :n], torch.cat([w[t] for w in want], 1).view(B, Hkv, n, d)), "%d looks" % polls
+        assert torch.all(codes[:, :, :, n:] == 0x7F)
+
+
+def test_two_large_quantisations_share_the_gpu(hippo):
+    g = torch.Generator(device="cuda").manual_seed(3)
+    data = [torch.randn((2, 1, 4, 90001, 128), generator=g, device="cuda").to(torch.bfloat16) for _ in range(2)]
+    alone = [hippo.hippo_quantize_kv_e4m3(k, v) for k, v in data]
+    torch.cuda.synchronize()
+    streams, together = [torch.cuda.Stream() for _ in data], [[], []]
+    for _ in range(3):
+        for i, s in enumerate(streams):
+            together[i].append(hippo.hippo_quantize_kv_e4m3(*data[i], stream=s))
+    torch.cuda.synchronize()
+    for ref, got in zip(alone, together):
+        for x in got:
+            assert all(torch.equal(a, b) for a, b in zip(ref, x))
