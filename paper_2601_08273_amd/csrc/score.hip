@@ -129,7 +129,7 @@ __device__ __forceinline__ void sattn_f32_body(const ScoreParams& p, SattnF32Sme
   };
   int buf = 0;
   for (int r0 = row_begin; r0 < row_end; r0 += RCH, buf ^= 1) {
-    wait_vmcnt<0>();                               // this wave's share of the chunk has arrived
+    wait_vmcnt_lds<0>();                           // this wave's share of the chunk has arrived, its row sums are in LDS
     if (PASS == 2 && tid < RCH) lse_s[buf][tid] = lse_reg;
     __syncthreads();                               // ... and everyone else's; everyone is done with the chunk before
     if (r0 + RCH < row_end) request_chunk(buf ^ 1, r0 + RCH);
@@ -371,8 +371,8 @@ __device__ __forceinline__ int sattn_once_body(const ScoreParams& p, const Score
   // that of the step before, which nobody writes any more, so that all waves leave at the same step.
   auto begin_step = [&](int c) -> bool {
     // (the wave that added the last sums leaves that one operation, issued after its transfers, in flight)
-    if (PUBLISH && c >= 2 && wave == (c & 3)) wait_vmcnt<1>();
-    else wait_vmcnt<0>();
+    if (PUBLISH && c >= 2 && wave == (c & 3)) wait_vmcnt_lds<1>();
+    else wait_vmcnt_lds<0>();
     __syncthreads();
     if (__builtin_amdgcn_readfirstlane(sm.large_s[(c + 1) & 1])) return false;
     if (c + 1 < n_chunks) request_chunk(c + 1);
@@ -796,7 +796,7 @@ __device__ __forceinline__ void sattn_mfma_body(const ScoreParams& p, SattnSmem<
   }
   bool plain = PASS == 1;                     // (wave-uniform)
   for (int r0 = row_begin; r0 < row_end; r0 += RCH, buf ^= 1) {
-    wait_vmcnt<0>();                          // this wave's share of the chunk (and its normalisers) has arrived
+    wait_vmcnt_lds<0>();                      // this wave's share of the chunk (and its normalisers) has arrived
     if (PASS == 2 && tid < RCH) sm.lse_s[buf][tid] = lse_reg;
     __syncthreads();                          // ... and everyone else's; everyone is done with the chunk before
     if (r0 + RCH < row_end) request_chunk(buf ^ 1, r0 + RCH);

@@ -579,3 +579,24 @@ def test_draft_cache_in_a_graph(hippo, n):
         outs = hippo.hippo_select_gather_kv(scores, 700, kc, vc, vid)
         torch.cuda.synchronize()
         assert all(torch.equal(a, b) for a, b in zip(held, outs))
+
+
+@pytest.mark.parametrize("dtype, d, G, layers, F, gh, gw, L", [
+    ("fp32", 64, 2, 2, 85, 13, 24, 26), ("fp32", 64, 2, 1, 128, 24, 24, 20),     # two sweeps of two chunks of rows
+    ("fp32", 128, 7, 1, 128, 12, 20, 12), ("fp32", 64, 7, 1, 16, 14, 14, 64),    # the same of 128 channels; one sweep
+    ("bf16", 64, 7, 1, 16, 16, 16, 64), ("bf16", 128, 7, 1, 64, 16, 16, 32),
+])
+def test_scores_are_the_same_bits_call_after_call(hippo, dtype, d, G, layers, F, gh, gw, L):
+    # what one wave leaves in LDS for another is there at the barrier between them: 300 calls, from memory and from the caches
+    g = torch.Generator(device="cuda").manual_seed(d + L)
+    n, tdt = F * gh * gw, torch.bfloat16 if dtype == "bf16" else torch.float32
+    q = [torch.randn((1, L, 2 * G, d), generator=g, device="cuda").to(tdt) for _ in range(layers)]
+    k = [torch.randn((1, 2, n, d), generator=g, device="cuda").to(tdt) for _ in range(layers)]
+    vid, away = hippo.video_desc(F, gh, gw, 0), torch.empty(600 << 20, dtype=torch.uint8, device="cuda")
+    ref = hippo.hippo_score_tokens_layers(q, k, vid, want_components=True)[1]
+    different = torch.zeros((), dtype=torch.int64, device="cuda")
+    for i in range(300):
+        if i % 3 == 0:
+            away.zero_()
+        different += (hippo.hippo_score_tokens_layers(q, k, vid, want_components=True)[1] != ref).any()
+    assert int(different) == 0
