@@ -645,19 +645,21 @@ constexpr int kSaWaves = 8;           // waves per block, 32 tokens each: two wa
 constexpr float kPlainMin = 0x1p-12f, kPlainMax = 0x1p14f;
 constexpr float kPlainSlack = 0x1p-6f;   // how far outside a wave's last plain sums may lie
 
-template <int D, int PASS>
+// MERGE > 0 (pass 2 of short videos): a block merges the row statistics of its run itself, one row a thread in the trip to
+// memory that brings the keys, and keeps the normalisers of all its rows; MERGE: 8-tile groups.  launch_sattn_mfma says when.
+template <int D, int PASS, int MERGE = 0>
 struct SattnSmem {
   static constexpr int RCH = 64;                 // query rows per LDS chunk
   static constexpr int ROWB = D * 2;             // unpadded rows, 16-byte pieces XOR-swizzled (lds_row_swizzle)
   static constexpr int RDEF = 256;               // pass 1 merges the waves' row statistics every RDEF rows
   __align__(16) unsigned char Qs[2][RCH * ROWB]; // two chunks: the next one lands while this one is multiplied
-  float lse_s[2][RCH];
+  float lse_s[MERGE > 0 ? kSaWaves * 64 / RCH : 2][RCH];
   float wm_s[PASS == 1 ? kSaWaves : 1][PASS == 1 ? RDEF : 1];
   float wl_s[PASS == 1 ? kSaWaves : 1][PASS == 1 ? RDEF : 1];
 };
 
-template <int D, int PASS>
-__device__ __forceinline__ void sattn_mfma_body(const ScoreParams& p, SattnSmem<D, PASS>& sm, const int tile,
+template <int D, int PASS, int MERGE = 0>
+__device__ __forceinline__ void sattn_mfma_body(const ScoreParams& p, SattnSmem<D, PASS, MERGE>& sm, const int tile,
                                                 const int vhk, const int bz) {
   const int b = bz % p.B, layer = bz / p.B;          // several layers' sweeps share a launch
   constexpr int NW = kSaWaves, NT = NW * 64;
@@ -705,6 +707,20 @@ __device__ __forceinline__ void sattn_mfma_body(const ScoreParams& p, SattnSmem<
     int n = n0 + i * KRPI + lane / CPR;
     n = n < p.Nv ? n : p.Nv - 1;                     // in bounds; masked below
     kraw[i] = *(const u32x4*)(kbase + (long long)n * p.sn + (lane % CPR) * 8);
+  }
+  // the tiles' statistics of one row of the run per thread, in the trip that brings the keys
+  constexpr int MS = MERGE > 0 ? MERGE : 1;
+  float st_m[8][MS], st_l[8][MS];
+  if constexpr (MERGE > 0) {
+    const int r = min(row_begin + tid, Rs - 1);
+#pragma unroll
+    for (int s = 0; s < 8; ++s)
+#pragma unroll
+      for (int u = 0; u < MS; ++u) {
+        const long long at = sattn_part_at(p, min(s + 8 * u, p.n_tile - 1), bz, hk, r);
+        st_m[s][u] = p.row_m[at];
+        st_l[s][u] = p.row_l[at];
+      }
   }
   bool tok_ok[TBW][4];
 #pragma unroll
@@ -767,7 +783,7 @@ __device__ __forceinline__ void sattn_mfma_body(const ScoreParams& p, SattnSmem<
       qg[u] -= carry * p.G;
       qi[u] += step_i + carry;
     }
-    if (PASS == 2 && tid < RCH) {
+    if (PASS == 2 && MERGE == 0 && tid < RCH) {
       const int r = r0 + tid;
       lse_reg = INFINITY;                     // padding rows contribute exp2(-inf) = 0
       if (r < Rs) lse_reg = p.row_lse[((long long)bz * p.Hkv + hk) * Rs + r];
@@ -794,14 +810,34 @@ __device__ __forceinline__ void sattn_mfma_body(const ScoreParams& p, SattnSmem<
       }
     }
   }
+  if constexpr (MERGE > 0) {
+    // as sattn_row_lse, in the same order: the same bits.  (Rows past the end: an infinite normaliser.)
+    float m8[8], l8[8], mx = -INFINITY, tot = 0.f;
+#pragma unroll
+    for (int s = 0; s < 8; ++s) {
+      m8[s] = -INFINITY;
+      l8[s] = 0.f;
+#pragma unroll
+      for (int u = 0; u < MS; ++u) {
+        if (s + 8 * u >= p.n_tile) st_m[s][u] = -INFINITY;
+        m8[s] = max_nan(m8[s], st_m[s][u]);
+      }
+#pragma unroll
+      for (int u = 0; u < MS; ++u) l8[s] += st_m[s][u] != -INFINITY ? st_l[s][u] * fast_exp2(st_m[s][u] - m8[s]) : 0.f;
+      mx = max_nan(mx, m8[s]);
+    }
+#pragma unroll
+    for (int s = 0; s < 8; ++s) tot += m8[s] != -INFINITY ? l8[s] * fast_exp2(m8[s] - mx) : 0.f;
+    sm.lse_s[tid / RCH][tid % RCH] = row_begin + tid < Rs ? mx + log2_of_sum(tot) : INFINITY;
+  }
   bool plain = PASS == 1;                     // (wave-uniform)
   for (int r0 = row_begin; r0 < row_end; r0 += RCH, buf ^= 1) {
     wait_vmcnt_lds<0>();                      // this wave's share of the chunk (and its normalisers) has arrived
-    if (PASS == 2 && tid < RCH) sm.lse_s[buf][tid] = lse_reg;
+    if (PASS == 2 && MERGE == 0 && tid < RCH) sm.lse_s[buf][tid] = lse_reg;
     __syncthreads();                          // ... and everyone else's; everyone is done with the chunk before
     if (r0 + RCH < row_end) request_chunk(buf ^ 1, r0 + RCH);
     const unsigned char* Qc = Qs + buf * CHUNKB;
-    const float* lse_c = sm.lse_s[buf];
+    const float* lse_c = sm.lse_s[MERGE > 0 ? (r0 - row_begin) / RCH : buf];
 
     auto products = [&](int rb, f32x4 (&z)[TBW]) {
 #pragma unroll
@@ -947,11 +983,11 @@ __device__ __forceinline__ void sattn_mfma_body(const ScoreParams& p, SattnSmem<
 // of them (every block re-reads the query rows of its head and run); the blocks that sweep the other
 // row run over the same 256 keys lie H_kv * n_tile places on -- on the same XCD, where the keys are.
 // Grid (H_kv, n_tile, n_rsplit * Bz).
-template <int D, int PASS>
+template <int D, int PASS, int MERGE = 0>
 __global__ __launch_bounds__(kSaWaves * 64) void sattn_mfma(ScoreParams p) {
-  __shared__ SattnSmem<D, PASS> sm;
+  __shared__ SattnSmem<D, PASS, MERGE> sm;
   const int rs = blockIdx.z % p.n_rsplit;
-  sattn_mfma_body<D, PASS>(p, sm, blockIdx.y, blockIdx.x + p.Hkv * rs, blockIdx.z / p.n_rsplit);
+  sattn_mfma_body<D, PASS, MERGE>(p, sm, blockIdx.y, blockIdx.x + p.Hkv * rs, blockIdx.z / p.n_rsplit);
 }
 
 // merge the per-tile row statistics: lse2 = m* + log2(sum_t l_t 2^(m_t - m*)).  A block takes 32
@@ -2083,6 +2119,16 @@ static hipError_t launch_sattn_mfma(const ScoreParams& p, hipStream_t st, long l
     hipLaunchKernelGGL(launch, fused, dim3(kSaWaves * 64), 0, st, p, (int)n_sattn, (int)r.lead);
   } else {
     hipLaunchKernelGGL((sattn_mfma<D, 1>), grid, dim3(kSaWaves * 64), 0, st, p);
+  }
+  // Up to 16 tiles, and a run of rows per block that its threads cover: pass 2 merges the row statistics itself.  Us a call
+  // from a graph, with a launch for the merge -> without: 4096 tokens x 14 heads, 64 text rows 19.7 -> 18.6, 4096 x 28, 256
+  // rows 31.6 -> 30.1, 4096 x 64, 256 rows 51.7 -> 50.4, 1368 x 4 x 2, 61 rows 16.5 -> 14.5, 2690 x 28 in 4 layers x 2 33.7 ->
+  // 31.9.  From 17 tiles on every block reads as much as the launch costs (6174 x 14 x 3 in four layers 44.4 -> 48.6, 4788 x 28
+  // x 2 39.2 -> 40.3, 5304 x 14 x 3 21.4 -> 21.1).
+  if (p.n_tile <= 16 && p.rows_per_split <= kSaWaves * 64) {
+    if (p.n_tile <= 8) hipLaunchKernelGGL((sattn_mfma<D, 2, 1>), grid, dim3(kSaWaves * 64), 0, st, p);
+    else hipLaunchKernelGGL((sattn_mfma<D, 2, 2>), grid, dim3(kSaWaves * 64), 0, st, p);
+    return hipGetLastError();
   }
   const long long rows = (long long)p.Bz * p.H * p.L;
   hipLaunchKernelGGL(sattn_row_lse, dim3((unsigned)((rows + 31) / 32)), dim3(256), 0, st, p);

@@ -600,3 +600,32 @@ def test_scores_are_the_same_bits_call_after_call(hippo, dtype, d, G, layers, F,
             away.zero_()
         different += (hippo.hippo_score_tokens_layers(q, k, vid, want_components=True)[1] != ref).any()
     assert int(different) == 0
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("n, L", [
+    # a tile and less; eight tiles and a token more; 16 (the most whose statistics pass 2 merges itself) and 17; 8, 9 chunks
+    # of rows a KV head; one row
+    (256, 1), (1, 9), (2048, 13), (2049, 64), (4095, 37), (4096, 128), (4097, 128), (300, 147), (700, 293),
+])
+def test_bf16_attention_mass_of_short_videos(hippo, n, L, d):
+    q, k = score_inputs(n + L, 2, L, 14, 2, d, n + 5, "bf16")
+    q[:, L // 2] *= 30.0                                              # a text row of large logits
+    q = prep(q, "bf16")
+    got = attention_mass(hippo, q, k, "bf16", 1, 1, n, 3)
+    assert_close(got, oracle.s_attn(q, k, 3, n), "bf16", "%d tokens, %d rows, d=%d" % (n, L, d))
+
+
+def test_bf16_attention_mass_of_long_runs_of_rows(hippo):
+    # a block's threads cover a run of 512 rows; longer ones have a launch for their statistics
+    for L in (256, 257, 320):
+        q, k = score_inputs(L, 1, L, 32, 8, 64, 2000, "bf16")
+        got = attention_mass(hippo, q, k, "bf16", 4, 20, 25, 0)
+        assert_close(got, oracle.s_attn(q, k, 0, 2000), "bf16", "%d text rows" % L)
+
+
+@pytest.mark.parametrize("dtype, channels", [("bf16", (8, 64, 72, 256, 448, 456)), ("fp32", (4, 64, 68, 128, 192, 196))])
+def test_embedding_terms_of_few_channels(hippo, dtype, channels):
+    # channels for one wave of the block, a piece more, for all waves but one, a piece more
+    for ch in channels:
+        test_embedding_terms_over_passes_of_channels(hippo, (1, 7, 6, 11, ch, 5, 5), dtype)
