@@ -1460,6 +1460,13 @@ __device__ __forceinline__ void emb_run32_body(const ScoreParams& p, EmbRunSmem<
   }
   unsigned char* strip = &sm.strip[0][wave][0];     // (two: the one that is read)
   unsigned strip_addr = (unsigned)(uintptr_t)strip;
+  // single pass: waves whose channels lie beyond the last one fetch and multiply nothing (two KV heads of 64 channels: six
+  // waves of eight, which took instructions and products' time from the sweep beside them), and nothing of theirs is
+  // summed.  us a call from a graph, with them -> without: bf16, 4096 tokens x 14 heads 18.6 -> 18.0, 23562 x 14 x 2 in four
+  // layers 59.1 -> 53.5, 37791 x 4 in four 45.8 -> 42.1; fp32, 3136 x 14 20.8 -> 20.1, 40320 x 4 in two 91 -> 82; of all 512
+  // channels (4992 to 16384 x 28) the same within 1.5 %.
+  const int n_active = WIDE ? NW : min(NW, (de + CW - 1) / CW);
+  const bool active = wave < n_active, all_active = WIDE || n_active == NW;
   auto request = [&](int frame, int pass) {         // single pass: frames lo, lo + 1, ... in turn
 #pragma unroll
     for (int i = 0; i < NT; ++i) {
@@ -1554,7 +1561,7 @@ __device__ __forceinline__ void emb_run32_body(const ScoreParams& p, EmbRunSmem<
   if constexpr (TWO) {
     issue();
     issue();
-  } else {
+  } else if (active) {
     request(lo, 0);
   }
   for (int fr = lo; fr <= hi; ++fr) {
@@ -1562,7 +1569,7 @@ __device__ __forceinline__ void emb_run32_body(const ScoreParams& p, EmbRunSmem<
     // D[i][j']: a lane holds column j' = j, rows i = 4g..4g+3.  Gram blocks (0,0) (0,1) (1,1); a neighbour frame
     // beyond the run is here for its norms and dot products: the diagonal blocks suffice.
     const bool own_frame = fr >= f0 && fr < f_end;  // (uniform)
-    if constexpr (!WIDE) {
+    if constexpr (!WIDE) if (active) {
       u32x4 cur[2][U];
       wait_vmcnt<0>();                              // the frame is in this wave's strip
 #pragma unroll
@@ -1580,15 +1587,18 @@ __device__ __forceinline__ void emb_run32_body(const ScoreParams& p, EmbRunSmem<
         *(f32x4*)(strip + (i * 64 + lane) * 16) = gram;
       }
 #pragma unroll
-      for (int rbk = 0; rbk < 2; ++rbk) {
-        dot[0][rbk] = (f32x4){0.f, 0.f, 0.f, 0.f};
+      for (int rbk = 0; rbk < 2; ++rbk) dot[0][rbk] = (f32x4){0.f, 0.f, 0.f, 0.f};
+      if (!F32 || fr > lo)                          // (fp32: 32 products of 32 clocks)
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-          dot[0][rbk] = emb_mma<F32>(cur[rbk][u], prev[rbk][u % UP], dot[0][rbk]);
-          prev[rbk][u % UP] = cur[rbk][u];
-        }
-      }
-    } else {
+        for (int rbk = 0; rbk < 2; ++rbk)
+#pragma unroll
+          for (int u = 0; u < U; ++u) dot[0][rbk] = emb_mma<F32>(cur[rbk][u], prev[rbk][u % UP], dot[0][rbk]);
+#pragma unroll
+      for (int rbk = 0; rbk < 2; ++rbk)
+#pragma unroll
+        for (int u = 0; u < U; ++u) prev[rbk][u % UP] = cur[rbk][u];
+    }
+    if constexpr (WIDE) {
       f32x4 gram[SETS][3];
 #pragma unroll
       for (int s = 0; s < SETS; ++s) {
@@ -1672,7 +1682,7 @@ __device__ __forceinline__ void emb_run32_body(const ScoreParams& p, EmbRunSmem<
           if (i != 1 || own_frame) *(f32x4*)(strip + s * kSetBytes + (i * 64 + lane) * 16) = gram[s][i];
     }
     // of a dot block only the diagonal (token with itself) is needed: lane (j, g = j/4), element j%4
-    if ((j >> 2) == g) {
+    if (active && (j >> 2) == g) {
 #pragma unroll
       for (int s = 0; s < SETS; ++s)
 #pragma unroll
@@ -1691,9 +1701,13 @@ __device__ __forceinline__ void emb_run32_body(const ScoreParams& p, EmbRunSmem<
       const int blk = wave;
       const unsigned used = TWO ? take ^ 1 : 0;  // the strips that took the partial sums
       f32x4 v = *(const f32x4*)(&sm.strip[used][0][0] + (blk * 64 + lane) * 16);
+      if (all_active) {                             // (all reads in flight)
 #pragma unroll
-      for (int w = 1; w < SETS * NW; ++w)
-        v += *(const f32x4*)(&sm.strip[used][w % NW][0] + (w / NW) * kSetBytes + (blk * 64 + lane) * 16);
+        for (int w = 1; w < SETS * NW; ++w)
+          v += *(const f32x4*)(&sm.strip[used][w % NW][0] + (w / NW) * kSetBytes + (blk * 64 + lane) * 16);
+      } else {
+        for (int w = 1; w < n_active; ++w) v += *(const f32x4*)(&sm.strip[used][w][0] + (blk * 64 + lane) * 16);
+      }
       const int ra = blk == 2 ? 1 : 0, rbk = blk == 0 ? 0 : 1;
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
@@ -1709,13 +1723,17 @@ __device__ __forceinline__ void emb_run32_body(const ScoreParams& p, EmbRunSmem<
       }
     } else if (wave == 3 && lane < MP) {
       float d = sm.redd[0][lane >> 4][lane & 15];
+      if (all_active) {
 #pragma unroll
-      for (int w = 1; w < SETS * NW; ++w) d += sm.redd[w][lane >> 4][lane & 15];
+        for (int w = 1; w < SETS * NW; ++w) d += sm.redd[w][lane >> 4][lane & 15];
+      } else {
+        for (int w = 1; w < n_active; ++w) d += sm.redd[w][lane >> 4][lane & 15];
+      }
       sm.dotv[lane] = d;
     }
     __syncthreads();
     if constexpr (TWO) issue();                 // the strips are free again: the next frame travels meanwhile
-    else if (fr < hi) request(fr + 1, 0);
+    else if (fr < hi && active) request(fr + 1, 0);
 
     // cosines of token a against tokens c0 .. c0 + CPT - 1 (its TPT threads cover the crop; padding rows hold
     // finite values and are masked); Eq. 5-6: their variance -- for the run's own frames only
@@ -2224,8 +2242,18 @@ hipError_t launch_score(const ScoreParams& p_in, const ScoreOnce& once_in, hipSt
     // 45.2 | 33.4; 19844 x 4, 47 rows (4 to 7) 51.8 | 50.4 | 41.9; longer still 52 -> 58 (4 to 8 of 9 that fit), 39.5 -> 40.5 (2 to 7).
     const long long room = 2 * kNumCU - n_sattn;
     if (once.row_word != nullptr && !wide && room > 0) {
-      const long long fits = (all_crops + room - 1) / room;
-      if (fits > run && fits <= std::min<long long>(8, 2 * std::max<long long>(1, run) + 2)) run = fits;
+      const long long longest = std::min<long long>(8, 2 * std::max<long long>(1, run) + 2);
+      long long fits = (all_crops + room - 1) / room;
+      if (fits > run && fits <= longest) {
+        // Runs do not come out even: what they need beyond the room waits for a slot, and only the video's last run, the
+        // shortest and last in the launch order, does so at no cost (5460 tokens x 4 heads x 4, 80 rows, 9 crops a frame: 12
+        // blocks too many 46.9, runs of 8 and not 7 36.7; 10920 x 4 x 2, 206 rows 52.8 and 38.7; 12 of the last run's 20 31.1
+        // against 33.2).
+        auto over = [&](long long r) { return crops_per_frame * ((p.F + r - 1) / r) * p.B - room > crops_per_frame; };
+        run = fits;
+        while (fits < longest && over(fits)) ++fits;
+        if (!over(fits)) run = fits;
+      }
     }
     p.emb_run = (int)std::max<long long>(1, std::min<long long>(std::min<long long>(8, p.F), run));
   }
