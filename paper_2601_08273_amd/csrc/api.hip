@@ -48,7 +48,7 @@ constexpr size_t kStaticScratchBytes = 8u << 20;   // hippo_verify_attention_sta
 
 struct AttnPlan {
   int R, row_chunk, n_chunks, S;
-  size_t off_m, off_l, bytes;
+  size_t off_m, off_l, off_e, bytes;
 };
 
 int plan_attention(int call, const hippo_kv_desc* kv, int q_len, int n_total, int num_splits, AttnPlan* pl) {
@@ -78,8 +78,16 @@ int plan_attention(int call, const hippo_kv_desc* kv, int q_len, int n_total, in
   const bool one_chunk = f32 && pl->R > 64 && pl->R <= 128 && n_tiles * heads > kNumCU &&
                          (kNumCU <= 64 * heads || n_tiles * heads >= 8 * kNumCU) &&
                          (num_splits > 0 || kNumCU / heads <= fit);
+  // 65 to 96 rows of a bf16 cache that no cache of the chip holds go in one block too: the second chunk's blocks keep half the
+  // transfers in flight on what the first chunk's fetch.  us a call, two chunks -> one: 4 x 8 heads x 128 x 37K, 72 rows 149 ->
+  // 115, from pages 169 -> 119, 96 rows 147 -> 126; 4 x 4 x 33K, 70 rows 71 -> 57; 64 x 8 x 1100, 91 rows 145 -> 133; 64
+  // channels, 4 x 8 x 37K, 72 rows 94 -> 76.  Of a cache that the last-level cache can hold not: 33K x 4, 91 rows of eight
+  // layers in turn 24.9 and 24.8, from pages 27.4 and 25.7, but of one layer 27.1 against 29.8; 16K 16.4 against 19.3.
+  const long long fit_wide = (long long)((kStaticScratchBytes - 4 * 256) / (slice_bytes + (size_t)heads * pl->R * 2 * sizeof(float)));
+  const bool wide = kv->dtype == HIPPO_DTYPE_BF16 && pl->R > 64 && pl->R <= 96 && num_splits == 0 && fit_wide >= 1 &&
+                    2 * heads * n_total * kv->head_dim * 2 > (256ll << 20);
   const int n_equal = (pl->R + 63) / 64;
-  pl->row_chunk = one_chunk ? (pl->R <= 96 ? 96 : 128) : f32 && pl->R > 64 ? 64 : ((pl->R + n_equal - 1) / n_equal + 15) / 16 * 16;
+  pl->row_chunk = wide ? 96 : one_chunk ? (pl->R <= 96 ? 96 : 128) : f32 && pl->R > 64 ? 64 : ((pl->R + n_equal - 1) / n_equal + 15) / 16 * 16;
   // short caches are bound by latency, not bytes: thin slices on many compute units win (bf16, 1896 rows, 7 query
   // rows: 59 slices of 32 rows beat 14 of 128 by 9 %)
   pl->n_chunks = (pl->R + pl->row_chunk - 1) / pl->row_chunk;
@@ -92,6 +100,7 @@ int plan_attention(int call, const hippo_kv_desc* kv, int q_len, int n_total, in
     S = (int)(kNumCU / per_split);          // rounded down: a block beyond the last compute unit would share one
     if (S < 1) S = 1;
     if (S > fit) S = (int)fit;
+    if (wide) S = (int)std::max<long long>(1, std::min<long long>(kNumCU / heads, fit_wide));   // (the exponents fit too)
     // A cache of a few tiles under up to 16 query rows goes in one slice, whose block writes the output itself: no merge
     // launch.  Where the line lies, us a call in a graph, slices and merge -> one slice (eager 10.7 -> 8): bf16, 7 rows,
     // 4 heads x 128: 100 rows 6.2 -> 4.1, 250 6.2 -> 5.3, 500 6.3 -> 8.3; 8 bits: 100 6.5 -> 4.8, 200 6.6 -> 6.4, 256 6.5 -> 6.4
@@ -110,7 +119,8 @@ int plan_attention(int call, const hippo_kv_desc* kv, int q_len, int n_total, in
   const size_t ml_bytes = align_up(slots * pl->R * sizeof(float), 256);
   pl->off_m = o_bytes;
   pl->off_l = o_bytes + ml_bytes;
-  pl->bytes = o_bytes + 2 * ml_bytes;
+  pl->off_e = o_bytes + 2 * ml_bytes;
+  pl->bytes = pl->off_e + (wide ? align_up(slots * pl->R * 2 * sizeof(float), 256) : 0);
   return HIPPO_OK;
 }
 
@@ -165,6 +175,7 @@ int attention_entry(int call, const void* q, int32_t q_len, const void* k_cache,
   p.part_o = workspace;
   p.part_m = reinterpret_cast<float*>(static_cast<char*>(workspace) + pl.off_m);
   p.part_l = reinterpret_cast<float*>(static_cast<char*>(workspace) + pl.off_l);
+  p.part_e = reinterpret_cast<float*>(static_cast<char*>(workspace) + pl.off_e);
   p.B = kv->batch; p.q_len = q_len; p.H = kv->n_q_heads; p.Hkv = kv->n_kv_heads;
   p.G = kv->n_q_heads / kv->n_kv_heads; p.R = pl.R;
   p.ctx_len = ctx_len; p.n_total = ctx_len + q_len;

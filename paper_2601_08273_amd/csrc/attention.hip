@@ -122,6 +122,7 @@ __device__ __forceinline__ int tile_swizzle(int r) {
 
 // four E4M3 codes of one dword -> bf16, exact
 typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2_t;
+typedef __attribute__((ext_vector_type(2))) _Float16 f16x2_t;
 typedef __attribute__((ext_vector_type(2))) int i32x2_t;
 typedef __attribute__((ext_vector_type(4))) int i32x4_t;
 __device__ __forceinline__ bf16x8 e4m3x8_to_bf16(int lo, int hi) {
@@ -141,6 +142,7 @@ template <int D, int RB, int TG, int TT, int NST, int MODE, bool KV8 = false, bo
 __global__ __launch_bounds__(RB * TG * 64) void attn_partial_grid(AttnParams p) {
   constexpr bool APPEND = MODE == 1, PAGED = MODE == 2;
   constexpr bool LONG32 = ROT && TT == 32;
+  constexpr bool SCALED = RB > 4;                      // more than 64 rows in one block: see its stores
   constexpr int ES = KV8 ? 1 : 2;                      // bytes per cache element
   using SM = GridSmem<D, TG, TT, NST, ES>;
   constexpr int WAVES = RB * TG;
@@ -506,14 +508,40 @@ __global__ __launch_bounds__(RB * TG * 64) void attn_partial_grid(AttnParams p) 
 #pragma unroll
       for (int w = 0; w < TG; ++w) f[w] *= inv;
     }
+    // A wide block's outputs leave as scaled fp16, as many bytes: its slices are half as long as those of two row chunks, and
+    // twice as many rounded to bf16 were further from 64 bits (33K x 4 heads, 91 rows 2.71e-3 -> 2.74e-3; like this 2.17e-3).
+    // One power of two for the wave's channels of a row, from the largest finite one.
+    float up = 1.f;
+    if constexpr (SCALED) {
+      float big = 0.f;
+#pragma unroll
+      for (int dd = 0; dd < DB / TG; ++dd) {
+        f32x4 o = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int w = 0; w < TG; ++w) {
+          if (w == TGC) o += acc[TGC + TG * dd] * f[w];
+          else o += other[w][dd] * f[w];
+        }
+        acc[TGC + TG * dd] = o;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) big = fabsf(o[e]) < INFINITY ? fmaxf(big, fabsf(o[e])) : big;
+      }
+      const int power = max(__builtin_amdgcn_frexp_expf(rows4_max(big)), -100) - 14;
+      up = ldexpf(1.f, -power);
+      if (g == 0 && row < p.R) p.part_e[(slot * p.R + row) * TG + TGC] = ldexpf(1.f, power);
+    }
 #pragma unroll
     for (int dd = 0; dd < DB / TG; ++dd) {
       const int db = TGC + TG * dd;
       f32x4 o = {0.f, 0.f, 0.f, 0.f};
+      if constexpr (SCALED) {
+        o = acc[TGC + TG * dd];
+      } else {
 #pragma unroll
-      for (int w = 0; w < TG; ++w) {
-        if (w == TGC) o += acc[TGC + TG * dd] * f[w];
-        else o += other[w][dd] * f[w];
+        for (int w = 0; w < TG; ++w) {
+          if (w == TGC) o += acc[TGC + TG * dd] * f[w];
+          else o += other[w][dd] * f[w];
+        }
       }
       // the slice's output leaves as bf16 (the merge weighs and sums it in fp32): half the bytes to write
       // here and to fetch in the merge, and the rounding is one more of the size the output's own has
@@ -521,8 +549,13 @@ __global__ __launch_bounds__(RB * TG * 64) void attn_partial_grid(AttnParams p) 
         typedef __attribute__((ext_vector_type(2))) float f32x2_t;
         const f32x2_t lo = {o[0], o[1]}, hi = {o[2], o[3]};
         uint2 w;
-        w.x = __builtin_bit_cast(unsigned, __builtin_convertvector(lo, bf16x2_t));
-        w.y = __builtin_bit_cast(unsigned, __builtin_convertvector(hi, bf16x2_t));
+        if constexpr (SCALED) {
+          w.x = __builtin_bit_cast(unsigned, __builtin_convertvector(lo * up, f16x2_t));
+          w.y = __builtin_bit_cast(unsigned, __builtin_convertvector(hi * up, f16x2_t));
+        } else {
+          w.x = __builtin_bit_cast(unsigned, __builtin_convertvector(lo, bf16x2_t));
+          w.y = __builtin_bit_cast(unsigned, __builtin_convertvector(hi, bf16x2_t));
+        }
         *(uint2*)(o_row + db * 16 + 4 * g) = w;
       }
     }
@@ -821,7 +854,8 @@ __global__ __launch_bounds__(RB * TG * 64) void attn_partial_f32(AttnParams p) {
 
 // =================================================================================================
 // Merge of the KV slices: out = sum_s 2^(m_s - m*) o_s / sum_s 2^(m_s - m*) l_s
-// The slices' outputs o_s are fp32 (PO16 = false: the fp32 kernel's) or bf16 (the bf16 kernel's).
+// The slices' outputs o_s are fp32 (the fp32 kernel's), bf16 (the bf16 kernel's) or scaled fp16 (its blocks of more than 64
+// rows).
 // One block per (query row, KV head, batch element).  The slices are spread over the threads: first
 // the S weights (one slice per thread, block-wide max and sum), then thread (sg, vec) accumulates
 // 16-byte vector `vec` of the row over slices sg, sg + NSG, ... and the NSG groups meet in LDS.
@@ -830,25 +864,31 @@ constexpr int kMaxSplits = 1024;
 
 // four consecutive elements of a slice's output; for bf16 the raw bits travel in the first two components
 // until the weights are known (the loads must all be in flight before anything waits for one of them)
-template <bool PO16>
+enum PartOut { kPartF32, kPartBf16, kPartF16 };
+constexpr int kWideGroups = 2;         // token groups of a block of more than 64 rows
+template <int PO>
 __device__ __forceinline__ f32x4 part_o_load4(const void* base, long long elem) {
-  if constexpr (!PO16) return *(const f32x4*)((const float*)base + elem);
+  if constexpr (PO == kPartF32) return *(const f32x4*)((const float*)base + elem);
   else {
     const uint2 w = *(const uint2*)((const uint16_t*)base + elem);
     return (f32x4){__uint_as_float(w.x), __uint_as_float(w.y), 0.f, 0.f};
   }
 }
-template <bool PO16>
+template <int PO>
 __device__ __forceinline__ f32x4 part_o_widen(f32x4 raw) {
-  if constexpr (!PO16) return raw;
-  else {
+  if constexpr (PO == kPartF32) return raw;
+  else if constexpr (PO == kPartF16) {
+    const unsigned lo = __float_as_uint(raw[0]), hi = __float_as_uint(raw[1]);
+    const f16x2_t x = __builtin_bit_cast(f16x2_t, lo), y = __builtin_bit_cast(f16x2_t, hi);
+    return (f32x4){(float)x[0], (float)x[1], (float)y[0], (float)y[1]};
+  } else {
     const unsigned x = __float_as_uint(raw[0]), y = __float_as_uint(raw[1]);
     return (f32x4){__uint_as_float(x << 16), __uint_as_float(x & 0xffff0000u), __uint_as_float(y << 16),
                    __uint_as_float(y & 0xffff0000u)};
   }
 }
 
-template <typename T, int D, bool PO16>
+template <typename T, int D, int PO>
 __global__ __launch_bounds__(256) void attn_combine(AttnParams p) {
   constexpr int VPR = D / 4;           // four-element vectors per row
   constexpr int NSG = 256 / VPR;       // slice groups
@@ -867,8 +907,14 @@ __global__ __launch_bounds__(256) void attn_combine(AttnParams p) {
 #pragma unroll
   for (int u = 0; u < PF; ++u) {
     const int s = min(sg + u * NSG, p.S - 1);             // past the last slice: a harmless repeat, not used
-    pre[u] = part_o_load4<PO16>(p.part_o, ((slot0 + s) * p.R + r) * D + vec * 4);
+    pre[u] = part_o_load4<PO>(p.part_o, ((slot0 + s) * p.R + r) * D + vec * 4);
   }
+  // scaled outputs: the power of two of this thread's channels (16-channel blocks are dealt to the token groups in turn)
+  auto scale_of = [&](int s) { return p.part_e[((slot0 + s) * p.R + r) * kWideGroups + vec / 4 % kWideGroups]; };
+  float pre_e[PF];
+  if constexpr (PO == kPartF16)
+#pragma unroll
+    for (int u = 0; u < PF; ++u) pre_e[u] = scale_of(min(sg + u * NSG, p.S - 1));
 
   // where the row's output goes: worked out while the loads are in flight (the division would otherwise
   // stand between the last barrier and the store)
@@ -892,8 +938,9 @@ __global__ __launch_bounds__(256) void attn_combine(AttnParams p) {
 #pragma unroll
     for (int u = 0; u < PF; ++u) {
       const int sl = sg + u * NSG;                        // < 64 whenever it is < S
-      const float ws = __shfl(w, sl & 63, 64);
-      if (sl < p.S) acc += part_o_widen<PO16>(pre[u]) * ws;
+      float ws = __shfl(w, sl & 63, 64);
+      if constexpr (PO == kPartF16) ws *= pre_e[u];
+      if (sl < p.S) acc += part_o_widen<PO>(pre[u]) * ws;
     }
   } else {
     // this thread's first slice statistics ride in the same trip
@@ -924,12 +971,12 @@ __global__ __launch_bounds__(256) void attn_combine(AttnParams p) {
 #pragma unroll
     for (int u = 0; u < PF; ++u) {
       const int sl = sg + u * NSG;
-      if (sl < p.S) acc += part_o_widen<PO16>(pre[u]) * w_s[sl];
+      if (sl < p.S) acc += part_o_widen<PO>(pre[u]) * (PO == kPartF16 ? w_s[sl] * pre_e[u] : w_s[sl]);
     }
 #pragma unroll 4
     for (int sl = sg + PF * NSG; sl < p.S; sl += NSG) {
-      const f32x4 o = part_o_widen<PO16>(part_o_load4<PO16>(p.part_o, ((slot0 + sl) * p.R + r) * D + vec * 4));
-      acc += o * w_s[sl];
+      const f32x4 o = part_o_widen<PO>(part_o_load4<PO>(p.part_o, ((slot0 + sl) * p.R + r) * D + vec * 4));
+      acc += o * (PO == kPartF16 ? w_s[sl] * scale_of(sl) : w_s[sl]);
     }
   }
   acc_s[sg][vec] = acc;
@@ -1048,6 +1095,13 @@ static hipError_t launch_grid_rb(const AttnParams& p, hipStream_t st) {
   return launch_grid<D, RB, 4, 16, 3>(p, st);
 }
 
+// 65 to 96 rows in one block (plan_attention says when; the cache exceeds the last-level cache): twelve waves in two token
+// groups, 128 KB of ring in stages of two 32-token tiles, of which all but one are in flight.
+template <int D>
+static hipError_t launch_grid_wide(const AttnParams& p, hipStream_t st) {
+  return launch_grid<D, 6, kWideGroups, 32, D == 128 ? 4 : 8, true, true>(p, st);
+}
+
 // fp8 cache: 32-token tiles only; short slices keep the whole slice in flight (two token groups, four
 // ring stages), long ones use four groups and two stages
 template <int D, int RB>
@@ -1079,6 +1133,7 @@ static hipError_t launch_mfma_d(const AttnParams& p, hipStream_t st) {
     case 2: return launch_grid_rb<D, 2>(p, st);
     case 3: return launch_grid_rb<D, 3>(p, st);
     case 4: return launch_grid_rb<D, 4>(p, st);
+    case 6: return launch_grid_wide<D>(p, st);
     default: return hipErrorInvalidValue;
   }
 }
@@ -1120,9 +1175,9 @@ static hipError_t launch_f32_d(const AttnParams& p, hipStream_t st) {
   }
 }
 
-template <typename T, int D, bool PO16>
+template <typename T, int D, int PO>
 static hipError_t launch_combine(const AttnParams& p, hipStream_t st) {
-  hipLaunchKernelGGL((attn_combine<T, D, PO16>), dim3(p.R, p.Hkv, p.B), dim3(256), 0, st, p);
+  hipLaunchKernelGGL((attn_combine<T, D, PO>), dim3(p.R, p.Hkv, p.B), dim3(256), 0, st, p);
   return hipGetLastError();
 }
 
@@ -1132,11 +1187,13 @@ hipError_t launch_attention(const AttnParams& p, int dtype, int head_dim, hipStr
     if (p.k_scale != nullptr) e = (head_dim == 128) ? launch_kv8_d<128>(p, st) : launch_kv8_d<64>(p, st);
     else e = (head_dim == 128) ? launch_mfma_d<128>(p, st) : launch_mfma_d<64>(p, st);
     if (e != hipSuccess || one_slice_call(p)) return e;
-    return (head_dim == 128) ? launch_combine<uint16_t, 128, true>(p, st) : launch_combine<uint16_t, 64, true>(p, st);
+    if (p.row_chunk > 64)
+      return (head_dim == 128) ? launch_combine<uint16_t, 128, kPartF16>(p, st) : launch_combine<uint16_t, 64, kPartF16>(p, st);
+    return (head_dim == 128) ? launch_combine<uint16_t, 128, kPartBf16>(p, st) : launch_combine<uint16_t, 64, kPartBf16>(p, st);
   }
   e = (head_dim == 128) ? launch_f32_d<128>(p, st) : launch_f32_d<64>(p, st);
   if (e != hipSuccess || one_slice_call(p)) return e;
-  return (head_dim == 128) ? launch_combine<float, 128, false>(p, st) : launch_combine<float, 64, false>(p, st);
+  return (head_dim == 128) ? launch_combine<float, 128, kPartF32>(p, st) : launch_combine<float, 64, kPartF32>(p, st);
 }
 
 }  // namespace hippo

@@ -253,6 +253,7 @@ struct AttnParams {
   void* part_o;     // [B, Hkv, S, R, D] unnormalised partial outputs: bf16 from the bf16 kernel, fp32 from the fp32 kernel
   float* part_m;    // [B, Hkv, S, R] running maxima (log2 domain)
   float* part_l;    // [B, Hkv, S, R] partial denominators
+  float* part_e;    // [B, Hkv, S, R, 2] what the scaled fp16 outputs of blocks of more than 64 rows are multiplied with
   int B, q_len, H, Hkv, G, R;
   int ctx_len, n_total;
   long long sb, sh, sn;   // element strides of K and V

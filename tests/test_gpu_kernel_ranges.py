@@ -629,3 +629,44 @@ def test_embedding_terms_of_few_channels(hippo, dtype, channels):
     # channels for one wave of the block, a piece more, for all waves but one, a piece more
     for ch in channels:
         test_embedding_terms_over_passes_of_channels(hippo, (1, 7, 6, 11, ch, 5, 5), dtype)
+
+
+@pytest.mark.parametrize("d, B, Hkv, q_len, G, ctx", [
+    # more than 256 MiB of K and V; 65, 72, 91 and 96 rows in one block, 97 in two; one slice a head, slices of a tile more or less
+    (128, 8, 8, 13, 5, 8200), (128, 4, 16, 9, 8, 8190), (64, 8, 8, 13, 7, 16390), (128, 2, 32, 12, 8, 8201), (128, 8, 8, 97, 1, 8200),
+    (64, 16, 32, 13, 7, 2100),
+])
+def test_65_to_96_rows_of_a_large_cache(hippo, d, B, Hkv, q_len, G, ctx):
+    g = torch.Generator(device="cuda").manual_seed(ctx + G)
+    shape = (B, Hkv, ctx + q_len, d)
+    k, v = (torch.randn(shape, generator=g, device="cuda").to(torch.bfloat16) for _ in range(2))
+    assert 4 * k.numel() > 256 << 20
+    q = torch.randn((B, q_len, Hkv * G, d), generator=g, device="cuda").to(torch.bfloat16)
+    unit = np.ones((B, Hkv, d))                                       # the slices' outputs keep their scale: of the values'
+    unit[0, 0], unit[0, 1, ::2] = 2.0 ** 100, 2.0 ** -20              # unit, which the bound below holds in
+    v *= torch.from_numpy(unit).cuda().unsqueeze(2)
+    v[-1, -1, :, 3] = float("inf")                                    # and what is not finite to its channel
+    q[1, :, :G] *= 8.0
+    out, lse = hippo.hippo_verify_attention(q, k, v, ctx, want_lse=True)
+    for b, hk in ((0, 0), (0, 1), (1, 0), (B - 1, Hkv - 1)):
+        heads = slice(hk * G, hk * G + G)
+        at = [c for c in range(d) if (b, hk, c) != (B - 1, Hkv - 1, 3)]
+        rows = [host(x[b:b + 1, hk:hk + 1].contiguous()) for x in (k, v[..., at])]
+        ref, ref_lse = oracle.attention(host(q[b:b + 1, :, heads].contiguous()), rows[0],
+                                        np.pad(rows[1], ((0, 0),) * 3 + ((0, d - len(at)),)), ctx)
+        got = host(out[b:b + 1, :, heads][..., at].contiguous())
+        assert_close(got / unit[b, hk, at], ref[..., :len(at)] / unit[b, hk, at], "bf16", "head %d of %d" % (hk, b))
+        np.testing.assert_allclose(host(lse[b:b + 1, heads].contiguous()), ref_lse, rtol=0, atol=2.0 ** -8)
+    assert not torch.isfinite(out[-1, :, -G:, 3]).any()
+    k2, v2 = k.clone(), v.clone()
+    k2[:, :, ctx:], v2[:, :, ctx:] = 7.0, 7.0
+    new = [x[:, :, ctx:].transpose(1, 2).contiguous() for x in (k, v)]
+    bits = lambda x: x.view(torch.int16)
+    assert torch.equal(bits(hippo.hippo_verify_attention(q, k2, v2, ctx, k_new=new[0], v_new=new[1])), bits(out))
+    assert torch.equal(k2, k) and torch.equal(v2, v)
+    del k2, v2
+    pools, table = pages([k, v], 3)
+    assert torch.equal(bits(hippo.hippo_verify_attention_paged(q, *pools, table, ctx)), bits(out))
+    static = torch.empty_like(out)
+    hippo.hippo_verify_attention_static(q, k, v, ctx, out=static)
+    assert torch.equal(bits(static), bits(out))
