@@ -14,7 +14,7 @@
 //                  exceeds u * total; one wave re-evaluates that cell and finds the word (inverse
 //                  CDF in index order).  The count is cleared by the first launch.
 // Bound by latency: the trips to memory that depend on each other.  Drawing in a launch of its own is a
-// start more on the GPU and a launch more to enqueue.  Us a call, three launches -> two, in a graph and
+// start more on the GPU and a launch more to enqueue.  Us a call, three launches -> two (of four waves a block), in a graph and
 // eager: 4 x 11 rows of 152064 bf16 words 15.7 -> 14.9 and 16.7 -> 14.7, 7 x 25 rows 29.2 -> 28.0 and
 // 28.2 -> 26.7, one sequence of 3 rows of 32000 words 12.4 -> 12.4 and 16.7 -> 14.2.
 // Greedy decoding (temperature 0) needs only the first launch over the target rows and a
@@ -66,6 +66,12 @@ constexpr int kSdThreads = 256;
 constexpr int kSdWaves = kSdThreads / 64;
 constexpr int kSdPerThread = kSdSeg / kSdThreads;   // 32 logits per thread, held in registers
 constexpr int kSdLdsStats = 1024;                   // segment statistics staged in LDS (16 KB)
+// The second launch has few blocks, whose chain of loads, exponentials and sums is what takes the time: sixteen waves share
+// a segment, one or two vectors a thread.  (The drawing at its end keeps to the first four waves.)  us a call from a graph, four
+// waves -> sixteen, with the maximum alone in the first launch: 4 x 11 rows of 152064 bf16 words 15.4 -> 13.1, fp32 16.0 ->
+// 14.0, 7 x 25 rows 27.1 -> 21.7, one sequence of 3 rows of 32000 words 12.0 -> 10.3, 16 x 11 rows 27.5 -> 26.4.
+constexpr int kSdCellThreads = 1024;
+constexpr int kSdCellPerThread = kSdSeg / kSdCellThreads;
 
 // Stores and loads of what other blocks of the launch read or wrote: device scope, past the caches of an XCD.
 __device__ __forceinline__ void store_agent(float* at, float v) {
@@ -86,12 +92,12 @@ __device__ __forceinline__ void load_vector(const T* row, int idx, int V, float*
     for (int e = 0; e < VEC; ++e) x[e] = (idx + e < V) ? Elem<T>::load(row + idx + e) : -INFINITY;
   }
 }
-template <typename T>
-__device__ __forceinline__ void load_segment(const T* row, int v0, int V, float (&x)[kSdPerThread]) {
+template <typename T, int THREADS>
+__device__ __forceinline__ void load_segment(const T* row, int v0, int V, float (&x)[kSdSeg / THREADS]) {
   constexpr int VEC = Elem<T>::kPerVec;
 #pragma unroll
-  for (int j = 0; j < kSdPerThread / VEC; ++j)
-    load_vector<T>(row, v0 + (j * kSdThreads + (int)threadIdx.x) * VEC, V, &x[j * VEC]);
+  for (int j = 0; j < kSdSeg / THREADS / VEC; ++j)
+    load_vector<T>(row, v0 + (j * THREADS + (int)threadIdx.x) * VEC, V, &x[j * VEC]);
 }
 
 // probability of a word from its logit and the row's statistics; the same expression, without
@@ -106,7 +112,8 @@ __device__ __forceinline__ float residual(float pp, float qq) {
   return r > 0.f ? r : 0.f;
 }
 
-template <typename T>
+// (sampling needs no argmax: a maximum takes a third of the instructions)
+template <typename T, bool GREEDY>
 __global__ __launch_bounds__(kSdThreads) void sd_row_stats(SpecParams p) {
   __shared__ float sh_m[kSdWaves];
   __shared__ int sh_a[kSdWaves];
@@ -118,7 +125,7 @@ __global__ __launch_bounds__(kSdThreads) void sd_row_stats(SpecParams p) {
       : static_cast<const T*>(p.q_logits) + ((long long)b * p.gamma + (row - p.gamma - 1)) * p.q_stride;
   const int v0 = seg * kSdSeg;
   float x[kSdPerThread];
-  load_segment<T>(base, v0, p.V, x);
+  load_segment<T, kSdThreads>(base, v0, p.V, x);
 
   constexpr int VEC = Elem<T>::kPerVec;
   float m = -INFINITY;
@@ -126,18 +133,22 @@ __global__ __launch_bounds__(kSdThreads) void sd_row_stats(SpecParams p) {
 #pragma unroll
   for (int i = 0; i < kSdPerThread; ++i) {     // ascending index inside the thread: strict > keeps the first
     const int idx = v0 + ((i / VEC) * kSdThreads + tid) * VEC + (i % VEC);
-    if (x[i] > m) { m = x[i]; arg = idx; }
+    if constexpr (!GREEDY) m = fmaxf(m, x[i]);               // (neither takes a NaN)
+    else if (x[i] > m) { m = x[i]; arg = idx; }
   }
-  wave_argmax(m, arg);
+  if constexpr (GREEDY) wave_argmax(m, arg);
+  else m = wave_max(m);
   if (lane == 0) { sh_m[wave] = m; sh_a[wave] = arg; }
   __syncthreads();
   m = sh_m[0]; arg = sh_a[0];
 #pragma unroll
-  for (int w = 1; w < kSdWaves; ++w)
-    if (sh_m[w] > m || (sh_m[w] == m && sh_a[w] < arg)) { m = sh_m[w]; arg = sh_a[w]; }
+  for (int w = 1; w < kSdWaves; ++w) {
+    if constexpr (!GREEDY) m = fmaxf(m, sh_m[w]);
+    else if (sh_m[w] > m || (sh_m[w] == m && sh_a[w] < arg)) { m = sh_m[w]; arg = sh_a[w]; }
+  }
 
   float z = 0.f;
-  if (p.c > 0.f && m > -INFINITY) {
+  if (!GREEDY && m > -INFINITY) {
 #pragma unroll
     for (int i = 0; i < kSdPerThread; ++i) z += fast_exp2((x[i] - m) * p.c);
   }
@@ -268,7 +279,7 @@ __device__ __forceinline__ void draw_word(const SpecParams& p, const int b, cons
 // Eq. 1 for all positions, first rejection, and (sampling mode) the cell sums of the distribution
 // the next token is drawn from.  Blocks of one sequence repeat the small first part identically.
 template <typename T>
-__global__ __launch_bounds__(kSdThreads) void sd_cells(SpecParams p) {
+__global__ __launch_bounds__(kSdCellThreads) void sd_cells(SpecParams p) {
   __shared__ float sh_mp[kSdMaxGamma + 1], sh_zp[kSdMaxGamma + 1], sh_mq[kSdMaxGamma], sh_zq[kSdMaxGamma];
   __shared__ int sh_argp[kSdMaxGamma + 1];
   __shared__ int sh_rej[kSdMaxGamma];
@@ -299,7 +310,7 @@ __global__ __launch_bounds__(kSdThreads) void sd_cells(SpecParams p) {
   const int n_stats = (greedy ? p.gamma + 1 : p.n_rows) * p.n_seg;
   const bool staged = n_stats <= kSdLdsStats;
   if (staged) {
-    for (int i = tid; i < n_stats; i += kSdThreads) sh_stats[i] = st[i];
+    for (int i = tid; i < n_stats; i += kSdCellThreads) sh_stats[i] = st[i];
     __syncthreads();
   }
   // merged statistics of every row: one row per group of 16 lanes (lanes over segments), so the
@@ -307,7 +318,7 @@ __global__ __launch_bounds__(kSdThreads) void sd_cells(SpecParams p) {
   {
     const int n_r = greedy ? p.gamma + 1 : p.n_rows;
     const int grp = tid >> 4, gl = tid & 15;
-    for (int row = grp; row < n_r; row += kSdThreads / 16) {
+    for (int row = grp; row < n_r; row += kSdCellThreads / 16) {
       const SegStat* rs = staged ? sh_stats + row * p.n_seg : st + (long long)row * p.n_seg;
       float m = -INFINITY;
       int arg = 0x7fffffff;
@@ -375,15 +386,16 @@ __global__ __launch_bounds__(kSdThreads) void sd_cells(SpecParams p) {
   if (seg == 0 && tid == 0) p.n_accept[b] = j;
 
   constexpr int VEC = Elem<T>::kPerVec;
-  constexpr int NV = kSdPerThread / VEC;
-  constexpr int CPS = NV * kSdWaves;             // cells per segment
+  constexpr int NV = kSdCellPerThread / VEC, WAVES = kSdCellThreads / 64;
+  constexpr int CPS = NV * WAVES;                // cells per segment
+  static_assert(CPS == kSdPerThread / VEC * kSdWaves, "a cell is a wave's vectors, whatever the waves of the block");
   const int v0 = seg * kSdSeg;
-  float xp[kSdPerThread];
-  load_segment<T>(pl + (long long)j * p.p_stride, v0, p.V, xp);
+  float xp[kSdCellPerThread];
+  load_segment<T, kSdCellThreads>(pl + (long long)j * p.p_stride, v0, p.V, xp);
   float sp[NV], sr[NV];
   if (rejected) {
-    float xq[kSdPerThread];
-    load_segment<T>(ql + (long long)j * p.q_stride, v0, p.V, xq);
+    float xq[kSdCellPerThread];
+    load_segment<T, kSdCellThreads>(ql + (long long)j * p.q_stride, v0, p.V, xq);
 #pragma unroll
     for (int v = 0; v < NV; ++v) {
       float a = 0.f, r = 0.f;
@@ -411,8 +423,8 @@ __global__ __launch_bounds__(kSdThreads) void sd_cells(SpecParams p) {
     const float a = wave_sum(sp[v]);
     const float r = wave_sum(sr[v]);
     if (lane == 0) {
-      store_agent(cells_p + v * kSdWaves + wave, a);
-      store_agent(cells_r + v * kSdWaves + wave, r);
+      store_agent(cells_p + v * WAVES + wave, a);
+      store_agent(cells_r + v * WAVES + wave, r);
     }
   }
   // The last of the sequence's blocks to get here draws the word: the others' cell sums are in memory by then, nobody
@@ -423,7 +435,7 @@ __global__ __launch_bounds__(kSdThreads) void sd_cells(SpecParams p) {
   __syncthreads();
   if (tid == 0) sh_j = __hip_atomic_fetch_add(p.arrived + b, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   __syncthreads();
-  if (sh_j != p.n_seg - 1) return;
+  if (sh_j != p.n_seg - 1 || tid >= kSdThreads) return;
   draw_word<T>(p, b, Chosen{j, rejected ? 1 : 0, mp, inv_zp, mq, inv_zq}, u_draw);
 }
 
@@ -431,8 +443,10 @@ template <typename T>
 hipError_t launch_typed(const SpecParams& p, hipStream_t st) {
   const bool greedy = !(p.c > 0.f);
   const int rows = greedy ? p.gamma + 1 : p.n_rows;
-  sd_row_stats<T><<<dim3(p.n_seg, rows, p.B), kSdThreads, 0, st>>>(p);
-  sd_cells<T><<<dim3(greedy ? 1 : p.n_seg, p.B), kSdThreads, 0, st>>>(p);
+  const dim3 grid(p.n_seg, rows, p.B);
+  if (greedy) sd_row_stats<T, true><<<grid, kSdThreads, 0, st>>>(p);
+  else sd_row_stats<T, false><<<grid, kSdThreads, 0, st>>>(p);
+  sd_cells<T><<<dim3(greedy ? 1 : p.n_seg, p.B), kSdCellThreads, 0, st>>>(p);
   return hipGetLastError();
 }
 

@@ -109,6 +109,16 @@ def test_sampling_parity(hippo, dtype, B, gamma, V, T, pad):
 
 
 @pytest.mark.parametrize("dtype", ["fp32", "bf16"])
+def test_sampling_at_the_edges_of_a_block_s_words(hippo, dtype):
+    # a word; one wave's vectors (256 words in fp32, 512 in bf16), less and one more; all waves but one's; a segment and one word
+    for V in (1, 255, 256, 257, 512, 520, 7680, 7681, 8191, 8193):
+        pl, ql, r = synth_logits(40, 2, max(V, 4), V, 0.6)
+        pl, ql = pl[..., :V], ql[..., :V]
+        tok = draw_from(ql, 1.0, r)
+        run_case(hippo, pl, ql, tok, r.random((40, 2)), r.random(40), 1.0, dtype, -V % 8, "%s V%d" % (dtype, V))
+
+
+@pytest.mark.parametrize("dtype", ["fp32", "bf16"])
 @pytest.mark.parametrize("B,V", [(1, 8), (70, 8200), (3, 1 << 20)])      # one block, two a sequence, the most there are
 def test_one_workspace_for_call_after_call(hippo, dtype, B, V):
     # the sequences' counts of finished blocks live in the workspace: whatever it holds before, and from replay to replay
