@@ -6,12 +6,12 @@
 // No atomics, and no result depends on an order between blocks: deterministic.
 // Bound by HBM: codes by a product and exact corrections instead of divisions, 16 source bytes per lane next to its
 // neighbour's (not 32 for 16 codes).  Large sources are read once (kv_quantize_once below).  Small ones, and heads of more than
-// 32 MB, take two launches: every block reduces |x| over its slice of a head's rows; then every block reduces the (few)
+// 48 MB, take two launches: every block reduces |x| over its slice of a head's rows; then every block reduces the (few)
 // slice maxima of its head again, encodes its slice and slice 0 stores the multiplier.  The second launch walks the slices
 // backwards, so that it begins with what the last-level cache still holds of the first, and stores its codes
 // non-temporally, so that they do not push the rest out; eight loads in flight.  Quantisation and a verification call over
-// the codes, us, two launches -> one sweep: 4 x 8 heads x 37K rows x 128 316 -> 234, 2 x 4 heads x 71K 153 -> 137, 3 x 8
-// heads x 21K 131 -> 109.
+// the codes, us, two launches -> one sweep: 4 x 8 heads x 37K rows x 128 315 -> 239, 2 x 4 heads x 71K 156 -> 126, 3 x 8
+// heads x 21K 135 -> 111, 1 x 8 x 130K 295 -> 226.
 #include "common.h"
 
 namespace hippo {
@@ -172,8 +172,8 @@ __global__ __launch_bounds__(kQuantThreads) void kv_encode(QuantParams p) {
   else encode_vectors<T, true>(p, q, mult);
 }
 
-// ---- the slice stays in registers ----------------------------------------------------------------
-// A block fetches its slice once, publishes the slice's maximum and encodes from its registers when all maxima of its
+// ---- the slice stays on the chip -------------------------------------------------------------------
+// A block fetches its slice once, into registers and LDS, publishes the slice's maximum and encodes when all maxima of its
 // head are there, so the source crosses the memory bus once instead of twice.  A word holds a slice's maximum and is its own
 // flag: a launch in front sets it to kQuantUnset, which no maximum's bits are, one relaxed device-scope store fills it,
 // and the first wave of every block of the head looks at all of them with one load instruction.
@@ -183,11 +183,14 @@ __global__ __launch_bounds__(kQuantThreads) void kv_encode(QuantParams p) {
 // What bounds it: HBM, and how many looks the words' memory channels serve; every look of a head goes to the same few
 // lines.  4 x 8 heads x 37K rows x 128 (608 MB in, 304 out), us: two launches that read the source twice 254; here without
 // any wait 163 (wrong, but the floor), slices of 64 KB whose threads look at a word each every half microsecond 253, whose
-// first wave looks for all 218, every two microseconds 202, slices of 128 KB 175 (5.2 TB/s), of 256 KB in one block a
-// compute unit 205; 24 vectors a thread and three waves a SIMD 177; one word and one counter a head by atomics 410.
+// first wave looks for all 218, every two microseconds 202, slices of 128 KB 175 to 188, of 256 KB in one block a
+// compute unit 205; 24 vectors a thread and three waves a SIMD 177; one word and one counter a head by atomics 410.  What
+// waits is what the chip holds: 64 KB of LDS a block beside its registers 175 (5.2 TB/s), 1 x 8 x 130K 201 -> 170, 2 x 4 x 71K
+// 110 -> 90, 3 x 8 x 21K 76 -> 72, 2 x 4 x 33K of fp32 83 -> 73; 72 KB no better, 32 KB half of it.
 constexpr unsigned kQuantUnset = 0xffffffffu;
-constexpr int kQuantHeld = 16;               // source vectors held per thread (64 registers: four waves a SIMD)
-constexpr int kQuantOnceThreads = 512;       // two blocks of 128 KB a compute unit
+constexpr int kQuantHeld = 16;               // source vectors held per thread in registers (64 of them: four waves a SIMD)
+constexpr int kQuantLds = 8;                 // ... and in LDS
+constexpr int kQuantOnceThreads = 512;       // two blocks of 192 KB a compute unit
 
 // words of a head: whole vectors of four
 __host__ __device__ constexpr int quant_words(int n_slices) { return (n_slices + 3) / 4 * 4; }
@@ -211,11 +214,16 @@ __device__ __forceinline__ float block_max(float v, float* red) {
 // A thread's vectors lie THREADS apart: a whole number of rows, so one address and a step reach them all.
 template <typename T, bool EXACT_DIV>
 __device__ __forceinline__ void encode_held(unsigned char* dst, long long step, int count, const u32x4 (&raw)[kQuantHeld],
-                                            float mult) {
+                                            const u32x4* rest, float mult) {
   const float r = 1.0f / mult;
 #pragma unroll
   for (int u = 0; u < kQuantHeld; ++u) {
     if (u < count) store_codes<T>(dst, encode_vec<T, EXACT_DIV>(raw[u], mult, r));
+    dst += step;
+  }
+#pragma unroll
+  for (int u = 0; u < kQuantLds; ++u) {
+    if (kQuantHeld + u < count) store_codes<T>(dst, encode_vec<T, EXACT_DIV>(rest[u * kQuantOnceThreads], mult, r));
     dst += step;
   }
 }
@@ -249,12 +257,13 @@ template <typename T, bool PAST>
 __global__ __launch_bounds__(kQuantOnceThreads, 4) void kv_quantize_once(QuantParams p) {
   __shared__ float red[2][kQuantOnceThreads / 64];
   __shared__ unsigned char missing[64];
+  __shared__ u32x4 rest_s[kQuantLds * kQuantOnceThreads];               // [vector][thread]: each its own
   constexpr int PV = Elem<T>::kPerVec, N = kQuantHeld, THREADS = kQuantOnceThreads;
   const int tid = threadIdx.x;
   const QuantSlice q = quant_slice<T>(p, blockIdx.x, blockIdx.y, blockIdx.z);
   const T* src = quant_src<T>(p, q);
   const long long e0 = q.lo + tid;
-  const int count = e0 < q.hi ? (int)((q.hi - e0 + THREADS - 1) / THREADS) : 0;     // this thread's vectors, at most N
+  const int count = e0 < q.hi ? (int)((q.hi - e0 + THREADS - 1) / THREADS) : 0;     // this thread's vectors, at most N and 8
   u32x4 raw[N];
   {
     const long long e = min(e0, q.hi - 1);
@@ -265,12 +274,21 @@ __global__ __launch_bounds__(kQuantOnceThreads, 4) void kv_quantize_once(QuantPa
       raw[u] = PAST ? __builtin_nontemporal_load((const u32x4*)at) : *(const u32x4*)at;
       if (u + 1 < count) at += step;
     }
+#pragma unroll
+    for (int u = 0; u < kQuantLds; ++u) {
+      dma16<PAST>(at, (unsigned)(uintptr_t)rest_s + (u * THREADS + (tid & ~63)) * 16);
+      if (N + u + 1 < count) at += step;
+    }
   }
+  const u32x4* const rest = rest_s + tid;
   float m = 0.f;
 #pragma unroll
   for (int u = 0; u < N; ++u) m = fmaxf(m, vec_absmax<T>(raw[u]));
 #pragma unroll
   for (int u = 0; u < N; ++u) asm volatile("" : "+v"(raw[u]));          // held as they came, not unpacked
+  wait_vmcnt<0>();
+#pragma unroll
+  for (int u = 0; u < kQuantLds; ++u) m = fmaxf(m, vec_absmax<T>(rest[u * THREADS]));
   m = block_max<THREADS>(m, red[0]);
   if (p.n_slices > 1) {
     unsigned* words = (unsigned*)p.partial + ((long long)(q.b * p.Hkv + q.hk) * 2 + q.which) * quant_words(p.n_slices);
@@ -300,11 +318,11 @@ __global__ __launch_bounds__(kQuantOnceThreads, 4) void kv_quantize_once(QuantPa
   unsigned char* dst = (unsigned char*)(q.which ? p.v_dst : p.k_dst) + (long long)q.b * p.dsb + (long long)q.hk * p.dsh +
                        (e0 >> q.vshift) * p.dsn + ((int)e0 & q.vmask) * PV;
   const long long step = (long long)(THREADS >> q.vshift) * p.dsn;
-  if (mult >= 0x1p-80f && mult <= 0x1p80f) encode_held<T, false>(dst, step, count, raw, mult);
-  else encode_held<T, true>(dst, step, count, raw, mult);
+  if (mult >= 0x1p-80f && mult <= 0x1p80f) encode_held<T, false>(dst, step, count, raw, rest, mult);
+  else encode_held<T, true>(dst, step, count, raw, rest, mult);
 }
 
-// From how many source bytes on the slices stay in registers, and are fetched past the caches.  us, two launches -> one
+// From how many source bytes on the slices stay on the chip, and are fetched past the caches (slices of 128 KB, without LDS).  us, two launches -> one
 // sweep, source from HBM: 32 MiB 18.9 -> 20.2, 47 25.6 -> 23.9, 65 32.0 -> 33.8 (8 heads of 16K rows) and 30.0 -> 23.8 (16 of
 // 8K), 98 48 -> 44, 260 112 -> 89, 781 371 -> 257; from the last-level cache: 32 17.9 -> 17.5, 64 30.7 -> 28.6, 98 43.2 -> 40.1.
 // Fetched past the caches, up to 256 MiB are 2 % faster from HBM and 3 to 10 % slower where that cache holds them.
@@ -322,7 +340,7 @@ int quant_slices(int n_rows, int head_dim) {
 template <typename T>
 static void launch(QuantParams p, hipStream_t st) {
   const long long n_vec = (long long)p.n_rows * (p.D / Elem<T>::kPerVec), heads = 2ll * p.Hkv * p.B;
-  constexpr long long held = (long long)kQuantOnceThreads * kQuantHeld;
+  constexpr long long held = (long long)kQuantOnceThreads * (kQuantHeld + kQuantLds);
   if (n_vec <= kQuantMaxSlices * held && heads * n_vec * 16 >= kQuantOnceBytes) {
     p.n_slices = (int)((n_vec + held - 1) / held);       // no more words than quant_slices, in whole vectors
     if (p.polls < 0) p.polls = 64;

@@ -250,13 +250,14 @@ def quantize(hippo, k, v, n, polls):
 
 
 @pytest.mark.parametrize("B, Hkv, n, d, dtype", [
-    (24, 12, 512, 128, "bf16"), (24, 12, 513, 128, "bf16"), (40, 6, 640, 128, "fp32"),   # one slice a head; two; three
-    (2, 3, 53001, 64, "bf16"), (1, 3, 25001, 128, "fp32"),                               # 52 and 98, the last ones short
-    (1, 2, 131072, 128, "bf16"), (1, 2, 131001, 64, "fp32"),                             # 256, the most
+    # one slice a head: registers full, the first vectors in LDS, both full; two; two
+    (24, 12, 512, 128, "bf16"), (24, 12, 513, 128, "bf16"), (16, 12, 768, 128, "bf16"), (16, 12, 769, 128, "bf16"),
+    (40, 6, 640, 128, "fp32"),
+    (2, 3, 53001, 64, "bf16"), (1, 3, 25001, 128, "fp32"), (1, 2, 131072, 128, "bf16"),  # 35, 66 and 171, the last ones short
     (2, 4, 68001, 128, "bf16"), (3, 4, 45003, 64, "fp32"),                               # fetched past the caches
 ])
 def test_large_sources_are_quantised_as_their_heads_are(hippo, B, Hkv, n, d, dtype):
-    """A source of many megabytes, whose slices stay in registers, against its heads one by one, which take two launches:
+    """A source of many megabytes, whose slices stay on the chip, against its heads one by one, which take two launches:
     the same codes and multipliers, whatever the blocks' waits come to."""
     g = torch.Generator(device="cuda").manual_seed(n)
     rows = torch.randn((2, B, Hkv, n + 2, d + 8), generator=g, device="cuda")[..., :d]
@@ -278,6 +279,19 @@ def test_large_sources_are_quantised_as_their_heads_are(hippo, B, Hkv, n, d, dty
         for t in (0, 1):
             assert torch.equal(codes[t, :, :, :n], torch.cat([w[t] for w in want], 1).view(B, Hkv, n, d)), "%d looks" % polls
         assert torch.all(codes[:, :, :, n:] == 0x7F)
+
+
+def test_quantised_heads_of_the_most_slices(hippo):
+    # 256 slices of 192 KB; a row of zeros more, which changes no maximum, takes two launches
+    g = torch.Generator(device="cuda").manual_seed(5)
+    n = 256 * 192 * 1024 // 256
+    x = torch.zeros((2, 1, 1, n + 1, 128), dtype=torch.bfloat16, device="cuda")
+    x[..., :n, :] = torch.randn((2, 1, 1, n, 128), generator=g, device="cuda")
+    want = hippo.hippo_quantize_kv_e4m3(*x)
+    for polls in (-1, 2):
+        codes, scale = quantize(hippo, x[0], x[1], n, polls)
+        assert torch.equal(scale, torch.stack(want[2:]))
+        assert all(torch.equal(codes[t, :, :, :n], want[t][:, :, :n]) for t in (0, 1))
 
 
 def test_two_large_quantisations_share_the_gpu(hippo):
