@@ -2005,7 +2005,7 @@ int score_token_tile(int dtype) { return dtype == HIPPO_DTYPE_BF16 ? kSaMfmaTile
 // blocks, two at a time, an odd last one alone.  520 unsplit blocks of 28 chunks, for example, put a third
 // block on a few units, which then start a 28-chunk sweep when all others are done (91 us against 81-83
 // with three or four runs); 256 blocks of 14 chunks are best cut in two (one round, two blocks per unit).
-int score_row_splits(int dtype, long long blocks_unsplit, int rows_per_kv_head, bool once) {
+int score_row_splits(int dtype, long long blocks_unsplit, int rows_per_kv_head, int head_dim, bool once) {
   int best = 1;
   if (dtype != HIPPO_DTYPE_BF16) {
     // fp32: a wave per SIMD nearly keeps the matrix unit busy, so a compute unit takes its blocks one after the other in
@@ -2038,6 +2038,18 @@ int score_row_splits(int dtype, long long blocks_unsplit, int rows_per_kv_head, 
       best_cost = cost;
     }
   }
+  // Short videos leave compute units without a block of the sweeps: finer cuts, up to a block on each (of 64 channels on seven
+  // eighths of them: 3780 tokens x 14 heads x 2 in two layers, 240 blocks for 120, 18.0 -> 18.5).  A block that is alone costs as
+  // above, but its first two chunks land together (one saves 0.6 us of two), and the more blocks, the longer their keys take,
+  // which each of a tile's fetches.  us a call from a graph, the cut above -> this: 4096 tokens x 14 heads, 64 text rows 17.9 ->
+  // 16.1 (3 runs -> 7), 1848 x 14, 183 rows 22.9 -> 18.1, 1400 x 28, 121 rows 22.6 -> 19.9, 3952 x 64, 17 rows 23.1 -> 21.1;
+  // 210 random calls 0.98 of the time; where it does not pay: 1824 x 28 in two layers, 34 rows, 4 runs for 2 18.0 -> 20.0.
+  auto alone = [&](int rs) {
+    const int cpb = (chunks + rs - 1) / rs;
+    return (cpb == 1 ? 1.89 : cpb * 1.29) + 2.5 + (head_dim == 128 ? 0.008 : 0.005) * (double)(blocks_unsplit * rs);
+  };
+  for (int rs = best + 1; rs <= 8 && rs <= chunks && blocks_unsplit * rs <= (head_dim == 128 ? kNumCU : kNumCU * 7 / 8); ++rs)
+    if (alone(rs) < alone(best) * 0.97) best = rs;
   return best;
 }
 
