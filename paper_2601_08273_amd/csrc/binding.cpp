@@ -184,7 +184,7 @@ PyObject* score(long long n_layers, const Tensor& q0, const Tensor& k0, const vo
   const Tensor emb = tensor_or_none(emb_o), mass = tensor_or_none(mass_o);
   long long emb_dim = 0, emb_stride = 0;
   if (emb.defined()) {
-    REQUIRE(emb.dim() == 3 && emb.stride(2) == 1 && emb.stride(0) == emb.size(1) * emb.stride(1));
+    REQUIRE(emb.dim() >= 3);
     emb_dim = emb.size(2);
     emb_stride = emb.stride(1);
   }
@@ -198,6 +198,10 @@ PyObject* score(long long n_layers, const Tensor& q0, const Tensor& k0, const vo
 PyObject* score_tokens(PyObject* const* a) {
   const Tensor &q = tensor(a[0]), &k = tensor(a[1]);
   REQUIRE(q.is_contiguous() && q.dim() == 4);
+  if (a[3] != Py_None) {
+    const Tensor& emb = tensor(a[3]);
+    REQUIRE(emb.dim() == 3 && emb.stride(2) == 1 && emb.stride(0) == emb.size(1) * emb.stride(1));
+  }
   const void *qs = ptr(q), *ks = ptr(k);
   return score(1, q, k, &qs, &ks, 0, a[2], a[3], a[4], a[5], a[6], a[7], a[8], "hippo_score_tokens");
 }

@@ -68,3 +68,11 @@ def test_whole_numbers_of_any_kind_are_taken():
     for n in (np.int64(38), np.int32(38), torch.tensor(38)):
         with pytest.raises(AssertionError):          # the length is read, then the caches' shapes are compared
             h.hippo_verify_attention(queries(), cache(), cache(N=41), n)
+
+
+def test_layers_take_embeddings_that_are_cut_from_a_longer_sequence():
+    # one batch element, whose stride nobody reads: not refused by the binding (without a GPU, by the stream it asks for)
+    emb = torch.zeros((1, 40, 64), dtype=torch.bfloat16)[:, 3:35]
+    with pytest.raises((h.HippoError, RuntimeError)):
+        h.hippo_score_tokens_layers([queries()], [cache(N=20)], VID, emb=emb, scores_out=torch.zeros((1, 32)),
+                                    workspace=torch.zeros(1 << 16, dtype=torch.uint8))
