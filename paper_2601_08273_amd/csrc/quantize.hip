@@ -322,11 +322,12 @@ __global__ __launch_bounds__(kQuantOnceThreads, 4) void kv_quantize_once(QuantPa
   else encode_held<T, true>(dst, step, count, raw, rest, mult);
 }
 
-// From how many source bytes on the slices stay on the chip, and are fetched past the caches (slices of 128 KB, without LDS).  us, two launches -> one
-// sweep, source from HBM: 32 MiB 18.9 -> 20.2, 47 25.6 -> 23.9, 65 32.0 -> 33.8 (8 heads of 16K rows) and 30.0 -> 23.8 (16 of
-// 8K), 98 48 -> 44, 260 112 -> 89, 781 371 -> 257; from the last-level cache: 32 17.9 -> 17.5, 64 30.7 -> 28.6, 98 43.2 -> 40.1.
+// From how many source bytes on the slices stay on the chip, and are fetched past the caches.  us, two launches -> one sweep,
+// source from HBM: 23 MiB 15.1 -> 17.3, 32 18.9 -> 19.2, 39 21.7 -> 20.6, 47 25.4 -> 21.6, 64 34.1 -> 30.9 (8 heads of 33K rows)
+// and 30.7 -> 28.0 (64 of 4K), 78 39 -> 33, 129 61 -> 49, 781 371 -> 250; from the last-level cache: 23 13.7 -> 14.5, 32 17.6 ->
+// 15.9, 64 31.6 -> 25.9.  Slices of 64 KB, more blocks, lose to two launches at 32 MiB (23.6) and above.
 // Fetched past the caches, up to 256 MiB are 2 % faster from HBM and 3 to 10 % slower where that cache holds them.
-constexpr long long kQuantOnceBytes = 72ll << 20, kQuantPastBytes = 256ll << 20;
+constexpr long long kQuantOnceBytes = 36ll << 20, kQuantPastBytes = 256ll << 20;
 
 int quant_slices(int n_rows, int head_dim) {
   // about 16 KB of codes per block, at most one slice per thread of the second reduction

@@ -255,6 +255,7 @@ def quantize(hippo, k, v, n, polls):
     (40, 6, 640, 128, "fp32"),
     (2, 3, 53001, 64, "bf16"), (1, 3, 25001, 128, "fp32"), (1, 2, 131072, 128, "bf16"),  # 35, 66 and 171, the last ones short
     (2, 4, 68001, 128, "bf16"), (3, 4, 45003, 64, "fp32"),                               # fetched past the caches
+    (1, 1, 73729, 128, "bf16"), (1, 8, 9217, 128, "bf16"),                               # just above 36 MiB
 ])
 def test_large_sources_are_quantised_as_their_heads_are(hippo, B, Hkv, n, d, dtype):
     """A source of many megabytes, whose slices stay on the chip, against its heads one by one, which take two launches:
@@ -271,8 +272,15 @@ def test_large_sources_are_quantised_as_their_heads_are(hippo, B, Hkv, n, d, dty
     rows[1, 0, 0, :n] = 0.0
     rows[0, -1, 0, :n] *= 2.0 ** -100
     k, v = rows.to(torch.bfloat16 if dtype == "bf16" else torch.float32)
-    want = [hippo.hippo_quantize_kv_e4m3(k[i:i + 1, j:j + 1], v[i:i + 1, j:j + 1], n_rows=n)
-            for i in range(B) for j in range(Hkv)]
+    want = []
+    for i in range(B):
+        for j in range(Hkv):          # pieces of less than 36 MiB, each with the row of its head's largest values
+            parts, top = [], at[i, j].view(1)
+            for lo in range(0, n, 65536):
+                index = torch.cat([torch.arange(lo, min(n, lo + 65536), device="cuda"), top])
+                parts.append(hippo.hippo_quantize_kv_e4m3(*(x[i:i + 1, j:j + 1, index] for x in (k, v))))
+            assert all(torch.equal(part[2 + t], parts[0][2 + t]) for part in parts for t in (0, 1))
+            want.append([torch.cat([part[t][:, :, :-1] for part in parts], 2) for t in (0, 1)] + list(parts[0][2:]))
     for polls in (-1, 0, 1):
         codes, scale = quantize(hippo, k, v, n, polls)
         assert torch.equal(scale, torch.stack([torch.cat([w[2 + t] for w in want]).view(B, Hkv) for t in (0, 1)]))
