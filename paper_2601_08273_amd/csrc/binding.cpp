@@ -176,18 +176,25 @@ PyObject* score(long long n_layers, const Tensor& q0, const Tensor& k0, const vo
   const hippo_video_desc vid = video(vid_o);
   const long long L = q0.size(1), n_vis = visual_tokens(vid);
   const uint32_t flags = (uint32_t)integer(flags_o);
-  const Tensor ws = workspace(ws_o, q0, [&] { return lib.hippo_score_layers_workspace_bytes(&kv, &vid, (int32_t)L, (int32_t)n_layers); });
-  Tensor scores = tensor_or_none(scores_o), comps;
-  if (!scores.defined() && !(flags & HIPPO_SCORE_ACCUMULATE_ONLY)) scores = empty({q0.size(0), n_vis}, at::kFloat, q0);
-  const bool want = truth(want_o);
-  if (want) comps = at::zeros({3, q0.size(0), n_vis}, at::TensorOptions().dtype(at::kFloat).device(q0.device()));
   const Tensor emb = tensor_or_none(emb_o), mass = tensor_or_none(mass_o);
   long long emb_dim = 0, emb_stride = 0;
   if (emb.defined()) {
     REQUIRE(emb.dim() >= 3);
     emb_dim = emb.size(2);
     emb_stride = emb.stride(1);
+    // What the kernels take for granted of embeddings that they read: the cache's type, channels side by side, batch elements
+    // N_v tokens apart.  (The stride of a single element is nobody's: it may be cut from a longer sequence.)
+    if (!(flags & HIPPO_SCORE_ACCUMULATE_ONLY) && (flags & (HIPPO_SCORE_TEMP | HIPPO_SCORE_SPA))) {
+      REQUIRE(emb.dim() == 3 && emb.stride(2) == 1 && emb.scalar_type() == k0.scalar_type());
+      REQUIRE(emb.size(0) == k0.size(0) && emb.size(1) >= n_vis);
+      REQUIRE(emb.size(0) == 1 || emb.stride(0) == n_vis * emb.stride(1));
+    }
   }
+  const Tensor ws = workspace(ws_o, q0, [&] { return lib.hippo_score_layers_workspace_bytes(&kv, &vid, (int32_t)L, (int32_t)n_layers); });
+  Tensor scores = tensor_or_none(scores_o), comps;
+  if (!scores.defined() && !(flags & HIPPO_SCORE_ACCUMULATE_ONLY)) scores = empty({q0.size(0), n_vis}, at::kFloat, q0);
+  const bool want = truth(want_o);
+  if (want) comps = at::zeros({3, q0.size(0), n_vis}, at::TensorOptions().dtype(at::kFloat).device(q0.device()));
   check(unlocked(lib.hippo_score_tokens_layers, (int32_t)n_layers, qs, (int32_t)L, ks, (int32_t)emb_layer, &kv,
                  (int32_t)k0.size(2), &vid, ptr(emb), (int32_t)emb_dim, (int64_t)emb_stride, flags, ptr<float>(mass),
                  ptr<float>(scores), ptr<float>(comps), ptr(ws), (size_t)ws.numel(), stream()),

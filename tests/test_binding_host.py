@@ -76,3 +76,30 @@ def test_layers_take_embeddings_that_are_cut_from_a_longer_sequence():
     with pytest.raises((h.HippoError, RuntimeError)):
         h.hippo_score_tokens_layers([queries()], [cache(N=20)], VID, emb=emb, scores_out=torch.zeros((1, 32)),
                                     workspace=torch.zeros(1 << 16, dtype=torch.uint8))
+
+
+def embeddings(B=1, n=32, ch=64, dtype=torch.bfloat16):
+    return torch.zeros((B, n, ch), dtype=dtype)
+
+
+@pytest.mark.parametrize("B, emb", [
+    (1, embeddings(ch=128)[..., ::2]),                               # channels that are not side by side
+    (2, embeddings(B=2, n=40)[:, 3:35]), (2, embeddings(B=2, n=40)),  # batch elements that are not N_v tokens apart
+    (1, embeddings(n=31)), (2, embeddings(B=1)),                     # too few tokens, too few batch elements
+    (1, embeddings(dtype=torch.float32)),                            # another type than the cache's
+    (1, embeddings()[None]),
+])
+def test_embeddings_that_the_kernels_would_misread(B, emb):
+    q, k = queries(B=B), cache(B=B)
+    given = dict(emb=emb, scores_out=torch.zeros((B, 32)), workspace=torch.zeros(1 << 16, dtype=torch.uint8))
+    with pytest.raises(AssertionError):
+        h.hippo_score_tokens(q, k, VID, **given)
+    with pytest.raises(AssertionError):
+        h.hippo_score_tokens_layers([q, q], [k, k], VID, **given)
+
+
+def test_embeddings_that_no_term_reads_are_not_looked_at():
+    with pytest.raises((h.HippoError, RuntimeError)):       # (without a GPU, refused by the stream it asks for)
+        h.hippo_score_tokens_layers([queries()], [cache(N=20)], VID, emb=embeddings(n=31, dtype=torch.float32),
+                                    flags=h.SCORE_ATTN, scores_out=torch.zeros((1, 32)),
+                                    workspace=torch.zeros(1 << 16, dtype=torch.uint8))
