@@ -214,9 +214,11 @@ PyObject* score_tokens(PyObject* const* a) {
 }
 
 PyObject* score_tokens_layers(PyObject* const* a) {
-  struct Items {                                               // a sequence's items, while this lives
-    PyObject* seq;
-    explicit Items(PyObject* o) : seq(PySequence_Check(o) ? PySequence_Fast(o, "a list of tensors") : nullptr) {
+  struct Items {                                               // the items of anything with a length and an index, while this
+    PyObject* seq = nullptr;                                   // lives: a list, a tuple, the layers stacked in one tensor
+    explicit Items(PyObject* o) {
+      if (PyObject_Size(o) >= 0 && (PySequence_Check(o) || PyMapping_Check(o)))
+        seq = PySequence_Fast(o, "expected one tensor per layer");
       if (seq != nullptr) return;
       if (!PyErr_Occurred()) PyErr_SetString(PyExc_TypeError, "expected a list of tensors, one per layer");
       throw Raised();

@@ -103,3 +103,16 @@ def test_embeddings_that_no_term_reads_are_not_looked_at():
         h.hippo_score_tokens_layers([queries()], [cache(N=20)], VID, emb=embeddings(n=31, dtype=torch.float32),
                                     flags=h.SCORE_ATTN, scores_out=torch.zeros((1, 32)),
                                     workspace=torch.zeros(1 << 16, dtype=torch.uint8))
+
+
+@pytest.mark.parametrize("as_layers", [list, tuple, torch.stack, lambda t: torch.nn.ParameterList([x for x in t])])
+def test_layers_come_in_anything_with_a_length_and_an_index(as_layers):
+    given = dict(scores_out=torch.zeros((1, 32)), workspace=torch.zeros(1 << 16, dtype=torch.uint8))
+    layers = lambda t: as_layers([t] * 3)
+    with pytest.raises((h.HippoError, RuntimeError)):       # (without a GPU, refused by the stream it asks for)
+        h.hippo_score_tokens_layers(layers(queries(dtype=torch.float32)), layers(cache(N=20, dtype=torch.float32)), VID, **given)
+    with pytest.raises(AssertionError):                     # one layer's queries more than its keys
+        h.hippo_score_tokens_layers(layers(queries(dtype=torch.float32)), [cache(dtype=torch.float32)] * 2, VID, **given)
+    for no_layers in (torch.tensor(1.0), {queries()}, iter([queries()]), None):
+        with pytest.raises(TypeError):
+            h.hippo_score_tokens_layers(no_layers, [cache()], VID, **given)
