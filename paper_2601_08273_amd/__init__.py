@@ -149,8 +149,8 @@ def _bound():
         try:
             from . import _binding as native
         except ImportError as e:
-            raise RuntimeError("_binding.so is not built: run `python -m paper_2601_08273_amd.build` "
-                               "(there is no fallback implementation)") from e
+            raise RuntimeError("_binding.so cannot be imported (%s): it is built for one torch and one Python by `python -m "
+                               "paper_2601_08273_amd.build` (there is no fallback implementation)" % e) from e
         native.bind(LIB_PATH, VideoDesc, HippoError)
         _native = native
     return _native

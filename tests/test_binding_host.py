@@ -1,4 +1,6 @@
 """The binding's own checks, which need no GPU: they come before anything is allocated or enqueued."""
+import sys
+
 import numpy as np
 import pytest
 import torch
@@ -116,3 +118,18 @@ def test_layers_come_in_anything_with_a_length_and_an_index(as_layers):
     for no_layers in (torch.tensor(1.0), {queries()}, iter([queries()]), None):
         with pytest.raises(TypeError):
             h.hippo_score_tokens_layers(no_layers, [cache()], VID, **given)
+
+
+def test_why_the_binding_cannot_be_imported_is_said(monkeypatch):
+    class Refuse:                                           # as a module built for another Python or torch is refused
+        @staticmethod
+        def find_spec(name, path=None, target=None):
+            if name == h.__name__ + "._binding":
+                raise ImportError("undefined symbol: of another torch")
+
+    monkeypatch.setattr(h, "_native", None)
+    monkeypatch.delattr(h, "_binding", raising=False)
+    monkeypatch.delitem(sys.modules, h.__name__ + "._binding", raising=False)
+    monkeypatch.setattr(sys, "meta_path", [Refuse] + sys.meta_path)
+    with pytest.raises(RuntimeError, match="undefined symbol: of another torch.*no fallback"):
+        h.hippo_verify_attention(queries(), cache(), cache(), 38)
