@@ -200,6 +200,10 @@ int hippo_select_gather_kv(const float* scores, int32_t k,
  * choice; the result does not depend on it beyond rounding (fp32 caches: fp32 throughout; 16- and 8-bit
  * caches: each slice's output reaches the merge rounded to bf16, its statistics in fp32).
  * ctx_len >= 0, q_len >= 1.
+ * Workspace: hippo_workspace_bytes.  With num_splits 0 it does not grow with seq_len once that gives
+ * every compute unit a slice, with one exception: 65 to 96 query rows a KV head (q_len H / H_kv) of bf16
+ * caches of more than 256 MiB (K and V) need about twice as much.  Such a call also takes a workspace of
+ * half that, as hippo_workspace_bytes says for a shorter cache, and is then 10 to 30 % slower.
  * Errors: NULL_ARG, BAD_SHAPE, BAD_DTYPE, BAD_ALIGN, WORKSPACE_TOO_SMALL, HIP.
  */
 int hippo_verify_attention(const void* q, int32_t q_len,

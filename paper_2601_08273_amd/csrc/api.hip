@@ -48,10 +48,12 @@ constexpr size_t kStaticScratchBytes = 8u << 20;   // hippo_verify_attention_sta
 
 struct AttnPlan {
   int R, row_chunk, n_chunks, S;
+  bool wide;                               // 65 to 96 bf16 rows in one block
   size_t off_m, off_l, off_e, bytes;
 };
 
-int plan_attention(int call, const hippo_kv_desc* kv, int q_len, int n_total, int num_splits, AttnPlan* pl) {
+int plan_attention(int call, const hippo_kv_desc* kv, int q_len, int n_total, int num_splits, AttnPlan* pl,
+                   bool may_be_wide = true) {
   (void)call;   // draft and verify share one launch heuristic (they differ in wave priority only)
   if (q_len < 1 || n_total < q_len || num_splits < 0) return HIPPO_ERR_BAD_SHAPE;
   const int G = kv->n_q_heads / kv->n_kv_heads;
@@ -84,8 +86,8 @@ int plan_attention(int call, const hippo_kv_desc* kv, int q_len, int n_total, in
   // channels, 4 x 8 x 37K, 72 rows 94 -> 76.  Of a cache that the last-level cache can hold not: 33K x 4, 91 rows of eight
   // layers in turn 24.9 and 24.8, from pages 27.4 and 25.7, but of one layer 27.1 against 29.8; 16K 16.4 against 19.3.
   const long long fit_wide = (long long)((kStaticScratchBytes - 4 * 256) / (slice_bytes + (size_t)heads * pl->R * 2 * sizeof(float)));
-  const bool wide = kv->dtype == HIPPO_DTYPE_BF16 && pl->R > 64 && pl->R <= 96 && num_splits == 0 && fit_wide >= 1 &&
-                    2 * heads * n_total * kv->head_dim * 2 > (256ll << 20);
+  const bool wide = pl->wide = may_be_wide && kv->dtype == HIPPO_DTYPE_BF16 && pl->R > 64 && pl->R <= 96 && num_splits == 0 &&
+                    fit_wide >= 1 && 2 * heads * n_total * kv->head_dim * 2 > (256ll << 20);
   const int n_equal = (pl->R + 63) / 64;
   pl->row_chunk = wide ? 96 : one_chunk ? (pl->R <= 96 ? 96 : 128) : f32 && pl->R > 64 ? 64 : ((pl->R + n_equal - 1) / n_equal + 15) / 16 * 16;
   // short caches are bound by latency, not bytes: thin slices on many compute units win (bf16, 1896 rows, 7 query
@@ -158,6 +160,10 @@ int attention_entry(int call, const void* q, int32_t q_len, const void* k_cache,
   if (append && (!aligned16(k_new) || !aligned16(v_new))) return HIPPO_ERR_BAD_ALIGN;
   AttnPlan pl;
   rc = plan_attention(call, kv, q_len, ctx_len + q_len, num_splits, &pl);
+  if (rc != HIPPO_OK) return rc;
+  // One block for 65 to 96 rows needs twice the workspace of two chunks.  A loop that sized its own before the cache grew past
+  // that line, or for more query rows, goes on in two chunks.
+  if (workspace_bytes < pl.bytes && pl.wide) rc = plan_attention(call, kv, q_len, ctx_len + q_len, num_splits, &pl, false);
   if (rc != HIPPO_OK) return rc;
   if (workspace_bytes < pl.bytes) return HIPPO_ERR_WORKSPACE_TOO_SMALL;
   int page_shift = 0;

@@ -137,6 +137,22 @@ def test_workspace_query(lib):
     assert h.workspace_bytes(h.CALL_SELECT_GATHER_KV, kv, vid, 0, 16646, 1639) >= 256
 
 
+def test_a_workspace_outlives_the_growth_of_its_cache(lib):
+    """What a decoding loop asked for at its first length, or for more query rows, is enough at every later one: 65 to 96 rows
+    of a bf16 cache beyond 256 MiB need twice as much in one block, and take two chunks where there is less."""
+    import torch
+    if torch.cuda.is_available():
+        pytest.skip("what passes the checks is launched")
+    for heads, group, d, q_len in itertools.product((1, 4, 8), (1, 5, 8), (64, 128), (9, 13, 16, 72, 91)):
+        kv = _kv(batch=4, n_q_heads=heads * group, n_kv_heads=heads, head_dim=d)
+        ask = lambda rows, n: h.workspace_bytes(h.CALL_VERIFY_ATTENTION, kv, None, rows, n)
+        for n in (4000, 30000, 60000, 150000, 300000, 600000):
+            for first in (ask(q_len, 4000), ask(2 * q_len, n) if 64 < q_len * group <= 96 else ask(q_len, n)):
+                assert _verify(lib, kv, q_len=q_len, ctx=n - q_len, ws_bytes=first) == h.ERR_HIP     # no GPU: the launch fails
+                assert _verify(lib, kv, q_len=q_len, ctx=n - q_len, ws_bytes=min(first, ask(q_len, 4000)) - 1) \
+                    == h.ERR_WORKSPACE_TOO_SMALL
+
+
 def _score(lib, kv, vid, l_txt=128, seq_len=16646, flags=h.SCORE_ALL, q=FAKE, k=FAKE, emb=None, emb_dim=0,
            emb_stride=0, mass=None, scores=FAKE, ws=FAKE, ws_bytes=1 << 32):
     return lib.hippo_score_tokens(q, l_txt, k, C.byref(kv), seq_len, C.byref(vid), emb, emb_dim, emb_stride,

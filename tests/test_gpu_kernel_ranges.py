@@ -670,3 +670,26 @@ def test_65_to_96_rows_of_a_large_cache(hippo, d, B, Hkv, q_len, G, ctx):
     static = torch.empty_like(out)
     hippo.hippo_verify_attention_static(q, k, v, ctx, out=static)
     assert torch.equal(bits(static), bits(out))
+
+
+@pytest.mark.parametrize("d, ctx, first_len, first_rows", [(64, 16500, 9000, 13), (64, 16500, 16513, 20), (128, 8300, 4000, 13)])
+def test_65_to_96_rows_in_a_workspace_of_before_the_cache_grew(hippo, d, ctx, first_len, first_rows):
+    # sized for a shorter cache, or for more rows: two chunks, the same bits as with their slices asked for
+    B, Hkv, q_len, G = 8, 8, 13, 7
+    g = torch.Generator(device="cuda").manual_seed(ctx)
+    k, v = (torch.randn((B, Hkv, ctx + q_len, d), generator=g, device="cuda").to(torch.bfloat16) for _ in range(2))
+    assert 4 * k.numel() > 256 << 20
+    q = torch.randn((B, q_len, Hkv * G, d), generator=g, device="cuda").to(torch.bfloat16)
+    kvd = hippo.kv_desc(k, Hkv * G)
+    first, asked = (hippo.workspace_bytes(hippo.CALL_VERIFY_ATTENTION, kvd, None, rows, n)
+                    for rows, n in ((first_rows, first_len), (q_len, ctx + q_len)))
+    assert first < asked
+    room = torch.full((first + 4096,), 0x5A, dtype=torch.uint8, device="cuda")
+    out = hippo.hippo_verify_attention(q, k, v, ctx, workspace=room[:first])
+    assert torch.all(room[first:] == 0x5A)
+    assert torch.equal(out, hippo.hippo_verify_attention(q, k, v, ctx, num_splits=2))
+    pools, table = pages([k, v], 3)
+    assert torch.equal(hippo.hippo_verify_attention_paged(q, *pools, table, ctx, workspace=room[:first]), out)
+    with pytest.raises(hippo.HippoError) as e:
+        hippo.hippo_verify_attention(q, k, v, ctx, workspace=room[:first // 2])
+    assert e.value.status == hippo.ERR_WORKSPACE_TOO_SMALL
