@@ -210,7 +210,8 @@ struct ScorePlan {
   size_t off_row_l, off_row_lse, off_col, off_sa, off_st, off_ss, bytes;
 };
 
-int plan_score(const hippo_kv_desc* kv, const hippo_video_desc* vid, int l_txt, int n_layers, ScorePlan* pl) {
+// finer: the finer cuts of short videos (see score_row_splits)
+int plan_score(const hippo_kv_desc* kv, const hippo_video_desc* vid, int l_txt, int n_layers, ScorePlan* pl, bool finer = true) {
   if (l_txt < 1 || l_txt > (1 << 20)) return HIPPO_ERR_BAD_SHAPE;
   if (n_layers < 1 || n_layers > kMaxScoreLayers || (long long)kv->batch * n_layers > 65535) return HIPPO_ERR_BAD_SHAPE;
   const long long Nv = (long long)vid->n_frames * vid->grid_h * vid->grid_w;
@@ -223,7 +224,7 @@ int plan_score(const hippo_kv_desc* kv, const hippo_video_desc* vid, int l_txt, 
   const int rows_per_kv_head = l_txt * (kv->n_q_heads / kv->n_kv_heads);
   pl->once = score_once(kv->dtype, Nv, rows_per_kv_head);
   pl->n_rsplit = score_row_splits(kv->dtype, (long long)pl->n_tile * kv->n_kv_heads * kv->batch * n_layers,
-                                  rows_per_kv_head, kv->head_dim, pl->once);
+                                  rows_per_kv_head, kv->head_dim, pl->once, finer);
   // launch limits of the sweeps (KV heads on grid x, key tiles on y, row runs x (layer, batch element) on z) and of
   // the row merge (32 rows per block)
   if (pl->n_tile > 65535 || (long long)kv->batch * n_layers * pl->n_rsplit > 65535 || kv->n_kv_heads > 65535 ||
@@ -397,6 +398,8 @@ int hippo_score_tokens_layers_polls(int32_t n_layers, const void* const* q_txt_l
   if (reinterpret_cast<uintptr_t>(workspace) & 255u) return HIPPO_ERR_BAD_ALIGN;
   ScorePlan pl;
   if ((rc = plan_score(kv, vid, l_txt, n_layers, &pl)) != HIPPO_OK) return rc;
+  // A short video's finer cut can need more than a longer one's: a workspace sized for that one serves without it.
+  if (workspace_bytes < pl.bytes && (rc = plan_score(kv, vid, l_txt, n_layers, &pl, false)) != HIPPO_OK) return rc;
   if (workspace_bytes < pl.bytes) return HIPPO_ERR_WORKSPACE_TOO_SMALL;
 
   ScoreParams p;

@@ -341,7 +341,8 @@ int score_token_tile(int dtype);   // tokens per block in the s_attn passes
 bool score_once(int dtype, long long n_vis, int rows_per_kv_head);   // s_attn in one sweep
 size_t score_once_rows(int rows_per_kv_head);      // rows of a KV head that it has words for
 extern const int kScoreOnceWords, kScoreOnceBins;  // its 64-bit words a row
-int score_row_splits(int dtype, long long blocks_unsplit, int rows_per_kv_head, int head_dim, bool once);
+int score_row_splits(int dtype, long long blocks_unsplit, int rows_per_kv_head, int head_dim, bool once,
+                     bool finer);
 
 struct SelectParams {
   const float* scores;

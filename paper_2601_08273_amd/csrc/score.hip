@@ -2005,7 +2005,7 @@ int score_token_tile(int dtype) { return dtype == HIPPO_DTYPE_BF16 ? kSaMfmaTile
 // blocks, two at a time, an odd last one alone.  520 unsplit blocks of 28 chunks, for example, put a third
 // block on a few units, which then start a 28-chunk sweep when all others are done (91 us against 81-83
 // with three or four runs); 256 blocks of 14 chunks are best cut in two (one round, two blocks per unit).
-int score_row_splits(int dtype, long long blocks_unsplit, int rows_per_kv_head, int head_dim, bool once) {
+int score_row_splits(int dtype, long long blocks_unsplit, int rows_per_kv_head, int head_dim, bool once, bool finer) {
   int best = 1;
   if (dtype != HIPPO_DTYPE_BF16) {
     // fp32: a wave per SIMD nearly keeps the matrix unit busy, so a compute unit takes its blocks one after the other in
@@ -2048,6 +2048,7 @@ int score_row_splits(int dtype, long long blocks_unsplit, int rows_per_kv_head, 
     const int cpb = (chunks + rs - 1) / rs;
     return (cpb == 1 ? 1.89 : cpb * 1.29) + 2.5 + (head_dim == 128 ? 0.008 : 0.005) * (double)(blocks_unsplit * rs);
   };
+  if (!finer) return best;
   for (int rs = best + 1; rs <= 8 && rs <= chunks && blocks_unsplit * rs <= (head_dim == 128 ? kNumCU : kNumCU * 7 / 8); ++rs)
     if (alone(rs) < alone(best) * 0.97) best = rs;
   return best;

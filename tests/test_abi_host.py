@@ -182,6 +182,27 @@ def test_score_argument_errors(lib):
     assert _score(lib, kv, h.video_desc(65535, 16, 16, 0), seq_len=65535 * 256, ws_bytes=4096) == h.ERR_WORKSPACE_TOO_SMALL
 
 
+def test_a_workspace_for_a_longer_video_serves_a_shorter_one(lib):
+    """The finer cuts of short videos take more column partials than some longer ones need: less is enough without them."""
+    import torch
+    if torch.cuda.is_available():
+        pytest.skip("what passes the checks is launched")
+    for (q_heads, heads, d), larger, smaller, least in (
+            ((16, 4, 64), (5, 3, 6, 134, 2), (5, 3, 6, 116, 2), 57600), ((16, 4, 64), (31, 12, 5, 42, 4), (31, 12, 5, 42, 3), 249600),
+            ((4, 4, 64), (113, 7, 5, 102, 2), (91, 7, 5, 102, 2), 228864),
+            ((32, 8, 128), (10, 14, 4, 118, 1), (10, 11, 4, 118, 1), 137216)):
+        kv = _kv(n_q_heads=q_heads, n_kv_heads=heads, head_dim=d)
+        ask = lambda f, gh, gw, l, n: lib.hippo_score_layers_workspace_bytes(C.byref(kv), C.byref(h.video_desc(f, gh, gw, 0)), l, n)
+        f, gh, gw, l, n = smaller
+        layers = (C.c_void_p * n)(*[FAKE] * n)
+        call = lambda bytes: lib.hippo_score_tokens_layers(n, layers, l, layers, 0, C.byref(kv), f * gh * gw,
+                                                           C.byref(h.video_desc(f, gh, gw, 0)), None, 0, 0, h.SCORE_ALL, None,
+                                                           FAKE, None, FAKE, bytes, None)
+        assert least < ask(*larger) < ask(*smaller)
+        assert call(ask(*larger)) == call(least) == h.ERR_HIP                  # no GPU: the launch fails
+        assert call(least - 1) == h.ERR_WORKSPACE_TOO_SMALL
+
+
 def test_select_argument_errors(lib):
     kv, vid = _kv(), h.video_desc(64, 16, 16, 128)
 

@@ -693,3 +693,17 @@ def test_65_to_96_rows_in_a_workspace_of_before_the_cache_grew(hippo, d, ctx, fi
     with pytest.raises(hippo.HippoError) as e:
         hippo.hippo_verify_attention(q, k, v, ctx, workspace=room[:first // 2])
     assert e.value.status == hippo.ERR_WORKSPACE_TOO_SMALL
+
+
+@pytest.mark.parametrize("H, Hkv, d, F, gh, gw, L", [(32, 8, 128, 10, 11, 4, 118), (14, 2, 64, 16, 16, 16, 64)])
+def test_short_videos_in_a_workspace_without_room_for_finer_cuts(hippo, H, Hkv, d, F, gh, gw, L):
+    n, vid = F * gh * gw, hippo.video_desc(F, gh, gw, 0)
+    q, k = score_inputs(L, 1, L, H, Hkv, d, n, "bf16")
+    qd, kd = dev(q, "bf16"), dev(k, "bf16")
+    need = hippo.workspace_bytes(hippo.CALL_SCORE_TOKENS, hippo.kv_desc(kd, H), vid, L, n)
+    ws = torch.full((need + 4096,), 0x5A, dtype=torch.uint8, device="cuda")
+    for short in (0, 256):                                  # all it asks for; a little less
+        mass = torch.zeros((1, n), device="cuda")
+        hippo.hippo_score_tokens(qd, kd, vid, flags=hippo.SCORE_ACCUMULATE_ONLY, attn_mass_inout=mass, workspace=ws[:need - short])
+        assert torch.all(ws[need - short:] == 0x5A)
+        assert_close(host(mass), oracle.s_attn(q, k, 0, n), "bf16", "%d bytes short" % short)
