@@ -302,8 +302,8 @@ int hippo_draft_attention_fp8kv(const void* q, int32_t q_len, const void* k_code
  * so the largest entry of every head maps to the largest code and nothing overflows.  src describes
  * k_src / v_src (dtype F32 or BF16), dst the code arrays (dtype FP8_E4M3, strides in bytes); both
  * agree in batch, n_kv_heads, head_dim.  k_scale / v_scale [B, H_kv] fp32 are OUTPUTS.  Inputs must
- * be finite (a NaN or infinity gives unspecified codes for its head).  Deterministic.  Workspace:
- * hippo_quantize_kv_workspace_bytes(src, n_rows).
+ * be finite (a NaN or infinity gives unspecified codes for its head).  The outputs must not overlap the
+ * sources.  Deterministic.  Workspace: hippo_quantize_kv_workspace_bytes(src, n_rows).
  * Errors: NULL_ARG, BAD_DTYPE, BAD_SHAPE (descriptor mismatch, n_rows < 1), BAD_ALIGN,
  *         WORKSPACE_TOO_SMALL, HIP.
  */

@@ -368,7 +368,7 @@ struct QuantParams {
   float* v_scale;
   float* partial;         // workspace: [B, Hkv, 2, n_slices] slice maxima
   int B, Hkv, D, n_rows, n_slices, src_dtype;
-  int polls;              // how often a thread looks for a slice's maximum before the block takes it itself; -1: as
+  int polls;              // how many looks in a row may bring no new slice's maximum before a block takes one itself; -1: as
                           // launch_quantize finds right
   long long ssb, ssh, ssn, dsb, dsh, dsn;   // element strides (dst: bytes)
 };

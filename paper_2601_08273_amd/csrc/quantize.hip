@@ -3,7 +3,7 @@
 // (batch element, KV head) and tensor.
 //   multiplier = max|x| / 448 over the head's rows (1 when the maximum is 0)
 //   code       = the E4M3 value nearest to x / multiplier, ties to the even code
-// No atomics, and no result depends on an order between blocks: deterministic.
+// No result depends on an order between blocks: deterministic.
 // Bound by HBM: codes by a product and exact corrections instead of divisions, 16 source bytes per lane next to its
 // neighbour's (not 32 for 16 codes).  Large sources are read once (kv_quantize_once below).  Small ones, and heads of more than
 // 48 MB, take two launches: every block reduces |x| over its slice of a head's rows; then every block reduces the (few)
@@ -70,9 +70,9 @@ __device__ __forceinline__ float* quant_partials(const QuantParams& p, const Qua
 constexpr int kQuantInFlight = 8;   // source vectors in flight per thread
 
 // max|x| over this thread's vectors of a slice
-template <typename T, int THREADS>
+template <typename T, int THREADS, int N>
 __device__ __forceinline__ float slice_absmax(const T* src, const QuantParams& p, const QuantSlice& q) {
-  constexpr int PV = Elem<T>::kPerVec, N = kQuantInFlight;
+  constexpr int PV = Elem<T>::kPerVec;
   float m = 0.f;
   for (long long e0 = q.lo + threadIdx.x; e0 < q.hi; e0 += N * THREADS) {
     u32x4 v[N];
@@ -91,7 +91,7 @@ template <typename T>
 __global__ __launch_bounds__(kQuantThreads) void kv_absmax(QuantParams p) {
   __shared__ float red[4];
   const QuantSlice q = quant_slice<T>(p, blockIdx.x, blockIdx.y, blockIdx.z);
-  const float m = block_max_256(slice_absmax<T, kQuantThreads>(quant_src<T>(p, q), p, q), red);
+  const float m = block_max_256(slice_absmax<T, kQuantThreads, kQuantInFlight>(quant_src<T>(p, q), p, q), red);
   if (threadIdx.x == 0) quant_partials(p, q)[blockIdx.x] = m;
 }
 
@@ -178,8 +178,13 @@ __global__ __launch_bounds__(kQuantThreads) void kv_encode(QuantParams p) {
 // flag: a launch in front sets it to kQuantUnset, which no maximum's bits are, one relaxed device-scope store fills it,
 // and the first wave of every block of the head looks at all of them with one load instruction.
 // A head's slices stand together in the launch order and are at most half of what the chip holds, so they run beside each
-// other while the next heads' slices load.  No result depends on a wait: a wave that has looked `polls` times in vain
-// leaves the missing slices to its block, which takes their maxima from the source itself.
+// other while the next heads' slices load.  No result depends on a wait: when `polls` looks in a row have brought nothing new,
+// the blocks that wait take the maxima of the missing slices from the source themselves, each of another one, and publish
+// them.  That is what other work on the chip comes to, several large quantisations above all: us a call each on streams of
+// their own, two launches | one sweep | a sweep whose every block takes all missing maxima for itself: three of 1 x 8 x 196K
+// 1198 | 1189 | 24600, four 1577 | 1468 | 25000, two 785 | 730 | 1380; three of 1 x 2 x 196K 306 | 304 | 1800; three of 1 x 8 x 130K
+// 789 | 673 | 980; three of 4 x 8 x 37K 820 | 503 | 503.  Twelve looks (20 us) where three sweeps' heads fit the chip, four above:
+// there three of 1 x 8 x 196K take 1476 with twelve, and one alone 257.5 with four, 257.0 with twelve.
 // What bounds it: HBM, and how many looks the words' memory channels serve; every look of a head goes to the same few
 // lines.  4 x 8 heads x 37K rows x 128 (608 MB in, 304 out), us: two launches that read the source twice 254; here without
 // any wait 163 (wrong, but the floor), slices of 64 KB whose threads look at a word each every half microsecond 253, whose
@@ -190,6 +195,7 @@ __global__ __launch_bounds__(kQuantThreads) void kv_encode(QuantParams p) {
 constexpr unsigned kQuantUnset = 0xffffffffu;
 constexpr int kQuantHeld = 16;               // source vectors held per thread in registers (64 of them: four waves a SIMD)
 constexpr int kQuantLds = 8;                 // ... and in LDS
+constexpr int kQuantHelped = 3;              // looks without a new word after the first slice that a block has helped out with
 constexpr int kQuantOnceThreads = 512;       // two blocks of 192 KB a compute unit
 
 // words of a head: whole vectors of four
@@ -229,22 +235,25 @@ __device__ __forceinline__ void encode_held(unsigned char* dst, long long step, 
 }
 
 // The maxima of a head's slices, four a lane (0 where there is none).  Bit i of the result: this lane's word i is missing.
-__device__ __forceinline__ unsigned look_for_maxima(const unsigned* words, int n_slices, int polls, float& m) {
+// Waits while words keep coming: until `polls` looks in a row have brought none.
+__device__ __forceinline__ unsigned look_for_maxima(const unsigned* words, int n_slices, const int polls, float& m) {
   const int lane = threadIdx.x & 63, at = 4 * lane;
   u32x4 w = {kQuantUnset, kQuantUnset, kQuantUnset, kQuantUnset};
-  unsigned missing = 0;
-  for (;;) {
-    missing = 0;
+  auto unset = [&] {
+    unsigned bits = 0;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) missing |= (w[i] == kQuantUnset && at + i < n_slices ? 1u : 0u) << i;
-    if (polls-- <= 0 || !__any(missing != 0)) break;
+    for (int i = 0; i < 4; ++i) bits |= (w[i] == kQuantUnset && at + i < n_slices ? 1u : 0u) << i;
+    return bits;
+  };
+  unsigned missing = unset();
+  for (int left = polls; left > 0 && __any(missing != 0); --left) {
+    if (left < polls) __builtin_amdgcn_s_sleep(64);                     // 4096 clocks
     // (lanes beyond the last word look at the first ones; a line of words is whole lanes' worth)
     asm volatile("global_load_dwordx4 %0, %1, off sc1\n\ts_waitcnt vmcnt(0)"
                  : "=&v"(w) : "v"(words + (at < n_slices ? at : 0)) : "memory");
-    bool there = true;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) there &= w[i] != kQuantUnset || at + i >= n_slices;
-    if (!__all(there) && polls > 0) __builtin_amdgcn_s_sleep(64);       // 4096 clocks
+    const unsigned now = unset();
+    if (__any(now != missing)) left = polls;
+    missing = now;
   }
   m = 0.f;
 #pragma unroll
@@ -253,10 +262,28 @@ __device__ __forceinline__ unsigned look_for_maxima(const unsigned* words, int n
   return missing;
 }
 
+// The slice of the `turn`-th missing word of the wave, counted modulo their number; -1: none is missing.
+__device__ __forceinline__ int missing_slice(unsigned missing, unsigned turn) {
+  if (!__any(missing != 0)) return -1;
+  const int lane = threadIdx.x & 63, own = __popc(missing);
+  int up_to = own;
+#pragma unroll
+  for (int d = 1; d < 64; d *= 2) {
+    const int below = __shfl_up(up_to, d, 64);
+    if (lane >= d) up_to += below;
+  }
+  const int all = __shfl(up_to, 63, 64);
+  int rank = (int)(turn % (unsigned)all) - (up_to - own), at = -1;      // among this lane's
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+    if (missing >> i & 1 && rank-- == 0) at = 4 * lane + i;
+  return __shfl(at, __ffsll((unsigned long long)__ballot(at >= 0)) - 1, 64);
+}
+
 template <typename T, bool PAST>
 __global__ __launch_bounds__(kQuantOnceThreads, 4) void kv_quantize_once(QuantParams p) {
   __shared__ float red[2][kQuantOnceThreads / 64];
-  __shared__ unsigned char missing[64];
+  __shared__ int help;
   __shared__ u32x4 rest_s[kQuantLds * kQuantOnceThreads];               // [vector][thread]: each its own
   constexpr int PV = Elem<T>::kPerVec, N = kQuantHeld, THREADS = kQuantOnceThreads;
   const int tid = threadIdx.x;
@@ -292,26 +319,30 @@ __global__ __launch_bounds__(kQuantOnceThreads, 4) void kv_quantize_once(QuantPa
   m = block_max<THREADS>(m, red[0]);
   if (p.n_slices > 1) {
     unsigned* words = (unsigned*)p.partial + ((long long)(q.b * p.Hkv + q.hk) * 2 + q.which) * quant_words(p.n_slices);
-    if (tid < 64) {
-      if (tid == 0) __hip_atomic_store(words + blockIdx.x, __float_as_uint(m), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      float others;
-      missing[tid] = (unsigned char)look_for_maxima(words, p.n_slices, p.polls, others);
-      others = wave_max(others);
-      if (tid == 0) red[1][0] = others;
-    }
-    __syncthreads();
+    if (tid == 0) __hip_atomic_store(words + blockIdx.x, __float_as_uint(m), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    auto look = [&](int polls) {                                        // the maxima that are there, and a slice whose is not
+      if (tid < 64) {
+        float others;
+        const int slice = missing_slice(look_for_maxima(words, p.n_slices, polls, others), blockIdx.x);
+        others = wave_max(others);
+        if (tid == 0) { red[1][0] = others; help = slice; }
+      }
+      __syncthreads();
+    };
+    look(p.polls);
+    // The blocks that wait in vain share the missing slices: each takes the maximum of another one and publishes it, unless it
+    // is there by then (a maximum has the same bits whoever takes it).  So one word more is there when it looks again.
+    if (help >= 0)
+      do {
+        const float here = block_max<THREADS>(slice_absmax<T, THREADS, 4>(src, p, quant_slice<T>(p, help, blockIdx.y, blockIdx.z)), red[0]);
+        unsigned unset = kQuantUnset;
+        if (tid == 0)
+          __hip_atomic_compare_exchange_strong(words + help, &unset, __float_as_uint(here), __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                               __HIP_MEMORY_SCOPE_AGENT);
+        __syncthreads();                                                // `help` and `red` are free again
+        look(kQuantHelped);
+      } while (help >= 0);
     m = fmaxf(m, red[1][0]);
-    if (__any(missing[tid & 63] != 0)) {                                // the same in every wave
-      float rest = 0.f;
-      for (int s = 0; s < p.n_slices; ++s)
-        if (missing[s >> 2] >> (s & 3) & 1) {
-          const float here = slice_absmax<T, THREADS>(src, p, quant_slice<T>(p, s, blockIdx.y, blockIdx.z));
-          // (published by now: its block may be writing codes, and a caller may have put them where the source is)
-          const unsigned w = __hip_atomic_load(words + s, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-          rest = fmaxf(rest, w != kQuantUnset ? __uint_as_float(w) : here);
-        }
-      m = fmaxf(m, block_max<THREADS>(rest, red[0]));
-    }
   }
   const float mult = m > 0.f ? m / 448.0f : 1.0f;
   if (blockIdx.x == 0 && tid == 0) (q.which ? p.v_scale : p.k_scale)[q.b * p.Hkv + q.hk] = mult;
@@ -344,7 +375,7 @@ static void launch(QuantParams p, hipStream_t st) {
   constexpr long long held = (long long)kQuantOnceThreads * (kQuantHeld + kQuantLds);
   if (n_vec <= kQuantMaxSlices * held && heads * n_vec * 16 >= kQuantOnceBytes) {
     p.n_slices = (int)((n_vec + held - 1) / held);       // no more words than quant_slices, in whole vectors
-    if (p.polls < 0) p.polls = 64;
+    if (p.polls < 0) p.polls = 3 * p.n_slices > 2 * kNumCU ? 4 : 12;
     const dim3 grid(p.n_slices, 2 * p.Hkv, p.B);
     const int words = (int)heads * quant_words(p.n_slices);
     if (p.n_slices > 1)

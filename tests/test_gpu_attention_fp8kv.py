@@ -315,3 +315,36 @@ def test_two_large_quantisations_share_the_gpu(hippo):
     for ref, got in zip(alone, together):
         for x in got:
             assert all(torch.equal(a, b) for a, b in zip(ref, x))
+
+
+def test_large_quantisations_at_once_do_not_take_each_others_work(hippo):
+    """Three calls whose heads do not fit the chip together: blocks wait for maxima of slices that have no place yet, and share
+    those between them.  (Each taking all of them took 30 times as long as one call after the other; here 1.5 times.)"""
+    g = torch.Generator(device="cuda").manual_seed(8)
+    data = [torch.randn((2, 1, 8, 196000, 128), generator=g, device="cuda").to(torch.bfloat16) for _ in range(3)]
+    alone = [hippo.hippo_quantize_kv_e4m3(k, v) for k, v in data]
+    streams = [torch.cuda.Stream() for _ in data]
+    out = [[torch.empty_like(x) for x in a[:2]] for a in alone]
+
+    def run(streams):
+        got, begin, ends = [], torch.cuda.Event(enable_timing=True), []
+        torch.cuda.synchronize()
+        begin.record()
+        for s in set(streams):
+            s.wait_event(begin)
+        for _ in range(4):
+            for (k, v), (kc, vc), s in zip(data, out, streams):
+                got.append(hippo.hippo_quantize_kv_e4m3(k, v, k_codes=kc, v_codes=vc, stream=s))
+        for s in set(streams):
+            ends.append(torch.cuda.Event(enable_timing=True))
+            ends[-1].record(s)
+        torch.cuda.synchronize()
+        return max(begin.elapsed_time(e) for e in ends), got[-3:]
+
+    run(streams)
+    in_turn = min(run(streams[:1] * 3)[0] for _ in range(3))
+    for _ in range(3):
+        time, got = run(streams)
+        assert time < 5 * in_turn
+        for ref, x in zip(alone, got):
+            assert all(torch.equal(a, b) for a, b in zip(ref, x))
