@@ -510,8 +510,10 @@ __global__ __launch_bounds__(RB * TG * 64) void attn_partial_grid(AttnParams p) 
     }
     // A wide block's outputs leave as scaled fp16, as many bytes: its slices are half as long as those of two row chunks, and
     // twice as many rounded to bf16 were further from 64 bits (33K x 4 heads, 91 rows 2.71e-3 -> 2.74e-3; like this 2.17e-3).
-    // One power of two for the wave's channels of a row, from the largest finite one.
+    // One power of two for the wave's channels of a row, from the largest finite one.  Channels that lie 31 powers of two and
+    // more below it would keep fewer bits than in bf16, then none: such a row's leave as bf16, with a factor of -1 that says so.
     float up = 1.f;
+    bool scaled = true;
     if constexpr (SCALED) {
       float big = 0.f;
 #pragma unroll
@@ -528,7 +530,16 @@ __global__ __launch_bounds__(RB * TG * 64) void attn_partial_grid(AttnParams p) 
       }
       const int power = max(__builtin_amdgcn_frexp_expf(rows4_max(big)), -100) - 14;
       up = ldexpf(1.f, -power);
-      if (g == 0 && row < p.R) p.part_e[(slot * p.R + row) * TG + TGC] = ldexpf(1.f, power);
+      bool spread = false;
+#pragma unroll
+      for (int dd = 0; dd < DB / TG; ++dd)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const float o = acc[TGC + TG * dd][e];
+          spread |= o != 0.f && fabsf(o * up) < 0x1p-17f;
+        }
+      scaled = rows4_max(spread ? 1.f : 0.f) == 0.f;       // the same in all four lanes of the row
+      if (g == 0 && row < p.R) p.part_e[(slot * p.R + row) * TG + TGC] = scaled ? ldexpf(1.f, power) : -1.f;
     }
 #pragma unroll
     for (int dd = 0; dd < DB / TG; ++dd) {
@@ -549,7 +560,7 @@ __global__ __launch_bounds__(RB * TG * 64) void attn_partial_grid(AttnParams p) 
         typedef __attribute__((ext_vector_type(2))) float f32x2_t;
         const f32x2_t lo = {o[0], o[1]}, hi = {o[2], o[3]};
         uint2 w;
-        if constexpr (SCALED) {
+        if (SCALED && scaled) {
           w.x = __builtin_bit_cast(unsigned, __builtin_convertvector(lo * up, f16x2_t));
           w.y = __builtin_bit_cast(unsigned, __builtin_convertvector(hi * up, f16x2_t));
         } else {
@@ -854,8 +865,8 @@ __global__ __launch_bounds__(RB * TG * 64) void attn_partial_f32(AttnParams p) {
 
 // =================================================================================================
 // Merge of the KV slices: out = sum_s 2^(m_s - m*) o_s / sum_s 2^(m_s - m*) l_s
-// The slices' outputs o_s are fp32 (the fp32 kernel's), bf16 (the bf16 kernel's) or scaled fp16 (its blocks of more than 64
-// rows).
+// The slices' outputs o_s are fp32 (the fp32 kernel's), bf16 (the bf16 kernel's) or, of its blocks of more than 64 rows, fp16
+// with a factor, or bf16 with -1 in its place.
 // One block per (query row, KV head, batch element).  The slices are spread over the threads: first
 // the S weights (one slice per thread, block-wide max and sum), then thread (sg, vec) accumulates
 // 16-byte vector `vec` of the row over slices sg, sg + NSG, ... and the NSG groups meet in LDS.
@@ -874,17 +885,21 @@ __device__ __forceinline__ f32x4 part_o_load4(const void* base, long long elem) 
     return (f32x4){__uint_as_float(w.x), __uint_as_float(w.y), 0.f, 0.f};
   }
 }
+// weight * the output; kPartF16: `factor` is what the kernel stored beside it
 template <int PO>
-__device__ __forceinline__ f32x4 part_o_widen(f32x4 raw) {
-  if constexpr (PO == kPartF32) return raw;
-  else if constexpr (PO == kPartF16) {
-    const unsigned lo = __float_as_uint(raw[0]), hi = __float_as_uint(raw[1]);
-    const f16x2_t x = __builtin_bit_cast(f16x2_t, lo), y = __builtin_bit_cast(f16x2_t, hi);
-    return (f32x4){(float)x[0], (float)x[1], (float)y[0], (float)y[1]};
-  } else {
+__device__ __forceinline__ f32x4 part_o_weighed(f32x4 raw, float weight, float factor) {
+  if constexpr (PO == kPartF32) return raw * weight;
+  else {
     const unsigned x = __float_as_uint(raw[0]), y = __float_as_uint(raw[1]);
-    return (f32x4){__uint_as_float(x << 16), __uint_as_float(x & 0xffff0000u), __uint_as_float(y << 16),
-                   __uint_as_float(y & 0xffff0000u)};
+    f32x4 o = {__uint_as_float(x << 16), __uint_as_float(x & 0xffff0000u), __uint_as_float(y << 16), __uint_as_float(y & 0xffff0000u)};
+    if constexpr (PO == kPartF16) {
+      const f16x2_t lo = __builtin_bit_cast(f16x2_t, x), hi = __builtin_bit_cast(f16x2_t, y);
+      if (factor > 0.f) {
+        o = (f32x4){(float)lo[0], (float)lo[1], (float)hi[0], (float)hi[1]};
+        weight *= factor;
+      }
+    }
+    return o * weight;
   }
 }
 
@@ -909,12 +924,12 @@ __global__ __launch_bounds__(256) void attn_combine(AttnParams p) {
     const int s = min(sg + u * NSG, p.S - 1);             // past the last slice: a harmless repeat, not used
     pre[u] = part_o_load4<PO>(p.part_o, ((slot0 + s) * p.R + r) * D + vec * 4);
   }
-  // scaled outputs: the power of two of this thread's channels (16-channel blocks are dealt to the token groups in turn)
-  auto scale_of = [&](int s) { return p.part_e[((slot0 + s) * p.R + r) * kWideGroups + vec / 4 % kWideGroups]; };
-  float pre_e[PF];
+  // the factor of this thread's channels (16-channel blocks are dealt to the token groups in turn)
+  auto factor_of = [&](int s) { return p.part_e[((slot0 + s) * p.R + r) * kWideGroups + vec / 4 % kWideGroups]; };
+  float pre_e[PF] = {};
   if constexpr (PO == kPartF16)
 #pragma unroll
-    for (int u = 0; u < PF; ++u) pre_e[u] = scale_of(min(sg + u * NSG, p.S - 1));
+    for (int u = 0; u < PF; ++u) pre_e[u] = factor_of(min(sg + u * NSG, p.S - 1));
 
   // where the row's output goes: worked out while the loads are in flight (the division would otherwise
   // stand between the last barrier and the store)
@@ -938,9 +953,8 @@ __global__ __launch_bounds__(256) void attn_combine(AttnParams p) {
 #pragma unroll
     for (int u = 0; u < PF; ++u) {
       const int sl = sg + u * NSG;                        // < 64 whenever it is < S
-      float ws = __shfl(w, sl & 63, 64);
-      if constexpr (PO == kPartF16) ws *= pre_e[u];
-      if (sl < p.S) acc += part_o_widen<PO>(pre[u]) * ws;
+      const float ws = __shfl(w, sl & 63, 64);
+      if (sl < p.S) acc += part_o_weighed<PO>(pre[u], ws, pre_e[u]);
     }
   } else {
     // this thread's first slice statistics ride in the same trip
@@ -971,12 +985,12 @@ __global__ __launch_bounds__(256) void attn_combine(AttnParams p) {
 #pragma unroll
     for (int u = 0; u < PF; ++u) {
       const int sl = sg + u * NSG;
-      if (sl < p.S) acc += part_o_widen<PO>(pre[u]) * (PO == kPartF16 ? w_s[sl] * pre_e[u] : w_s[sl]);
+      if (sl < p.S) acc += part_o_weighed<PO>(pre[u], w_s[sl], pre_e[u]);
     }
 #pragma unroll 4
     for (int sl = sg + PF * NSG; sl < p.S; sl += NSG) {
-      const f32x4 o = part_o_widen<PO>(part_o_load4<PO>(p.part_o, ((slot0 + sl) * p.R + r) * D + vec * 4));
-      acc += o * (PO == kPartF16 ? w_s[sl] * scale_of(sl) : w_s[sl]);
+      acc += part_o_weighed<PO>(part_o_load4<PO>(p.part_o, ((slot0 + sl) * p.R + r) * D + vec * 4), w_s[sl],
+                                PO == kPartF16 ? factor_of(sl) : 0.f);
     }
   }
   acc_s[sg][vec] = acc;

@@ -250,10 +250,12 @@ struct AttnParams {
   const void* v;
   void* out;
   float* lse;       // may be null
-  void* part_o;     // [B, Hkv, S, R, D] unnormalised partial outputs: bf16 from the bf16 kernel, fp32 from the fp32 kernel
+  void* part_o;     // [B, Hkv, S, R, D] unnormalised partial outputs: fp32 from the fp32 kernel, bf16 from the bf16 kernel, and
+                    // from its blocks of more than 64 rows 16 bits that part_e explains
   float* part_m;    // [B, Hkv, S, R] running maxima (log2 domain)
   float* part_l;    // [B, Hkv, S, R] partial denominators
-  float* part_e;    // [B, Hkv, S, R, 2] what the scaled fp16 outputs of blocks of more than 64 rows are multiplied with
+  float* part_e;    // [B, Hkv, S, R, 2] of blocks of more than 64 rows: what the outputs are multiplied with, which are fp16,
+                    // or -1: they are bf16
   int B, q_len, H, Hkv, G, R;
   int ctx_len, n_total;
   long long sb, sh, sn;   // element strides of K and V

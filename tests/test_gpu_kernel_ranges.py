@@ -707,3 +707,26 @@ def test_short_videos_in_a_workspace_without_room_for_finer_cuts(hippo, H, Hkv, 
         hippo.hippo_score_tokens(qd, kd, vid, flags=hippo.SCORE_ACCUMULATE_ONLY, attn_mass_inout=mass, workspace=ws[:need - short])
         assert torch.all(ws[need - short:] == 0x5A)
         assert_close(host(mass), oracle.s_attn(q, k, 0, n), "bf16", "%d bytes short" % short)
+
+
+@pytest.mark.parametrize("d, B, Hkv, q_len, G, ctx", [(128, 8, 8, 13, 5, 8200), (64, 8, 8, 13, 7, 16390), (128, 2, 32, 12, 8, 8201)])
+def test_65_to_96_rows_keep_channels_of_any_unit(hippo, d, B, Hkv, q_len, G, ctx):
+    """Channels far below their neighbours keep the bits that bf16 slices give them: each is compared in its own unit."""
+    g = torch.Generator(device="cuda").manual_seed(ctx + d)
+    k, v = (torch.randn((B, Hkv, ctx + q_len, d), generator=g, device="cuda").to(torch.bfloat16) for _ in range(2))
+    assert 4 * k.numel() > 256 << 20
+    q = torch.randn((B, q_len, Hkv * G, d), generator=g, device="cuda").to(torch.bfloat16)
+    unit = np.ones((B, Hkv, d))
+    unit[0, 0, ::2], unit[0, 1, 1::4], unit[1, 0, :d // 2], unit[1, 1, 5] = 2.0 ** -33, 2.0 ** -45, 2.0 ** -90, 2.0 ** 60
+    unit[0, 2], unit[0, 2, 9] = 2.0 ** -105, 0.0
+    v *= torch.from_numpy(unit).cuda().unsqueeze(2)
+    out = hippo.hippo_verify_attention(q, k, v, ctx)
+    for b, hk in ((0, 0), (0, 1), (1, 0), (1, 1), (0, 2)):
+        heads, at = slice(hk * G, hk * G + G), np.flatnonzero(unit[b, hk])
+        own = unit[b, hk, at]
+        ref, _ = oracle.attention(host(q[b:b + 1, :, heads].contiguous()), host(k[b:b + 1, hk:hk + 1].contiguous()),
+                                  np.pad(host(v[b:b + 1, hk:hk + 1][..., at].contiguous()) / own, ((0, 0),) * 3 + ((0, d - len(at)),)),
+                                  ctx)
+        got = host(out[b:b + 1, :, heads].contiguous())
+        assert_close(got[..., at] / own, ref[..., :len(at)], "bf16", "head %d of %d" % (hk, b))
+        assert not got[..., unit[b, hk] == 0].any()
