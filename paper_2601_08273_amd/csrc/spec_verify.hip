@@ -66,12 +66,14 @@ constexpr int kSdThreads = 256;
 constexpr int kSdWaves = kSdThreads / 64;
 constexpr int kSdPerThread = kSdSeg / kSdThreads;   // 32 logits per thread, held in registers
 constexpr int kSdLdsStats = 1024;                   // segment statistics staged in LDS (16 KB)
-// The second launch has few blocks, whose chain of loads, exponentials and sums is what takes the time: sixteen waves share
+// The second launch mostly has few blocks, whose chain of loads, exponentials and sums is what takes the time: sixteen waves share
 // a segment, one or two vectors a thread.  (The drawing at its end keeps to the first four waves.)  us a call from a graph, four
 // waves -> sixteen, with the maximum alone in the first launch: 4 x 11 rows of 152064 bf16 words 15.4 -> 13.1, fp32 16.0 ->
-// 14.0, 7 x 25 rows 27.1 -> 21.7, one sequence of 3 rows of 32000 words 12.0 -> 10.3, 16 x 11 rows 27.5 -> 26.4.
+// 14.0, 7 x 25 rows 27.1 -> 21.7, one sequence of 3 rows of 32000 words 12.0 -> 10.3.  Up to a block a compute unit: there the
+// slowest of 56 random calls of 8 to 64 sequences took 0.90 of the time, but with more blocks eight of 27 took 1.04 to 1.17 (46
+// sequences x 9 rows of 185880 bf16 words 45.2 -> 53.0, 36 x 3 of 138008 23.7 -> 26.9, 17 x 9 of 134312 fp32 words 27.5 -> 28.7):
+// the first part, which every block repeats, then takes the units four times the waves.
 constexpr int kSdCellThreads = 1024;
-constexpr int kSdCellPerThread = kSdSeg / kSdCellThreads;
 
 // Stores and loads of what other blocks of the launch read or wrote: device scope, past the caches of an XCD.
 __device__ __forceinline__ void store_agent(float* at, float v) {
@@ -148,7 +150,9 @@ __global__ __launch_bounds__(kSdThreads) void sd_row_stats(SpecParams p) {
   }
 
   float z = 0.f;
-  if (!GREEDY && m > -INFINITY) {
+  // (p.c is 0 in greedy decoding.  Asked for all the same: without these exponentials the compiler keeps the comparisons above in
+  // scalar registers, and greedy calls of 10 to 60 bf16 sequences take 1.02 to 1.04 of the time.)
+  if (p.c > 0.f && m > -INFINITY) {
 #pragma unroll
     for (int i = 0; i < kSdPerThread; ++i) z += fast_exp2((x[i] - m) * p.c);
   }
@@ -278,8 +282,8 @@ __device__ __forceinline__ void draw_word(const SpecParams& p, const int b, cons
 
 // Eq. 1 for all positions, first rejection, and (sampling mode) the cell sums of the distribution
 // the next token is drawn from.  Blocks of one sequence repeat the small first part identically.
-template <typename T>
-__global__ __launch_bounds__(kSdCellThreads) void sd_cells(SpecParams p) {
+template <typename T, int THREADS>
+__global__ __launch_bounds__(THREADS) void sd_cells(SpecParams p) {
   __shared__ float sh_mp[kSdMaxGamma + 1], sh_zp[kSdMaxGamma + 1], sh_mq[kSdMaxGamma], sh_zq[kSdMaxGamma];
   __shared__ int sh_argp[kSdMaxGamma + 1];
   __shared__ int sh_rej[kSdMaxGamma];
@@ -310,7 +314,7 @@ __global__ __launch_bounds__(kSdCellThreads) void sd_cells(SpecParams p) {
   const int n_stats = (greedy ? p.gamma + 1 : p.n_rows) * p.n_seg;
   const bool staged = n_stats <= kSdLdsStats;
   if (staged) {
-    for (int i = tid; i < n_stats; i += kSdCellThreads) sh_stats[i] = st[i];
+    for (int i = tid; i < n_stats; i += THREADS) sh_stats[i] = st[i];
     __syncthreads();
   }
   // merged statistics of every row: one row per group of 16 lanes (lanes over segments), so the
@@ -318,7 +322,7 @@ __global__ __launch_bounds__(kSdCellThreads) void sd_cells(SpecParams p) {
   {
     const int n_r = greedy ? p.gamma + 1 : p.n_rows;
     const int grp = tid >> 4, gl = tid & 15;
-    for (int row = grp; row < n_r; row += kSdCellThreads / 16) {
+    for (int row = grp; row < n_r; row += THREADS / 16) {
       const SegStat* rs = staged ? sh_stats + row * p.n_seg : st + (long long)row * p.n_seg;
       float m = -INFINITY;
       int arg = 0x7fffffff;
@@ -386,16 +390,16 @@ __global__ __launch_bounds__(kSdCellThreads) void sd_cells(SpecParams p) {
   if (seg == 0 && tid == 0) p.n_accept[b] = j;
 
   constexpr int VEC = Elem<T>::kPerVec;
-  constexpr int NV = kSdCellPerThread / VEC, WAVES = kSdCellThreads / 64;
+  constexpr int NV = kSdSeg / THREADS / VEC, WAVES = THREADS / 64;
   constexpr int CPS = NV * WAVES;                // cells per segment
   static_assert(CPS == kSdPerThread / VEC * kSdWaves, "a cell is a wave's vectors, whatever the waves of the block");
   const int v0 = seg * kSdSeg;
-  float xp[kSdCellPerThread];
-  load_segment<T, kSdCellThreads>(pl + (long long)j * p.p_stride, v0, p.V, xp);
+  float xp[kSdSeg / THREADS];
+  load_segment<T, THREADS>(pl + (long long)j * p.p_stride, v0, p.V, xp);
   float sp[NV], sr[NV];
   if (rejected) {
-    float xq[kSdCellPerThread];
-    load_segment<T, kSdCellThreads>(ql + (long long)j * p.q_stride, v0, p.V, xq);
+    float xq[kSdSeg / THREADS];
+    load_segment<T, THREADS>(ql + (long long)j * p.q_stride, v0, p.V, xq);
 #pragma unroll
     for (int v = 0; v < NV; ++v) {
       float a = 0.f, r = 0.f;
@@ -435,7 +439,7 @@ __global__ __launch_bounds__(kSdCellThreads) void sd_cells(SpecParams p) {
   __syncthreads();
   if (tid == 0) sh_j = __hip_atomic_fetch_add(p.arrived + b, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   __syncthreads();
-  if (sh_j != p.n_seg - 1 || tid >= kSdThreads) return;
+  if (sh_j != p.n_seg - 1 || tid >= kSdThreads) return;       // (the first four waves draw)
   draw_word<T>(p, b, Chosen{j, rejected ? 1 : 0, mp, inv_zp, mq, inv_zq}, u_draw);
 }
 
@@ -446,7 +450,9 @@ hipError_t launch_typed(const SpecParams& p, hipStream_t st) {
   const dim3 grid(p.n_seg, rows, p.B);
   if (greedy) sd_row_stats<T, true><<<grid, kSdThreads, 0, st>>>(p);
   else sd_row_stats<T, false><<<grid, kSdThreads, 0, st>>>(p);
-  sd_cells<T><<<dim3(greedy ? 1 : p.n_seg, p.B), kSdCellThreads, 0, st>>>(p);
+  const dim3 cells(greedy ? 1 : p.n_seg, p.B);
+  if ((long long)cells.x * p.B <= kNumCU) sd_cells<T, kSdCellThreads><<<cells, kSdCellThreads, 0, st>>>(p);
+  else sd_cells<T, kSdThreads><<<cells, kSdThreads, 0, st>>>(p);
   return hipGetLastError();
 }
 

@@ -119,6 +119,25 @@ def test_sampling_at_the_edges_of_a_block_s_words(hippo, dtype):
 
 
 @pytest.mark.parametrize("dtype", ["fp32", "bf16"])
+@pytest.mark.parametrize("B, V", [(32, 8 * 8192), (33, 8 * 8192), (86, 2 * 8192 + 8), (257, 4104), (10, 25 * 8192 + 16)])
+def test_many_sequences_are_judged_as_each_alone(hippo, dtype, B, V):
+    # 256 blocks of cells and more, which have four waves and not sixteen; a second segment of a few words, and none
+    g = torch.Generator(device="cuda").manual_seed(B)
+    p, q = (torch.randn((B, 3 - i, V), generator=g, device="cuda").to(torch.bfloat16 if dtype == "bf16" else torch.float32)
+            for i in range(2))
+    tok = torch.randint(0, V, (B, 2), generator=g, device="cuda", dtype=torch.int32)
+    u, us = torch.rand((B, 2), generator=g, device="cuda") ** 2, torch.rand((B,), generator=g, device="cuda")
+    for temperature in (0.7, 0.0):
+        out = hippo.hippo_spec_verify(p, q, tok, u, us, temperature, want_alpha=True)
+        if temperature:
+            assert 0 < int(out[0].sum()) < 2 * B                      # some accepted, some not
+        for lo in range(0, B, 7):
+            few = slice(lo, lo + 7)
+            alone = hippo.hippo_spec_verify(p[few], q[few], tok[few], u[few], us[few], temperature, want_alpha=True)
+            assert all(torch.equal(a, b[few]) for a, b in zip(alone, out))
+
+
+@pytest.mark.parametrize("dtype", ["fp32", "bf16"])
 @pytest.mark.parametrize("B,V", [(1, 8), (70, 8200), (3, 1 << 20)])      # one block, two a sequence, the most there are
 def test_one_workspace_for_call_after_call(hippo, dtype, B, V):
     # the sequences' counts of finished blocks live in the workspace: whatever it holds before, and from replay to replay
