@@ -1996,9 +1996,9 @@ __global__ __launch_bounds__(256) void fuse_scores_reg(ScoreParams p) {
 // =================================================================================================
 int score_token_tile(int dtype) { return dtype == HIPPO_DTYPE_BF16 ? kSaMfmaTile : kSaF32Tile; }
 
-// Row splits of the s_attn sweeps (bf16 path): enough blocks for two per compute unit, which is what
-// lets the MFMA and the exp work of different waves overlap; a split keeps at least two 64-row chunks.
-// How many runs the query rows of a KV head are cut into (one block of the sweeps per run).  A compute
+// How many runs the query rows of a KV head are cut into (one block of the sweeps per run).  In bf16 two blocks a compute unit
+// let the MFMA and the exp work of different waves overlap, with runs of at least two 64-row chunks; where even those leave
+// units without a block, finer cuts follow below.  A compute
 // unit holds two sweep blocks; measured at the 16K shape, two co-resident blocks take 2.1 us per 64-row
 // chunk each, a block alone 1.29 us, and a block's start (keys, first chunk) 3.2 resp. 2.5 us.  The
 // blocks are dealt to the compute units in rounds, so what counts is the busiest unit: ceil(blocks / 256)
@@ -2038,19 +2038,32 @@ int score_row_splits(int dtype, long long blocks_unsplit, int rows_per_kv_head, 
       best_cost = cost;
     }
   }
-  // Short videos leave compute units without a block of the sweeps: finer cuts, up to a block on each (of 64 channels on seven
-  // eighths of them: 3780 tokens x 14 heads x 2 in two layers, 240 blocks for 120, 18.0 -> 18.5).  A block that is alone costs as
-  // above, but its first two chunks land together (one saves 0.6 us of two), and the more blocks, the longer their keys take,
-  // which each of a tile's fetches.  us a call from a graph, the cut above -> this: 4096 tokens x 14 heads, 64 text rows 17.9 ->
-  // 16.1 (3 runs -> 7), 1848 x 14, 183 rows 22.9 -> 18.1, 1400 x 28, 121 rows 22.6 -> 19.9, 3952 x 64, 17 rows 23.1 -> 21.1;
-  // 210 random calls 0.98 of the time; where it does not pay: 1824 x 28 in two layers, 34 rows, 4 runs for 2 18.0 -> 20.0.
+  // Short videos leave compute units without a block of the sweeps: finer cuts, up to a block on seven eighths of them (64
+  // channels: 3780 tokens x 14 heads x 2 in two layers, 240 blocks for 120, 18.0 -> 18.5) or, of 128 channels in runs of three
+  // and more chunks, on all.  A block that is alone costs as above, but its first two chunks land together (one saves 0.6 us
+  // of two), and the more blocks, the longer their keys take, which each of a tile's fetches.  us a call from a graph, the cut
+  // above -> this: 4096 tokens x 14 heads, 64 text rows 17.9 -> 16.1 (3 runs -> 7), 1848 x 14, 183 rows 22.9 -> 18.1, 1400 x 28,
+  // 121 rows 22.6 -> 19.9.  Where that saves little, the column partials of more runs and the blocks that riders wait for cost as
+  // much: not for a quarter or a fifth of a run's chunks (64 channels, four chunks -> three, 4 -> 5 runs 20.9 -> 23.8), not for one
+  // chunk on three quarters of the units and more (two for three: 6825 x 28, 26 rows, 216 blocks 25.2 -> 28.4, 1836 x 64 in two
+  // layers, 17 rows, 256 blocks 20.4 -> 22.1), not for one and more than two runs more of 64 channels (3 -> 6 and 4 -> 8: 46
+  // calls 0.997, the slowest 1.08).  Random calls that it cuts finer, 959 without these three conditions 0.934 of the time, 38 of
+  // them slower by 2 to 14 %; 550 others with them 0.922, 13 by 2 to 4 %.
   auto alone = [&](int rs) {
     const int cpb = (chunks + rs - 1) / rs;
     return (cpb == 1 ? 1.89 : cpb * 1.29) + 2.5 + (head_dim == 128 ? 0.008 : 0.005) * (double)(blocks_unsplit * rs);
   };
   if (!finer) return best;
-  for (int rs = best + 1; rs <= 8 && rs <= chunks && blocks_unsplit * rs <= (head_dim == 128 ? kNumCU : kNumCU * 7 / 8); ++rs)
+  const int former = best, former_cpb = (chunks + best - 1) / best;
+  for (int rs = best + 1; rs <= 8 && rs <= chunks; ++rs) {
+    const int cpb = (chunks + rs - 1) / rs;
+    const long long blocks = blocks_unsplit * rs;
+    if (blocks > (head_dim == 128 && cpb >= 3 ? kNumCU : kNumCU * 7 / 8)) continue;
+    if (3 * cpb > 2 * former_cpb) continue;
+    if (former_cpb - cpb == 1 && 4 * blocks >= 3 * kNumCU) continue;
+    if (head_dim != 128 && former_cpb == 2 && rs - former > 2) continue;
     if (alone(rs) < alone(best) * 0.97) best = rs;
+  }
   return best;
 }
 

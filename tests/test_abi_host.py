@@ -182,14 +182,32 @@ def test_score_argument_errors(lib):
     assert _score(lib, kv, h.video_desc(65535, 16, 16, 0), seq_len=65535 * 256, ws_bytes=4096) == h.ERR_WORKSPACE_TOO_SMALL
 
 
+@pytest.mark.parametrize("H, Hkv, d, n, L, layers, runs", [
+    # one chunk of three on three quarters of the compute units and more; of fewer
+    (64, 8, 128, 1836, 17, 2, 1), (28, 4, 128, 7680, 21, 1, 1), (28, 4, 128, 6825, 26, 1, 1), (28, 4, 128, 5120, 26, 1, 2),
+    (14, 2, 64, 4600, 128, 1, 4), (14, 2, 64, 4600, 184, 1, 6), (4, 2, 64, 3360, 161, 1, 3),  # a chunk of four; two of six; six runs
+    (14, 2, 64, 4096, 64, 1, 7), (28, 4, 128, 1400, 121, 1, 7), (28, 4, 128, 7000, 40, 1, 2),
+])
+def test_runs_of_rows_of_short_videos(lib, H, Hkv, d, n, L, layers, runs):
+    """Finer cuts where they save a third of a run's chunks and more: the column partials that are asked for say how many runs
+    there are."""
+    al = lambda x: (x + 255) // 256 * 256
+    rows, tiles = H * L * layers, (n + 255) // 256
+    rest = 2 * al(rows * tiles * 4) + al(rows * 4) + 3 * al(n * 4)
+    need = lib.hippo_score_layers_workspace_bytes(C.byref(_kv(n_q_heads=H, n_kv_heads=Hkv, head_dim=d)),
+                                                  C.byref(h.video_desc(1, 1, n, 0)), L, layers)
+    assert need - rest == al(layers * Hkv * runs * n * 4)
+
+
 def test_a_workspace_for_a_longer_video_serves_a_shorter_one(lib):
     """The finer cuts of short videos take more column partials than some longer ones need: less is enough without them."""
     import torch
     if torch.cuda.is_available():
         pytest.skip("what passes the checks is launched")
     for (q_heads, heads, d), larger, smaller, least in (
-            ((16, 4, 64), (5, 3, 6, 134, 2), (5, 3, 6, 116, 2), 57600), ((16, 4, 64), (31, 12, 5, 42, 4), (31, 12, 5, 42, 3), 249600),
-            ((4, 4, 64), (113, 7, 5, 102, 2), (91, 7, 5, 102, 2), 228864),
+            ((16, 2, 64), (492, 3, 4, 26, 1), (492, 3, 4, 18, 1), 175360),
+            ((8, 1, 128), (10, 11, 21, 29, 4), (10, 11, 21, 29, 3), 142592),
+            ((1, 1, 64), (506, 3, 9, 139, 2), (331, 3, 9, 139, 2), 258816),
             ((32, 8, 128), (10, 14, 4, 118, 1), (10, 11, 4, 118, 1), 137216)):
         kv = _kv(n_q_heads=q_heads, n_kv_heads=heads, head_dim=d)
         ask = lambda f, gh, gw, l, n: lib.hippo_score_layers_workspace_bytes(C.byref(kv), C.byref(h.video_desc(f, gh, gw, 0)), l, n)
