@@ -358,7 +358,11 @@ __global__ __launch_bounds__(kQuantOnceThreads, 4) void kv_quantize_once(QuantPa
 // and 30.7 -> 28.0 (64 of 4K), 78 39 -> 33, 129 61 -> 49, 781 371 -> 250; from the last-level cache: 23 13.7 -> 14.5, 32 17.6 ->
 // 15.9, 64 31.6 -> 25.9.  Slices of 64 KB, more blocks, lose to two launches at 32 MiB (23.6) and above.
 // Fetched past the caches, up to 256 MiB are 2 % faster from HBM and 3 to 10 % slower where that cache holds them.
+// Many short heads leave a block little to hold, and two launches have more blocks on a compute unit.  By the bytes of a head,
+// us: 13 KB (2048 x 102 rows x 64) 23.7 -> 36.3, 15 KB 26.8 -> 36.8, 26 KB 24.2 -> 22.8, 28 KB 43.7 -> 42.2, 36 KB 55.3 -> 46.4; of
+// 256 MiB and more 28 KB 171 -> 240, 35 KB 94 -> 117, 42 KB 269 -> 276, 47 KB 302 -> 289, 52 KB 148 -> 131.
 constexpr long long kQuantOnceBytes = 36ll << 20, kQuantPastBytes = 256ll << 20;
+constexpr long long kQuantOnceHead = 24ll << 10, kQuantPastHead = 44ll << 10;
 
 int quant_slices(int n_rows, int head_dim) {
   // about 16 KB of codes per block, at most one slice per thread of the second reduction
@@ -373,7 +377,8 @@ template <typename T>
 static void launch(QuantParams p, hipStream_t st) {
   const long long n_vec = (long long)p.n_rows * (p.D / Elem<T>::kPerVec), heads = 2ll * p.Hkv * p.B;
   constexpr long long held = (long long)kQuantOnceThreads * (kQuantHeld + kQuantLds);
-  if (n_vec <= kQuantMaxSlices * held && heads * n_vec * 16 >= kQuantOnceBytes) {
+  const bool past = heads * n_vec * 16 >= kQuantPastBytes;
+  if (n_vec <= kQuantMaxSlices * held && heads * n_vec * 16 >= kQuantOnceBytes && n_vec * 16 >= (past ? kQuantPastHead : kQuantOnceHead)) {
     p.n_slices = (int)((n_vec + held - 1) / held);       // no more words than quant_slices, in whole vectors
     if (p.polls < 0) p.polls = 3 * p.n_slices > 2 * kNumCU ? 4 : 12;
     const dim3 grid(p.n_slices, 2 * p.Hkv, p.B);
@@ -381,7 +386,7 @@ static void launch(QuantParams p, hipStream_t st) {
     if (p.n_slices > 1)
       hipLaunchKernelGGL(quant_clear, dim3((words + kQuantThreads - 1) / kQuantThreads), dim3(kQuantThreads), 0, st,
                          (unsigned*)p.partial, words);
-    if (heads * n_vec * 16 >= kQuantPastBytes)
+    if (past)
       hipLaunchKernelGGL((kv_quantize_once<T, true>), grid, dim3(kQuantOnceThreads), 0, st, p);
     else
       hipLaunchKernelGGL((kv_quantize_once<T, false>), grid, dim3(kQuantOnceThreads), 0, st, p);

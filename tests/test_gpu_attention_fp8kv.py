@@ -289,6 +289,30 @@ def test_large_sources_are_quantised_as_their_heads_are(hippo, B, Hkv, n, d, dty
         assert torch.all(codes[:, :, :, n:] == 0x7F)
 
 
+@pytest.mark.parametrize("B, Hkv, n, d, n_parts", [(64, 32, 102, 64, 2), (260, 32, 108, 128, 13)])
+def test_many_short_heads_take_no_longer_together(hippo, B, Hkv, n, d, n_parts):
+    # more than 36 MiB and more than 256 MiB in heads that are too short for a block of the one sweep: not slower than in parts
+    g = torch.Generator(device="cuda").manual_seed(n)
+    k, v = (torch.randn((B, Hkv, n, d), generator=g, device="cuda").to(torch.bfloat16) for _ in range(2))
+    parts = [slice(i, i + B // n_parts) for i in range(0, B, B // n_parts)]
+    calls = [lambda: [hippo.hippo_quantize_kv_e4m3(k, v)], lambda: [hippo.hippo_quantize_kv_e4m3(k[p], v[p]) for p in parts]]
+    whole, apart = calls[0]()[0], calls[1]()
+    assert all(torch.equal(x, torch.cat([part[i] for part in apart])) for i, x in enumerate(whole))
+    times = []
+    for call in calls:
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph):
+            for _ in range(10):
+                call()
+        best = []
+        for _ in range(5):
+            begin, end = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+            graph.replay(), begin.record(), graph.replay(), end.record(), torch.cuda.synchronize()
+            best.append(begin.elapsed_time(end))
+        times.append(min(best))
+    assert times[0] < 1.05 * times[1]
+
+
 def test_quantised_heads_of_the_most_slices(hippo):
     # 256 slices of 192 KB; a row of zeros more, which changes no maximum, takes two launches
     g = torch.Generator(device="cuda").manual_seed(5)
