@@ -183,11 +183,12 @@ PyObject* score(long long n_layers, const Tensor& q0, const Tensor& k0, const vo
     emb_dim = emb.size(2);
     emb_stride = emb.stride(1);
     // What the kernels take for granted of embeddings that they read: the cache's type, channels side by side, batch elements
-    // N_v tokens apart.  (The stride of a single element is nobody's: it may be cut from a longer sequence.)
+    // N_v tokens apart.  (The stride of a single element is nobody's: it may be cut from a longer sequence.  Elements beyond the
+    // caches' are nobody's either.)
     if (!(flags & HIPPO_SCORE_ACCUMULATE_ONLY) && (flags & (HIPPO_SCORE_TEMP | HIPPO_SCORE_SPA))) {
       REQUIRE(emb.dim() == 3 && emb.stride(2) == 1 && emb.scalar_type() == k0.scalar_type());
-      REQUIRE(emb.size(0) == k0.size(0) && emb.size(1) >= n_vis);
-      REQUIRE(emb.size(0) == 1 || emb.stride(0) == n_vis * emb.stride(1));
+      REQUIRE(emb.size(0) >= k0.size(0) && emb.size(1) >= n_vis);
+      REQUIRE(k0.size(0) == 1 || emb.stride(0) == n_vis * emb.stride(1));
     }
   }
   const Tensor ws = workspace(ws_o, q0, [&] { return lib.hippo_score_layers_workspace_bytes(&kv, &vid, (int32_t)L, (int32_t)n_layers); });

@@ -100,6 +100,16 @@ def test_embeddings_that_the_kernels_would_misread(B, emb):
         h.hippo_score_tokens_layers([q, q], [k, k], VID, **given)
 
 
+@pytest.mark.parametrize("B, emb", [(1, embeddings(B=2)), (2, embeddings(B=3)), (1, embeddings(B=2, n=40))])
+def test_more_embeddings_than_the_caches_have_elements(B, emb):
+    given = dict(emb=emb, scores_out=torch.zeros((B, 32)), workspace=torch.zeros(1 << 16, dtype=torch.uint8))
+    q, k = queries(B=B), cache(B=B, N=20)
+    with pytest.raises((h.HippoError, RuntimeError)):       # (without a GPU, refused by the stream it asks for)
+        h.hippo_score_tokens(q, k, VID, **given)
+    with pytest.raises((h.HippoError, RuntimeError)):
+        h.hippo_score_tokens_layers([q, q], [k, k], VID, **given)
+
+
 def test_embeddings_that_no_term_reads_are_not_looked_at():
     with pytest.raises((h.HippoError, RuntimeError)):       # (without a GPU, refused by the stream it asks for)
         h.hippo_score_tokens_layers([queries()], [cache(N=20)], VID, emb=embeddings(n=31, dtype=torch.float32),
