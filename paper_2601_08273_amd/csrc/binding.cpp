@@ -350,7 +350,8 @@ PyObject* attention_paged(PyObject* const* a) {
   const Tensor &k = tensor(a[2]), &v = tensor(a[3]), &table = tensor(a[4]);
   REQUIRE(k.dim() == 4 && k.stride(3) == 1);
   REQUIRE(same_layout(v, k));
-  REQUIRE(table.scalar_type() == at::kInt && table.is_contiguous() && table.dim() == 2 && table.size(0) == c.q.size(0));
+  REQUIRE(table.scalar_type() == at::kInt && table.is_contiguous() && table.dim() >= 2 && table.size(0) == c.q.size(0));
+  REQUIRE(table.numel() == table.size(0) * table.size(1));     // [B, max_pages], or with dimensions of 1 behind
   hippo_paged_kv_desc pd;
   pd.batch = (int32_t)c.q.size(0);
   pd.n_q_heads = (int32_t)c.q.size(2);

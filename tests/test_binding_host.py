@@ -34,6 +34,7 @@ VID = h.video_desc(2, 4, 4, 2)
     (lambda: h.hippo_verify_attention_fp8kv(queries(), cache(dtype=torch.uint8), cache(dtype=torch.uint8),
                                             torch.ones(1, 3), torch.ones(1, 3), 38), AssertionError),
     (lambda: h.hippo_verify_attention_paged(queries(), cache(), cache(), torch.zeros((1, 3)), 38), AssertionError),
+    (lambda: h.hippo_verify_attention_paged(queries(), cache(), cache(), torch.zeros((1, 3, 2), dtype=torch.int32), 38), AssertionError),
     (lambda: h.hippo_score_tokens(queries(), cache(), (2, 4, 4, 2, 5, 5)), TypeError),
     (lambda: h.hippo_score_tokens(queries(), cache()[0], VID), AssertionError),
     (lambda: h.hippo_score_tokens(queries(), cache(), VID, scores_out=queries(), workspace=queries(),
@@ -128,6 +129,13 @@ def test_layers_come_in_anything_with_a_length_and_an_index(as_layers):
     for no_layers in (torch.tensor(1.0), {queries()}, iter([queries()]), None):
         with pytest.raises(TypeError):
             h.hippo_score_tokens_layers(no_layers, [cache()], VID, **given)
+
+
+def test_page_tables_with_a_dimension_of_one_behind():
+    pool = cache(N=2)
+    with pytest.raises((h.HippoError, RuntimeError)):       # (without a GPU, refused by the stream it asks for)
+        h.hippo_verify_attention_paged(queries(), pool, pool, torch.zeros((1, 3, 1), dtype=torch.int32), 38,
+                                       workspace=torch.zeros(1 << 16, dtype=torch.uint8))
 
 
 def test_why_the_binding_cannot_be_imported_is_said(monkeypatch):
