@@ -60,7 +60,7 @@ int plan_attention(int call, const hippo_kv_desc* kv, int q_len, int n_total, in
   if ((long long)G * q_len > 4096) return HIPPO_ERR_BAD_SHAPE;
   pl->R = G * q_len;
   const bool f32 = kv->dtype == HIPPO_DTYPE_F32;
-  // A block takes at most 64 rows of a 16- or 8-bit cache: more go in equal chunks, the same slices and tiles in every
+  // A block takes at most 64 rows of a 16- or 8-bit cache (96 of a large bf16 one, below): more go in equal chunks, the same slices and tiles in every
   // cache format (chunks of 64 and a rest -> equal ones, us a call with K and V in the last-level cache / from HBM: 33K x 4
   // heads, 91 rows 23.3 -> 21.0 / 28.0 -> 26.4; 8K, 91 rows 14.4 -> 13.6 / 14.5 -> 13.6; 2 x 8 heads x 20K, 72 rows 40.1 -> 35.9 /
   // 54.2 -> 53.4; 8-bit 33K, 91 rows 24.6 -> 20.7 / 25.2 -> 21.5).  The fp32 kernel takes 65 to 128 in one chunk: two chunks
@@ -82,12 +82,20 @@ int plan_attention(int call, const hippo_kv_desc* kv, int q_len, int n_total, in
                          (num_splits > 0 || kNumCU / heads <= fit);
   // 65 to 96 rows of a bf16 cache that no cache of the chip holds go in one block too: the second chunk's blocks keep half the
   // transfers in flight on what the first chunk's fetch.  us a call, two chunks -> one: 4 x 8 heads x 128 x 37K, 72 rows 149 ->
-  // 115, from pages 169 -> 119, 96 rows 147 -> 126; 4 x 4 x 33K, 70 rows 71 -> 57; 64 x 8 x 1100, 91 rows 145 -> 133; 64
-  // channels, 4 x 8 x 37K, 72 rows 94 -> 76.  Of a cache that the last-level cache can hold not: 33K x 4, 91 rows of eight
+  // 115, from pages 169 -> 119, 96 rows 147 -> 126; 4 x 4 x 33K, 70 rows 71 -> 57; 64 channels, 4 x 8 x 37K, 72 rows 94 -> 76.
+  // Of a cache that the last-level cache can hold not: 33K x 4 heads, 91 rows of eight
   // layers in turn 24.9 and 24.8, from pages 27.4 and 25.7, but of one layer 27.1 against 29.8; 16K 16.4 against 19.3.
+  // Nor where the heads (batch elements x KV heads) come in a second round and the chunks of a head on one XCD, at the same
+  // time, so that its L2 serves the second chunk: KV heads a multiple of 8, up to 160, of 64 channels (two chunks' time = 1: 264 to
+  // 384 heads 1.02 to 1.25, 38 x 8 x 9359, 77 rows 214 -> 258 us; 400 to 512 0.90 to 1.05; 528 to 640 1.04 to 1.18; more 0.97 to 1.13;
+  // KV heads of 192 and more, or 12, 20, 36 0.72 to 0.99), up to 32 of 128 channels, up to 384 heads (0.94 to 1.07; of 40 to 96 0.80 to
+  // 0.99, 400 heads and more, two rounds for four of chunks, 0.79 to 0.94).  Up to 256 heads 0.68 to 1.00.
+  // A slice of each head has to fit the static array: 128 channels, 96 rows up to 321 heads, 64 channels 606; more take two chunks.
+  const bool shared = heads > kNumCU && kv->n_kv_heads % 8 == 0 &&
+                      (kv->head_dim == 64 ? kv->n_kv_heads <= 160 : kv->n_kv_heads <= 32 && heads <= 384);
   const long long fit_wide = (long long)((kStaticScratchBytes - 4 * 256) / (slice_bytes + (size_t)heads * pl->R * 2 * sizeof(float)));
   const bool wide = pl->wide = may_be_wide && kv->dtype == HIPPO_DTYPE_BF16 && pl->R > 64 && pl->R <= 96 && num_splits == 0 &&
-                    fit_wide >= 1 && 2 * heads * n_total * kv->head_dim * 2 > (256ll << 20);
+                    !shared && fit_wide >= 1 && 2 * heads * n_total * kv->head_dim * 2 > (256ll << 20);
   const int n_equal = (pl->R + 63) / 64;
   pl->row_chunk = wide ? 96 : one_chunk ? (pl->R <= 96 ? 96 : 128) : f32 && pl->R > 64 ? 64 : ((pl->R + n_equal - 1) / n_equal + 15) / 16 * 16;
   // short caches are bound by latency, not bytes: thin slices on many compute units win (bf16, 1896 rows, 7 query

@@ -137,6 +137,22 @@ def test_workspace_query(lib):
     assert h.workspace_bytes(h.CALL_SELECT_GATHER_KV, kv, vid, 0, 16646, 1639) >= 256
 
 
+@pytest.mark.parametrize("batch, heads, d, rows, one", [
+    (32, 8, 64, 80, True), (33, 8, 64, 80, False), (33, 8, 64, 64, False), (12, 32, 64, 96, False), (80, 8, 64, 68, False),
+    (2, 160, 64, 80, False), (2, 192, 64, 80, True), (66, 4, 64, 80, True), (22, 12, 64, 80, True), (300, 1, 64, 80, True),
+    (32, 8, 128, 80, True), (33, 8, 128, 80, False), (12, 32, 128, 80, False), (8, 40, 128, 80, True), (50, 8, 128, 68, True),
+    (321, 1, 128, 96, True), (322, 1, 128, 96, False), (606, 1, 64, 96, True), (607, 1, 64, 96, False),
+])
+def test_which_heads_take_65_to_96_rows_in_one_block(lib, batch, heads, d, rows, one):
+    """The workspace says it: one block for all rows also stores two factors a row and slice."""
+    al = lambda x: (x + 255) // 256 * 256
+    kv = _kv(batch=batch, n_q_heads=heads * rows, n_kv_heads=heads, head_dim=d)
+    slots = batch * heads * rows                            # rounds of one slice a head
+    two = al(slots * d * 2) + 2 * al(slots * 4)
+    need = h.workspace_bytes(h.CALL_VERIFY_ATTENTION, kv, None, 1, (300 << 20) // (4 * batch * heads * d))
+    assert need == two + (al(slots * 8) if one else 0)
+
+
 def test_a_workspace_outlives_the_growth_of_its_cache(lib):
     """What a decoding loop asked for at its first length, or for more query rows, is enough at every later one: 65 to 96 rows
     of a bf16 cache beyond 256 MiB need twice as much in one block, and take two chunks where there is less."""
