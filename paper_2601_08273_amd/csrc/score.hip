@@ -1391,13 +1391,14 @@ __device__ __forceinline__ f32x4 emb_mma(const u32x4& a, const u32x4& b, f32x4 a
 
 // One crop position `pos` of batch element b over the frames f0 .. f0 + p.emb_run - 1 (cut at the
 // video's end), by the 64 * NW threads of a block; every thread must call it (block-wide barriers).
-// KIND: channels of one pass; of several, fetched again for the next frame, through one strip or two; of two passes, held.
-enum EmbKind { kOnePass, kRefetch, kRefetch2, kHold };
+// KIND: channels of one pass, of all the block's waves or of few; of several passes, fetched again for the next frame, through
+// one strip or two; of two passes, held.
+enum EmbKind { kOnePass, kFew, kRefetch, kRefetch2, kHold };
 constexpr int emb_strips(int kind) { return kind >= kRefetch2 ? 2 : 1; }
 template <bool F32, int U, int NW, int KIND>
 __device__ __forceinline__ void emb_run32_body(const ScoreParams& p, EmbRunSmem<U, NW, emb_strips(KIND)>& sm, const int tid,
                                                const int pos, const int f0, const int b) {
-  constexpr bool WIDE = KIND != kOnePass, TWO = KIND >= kRefetch2, HOLD = KIND == kHold;
+  constexpr bool WIDE = KIND > kFew, TWO = KIND >= kRefetch2, HOLD = KIND == kHold;
   constexpr int MP = EmbRunSmem<U, NW, emb_strips(KIND)>::MP;
   static_assert(!TWO || NW == 8, "one set of partial sums");
   constexpr int TPT = NW * 64 / MP, CPT = MP / TPT; // threads per token, cosines per thread
@@ -1460,13 +1461,16 @@ __device__ __forceinline__ void emb_run32_body(const ScoreParams& p, EmbRunSmem<
   }
   unsigned char* strip = &sm.strip[0][wave][0];     // (two: the one that is read)
   unsigned strip_addr = (unsigned)(uintptr_t)strip;
-  // single pass: waves whose channels lie beyond the last one fetch and multiply nothing (two KV heads of 64 channels: six
-  // waves of eight, which took instructions and products' time from the sweep beside them), and nothing of theirs is
-  // summed.  us a call from a graph, with them -> without: bf16, 4096 tokens x 14 heads 18.6 -> 18.0, 23562 x 14 x 2 in four
-  // layers 59.1 -> 53.5, 37791 x 4 in four 45.8 -> 42.1; fp32, 3136 x 14 20.8 -> 20.1, 40320 x 4 in two 91 -> 82; of all 512
-  // channels (4992 to 16384 x 28) the same within 1.5 %.
-  const int n_active = WIDE ? NW : min(NW, (de + CW - 1) / CW);
-  const bool active = wave < n_active, all_active = WIDE || n_active == NW;
+  // Few channels: waves whose own lie beyond the last one fetch and multiply nothing (two KV heads of 64 channels: six waves
+  // of eight, which took instructions and products' time from the sweep beside them), and nothing of theirs is summed.
+  // us a call from a graph, with them -> without: bf16, 4096 tokens x 14 heads 18.6 -> 18.0, 23562 x 14 x 2 in four layers 59.1
+  // -> 53.5; fp32, 3136 x 14, 64 rows 20.3 -> 19.2 (the products with the frame before the first left out as well); 1837 random calls
+  // of few fp32 channels 0.950 of the time, 1953 of bf16 0.860 (with other steps).  A kind of its own: with the question in the
+  // kernel of all waves, and the first products left out there, calls of 256 fp32 channels took up to 1.2 of the time beside the
+  // sweep, though not alone: 29475 tokens x 4 heads, 23 text rows 65 -> 78, 31680 x 4, 55 rows 75 -> 84.5, 3120 x 2 x 3 in two
+  // layers 28 -> 30; bf16, 29232 x 4 heads x 128, 122 rows 42.0 -> 43.5.
+  const int n_active = KIND == kFew ? min(NW, (de + CW - 1) / CW) : NW;
+  const bool active = KIND != kFew || wave < n_active;
   auto request = [&](int frame, int pass) {         // single pass: frames lo, lo + 1, ... in turn
 #pragma unroll
     for (int i = 0; i < NT; ++i) {
@@ -1588,7 +1592,7 @@ __device__ __forceinline__ void emb_run32_body(const ScoreParams& p, EmbRunSmem<
       }
 #pragma unroll
       for (int rbk = 0; rbk < 2; ++rbk) dot[0][rbk] = (f32x4){0.f, 0.f, 0.f, 0.f};
-      if (!F32 || fr > lo)                          // (fp32: 32 products of 32 clocks)
+      if (!F32 || KIND != kFew || fr > lo)          // (32 fp32 products of 32 clocks)
 #pragma unroll
         for (int rbk = 0; rbk < 2; ++rbk)
 #pragma unroll
@@ -1701,7 +1705,7 @@ __device__ __forceinline__ void emb_run32_body(const ScoreParams& p, EmbRunSmem<
       const int blk = wave;
       const unsigned used = TWO ? take ^ 1 : 0;  // the strips that took the partial sums
       f32x4 v = *(const f32x4*)(&sm.strip[used][0][0] + (blk * 64 + lane) * 16);
-      if (all_active) {                             // (all reads in flight)
+      if constexpr (KIND != kFew) {                 // (all reads in flight)
 #pragma unroll
         for (int w = 1; w < SETS * NW; ++w)
           v += *(const f32x4*)(&sm.strip[used][w % NW][0] + (w / NW) * kSetBytes + (blk * 64 + lane) * 16);
@@ -1723,7 +1727,7 @@ __device__ __forceinline__ void emb_run32_body(const ScoreParams& p, EmbRunSmem<
       }
     } else if (wave == 3 && lane < MP) {
       float d = sm.redd[0][lane >> 4][lane & 15];
-      if (all_active) {
+      if constexpr (KIND != kFew) {
 #pragma unroll
         for (int w = 1; w < SETS * NW; ++w) d += sm.redd[w][lane >> 4][lane & 15];
       } else {
@@ -1794,7 +1798,7 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 3 : 2) void emb_scores_run32(Sco
 // per SIMD keeps the matrix unit busy, so a riding block's trips to memory cost next to nothing; in a launch of their own the crops took
 // as long as the sweep (3136 tokens: 10.5 us of pass 1 and 13 of crops, together 14.7).  Up to 168 registers a wave, 38 KB of
 // LDS: three blocks on a compute unit.
-template <int D, bool WIDE>
+template <int D, int KIND>
 __global__ __launch_bounds__(256, 3) void sattn_f32_pass1_with_emb(ScoreParams p, int n_sattn) {
   union Smem {
     SattnF32Smem<D> sa;
@@ -1808,12 +1812,12 @@ __global__ __launch_bounds__(256, 3) void sattn_f32_pass1_with_emb(ScoreParams p
     sattn_f32_body<D, 1>(p, sm.sa, tile, hk, rest2 % p.n_rsplit, rest2 / p.n_rsplit);
     return;
   }
-  emb_run32_block<true, 4, 4, WIDE ? kRefetch : kOnePass>(p, sm.run, (unsigned)(blk - n_sattn));
+  emb_run32_block<true, 4, 4, KIND>(p, sm.run, (unsigned)(blk - n_sattn));
 }
 
 // The same beside the one sweep (3136 tokens: 15.4 us; 936 tokens, whole calls, beside a sweep 30.6 -> 22.2, 3 x 7220 tokens in
 // two layers 130 -> 105).  Five chunks of exponentials take up to 254 registers: two blocks on a compute unit.
-template <int D, bool WIDE>
+template <int D, int KIND>
 __global__ __launch_bounds__(256, 2) void sattn_once_with_emb(ScoreParams p, ScoreOnce once, int n_sattn) {
   union Smem {
     SattnOnceSmem<D> once;
@@ -1822,7 +1826,7 @@ __global__ __launch_bounds__(256, 2) void sattn_once_with_emb(ScoreParams p, Sco
   };
   __shared__ Smem sm;
   if ((int)blockIdx.x < n_sattn) sattn_once_block<D>(p, once, sm.once, sm.sweep, blockIdx.x);
-  else emb_run32_block<true, 4, 4, WIDE ? kRefetch : kOnePass>(p, sm.run, blockIdx.x - (unsigned)n_sattn);
+  else emb_run32_block<true, 4, 4, KIND>(p, sm.run, blockIdx.x - (unsigned)n_sattn);
 }
 
 // Pass 1 of s_attn and the embedding terms in ONE launch: the first n_sattn blocks run the
@@ -2084,31 +2088,33 @@ size_t score_once_rows(int rows_per_kv_head) {
 }
 const int kScoreOnceWords = kOnceCopies, kScoreOnceBins = kOnceBins;
 
-// riders: blocks of the embedding terms beside the sweep (wide: of more channels than a pass takes)
+// riders: blocks of the embedding terms beside the sweep, of the kind kOnePass, kFew or kRefetch
 template <int D>
-static hipError_t launch_sattn_once(const ScoreParams& p, const ScoreOnce& once, hipStream_t st, long long riders, bool wide) {
+static hipError_t launch_sattn_once(const ScoreParams& p, const ScoreOnce& once, hipStream_t st, long long riders, int kind) {
   const long long n_sattn = (long long)p.n_tile * p.Hkv * p.n_rsplit * p.Bz;
   const long long n_clear = (long long)(once.clear_bytes / sizeof(u32x4));
   hipLaunchKernelGGL(sattn_once_clear, dim3((unsigned)((n_clear + 255) / 256)), dim3(256), 0, st, (u32x4*)once.row_word,
                      n_clear);
   const dim3 grid((unsigned)(n_sattn + riders));
-  if (wide) hipLaunchKernelGGL((sattn_once_with_emb<D, true>), grid, dim3(256), 0, st, p, once, (int)n_sattn);
-  else hipLaunchKernelGGL((sattn_once_with_emb<D, false>), grid, dim3(256), 0, st, p, once, (int)n_sattn);
+  const auto launch = kind == kRefetch ? sattn_once_with_emb<D, kRefetch>
+                      : kind == kFew   ? sattn_once_with_emb<D, kFew>
+                                       : sattn_once_with_emb<D, kOnePass>;
+  hipLaunchKernelGGL(launch, grid, dim3(256), 0, st, p, once, (int)n_sattn);
   hipLaunchKernelGGL(sattn_f32_redo<D>, dim3((unsigned)n_sattn), dim3(256), 0, st, p, once);
   return hipGetLastError();
 }
 
 template <int D>
-static hipError_t launch_sattn_f32(const ScoreParams& p, hipStream_t st, long long riders, bool wide) {
+static hipError_t launch_sattn_f32(const ScoreParams& p, hipStream_t st, long long riders, int kind) {
   if (p.n_tile > 65535 || (long long)p.n_rsplit * p.Bz > 65535) return hipErrorInvalidValue;
   const dim3 grid(p.Hkv, p.n_tile, p.n_rsplit * p.Bz);     // KV head fastest, as the bf16 sweeps
   if (riders > 0) {
     const long long n_sattn = (long long)p.n_tile * p.Hkv * p.n_rsplit * p.Bz;
     const dim3 fused((unsigned)(n_sattn + riders));
-    if (wide)
-      hipLaunchKernelGGL((sattn_f32_pass1_with_emb<D, true>), fused, dim3(256), 0, st, p, (int)n_sattn);
-    else
-      hipLaunchKernelGGL((sattn_f32_pass1_with_emb<D, false>), fused, dim3(256), 0, st, p, (int)n_sattn);
+    const auto launch = kind == kRefetch ? sattn_f32_pass1_with_emb<D, kRefetch>
+                        : kind == kFew   ? sattn_f32_pass1_with_emb<D, kFew>
+                                         : sattn_f32_pass1_with_emb<D, kOnePass>;
+    hipLaunchKernelGGL(launch, fused, dim3(256), 0, st, p, (int)n_sattn);
   } else {
     hipLaunchKernelGGL((sattn_f32<D, 1>), grid, dim3(256), 0, st, p);
   }
@@ -2118,7 +2124,7 @@ static hipError_t launch_sattn_f32(const ScoreParams& p, hipStream_t st, long lo
   return hipGetLastError();
 }
 
-// riders: 0 = pass 1 in a launch of its own, else that many riding blocks (wide: of more channels than a pass takes)
+// riders: 0 = pass 1 in a launch of its own, else that many riding blocks, of the kind kOnePass, kFew or a wide one
 // bf16 riders of more than 512 channels: which of them, and how many stand in front of the sweep's blocks.
 // The two-strip ones take a third of the compute units' block slots from the launch; what longer takes (a rider, by its
 // frames and passes, or a block of the sweep, by its chunks of 64 rows) goes first.  us a call from a graph, one strip | two
@@ -2149,16 +2155,17 @@ static Riders wide_bf16_riders(const ScoreParams& p, long long n_sattn, long lon
 }
 
 template <int D>
-static hipError_t launch_sattn_mfma(const ScoreParams& p, hipStream_t st, long long riders, bool wide) {
+static hipError_t launch_sattn_mfma(const ScoreParams& p, hipStream_t st, long long riders, int kind) {
   if (p.n_tile > 65535 || (long long)p.n_rsplit * p.Bz > 65535) return hipErrorInvalidValue;
   dim3 grid(p.Hkv, p.n_tile, p.n_rsplit * p.Bz);
   if (riders > 0) {
     const long long n_sattn = (long long)p.n_tile * p.Hkv * p.n_rsplit * p.Bz;
     const dim3 fused((unsigned)(n_sattn + riders));
-    const Riders r = wide ? wide_bf16_riders(p, n_sattn, riders) : Riders{kOnePass, 0};
+    const Riders r = kind == kRefetch ? wide_bf16_riders(p, n_sattn, riders) : Riders{kind, 0};
     const auto launch = r.kind == kHold       ? sattn_pass1_with_emb<D, kHold>
                         : r.kind == kRefetch2 ? sattn_pass1_with_emb<D, kRefetch2>
                         : r.kind == kRefetch  ? sattn_pass1_with_emb<D, kRefetch>
+                        : r.kind == kFew      ? sattn_pass1_with_emb<D, kFew>
                                               : sattn_pass1_with_emb<D, kOnePass>;
     hipLaunchKernelGGL(launch, fused, dim3(kSaWaves * 64), 0, st, p, (int)n_sattn, (int)r.lead);
   } else {
@@ -2259,6 +2266,8 @@ hipError_t launch_score(const ScoreParams& p_in, const ScoreOnce& once_in, hipSt
   const int de = p.emb ? p.emb_dim : p.Hkv * p.D;
   const bool small_crops = p.ch * p.cw <= 32;
   const bool wide = de > (bf16 ? 512 : 256);
+  // (a wave takes 64 channels)
+  const int kind = wide ? kRefetch : de <= (bf16 ? 512 : 256) - 64 ? kFew : kOnePass;
   const long long n_sattn = (long long)p.n_tile * p.Hkv * p.n_rsplit * p.Bz, all_crops = crops_per_frame * p.F * p.B;
   {
     long long run = all_crops / kNumCU;
@@ -2295,13 +2304,13 @@ hipError_t launch_score(const ScoreParams& p_in, const ScoreOnce& once_in, hipSt
   const long long riders = emb_rides ? n_riders : 0;
   if ((p.flags & HIPPO_SCORE_ATTN) || accumulate_only) {
     if (p.dtype == HIPPO_DTYPE_BF16)
-      e = (p.D == 128) ? launch_sattn_mfma<128>(p, st, riders, wide)
-                       : launch_sattn_mfma<64>(p, st, riders, wide);
+      e = (p.D == 128) ? launch_sattn_mfma<128>(p, st, riders, kind)
+                       : launch_sattn_mfma<64>(p, st, riders, kind);
     else if (once.row_word != nullptr)
-      e = (p.D == 128) ? launch_sattn_once<128>(p, once, st, riders, wide)
-                       : launch_sattn_once<64>(p, once, st, riders, wide);
+      e = (p.D == 128) ? launch_sattn_once<128>(p, once, st, riders, kind)
+                       : launch_sattn_once<64>(p, once, st, riders, kind);
     else
-      e = (p.D == 128) ? launch_sattn_f32<128>(p, st, riders, wide) : launch_sattn_f32<64>(p, st, riders, wide);
+      e = (p.D == 128) ? launch_sattn_f32<128>(p, st, riders, kind) : launch_sattn_f32<64>(p, st, riders, kind);
     if (e != hipSuccess) return e;
     if (accumulate_only) {   // otherwise the fusion kernel finishes the attention mass itself
       const long long n = (long long)p.B * p.Nv;
@@ -2320,10 +2329,12 @@ hipError_t launch_score(const ScoreParams& p_in, const ScoreOnce& once_in, hipSt
       // 108; 19800 of 2048 53, not 48; 18590 of 1536 40, not 38; 4056 of 2048 to 3584 within 10 % either way)
       if (bf16 && de > 1024) hipLaunchKernelGGL((emb_scores_run32<false, 8, kRefetch>), runs, dim3(512), 0, st, p);
       else if (bf16 && wide) hipLaunchKernelGGL((emb_scores_run32<false, 8, kHold>), runs, dim3(512), 0, st, p);
+      else if (bf16 && kind == kFew) hipLaunchKernelGGL((emb_scores_run32<false, 8, kFew>), runs, dim3(512), 0, st, p);
       else if (bf16) hipLaunchKernelGGL((emb_scores_run32<false, 8, kOnePass>), runs, dim3(512), 0, st, p);
       else if (wide && de <= 512) hipLaunchKernelGGL((emb_scores_run32<true, 8, kOnePass>), runs, dim3(512), 0, st, p);
       else if (wide && eight_waves) hipLaunchKernelGGL((emb_scores_run32<true, 8, kRefetch>), runs, dim3(512), 0, st, p);
       else if (wide) hipLaunchKernelGGL((emb_scores_run32<true, 4, kRefetch>), runs, dim3(256), 0, st, p);
+      else if (kind == kFew) hipLaunchKernelGGL((emb_scores_run32<true, 4, kFew>), runs, dim3(256), 0, st, p);
       else hipLaunchKernelGGL((emb_scores_run32<true, 4, kOnePass>), runs, dim3(256), 0, st, p);
     } else if (!bf16) {
       hipLaunchKernelGGL(emb_scores, grid, dim3(256), 0, st, p);

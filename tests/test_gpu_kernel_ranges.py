@@ -631,10 +631,35 @@ def test_embedding_terms_of_few_channels(hippo, dtype, channels):
         test_embedding_terms_over_passes_of_channels(hippo, (1, 7, 6, 11, ch, 5, 5), dtype)
 
 
+def best_time(call):
+    """ms of ten calls in a graph, the least of five replays"""
+    call()
+    graph, (begin, end) = torch.cuda.CUDAGraph(), (torch.cuda.Event(enable_timing=True) for _ in range(2))
+    with torch.cuda.graph(graph):
+        for _ in range(10):
+            call()
+    times = []
+    for _ in range(5):
+        graph.replay(), begin.record(), graph.replay(), end.record(), torch.cuda.synchronize()
+        times.append(begin.elapsed_time(end))
+    return min(times)
+
+
+@pytest.mark.parametrize("frames, gh, gw, L, crop", [(655, 15, 3, 23, (3, 3)), (175, 9, 20, 4, (3, 4))])
+def test_embedding_terms_beside_the_sweep_take_no_longer_than_after_it(hippo, frames, gh, gw, L, crop):
+    # 256 fp32 channels, all that a block takes in a pass: 65 us together and 70 apart, 64 and 69
+    n = frames * gh * gw
+    g = torch.Generator(device="cuda").manual_seed(frames)
+    q, k = torch.randn((1, L, 4, 64), generator=g, device="cuda"), torch.randn((1, 4, n, 64), generator=g, device="cuda")
+    vid = hippo.video_desc(frames, gh, gw, 0, *crop)
+    time = lambda flags: best_time(lambda: hippo.hippo_score_tokens(q, k, vid, flags=flags))
+    assert time(hippo.SCORE_ALL) < time(hippo.SCORE_ATTN) + time(hippo.SCORE_TEMP | hippo.SCORE_SPA)
+
+
 @pytest.mark.parametrize("d, B, Hkv, q_len, G, ctx", [
     # more than 256 MiB of K and V; 65, 72, 91 and 96 rows in one block, 97 in two; one slice a head, slices of a tile more or less
     (128, 8, 8, 13, 5, 8200), (128, 4, 16, 9, 8, 8190), (64, 8, 8, 13, 7, 16390), (128, 2, 32, 12, 8, 8201), (128, 8, 8, 97, 1, 8200),
-    (64, 16, 32, 13, 7, 2100),
+    (64, 16, 32, 13, 7, 2100), (64, 66, 4, 13, 7, 4000),               # 512 heads in two chunks, 264 in one block a head
 ])
 def test_65_to_96_rows_of_a_large_cache(hippo, d, B, Hkv, q_len, G, ctx):
     g = torch.Generator(device="cuda").manual_seed(ctx + G)
