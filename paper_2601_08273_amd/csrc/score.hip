@@ -2175,8 +2175,11 @@ static hipError_t launch_sattn_mfma(const ScoreParams& p, hipStream_t st, long l
   // from a graph, with a launch for the merge -> without: 4096 tokens x 14 heads, 64 text rows 19.7 -> 18.6, 4096 x 28, 256
   // rows 31.6 -> 30.1, 4096 x 64, 256 rows 51.7 -> 50.4, 1368 x 4 x 2, 61 rows 16.5 -> 14.5, 2690 x 28 in 4 layers x 2 33.7 ->
   // 31.9.  From 17 tiles on every block reads as much as the launch costs (6174 x 14 x 3 in four layers 44.4 -> 48.6, 4788 x 28
-  // x 2 39.2 -> 40.3, 5304 x 14 x 3 21.4 -> 21.1).
-  if (p.n_tile <= 16 && p.rows_per_split <= kSaWaves * 64) {
+  // x 2 39.2 -> 40.3, 5304 x 14 x 3 21.4 -> 21.1).  So do many rounds of blocks: without the launch, 2934 random calls took, of 9 to
+  // 16 tiles, 0.94 of the time up to 512 blocks, 0.98 up to 768, 0.99 up to 1024, 1.00 to 1.03 up to 2048, beyond 1.01 to 1.08 (3724
+  // x 32 heads x 6 in four layers, 22 rows 104 -> 115); of up to 8 tiles 0.91, 0.96, 0.97, up to 4096 0.97 to 1.00, beyond 1.01 to 1.03.
+  const long long blocks = (long long)p.n_tile * p.Hkv * p.n_rsplit * p.Bz;
+  if (p.n_tile <= 16 && p.rows_per_split <= kSaWaves * 64 && blocks <= (p.n_tile <= 8 ? 16 : 4) * kNumCU) {
     if (p.n_tile <= 8) hipLaunchKernelGGL((sattn_mfma<D, 2, 1>), grid, dim3(kSaWaves * 64), 0, st, p);
     else hipLaunchKernelGGL((sattn_mfma<D, 2, 2>), grid, dim3(kSaWaves * 64), 0, st, p);
     return hipGetLastError();

@@ -616,6 +616,26 @@ def test_bf16_attention_mass_of_short_videos(hippo, n, L, d):
     assert_close(got, oracle.s_attn(q, k, 3, n), "bf16", "%d tokens, %d rows, d=%d" % (n, L, d))
 
 
+@pytest.mark.parametrize("n, Hkv, parts", [(2500, 8, (12, 13)), (2500, 16, (6, 7, 25)), (1000, 32, (32, 33))])
+def test_bf16_attention_mass_of_many_short_videos(hippo, n, Hkv, parts):
+    # up to 1024 blocks of 10 tiles, 4096 of 4, pass 2 merges the statistics; one batch element more: the same bits, a launch
+    q, k = score_inputs(n, max(parts), 9, 2 * Hkv, Hkv, 64, n, "bf16")
+    whole = attention_mass(hippo, q, k, "bf16", 1, 1, n, 0)
+    assert_close(whole[:1], oracle.s_attn(q[:1], k[:1], 0, n), "bf16", "%d tokens" % n)
+    for some in parts:
+        assert np.array_equal(attention_mass(hippo, q[:some], k[:some], "bf16", 1, 1, n, 0), whole[:some])
+
+
+def test_bf16_calls_of_many_short_videos_take_no_longer_together(hippo):
+    # 37 us for the 960 blocks of one batch element, 101 for the 5760 of six; 112 where every block merges the statistics
+    g = torch.Generator(device="cuda").manual_seed(6)
+    q = [torch.randn((6, 22, 32, 64), generator=g, device="cuda").to(torch.bfloat16) for _ in range(4)]
+    k = [torch.randn((6, 16, 3724, 64), generator=g, device="cuda").to(torch.bfloat16) for _ in range(4)]
+    vid = hippo.video_desc(19, 14, 14, 0)
+    one = best_time(lambda: hippo.hippo_score_tokens_layers([x[:1] for x in q], [x[:1] for x in k], vid))
+    assert best_time(lambda: hippo.hippo_score_tokens_layers(q, k, vid)) < 2.9 * one
+
+
 def test_bf16_attention_mass_of_long_runs_of_rows(hippo):
     # a block's threads cover a run of 512 rows; longer ones have a launch for their statistics
     for L in (256, 257, 320):
