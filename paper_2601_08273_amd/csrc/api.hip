@@ -232,7 +232,7 @@ int plan_score(const hippo_kv_desc* kv, const hippo_video_desc* vid, int l_txt, 
   const int rows_per_kv_head = l_txt * (kv->n_q_heads / kv->n_kv_heads);
   pl->once = score_once(kv->dtype, Nv, rows_per_kv_head);
   pl->n_rsplit = score_row_splits(kv->dtype, (long long)pl->n_tile * kv->n_kv_heads * kv->batch * n_layers,
-                                  rows_per_kv_head, kv->head_dim, pl->once, finer);
+                                  rows_per_kv_head, kv->head_dim, pl->once, finer, kv->n_kv_heads * n_layers);
   // launch limits of the sweeps (KV heads on grid x, key tiles on y, row runs x (layer, batch element) on z) and of
   // the row merge (32 rows per block)
   if (pl->n_tile > 65535 || (long long)kv->batch * n_layers * pl->n_rsplit > 65535 || kv->n_kv_heads > 65535 ||

@@ -344,7 +344,7 @@ bool score_once(int dtype, long long n_vis, int rows_per_kv_head);   // s_attn i
 size_t score_once_rows(int rows_per_kv_head);      // rows of a KV head that it has words for
 extern const int kScoreOnceWords, kScoreOnceBins;  // its 64-bit words a row
 int score_row_splits(int dtype, long long blocks_unsplit, int rows_per_kv_head, int head_dim, bool once,
-                     bool finer);
+                     bool finer, int col_parts);
 
 struct SelectParams {
   const float* scores;

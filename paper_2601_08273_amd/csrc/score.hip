@@ -2009,7 +2009,8 @@ int score_token_tile(int dtype) { return dtype == HIPPO_DTYPE_BF16 ? kSaMfmaTile
 // blocks, two at a time, an odd last one alone.  520 unsplit blocks of 28 chunks, for example, put a third
 // block on a few units, which then start a 28-chunk sweep when all others are done (91 us against 81-83
 // with three or four runs); 256 blocks of 14 chunks are best cut in two (one round, two blocks per unit).
-int score_row_splits(int dtype, long long blocks_unsplit, int rows_per_kv_head, int head_dim, bool once, bool finer) {
+int score_row_splits(int dtype, long long blocks_unsplit, int rows_per_kv_head, int head_dim, bool once, bool finer,
+                     int col_parts) {
   int best = 1;
   if (dtype != HIPPO_DTYPE_BF16) {
     // fp32: a wave per SIMD nearly keeps the matrix unit busy, so a compute unit takes its blocks one after the other in
@@ -2053,10 +2054,15 @@ int score_row_splits(int dtype, long long blocks_unsplit, int rows_per_kv_head, 
   // layers, 17 rows, 256 blocks 20.4 -> 22.1), not for one and more than two runs more of 64 channels (3 -> 6 and 4 -> 8: 46
   // calls 0.997, the slowest 1.08).  Random calls that it cuts finer, 959 without these three conditions 0.934 of the time, 38 of
   // them slower by 2 to 14 %; 550 others with them 0.922, 13 by 2 to 4 %.
-  auto alone = [&](int rs) {
+  // And every run is a column partial more a token for each KV head and layer, which the fusion's one block a frame adds up: not
+  // where that is more than the sweeps save (one frame of 396 tokens x 8 heads in four layers, 154 rows, 32 -> 96 partials 18.9 ->
+  // 22.8; 3 frames of 272 tokens x 64 heads, 55 rows, 24 -> 56 18.0 -> 21.0; of 662 calls cut finer the 25 that it stops took 1.03
+  // of the time, 1.2 at the most).
+  auto sweep = [&](int rs) {
     const int cpb = (chunks + rs - 1) / rs;
-    return (cpb == 1 ? 1.89 : cpb * 1.29) + 2.5 + (head_dim == 128 ? 0.008 : 0.005) * (double)(blocks_unsplit * rs);
+    return cpb == 1 ? 1.89 : cpb * 1.29;
   };
+  auto alone = [&](int rs) { return sweep(rs) + 2.5 + (head_dim == 128 ? 0.008 : 0.005) * (double)(blocks_unsplit * rs); };
   if (!finer) return best;
   const int former = best, former_cpb = (chunks + best - 1) / best;
   for (int rs = best + 1; rs <= 8 && rs <= chunks; ++rs) {
@@ -2066,6 +2072,7 @@ int score_row_splits(int dtype, long long blocks_unsplit, int rows_per_kv_head, 
     if (3 * cpb > 2 * former_cpb) continue;
     if (former_cpb - cpb == 1 && 4 * blocks >= 3 * kNumCU) continue;
     if (head_dim != 128 && former_cpb == 2 && rs - former > 2) continue;
+    if (col_parts * (rs - former) > 16 + 12 * (sweep(former) - sweep(rs))) continue;
     if (alone(rs) < alone(best) * 0.97) best = rs;
   }
   return best;

@@ -203,6 +203,8 @@ def test_score_argument_errors(lib):
     (64, 8, 128, 1836, 17, 2, 1), (28, 4, 128, 7680, 21, 1, 1), (28, 4, 128, 6825, 26, 1, 1), (28, 4, 128, 5120, 26, 1, 2),
     (14, 2, 64, 4600, 128, 1, 4), (14, 2, 64, 4600, 184, 1, 6), (4, 2, 64, 3360, 161, 1, 3),  # a chunk of four; two of six; six runs
     (14, 2, 64, 4096, 64, 1, 7), (28, 4, 128, 1400, 121, 1, 7), (28, 4, 128, 7000, 40, 1, 2),
+    # 64 partials a token more for two chunks of three, 32 and 16 for one of two; 40 and 24 for one of three
+    (8, 8, 64, 396, 154, 4, 1), (16, 8, 64, 462, 35, 4, 1), (16, 4, 128, 374, 30, 4, 2), (80, 10, 64, 768, 55, 1, 4), (64, 8, 64, 816, 55, 1, 7),
 ])
 def test_runs_of_rows_of_short_videos(lib, H, Hkv, d, n, L, layers, runs):
     """Finer cuts where they save a third of a run's chunks and more: the column partials that are asked for say how many runs
@@ -224,7 +226,7 @@ def test_a_workspace_for_a_longer_video_serves_a_shorter_one(lib):
             ((16, 2, 64), (492, 3, 4, 26, 1), (492, 3, 4, 18, 1), 175360),
             ((8, 1, 128), (10, 11, 21, 29, 4), (10, 11, 21, 29, 3), 142592),
             ((1, 1, 64), (506, 3, 9, 139, 2), (331, 3, 9, 139, 2), 258816),
-            ((32, 8, 128), (10, 14, 4, 118, 1), (10, 11, 4, 118, 1), 137216)):
+            ((32, 8, 128), (28, 13, 8, 46, 1), (27, 13, 8, 46, 1), 259072)):
         kv = _kv(n_q_heads=q_heads, n_kv_heads=heads, head_dim=d)
         ask = lambda f, gh, gw, l, n: lib.hippo_score_layers_workspace_bytes(C.byref(kv), C.byref(h.video_desc(f, gh, gw, 0)), l, n)
         f, gh, gw, l, n = smaller

@@ -740,7 +740,7 @@ def test_65_to_96_rows_in_a_workspace_of_before_the_cache_grew(hippo, d, ctx, fi
     assert e.value.status == hippo.ERR_WORKSPACE_TOO_SMALL
 
 
-@pytest.mark.parametrize("H, Hkv, d, F, gh, gw, L", [(32, 8, 128, 10, 11, 4, 118), (14, 2, 64, 16, 16, 16, 64)])
+@pytest.mark.parametrize("H, Hkv, d, F, gh, gw, L", [(32, 8, 128, 27, 13, 8, 46), (14, 2, 64, 16, 16, 16, 64)])
 def test_short_videos_in_a_workspace_without_room_for_finer_cuts(hippo, H, Hkv, d, F, gh, gw, L):
     n, vid = F * gh * gw, hippo.video_desc(F, gh, gw, 0)
     q, k = score_inputs(L, 1, L, H, Hkv, d, n, "bf16")
