@@ -2051,13 +2051,12 @@ int score_row_splits(int dtype, long long blocks_unsplit, int rows_per_kv_head, 
   // 121 rows 22.6 -> 19.9.  Where that saves little, the column partials of more runs and the blocks that riders wait for cost as
   // much: not for a quarter or a fifth of a run's chunks (64 channels, four chunks -> three, 4 -> 5 runs 20.9 -> 23.8), not for one
   // chunk on three quarters of the units and more (two for three: 6825 x 28, 26 rows, 216 blocks 25.2 -> 28.4, 1836 x 64 in two
-  // layers, 17 rows, 256 blocks 20.4 -> 22.1), not for one and more than two runs more of 64 channels (3 -> 6 and 4 -> 8: 46
-  // calls 0.997, the slowest 1.08).  Random calls that it cuts finer, 959 without these three conditions 0.934 of the time, 38 of
-  // them slower by 2 to 14 %; 550 others with them 0.922, 13 by 2 to 4 %.
+  // layers, 17 rows, 256 blocks 20.4 -> 22.1).
   // And every run is a column partial more a token for each KV head and layer, which the fusion's one block a frame adds up: not
   // where that is more than the sweeps save (one frame of 396 tokens x 8 heads in four layers, 154 rows, 32 -> 96 partials 18.9 ->
   // 22.8; 3 frames of 272 tokens x 64 heads, 55 rows, 24 -> 56 18.0 -> 21.0; of 662 calls cut finer the 25 that it stops took 1.03
-  // of the time, 1.2 at the most).
+  // of the time, 1.2 at the most).  Of 5881 random calls of 300 to 24000 tokens two take more than 1.02 of the time that they had
+  // before finer cuts and the merge in pass 2, 1.04 the most; those of up to 4096 tokens 0.89.
   auto sweep = [&](int rs) {
     const int cpb = (chunks + rs - 1) / rs;
     return cpb == 1 ? 1.89 : cpb * 1.29;
@@ -2071,7 +2070,6 @@ int score_row_splits(int dtype, long long blocks_unsplit, int rows_per_kv_head, 
     if (blocks > (head_dim == 128 && cpb >= 3 ? kNumCU : kNumCU * 7 / 8)) continue;
     if (3 * cpb > 2 * former_cpb) continue;
     if (former_cpb - cpb == 1 && 4 * blocks >= 3 * kNumCU) continue;
-    if (head_dim != 128 && former_cpb == 2 && rs - former > 2) continue;
     if (col_parts * (rs - former) > 16 + 12 * (sweep(former) - sweep(rs))) continue;
     if (alone(rs) < alone(best) * 0.97) best = rs;
   }

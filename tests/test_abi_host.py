@@ -201,7 +201,7 @@ def test_score_argument_errors(lib):
 @pytest.mark.parametrize("H, Hkv, d, n, L, layers, runs", [
     # one chunk of three on three quarters of the compute units and more; of fewer
     (64, 8, 128, 1836, 17, 2, 1), (28, 4, 128, 7680, 21, 1, 1), (28, 4, 128, 6825, 26, 1, 1), (28, 4, 128, 5120, 26, 1, 2),
-    (14, 2, 64, 4600, 128, 1, 4), (14, 2, 64, 4600, 184, 1, 6), (4, 2, 64, 3360, 161, 1, 3),  # a chunk of four; two of six; six runs
+    (14, 2, 64, 4600, 128, 1, 4), (14, 2, 64, 4600, 184, 1, 6), (4, 2, 64, 3360, 161, 1, 6),  # a chunk of four; two of six; one of two
     (14, 2, 64, 4096, 64, 1, 7), (28, 4, 128, 1400, 121, 1, 7), (28, 4, 128, 7000, 40, 1, 2),
     # 64 partials a token more for two chunks of three, 32 and 16 for one of two; 40 and 24 for one of three
     (8, 8, 64, 396, 154, 4, 1), (16, 8, 64, 462, 35, 4, 1), (16, 4, 128, 374, 30, 4, 2), (80, 10, 64, 768, 55, 1, 4), (64, 8, 64, 816, 55, 1, 7),
