@@ -72,7 +72,8 @@ constexpr int kSdLdsStats = 1024;                   // segment statistics staged
 // 14.0, 7 x 25 rows 27.1 -> 21.7, one sequence of 3 rows of 32000 words 12.0 -> 10.3.  Up to a block a compute unit: there the
 // slowest of 56 random calls of 8 to 64 sequences took 0.90 of the time, but with more blocks eight of 27 took 1.04 to 1.17 (46
 // sequences x 9 rows of 185880 bf16 words 45.2 -> 53.0, 36 x 3 of 138008 23.7 -> 26.9, 17 x 9 of 134312 fp32 words 27.5 -> 28.7):
-// the first part, which every block repeats, then takes the units four times the waves.
+// the first part, which every block repeats, then takes the units four times the waves.  Nor in greedy decoding of up to 16 rows,
+// which four waves merge at once and which has no cells: 3163 random calls took 1.004 of the time.
 constexpr int kSdCellThreads = 1024;
 
 // Stores and loads of what other blocks of the launch read or wrote: device scope, past the caches of an XCD.
@@ -451,7 +452,7 @@ hipError_t launch_typed(const SpecParams& p, hipStream_t st) {
   if (greedy) sd_row_stats<T, true><<<grid, kSdThreads, 0, st>>>(p);
   else sd_row_stats<T, false><<<grid, kSdThreads, 0, st>>>(p);
   const dim3 cells(greedy ? 1 : p.n_seg, p.B);
-  if ((long long)cells.x * p.B <= kNumCU) sd_cells<T, kSdCellThreads><<<cells, kSdCellThreads, 0, st>>>(p);
+  if ((long long)cells.x * p.B <= kNumCU && !(greedy && rows <= 16)) sd_cells<T, kSdCellThreads><<<cells, kSdCellThreads, 0, st>>>(p);
   else sd_cells<T, kSdThreads><<<cells, kSdThreads, 0, st>>>(p);
   return hipGetLastError();
 }

@@ -238,7 +238,7 @@ def test_masked_words_edge_uniforms_and_bad_tokens(hippo, dtype):
 
 
 @pytest.mark.parametrize("dtype", ["fp32", "bf16"])
-@pytest.mark.parametrize("B,gamma,V", [(64, 5, 1000), (16, 8, 40003), (4, 5, 151936), (8, 1, 8193), (8, 0, 5000)])
+@pytest.mark.parametrize("B,gamma,V", [(64, 5, 1000), (16, 8, 40003), (4, 5, 151936), (8, 1, 8193), (8, 0, 5000), (3, 15, 40003), (3, 16, 9001)])
 def test_greedy_bit_exact(hippo, dtype, B, gamma, V):
     r = np.random.default_rng(V + gamma)
     pl = prep(r.standard_normal((B, gamma + 1, V)).astype(np.float32), dtype)
