@@ -289,28 +289,22 @@ def test_large_sources_are_quantised_as_their_heads_are(hippo, B, Hkv, n, d, dty
         assert torch.all(codes[:, :, :, n:] == 0x7F)
 
 
-@pytest.mark.parametrize("B, Hkv, n, d, n_parts", [(64, 32, 102, 64, 2), (260, 32, 108, 128, 13)])
-def test_many_short_heads_take_no_longer_together(hippo, B, Hkv, n, d, n_parts):
-    # more than 36 MiB and more than 256 MiB in heads that are too short for a block of the one sweep: not slower than in parts
+@pytest.mark.parametrize("B, Hkv, n, d, dtype, once", [
+    # 24 KB a head from 36 MiB on, 44 KB from 256 MiB on; just below 36 MiB, and there
+    (64, 32, 191, 64, "bf16", False), (64, 32, 192, 64, "bf16", True), (32, 32, 47, 128, "fp32", False), (32, 32, 48, 128, "fp32", True),
+    (94, 32, 175, 128, "bf16", False), (94, 32, 176, 128, "bf16", True), (260, 32, 108, 128, "bf16", False),
+    (1, 8, 9215, 128, "bf16", False), (1, 8, 9216, 128, "bf16", True),
+])
+def test_which_heads_are_quantised_in_one_sweep(hippo, kernels, B, Hkv, n, d, dtype, once):
     g = torch.Generator(device="cuda").manual_seed(n)
-    k, v = (torch.randn((B, Hkv, n, d), generator=g, device="cuda").to(torch.bfloat16) for _ in range(2))
-    parts = [slice(i, i + B // n_parts) for i in range(0, B, B // n_parts)]
-    calls = [lambda: [hippo.hippo_quantize_kv_e4m3(k, v)], lambda: [hippo.hippo_quantize_kv_e4m3(k[p], v[p]) for p in parts]]
-    whole, apart = calls[0]()[0], calls[1]()
-    assert all(torch.equal(x, torch.cat([part[i] for part in apart])) for i, x in enumerate(whole))
-    times = []
-    for call in calls:
-        graph = torch.cuda.CUDAGraph()
-        with torch.cuda.graph(graph):
-            for _ in range(10):
-                call()
-        best = []
-        for _ in range(5):
-            begin, end = (torch.cuda.Event(enable_timing=True) for _ in range(2))
-            graph.replay(), begin.record(), graph.replay(), end.record(), torch.cuda.synchronize()
-            best.append(begin.elapsed_time(end))
-        times.append(min(best))
-    assert times[0] < 1.05 * times[1]
+    k, v = (torch.randn((B, Hkv, n, d), generator=g, device="cuda").to(torch.float32 if dtype == "fp32" else torch.bfloat16)
+            for _ in range(2))
+    names = kernels(lambda: hippo.hippo_quantize_kv_e4m3(k, v))
+    assert any("kv_quantize_once" in x for x in names) == once
+    assert any("kv_absmax" in x for x in names) != once
+    whole = hippo.hippo_quantize_kv_e4m3(k, v)
+    few = slice(0, None, 9)                                 # in two launches, unless they are many heads too
+    assert all(torch.equal(x[few], y) for x, y in zip(whole, hippo.hippo_quantize_kv_e4m3(k[few], v[few])))
 
 
 def test_quantised_heads_of_the_most_slices(hippo):

@@ -626,14 +626,17 @@ def test_bf16_attention_mass_of_many_short_videos(hippo, n, Hkv, parts):
         assert np.array_equal(attention_mass(hippo, q[:some], k[:some], "bf16", 1, 1, n, 0), whole[:some])
 
 
-def test_bf16_calls_of_many_short_videos_take_no_longer_together(hippo):
-    # 37 us for the 960 blocks of one batch element, 101 for the 5760 of six; 112 where every block merges the statistics
-    g = torch.Generator(device="cuda").manual_seed(6)
-    q = [torch.randn((6, 22, 32, 64), generator=g, device="cuda").to(torch.bfloat16) for _ in range(4)]
-    k = [torch.randn((6, 16, 3724, 64), generator=g, device="cuda").to(torch.bfloat16) for _ in range(4)]
-    vid = hippo.video_desc(19, 14, 14, 0)
-    one = best_time(lambda: hippo.hippo_score_tokens_layers([x[:1] for x in q], [x[:1] for x in k], vid))
-    assert best_time(lambda: hippo.hippo_score_tokens_layers(q, k, vid)) < 2.9 * one
+@pytest.mark.parametrize("n, Hkv, layers, B, merged", [
+    # ten tiles of 256 tokens or four: pass 2 merges the row statistics of up to 1024 blocks, or 4096, and a launch those of more
+    (2500, 8, 1, 12, True), (2500, 8, 1, 13, False), (3724, 16, 4, 1, True), (3724, 16, 4, 6, False),
+    (1000, 32, 1, 32, True), (1000, 32, 1, 33, False), (4096, 2, 1, 1, True), (4097, 2, 1, 1, False),
+])
+def test_where_pass_2_of_bf16_scoring_merges_the_row_statistics(hippo, kernels, n, Hkv, layers, B, merged):
+    q = torch.zeros((layers, B, 9, 2 * Hkv, 64), dtype=torch.bfloat16, device="cuda")
+    k = torch.zeros((layers, B, Hkv, n, 64), dtype=torch.bfloat16, device="cuda")
+    names = kernels(lambda: hippo.hippo_score_tokens_layers(q, k, hippo.video_desc(1, 1, n, 0), flags=hippo.SCORE_ATTN))
+    assert [x for x in names if "sattn_mfmaILi64ELi2E" in x]
+    assert any("sattn_row_lse" in x for x in names) != merged
 
 
 def test_bf16_attention_mass_of_long_runs_of_rows(hippo):
@@ -651,29 +654,20 @@ def test_embedding_terms_of_few_channels(hippo, dtype, channels):
         test_embedding_terms_over_passes_of_channels(hippo, (1, 7, 6, 11, ch, 5, 5), dtype)
 
 
-def best_time(call):
-    """ms of ten calls in a graph, the least of five replays"""
-    call()
-    graph, (begin, end) = torch.cuda.CUDAGraph(), (torch.cuda.Event(enable_timing=True) for _ in range(2))
-    with torch.cuda.graph(graph):
-        for _ in range(10):
-            call()
-    times = []
-    for _ in range(5):
-        graph.replay(), begin.record(), graph.replay(), end.record(), torch.cuda.synchronize()
-        times.append(begin.elapsed_time(end))
-    return min(times)
-
-
-@pytest.mark.parametrize("frames, gh, gw, L, crop", [(655, 15, 3, 23, (3, 3)), (175, 9, 20, 4, (3, 4))])
-def test_embedding_terms_beside_the_sweep_take_no_longer_than_after_it(hippo, frames, gh, gw, L, crop):
-    # 256 fp32 channels, all that a block takes in a pass: 65 us together and 70 apart, 64 and 69
-    n = frames * gh * gw
-    g = torch.Generator(device="cuda").manual_seed(frames)
-    q, k = torch.randn((1, L, 4, 64), generator=g, device="cuda"), torch.randn((1, 4, n, 64), generator=g, device="cuda")
-    vid = hippo.video_desc(frames, gh, gw, 0, *crop)
-    time = lambda flags: best_time(lambda: hippo.hippo_score_tokens(q, k, vid, flags=flags))
-    assert time(hippo.SCORE_ALL) < time(hippo.SCORE_ATTN) + time(hippo.SCORE_TEMP | hippo.SCORE_SPA)
+@pytest.mark.parametrize("dtype, Hkv, d, few", [
+    ("fp32", 4, 64, False), ("fp32", 2, 128, False), ("fp32", 3, 64, True), ("fp32", 1, 128, True),
+    ("bf16", 8, 64, False), ("bf16", 4, 128, False), ("bf16", 7, 64, True), ("bf16", 3, 128, True),
+])
+def test_which_embedding_blocks_ask_for_waves_without_channels(hippo, kernels, dtype, Hkv, d, few):
+    # those of 192 fp32 channels or 448 bf16 ones and fewer; beside the sweep (one or two of fp32) and in a launch of their own
+    tdt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    q, k = torch.ones((1, 23, Hkv, d), dtype=tdt, device="cuda"), torch.ones((1, Hkv, 655 * 45, d), dtype=tdt, device="cuda")
+    for frames in (655, 40):
+        vid = hippo.video_desc(frames, 15, 3, 0, 3, 3)
+        beside = kernels(lambda: hippo.hippo_score_tokens(q, k[:, :, :frames * 45], vid))
+        assert [x for x in beside if "with_embILi%dELi%dE" % (d, few) in x], beside
+    alone = kernels(lambda: hippo.hippo_score_tokens(q, k, hippo.video_desc(655, 15, 3, 0, 3, 3), flags=hippo.SCORE_TEMP | hippo.SCORE_SPA))
+    assert [x for x in alone if "emb_scores_run32" in x and "ELi%dEEE" % few in x], alone
 
 
 @pytest.mark.parametrize("d, B, Hkv, q_len, G, ctx", [
