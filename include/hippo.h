@@ -198,7 +198,7 @@ int hippo_select_gather_kv(const float* scores, int32_t k,
  * log of the softmax denominator (of the scaled logits).  softmax_scale <= 0 means 1/sqrt(d).
  * num_splits: how many slices the KV range is cut into (flash-decoding style), 0 = library's
  * choice; the result does not depend on it beyond rounding (fp32 caches: fp32 throughout; 16- and 8-bit
- * caches: each slice's output reaches the merge rounded to bf16, its statistics in fp32).
+ * caches: each slice's output reaches the merge rounded to bf16 or finer, its statistics in fp32).
  * ctx_len >= 0, q_len >= 1.
  * Workspace: hippo_workspace_bytes.  With num_splits 0 it does not grow with seq_len once that gives
  * every compute unit a slice, with one exception: 65 to 96 query rows a KV head (q_len H / H_kv) of bf16

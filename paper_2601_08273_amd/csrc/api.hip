@@ -60,8 +60,9 @@ int plan_attention(int call, const hippo_kv_desc* kv, int q_len, int n_total, in
   if ((long long)G * q_len > 4096) return HIPPO_ERR_BAD_SHAPE;
   pl->R = G * q_len;
   const bool f32 = kv->dtype == HIPPO_DTYPE_F32;
-  // A block takes at most 64 rows of a 16- or 8-bit cache (96 of a large bf16 one, below): more go in equal chunks, the same slices and tiles in every
-  // cache format (chunks of 64 and a rest -> equal ones, us a call with K and V in the last-level cache / from HBM: 33K x 4
+  // A block takes at most 64 rows of a 16- or 8-bit cache (96 of a large bf16 one, below): more go in equal chunks, the same
+  // slices and tiles in every cache format (chunks of 64 and a rest -> equal ones, us a call with K and V in the last-level
+  // cache / from HBM, before one block took up to 96 rows of the large ones: 33K x 4
   // heads, 91 rows 23.3 -> 21.0 / 28.0 -> 26.4; 8K, 91 rows 14.4 -> 13.6 / 14.5 -> 13.6; 2 x 8 heads x 20K, 72 rows 40.1 -> 35.9 /
   // 54.2 -> 53.4; 8-bit 33K, 91 rows 24.6 -> 20.7 / 25.2 -> 21.5).  The fp32 kernel takes 65 to 128 in one chunk: two chunks
   // stream the whole cache twice and give every slice half the compute units (a call over 70K x 2 heads x 64 channels, 70 rows: 43 us in one chunk, 52 in two; four
@@ -81,10 +82,11 @@ int plan_attention(int call, const hippo_kv_desc* kv, int q_len, int n_total, in
                          (kNumCU <= 64 * heads || n_tiles * heads >= 8 * kNumCU) &&
                          (num_splits > 0 || kNumCU / heads <= fit);
   // 65 to 96 rows of a bf16 cache that no cache of the chip holds go in one block too: the second chunk's blocks keep half the
-  // transfers in flight on what the first chunk's fetch.  us a call, two chunks -> one: 4 x 8 heads x 128 x 37K, 72 rows 149 ->
-  // 115, from pages 169 -> 119, 96 rows 147 -> 126; 4 x 4 x 33K, 70 rows 71 -> 57; 64 channels, 4 x 8 x 37K, 72 rows 94 -> 76.
-  // Of a cache that the last-level cache can hold not: 33K x 4 heads, 91 rows of eight
-  // layers in turn 24.9 and 24.8, from pages 27.4 and 25.7, but of one layer 27.1 against 29.8; 16K 16.4 against 19.3.
+  // transfers in flight on what the first chunk's fetch.  us a call from a graph over two caches in turn, two chunks -> one:
+  // 4 x 8 heads x 128 x 37000, 72 rows 130 -> 108, from pages 149 -> 112; 37127, 96 rows 130 -> 108, from pages 152 -> 116;
+  // 4 x 4 x 33000, 70 rows 62 -> 52, from pages 72 -> 58; 64 channels, 4 x 8 x 37000, 72 rows 86 -> 76, from pages 95 -> 78.
+  // Of a cache that the last-level cache can hold not: 33K x 4 heads, 91 rows of eight layers in turn 24.9 and 24.8, from
+  // pages 27.4 and 25.7, but of one layer 27.1 against 29.8; 16K 16.4 against 19.3.
   // Nor where the heads (batch elements x KV heads) come in a second round and the chunks of a head on one XCD, at the same
   // time, so that its L2 serves the second chunk: KV heads a multiple of 8, up to 160, of 64 channels (two chunks' time = 1: 264 to
   // 384 heads 1.02 to 1.25, 38 x 8 x 9359, 77 rows 214 -> 258 us; 400 to 512 0.90 to 1.05; 528 to 640 1.04 to 1.18; more 0.97 to 1.13;

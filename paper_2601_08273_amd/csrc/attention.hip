@@ -1084,8 +1084,11 @@ static hipError_t launch_grid_rb(const AttnParams& p, hipStream_t st) {
     const bool nt = stream_exceeds_caches(p, D, 2);
     // A stream that no cache holds, under three row blocks (of 128 channels: more than one chunk of them) or, of 64 channels,
     // one chunk of four: stages of 16-token tiles, four of them, keep three quarters of the ring in flight under a stage's
-    // products, two of 32-token tiles half of it.  Us a call, 32-token tiles -> 16: 4 x 8 heads x 128 x 20K, 72 rows 90.5 ->
-    // 80.4, 36K, 96 rows 140.6 -> 126.9; of 64 channels, 40K, 40 rows 64.5 -> 58.2, 64 rows 66.3 -> 60.2, 72 rows 100.0 -> 90.9;
+    // products, two of 32-token tiles half of it.  Several chunks are 129 to 144 rows, and 65 to 96 that plan_attention leaves
+    // in two: of many heads, of a slice count or workspace of the caller's.  us a call, 32-token tiles -> 16: 144 rows, 4 x 8
+    // heads x 128 x 37000 239 -> 207, from pages 278 -> 248, x 20000 136 -> 118; 33 x 8 x 2558, 77 rows 139 -> 127, 44 x 8 x
+    // 2600, 96 rows 164 -> 152; 4 x 8 x 36000, 96 rows in two chunks 137 -> 130; of 64 channels, 40K, 40 rows 64.5 -> 58.2,
+    // 64 rows 66.3 -> 60.2, 37000, 144 rows 156 -> 155, from pages 200 -> 182; 38 x 8 x 9359, 77 rows 216 -> 220, from pages 285 -> 269;
     // one chunk of 128 channels only waits for HBM (2 x 8 x 37K, 64 rows 58.3 against 59.8), two chunks of four row blocks
     // gain nothing (4 x 8 x 128 x 20K, 104 rows 84.8 and 85.7; 64 channels x 40K 102 and 104).
     // Where the last-level cache can hold K and V the smaller tiles pay only while it does not, as in a round over many

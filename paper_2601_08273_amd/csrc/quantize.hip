@@ -5,11 +5,11 @@
 //   code       = the E4M3 value nearest to x / multiplier, ties to the even code
 // No result depends on an order between blocks: deterministic.
 // Bound by HBM: codes by a product and exact corrections instead of divisions, 16 source bytes per lane next to its
-// neighbour's (not 32 for 16 codes).  Large sources are read once (kv_quantize_once below).  Small ones, and heads of more than
-// 48 MB, take two launches: every block reduces |x| over its slice of a head's rows; then every block reduces the (few)
-// slice maxima of its head again, encodes its slice and slice 0 stores the multiplier.  The second launch walks the slices
-// backwards, so that it begins with what the last-level cache still holds of the first, and stores its codes
-// non-temporally, so that they do not push the rest out; eight loads in flight.  Quantisation and a verification call over
+// neighbour's (not 32 for 16 codes).  Large sources are read once (kv_quantize_once below).  Small ones, many short heads, and
+// heads of more than 48 MB take two launches: every block reduces |x| over its slice of a head's rows; then every block
+// reduces the (few) slice maxima of its head again, encodes its slice and slice 0 stores the multiplier.  The second launch
+// walks the slices backwards, so that it begins with what the last-level cache still holds of the first, and stores its
+// codes non-temporally, so that they do not push the rest out; eight loads in flight.  Quantisation and a verification call over
 // the codes, us, two launches -> one sweep: 4 x 8 heads x 37K rows x 128 315 -> 239, 2 x 4 heads x 71K 156 -> 126, 3 x 8
 // heads x 21K 135 -> 111, 1 x 8 x 130K 295 -> 226.
 #include "common.h"
