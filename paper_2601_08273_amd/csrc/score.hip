@@ -2274,8 +2274,9 @@ hipError_t launch_score(const ScoreParams& p_in, const ScoreOnce& once_in, hipSt
   const int de = p.emb ? p.emb_dim : p.Hkv * p.D;
   const bool small_crops = p.ch * p.cw <= 32;
   const bool wide = de > (bf16 ? 512 : 256);
-  // (a wave takes 64 channels)
-  const int kind = wide ? kRefetch : de <= (bf16 ? 512 : 256) - 64 ? kFew : kOnePass;
+  // (A wave takes 64 channels: kFew where one of four has none, or two of eight.  One of eight gains less than the questions
+  // cost: 518 random bf16 calls of 392 to 448 channels 1.015 of the time with kFew, 767 of up to 384 0.995.)
+  int kind = wide ? kRefetch : de <= (bf16 ? 384 : 192) ? kFew : kOnePass;
   const long long n_sattn = (long long)p.n_tile * p.Hkv * p.n_rsplit * p.Bz, all_crops = crops_per_frame * p.F * p.B;
   {
     long long run = all_crops / kNumCU;
