@@ -358,11 +358,12 @@ __global__ __launch_bounds__(kQuantOnceThreads, 4) void kv_quantize_once(QuantPa
 // and 30.7 -> 28.0 (64 of 4K), 78 39 -> 33, 129 61 -> 49, 781 371 -> 250; from the last-level cache: 23 13.7 -> 14.5, 32 17.6 ->
 // 15.9, 64 31.6 -> 25.9.  Slices of 64 KB, more blocks, lose to two launches at 32 MiB (23.6) and above.
 // Fetched past the caches, up to 256 MiB are 2 % faster from HBM and 3 to 10 % slower where that cache holds them.
-// Many short heads leave a block little to hold, and two launches have more blocks on a compute unit.  By the bytes of a head,
-// us: 13 KB (2048 x 102 rows x 64) 23.7 -> 36.3, 15 KB 26.8 -> 36.8, 26 KB 24.2 -> 22.8, 28 KB 43.7 -> 42.2, 36 KB 55.3 -> 46.4; of
-// 256 MiB and more 28 KB 171 -> 240, 35 KB 94 -> 117, 42 KB 269 -> 276, 47 KB 302 -> 289, 52 KB 148 -> 131.
+// Many short heads leave a block little to hold, and two launches have more blocks on a compute unit.  One sweep's time in two
+// launches', by the bytes of a head, over 38 to 250 MiB of bf16: 16 KB 1.27 to 1.40, 20 KB 1.13 to 1.16, 24 KB 1.01 to 1.11, 26 KB 0.95
+// to 1.00, 32 KB 0.85 to 0.91, 64 KB 0.64 to 0.75; over 262 | 300 | 400 | 600 MiB: 24 KB 1.55 | 1.58 | 1.48 | 1.48, 40 KB 1.12 | 1.07 | 1.08 |
+// 1.01, 44 KB 1.07 | 1.04 | 1.02 | 0.94, 48 KB 1.02 | 0.99 | 0.97 | 0.89, 56 KB 0.94 | 0.93 | 0.88 | 0.85.  (2048 x 102 rows x 64 23.7 -> 36.3 us.)
 constexpr long long kQuantOnceBytes = 36ll << 20, kQuantPastBytes = 256ll << 20;
-constexpr long long kQuantOnceHead = 24ll << 10, kQuantPastHead = 44ll << 10;
+constexpr long long kQuantOnceHead = 26ll << 10, kQuantPastHead = 50ll << 10;
 
 int quant_slices(int n_rows, int head_dim) {
   // about 16 KB of codes per block, at most one slice per thread of the second reduction

@@ -290,9 +290,9 @@ def test_large_sources_are_quantised_as_their_heads_are(hippo, B, Hkv, n, d, dty
 
 
 @pytest.mark.parametrize("B, Hkv, n, d, dtype, once", [
-    # 24 KB a head from 36 MiB on, 44 KB from 256 MiB on; just below 36 MiB, and there
-    (64, 32, 191, 64, "bf16", False), (64, 32, 192, 64, "bf16", True), (32, 32, 47, 128, "fp32", False), (32, 32, 48, 128, "fp32", True),
-    (94, 32, 175, 128, "bf16", False), (94, 32, 176, 128, "bf16", True), (260, 32, 108, 128, "bf16", False),
+    # 26 KB a head from 36 MiB on, 50 KB from 256 MiB on; just below 36 MiB, and there
+    (64, 32, 207, 64, "bf16", False), (64, 32, 208, 64, "bf16", True), (32, 32, 51, 128, "fp32", False), (32, 32, 52, 128, "fp32", True),
+    (94, 32, 199, 128, "bf16", False), (94, 32, 200, 128, "bf16", True), (260, 32, 108, 128, "bf16", False),
     (1, 8, 9215, 128, "bf16", False), (1, 8, 9216, 128, "bf16", True),
 ])
 def test_which_heads_are_quantised_in_one_sweep(hippo, kernels, B, Hkv, n, d, dtype, once):
