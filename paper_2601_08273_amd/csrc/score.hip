@@ -2311,6 +2311,15 @@ hipError_t launch_score(const ScoreParams& p_in, const ScoreOnce& once_in, hipSt
     n_riders = crops_per_frame * ((p.F + p.emb_run - 1) / p.emb_run) * p.B;
   }
   const long long riders = emb_rides ? n_riders : 0;
+  // fp32 riders of few channels, a few blocks of which wait for the others' slots: of little text they and nothing else are the
+  // launch's end, and came 3 to 8 us later as kFew (1900 tokens x 2 heads x 3 in four layers, 2 rows, 192 channels, 28 blocks beyond
+  // 43.9 -> 52.1 us; in two sweeps, where four blocks fit a unit, 18656 x 2 x 3, 4 rows, 356 beyond 64 -> 75; without waiting blocks
+  // 0.97 of the time).  Of 4507 random calls of up to 32 rows with 256 to 1600 blocks 60 took more than 1.03 of the time, 1.19 the
+  // most; of 3563 with this 17, 1.11 the most.
+  if (!bf16 && kind == kFew && de > 64 && riders > 0) {
+    const long long beyond = n_sattn + riders - (once.row_word != nullptr ? 2 : 4) * kNumCU;
+    if (beyond > 0 && beyond <= (once.row_word != nullptr ? 32 : de > 128 ? 512 : 0)) kind = kOnePass;
+  }
   if ((p.flags & HIPPO_SCORE_ATTN) || accumulate_only) {
     if (p.dtype == HIPPO_DTYPE_BF16)
       e = (p.D == 128) ? launch_sattn_mfma<128>(p, st, riders, kind)

@@ -662,12 +662,31 @@ def test_which_embedding_blocks_ask_for_waves_without_channels(hippo, kernels, d
     # those of 192 fp32 channels or 384 bf16 ones and fewer; beside the sweep (one or two of fp32) and in a launch of their own
     tdt = torch.bfloat16 if dtype == "bf16" else torch.float32
     q, k = torch.ones((1, 23, Hkv, d), dtype=tdt, device="cuda"), torch.ones((1, Hkv, 655 * 45, d), dtype=tdt, device="cuda")
-    for frames in (655, 40):
+    for frames in (400, 40):
         vid = hippo.video_desc(frames, 15, 3, 0, 3, 3)
         beside = kernels(lambda: hippo.hippo_score_tokens(q, k[:, :, :frames * 45], vid))
         assert [x for x in beside if "with_embILi%dELi%dE" % (d, few) in x], beside
     alone = kernels(lambda: hippo.hippo_score_tokens(q, k, hippo.video_desc(655, 15, 3, 0, 3, 3), flags=hippo.SCORE_TEMP | hippo.SCORE_SPA))
     assert [x for x in alone if "emb_scores_run32" in x and "ELi%dEEE" % few in x], alone
+
+
+@pytest.mark.parametrize("B, Hkv, d, L, video, channels, few", [
+    # one sweep: 504 blocks, and 516, of which 512 run at once; two sweeps: 1341, of which 1024 do
+    (4, 3, 128, 4, (46, 6, 12, 0, 5, 5), 192, True), (4, 3, 128, 4, (47, 6, 12, 0, 5, 5), 192, False),
+    (4, 3, 128, 4, (47, 6, 12, 0, 5, 5), 64, True),
+    (3, 3, 64, 16, (50, 14, 17, 0, 4, 3), 192, False), (3, 3, 64, 16, (50, 14, 17, 0, 4, 3), 128, True),
+])
+def test_fp32_embedding_blocks_beyond_what_runs_at_once(hippo, kernels, B, Hkv, d, L, video, channels, few):
+    n = video[0] * video[1] * video[2]
+    g = torch.Generator(device="cuda").manual_seed(n)
+    q, k, emb = (torch.randn(shape, generator=g, device="cuda") for shape in ((B, L, 2 * Hkv, d), (B, Hkv, n, d), (B, n, channels)))
+    vid = hippo.video_desc(*video)
+    names = kernels(lambda: hippo.hippo_score_tokens(q, k, vid, emb=emb))
+    assert [x for x in names if "with_embILi%dELi%dE" % (d, few) in x], names
+    # the terms of a launch of their own, whose blocks are all of few channels: the same bits
+    both, alone = (hippo.hippo_score_tokens(q, k, vid, emb=emb, flags=flags, want_components=True)[1]
+                   for flags in (hippo.SCORE_ALL, hippo.SCORE_TEMP | hippo.SCORE_SPA))
+    assert torch.equal(both[1:], alone[1:])
 
 
 @pytest.mark.parametrize("d, B, Hkv, q_len, G, ctx", [
